@@ -231,7 +231,10 @@ hdqt::GemmArgs plan_gemm(const void* qA, const void* qB, int bA, int bB, const f
     g.qA = static_cast<const uint8_t*>(qA); g.qB = static_cast<const uint8_t*>(qB);
     g.pitchA = hdqt_codes_pitch(D, bA); g.pitchB = hdqt_codes_pitch(D, bB);
     g.bA = bA; g.bB = bB; g.RA = RA; g.RB = RB; g.D = D;
-    g.s = s < D ? s : D;
+    // a contraction of one tile may as well end on a step of the matrix-core kernel: the codes
+    // behind a row's end count as zeros (K = 27 in tiles of 32: one step instead of the generic
+    // kernel)
+    g.s = s < D ? s : (keep_tiles ? D : (D + 31) / 32 * 32);
     g.acc_lo = acc_bits >= 32 ? INT_MIN : -(1 << (acc_bits - 1));
     g.acc_hi = acc_bits >= 32 ? INT_MAX : (1 << (acc_bits - 1)) - 1;
     if (!keep_tiles) {

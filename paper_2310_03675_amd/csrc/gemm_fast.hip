@@ -4,8 +4,9 @@
 // each tile's sum clamped to the a-bit accumulator range, 32-bit total), for
 //   both operands packed 4-bit, or both with a byte per code (the WIDE instances: the
 //   bytes go to LDS as they are, nothing is scaled, generic clamp only);
-//   s a multiple of 32 (or 16), D a multiple of 8 (packed) or 4 (bytes): rows of whole dwords;
-//   a row that ends inside a 32-code unit is padded with zeros on its way to LDS.
+//   s a multiple of 32 (or 16), or one tile; a row that ends inside a 32-code unit is padded
+//   with zeros on its way to LDS, and rows that are no whole dwords (D no multiple of 8 packed
+//   codes or 4 bytes) are shifted into place there (the FLEX instances).
 //
 // What differs from the generic kernel:
 //   * v_mfma_i32_32x32x32_i8: one MFMA consumes 32 contraction positions.
@@ -117,6 +118,7 @@ constexpr float kReqMagic = 12582912.0f;   // 1.5 * 2^23
 template <int UNITS_A, int UNITS_B>
 struct Staged {
     uint4 a[UNITS_A], b[UNITS_B];     // (row, k-step) units per operand per thread
+    uint32_t xa, xb;                  // FLEX: the dword behind the unit
 };
 
 // Operands are read through buffer descriptors that cover exactly their bytes: a unit that
@@ -130,7 +132,8 @@ constexpr uint32_t kOutside = 0x80000000u;      // operands are smaller than 2 G
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t operand_rsrc(const uint8_t* q, int64_t bytes)
 {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(q), 0, (int)bytes, 0x00020000);
+    // (up to the end of the last dword: the base is 16-byte aligned, so that is the same page)
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(q), 0, (int)((bytes + 3) & ~(int64_t)3), 0x00020000);
 }
 
 __device__ __forceinline__ uint4 load_unit(__amdgpu_buffer_rsrc_t rs, int64_t pitch, int64_t R, int64_t row,
@@ -150,6 +153,32 @@ __device__ __forceinline__ uint4 load_unit_wide(__amdgpu_buffer_rsrc_t rs, int64
     return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
 }
 
+// FLEX: rows of any length in bytes.  A unit is fetched as the aligned dwords that hold it, one
+// more than it has, and shifted into place when it goes to LDS (shift_unit): a row's phase,
+// (row * pitch) mod 4, is the same at every stage and every output tile of a thread, because
+// stages advance by 64 (128) bytes and output tiles by 128 (64) rows.
+__device__ __forceinline__ void load_unit_any(__amdgpu_buffer_rsrc_t rs, uint32_t byte_off, bool ok, uint4* u, int n16,
+                                              uint32_t& extra)
+{
+    const uint32_t off = ok ? byte_off & ~3u : kOutside;
+    for (int i = 0; i < n16; ++i)
+        u[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16 * i, 0, 0));
+    extra = __builtin_amdgcn_raw_buffer_load_b32(rs, off + 16 * n16, 0, 0);
+}
+
+template <int N16>
+__device__ __forceinline__ void shift_unit(uint4* u, uint32_t extra, uint32_t phase)
+{
+#pragma unroll
+    for (int i = 0; i < N16; ++i) {
+        const uint32_t next = i + 1 < N16 ? u[i + 1].x : extra;
+        u[i].x = __builtin_amdgcn_alignbyte(u[i].y, u[i].x, phase);
+        u[i].y = __builtin_amdgcn_alignbyte(u[i].z, u[i].y, phase);
+        u[i].z = __builtin_amdgcn_alignbyte(u[i].w, u[i].z, phase);
+        u[i].w = __builtin_amdgcn_alignbyte(next, u[i].w, phase);
+    }
+}
+
 __device__ __forceinline__ void store_unit(uint8_t* lds_row_k, const uint4& w)
 {
     const uint32_t m = 0xF0F0F0F0u;
@@ -162,7 +191,20 @@ __device__ __forceinline__ void store_unit(uint8_t* lds_row_k, const uint4& w)
 // A unit that straddles the end of a row (D no multiple of 32) was loaded with the first codes
 // of the next row behind its own: dword j holds `per_dword` codes starting at first + j *
 // per_dword of the unit and is kept only where that lies below `valid`, the number of the
-// unit's codes inside the row (a multiple of per_dword, see gemm_fast_eligible).
+// unit's codes inside the row (a multiple of per_dword here, any number in mask_tail_any).
+__device__ __forceinline__ void mask_tail_any(uint4& w, int valid, int per_dword, int first)
+{
+    const int bits = 32 / per_dword;
+    auto keep = [&](int at) -> uint32_t {
+        const int n = valid - at;        // codes of this dword inside the row
+        return n <= 0 ? 0u : (n >= per_dword ? 0xFFFFFFFFu : (1u << (bits * n)) - 1u);
+    };
+    w.x &= keep(first);
+    w.y &= keep(first + per_dword);
+    w.z &= keep(first + 2 * per_dword);
+    w.w &= keep(first + 3 * per_dword);
+}
+
 __device__ __forceinline__ void mask_tail(uint4& w, int valid, int per_dword, int first)
 {
     w.x = first < valid ? w.x : 0u;
@@ -281,11 +323,19 @@ __device__ __forceinline__ int clamp3(int v, int lo, int hi)
 // of a tile (all of a wave's values in flight together) and the output is written where it is
 // positive, +0 elsewhere.  An instance of its own: the 32 values cost registers.  (The fold
 // epilogue masks with a run-time test: it reads one value per output element anyway.)
+// FLEX: rows of codes that are no whole dwords (D no multiple of 8, or of 4 with a byte per
+// code), and the outputs the other instances of an epilogue do not write (bfloat16, masked):
+// chosen at run time, element by element.  What it replaces there is the generic kernel of
+// gemm.hip, which fetches, sign-extends and pads code by code and is bound by that: a forward
+// call of 2947 x 561 x 561 in tiles of 32, quantization included, 178 -> 38 us; a square one
+// of 3309 rows 2430 -> 306 us.  One dword more per unit and four byte shifts are what the
+// alignment costs; one stage of loads in flight instead of two keeps it at four waves per SIMD.
 template <int EPI, int KS, bool STREAM, int WAVES, bool BF16, bool FOLD, bool WIDE = false, bool NARROW = false,
-          bool MASK = false, bool PAIR = false>
+          bool MASK = false, bool PAIR = false, bool FLEX = false>
 __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void gemm_i4_kernel(GemmArgs g)
 {
     static_assert(!PAIR || FOLD, "pair mode is a way of folding");
+    static_assert(!FLEX || (!BF16 && !FOLD && !NARROW && !MASK && !STREAM), "flexible instances decide these at run time");
     static_assert(!MASK || (!BF16 && !FOLD && !WIDE && !NARROW), "masked output: plain packed instances only");
     static_assert(!NARROW || (WAVES == 8 && !BF16 && !FOLD && !WIDE), "narrow tiles: plain packed instances only");
     constexpr int TM = BM, TN = NARROW ? 64 : BN;   // the workgroup's tile
@@ -328,6 +378,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
     constexpr int UNITS = TM * NSTEP / NTHREADS;    // 16-byte units of A per thread
     constexpr int UNITS_B = UNITS;                  // of B (narrow: only the threads of rows < TN)
     static_assert(!kPairs64 || KS == KS_LONG, "a pair of 64-code tiles is one long stage");
+    static_assert(!FLEX || UNITS == 1, "one unit per thread and operand");
     __shared__ __attribute__((aligned(16))) uint8_t As[2][TM][LDP];
     __shared__ __attribute__((aligned(16))) uint8_t Bs[2][TN][LDP];
     // second reading: per tile of this part, the running maximum (times 256) in the first pass,
@@ -413,6 +464,8 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
     const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
     const float dq = (g.scaleA[0] * g.scaleB[0]) * g.inv_n;
 
+    const uint32_t phaseA = FLEX ? ((uint32_t)lrow * (uint32_t)g.pitchA) & 3u : 0u;
+    const uint32_t phaseB = FLEX ? ((uint32_t)lrow * (uint32_t)g.pitchB) & 3u : 0u;
     const __amdgpu_buffer_rsrc_t rsA = operand_rsrc(g.qA, g.RA * g.pitchA), rsB = operand_rsrc(g.qB, g.RB * g.pitchB);
 
     // ---- the load stream: position of the next stage to fetch
@@ -427,7 +480,12 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
 #pragma unroll
         for (int i = 0; i < UNITS; ++i) {
             const int r = lrow + ROWS_PER_PASS * i;
-            if constexpr (WIDE) {
+            if constexpr (FLEX) {
+                const int64_t k = f_k + lks * KSTEP, ra = row0 + r, rb = col0 + r;
+                const uint32_t kb = (uint32_t)(WIDE ? k : k >> 1);
+                load_unit_any(rsA, (uint32_t)ra * (uint32_t)g.pitchA + kb, ra < g.RA && k < ke, st.a, REGS, st.xa);
+                load_unit_any(rsB, (uint32_t)rb * (uint32_t)g.pitchB + kb, rb < g.RB && k < ke, st.b, REGS, st.xb);
+            } else if constexpr (WIDE) {
 #pragma unroll
                 for (int hf = 0; hf < 2; ++hf) {
                     st.a[2 * i + hf] = load_unit_wide(rsA, g.pitchA, g.RA, a_row(r), f_k + lks * KSTEP, ke, hf);
@@ -537,6 +595,10 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
     auto stage = [&](Staged<UNITS * REGS, UNITS_B * REGS>& st, const int buf, auto gave_up) {
         constexpr bool kGaveUp = decltype(gave_up)::value;
         constexpr bool kTest = kCert && !kGaveUp;
+        if constexpr (FLEX) {
+            shift_unit<REGS>(st.a, st.xa, phaseA);
+            shift_unit<REGS>(st.b, st.xb, phaseB);
+        }
         if (g.D & (KSTEP - 1)) {
             // rows that end inside a 32-code unit: the thread's units of this stage all start at
             // the same position of their rows
@@ -544,6 +606,11 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
             if (valid < KSTEP) {
 #pragma unroll
                 for (int i = 0; i < UNITS * REGS; ++i) {
+                    if constexpr (FLEX) {
+                        mask_tail_any(st.a[i], (int)valid, WIDE ? 4 : 8, WIDE ? 16 * (i & 1) : 0);
+                        mask_tail_any(st.b[i], (int)valid, WIDE ? 4 : 8, WIDE ? 16 * (i & 1) : 0);
+                        continue;
+                    }
                     mask_tail(st.a[i], (int)valid, WIDE ? 4 : 8, WIDE ? 16 * (i & 1) : 0);
                     if (i < UNITS_B * REGS) mask_tail(st.b[i], (int)valid, WIDE ? 4 : 8, WIDE ? 16 * (i & 1) : 0);
                 }
@@ -1118,10 +1185,11 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
         const bool interior = (row0 + TM <= g.RA) && (col0 + TN <= g.RB);
         float* ob = (g.splits == 1 && g.out) ? g.out + tile_off : nullptr;
         // (the narrow output has kernel instances of its own: its epilogue costs the others registers)
-        uint16_t* hb = (BF16 && g.splits == 1 && g.out_bf16) ? g.out_bf16 + tile_off : nullptr;
+        uint16_t* hb = ((BF16 || FLEX) && g.splits == 1 && g.out_bf16) ? g.out_bf16 + tile_off : nullptr;
+        const float* fm = (FLEX && g.mask_src) ? g.mask_src + tile_off : nullptr;
         // bfloat16 output of an interior tile with an even row length: lanes l and l ^ 1 hold
         // neighbouring columns and trade their values, so that every lane stores one dword
-        const bool pair_bf16 = hb && interior && (g.RB % 2 == 0);
+        const bool pair_bf16 = BF16 && hb && interior && (g.RB % 2 == 0);
         const bool slice16 = g.splits > 1 && g.partial16;
         int32_t* ab = slice16 ? nullptr
                               : (g.splits > 1 ? g.partial + (int64_t)blockIdx.x * g.RA * g.RB + tile_off
@@ -1180,7 +1248,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
         // nothing is tested per element, so the 32 stores of a wave are one run of
         // conversions and stores (with the tests, each store sat in an exec-masked block of
         // its own behind its own branches).
-        const bool plain_out = !MASK && interior && ob && !ab && !ab16 && !(BF16 && hb);
+        const bool plain_out = !MASK && !fm && interior && ob && !ab && !ab16 && !((BF16 || FLEX) && hb);
         if (plain_out) {
 #pragma unroll
             for (int a = 0; a < RS; ++a)
@@ -1199,7 +1267,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
         // the same for the 16-bit slices of a split contraction (measured on the benchmark
         // layer's weight gradient: 25.4 -> 23.2 us; a third block for 32-bit slices made every
         // kernel a little slower and nothing faster)
-        const bool plain_slices = interior && ab16 && !ob && !ab && !(BF16 && hb);
+        const bool plain_slices = interior && ab16 && !ob && !ab && !((BF16 || FLEX) && hb);
         if (plain_slices) {
 #pragma unroll
             for (int a = 0; a < RS; ++a)
@@ -1227,7 +1295,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
                     bool ok = interior;
                     if (!interior)
                         ok = (row0 + lane_row + rr < g.RA) && (col0 + lane_col + c * 32 < g.RB);
-                    if (BF16 && hb && !pair_bf16 && ok) (hb + uo)[lane_off] = (uint16_t)bf16_bits((float)v * dq);
+                    if ((BF16 || FLEX) && hb && !pair_bf16 && ok) (hb + uo)[lane_off] = (uint16_t)bf16_bits((float)v * dq);
                     if (ok) {
                         if (ab) (ab + uo)[lane_off] = v;
                         if (ab16) (ab16 + uo)[lane_off] = (int16_t)v;
@@ -1236,6 +1304,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
                             // would drop the streaming hint)
                             float f = (float)v * dq;
                             if constexpr (MASK) f = mk[a][c][r] > 0.0f ? f : 0.0f;
+                            if (FLEX && fm) f = (fm + uo)[lane_off] > 0.0f ? f : 0.0f;
                             if (STREAM) __builtin_nontemporal_store(f, &(ob + uo)[lane_off]);
                             else (ob + uo)[lane_off] = f;
                         }
@@ -1254,7 +1323,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
     // less than a trip to L2 under load), one stage ahead in the s = 64 instance, which has
     // no eight registers to spare at four waves per SIMD.
     // (the fold epilogue needs the registers; with a byte per code a stage in flight is twice as many)
-    constexpr bool kDeep = !kPairs64 && !FOLD && !WIDE;
+    constexpr bool kDeep = !kPairs64 && !FOLD && !WIDE && !FLEX;
     // EPI_CERT8_S32 has the loop of its given-up stages (see `stage`) in the instances for
     // outputs that stay in the caches.  Those for streamed outputs go on in the testing stage
     // with every flag down: with the second loop compiled in, their testing stage came out 14 %
@@ -1304,7 +1373,7 @@ bool sat8_path(const GemmArgs& g) { return g.acc_hi == 127 && (g.s == 16 || g.s 
 // tiles of 32 or 64 codes.  Fills in the operand factors when `plan` is given.
 bool sat16_path(const GemmArgs& g, GemmArgs* plan = nullptr)
 {
-    if ((g.s != 16 && g.s != 32 && g.s != 64) || g.fold || g.out_bf16 || g.acc_hi > 32767) return false;
+    if ((g.s != 16 && g.s != 32 && g.s != 64) || g.fold || g.acc_hi > 32767) return false;
     if ((g.bA > 4) != (g.bB > 4)) return false;
     if (g.bA <= 4 && sat8_path(g)) return false;      // has its own, cheaper instances
     int a = 1;
@@ -1373,15 +1442,15 @@ bool gemm_fold_plan(GemmArgs* g, int64_t batch, int C, int H, int W, int kh, int
 bool gemm_fast_eligible(const GemmArgs& g)
 {
     if ((g.bA > 4) != (g.bB > 4)) return false;      // packed or bytes, the same on both sides
-    // rows of whole dwords (the 16-byte loads then start on one); a row may end inside a 32-code
-    // unit, whose remainder the kernel clears
-    if (g.D % (g.bA > 4 ? 4 : 8) != 0) return false;
+    // a row may end inside a 32-code unit, whose remainder the kernel clears; rows that are no
+    // whole dwords, and outputs an epilogue has no instance for, take the FLEX ones
+    if (g.fold && g.D % KSTEP != 0) return false;
     if (g.RB > ((int64_t)1 << 21)) return false;     // 32-bit offsets inside an output tile
     // 32-bit offsets into the operands, with room for the "outside" offset
     if ((g.RA + 256) * g.pitchA >= ((int64_t)1 << 31) || (g.RB + 256) * g.pitchB >= ((int64_t)1 << 31)) return false;
     if (g.s == 16) {
         // two tiles per 32-code step: saturating epilogues only, parts that start on a step
-        if (g.fold || g.out_bf16 || (g.splits > 1 && g.tiles_per_split % 2 != 0)) return false;
+        if (g.fold || (g.splits > 1 && g.tiles_per_split % 2 != 0)) return false;
         if (sat16_path(g) || (g.bA <= 4 && sat8_path(g))) return true;
         // compare-select clamp: totals (times 256 with packed codes) must stay inside int32
         const int64_t max_prod = ((int64_t)1 << (g.bA - 1)) * ((int64_t)1 << (g.bB - 1));
@@ -1394,7 +1463,7 @@ bool gemm_fast_eligible(const GemmArgs& g)
     if (g.bA > 4) {
         // a byte per code: nothing is scaled; a tile's sum (|code| <= 128 on both sides) and
         // a part's total must stay inside int32
-        if (g.fold || g.out_bf16) return false;
+        if (g.fold) return false;
         const int64_t tile_max = g.s << 14, acc_max = (int64_t)g.acc_hi + 1;
         const int64_t per_tile = tile_max < acc_max ? tile_max : acc_max;
         if (g.s >= ((int64_t)1 << 16)) return false;
@@ -1416,9 +1485,17 @@ bool gemm_fast_eligible(const GemmArgs& g)
 bool gemm_fast_masks(const GemmArgs& g)
 {
     if (!g.mask_src || !g.out || !gemm_fast_eligible(g)) return false;
-    if (g.fold) return true;
-    if (g.splits > 1 || g.out_bf16 || g.bA > 4 || g.s == 16) return false;
-    return !sat16_path(g);
+    return g.splits == 1 && !g.out_bf16;
+}
+
+// Rows of codes that are no whole dwords, and outputs that only some epilogues have instances
+// for: bfloat16 and masked ones with tiles of 16, with the int16 saturation or with a byte per
+// code.
+static bool flexible(const GemmArgs& g)
+{
+    if (g.fold) return false;
+    if (g.D % (g.bA > 4 ? 4 : 8) != 0) return true;
+    return (g.out_bf16 || (g.mask_src && g.splits == 1)) && (g.bA > 4 || g.s == 16 || sat16_path(g));
 }
 
 // Outputs of at most 64 columns take the 128 x 64 workgroup tile where such instances exist
@@ -1444,7 +1521,7 @@ static bool narrow_tiles(const GemmArgs& g)
 // six interleaved runs; with fewer column tiles (576 or 320 columns) it is 5 to 7 % slower.
 static bool cert_tiles(const GemmArgs& g, int64_t n_ct)
 {
-    if (g.fold || g.out_bf16 || g.bA > 4 || g.bB > 4 || g.mask_src) return false;
+    if (g.fold || g.out_bf16 || g.bA > 4 || g.bB > 4 || g.mask_src || flexible(g)) return false;
     if (g.acc_hi != 127 || g.s != 32 || g.tiles_per_split > 255) return false;
     if (g.tiles_per_split * g.s > 4 * KS_LONG) return true;
     return g.stream_out && n_ct >= 8 && g.D >= KS_LONG;
@@ -1514,7 +1591,8 @@ hipError_t launch_gemm_fast(const GemmArgs& g_in, hipStream_t stream)
     g.acc_hi_scaled = hi > INT32_MAX ? INT32_MAX : (int)hi;
     // Short contractions (at most two stages per output tile): a workgroup walks along
     // its row strip of the output as long as that leaves about two workgroups per CU.
-    const bool narrow = narrow_tiles(g);
+    const bool flex = flexible(g);
+    const bool narrow = !flex && narrow_tiles(g);
     int64_t n_ct = (g.RB + BN - 1) / BN, n_rt = (g.RA + BM - 1) / BM;
     if (narrow) n_ct = (g.RB + 63) / 64;
     if (g.fold) {
@@ -1561,7 +1639,26 @@ hipError_t launch_gemm_fast(const GemmArgs& g_in, hipStream_t stream)
         if (g.stream_out) hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, true, kWaves, false, false, WIDE>), grid, block, 0, stream, g); \
         else hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, false, kWaves, false, false, WIDE>), grid, block, 0, stream, g); \
     } while (0)
-    if (g.s == 16) {
+    if (flex) {
+#define HDQT_LAUNCH_FLEX(EPI, WIDE)                                                                   \
+    hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, false, kWaves, false, false, WIDE, false, false, false, true>), \
+                       grid, dim3(64 * kWaves), 0, stream, g)
+#define HDQT_LAUNCH_FLEX2(EPI) do { if (wide) HDQT_LAUNCH_FLEX(EPI, true); else HDQT_LAUNCH_FLEX(EPI, false); } while (0)
+        if (g.s == 16) {
+            if (sat16) HDQT_LAUNCH_FLEX2(EPI_SAT16_S16);
+            else if (!wide && sat8_path(g)) HDQT_LAUNCH_FLEX(EPI_SAT8_S16, false);
+            else HDQT_LAUNCH_FLEX2(EPI_CLAMP_S16);
+        } else if (sat16) {
+            if (g.s == 32) HDQT_LAUNCH_FLEX2(EPI_SAT16_S32);
+            else HDQT_LAUNCH_FLEX2(EPI_SAT16_S64);
+        } else if (!wide && sat8_path(g)) {
+            if (g.s == 32) HDQT_LAUNCH_FLEX(EPI_SAT8_S32, false);
+            else HDQT_LAUNCH_FLEX(EPI_SAT8_S64, false);
+        } else if (g.s % KS_LONG == 0) HDQT_LAUNCH_FLEX2(EPI_STAGES);
+        else HDQT_LAUNCH_FLEX2(EPI_GENERIC);
+#undef HDQT_LAUNCH_FLEX2
+#undef HDQT_LAUNCH_FLEX
+    } else if (g.s == 16) {
         if (sat16 && wide) HDQT_LAUNCH_SAT16(EPI_SAT16_S16, true);
         else if (sat16) HDQT_LAUNCH_SAT16(EPI_SAT16_S16, false);
         else if (!wide && sat8_path(g)) HDQT_LAUNCH_SAT16(EPI_SAT8_S16, false);
