@@ -766,9 +766,9 @@ def main():
             return dt_f, {n_: tot / l * 1e3 for n_, (l, tot) in B.profile_collect().items()}
         fb = {}
         pf = prm[kinds[0]]
-        # contraction lengths that are no multiple of 32: a multiple of 8 still runs the matrix-core
+        # contraction lengths that are no multiple of 32: a multiple of 8 runs the plain matrix-core
         # kernel (the rows' last 16-byte unit is padded with zeros on its way to LDS), anything else
-        # the generic tiled kernel
+        # its instances for ragged rows
         for key, Kf in (("fwd_K_multiple_of_8_not_32", K - 8), ("fwd_K_not_multiple_of_8", K - 4)):
             Xf, Wf = X[:, :Kf].contiguous(), W[:Kf].contiguous()
             dt_f, k_f = timed(lambda: B.gemm(kinds[0], Xf, Wf, M, Kf, N, pf))
@@ -779,7 +779,7 @@ def main():
         dt_f, k_f = timed(lambda: B.gemm(kinds[0], X, W, M, K, N, pm))
         fb["fwd_mixed_4bit_8bit"] = {"shape": [M, K, N], "ms": dt_f * 1e3, "kernels_us": k_f,
                                     "TOPS": 2.0 * M * K * N / dt_f / 1e12}
-        # axis-0 quantization of a tensor whose column count is no multiple of 4 (generic column kernel)
+        # axis-0 quantization of a tensor whose column count is no multiple of 4 (any-shape kernel)
         Xq = X[:, :K - 2].contiguous()
         dt_f, k_f = timed(lambda: B.quantize(Xq, 0, n, pf.A, 0))
         fb["quantize_axis0_cols_not_multiple_of_4"] = {

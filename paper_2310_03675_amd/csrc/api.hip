@@ -141,9 +141,9 @@ int choose_splits(int64_t RA, int64_t RB, int64_t D, int64_t n_tiles)
 
 constexpr size_t kMetaBytes = (sizeof(hdqt::QMeta) + 255) / 256 * 256;
 
-int run_quantize(const float* T, int64_t rows, int64_t cols, int axis, int n_eff,
-                 const hdqt_operand_t* op, uint64_t seed, hdqt::QMeta* meta, void* codes,
-                 float* scale_out, hipStream_t stream)
+hdqt::QuantArgs make_quant_args(const float* T, int64_t rows, int64_t cols, int axis, int n_eff,
+                                const hdqt_operand_t* op, uint64_t seed, hdqt::QMeta* meta, void* codes,
+                                float* scale_out)
 {
     hdqt::QuantArgs q{};
     q.T = T; q.rows = rows; q.cols = cols; q.axis = axis;
@@ -152,8 +152,7 @@ int run_quantize(const float* T, int64_t rows, int64_t cols, int axis, int n_eff
     q.clip = op->clip; q.tensor_id = op->tensor_id;
     q.seed_lo = (uint32_t)seed; q.seed_hi = (uint32_t)(seed >> 32);
     q.meta = meta; q.codes = static_cast<uint8_t*>(codes); q.scale_out = scale_out;
-    const hipError_t e = hdqt::launch_quantize(q, stream);
-    return e == hipSuccess ? HDQT_OK : hip_fail(e);
+    return q;
 }
 
 hdqt::DualArgs make_dual_args(const float* T, int64_t rows, int64_t cols, int n1,
@@ -201,23 +200,98 @@ bool set_conv_source(hdqt::DualArgs* d, const hdqt_conv_t* geo)
     return hdqt::dual_conv_plan(d);
 }
 
-// Both quantizations of one tensor (axis 1 and axis 0): from a single read per
-// pass when the fused kernel takes the shape, else one after the other.  Both
-// calibration records must be zero.
-int run_quantize_pair(const float* T, int64_t rows, int64_t cols, int n1, const hdqt_operand_t* op1,
-                      uint64_t seed1, int n0, const hdqt_operand_t* op0, uint64_t seed0,
-                      hdqt::QMeta* meta1, hdqt::QMeta* meta0, void* codes1, void* codes0,
-                      float* scale1_out, float* scale0_out, hipStream_t stream, int profile_tag = 0)
+// Everything one call quantizes, at most kMaxSet (tensor, axis) pairs: tensors along both axes
+// (whole) and along one.
+struct QuantSet {
+    hdqt::DualArgs both[hdqt::kMaxDualBatch];
+    hdqt::QuantArgs one[hdqt::kMaxAny];
+    int n_both = 0, n_one = 0;
+    void add(const hdqt::DualArgs& d) { both[n_both++] = d; }
+    void add(const hdqt::QuantArgs& q) { one[n_one++] = q; }
+};
+
+hdqt::QuantArgs half_of(const hdqt::DualArgs& d, int axis)
 {
-    const hdqt::DualArgs d = make_dual_args(T, rows, cols, n1, op1, seed1, n0, op0, seed0, meta1, meta0,
-                                            codes1, codes0, scale1_out, scale0_out, profile_tag);
-    if (hdqt::quantize_dual_eligible(d)) {
-        const hipError_t e = hdqt::launch_quantize_dual(d, stream);
-        return e == hipSuccess ? HDQT_OK : hip_fail(e);
+    hdqt::QuantArgs q{};
+    q.T = d.T; q.rows = d.rows; q.cols = d.cols; q.axis = axis;
+    q.log2n = axis ? d.log2n_row : d.log2n_col;
+    q.b = axis ? d.b_row : d.b_col; q.stochastic = axis ? d.st_row : d.st_col;
+    q.clip = axis ? d.clip_row : d.clip_col; q.tensor_id = axis ? d.tid_row : d.tid_col;
+    q.seed_lo = axis ? d.seed_row_lo : d.seed_col_lo; q.seed_hi = axis ? d.seed_row_hi : d.seed_col_hi;
+    q.meta = axis ? d.meta_row : d.meta_col; q.codes = axis ? d.codes_row : d.codes_col;
+    q.scale_out = axis ? d.scale_row_out : d.scale_col_out;
+    return q;
+}
+
+// Elements (over all pairs) up to which a whole set goes to the any-shape kernel.
+constexpr int64_t kAnySet = (int64_t)1 << 20;
+// Elements up to which a pair that a tuned kernel would take joins the any-shape pairs of the set:
+// it saves the two launches of its own.
+constexpr int64_t kAnyPair = (int64_t)1 << 20;
+
+// Quantizes a set: one launch per pass for all tensors that the two-axis and the any-shape kernel
+// take (two for pass 2 where the rounding modes do not go together), two launches per large tensor
+// that has a single-axis kernel.  `records`, `record_bytes`: the calibration records of all of them.
+int run_quantize_set(const QuantSet& s, void* records, size_t record_bytes, hipStream_t stream)
+{
+    int64_t work = 0;
+    for (int k = 0; k < s.n_both; ++k) work += 2 * s.both[k].rows * s.both[k].cols;
+    for (int k = 0; k < s.n_one; ++k) work += s.one[k].rows * s.one[k].cols;
+    const bool small = work <= kAnySet;
+
+    hdqt::DualArgs dual[hdqt::kMaxDualBatch];
+    hdqt::QuantArgs alone[hdqt::kMaxAny];
+    hdqt::AnyBatch any{};
+    int n_dual = 0, n_alone = 0;
+    auto place = [&](const hdqt::QuantArgs& q) {
+        if (small || q.rows * q.cols <= kAnyPair || !hdqt::quantize_fast_eligible(q)) hdqt::plan_any(q, &any);
+        else alone[n_alone++] = q;
+    };
+    for (int k = 0; k < s.n_both; ++k) {
+        const hdqt::DualArgs& d = s.both[k];
+        if (d.conv || (!small && hdqt::quantize_dual_eligible(d))) {
+            dual[n_dual++] = d;
+        } else {
+            place(half_of(d, 1));
+            place(half_of(d, 0));
+        }
     }
-    const int rc = run_quantize(T, rows, cols, 1, n1, op1, seed1, meta1, codes1, scale1_out, stream);
-    if (rc) return rc;
-    return run_quantize(T, rows, cols, 0, n0, op0, seed0, meta0, codes0, scale0_out, stream);
+    for (int k = 0; k < s.n_one; ++k) place(s.one[k]);
+
+    // maxima side by side, and nothing to clear, if every tensor has few enough workgroups
+    bool dense = n_alone == 0;
+    for (int k = 0; k < n_dual; ++k) dense = dense && hdqt::dual_workgroups(dual[k]) <= hdqt::kDenseMost;
+    for (int k = 0; k < any.n; ++k) dense = dense && any.p[k].count <= hdqt::kDenseMost;
+    for (int k = 0; k < any.n; ++k) any.p[k].dense = dense ? any.p[k].count : 0;
+    hipError_t e = hipSuccess;
+    if (!dense) e = hdqt::launch_zero2(static_cast<uint32_t*>(records), (int64_t)(record_bytes / 4), nullptr, 0, stream);
+
+    const bool ride = n_dual && any.total < (1 << 20);
+    if (n_dual) {
+        const hdqt::AnyBatch* riders = ride ? &any : nullptr;
+        if (e == hipSuccess) e = hdqt::launch_dual_pass1(dual, n_dual, dense, riders, stream);
+        // Pass 2: all in one launch if the rounding modes go together, the last tensor (a layer's
+        // G) first: its tiles take longest (two random streams) and start while the chip fills.
+        hdqt::DualArgs ord[hdqt::kMaxDualBatch];
+        for (int k = 0; k < n_dual; ++k) ord[k] = dual[(k + n_dual - 1) % n_dual];
+        if (hdqt::dual_pass2_batchable(ord, n_dual)) {
+            if (e == hipSuccess) e = hdqt::launch_dual_pass2(ord, n_dual, dense, riders, stream);
+        } else {
+            int done = 0;
+            while (done < n_dual && e == hipSuccess) {
+                int take = n_dual - done;
+                while (take > 1 && !hdqt::dual_pass2_batchable(dual + done, take)) --take;
+                e = hdqt::launch_dual_pass2(dual + done, take, dense, done ? nullptr : riders, stream);
+                done += take;
+            }
+        }
+    }
+    if (any.n && !ride) {
+        if (e == hipSuccess) e = hdqt::launch_any(any, 1, stream);
+        if (e == hipSuccess) e = hdqt::launch_any(any, 2, stream);
+    }
+    for (int k = 0; k < n_alone && e == hipSuccess; ++k) e = hdqt::launch_quantize_fast(alone[k], stream);
+    return e == hipSuccess ? HDQT_OK : hip_fail(e);
 }
 
 // Resolve tile length, accumulator range and the split of the contraction.
@@ -391,16 +465,10 @@ int run_gemm(int kind, const float* P, const float* Q, float* out, int64_t M, in
                                  out_bf16);
     if (mask_src && (misaligned(mask_src) || !out)) return out ? HDQT_EALIGN : HDQT_EINVAL_NULL;
     g.mask_src = mask_src;
-    // one launch clears both calibration records (they are adjacent)
-    hipError_t e = hdqt::launch_zero2(reinterpret_cast<uint32_t*>(metaA), (int64_t)(2 * kMetaBytes / 4),
-                                      nullptr, 0, stream);
-    if (e != hipSuccess) return hip_fail(e);
-    rc = run_quantize(P, o.a_rows, o.a_cols, o.a_axis, L.n_eff, &prm->A, prm->seed, metaA, codesA,
-                      nullptr, stream);
-    if (rc) return rc;
-    rc = run_quantize(Q, o.b_rows, o.b_cols, o.b_axis, L.n_eff, &prm->B, prm->seed, metaB, codesB,
-                      nullptr, stream);
-    if (rc) return rc;
+    QuantSet set;
+    set.add(make_quant_args(P, o.a_rows, o.a_cols, o.a_axis, L.n_eff, &prm->A, prm->seed, metaA, codesA, nullptr));
+    set.add(make_quant_args(Q, o.b_rows, o.b_cols, o.b_axis, L.n_eff, &prm->B, prm->seed, metaB, codesB, nullptr));
+    if ((rc = run_quantize_set(set, metaA, 2 * kMetaBytes, stream))) return rc;
     return run_planned_gemm(g, base + L.acc, L.total - L.acc, stream);
 }
 
@@ -679,12 +747,10 @@ int hdqt_quantize(const float* T, int64_t rows, int64_t cols, int axis, int had_
     if (misaligned(T) || misaligned(codes_out) || misaligned(workspace)) return HDQT_EALIGN;
     if ((reinterpret_cast<uintptr_t>(scale_out) & 3u) != 0) return HDQT_EALIGN;
     const int64_t D = axis ? cols : rows;
-    const hipError_t e = hdqt::launch_zero2(static_cast<uint32_t*>(workspace), hdqt::kQMetaDwords,
-                                            nullptr, 0, static_cast<hipStream_t>(stream));
-    if (e != hipSuccess) return hip_fail(e);
-    return run_quantize(T, rows, cols, axis, hdqt_n_eff(D, had_block), op, seed,
-                        static_cast<hdqt::QMeta*>(workspace), codes_out, scale_out,
-                        static_cast<hipStream_t>(stream));
+    QuantSet set;
+    set.add(make_quant_args(T, rows, cols, axis, hdqt_n_eff(D, had_block), op, seed,
+                            static_cast<hdqt::QMeta*>(workspace), codes_out, scale_out));
+    return run_quantize_set(set, workspace, kMetaBytes, static_cast<hipStream_t>(stream));
 }
 
 size_t hdqt_quantize_dual_workspace_size(void) { return 2 * kMetaBytes; }
@@ -709,12 +775,10 @@ int hdqt_quantize_dual(const float* T, int64_t rows, int64_t cols, int had_block
     char* base = static_cast<char*>(workspace);
     hdqt::QMeta* meta1 = reinterpret_cast<hdqt::QMeta*>(base);
     hdqt::QMeta* meta0 = reinterpret_cast<hdqt::QMeta*>(base + kMetaBytes);
-    const hipError_t e = hdqt::launch_zero2(reinterpret_cast<uint32_t*>(base),
-                                            (int64_t)(2 * kMetaBytes / 4), nullptr, 0, stream);
-    if (e != hipSuccess) return hip_fail(e);
-    return run_quantize_pair(T, rows, cols, hdqt_n_eff(cols, had_block), op_axis1, seed,
-                             hdqt_n_eff(rows, had_block), op_axis0, seed, meta1, meta0, codes_axis1,
-                             codes_axis0, scale_axis1, scale_axis0, stream);
+    QuantSet set;
+    set.add(make_dual_args(T, rows, cols, hdqt_n_eff(cols, had_block), op_axis1, seed, hdqt_n_eff(rows, had_block),
+                           op_axis0, seed, meta1, meta0, codes_axis1, codes_axis0, scale_axis1, scale_axis0, 0));
+    return run_quantize_set(set, base, 2 * kMetaBytes, stream);
 }
 
 int hdqt_quantize_dual_im2col(const float* act, const hdqt_conv_t* geo, int had_block,
@@ -742,10 +806,9 @@ int hdqt_quantize_dual_im2col(const float* act, const hdqt_conv_t* geo, int had_
                                       hdqt_n_eff(rows, had_block), op_axis0, seed, meta1, meta0,
                                       codes_axis1, codes_axis0, scale_axis1, scale_axis0, 0);
     if (!set_conv_source(&d, geo) || !hdqt::quantize_dual_eligible(d)) return HDQT_EINVAL_GEOMETRY;
-    hipError_t e = hdqt::launch_zero2(reinterpret_cast<uint32_t*>(base), (int64_t)(2 * kMetaBytes / 4),
-                                      nullptr, 0, stream);
-    if (e == hipSuccess) e = hdqt::launch_quantize_dual(d, stream);
-    return e == hipSuccess ? HDQT_OK : hip_fail(e);
+    QuantSet set;
+    set.add(d);
+    return run_quantize_set(set, base, 2 * kMetaBytes, stream);
 }
 
 int hdqt_im2col(const float* act, int64_t batch, int channels, int height, int width, int kh, int kw,
@@ -857,15 +920,10 @@ int hdqt_gemm_requant(int gemm_kind, const float* P, const float* Q, float* out,
     char* base = static_cast<char*>(workspace);
     hdqt::QMeta* metaA = reinterpret_cast<hdqt::QMeta*>(base + L.scaleA);
     hdqt::QMeta* metaB = reinterpret_cast<hdqt::QMeta*>(base + L.scaleB);
-    hipError_t e = hdqt::launch_zero2(reinterpret_cast<uint32_t*>(metaA), (int64_t)(2 * kMetaBytes / 4),
-                                      nullptr, 0, stream);
-    if (e != hipSuccess) return hip_fail(e);
-    rc = run_quantize(P, o.a_rows, o.a_cols, o.a_axis, L.n_eff, &params->A, params->seed, metaA,
-                      base + L.codesA, nullptr, stream);
-    if (rc) return rc;
-    rc = run_quantize(Q, o.b_rows, o.b_cols, o.b_axis, L.n_eff, &params->B, params->seed, metaB,
-                      base + L.codesB, nullptr, stream);
-    if (rc) return rc;
+    QuantSet set;
+    set.add(make_quant_args(P, o.a_rows, o.a_cols, o.a_axis, L.n_eff, &params->A, params->seed, metaA, base + L.codesA, nullptr));
+    set.add(make_quant_args(Q, o.b_rows, o.b_cols, o.b_axis, L.n_eff, &params->B, params->seed, metaB, base + L.codesB, nullptr));
+    if ((rc = run_quantize_set(set, metaA, 2 * kMetaBytes, stream))) return rc;
     return run_requant(base + L.codesA, base + L.codesB, params->A.b, params->B.b, &metaA->scale,
                        &metaB->scale, L.RA, L.RB, L.D, L.n_eff, params->acc_bits, params->s, out, acc_out,
                        base + L.acc, workspace_bytes - L.acc, stream);
@@ -910,65 +968,27 @@ int run_layer_step(const float* X, const hdqt_conv_t* geo, const float* W, const
               nW = L.n_eff[HDQT_GEMM_BWD_WEIGHT];
     // X along K (forward) and along M (weight gradient); W along N (input gradient) and
     // along K (forward); G along N (input gradient) and along M (weight gradient)
-    bool g_done = false;
-    hipError_t e;
-    if (!with_dx) {
-        if (geo) return HDQT_EINVAL_GEOMETRY;       // (hdqt_conv_step asks for dXcol)
-        e = hdqt::launch_zero2(reinterpret_cast<uint32_t*>(base), (int64_t)(L.zero_bytes / 4), nullptr, 0,
-                               stream);
-        if (e != hipSuccess) return hip_fail(e);
-    } else {
-        hdqt::DualArgs dX3[3] = {
-            make_dual_args(X, M, K, nF, &fwd->A, fwd->seed, nW, &bwd_weight->A, bwd_weight->seed,
-                           meta(T_X1), meta(T_X0), codes(T_X1), codes(T_X0), nullptr, nullptr, 1),
-            make_dual_args(W, K, N, nI, &bwd_input->B, bwd_input->seed, nF, &fwd->B, fwd->seed,
-                           meta(T_W1), meta(T_W0), codes(T_W1), codes(T_W0), nullptr, nullptr, 2),
-            make_dual_args(G, M, N, nI, &bwd_input->A, bwd_input->seed, nW, &bwd_weight->B,
-                           bwd_weight->seed, meta(T_G1), meta(T_G0), codes(T_G1), codes(T_G0), nullptr,
-                           nullptr, 3)};
-        if (geo && !set_conv_source(&dX3[0], geo)) return HDQT_EINVAL_GEOMETRY;
-        const hdqt::DualArgs &dx = dX3[0], &dw = dX3[1], &dg = dX3[2];
-        const bool dual = hdqt::quantize_dual_eligible(dx) && hdqt::quantize_dual_eligible(dw) &&
-                          hdqt::quantize_dual_eligible(dg);
-        // an activation source is read by the two-axis kernels only (nothing is launched before
-        // this is known)
-        if (geo && !dual) return HDQT_EINVAL_GEOMETRY;
-        e = hdqt::launch_zero2(reinterpret_cast<uint32_t*>(base), (int64_t)(L.zero_bytes / 4), nullptr, 0,
-                               stream);
-        if (e != hipSuccess) return hip_fail(e);
-        if (dual) {
-            // all three tensors take the two-axis kernels: one launch finds all six maxima,
-            // and W's codes ride along with X's when the rounding modes agree
-            e = hdqt::launch_dual_pass1(dX3, 3, stream);
-            if (e != hipSuccess) return hip_fail(e);
-            // G first: its tiles take longest (two random streams) and start while the chip fills
-            const hdqt::DualArgs gxw[3] = {dg, dx, dw};
-            if (hdqt::dual_pass2_batchable(gxw, 3)) {
-                e = hdqt::launch_dual_pass2(gxw, 3, stream);
-            } else {
-                if (hdqt::dual_pass2_batchable(dX3, 2)) {
-                    e = hdqt::launch_dual_pass2(dX3, 2, stream);
-                } else {
-                    e = hdqt::launch_dual_pass2(&dx, 1, stream);
-                    if (e == hipSuccess) e = hdqt::launch_dual_pass2(&dw, 1, stream);
-                }
-                if (e == hipSuccess) e = hdqt::launch_dual_pass2(&dg, 1, stream);
-            }
-            if (e != hipSuccess) return hip_fail(e);
-            g_done = true;
+    if (geo && !with_dx) return HDQT_EINVAL_GEOMETRY;       // (hdqt_conv_step asks for dXcol)
+    QuantSet set;
+    set.add(make_dual_args(X, M, K, nF, &fwd->A, fwd->seed, nW, &bwd_weight->A, bwd_weight->seed, meta(T_X1),
+                           meta(T_X0), codes(T_X1), codes(T_X0), nullptr, nullptr, 1));
+    if (with_dx) {
+        set.add(make_dual_args(W, K, N, nI, &bwd_input->B, bwd_input->seed, nF, &fwd->B, fwd->seed, meta(T_W1),
+                               meta(T_W0), codes(T_W1), codes(T_W0), nullptr, nullptr, 2));
+        set.add(make_dual_args(G, M, N, nI, &bwd_input->A, bwd_input->seed, nW, &bwd_weight->B, bwd_weight->seed,
+                               meta(T_G1), meta(T_G0), codes(T_G1), codes(T_G0), nullptr, nullptr, 3));
+        // an activation source is read by the two-axis kernels only, and its layer's other tensors
+        // are of a kind they take (nothing is launched before this is known)
+        if (geo) {
+            if (!set_conv_source(&set.both[0], geo)) return HDQT_EINVAL_GEOMETRY;
+            for (int k = 0; k < 3; ++k)
+                if (!hdqt::quantize_dual_eligible(set.both[k])) return HDQT_EINVAL_GEOMETRY;
         }
+    } else {
+        set.add(make_quant_args(W, K, N, 0, nF, &fwd->B, fwd->seed, meta(T_W0), codes(T_W0), nullptr));
+        set.add(make_quant_args(G, M, N, 0, nW, &bwd_weight->B, bwd_weight->seed, meta(T_G0), codes(T_G0), nullptr));
     }
-    if (!g_done) {
-        rc = run_quantize_pair(X, M, K, nF, &fwd->A, fwd->seed, nW, &bwd_weight->A, bwd_weight->seed,
-                               meta(T_X1), meta(T_X0), codes(T_X1), codes(T_X0), nullptr, nullptr, stream, 1);
-        if (rc) return rc;
-        if (with_dx)
-            rc = run_quantize_pair(W, K, N, nI, &bwd_input->B, bwd_input->seed, nF, &fwd->B, fwd->seed,
-                                   meta(T_W1), meta(T_W0), codes(T_W1), codes(T_W0), nullptr, nullptr, stream, 2);
-        else
-            rc = run_quantize(W, K, N, 0, nF, &fwd->B, fwd->seed, meta(T_W0), codes(T_W0), nullptr, stream);
-        if (rc) return rc;
-    }
+    if ((rc = run_quantize_set(set, base, L.zero_bytes, stream))) return rc;
     hdqt::GemmArgs g_fwd = plan_gemm(codes(T_X1), codes(T_W0), fwd->A.b, fwd->B.b, &meta(T_X1)->scale,
                                      &meta(T_W0)->scale, M, N, K, nF, fwd->acc_bits, fwd->s, Z, nullptr,
                                      1 + HDQT_GEMM_FWD);
@@ -982,19 +1002,8 @@ int run_layer_step(const float* X, const hdqt_conv_t* geo, const float* W, const
     rc = run_planned_gemm(g_fwd, acc(HDQT_GEMM_FWD), L.acc_bytes[HDQT_GEMM_FWD], stream);
     if (rc) return rc;
 
-    // ---- backward: G along N and along M.  The weight gradient goes first: its
-    // operand, X's codes along M, was written by the forward part and is the older
+    // ---- backward.  The weight gradient goes first: its operand, X's codes along M, is the older
     // data in the memory-side cache; the input gradient's large output comes last.
-    if (g_done)
-        rc = HDQT_OK;
-    else if (with_dx)
-        rc = run_quantize_pair(G, M, N, nI, &bwd_input->A, bwd_input->seed, nW, &bwd_weight->B,
-                               bwd_weight->seed, meta(T_G1), meta(T_G0), codes(T_G1), codes(T_G0),
-                               nullptr, nullptr, stream, 3);
-    else
-        rc = run_quantize(G, M, N, 0, nW, &bwd_weight->B, bwd_weight->seed, meta(T_G0), codes(T_G0),
-                          nullptr, stream);
-    if (rc) return rc;
     rc = run_planned_gemm(plan_gemm(codes(T_X0), codes(T_G0), bwd_weight->A.b, bwd_weight->B.b,
                                     &meta(T_X0)->scale, &meta(T_G0)->scale, K, N, M, nW,
                                     bwd_weight->acc_bits, bwd_weight->s, dW, nullptr,
@@ -1079,34 +1088,22 @@ int run_layer_fwd(const float* X, const hdqt_conv_t* geo, const float* W, float*
     char* base = static_cast<char*>(workspace);
     char* sv = static_cast<char*>(saved);
     auto meta = [&](size_t off) { return reinterpret_cast<hdqt::QMeta*>(base + off); };
-    hdqt::DualArgs dconv{};
+    QuantSet set;
+    if (bwd_weight)
+        set.add(make_dual_args(X, M, K, L.n_fwd, &fwd->A, fwd->seed, L.n_bww, &bwd_weight->A, bwd_weight->seed,
+                               meta(L.metaX1), meta(L.metaX0), base + L.codesX1, sv + kSavedHeader, nullptr,
+                               reinterpret_cast<float*>(sv), 1));
+    else
+        set.add(make_quant_args(X, M, K, 1, L.n_fwd, &fwd->A, fwd->seed, meta(L.metaX1), base + L.codesX1, nullptr));
     if (geo) {
         // an activation source is read by the two-axis kernels only: both code sets are made,
         // and nothing is launched before the geometry is known to be taken
         if (!bwd_weight) return HDQT_EINVAL_NULL;
-        dconv = make_dual_args(X, M, K, L.n_fwd, &fwd->A, fwd->seed, L.n_bww, &bwd_weight->A,
-                               bwd_weight->seed, meta(L.metaX1), meta(L.metaX0), base + L.codesX1,
-                               sv + kSavedHeader, nullptr, reinterpret_cast<float*>(sv), 1);
-        if (!set_conv_source(&dconv, geo) || !hdqt::quantize_dual_eligible(dconv))
+        if (!set_conv_source(&set.both[0], geo) || !hdqt::quantize_dual_eligible(set.both[0]))
             return HDQT_EINVAL_GEOMETRY;
     }
-    hipError_t e = hdqt::launch_zero2(reinterpret_cast<uint32_t*>(base), (int64_t)(3 * kMetaBytes / 4),
-                                      nullptr, 0, stream);
-    if (e != hipSuccess) return hip_fail(e);
-    if (geo) {
-        e = hdqt::launch_quantize_dual(dconv, stream);
-        rc = e == hipSuccess ? HDQT_OK : hip_fail(e);
-    } else if (bwd_weight)
-        rc = run_quantize_pair(X, M, K, L.n_fwd, &fwd->A, fwd->seed, L.n_bww, &bwd_weight->A,
-                               bwd_weight->seed, meta(L.metaX1), meta(L.metaX0), base + L.codesX1,
-                               sv + kSavedHeader, nullptr, reinterpret_cast<float*>(sv), stream, 1);
-    else
-        rc = run_quantize(X, M, K, 1, L.n_fwd, &fwd->A, fwd->seed, meta(L.metaX1), base + L.codesX1,
-                          nullptr, stream);
-    if (rc) return rc;
-    rc = run_quantize(W, K, N, 0, L.n_fwd, &fwd->B, fwd->seed, meta(L.metaW0), base + L.codesW0, nullptr,
-                      stream);
-    if (rc) return rc;
+    set.add(make_quant_args(W, K, N, 0, L.n_fwd, &fwd->B, fwd->seed, meta(L.metaW0), base + L.codesW0, nullptr));
+    if ((rc = run_quantize_set(set, base, 3 * kMetaBytes, stream))) return rc;
     return run_planned_gemm(plan_gemm(base + L.codesX1, base + L.codesW0, fwd->A.b, fwd->B.b,
                                       &meta(L.metaX1)->scale, &meta(L.metaW0)->scale, M, N, K, L.n_fwd,
                                       fwd->acc_bits, fwd->s, Z, nullptr, 1 + HDQT_GEMM_FWD),
@@ -1182,26 +1179,24 @@ int run_layer_bwd(const float* G, const float* W, const void* saved, const hdqt_
     } else if (geo) {
         return HDQT_EINVAL_NULL;
     }
-    hipError_t e = hdqt::launch_zero2(reinterpret_cast<uint32_t*>(base), (int64_t)(3 * kMetaBytes / 4),
-                                      nullptr, 0, stream);
-    if (e != hipSuccess) return hip_fail(e);
-    if (with_dx)
-        rc = run_quantize_pair(G, M, N, L.n_bwi, &bwd_input->A, bwd_input->seed, L.n_bww, &bwd_weight->B,
+    QuantSet set;
+    if (with_dx) {
+        set.add(make_dual_args(G, M, N, L.n_bwi, &bwd_input->A, bwd_input->seed, L.n_bww, &bwd_weight->B,
                                bwd_weight->seed, meta(L.metaG1), meta(L.metaG0), base + L.codesG1,
-                               base + L.codesG0, nullptr, nullptr, stream, 3);
-    else
-        rc = run_quantize(G, M, N, 0, L.n_bww, &bwd_weight->B, bwd_weight->seed, meta(L.metaG0),
-                          base + L.codesG0, nullptr, stream);
-    if (rc) return rc;
+                               base + L.codesG0, nullptr, nullptr, 3));
+        set.add(make_quant_args(W, K, N, 1, L.n_bwi, &bwd_input->B, bwd_input->seed, meta(L.metaW1),
+                                base + L.codesW1, nullptr));
+    } else {
+        set.add(make_quant_args(G, M, N, 0, L.n_bww, &bwd_weight->B, bwd_weight->seed, meta(L.metaG0),
+                                base + L.codesG0, nullptr));
+    }
+    if ((rc = run_quantize_set(set, base, 3 * kMetaBytes, stream))) return rc;
     rc = run_planned_gemm(plan_gemm(sv + kSavedHeader, base + L.codesG0, bwd_weight->A.b, bwd_weight->B.b,
                                     reinterpret_cast<const float*>(sv), &meta(L.metaG0)->scale, K, N, M,
                                     L.n_bww, bwd_weight->acc_bits, bwd_weight->s, dW, nullptr,
                                     1 + HDQT_GEMM_BWD_WEIGHT),
                           base + L.acc[1], L.acc_bytes[1], stream);
     if (rc || !with_dx) return rc;
-    rc = run_quantize(W, K, N, 1, L.n_bwi, &bwd_input->B, bwd_input->seed, meta(L.metaW1),
-                      base + L.codesW1, nullptr, stream);
-    if (rc) return rc;
     return run_planned_gemm(g_dx, base + L.acc[0], L.acc_bytes[0], stream);
 }
 

@@ -9,14 +9,18 @@ namespace hdqt {
 constexpr int kMaxHadamard = 256;   // largest supported block order
 constexpr int kWave = 64;
 
-// Per-operand calibration record in the workspace.  max|y| is reduced with
-// integer atomicMax on the bit patterns (non-negative floats order like unsigned
-// integers).  Atomics on one address are serialised, so the workgroups spread
-// over 64 slots, each on its own 128-byte line; pass 2 reads one slot per lane
-// and finishes the reduction inside the wave.  `scale` is the value of one
-// code step, written by pass 2.
+// Per-operand calibration record in the workspace.  `scale` is the value of one code step,
+// written by pass 2; max|y| is reduced in one of two ways, the same for every tensor of a launch:
+//   * up to kDenseMost workgroups of pass 1 store their maxima side by side, one word each, and
+//     every wave of pass 2 reads them all.  Nothing has to be cleared beforehand: the launch
+//     that clears the records is 2.5 us and a gap, one of six of a small layer's step.
+//   * more workgroups use integer atomicMax on the bit patterns (non-negative floats order like
+//     unsigned integers) in a record that was cleared.  Atomics on one address are serialised,
+//     so the workgroups spread over 64 slots, each on its own 128-byte line; pass 2 reads one
+//     slot per lane and finishes the reduction inside the wave.
 constexpr int kAmaxSlots = 64;
 constexpr int kAmaxSlotStride = 32;     // dwords
+constexpr int kDenseMost = 1024;        // sixteen words per lane of pass 2
 struct QMeta {
     float scale;
     uint32_t pad[31];
@@ -38,6 +42,23 @@ struct QuantArgs {
     QMeta* meta;            // device
     uint8_t* codes;         // device, packed, contraction-major
     float* scale_out;       // device, may alias &meta->scale, may be null
+};
+
+// How the any-shape kernel cuts one tensor of a launch (plan_any).
+struct AnyPlan {
+    int first;              // the tensor's first workgroup in the launch
+    int count;              // its workgroups
+    int dense;              // `count` if the maxima stand side by side, 0 for atomic slots
+    int gx;                 // axis 0: workgroups along the columns
+    int wc;                 // axis 0: waves side by side in a workgroup (1, 2 or 4)
+    uint32_t upl;           // axis 1: threads per line
+};
+constexpr int kMaxAny = 6;
+struct AnyBatch {
+    QuantArgs t[kMaxAny];
+    AnyPlan p[kMaxAny];
+    int n;
+    int total;              // workgroups
 };
 
 // One tensor quantized along both axes from one read ("row" = axis 1, along the
@@ -130,7 +151,9 @@ struct Im2colArgs {
 hipError_t launch_im2col(const Im2colArgs& a, hipStream_t stream);
 
 // Launchers (host).  Each returns the hipError_t of its last launch.
-hipError_t launch_quantize(const QuantArgs& q, hipStream_t stream);
+// any-shape kernel: add a tensor to a batch (false: it is full); a launch of a whole batch
+bool plan_any(const QuantArgs& q, AnyBatch* b);
+hipError_t launch_any(const AnyBatch& b, int pass, hipStream_t stream);
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t stream);
 // Second reading of the low-bit accumulator: every tile's partial sums to g.partial and their
 // maxima to g.tile_max, then Q with acc_bits per tile and the sum over tiles (see gemm.hip).
@@ -144,8 +167,11 @@ bool gemm_requant_fast_eligible(const GemmArgs& g, int acc_bits);
 hipError_t launch_gemm_requant_fast(const GemmArgs& g, int acc_bits, int pass, hipStream_t stream);
 constexpr int kMaxDualBatch = 3;
 // the two passes of the two-axis quantization, each for up to kMaxDualBatch tensors in one launch
-hipError_t launch_dual_pass1(const DualArgs* qs, int n, hipStream_t stream);
-hipError_t launch_dual_pass2(const DualArgs* qs, int n, hipStream_t stream);
+// ("ride": tensors of the any-shape kernel that share the launch; dense: the maxima of every tensor
+// of the launch stand side by side, see QMeta)
+hipError_t launch_dual_pass1(const DualArgs* qs, int n, bool dense, const AnyBatch* ride, hipStream_t stream);
+hipError_t launch_dual_pass2(const DualArgs* qs, int n, bool dense, const AnyBatch* ride, hipStream_t stream);
+int64_t dual_workgroups(const DualArgs& q);
 bool dual_pass2_batchable(const DualArgs* qs, int n);
 // fills the patch extents of a convolution source; false if the kernels do not take the geometry
 bool dual_conv_plan(DualArgs* q);
@@ -167,17 +193,17 @@ bool gemm_fast_masks(const GemmArgs& g);
 // Optional per-kernel timing (off by default).  When enabled through the C ABI,
 // every launch is bracketed by two HIP events on its stream.
 enum KernelId {
-    K_FILL = 0, K_ROW_ABSMAX, K_ROW_QUANT, K_COL_ABSMAX, K_COL_QUANT, K_PLAIN_ABSMAX,
-    K_PLAIN_QUANT, K_GEMM_ALIGNED, K_GEMM_GENERIC, K_REDUCE, K_GEMM_I4, K_DUAL_ABSMAX, K_DUAL_QUANT,
+    K_FILL = 0, K_ROW_ABSMAX, K_ROW_QUANT, K_COL_ABSMAX, K_COL_QUANT, K_ANY_ABSMAX,
+    K_ANY_QUANT, K_GEMM_ALIGNED, K_GEMM_GENERIC, K_REDUCE, K_GEMM_I4, K_DUAL_ABSMAX, K_DUAL_QUANT,
     K_GEMM_I4_FWD, K_GEMM_I4_BWD_INPUT, K_GEMM_I4_BWD_WEIGHT,
     K_DUAL_ABSMAX_X, K_DUAL_ABSMAX_W, K_DUAL_ABSMAX_G, K_DUAL_QUANT_X, K_DUAL_QUANT_W, K_DUAL_QUANT_G,
     K_DUAL_ABSMAX_BATCH, K_DUAL_QUANT_BATCH, K_REQUANT_TILES, K_REQUANT_SUM, K_IM2COL, K_RELU_MASK,
+    K_GEMM_RAGGED,
     K_COUNT
 };
 bool quantize_fast_eligible(const QuantArgs& q);
 hipError_t launch_quantize_fast(const QuantArgs& q, hipStream_t stream);
 bool quantize_dual_eligible(const DualArgs& q);
-hipError_t launch_quantize_dual(const DualArgs& q, hipStream_t stream);
 bool gemm_fast_eligible(const GemmArgs& g);
 hipError_t launch_gemm_fast(const GemmArgs& g, hipStream_t stream);
 const char* kernel_name(int id);
@@ -236,25 +262,6 @@ __device__ __forceinline__ float inverse_step(float amax_clipped, int b)
     return (float)(levels / (double)amax_clipped);
 }
 
-// Rounding step of Q.  v = y * inv; nearest-even, or floor + Bernoulli(frac)
-// with a 16-bit threshold; then the clamp to the b-bit range.
-__device__ __forceinline__ int quantize_value(float y, float inv, int qmin, int qmax,
-                                              bool stochastic, uint32_t u16)
-{
-    const float v = y * inv;
-    float q;
-    if (stochastic) {
-        const float fl = floorf(v);
-        const float frac = v - fl;
-        q = fl + (((float)u16 < frac * 65536.0f) ? 1.0f : 0.0f);
-    } else {
-        q = rintf(v);
-    }
-    q = fminf(fmaxf(q, (float)qmin), (float)qmax);
-    return (int)q;
-}
-
-
 // ---- calibration helpers --------------------------------------------------
 
 __device__ __forceinline__ float wave_max_shfl(float m)
@@ -264,9 +271,21 @@ __device__ __forceinline__ float wave_max_shfl(float m)
     return m;
 }
 
-// One atomicMax per workgroup (256 threads), into the workgroup's slot, and only
-// if it can raise the slot.  `smem` holds one float per wave.
-__device__ __forceinline__ void block_atomic_max(float m, QMeta* meta, float* smem)
+// The workgroup's maximum into its record.  dense: the word of its own (number `local`); else
+// one atomicMax into slot local % 64, and only if it can raise the slot.
+__device__ __forceinline__ void record_word(float m, QMeta* meta, int local, int dense)
+{
+    const uint32_t bits = __float_as_uint(m);
+    if (dense) {
+        meta->amax[local] = bits;
+        return;
+    }
+    uint32_t* target = &meta->amax[((uint32_t)local % kAmaxSlots) * kAmaxSlotStride];
+    if (bits > __hip_atomic_load(target, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(target, bits);
+}
+
+// The same from every thread's maximum (256 threads).  `smem` holds one float per wave.
+__device__ __forceinline__ void record_max(float m, QMeta* meta, float* smem, int local, int dense)
 {
     m = wave_max_shfl(m);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -275,11 +294,7 @@ __device__ __forceinline__ void block_atomic_max(float m, QMeta* meta, float* sm
     if (threadIdx.x == 0) {
         float r = smem[0];
         for (int w = 1; w < (int)(blockDim.x >> 6); ++w) r = fmaxf(r, smem[w]);
-        const uint32_t slot = (blockIdx.x + blockIdx.y * gridDim.x) % kAmaxSlots;
-        uint32_t* target = &meta->amax[slot * kAmaxSlotStride];
-        const uint32_t bits = __float_as_uint(r);
-        if (bits > __hip_atomic_load(target, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-            atomicMax(target, bits);
+        record_word(r, meta, local, dense);
     }
 }
 
@@ -288,10 +303,26 @@ struct Scaling {
     float scale;    // value of one code step
 };
 
-// Must be reached by whole waves: lane l reads slot l.
-__device__ __forceinline__ Scaling load_scaling(const QMeta* meta, float clip, int b)
+// Must be reached by whole waves: lane l reads slot l, or the words l, l + 64, ... of `dense`.
+__device__ __forceinline__ Scaling load_scaling(const QMeta* meta, float clip, int b, int dense = 0)
 {
-    const float slot = __uint_as_float(meta->amax[(threadIdx.x & 63) * kAmaxSlotStride]);
+    const int lane = threadIdx.x & 63;
+    float slot;
+    if (dense) {
+        slot = 0.0f;
+        for (int i = 0; i < dense; i += 256) {
+            uint32_t w[4];       // (clamped: four loads in flight, a word twice does no harm)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int at = i + 64 * k + lane;
+                w[k] = meta->amax[at < dense ? at : dense - 1];
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) slot = fmaxf(slot, __uint_as_float(w[k]));
+        }
+    } else {
+        slot = __uint_as_float(meta->amax[lane * kAmaxSlotStride]);
+    }
     const float amax = wave_max_shfl(slot);
     const float amax_c = clip * amax;
     Scaling s;

@@ -1611,7 +1611,7 @@ hipError_t launch_gemm_fast(const GemmArgs& g_in, hipStream_t stream)
         if (gx < 1) gx = 1;
     }
     const dim3 grid((unsigned)g.splits, (unsigned)n_rt, (unsigned)gx);
-    ProfileScope ps(g.profile_tag ? K_GEMM_I4_FWD + (g.profile_tag - 1) : K_GEMM_I4, stream);
+    ProfileScope ps(flex ? K_GEMM_RAGGED : g.profile_tag ? K_GEMM_I4_FWD + (g.profile_tag - 1) : K_GEMM_I4, stream);
 #define HDQT_LAUNCH_I4(EPI)                                                                          \
     do {                                                                                             \
         const dim3 block(64 * kWaves);                                                               \

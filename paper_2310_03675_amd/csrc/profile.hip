@@ -31,11 +31,12 @@ const char* kernel_name(int id)
 {
     static const char* names[K_COUNT] = {
         "zero", "fwht_row_absmax", "fwht_row_quant", "fwht_col_absmax", "fwht_col_quant",
-        "plain_absmax", "plain_quant", "gemm_tiled_aligned", "gemm_tiled_generic", "reduce_splits",
+        "fwht_any_absmax", "fwht_any_quant", "gemm_tiled_aligned", "gemm_tiled_generic", "reduce_splits",
         "gemm_i4", "fwht_dual_absmax", "fwht_dual_quant", "gemm_i4_fwd", "gemm_i4_bwd_input",
         "gemm_i4_bwd_weight", "fwht_dual_absmax_X", "fwht_dual_absmax_W", "fwht_dual_absmax_G",
         "fwht_dual_quant_X", "fwht_dual_quant_W", "fwht_dual_quant_G", "fwht_dual_absmax_batch",
-        "fwht_dual_quant_batch", "requant_tile_sums", "requant_quantize_sum", "im2col", "relu_mask"};
+        "fwht_dual_quant_batch", "requant_tile_sums", "requant_quantize_sum", "im2col", "relu_mask",
+        "gemm_tiled_ragged"};
     return (id >= 0 && id < K_COUNT) ? names[id] : "?";
 }
 

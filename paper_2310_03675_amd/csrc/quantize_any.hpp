@@ -1,0 +1,243 @@
+// Hadamard-domain quantization of a tensor of any shape along one axis: the device side shared by
+// the batch kernel (quantize.hip) and the launches in which small tensors ride along with a large
+// one (quantize_dual.hip).
+//
+// A thread holds eight consecutive contraction indices and nothing else, so a small tensor is
+// spread over as many waves as it has (a layer of 64 x 256 x 128: 44 workgroups for its six code
+// sets instead of 4 waves with 64 values a lane).
+//   axis 1: thread = eight codes of one line; larger strides pair neighbouring lanes.  Lines of
+//     any length: a line's last thread holds what is left, the codes behind it are zeros.
+//   axis 0: lane (rg, cg) = (lane / 8, lane % 8) has rows 8 rg .. 8 rg + 7 of column cg of the
+//     wave's 64 x 8 piece; strides 8, 16, 32 pair lanes, 64 and 128 pair waves through LDS.
+// The butterfly runs with strides 1, 2, 4, ..., n/2 in that order: this fixes the binary32
+// rounding to the balanced pairwise tree over the signed terms in natural index order.
+#pragma once
+#include "common.hpp"
+#include "lane_ops.hpp"
+
+namespace hdqt {
+namespace any {
+
+using namespace lanes;
+
+constexpr int kThreads = 256;
+constexpr int kRandPitch = 5;                                // dwords per row of random halfwords
+constexpr int kLdsFloats = 8 * kThreads;                     // cross-wave exchange; the random words of
+static_assert(4 * 64 * kRandPitch <= kLdsFloats, "four waves' random words fit the exchange buffer");
+
+// rows of any length in bytes or elements: dwords at any address
+struct __attribute__((packed, aligned(4))) Float4 { float x, y, z, w; };
+struct __attribute__((packed)) Dword { uint32_t v; };
+
+// The eight halfwords of elements e .. e+7 (e & 7 == 0: one Philox block, else two).
+__device__ __forceinline__ void random8(const QuantArgs& q, uint64_t e, uint32_t r[4])
+{
+    const uint64_t blk = e >> 3;
+    philox4x32_10((uint32_t)blk, (uint32_t)(blk >> 32), q.tensor_id, 0u, q.seed_lo, q.seed_hi, r);
+    if ((q.cols & 7) == 0) return;       // (uniform) e is a multiple of 8 then
+    uint32_t n[4];
+    philox4x32_10((uint32_t)(blk + 1), (uint32_t)((blk + 1) >> 32), q.tensor_id, 0u, q.seed_lo, q.seed_hi, n);
+    // the 16 halfwords from number e & 7 on
+    const uint32_t sh = (uint32_t)e & 7u;
+    const uint32_t m4 = (sh & 4) ? ~0u : 0u, m2 = (sh & 2) ? ~0u : 0u;
+    const uint32_t w[8] = {r[0], r[1], r[2], r[3], n[0], n[1], n[2], n[3]};
+    uint32_t x[6], y[5];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) x[k] = (w[k + 2] & m4) | (w[k] & ~m4);
+#pragma unroll
+    for (int k = 0; k < 5; ++k) y[k] = (x[k + 1] & m2) | (x[k] & ~m2);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) r[k] = __builtin_amdgcn_alignbyte(y[k + 1], y[k], 2 * (sh & 1));
+}
+
+// eight codes of one line, `count` of them inside it (the others are zeros)
+__device__ __forceinline__ void store8(const QuantArgs& q, const uint32_t cw[8], uint8_t* dst, int count)
+{
+    if (q.b <= 4) {
+        const uint32_t w = pack_nibbles(cw);
+        if (count >= 8) reinterpret_cast<Dword*>(dst)->v = w;
+        else
+            for (int k = 0; 2 * k < count; ++k) dst[k] = (uint8_t)(w >> (8 * k));
+    } else {
+        const uint32_t w0 = pack_bytes(cw), w1 = pack_bytes(cw + 4);
+        if (count >= 8) {
+            reinterpret_cast<Dword*>(dst)[0].v = w0;
+            reinterpret_cast<Dword*>(dst)[1].v = w1;
+        } else {
+            for (int k = 0; k < count; ++k) dst[k] = (uint8_t)((k < 4 ? w0 : w1) >> (8 * (k & 3)));
+        }
+    }
+}
+
+__device__ __forceinline__ void emit(const QuantArgs& q, const float v[8], const uint32_t rnd[4], float inv,
+                                     uint8_t* dst, int count)
+{
+    const float qminf = (float)(-(1 << (q.b - 1))), qmaxf = (float)((1 << (q.b - 1)) - 1);
+    const float magic = kMagic + (q.b <= 4 ? 8.0f : 128.0f);
+    uint32_t cw[8];
+    if (q.stochastic) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            cw[i] = code_word<true>(v[i], inv, qminf, qmaxf, magic, sr_halfword(rnd, (uint32_t)i));
+    } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) cw[i] = code_word<false>(v[i], inv, qminf, qmaxf, magic, 0u);
+    }
+    store8(q, cw, dst, count);
+}
+
+// One workgroup of one tensor: transform, then the maximum (returned) or the codes.  `local` is
+// the workgroup's number within the tensor, `p` how the tensor is cut (plan_any).
+template <bool QUANT>
+__device__ __forceinline__ float block(const QuantArgs& q, const AnyPlan& p, int local, float* lds)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    float v[8];
+    uint32_t rnd[4] = {0, 0, 0, 0};
+    uint8_t* dst = nullptr;
+    int count = 0;                       // codes of this thread inside the tensor
+    const int64_t pitch = q.b <= 4 ? ((q.axis ? q.cols : q.rows) + 1) >> 1 : (q.axis ? q.cols : q.rows);
+    const int per = q.b <= 4 ? 4 : 8;    // bytes of eight codes
+    if (q.axis) {
+        // (the workgroup's first line: a 32-bit division wherever that is enough)
+        const int64_t base = (int64_t)local * kThreads;
+        const int64_t line0 = local < (1 << 23) ? (int64_t)((uint32_t)base / p.upl) : base / (int64_t)p.upl;
+        const uint32_t at = (uint32_t)(base - line0 * p.upl) + (uint32_t)tid;
+        const uint32_t down = at / p.upl;
+        const uint32_t j = at - down * p.upl;
+        const int64_t line = line0 + down;
+        const float* src = q.T + line * q.cols + 8 * (int64_t)j;
+        if (line < q.rows) {
+            const int64_t left = q.cols - 8 * (int64_t)j;
+            count = left < 8 ? (int)left : 8;
+        }
+        if (count == 8) {
+            const Float4 lo = reinterpret_cast<const Float4*>(src)[0], hi = reinterpret_cast<const Float4*>(src)[1];
+            v[0] = lo.x; v[1] = lo.y; v[2] = lo.z; v[3] = lo.w;
+            v[4] = hi.x; v[5] = hi.y; v[6] = hi.z; v[7] = hi.w;
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = i < count ? src[i] : 0.0f;
+        }
+        butterfly8(v, q.log2n);
+        if (q.log2n > 3) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = stage_dpp<1>(v[i], (uint32_t)(lane & 1) << 31);
+        }
+        if (q.log2n > 4) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = stage_dpp<2>(v[i], (uint32_t)(lane & 2) << 30);
+        }
+        if (q.log2n > 5) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = stage_dpp<4>(v[i], (uint32_t)(lane & 4) << 29);
+        }
+        if (q.log2n > 6) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = stage_dpp<8>(v[i], (uint32_t)(lane & 8) << 28);
+        }
+        if (q.log2n > 7) {
+#pragma unroll
+            for (int i = 0; i < 8; i += 2) stage_swap<false>(v[i], v[i + 1]);
+        }
+        if (QUANT) {
+            dst = q.codes + line * pitch + (int64_t)j * per;
+            if (q.stochastic) random8(q, (uint64_t)(line * q.cols) + 8 * (uint64_t)j, rnd);
+        }
+    } else {
+        const int64_t by = local / p.gx, bx = local - by * p.gx;
+        const int wc = wave & (p.wc - 1), wr = wave / p.wc;
+        const int rg = lane >> 3, cg = lane & 7;
+        const int64_t row0 = (by * (4 / p.wc) + wr) * 64, col0 = (bx * p.wc + wc) * 8;       // the wave's piece
+        const int64_t row = row0 + rg * 8, col = col0 + cg;
+        if (col < q.cols && row < q.rows) {
+            const int64_t left = q.rows - row;
+            count = left < 8 ? (int)left : 8;
+        }
+        // (clamped addresses: every load is unconditional)
+        const int64_t rc = count ? row : 0, cc = count ? col : 0;
+        const float* src = q.T + rc * q.cols + cc;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = src[(i < count ? i : 0) * q.cols];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = i < count ? v[i] : 0.0f;
+        butterfly8(v, q.log2n);
+        if (q.log2n > 3) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = stage_dpp<8>(v[i], (uint32_t)(lane & 8) << 28);
+        }
+        if (q.log2n > 4) {
+#pragma unroll
+            for (int i = 0; i < 8; i += 2) stage_swap<false>(v[i], v[i + 1]);
+        }
+        if (q.log2n > 5) {
+#pragma unroll
+            for (int i = 0; i < 8; i += 2) stage_swap<true>(v[i], v[i + 1]);
+        }
+        // strides 64 and 128: the partner is another wave (four waves on top of each other: plan_any)
+        for (int st = 6; st < q.log2n; ++st) {
+            const int mask = 64 << (st - 6);
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < 8; ++i) lds[i * kThreads + tid] = v[i];
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float other = lds[i * kThreads + (tid ^ mask)];
+                v[i] = (tid & mask) ? other - v[i] : v[i] + other;
+            }
+        }
+        if (QUANT) {
+            dst = q.codes + col * pitch + (row >> 3) * per;
+            if (q.stochastic) {
+                // the wave's 64 rows of eight halfwords: lane (rg, cg) draws row 8 rg + cg, then
+                // reads column cg of its own eight rows
+                if (q.log2n > 6) __syncthreads();
+                uint32_t* words = reinterpret_cast<uint32_t*>(lds) + wave * 64 * kRandPitch;
+                random8(q, (uint64_t)((row + cg) * q.cols + col0), rnd);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) words[(rg * 8 + cg) * kRandPitch + k] = rnd[k];
+                // LDS operations of one wave are carried out in order; the fence keeps the compiler
+                // from moving the reads above the writes of other lanes
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                const uint16_t* half = reinterpret_cast<const uint16_t*>(words);
+#pragma unroll
+                for (int i = 0; i < 8; i += 2)
+                    rnd[i >> 1] = (uint32_t)half[(rg * 8 + i) * 2 * kRandPitch + cg] |
+                                  (uint32_t)half[(rg * 8 + i + 1) * 2 * kRandPitch + cg] << 16;
+            }
+        }
+    }
+    if (QUANT) {
+        const Scaling sc = load_scaling(q.meta, q.clip, q.b, p.dense);
+        if (local == 0 && tid == 0) {
+            q.meta->scale = sc.scale;
+            if (q.scale_out) *q.scale_out = sc.scale;
+        }
+        if (count) emit(q, v, rnd, sc.inv, dst, count);
+        return 0.0f;
+    }
+    float amax = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf(v[i]));
+    return amax;
+}
+
+// both passes of workgroup `vb` of a batch; `red`: one float per wave
+template <bool QUANT>
+__device__ __forceinline__ void batch_block(const AnyBatch& b, int vb, float* red, float* lds)
+{
+    int k = 0;
+    while (k + 1 < b.n && vb >= b.p[k + 1].first) ++k;
+    const QuantArgs& q = b.t[k];
+    const AnyPlan& p = b.p[k];
+    int local = vb - p.first;
+    if (QUANT) local = p.count - 1 - local;      // what pass 1 read last is in the caches still
+    const float m = block<QUANT>(q, p, local, lds);
+    if (!QUANT) record_max(m, q.meta, red, local, p.dense);
+}
+
+} // namespace any
+} // namespace hdqt

@@ -30,6 +30,7 @@
 
 #include "common.hpp"
 #include "lane_ops.hpp"
+#include "quantize_any.hpp"
 
 namespace hdqt {
 
@@ -398,9 +399,9 @@ __device__ __forceinline__ void col_codes(const Tile& t, const DualCtx& x, int64
         }
 }
 
-// One atomicMax per workgroup and record (see block_atomic_max in common.hpp).
-__device__ __forceinline__ void block_atomic_max2(float m_row, float m_col, QMeta* meta_row,
-                                                  QMeta* meta_col, float (*smem)[2], uint32_t block_id)
+// Both maxima of the workgroup into their records (see QMeta).
+__device__ __forceinline__ void record_max2(float m_row, float m_col, QMeta* meta_row,
+                                            QMeta* meta_col, float (*smem)[2], int local, int dense)
 {
     m_row = wave_max(m_row);
     m_col = wave_max(m_col);
@@ -411,12 +412,7 @@ __device__ __forceinline__ void block_atomic_max2(float m_row, float m_col, QMet
         const int which = threadIdx.x;
         float r = smem[0][which];
         for (int w = 1; w < kThreads / kWave; ++w) r = fmaxf(r, smem[w][which]);
-        QMeta* meta = which ? meta_col : meta_row;
-        const uint32_t slot = block_id % kAmaxSlots;
-        uint32_t* target = &meta->amax[slot * kAmaxSlotStride];
-        const uint32_t bits = __float_as_uint(r);
-        if (bits > __hip_atomic_load(target, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-            atomicMax(target, bits);
+        record_word(r, which ? meta_col : meta_row, local, dense);
     }
 }
 
@@ -504,6 +500,7 @@ struct DualBatch {
     int gx[kMaxDualBatch];       // workgroups along the columns
     int WC[kMaxDualBatch];       // waves side by side in a workgroup (1, 2 or 4)
     int lds_per_wave;            // floats of LDS per wave (convolution sources), a multiple of 4
+    int dense;                   // the maxima stand side by side (see QMeta)
     int spread;                  // pass 2: every spread-th workgroup of the grid is one of tensor 0 (0: off)
 };
 
@@ -563,23 +560,28 @@ __device__ __forceinline__ void dual_block(const DualBatch& b, int k, int vb, fl
         else tile_load(t, q, x, row0, col0);
     }
     if (QUANT) {
-        const Scaling s_row = load_scaling(q.meta_row, q.clip_row, q.b_row);
-        const Scaling s_col = load_scaling(q.meta_col, q.clip_col, q.b_col);
+        const int dense = b.dense ? count : 0;
+        const Scaling s_row = load_scaling(q.meta_row, q.clip_row, q.b_row, dense);
+        const Scaling s_col = load_scaling(q.meta_col, q.clip_col, q.b_col, dense);
         dual_set_scaling(x, q, s_row, s_col, local == 0);
         if (live) dual_codes<(ROUND & 1) != 0, (ROUND & 2) != 0, (ROUND & kRoundWide) != 0>(t, x, row0, col0);
     } else {
         float amax_row = 0.0f, amax_col = 0.0f;
         if (live) dual_absmax(t, x, row0, col0, amax_row, amax_col);
-        block_atomic_max2(amax_row, amax_col, q.meta_row, q.meta_col, red, (uint32_t)local);
+        record_max2(amax_row, amax_col, q.meta_row, q.meta_col, red, local, b.dense);
     }
 }
 
 template <bool QUANT, int ROUND, bool N64, bool CONV>
-__global__ __launch_bounds__(kThreads) void fwht_dual_kernel(DualBatch b)
+__global__ __launch_bounds__(kThreads) void fwht_dual_kernel(DualBatch b, AnyBatch ride)
 {
     __shared__ float red[kThreads / kWave][2];
-    extern __shared__ __attribute__((aligned(16))) float lds[];      // CONV: one patch per wave
+    extern __shared__ __attribute__((aligned(16))) float lds[];      // CONV: one patch per wave; riders' exchange
 
+    if ((int)blockIdx.x >= b.first[b.n]) {
+        any::batch_block<QUANT>(ride, (int)blockIdx.x - b.first[b.n], &red[0][0], lds);
+        return;
+    }
     const int vb = QUANT ? batch_order(b) : (int)blockIdx.x;
     int k = 0;
     while (k + 1 < b.n && vb >= b.first[k + 1]) ++k;
@@ -600,18 +602,24 @@ bool all_order_64(const DualArgs* qs, int n)
     return true;
 }
 
-bool make_batch(const DualArgs* qs, int n, DualBatch* b)
+// waves of a workgroup side by side, and the workgroups of a tensor
+int waves_across(const DualArgs& q)
+{
+    const int64_t strips = q.cols / kTile;
+    return (strips % 4 == 0) ? 4 : (strips % 2 == 0) ? 2 : 1;
+}
+
+bool make_batch(const DualArgs* qs, int n, bool dense, const AnyBatch* ride, DualBatch* b)
 {
     if (n < 1 || n > kMaxDualBatch) return false;
     b->n = n;
+    b->dense = dense ? 1 : 0;
     int64_t total = 0;
     int lds = 0;
     for (int k = 0; k < n; ++k) {
         const DualArgs& q = qs[k];
-        const int64_t strips = q.cols / kTile;
-        const int WC = (strips % 4 == 0) ? 4 : (strips % 2 == 0) ? 2 : 1;
-        const int64_t tall = (int64_t)kTile * (4 / WC);
-        const int64_t gx = strips / WC, gy = (q.rows + tall - 1) / tall;
+        const int WC = waves_across(q);
+        const int64_t gx = q.cols / kTile / WC, wgs = dual_workgroups(q);
         b->t[k] = q;
         if (q.conv) {
             const int need = ((q.pCN * q.pPH * q.pPW + 3) & ~3) + kTile;
@@ -620,9 +628,10 @@ bool make_batch(const DualArgs* qs, int n, DualBatch* b)
         b->first[k] = (int)total;
         b->gx[k] = (int)gx;
         b->WC[k] = WC;
-        total += gx * gy;
-        if (total >= ((int64_t)1 << 31)) return false;
+        total += wgs;
+        if (total >= ((int64_t)1 << 30)) return false;
     }
+    if (ride && ride->total >= (1 << 30)) return false;
     b->first[n] = (int)total;
     b->lds_per_wave = lds;
     b->spread = 0;
@@ -630,6 +639,13 @@ bool make_batch(const DualArgs* qs, int n, DualBatch* b)
 }
 
 } // namespace
+
+int64_t dual_workgroups(const DualArgs& q)
+{
+    const int WC = waves_across(q);
+    const int64_t tall = (int64_t)kTile * (4 / WC);
+    return (q.cols / kTile / WC) * ((q.rows + tall - 1) / tall);
+}
 
 // Geometries the im2col source takes: odd windows, and tiles of 64 pixels that are whole
 // image rows (W a power of two up to 64, H*W a multiple of 64) or lie inside one row
@@ -662,24 +678,35 @@ bool quantize_dual_eligible(const DualArgs& q)
            (q.rows / kTile) * (q.cols / kTile) < ((int64_t)1 << 30);
 }
 
-// Pass 1 (both maxima) of n tensors in one launch; their calibration records must be zero.
-hipError_t launch_dual_pass1(const DualArgs* qs, int n, hipStream_t stream)
+// Dynamic LDS of a launch: the patches of a convolution source, or the riders' exchange
+size_t launch_lds(const DualBatch& b, const AnyBatch* ride)
 {
+    size_t lds = (size_t)(kThreads / kWave) * b.lds_per_wave;
+    if (ride && ride->n && lds < any::kLdsFloats) lds = any::kLdsFloats;
+    return lds * sizeof(float);
+}
+
+// Pass 1 (all maxima) of n tensors and the riders in one launch; without `dense` their
+// calibration records must be zero.
+hipError_t launch_dual_pass1(const DualArgs* qs, int n, bool dense, const AnyBatch* ride, hipStream_t stream)
+{
+    static const AnyBatch none{};
+    if (!ride) ride = &none;
     DualBatch b;
-    if (!make_batch(qs, n, &b)) return hipErrorInvalidValue;
+    if (!make_batch(qs, n, dense, ride, &b)) return hipErrorInvalidValue;
     const int id = n > 1 ? K_DUAL_ABSMAX_BATCH
                          : (qs[0].profile_tag ? K_DUAL_ABSMAX_X + (qs[0].profile_tag - 1) : K_DUAL_ABSMAX);
     ProfileScope ps(id, stream);
-    const dim3 grid((unsigned)b.first[n]), block(kThreads);
-    const size_t lds = (size_t)(kThreads / kWave) * b.lds_per_wave * sizeof(float);
+    const dim3 grid((unsigned)(b.first[n] + ride->total)), block(kThreads);
+    const size_t lds = launch_lds(b, ride);
     const bool n64 = all_order_64(qs, n);
-    if (lds) {      // a convolution source among the tensors
-        if (n64) hipLaunchKernelGGL((fwht_dual_kernel<false, 0, true, true>), grid, block, lds, stream, b);
-        else hipLaunchKernelGGL((fwht_dual_kernel<false, 0, false, true>), grid, block, lds, stream, b);
+    if (b.lds_per_wave) {      // a convolution source among the tensors
+        if (n64) hipLaunchKernelGGL((fwht_dual_kernel<false, 0, true, true>), grid, block, lds, stream, b, *ride);
+        else hipLaunchKernelGGL((fwht_dual_kernel<false, 0, false, true>), grid, block, lds, stream, b, *ride);
     } else if (n64) {
-        hipLaunchKernelGGL((fwht_dual_kernel<false, 0, true, false>), grid, block, 0, stream, b);
+        hipLaunchKernelGGL((fwht_dual_kernel<false, 0, true, false>), grid, block, lds, stream, b, *ride);
     } else {
-        hipLaunchKernelGGL((fwht_dual_kernel<false, 0, false, false>), grid, block, 0, stream, b);
+        hipLaunchKernelGGL((fwht_dual_kernel<false, 0, false, false>), grid, block, lds, stream, b, *ride);
     }
     return hipGetLastError();
 }
@@ -699,25 +726,28 @@ bool dual_pass2_batchable(const DualArgs* qs, int n)
 }
 
 // Pass 2 (both code sets) of n tensors in one launch (see dual_pass2_batchable).
-hipError_t launch_dual_pass2(const DualArgs* qs, int n, hipStream_t stream)
+hipError_t launch_dual_pass2(const DualArgs* qs, int n, bool dense, const AnyBatch* ride, hipStream_t stream)
 {
+    static const AnyBatch none{};
+    if (!ride) ride = &none;
     DualBatch b;
-    if (!make_batch(qs, n, &b) || !dual_pass2_batchable(qs, n)) return hipErrorInvalidValue;
+    if (!make_batch(qs, n, dense, ride, &b) || !dual_pass2_batchable(qs, n)) return hipErrorInvalidValue;
     bool same = true;
     for (int k = 1; k < n; ++k)
         if (qs[k].st_row != qs[0].st_row || qs[k].st_col != qs[0].st_col) same = false;
     const int id = n > 1 ? K_DUAL_QUANT_BATCH
                          : (qs[0].profile_tag ? K_DUAL_QUANT_X + (qs[0].profile_tag - 1) : K_DUAL_QUANT);
     ProfileScope ps(id, stream);
-    const dim3 grid((unsigned)b.first[n]), block(kThreads);
+    const dim3 grid((unsigned)(b.first[n] + ride->total)), block(kThreads);
     const bool n64 = all_order_64(qs, n);
-    const size_t lds = (size_t)(kThreads / kWave) * b.lds_per_wave * sizeof(float);
+    const size_t lds = launch_lds(b, ride);
+    const bool conv = b.lds_per_wave != 0;
 #define HDQT_LAUNCH_PASS2(ROUND)                                                                     \
     do {                                                                                            \
-        if (lds && n64) hipLaunchKernelGGL((fwht_dual_kernel<true, ROUND, true, true>), grid, block, lds, stream, b); \
-        else if (lds) hipLaunchKernelGGL((fwht_dual_kernel<true, ROUND, false, true>), grid, block, lds, stream, b); \
-        else if (n64) hipLaunchKernelGGL((fwht_dual_kernel<true, ROUND, true, false>), grid, block, 0, stream, b); \
-        else hipLaunchKernelGGL((fwht_dual_kernel<true, ROUND, false, false>), grid, block, 0, stream, b); \
+        if (conv && n64) hipLaunchKernelGGL((fwht_dual_kernel<true, ROUND, true, true>), grid, block, lds, stream, b, *ride); \
+        else if (conv) hipLaunchKernelGGL((fwht_dual_kernel<true, ROUND, false, true>), grid, block, lds, stream, b, *ride); \
+        else if (n64) hipLaunchKernelGGL((fwht_dual_kernel<true, ROUND, true, false>), grid, block, lds, stream, b, *ride); \
+        else hipLaunchKernelGGL((fwht_dual_kernel<true, ROUND, false, false>), grid, block, lds, stream, b, *ride); \
     } while (0)
     const int mode = !same ? kRoundPerTensor : (qs[0].st_row ? 1 : 0) | (qs[0].st_col ? 2 : 0);
     // A stochastic tensor in front of nearest ones: its workgroups among theirs (see batch_order),
@@ -753,14 +783,9 @@ hipError_t launch_dual_pass2(const DualArgs* qs, int n, hipStream_t stream)
     return hipGetLastError();
 }
 
-// Pass 1 and pass 2 of one tensor.  (A one-launch variant for small tensors -- tile
-// kept in registers across a grid-wide barrier -- was built and measured: correct,
-// but the cooperative launch it needs for a guaranteed co-resident grid costs about
-// 25 us more than an ordinary launch on this stack, more than the launch it saves.)
-hipError_t launch_quantize_dual(const DualArgs& q, hipStream_t stream)
-{
-    const hipError_t e = launch_dual_pass1(&q, 1, stream);
-    return e != hipSuccess ? e : launch_dual_pass2(&q, 1, stream);
-}
+// (A one-launch variant for small tensors -- tile kept in registers across a grid-wide barrier --
+// was built and measured: correct, but the cooperative launch it needs for a guaranteed
+// co-resident grid costs about 25 us more than an ordinary launch on this stack, more than the
+// launch it saves.)
 
 } // namespace hdqt

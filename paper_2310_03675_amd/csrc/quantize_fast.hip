@@ -1,6 +1,6 @@
 // Hadamard-domain quantization, tuned kernels (gfx950).
 //
-// Same arithmetic as quantize.hip (butterfly strides 1, 2, 4, ... in that
+// Same arithmetic as quantize_any.hpp (butterfly strides 1, 2, 4, ... in that
 // order; one multiplication, one rounding, one clamp per value), different
 // machinery:
 //   * cross-lane butterfly stages use DPP moves (lane xor 1, 2, 4, 8) and the
@@ -15,7 +15,7 @@
 //     Block orders 128 and 256 hold all 256 rows of the strip at once: the last one or
 //     two butterfly stages pair the registers of different 64-row steps.
 // Covers block orders up to 256 on both axes (axis 0: column counts that are multiples of
-// 4); everything else stays with the generic kernels.
+// 4); everything else, and small tensors, take the any-shape kernel.
 
 #include "common.hpp"
 #include "lane_ops.hpp"
@@ -199,7 +199,7 @@ __global__ __launch_bounds__(kThreads) void fwht_row_fast_kernel(QuantArgs q)
         g_cur = g_nxt;
         it = it_next;
     }
-    if (!QUANT) block_atomic_max(amax, q.meta, red);
+    if (!QUANT) record_max(amax, q.meta, red, (int)blockIdx.x, 0);
 }
 
 // ---------------------------------------------------------------------------
@@ -419,7 +419,7 @@ __global__ __launch_bounds__(kThreads) void fwht_col_fast_kernel(QuantArgs q, in
     }
 
     if (!QUANT) {
-        block_atomic_max(amax, q.meta, red);
+        record_max(amax, q.meta, red, (int)(blockIdx.x + blockIdx.y * gridDim.x), 0);
         return;
     }
     __syncthreads();

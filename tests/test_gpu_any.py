@@ -1,0 +1,68 @@
+"""GPU parity of the any-shape quantizer: shapes that are multiples of nothing, both ways of
+collecting the maxima (side by side, and in slots that were cleared), and tensors that ride along
+in a launch of the two-axis kernel."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import capi
+from paper_2310_03675_amd import binding as B
+from paper_2310_03675_amd import workloads
+from test_gpu_parity import check_quantize, dev, host, o_operand
+
+pytestmark = pytest.mark.gpu
+NE, ST = B.ROUND_NEAREST, B.ROUND_STOCHASTIC
+
+
+@pytest.mark.parametrize("axis", [0, 1])
+@pytest.mark.parametrize("b,rounding", [(4, NE), (4, ST), (3, ST), (8, ST), (7, NE)])
+@pytest.mark.parametrize("rows,cols", [(1, 1), (1, 9), (9, 1), (63, 17), (64, 8), (65, 33), (192, 31), (256, 30),
+                                       (130, 12), (128, 561), (561, 11)])
+def test_quantize_any_shape(rows, cols, axis, b, rounding):
+    rng = np.random.default_rng(rows * 1009 + cols)
+    T = (rng.standard_normal((rows, cols)) * 2.0).astype(np.float32)
+    for n in (1, 8, 64, 128, 256):
+        check_quantize(T, axis, n, B.Operand(b, rounding, 0.975, 5), seed=0x1_0000_0007)
+
+
+@pytest.mark.parametrize("rows,cols,axis", [(3001, 1001, 0), (3001, 1001, 1), (4160, 770, 0)])
+def test_quantize_many_workgroups(rows, cols, axis):
+    """More workgroups than maxima that stand side by side; a workspace with leftovers in it."""
+    T = np.random.default_rng(rows).standard_normal((rows, cols)).astype(np.float32)
+    check_quantize(T, axis, 64, B.Operand(4, ST, 1.0, 2), seed=3)
+
+
+def test_zeros_and_lone_values():
+    for rows, cols in ((65, 33), (64, 64)):
+        for axis in (0, 1):
+            T = np.zeros((rows, cols), np.float32)
+            check_quantize(T, axis, 16, B.Operand(4, ST, 1.0, 2))
+            T[-1, -1] = -3.0
+            check_quantize(T, axis, 16, B.Operand(4, NE, 1.0, 2))
+
+
+@pytest.mark.parametrize("M,K,N,n,dx", [(200, 132, 70, 64, True), (64, 256, 128, 16, True), (128, 561, 11, 64, True),
+                                        (131, 27, 64, 32, False), (1024, 1152, 100, 64, True),
+                                        (2048, 640, 70, 64, False), (1088, 576, 24, 64, True), (512, 640, 384, 256, True)])
+def test_step_equals_three_products(M, K, N, n, dx):
+    """One call's sets (small ones, riders beside a large tensor, all on their own) against each
+    product by itself, and the two calls of a training loop against both."""
+    layer = workloads.fc_layer(M, K, N, seed=7)
+    X, W, G = (dev(t) for t in (layer.X, layer.W, layer.G))
+    op = lambda rnd, tid: B.Operand(4, rnd, 1.0, tid)
+    prm = [B.Params(had_block=n, acc_bits=8, s=32, seed=9, A=a, B=b)
+           for a, b in ((op(NE, 0), op(NE, 1)), (op(ST, 6), op(NE, 5)), (op(NE, 8), op(ST, 10)))]
+    kinds = ((B.GEMM_FWD, X, W), (B.GEMM_BWD_INPUT, G, W), (B.GEMM_BWD_WEIGHT, X, G))
+    want = [B.gemm(kind, P, Q, M, K, N, p)[0] for (kind, P, Q), p in zip(kinds, prm)]
+    if not dx:
+        prm[1] = None
+    ws = torch.full((B.layer_step_workspace_size(M, K, N, *prm),), 0x7F, dtype=torch.uint8, device="cuda:0")
+    Z, dX, dW = B.layer_step(X, W, G, *prm, workspace=ws, out=(torch.empty_like(want[0]), torch.empty_like(X) if dx else None,
+                                                              torch.empty_like(W)))[:3]
+    assert torch.equal(Z, want[0]) and torch.equal(dW, want[2]) and (not dx or torch.equal(dX, want[1]))
+    Z, saved = B.layer_fwd(X, W, prm[0], prm[2])
+    dX, dW = B.layer_bwd(G, W, saved, K, prm[1], prm[2])
+    assert torch.equal(Z, want[0]) and torch.equal(dW, want[2]) and (not dx or torch.equal(dX, want[1]))
+    codes, scale, _ = capi.quantize(layer.X.numpy(), 1, n, o_operand(prm[0].A), 9)
+    got, got_scale = B.quantize(X, 1, n, prm[0].A, 9)
+    assert host(got_scale)[0] == scale and np.array_equal(host(got), capi.pack_codes(codes, 4))
