@@ -389,6 +389,10 @@ size_t partial_bytes(int64_t RA, int64_t RB, int64_t D, int64_t s)
 int run_planned_gemm(hdqt::GemmArgs g, void* ws, size_t ws_bytes, hipStream_t stream)
 {
     hipError_t e;
+    if (hdqt::gemm_small_eligible(g)) {
+        e = hdqt::launch_gemm_small(&g, 1, stream);
+        return e == hipSuccess ? HDQT_OK : hip_fail(e);
+    }
     if (g.splits > 1) {
         if (!ws || ws_bytes < (size_t)g.splits * (size_t)(g.RA * g.RB) * sizeof(int32_t))
             return HDQT_EWORKSPACE;
@@ -415,6 +419,28 @@ int run_planned_gemm(hdqt::GemmArgs g, void* ws, size_t ws_bytes, hipStream_t st
         e = hdqt::launch_relu_mask(g.out, g.mask_src, count, stream);
     }
     return e == hipSuccess ? HDQT_OK : hip_fail(e);
+}
+
+// Products that do not depend on one another, in this order: the small ones in one launch, the
+// others one by one, each with its own slices' workspace.
+struct PlannedGemm { hdqt::GemmArgs g; void* ws; size_t ws_bytes; };
+
+int run_planned_gemms(const PlannedGemm* ps, int n, hipStream_t stream)
+{
+    hdqt::GemmArgs small[hdqt::kMaxSmallBatch];
+    int n_small = 0;
+    for (int k = 0; k < n; ++k)
+        if (hdqt::gemm_small_eligible(ps[k].g)) small[n_small++] = ps[k].g;
+    if (n_small) {
+        const hipError_t e = hdqt::launch_gemm_small(small, n_small, stream);
+        if (e != hipSuccess) return hip_fail(e);
+    }
+    for (int k = 0; k < n; ++k) {
+        if (hdqt::gemm_small_eligible(ps[k].g)) continue;
+        const int rc = run_planned_gemm(ps[k].g, ps[k].ws, ps[k].ws_bytes, stream);
+        if (rc) return rc;
+    }
+    return HDQT_OK;
 }
 
 int run_gemm_codes(const void* qA, const void* qB, int bA, int bB, const float* scaleA,
@@ -999,22 +1025,21 @@ int run_layer_step(const float* X, const hdqt_conv_t* geo, const float* W, const
     // the next call's pass over X 66.6 -> 60.8 us.)  The forward call on its own keeps the
     // 128 MB mark: its caller reads Z next.
     if (M * N * (int64_t)sizeof(float) >= ((int64_t)16 << 20)) g_fwd.stream_out = 1;
-    rc = run_planned_gemm(g_fwd, acc(HDQT_GEMM_FWD), L.acc_bytes[HDQT_GEMM_FWD], stream);
-    if (rc) return rc;
-
-    // ---- backward.  The weight gradient goes first: its operand, X's codes along M, is the older
-    // data in the memory-side cache; the input gradient's large output comes last.
-    rc = run_planned_gemm(plan_gemm(codes(T_X0), codes(T_G0), bwd_weight->A.b, bwd_weight->B.b,
-                                    &meta(T_X0)->scale, &meta(T_G0)->scale, K, N, M, nW,
-                                    bwd_weight->acc_bits, bwd_weight->s, dW, nullptr,
-                                    1 + HDQT_GEMM_BWD_WEIGHT),
-                          acc(HDQT_GEMM_BWD_WEIGHT), L.acc_bytes[HDQT_GEMM_BWD_WEIGHT], stream);
-    if (rc || !with_dx) return rc;
-    return run_planned_gemm(plan_gemm(codes(T_G1), codes(T_W1), bwd_input->A.b, bwd_input->B.b,
-                                      &meta(T_G1)->scale, &meta(T_W1)->scale, M, K, N, nI,
-                                      bwd_input->acc_bits, bwd_input->s, dX, nullptr,
-                                      1 + HDQT_GEMM_BWD_INPUT),
-                            acc(HDQT_GEMM_BWD_INPUT), L.acc_bytes[HDQT_GEMM_BWD_INPUT], stream);
+    // The weight gradient goes before the input gradient: its operand, X's codes along M, is the
+    // older data in the memory-side cache; the input gradient's large output comes last.
+    PlannedGemm ps[3];
+    int n = 0;
+    ps[n++] = {g_fwd, acc(HDQT_GEMM_FWD), L.acc_bytes[HDQT_GEMM_FWD]};
+    ps[n++] = {plan_gemm(codes(T_X0), codes(T_G0), bwd_weight->A.b, bwd_weight->B.b, &meta(T_X0)->scale,
+                         &meta(T_G0)->scale, K, N, M, nW, bwd_weight->acc_bits, bwd_weight->s, dW, nullptr,
+                         1 + HDQT_GEMM_BWD_WEIGHT),
+               acc(HDQT_GEMM_BWD_WEIGHT), L.acc_bytes[HDQT_GEMM_BWD_WEIGHT]};
+    if (with_dx)
+        ps[n++] = {plan_gemm(codes(T_G1), codes(T_W1), bwd_input->A.b, bwd_input->B.b, &meta(T_G1)->scale,
+                             &meta(T_W1)->scale, M, K, N, nI, bwd_input->acc_bits, bwd_input->s, dX, nullptr,
+                             1 + HDQT_GEMM_BWD_INPUT),
+                   acc(HDQT_GEMM_BWD_INPUT), L.acc_bytes[HDQT_GEMM_BWD_INPUT]};
+    return run_planned_gemms(ps, n, stream);
 }
 
 } // namespace
@@ -1191,13 +1216,14 @@ int run_layer_bwd(const float* G, const float* W, const void* saved, const hdqt_
                                 base + L.codesG0, nullptr));
     }
     if ((rc = run_quantize_set(set, base, 3 * kMetaBytes, stream))) return rc;
-    rc = run_planned_gemm(plan_gemm(sv + kSavedHeader, base + L.codesG0, bwd_weight->A.b, bwd_weight->B.b,
-                                    reinterpret_cast<const float*>(sv), &meta(L.metaG0)->scale, K, N, M,
-                                    L.n_bww, bwd_weight->acc_bits, bwd_weight->s, dW, nullptr,
-                                    1 + HDQT_GEMM_BWD_WEIGHT),
-                          base + L.acc[1], L.acc_bytes[1], stream);
-    if (rc || !with_dx) return rc;
-    return run_planned_gemm(g_dx, base + L.acc[0], L.acc_bytes[0], stream);
+    PlannedGemm ps[2];
+    int n = 0;
+    ps[n++] = {plan_gemm(sv + kSavedHeader, base + L.codesG0, bwd_weight->A.b, bwd_weight->B.b,
+                         reinterpret_cast<const float*>(sv), &meta(L.metaG0)->scale, K, N, M, L.n_bww,
+                         bwd_weight->acc_bits, bwd_weight->s, dW, nullptr, 1 + HDQT_GEMM_BWD_WEIGHT),
+               base + L.acc[1], L.acc_bytes[1]};
+    if (with_dx) ps[n++] = {g_dx, base + L.acc[0], L.acc_bytes[0]};
+    return run_planned_gemms(ps, n, stream);
 }
 
 } // namespace

@@ -198,12 +198,17 @@ enum KernelId {
     K_GEMM_I4_FWD, K_GEMM_I4_BWD_INPUT, K_GEMM_I4_BWD_WEIGHT,
     K_DUAL_ABSMAX_X, K_DUAL_ABSMAX_W, K_DUAL_ABSMAX_G, K_DUAL_QUANT_X, K_DUAL_QUANT_W, K_DUAL_QUANT_G,
     K_DUAL_ABSMAX_BATCH, K_DUAL_QUANT_BATCH, K_REQUANT_TILES, K_REQUANT_SUM, K_IM2COL, K_RELU_MASK,
-    K_GEMM_RAGGED,
+    K_GEMM_RAGGED, K_GEMM_SMALL,
     K_COUNT
 };
 bool quantize_fast_eligible(const QuantArgs& q);
 hipError_t launch_quantize_fast(const QuantArgs& q, hipStream_t stream);
 bool quantize_dual_eligible(const DualArgs& q);
+// products that cannot fill the chip with large tiles: up to kMaxSmallBatch of them in one launch,
+// never split (gemm_small.hip)
+constexpr int kMaxSmallBatch = 3;
+bool gemm_small_eligible(const GemmArgs& g);
+hipError_t launch_gemm_small(const GemmArgs* gs, int n, hipStream_t stream);
 bool gemm_fast_eligible(const GemmArgs& g);
 hipError_t launch_gemm_fast(const GemmArgs& g, hipStream_t stream);
 const char* kernel_name(int id);

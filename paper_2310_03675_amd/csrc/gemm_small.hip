@@ -1,0 +1,334 @@
+// Integer matmul for products that cannot fill the chip with 128 x 128 tiles (gfx950).
+//
+// Same arithmetic as gemm_fast.hip: packed 4-bit codes or a byte per code, v_mfma_i32_32x32x32_i8,
+// every tile of s codes clamped to the accumulator, 32-bit totals, dequantized once.
+//
+// What bounds these products is a chain, not a rate: with 128 x 128 tiles a layer of 128 x 561 x 561
+// has five workgroups, each of whose SIMDs multiplies, clamps and adds 18 steps of 8 blocks one
+// after the other (11 us), and a split contraction adds a launch.  Here a workgroup owns one
+// block of 32 x 32 outputs and its waves share the contraction between them, whole tiles
+// each; the totals meet in LDS, so that nothing is left for a second launch.  The operands go
+// from memory straight to the registers the matrix core reads (a lane's 16 codes of a step are
+// eight consecutive bytes), four steps ahead of the multiplication and without a barrier.  Every
+// element is fetched once per 32 rows of the other operand: small products live in the L2 caches.
+// Up to three products share a launch (a layer's forward product and both gradients).
+
+#include "common.hpp"
+
+#include <limits.h>
+#include <type_traits>
+
+namespace hdqt {
+
+namespace {
+
+typedef int v2i __attribute__((ext_vector_type(2)));
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v16i __attribute__((ext_vector_type(16)));
+typedef short v2s __attribute__((ext_vector_type(2)));
+
+constexpr int kStep = 32;            // codes per MFMA
+constexpr int kWaves = 8;            // waves of a workgroup
+
+// MODE_TILES: tiles of whole steps, compare-select clamp.  MODE_SAT8: tiles of one step, 8-bit
+// accumulators, packed codes: two tile sums per saturating conversion, added by one dot product
+// (see EPI_SAT8_S32 in gemm_fast.hip).  MODE_HALF: tiles of 16 codes, two per step.
+enum Mode { MODE_TILES = 0, MODE_SAT8 = 1, MODE_HALF = 2 };
+constexpr int kModeWide = 4;
+
+// codes at any byte address
+struct __attribute__((packed)) Bytes4 { uint32_t v; };
+struct __attribute__((packed)) Bytes8 { uint32_t x, y; };
+
+// The 8 bytes of codes at byte `at` of an operand, of which `codes` (any number, also none) lie
+// inside their line, the others as zeros: the 8 bytes up to the line's end (or the operand's first 8,
+// where that would begin in front of it; operands have at least 8), shifted into place.
+template <bool WIDE>
+__device__ __forceinline__ uint64_t load_tail(const uint8_t* q, uint32_t at, int codes)
+{
+    constexpr int kBits = WIDE ? 8 : 4;
+    if (codes <= 0) return 0;
+    if (codes > 64 / kBits) codes = 64 / kBits;
+    const uint32_t bytes = (uint32_t)(codes * kBits + 7) / 8, end = at + bytes, start = end > 8 ? end - 8 : 0;
+    const Bytes8 b = *reinterpret_cast<const Bytes8*>(q + start);
+    const uint64_t w = ((uint64_t)b.y << 32 | b.x) >> (8 * (at - start));
+    return codes * kBits == 64 ? w : w & (((uint64_t)1 << (codes * kBits)) - 1);
+}
+
+// A lane's 16 codes of a step: 2 dwords, 4 with a byte per code.  (One value, not an array: that
+// way a group of them stays in registers whatever the branches around the loads.)
+template <bool WIDE>
+using Codes = uint32_t __attribute__((ext_vector_type(WIDE ? 4 : 2)));
+
+// The step at code k: the lane's half of it, or (HALF) its halves of the step's two tiles.  `line` is
+// the byte of the lane's line in the operand, `left` the codes of the line from k on (TAIL: fewer
+// than a step's).
+template <bool WIDE, bool HALF, bool TAIL>
+__device__ __forceinline__ Codes<WIDE> load_step(const uint8_t* q, uint32_t line, int64_t k, int half, int64_t left)
+{
+    constexpr int N = WIDE ? 4 : 2, PER = HALF ? N / 2 : N;              // dwords, dwords of one run
+    const uint32_t k_byte = (uint32_t)(WIDE ? k : k >> 1);
+    const uint8_t* step = q + k_byte;                                    // (the same in every lane)
+    Codes<WIDE> w;
+#pragma unroll
+    for (int i = 0; i < N; i += 2) {
+        // dwords i and i + 1: of one run, or (HALF, packed) one of either tile
+        const int code = HALF ? 16 * (i / PER) + 8 * half : 16 * half + 4 * (WIDE ? i : 0);
+        const uint32_t at = line + (uint32_t)(WIDE ? code : code >> 1);
+        if constexpr (TAIL && PER == 1) {
+            w[0] = (uint32_t)load_tail<WIDE>(q, k_byte + at, (int)left - code);
+            w[1] = (uint32_t)load_tail<WIDE>(q, k_byte + at + 8, (int)left - code - 16);
+        } else if constexpr (TAIL) {
+            const uint64_t two = load_tail<WIDE>(q, k_byte + at, (int)left - code);
+            w[i] = (uint32_t)two;
+            w[i + 1] = (uint32_t)(two >> 32);
+        } else if constexpr (PER == 1) {
+            w[0] = reinterpret_cast<const Bytes4*>(step + at)->v;
+            w[1] = reinterpret_cast<const Bytes4*>(step + 8 + at)->v;
+        } else {
+            const Bytes8 two = *reinterpret_cast<const Bytes8*>(step + at);
+            w[i] = two.x;
+            w[i + 1] = two.y;
+        }
+    }
+    return w;
+}
+
+// the fragment(s) the matrix core wants: packed codes as bytes 16 * code, even positions first
+template <bool WIDE>
+__device__ __forceinline__ v4i whole(Codes<WIDE> w)
+{
+    if constexpr (WIDE) {
+        return v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
+    } else {
+        const uint32_t m = 0xF0F0F0F0u;
+        return v4i{(int)((w[0] << 4) & m), (int)((w[1] << 4) & m), (int)(w[0] & m), (int)(w[1] & m)};
+    }
+}
+
+template <bool WIDE>
+__device__ __forceinline__ long tile_half(Codes<WIDE> w, int t)
+{
+    const uint32_t m = 0xF0F0F0F0u;
+    v2i p;
+    if constexpr (WIDE) p = t ? v2i{(int)w[2], (int)w[3]} : v2i{(int)w[0], (int)w[1]};
+    else p = v2i{(int)(((t ? w[1] : w[0]) << 4) & m), (int)((t ? w[1] : w[0]) & m)};
+    return __builtin_bit_cast(long, p);
+}
+
+__device__ __forceinline__ int clamp3(int v, int lo, int hi)      // (plain C++: see gemm_fast.hip)
+{
+    const int t = v < lo ? lo : v;
+    return t > hi ? hi : t;
+}
+
+// The totals of a wave: the 32 x 32 block at (row0, col0), codes [k_begin, k_end), whole tiles.
+template <bool WIDE, int MODE>
+__device__ __forceinline__ v16i contract(const GemmArgs& g, int64_t row0, int64_t col0, int64_t k_begin, int64_t k_end)
+{
+    constexpr bool HALF = MODE == MODE_HALF;
+    constexpr int G = WIDE || HALF ? 2 : 4;  // steps per group of loads (tiles of 16 keep the sums of two a step)
+    const int lane = threadIdx.x & 63, half = lane >> 5;
+    // (rows outside the operands: the last one, nothing of it is written)
+    const int64_t ra = row0 + (lane & 31), rb = col0 + (lane & 31);
+    const uint32_t la = (uint32_t)(ra < g.RA ? ra : g.RA - 1) * (uint32_t)g.pitchA;
+    const uint32_t lb = (uint32_t)(rb < g.RB ? rb : g.RB - 1) * (uint32_t)g.pitchB;
+    struct Group {
+        Codes<WIDE> a[G], b[G];
+    };
+    const int64_t whole_steps = k_end > k_begin ? (k_end - k_begin) / kStep : 0, k_whole = k_begin + whole_steps * kStep;
+    // the group of steps at k; past the whole steps: zeros (a tile of them adds nothing)
+    auto fetch = [&](Group& f, int64_t k) {
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            Codes<WIDE> a = 0, b = 0;
+            if (k + kStep * i < k_whole) {
+                a = load_step<WIDE, HALF, false>(g.qA, la, k + kStep * i, half, 0);
+                b = load_step<WIDE, HALF, false>(g.qB, lb, k + kStep * i, half, 0);
+            }
+            f.a[i] = a;
+            f.b[i] = b;
+        }
+    };
+    const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    const int lo = g.acc_lo_scaled, hi = g.acc_hi_scaled;
+    const int steps_per_tile = (int)(g.s / kStep);
+    int in_tile = 0;
+    v16i total = zero, part = zero;          // part: the sums of the running tile (MODE_TILES)
+    auto finish_tile = [&] {
+        in_tile = 0;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) total[r] += clamp3(part[r], lo, hi);
+        part = zero;
+    };
+    // the first `valid` steps of a group count; COUNT: how many there are at most
+    auto multiply = [&](const Group& f, int64_t valid, auto count) {
+        constexpr int COUNT = decltype(count)::value;
+#pragma unroll
+        for (int i = 0; i < COUNT; i += MODE == MODE_SAT8 ? 2 : 1) {
+            if constexpr (MODE == MODE_SAT8) {
+                const v16i p0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(whole<WIDE>(f.a[i]), whole<WIDE>(f.b[i]), zero, 0, 0, 0);
+                v16i p1 = zero;
+                if (i + 1 < COUNT) {
+                    const int j = i + 1 < G ? i + 1 : 0;
+                    p1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(whole<WIDE>(f.a[j]), whole<WIDE>(f.b[j]), zero, 0, 0, 0);
+                }
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const v2s pk = __builtin_amdgcn_cvt_pk_i16(p0[r], p1[r]);
+                    total[r] = __builtin_amdgcn_sdot4(__builtin_bit_cast(int, pk), 0x01000100, total[r], false);
+                }
+            } else if constexpr (HALF) {
+                const v16i p0 = __builtin_amdgcn_mfma_i32_32x32x16_i8(tile_half<WIDE>(f.a[i], 0), tile_half<WIDE>(f.b[i], 0), zero, 0, 0, 0);
+                const v16i p1 = __builtin_amdgcn_mfma_i32_32x32x16_i8(tile_half<WIDE>(f.a[i], 1), tile_half<WIDE>(f.b[i], 1), zero, 0, 0, 0);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) total[r] += clamp3(p0[r], lo, hi) + clamp3(p1[r], lo, hi);
+            } else {
+                part = __builtin_amdgcn_mfma_i32_32x32x32_i8(whole<WIDE>(f.a[i]), whole<WIDE>(f.b[i]), part, 0, 0, 0);
+                if (i < valid && ++in_tile == steps_per_tile) finish_tile();
+            }
+        }
+    };
+    Group now, next;
+    fetch(now, k_begin);
+    for (int64_t done = 0; done < whole_steps; done += G) {
+        fetch(next, k_begin + (done + G) * kStep);
+        multiply(now, whole_steps - done, std::integral_constant<int, G>{});
+        now = next;
+    }
+    if (k_whole < k_end) {                   // the line ends inside a step
+        Group last{};
+        last.a[0] = load_step<WIDE, HALF, true>(g.qA, la, k_whole, half, k_end - k_whole);
+        last.b[0] = load_step<WIDE, HALF, true>(g.qB, lb, k_whole, half, k_end - k_whole);
+        multiply(last, 1, std::integral_constant<int, 1>{});
+    }
+    if (MODE == MODE_TILES && in_tile) finish_tile();
+    if (!WIDE && MODE != MODE_SAT8) {        // (exact: every sum carries the factor 16 * 16)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) total[r] >>= 8;
+    }
+    return total;
+}
+
+struct SmallBatch {
+    GemmArgs g[kMaxSmallBatch];
+    int n;
+    int first[kMaxSmallBatch + 1];
+    int n_ct[kMaxSmallBatch];
+    int mode[kMaxSmallBatch];        // Mode, + kModeWide with a byte per code
+};
+
+__global__ __launch_bounds__(64 * kWaves, 4) void gemm_small_kernel(SmallBatch b)
+{
+    __shared__ int meet[kWaves][16][64];
+    int p = 0;
+    while (p + 1 < b.n && (int)blockIdx.x >= b.first[p + 1]) ++p;
+    const GemmArgs& g = b.g[p];
+    const int local = (int)blockIdx.x - b.first[p];
+    const int rt = local / b.n_ct[p], ct = local - rt * b.n_ct[p];
+    const int64_t row0 = (int64_t)rt * 32, col0 = (int64_t)ct * 32;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+
+    // the wave's share of the contraction, in tiles (in steps, where a step holds two tiles or
+    // nothing is clamped)
+    const int64_t unit = g.s < kStep || g.acc_hi == INT_MAX ? kStep : g.s;
+    const int64_t units = (g.D + unit - 1) / unit;
+    const int64_t k_begin = units * wave / kWaves * unit;
+    int64_t k_end = units * (wave + 1) / kWaves * unit;
+    if (k_end > g.D) k_end = g.D;
+
+    v16i total;
+    switch (b.mode[p]) {
+    case MODE_TILES: total = contract<false, MODE_TILES>(g, row0, col0, k_begin, k_end); break;
+    case MODE_SAT8: total = contract<false, MODE_SAT8>(g, row0, col0, k_begin, k_end); break;
+    case MODE_HALF: total = contract<false, MODE_HALF>(g, row0, col0, k_begin, k_end); break;
+    case MODE_TILES + kModeWide: total = contract<true, MODE_TILES>(g, row0, col0, k_begin, k_end); break;
+    default: total = contract<true, MODE_HALF>(g, row0, col0, k_begin, k_end); break;
+    }
+
+#pragma unroll
+    for (int r = 0; r < 16; ++r) meet[wave][r][lane] = total[r];
+    __syncthreads();
+    const float dq = (g.scaleA[0] * g.scaleB[0]) * g.inv_n;
+    const int64_t col = col0 + (lane & 31);
+#pragma unroll
+    for (int i = 0; i < 16 / kWaves; ++i) {
+        const int r = wave * (16 / kWaves) + i;
+        int v = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) v += meet[w][r][lane];
+        const int64_t row = row0 + 8 * (r >> 2) + (r & 3) + 4 * (lane >> 5);
+        if (row < g.RA && col < g.RB) {
+            const int64_t o = row * g.RB + col;
+            float f = (float)v * dq;
+            if (g.acc_out) g.acc_out[o] = v;
+            if (g.out_bf16) g.out_bf16[o] = (uint16_t)bf16_bits(f);
+            if (g.out) {
+                if (g.mask_src && !(g.mask_src[o] > 0.0f)) f = 0.0f;
+                g.out[o] = f;
+            }
+        }
+    }
+}
+
+int mode_of(const GemmArgs& g)
+{
+    if (g.s < kStep) return MODE_HALF + (g.bA > 4 ? kModeWide : 0);
+    if (g.bA <= 4 && g.s == kStep && g.acc_hi == 127) return MODE_SAT8;
+    return MODE_TILES + (g.bA > 4 ? kModeWide : 0);
+}
+
+// The products this kernel is the faster one for.  Measured on codes alone, the large tiles'
+// kernel (with the sum over a split contraction's parts) against this one, 4-bit codes, tiles of
+// 32: 128 x 561 x 561 (rows x columns x contraction) 13.7 / 7.4 us, 7.4 being what any call costs;
+// 1024 x 256 x 1024 14.6 / 7.5; 8192 x 128 x 1152 23.6 / 10.7; 512 x 512 x 4608 24.0 / 12.5.  Beyond:
+// 1152 x 128 x 8192 16.5 / 18.0 (a wave's chain of steps is too long), 2048 x 512 x 4608 28.7 / 38.3
+// (too many steps in all: the operands come from L2 once per 32 rows), 131072 x 64 x 27 26.7 / 40.3
+// (too many workgroups with one step each).  Between 512 and 1024 blocks it wins only where the
+// other one splits the contraction: 2048 x 512 x 512 15.8 / 8.9 with tiles of 32 (split), 8.2 / 9.9
+// with tiles of 64 (not split).
+bool small_enough(const GemmArgs& g)
+{
+    const int64_t blocks = ((g.RA + 31) / 32) * ((g.RB + 31) / 32), steps = (g.D + kStep - 1) / kStep;
+    return g.D <= 4608 && blocks <= (g.splits > 1 ? 1024 : 512) && blocks * steps <= 36864 &&
+           (g.RA + g.RB) * (g.pitchA + g.pitchB) < ((int64_t)1 << 31);
+}
+
+} // namespace
+
+bool gemm_small_eligible(const GemmArgs& g)
+{
+    if (g.fold || (g.bA > 4) != (g.bB > 4)) return false;      // packed or bytes, the same on both sides
+    if (g.s != 16 && g.s % kStep != 0) return false;
+    if (g.RA * g.pitchA < 8 || g.RB * g.pitchB < 8) return false;      // (see load_tail)
+    if (mode_of(g) == MODE_SAT8) return small_enough(g);       // unscaled totals: covered by the API's range check
+    // a tile's sum and the totals, times 256 with packed codes, must stay inside int32
+    const int64_t max_prod = ((int64_t)1 << (g.bA - 1)) * ((int64_t)1 << (g.bB - 1)), room = g.bA > 4 ? ((int64_t)1 << 31) : ((int64_t)1 << 23);
+    const int64_t tile_max = g.s * max_prod, acc_max = (int64_t)g.acc_hi + 1;
+    const int64_t n_tiles = (g.D + g.s - 1) / g.s;
+    return tile_max < room && (tile_max < acc_max ? tile_max : acc_max) * n_tiles < room && small_enough(g);
+}
+
+hipError_t launch_gemm_small(const GemmArgs* gs, int n, hipStream_t stream)
+{
+    if (n < 1 || n > kMaxSmallBatch) return hipErrorInvalidValue;
+    SmallBatch b{};
+    b.n = n;
+    int64_t total = 0;
+    for (int k = 0; k < n; ++k) {
+        GemmArgs& g = b.g[k] = gs[k];
+        const int64_t f = g.bA > 4 ? 1 : 256, lo = (int64_t)g.acc_lo * f, hi = (int64_t)g.acc_hi * f;
+        g.acc_lo_scaled = lo < INT_MIN ? INT_MIN : (int)lo;
+        g.acc_hi_scaled = hi > INT_MAX ? INT_MAX : (int)hi;
+        b.mode[k] = mode_of(g);
+        b.n_ct[k] = (int)((g.RB + 31) / 32);
+        b.first[k] = (int)total;
+        total += b.n_ct[k] * ((g.RA + 31) / 32);
+    }
+    b.first[n] = (int)total;
+    ProfileScope ps(n > 1 ? K_GEMM_SMALL : gs[0].profile_tag ? K_GEMM_I4_FWD + (gs[0].profile_tag - 1) : K_GEMM_I4, stream);
+    hipLaunchKernelGGL(gemm_small_kernel, dim3((unsigned)total), dim3(64 * kWaves), 0, stream, b);
+    return hipGetLastError();
+}
+
+} // namespace hdqt

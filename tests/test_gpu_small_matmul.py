@@ -1,0 +1,42 @@
+"""GPU parity of the matmul on both sides of the line between its two kernels: small products (32 x 32
+blocks, the contraction shared by a workgroup's waves) and those just behind it, which go to the
+large tiles: long contractions, and outputs of many blocks."""
+import pytest
+
+from paper_2310_03675_amd import binding as B  # noqa: F401
+from test_gpu_parity import check_gemm_codes
+
+pytestmark = pytest.mark.gpu
+
+PACKED = ((32, 8), (64, 8), (16, 8), (32, 12), (16, 9), (16, 6), (96, 32), (128, 16), (256, 16), (8192, 32))
+BYTES = ((32, 16), (64, 16), (16, 16), (16, 12), (96, 32), (32, 12), (256, 16))
+
+
+def both_kinds(RA, RB, D, extreme):
+    for s, a in PACKED:
+        check_gemm_codes(RA, RB, D, 4, 4, s, a, extreme=extreme)
+    for s, a in BYTES:
+        check_gemm_codes(RA, RB, D, 8, 7, s, a, extreme=extreme)
+
+
+@pytest.mark.parametrize("D", [1, 8, 15, 16, 17, 31, 33, 64, 95, 250, 257, 561, 1000])
+def test_small_products(D):
+    """Contractions that end anywhere in a step, with more waves than steps and the other way
+    round; blocks that end inside a row and a column block; one row."""
+    both_kinds(33, 65, D, 0.4)
+    both_kinds(1, 40, D, 0.1)
+
+
+def test_small_products_at_the_longest_contraction():
+    both_kinds(40, 33, 4608, 0.3)
+    both_kinds(33, 31, 4607, 0.05)
+
+
+@pytest.mark.parametrize("D", [4640, 5003, 8200])
+def test_long_contractions_on_large_tiles(D):
+    both_kinds(131, 70, D, 0.3)
+
+
+@pytest.mark.parametrize("D", [27, 64, 100, 129, 520])
+def test_many_blocks_on_large_tiles(D):
+    both_kinds(1100, 1000, D, 0.2)
