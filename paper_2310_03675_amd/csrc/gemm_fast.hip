@@ -122,9 +122,8 @@ struct Staged {
 };
 
 // Operands are read through buffer descriptors that cover exactly their bytes: a unit that
-// lies outside (a row beyond the last one, a position beyond the part's end, a halo row of
-// the fold) is given an offset beyond the descriptor's range and comes back as zeros from
-// the hardware's range check.  No branch surrounds the load, so the compiler can count the
+// lies outside (a row beyond the last one, a position beyond the part's end) is given an offset
+// beyond the descriptor's range and comes back as zeros from the hardware's range check.  No branch surrounds the load, so the compiler can count the
 // loads in flight: with the load inside an `if` it waited for all of them at the top of
 // every stage, the ones just issued for the stage after next included.
 typedef unsigned int u4v __attribute__((ext_vector_type(4)));
@@ -321,8 +320,7 @@ __device__ __forceinline__ int clamp3(int v, int lo, int hi)
 // nothing.
 // MASK (plain fp32 output only): g.mask_src, a tensor of the output's shape, is read at the end
 // of a tile (all of a wave's values in flight together) and the output is written where it is
-// positive, +0 elsewhere.  An instance of its own: the 32 values cost registers.  (The fold
-// epilogue masks with a run-time test: it reads one value per output element anyway.)
+// positive, +0 elsewhere.  An instance of its own: the 32 values cost registers.
 // FLEX: rows of codes that are no whole dwords (D no multiple of 8, or of 4 with a byte per
 // code), and the outputs the other instances of an epilogue do not write (bfloat16, masked):
 // chosen at run time, element by element.  What it replaces there is the generic kernel of
@@ -330,21 +328,20 @@ __device__ __forceinline__ int clamp3(int v, int lo, int hi)
 // call of 2947 x 561 x 561 in tiles of 32, quantization included, 178 -> 38 us; a square one
 // of 3309 rows 2430 -> 306 us.  One dword more per unit and four byte shifts are what the
 // alignment costs; one stage of loads in flight instead of two keeps it at four waves per SIMD.
-template <int EPI, int KS, bool STREAM, int WAVES, bool BF16, bool FOLD, bool WIDE = false, bool NARROW = false,
-          bool MASK = false, bool PAIR = false, bool FLEX = false>
+template <int EPI, int KS, bool STREAM, int WAVES, bool BF16, bool WIDE = false, bool NARROW = false,
+          bool MASK = false, bool FLEX = false>
 __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void gemm_i4_kernel(GemmArgs g)
 {
-    static_assert(!PAIR || FOLD, "pair mode is a way of folding");
-    static_assert(!FLEX || (!BF16 && !FOLD && !NARROW && !MASK && !STREAM), "flexible instances decide these at run time");
-    static_assert(!MASK || (!BF16 && !FOLD && !WIDE && !NARROW), "masked output: plain packed instances only");
-    static_assert(!NARROW || (WAVES == 8 && !BF16 && !FOLD && !WIDE), "narrow tiles: plain packed instances only");
+    static_assert(!FLEX || (!BF16 && !NARROW && !MASK && !STREAM), "flexible instances decide these at run time");
+    static_assert(!MASK || (!BF16 && !WIDE && !NARROW), "masked output: plain packed instances only");
+    static_assert(!NARROW || (WAVES == 8 && !BF16 && !WIDE), "narrow tiles: plain packed instances only");
     constexpr int TM = BM, TN = NARROW ? 64 : BN;   // the workgroup's tile
     // ROWWIDE (streamed outputs, i.e. at least 128 MB): a wave is one block high and two wide
     // instead of two high and one wide, so that its two stores of a row are neighbours (256
     // bytes; streaming stores of 256-byte pieces reach 5.0 TB/s where 128-byte pieces reach
     // 4.6).  Same fragment reads per MFMA.  The benchmark layer's input gradient inside the
     // step: 73.3 -> 70.6 us; its bfloat16 variant 57.7 -> 55.4 us.
-    constexpr bool ROWWIDE = STREAM && !NARROW && !FOLD && WAVES == 8;
+    constexpr bool ROWWIDE = STREAM && !NARROW && WAVES == 8;
     constexpr int RS = (NARROW || ROWWIDE) ? 1 : 2; // 32-row MFMA blocks per wave
     constexpr int WROWS = 32 * RS;
     constexpr bool kSat16 = (EPI == EPI_SAT16_S32 || EPI == EPI_SAT16_S64 || EPI == EPI_SAT16_S16);
@@ -358,10 +355,10 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
     constexpr bool kReqMax = (EPI == EPI_REQ_MAX || EPI == EPI_REQ_MAX_S32);
     constexpr bool kReqSum = (EPI == EPI_REQ_SUM || EPI == EPI_REQ_SUM_S32), kReq = kReqMax || kReqSum;
     constexpr bool kReqS32 = (EPI == EPI_REQ_MAX_S32 || EPI == EPI_REQ_SUM_S32);
-    static_assert(!kReq || (!BF16 && !FOLD && !WIDE && !NARROW && !MASK), "second reading: plain packed instances only");
+    static_assert(!kReq || (!BF16 && !WIDE && !NARROW && !MASK), "second reading: plain packed instances only");
     constexpr bool kCert16 = (EPI == EPI_CERT16_S32);
     constexpr bool kCert = (EPI == EPI_CERT8_S32) || kCert16;
-    static_assert(!kCert || (WAVES == 8 && KS == KS_LONG && !BF16 && !FOLD && !WIDE && !MASK), "certified tiles: plain packed instances only");
+    static_assert(!kCert || (WAVES == 8 && KS == KS_LONG && !BF16 && !WIDE && !MASK), "certified tiles: plain packed instances only");
     const int fin_shift = (kSat16 || kCert16) ? g.fin_shift : ((kSat8 || kReq || kCert) ? 0 : SHIFT);
     const uint32_t low_clear = (kSat16 || kCert16) ? (0xFFFFu & (0xFFFFu << g.fin_shift)) * 0x00010001u : 0u;
     constexpr int REGS = WIDE ? 2 : 1;                 // 16-byte registers per unit in flight
@@ -405,25 +402,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
     const int lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
     const int64_t row0 = (int64_t)blockIdx.y * TM;
-    // fold: a column tile is f_cg whole channels (f_cg * kh * kw <= 128 columns)
-    const int col_stride = FOLD ? g.f_cg * g.fkh * g.fkw : TN;
-    const int n_ct = FOLD ? (g.fC + g.f_cg - 1) / g.f_cg : (int)((g.RB + TN - 1) / TN);
-    // fold, strip mode: row tile = f_rows_c image rows of one image starting (kh-1)/2 rows above
-    // the rows it writes; rows outside the image are zero
-    const int f_ph = FOLD ? (g.fkh - 1) / 2 : 0, f_pw = FOLD ? (g.fkw - 1) / 2 : 0;
-    const int f_img = (FOLD && !g.f_imgs) ? (int)blockIdx.y / g.f_strips : 0;
-    const int f_y0 = (FOLD && !g.f_imgs) ? ((int)blockIdx.y % g.f_strips) * g.f_rows_out - f_ph : 0;
-    // fold, pair mode: row tiles 2 blockIdx.y and 2 blockIdx.y + 1 are the two halves of image
-    // blockIdx.y; the load stream and the multiply stream each know which half they are at
-    constexpr bool f_pair = PAIR;     // (an instance of its own: where a pixel's accumulators lie is then a compile-time choice)
-    int f_half = 0, c_half = 0;
-    auto a_row = [&](int r) -> int64_t {          // source row of qA for row r of the tile, -1: zero
-        if (f_pair) return ((int64_t)blockIdx.y * 2 + f_half) * TM + r;
-        if (!FOLD || g.f_imgs) return row0 + r;
-        const int yy = f_y0 + (r >> g.f_log2w);
-        if (yy < 0 || yy >= g.fH) return -1;
-        return ((int64_t)f_img * g.fH + yy) * g.fW + (r & (g.fW - 1));
-    };
+    const int n_ct = (int)((g.RB + TN - 1) / TN);
 
     const int64_t t_begin = (int64_t)blockIdx.x * g.tiles_per_split;
     int64_t t_end = t_begin + g.tiles_per_split;
@@ -476,7 +455,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
         // operands: the number of loads in flight then does not depend on the path taken, and
         // the wait at the top of a stage can leave the newer stage's loads in flight)
         const int64_t ke = f_ct < n_ct ? k_end : 0;
-        const int64_t col0 = (int64_t)f_ct * col_stride;
+        const int64_t col0 = (int64_t)f_ct * TN;
 #pragma unroll
         for (int i = 0; i < UNITS; ++i) {
             const int r = lrow + ROWS_PER_PASS * i;
@@ -488,11 +467,11 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
             } else if constexpr (WIDE) {
 #pragma unroll
                 for (int hf = 0; hf < 2; ++hf) {
-                    st.a[2 * i + hf] = load_unit_wide(rsA, g.pitchA, g.RA, a_row(r), f_k + lks * KSTEP, ke, hf);
+                    st.a[2 * i + hf] = load_unit_wide(rsA, g.pitchA, g.RA, row0 + r, f_k + lks * KSTEP, ke, hf);
                     st.b[2 * i + hf] = load_unit_wide(rsB, g.pitchB, g.RB, col0 + r, f_k + lks * KSTEP, ke, hf);
                 }
             } else {
-                st.a[i] = load_unit(rsA, g.pitchA, g.RA, a_row(r), f_k + lks * KSTEP, ke);
+                st.a[i] = load_unit(rsA, g.pitchA, g.RA, row0 + r, f_k + lks * KSTEP, ke);
                 // (narrow: the threads of rows 64 .. 127 of the pass have no unit of B: row -1)
                 if (i < UNITS_B)
                     st.b[i] = load_unit(rsB, g.pitchB, g.RB, (!NARROW || r < TN) ? col0 + r : -1,
@@ -502,8 +481,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
         f_k += KS;
         if (f_k >= k_end) {
             f_k = k_begin;
-            if (f_pair && f_half == 0) f_half = 1;      // the image's other half, same column tile
-            else { f_half = 0; f_ct += gridDim.z; }
+            f_ct += gridDim.z;
         }
     };
     auto frag = [&](const uint8_t(*lds)[LDP], int base_row, int ks) -> v4i {
@@ -1016,168 +994,6 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
 #pragma unroll
                     for (int r = 0; r < 16; ++r) total[a][c][r] = (int)((uint32_t)total[a][c][r] - corr);
         }
-        if constexpr (PAIR) {
-            // ---- fold, pair mode (images of 256 pixels, one stage per tile): half 0 multiplied out
-            // of buffer 0 and half 1 out of buffer 1, so the image's 256 pixel rows of accumulators
-            // (int16) lie in four quarters of 64 -- As[0], Bs[0] (half 0, written while half 1
-            // still needs the buffers 1), As[1], Bs[1] (half 1) -- and are folded after the second
-            // half.  Offsets in int16 from the start of As.
-            constexpr int AP = 130;      // pitch in int16 (65 dwords: neighbouring pixels, neighbouring banks)
-            constexpr int kQuarter = 64 * AP;
-            static_assert(sizeof(As[0]) >= ((size_t)kQuarter + BN) * sizeof(int16_t) &&
-                          sizeof(Bs[0]) >= (size_t)kQuarter * sizeof(int16_t), "a quarter must fit one stage buffer");
-            int16_t* accP = reinterpret_cast<int16_t*>(&As[0][0][0]);
-            const int dB = (int)((reinterpret_cast<uintptr_t>(&Bs[0][0][0]) - reinterpret_cast<uintptr_t>(&As[0][0][0])) / 2);
-            constexpr int dBuf = (int)(sizeof(As[0]) / 2);
-            auto quarter = [&](int qi) { return (qi & 1) * dB + (qi >> 1) * dBuf; };
-            __syncthreads();             // every wave is done reading this half's operands
-            {
-                // (a wave's 64 rows are one quarter: wm = 0, 1; rr + 4 * (lane >> 5) < 64)
-                int16_t* dst = accP + quarter(2 * c_half + wm) + (4 * (lane >> 5)) * AP + lane_col;
-#pragma unroll
-                for (int a = 0; a < RS; ++a)
-#pragma unroll
-                    for (int c = 0; c < CS; ++c)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            const int rr = a * 32 + 8 * (r >> 2) + (r & 3);
-                            dst[rr * AP + c * 32] = (int16_t)(total[a][c][r] >> fin_shift);
-                            total[a][c][r] = 0;
-                        }
-            }
-            c_k = k_begin;
-            if (c_half == 0) {
-                // the words read for taps outside the image, behind the first quarter
-                if (tid < BN) accP[kQuarter + tid] = 0;
-                c_half = 1;              // (the barrier of the next stage orders these writes)
-                return;
-            }
-            c_half = 0;
-            __syncthreads();
-            const int W = g.fW, H = g.fH, kw = g.fkw, khw = g.fkh * g.fkw;
-            const int q = tid & 255;                         // pixel of the image
-            const int ry = q >> g.f_log2w, x = q & (W - 1);
-            int off[9];
-            int ty = 0, tx = 0;
-#pragma unroll
-            for (int t = 0; t < 9; ++t) {
-                const int ryp = ry - ty + f_ph, xp = x - tx + f_pw;
-                const bool ok = t < khw && ryp >= 0 && ryp < H && xp >= 0 && xp < W;
-                const int p = (ryp << g.f_log2w) + xp;
-                off[t] = ok ? quarter(p >> 6) + (p & 63) * AP + t : kQuarter;
-                if (++tx == kw) { tx = 0; ++ty; }
-            }
-            const int cbase = c_ct * g.f_cg;
-            // the thread's channels: c0, c0 + 2, ... below c_end; their outputs lie a whole image apart
-            const int c0 = tid >> 8, c_end = min(g.f_cg, g.fC - cbase);
-            const int64_t o0 = ((int64_t)blockIdx.y * g.fC + cbase + c0) * (H * W) + q;
-            const int64_t o_step = (int64_t)(NTHREADS / 256) * (H * W);
-            float* po = g.out + o0;
-            const float* pm = g.mask_src ? g.mask_src + o0 : nullptr;
-            const int16_t* col = accP + c0 * khw;
-            for (int c = c0; c < c_end; c += NTHREADS / 256) {
-                int sum = 0;
-#pragma unroll
-                for (int t = 0; t < 9; ++t) sum += col[off[t]];
-                float f = (float)sum * dq;
-                if (pm) { f = pm[0] > 0.0f ? f : 0.0f; pm += o_step; }
-                po[0] = f;
-                po += o_step;
-                col += (NTHREADS / 256) * khw;
-            }
-            __syncthreads();             // the next stage overwrites the buffers the sums were read from
-            c_ct += gridDim.z;
-            return;
-        }
-        if constexpr (FOLD) {
-            // ---- fold: the tile's accumulators go to LDS (int16: at most 255 tiles of +-128),
-            // then every thread adds up the kh*kw taps of its pixels and channels.  Both operand
-            // buffers are free here: the stages still to come are in registers.
-            constexpr int AP = 130;      // pitch in int16 (65 dwords: neighbouring pixels, neighbouring banks)
-            static_assert(sizeof(As) >= ((size_t)BM * AP + BN) * sizeof(int16_t), "accumulator tile must fit the A buffers");
-            int16_t* accT = reinterpret_cast<int16_t*>(&As[0][0][0]);
-            __syncthreads();             // every wave is done reading this stage's operands
-#pragma unroll
-            for (int a = 0; a < RS; ++a)
-#pragma unroll
-                for (int c = 0; c < CS; ++c)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int rr = a * 32 + 8 * (r >> 2) + (r & 3);
-                        const int v = total[a][c][r] >> fin_shift;
-                        total[a][c][r] = 0;
-                        accT[(lane_row + rr) * AP + lane_col + c * 32] = (int16_t)v;
-                    }
-            // the word behind the tile, read for taps outside the image; c * khw + BM * AP stays
-            // inside the A buffers for every channel of a column tile
-            if (tid < BN) accT[BM * AP + tid] = 0;
-            __syncthreads();
-            const int W = g.fW, H = g.fH, kw = g.fkw, khw = g.fkh * g.fkw;
-            const int q = tid & (BM - 1);                 // pixel of the tile
-            int il = 0, ry, rows_part, y;
-            int64_t b;
-            bool out_ok;
-            const int x = q & (W - 1);
-            if (g.f_imgs) {                               // whole images: q = (image, row, position)
-                il = q >> g.f_log2hw;
-                ry = (q & ((1 << g.f_log2hw) - 1)) >> g.f_log2w;
-                rows_part = H;
-                b = (int64_t)blockIdx.y * g.f_imgs + il;
-                y = ry;
-                out_ok = b < g.fbatch;
-            } else {                                      // a strip of one image, halo rows first and last
-                ry = q >> g.f_log2w;
-                rows_part = g.f_rows_c;
-                b = f_img;
-                y = f_y0 + ry;
-                out_ok = ry >= f_ph && ry < f_ph + g.f_rows_out && y < H;
-            }
-            const int cbase = c_ct * g.f_cg;
-            const int16_t* img_part = accT + (il << g.f_log2hw) * AP;      // (il = 0 in strip mode)
-            if (khw <= 9) {
-                // up to nine taps: where each one reads, worked out once for the pixel (a tap whose
-                // source pixel lies outside reads the zero word behind the tile), then three
-                // instructions per tap and channel
-                int off[9];
-                int ty = 0, tx = 0;
-#pragma unroll
-                for (int t = 0; t < 9; ++t) {
-                    const int ryp = ry - ty + f_ph, xp = x - tx + f_pw;
-                    const bool ok = t < khw && ryp >= 0 && ryp < rows_part && xp >= 0 && xp < W;
-                    off[t] = ok ? ((il << g.f_log2hw) + (ryp << g.f_log2w) + xp) * AP + t : BM * AP;
-                    if (++tx == kw) { tx = 0; ++ty; }
-                }
-                for (int c = tid / BM; c < g.f_cg; c += NTHREADS / BM) {
-                    if (!out_ok || cbase + c >= g.fC) continue;
-                    const int16_t* col = accT + c * khw;
-                    int sum = 0;
-#pragma unroll
-                    for (int t = 0; t < 9; ++t) sum += col[off[t]];
-                    const int64_t o = (((int64_t)b * g.fC + cbase + c) * H + y) * W + x;
-                    g.out[o] = (g.mask_src && !(g.mask_src[o] > 0.0f)) ? 0.0f : (float)sum * dq;
-                }
-            } else {
-                for (int c = tid / BM; c < g.f_cg; c += NTHREADS / BM) {
-                    if (!out_ok || cbase + c >= g.fC) continue;
-                    int sum = 0;
-                    for (int ty = 0; ty < g.fkh; ++ty) {
-                        const int ryp = ry - ty + f_ph;
-                        if (ryp < 0 || ryp >= rows_part) continue;
-                        for (int tx = 0; tx < kw; ++tx) {
-                            const int xp = x - tx + f_pw;
-                            if (xp < 0 || xp >= W) continue;
-                            sum += img_part[((ryp << g.f_log2w) + xp) * AP + c * khw + ty * kw + tx];
-                        }
-                    }
-                    const int64_t o = (((int64_t)b * g.fC + cbase + c) * H + y) * W + x;
-                    g.out[o] = (g.mask_src && !(g.mask_src[o] > 0.0f)) ? 0.0f : (float)sum * dq;
-                }
-            }
-            __syncthreads();             // the next stage overwrites the buffers the sums were read from
-            c_k = k_begin;
-            c_ct += gridDim.z;
-            return;
-        }
         // Element (a, c, r) of the lane lies at tile_off + (32a + 8(r/4) + r%4) RB + 32c
         // (uniform) + lane_off (per lane, 32 bits: RB <= 2^21 on this path).
         const int64_t col0 = (int64_t)c_ct * TN;
@@ -1322,8 +1138,8 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
     // it (one stage of 128 codes is 8 MFMAs per wave, about 0.5 us of matrix time per SIMD,
     // less than a trip to L2 under load), one stage ahead in the s = 64 instance, which has
     // no eight registers to spare at four waves per SIMD.
-    // (the fold epilogue needs the registers; with a byte per code a stage in flight is twice as many)
-    constexpr bool kDeep = !kPairs64 && !FOLD && !WIDE && !FLEX;
+    // (with a byte per code a stage in flight is twice as many registers)
+    constexpr bool kDeep = !kPairs64 && !WIDE && !FLEX;
     // EPI_CERT8_S32 has the loop of its given-up stages (see `stage`) in the instances for
     // outputs that stay in the caches.  Those for streamed outputs go on in the testing stage
     // with every flag down: with the second loop compiled in, their testing stage came out 14 %
@@ -1393,58 +1209,11 @@ bool sat16_path(const GemmArgs& g, GemmArgs* plan = nullptr)
 
 } // namespace
 
-// Geometries the fold epilogue takes: W a power of two up to 128; either whole images per
-// 128-pixel row tile (H*W a power of two up to 128) or strips of 128 / W image rows of which
-// kh - 1 are halo (recomputed by the neighbouring strips); odd windows of at most 128 taps.
-bool gemm_fold_plan(GemmArgs* g, int64_t batch, int C, int H, int W, int kh, int kw)
-{
-    auto pow2 = [](int v) { return v > 0 && (v & (v - 1)) == 0; };
-    auto log2i = [](int v) { int l = 0; while ((1 << l) < v) ++l; return l; };
-    if (batch < 1 || C < 1 || H < 1 || W < 1 || kh < 1 || kw < 1 || kh % 2 == 0 || kw % 2 == 0) return false;
-    if (!pow2(W) || W > BM || kh * kw > BN || kh > 15 || kw > 15) return false;
-    if (g->RA != batch * (int64_t)H * W || g->RB != (int64_t)C * kh * kw || g->D % KSTEP != 0) return false;
-    g->splits = 1;                        // short contractions; the fold needs whole totals
-    g->tiles_per_split = g->n_tiles;
-    if (batch * (int64_t)C * H * W >= ((int64_t)1 << 40)) return false;
-    g->fold = 1;
-    g->fbatch = batch; g->fC = C; g->fH = H; g->fW = W; g->fkh = kh; g->fkw = kw;
-    g->f_log2w = log2i(W);
-    g->f_cg = BN / (kh * kw);
-    const int64_t hw = (int64_t)H * W;
-    if (hw <= BM) {
-        if (!pow2((int)hw)) return false;
-        g->f_imgs = BM / (int)hw;
-        g->f_log2hw = log2i((int)hw);
-        g->f_rows_c = H; g->f_rows_out = H; g->f_strips = 1;
-    } else if (hw == 2 * BM && kh * kw <= 9 && kh * kw > 1 && g->D <= KS_LONG && batch <= 65535) {
-        // an image is two row tiles and a tile one stage: both halves in one workgroup, no halo
-        g->f_pair = 1;
-        g->f_imgs = 0;
-        g->f_log2hw = 8;
-        g->f_rows_c = H; g->f_rows_out = H; g->f_strips = 1;
-    } else {
-        g->f_imgs = 0;
-        g->f_log2hw = 7;                  // unused: one image part per tile
-        g->f_rows_c = BM / W;
-        g->f_rows_out = g->f_rows_c - (kh - 1);
-        if (g->f_rows_out < 1) return false;
-        g->f_strips = (H + g->f_rows_out - 1) / g->f_rows_out;
-        if (batch * g->f_strips > 65535) return false;      // grid.y
-    }
-    if (g->f_imgs && (batch + g->f_imgs - 1) / g->f_imgs > 65535) return false;
-    // int16 accumulator tile: |total| <= tiles * min(2^(a-1), what a tile's products can add up to)
-    const int64_t tile_sum = g->s * (((int64_t)1 << (g->bA - 1)) * ((int64_t)1 << (g->bB - 1)));
-    const int64_t per_tile = tile_sum < (int64_t)g->acc_hi + 1 ? tile_sum : (int64_t)g->acc_hi + 1;
-    if (per_tile > 32767 || per_tile * g->n_tiles > 32767) return false;
-    return gemm_fast_eligible(*g);
-}
-
 bool gemm_fast_eligible(const GemmArgs& g)
 {
     if ((g.bA > 4) != (g.bB > 4)) return false;      // packed or bytes, the same on both sides
     // a row may end inside a 32-code unit, whose remainder the kernel clears; rows that are no
     // whole dwords, and outputs an epilogue has no instance for, take the FLEX ones
-    if (g.fold && g.D % KSTEP != 0) return false;
     if (g.RB > ((int64_t)1 << 21)) return false;     // 32-bit offsets inside an output tile
     // 32-bit offsets into the operands, with room for the "outside" offset
     if ((g.RA + 256) * g.pitchA >= ((int64_t)1 << 31) || (g.RB + 256) * g.pitchB >= ((int64_t)1 << 31)) return false;
@@ -1478,7 +1247,7 @@ bool gemm_fast_eligible(const GemmArgs& g)
     return per_tile * g.tiles_per_split < ((int64_t)1 << 22);
 }
 
-// Whether the kernel applies g.mask_src itself: the fold epilogue, and the instances of the
+// Whether the kernel applies g.mask_src itself: the instances of the
 // packed-code epilogues HDQT_LAUNCH_I4 covers with a whole, unsplit output.  Everything else
 // is masked by a pass of its own after the matmul (or by the pass that adds a split
 // contraction's slices).
@@ -1566,7 +1335,7 @@ hipError_t launch_gemm_requant_fast(const GemmArgs& g_in, int acc_bits, int pass
     const dim3 grid((unsigned)g.splits, (unsigned)n_rt, (unsigned)gx), block(64 * kWaves);
     ProfileScope ps(pass == 1 ? K_REQUANT_TILES : K_REQUANT_SUM, stream);
 #define HDQT_LAUNCH_REQ(EPI, STREAM) \
-    hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, STREAM, kWaves, false, false>), grid, block, 0, stream, g)
+    hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, STREAM, kWaves, false>), grid, block, 0, stream, g)
     const bool s32 = g.s == KSTEP;
     if (pass == 1) {
         if (s32) HDQT_LAUNCH_REQ(EPI_REQ_MAX_S32, false);
@@ -1595,13 +1364,9 @@ hipError_t launch_gemm_fast(const GemmArgs& g_in, hipStream_t stream)
     const bool narrow = !flex && narrow_tiles(g);
     int64_t n_ct = (g.RB + BN - 1) / BN, n_rt = (g.RA + BM - 1) / BM;
     if (narrow) n_ct = (g.RB + 63) / 64;
-    if (g.fold) {
-        n_ct = (g.fC + g.f_cg - 1) / g.f_cg;
-        n_rt = g.f_imgs ? (g.fbatch + g.f_imgs - 1) / g.f_imgs : g.fbatch * g.f_strips;      // (pair mode: images)
-    }
     const bool s32 = sat8_path(g) && g.s == 32;
     const bool sat16 = sat16_path(g, &g);
-    const bool masked = gemm_fast_masks(g) && !g.fold;
+    const bool masked = gemm_fast_masks(g);
     const int64_t KS = KS_LONG;
     const int64_t stages = (g.tiles_per_split * g.s + KS - 1) / KS;
     int64_t gx = n_ct;
@@ -1616,32 +1381,28 @@ hipError_t launch_gemm_fast(const GemmArgs& g_in, hipStream_t stream)
     do {                                                                                             \
         const dim3 block(64 * kWaves);                                                               \
         if (masked) {                                                                                \
-            if (g.stream_out) hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, true, kWaves, false, false, false, false, true>), grid, block, 0, stream, g); \
-            else hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, false, kWaves, false, false, false, false, true>), grid, block, 0, stream, g); \
-        } else if (g.fold && g.f_pair)                                                               \
-            hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, false, kWaves, false, true, false, false, false, true>), grid, block, 0, stream, g); \
-        else if (g.fold)                                                                             \
-            hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, false, kWaves, false, true>), grid, block, 0, stream, g); \
-        else if (narrow) {                                                                           \
             if (g.stream_out) hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, true, kWaves, false, false, false, true>), grid, block, 0, stream, g); \
             else hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, false, kWaves, false, false, false, true>), grid, block, 0, stream, g); \
+        } else if (narrow) {                                                                           \
+            if (g.stream_out) hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, true, kWaves, false, false, true>), grid, block, 0, stream, g); \
+            else hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, false, kWaves, false, false, true>), grid, block, 0, stream, g); \
         } else if (g.out_bf16) {                                                                     \
-            if (g.stream_out) hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, true, kWaves, true, false>), grid, block, 0, stream, g); \
-            else hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, false, kWaves, true, false>), grid, block, 0, stream, g); \
+            if (g.stream_out) hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, true, kWaves, true>), grid, block, 0, stream, g); \
+            else hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, false, kWaves, true>), grid, block, 0, stream, g); \
         } else if (g.stream_out)                                                                     \
-            hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, true, kWaves, false, false>), grid, block, 0, stream, g); \
+            hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, true, kWaves, false>), grid, block, 0, stream, g); \
         else                                                                                         \
-            hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, false, kWaves, false, false>), grid, block, 0, stream, g); \
+            hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, false, kWaves, false>), grid, block, 0, stream, g); \
     } while (0)
 #define HDQT_LAUNCH_SAT16(EPI, WIDE)                                                                  \
     do {                                                                                             \
         const dim3 block(64 * kWaves);                                                               \
-        if (g.stream_out) hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, true, kWaves, false, false, WIDE>), grid, block, 0, stream, g); \
-        else hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, false, kWaves, false, false, WIDE>), grid, block, 0, stream, g); \
+        if (g.stream_out) hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, true, kWaves, false, WIDE>), grid, block, 0, stream, g); \
+        else hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, false, kWaves, false, WIDE>), grid, block, 0, stream, g); \
     } while (0)
     if (flex) {
 #define HDQT_LAUNCH_FLEX(EPI, WIDE)                                                                   \
-    hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, false, kWaves, false, false, WIDE, false, false, false, true>), \
+    hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, false, kWaves, false, WIDE, false, false, true>), \
                        grid, dim3(64 * kWaves), 0, stream, g)
 #define HDQT_LAUNCH_FLEX2(EPI) do { if (wide) HDQT_LAUNCH_FLEX(EPI, true); else HDQT_LAUNCH_FLEX(EPI, false); } while (0)
         if (g.s == 16) {
@@ -1673,18 +1434,18 @@ hipError_t launch_gemm_fast(const GemmArgs& g_in, hipStream_t stream)
     } else if (wide) {
         const dim3 block(64 * kWaves);
         if (g.s % KS_LONG == 0) {
-            if (g.stream_out) hipLaunchKernelGGL((gemm_i4_kernel<EPI_STAGES, KS_LONG, true, kWaves, false, false, true>), grid, block, 0, stream, g);
-            else hipLaunchKernelGGL((gemm_i4_kernel<EPI_STAGES, KS_LONG, false, kWaves, false, false, true>), grid, block, 0, stream, g);
+            if (g.stream_out) hipLaunchKernelGGL((gemm_i4_kernel<EPI_STAGES, KS_LONG, true, kWaves, false, true>), grid, block, 0, stream, g);
+            else hipLaunchKernelGGL((gemm_i4_kernel<EPI_STAGES, KS_LONG, false, kWaves, false, true>), grid, block, 0, stream, g);
         } else {
-            if (g.stream_out) hipLaunchKernelGGL((gemm_i4_kernel<EPI_GENERIC, KS_LONG, true, kWaves, false, false, true>), grid, block, 0, stream, g);
-            else hipLaunchKernelGGL((gemm_i4_kernel<EPI_GENERIC, KS_LONG, false, kWaves, false, false, true>), grid, block, 0, stream, g);
+            if (g.stream_out) hipLaunchKernelGGL((gemm_i4_kernel<EPI_GENERIC, KS_LONG, true, kWaves, false, true>), grid, block, 0, stream, g);
+            else hipLaunchKernelGGL((gemm_i4_kernel<EPI_GENERIC, KS_LONG, false, kWaves, false, true>), grid, block, 0, stream, g);
         }
     } else if (s32 && !masked && !narrow && cert_tiles(g, n_ct)) {
         const dim3 block(64 * kWaves);
         if (g.stream_out)
-            hipLaunchKernelGGL((gemm_i4_kernel<EPI_CERT8_S32, KS_LONG, true, kWaves, false, false>), grid, block, 0, stream, g);
+            hipLaunchKernelGGL((gemm_i4_kernel<EPI_CERT8_S32, KS_LONG, true, kWaves, false>), grid, block, 0, stream, g);
         else
-            hipLaunchKernelGGL((gemm_i4_kernel<EPI_CERT8_S32, KS_LONG, false, kWaves, false, false>), grid, block, 0, stream, g);
+            hipLaunchKernelGGL((gemm_i4_kernel<EPI_CERT8_S32, KS_LONG, false, kWaves, false>), grid, block, 0, stream, g);
     } else if (s32) HDQT_LAUNCH_I4(EPI_SAT8_S32);
     else if (sat8_path(g)) HDQT_LAUNCH_I4(EPI_SAT8_S64);
     else if (g.s % KS_LONG == 0) HDQT_LAUNCH_I4(EPI_STAGES);
