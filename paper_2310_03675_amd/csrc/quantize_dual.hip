@@ -79,7 +79,7 @@ __device__ __forceinline__ void tile_load(Tile& t, const DualArgs& q, const Dual
 // with coalesced reads, then gathers its 64 x 64 values from there: an element's patch
 // address is (row part of its pixel) + (column part of its channel and tap).
 // The activation is read from HBM about once per pass instead of kh*kw times.
-constexpr int kPatchUnroll = 32;
+constexpr int kPatchUnroll = 6;
 
 __device__ __forceinline__ void tile_load_conv(Tile& t, const DualArgs& q, const DualCtx& x,
                                                int64_t row0, int64_t col0, float* patch, int lane)
@@ -97,43 +97,63 @@ __device__ __forceinline__ void tile_load_conv(Tile& t, const DualArgs& q, const
     const int y_first = (int)(rem / (uint32_t)W), x_first = (int)(rem - (uint32_t)y_first * (uint32_t)W);
     const int c_lo = (int)(k0 / (uint32_t)khw);
 
-    // ---- patch: row q = (channel c_lo + q / PH, image row y_first - ph + q % PH).  Rows of up
-    // to 32 words go two per step (32 lanes each).  What costs here is the number of load
-    // round trips, not the instructions: kPatchUnroll steps issue their loads together
-    // (every address is clamped into the activation, so no load is conditional), then store.
-    // (One row per step with scalar row arithmetic halves the vector instructions and is
-    // 35 % slower: twice the round trips.)
-    const bool two = PW <= 32;
-    const int lpr = two ? 32 : 64, rpi = two ? 2 : 1;
-    const int lrow = two ? (lane >> 5) : 0, lx = lane & (lpr - 1);
+    // ---- patch: row r = (channel c_lo + r / PH, image row y_first - ph + r % PH).  The tile's own
+    // columns are whole image rows, or 64 pixels from a multiple of 64 on: four pixels per lane and
+    // load, kPatchUnroll loads in flight (every address is clamped into the activation, so no load
+    // is conditional).  (One pixel per lane and load cost 64 times the twelve instructions of its
+    // address and border test, a third of the kernel: 262144 x 576 from 256 x 64 x 32 x 32, pass 1
+    // 143 -> 91 us, pass 2 180 -> 135 us.)
+    const int wt = W < kTile ? W : kTile;
     const int rows_total = CN * PH;
-    const int steps = (rows_total + rpi - 1) / rpi;
     const float* img = q.T + (int64_t)b * C * H * W;
-    for (int ch = 0; ch * lpr < PW; ++ch) {
-        const int pxx = ch * lpr + lx;
-        const int gx = x_first - pw + pxx;
-        const bool col_ok = pxx < PW && gx >= 0 && gx < W;
-        const int gxc = gx < 0 ? 0 : (gx >= W ? W - 1 : gx);
-        int c_rel = 0, pyy = lrow;
-        while (pyy >= PH) { pyy -= PH; ++c_rel; }
-        for (int it0 = 0; it0 < steps; it0 += kPatchUnroll) {
-            float v[kPatchUnroll];
-            bool keep[kPatchUnroll];
+    // (r / PH for r below 2^20 / PH: dual_conv_plan)
+    const uint32_t inv_ph = ((1u << 20) + (uint32_t)PH - 1) / (uint32_t)PH;
+    auto source = [&](int r, int& off) {          // whether row r lies in the activation, and where
+        const int c_rel = (int)(((uint32_t)r * inv_ph) >> 20);
+        const int gy = y_first - ph + r - c_rel * PH, c = c_lo + c_rel;
+        const int gyc = gy < 0 ? 0 : (gy >= H ? H - 1 : gy), cc = c >= C ? C - 1 : c;
+        off = (cc * H + gyc) * W;
+        return gy == gyc && c < C;
+    };
+    if (wt >= 4) {
+        const int log2u = 29 - __builtin_clz((unsigned)wt);      // (wt is a power of two) units of four pixels per row
+        const int units = rows_total << log2u;
+        for (int u0 = 0; u0 < units; u0 += 64 * kPatchUnroll) {
+            float4 v[kPatchUnroll];
+            int dst[kPatchUnroll];
 #pragma unroll
-            for (int u = 0; u < kPatchUnroll; ++u) {
-                const int gy = y_first - ph + pyy, c = c_lo + c_rel;
-                const int gyc = gy < 0 ? 0 : (gy >= H ? H - 1 : gy);
-                const int cc = c >= C ? C - 1 : c;
-                v[u] = img[(cc * H + gyc) * W + gxc];
-                keep[u] = col_ok && gy >= 0 && gy < H && c < C;
-                pyy += rpi;
-                while (pyy >= PH) { pyy -= PH; ++c_rel; }
+            for (int k = 0; k < kPatchUnroll; ++k) {
+                const int u = u0 + 64 * k + lane, r = u >> log2u, xq = (u - (r << log2u)) * 4;
+                int off;
+                const bool in = source(r, off);
+                v[k] = *reinterpret_cast<const float4*>(img + off + x_first + xq);
+                if (!in) v[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                dst[k] = u < units ? r * PW + pw + xq : -1;
             }
 #pragma unroll
-            for (int u = 0; u < kPatchUnroll; ++u) {
-                const int qrow = (it0 + u) * rpi + lrow;
-                if (pxx < PW && qrow < rows_total) patch[qrow * PW + pxx] = keep[u] ? v[u] : 0.0f;
+            for (int k = 0; k < kPatchUnroll; ++k) {
+                if (dst[k] < 0) continue;
+                float* d = patch + dst[k];
+                d[0] = v[k].x; d[1] = v[k].y; d[2] = v[k].z; d[3] = v[k].w;
             }
+        }
+    }
+    // ---- the window's columns beside them (all columns of images one or two pixels wide): zeros
+    // next to a whole image row, else pixels one by one
+    const int n_side = wt >= 4 ? kw - 1 : PW;
+    if (n_side) {
+        const uint32_t inv_ns = ((1u << 20) + (uint32_t)n_side - 1) / (uint32_t)n_side;
+        for (int e = lane; e < rows_total * n_side; e += 64) {
+            const int r = (int)(((uint32_t)e * inv_ns) >> 20), k = e - r * n_side;
+            const int px = wt >= 4 && k >= pw ? wt + k : k, gx = x_first - pw + px;
+            float v = 0.0f;
+            if (gx >= 0 && gx < W) {
+                int off;
+                const bool in = source(r, off);
+                v = img[off + gx];
+                if (!in) v = 0.0f;
+            }
+            patch[r * PW + px] = v;
         }
     }
     // ---- column parts of the tile's 64 columns, one per lane
