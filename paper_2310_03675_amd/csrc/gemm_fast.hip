@@ -60,7 +60,7 @@ constexpr int kScaleShift = 8;        // both operands carry a factor 16
 enum Epilogue { EPI_GENERIC = 0, EPI_SAT8_S32 = 1, EPI_SAT8_S64 = 2, EPI_STAGES = 3, EPI_SAT16_S32 = 4,
                 EPI_SAT16_S64 = 5, EPI_SAT8_S16 = 6, EPI_SAT16_S16 = 7, EPI_CLAMP_S16 = 8,
                 EPI_REQ_MAX = 9, EPI_REQ_SUM = 10, EPI_REQ_MAX_S32 = 11, EPI_REQ_SUM_S32 = 12,
-                EPI_CERT8_S32 = 13, EPI_CERT16_S32 = 14 };
+                EPI_CERT8_S32 = 13, EPI_CERT16_S32 = 14, EPI_CLAMP_S64 = 15 };
 // EPI_CERT8_S32: 8-bit accumulators, tiles of 32 packed 4-bit codes, as EPI_SAT8_S32 -- but a
 // tile whose sums provably stay inside the accumulator is not clamped at all.  The proof is
 // the Cauchy-Schwarz bound: |sum_k a_k b_k| <= sqrt(sum a_k^2 * sum b_k^2), so with nA the largest
@@ -99,6 +99,8 @@ constexpr int kReqTable = 512;         // tiles of one part of the contraction (
 constexpr float kReqMagic = 12582912.0f;   // 1.5 * 2^23
 // EPI_CLAMP_S16: tiles of 16 codes with the compare-select clamp, for the accumulator widths
 // neither conversion trick covers (fewer bits than bA + bB).
+// EPI_CLAMP_S64: the same for tiles of 64 bytes (their tile ends known at compile time, as those of
+// the other _S64 instances: the generic loop tests after every step).
 // The _S16 instances (tiles of 16 codes) split every 32-code step into two
 // v_mfma_i32_32x32x16_i8: the 16-byte LDS fragment of a lane already holds, in its low and
 // high halves, what that instruction wants from the lane for the first and the second tile
@@ -129,10 +131,11 @@ struct Staged {
 typedef unsigned int u4v __attribute__((ext_vector_type(4)));
 constexpr uint32_t kOutside = 0x80000000u;      // operands are smaller than 2 GiB (gemm_fast_eligible)
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t operand_rsrc(const uint8_t* q, int64_t bytes)
+// (FLEX reads whole dwords, up to the end of the last one: the base is 16-byte aligned, so that is
+// the same page)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t operand_rsrc(const uint8_t* q, int64_t bytes, bool flex = false)
 {
-    // (up to the end of the last dword: the base is 16-byte aligned, so that is the same page)
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(q), 0, (int)((bytes + 3) & ~(int64_t)3), 0x00020000);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(q), 0, (int)(flex ? (bytes + 3) & ~(int64_t)3 : bytes), 0x00020000);
 }
 
 __device__ __forceinline__ uint4 load_unit(__amdgpu_buffer_rsrc_t rs, int64_t pitch, int64_t R, int64_t row,
@@ -348,7 +351,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
     constexpr bool kSat8 = (EPI == EPI_SAT8_S32 || EPI == EPI_SAT8_S64 || EPI == EPI_SAT8_S16);
     constexpr bool kPairs16 = (EPI == EPI_SAT8_S16 || EPI == EPI_SAT16_S16 || EPI == EPI_CLAMP_S16);      // pairs of 16-code tiles
     constexpr bool kPairs32 = (EPI == EPI_SAT8_S32 || EPI == EPI_SAT16_S32);      // pairs of 32-code tiles
-    constexpr bool kPairs64 = (EPI == EPI_SAT8_S64 || EPI == EPI_SAT16_S64);      // pairs of 64-code tiles
+    constexpr bool kPairs64 = (EPI == EPI_SAT8_S64 || EPI == EPI_SAT16_S64 || EPI == EPI_CLAMP_S64);      // pairs of 64-code tiles
     static_assert(!WIDE || !kSat8, "the 8-bit clamp trick needs the factor 256 of the nibble unpack");
     constexpr int SHIFT = WIDE ? 0 : kScaleShift;      // factor the totals carry, as a shift
     // factor left in a finished total, as a shift: none after the 8-bit trick
@@ -445,7 +448,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
 
     const uint32_t phaseA = FLEX ? ((uint32_t)lrow * (uint32_t)g.pitchA) & 3u : 0u;
     const uint32_t phaseB = FLEX ? ((uint32_t)lrow * (uint32_t)g.pitchB) & 3u : 0u;
-    const __amdgpu_buffer_rsrc_t rsA = operand_rsrc(g.qA, g.RA * g.pitchA), rsB = operand_rsrc(g.qB, g.RB * g.pitchB);
+    const __amdgpu_buffer_rsrc_t rsA = operand_rsrc(g.qA, g.RA * g.pitchA, FLEX), rsB = operand_rsrc(g.qB, g.RB * g.pitchB, FLEX);
 
     // ---- the load stream: position of the next stage to fetch
     int f_ct = blockIdx.z;
@@ -799,17 +802,36 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
             for (int pr = 0; pr < (kPairs32 ? NSTEP / 2 : 1); ++pr) {
                 constexpr int SPT = kPairs32 ? 1 : 2;      // steps per tile
                 v4i fa[2 * SPT][RS], fb[2 * SPT][CS];
+                // LEAN (pairs of 64-code tiles in the instances with two registers more per unit in
+                // flight, which spilled 8 to 20 of them): a block's fragments are read when its turn
+                // comes, not all at once -- of A, or of B where the wave is one block high
+                constexpr bool LEAN = kPairs64 && (FLEX || WIDE);
+                auto read_a = [&](const int h) {
 #pragma unroll
-                for (int q = 0; q < 2 * SPT; ++q)
+                    for (int q = 0; q < 2 * SPT; ++q) fa[q][h] = frag(As[buf], wm * WROWS + h * 32, pr * 2 * SPT + q);
+                };
+                auto read_b = [&](const int h) {
 #pragma unroll
-                    for (int h = 0; h < HS; ++h) {
-                        if (h < RS) fa[q][h] = frag(As[buf], wm * WROWS + h * 32, pr * 2 * SPT + q);
-                        if (h < CS) fb[q][h] = frag(Bs[buf], wn * WCOLS + h * 32, pr * 2 * SPT + q);
-                    }
+                    for (int q = 0; q < 2 * SPT; ++q) fb[q][h] = frag(Bs[buf], wn * WCOLS + h * 32, pr * 2 * SPT + q);
+                };
+                if constexpr (!LEAN) {
+#pragma unroll
+                    for (int q = 0; q < 2 * SPT; ++q)
+#pragma unroll
+                        for (int h = 0; h < HS; ++h) {
+                            if (h < RS) fa[q][h] = frag(As[buf], wm * WROWS + h * 32, pr * 2 * SPT + q);
+                            if (h < CS) fb[q][h] = frag(Bs[buf], wn * WCOLS + h * 32, pr * 2 * SPT + q);
+                        }
+                }
 #pragma unroll
                 for (int a = 0; a < RS; ++a)
 #pragma unroll
                     for (int c = 0; c < CS; ++c) {
+                        if constexpr (LEAN) {
+                            if (a + c) __builtin_amdgcn_sched_barrier(0);
+                            if (c == 0) read_a(a);
+                            if (a == 0) read_b(c);
+                        }
                         v16i p0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[0][a], fb[0][c], zero, 0, 0, 0);
                         if (SPT == 2)
                             p0 = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[1][a], fb[1][c], p0, 0, 0, 0);
@@ -817,9 +839,13 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
                         if (SPT == 2)
                             p1 = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[SPT + 1][a], fb[SPT + 1][c], p1, 0, 0, 0);
 #pragma unroll
-                        for (int r = 0; r < 16; ++r)
-                            total[a][c][r] = kSat16 ? add_sat16_pair(total[a][c][r], p0[r], p1[r], low_clear)
-                                                    : add_sat8_pair(total[a][c][r], p0[r], p1[r]);
+                        for (int r = 0; r < 16; ++r) {
+                            if constexpr (EPI == EPI_CLAMP_S64)
+                                total[a][c][r] += clamp3(p0[r], lo, hi) + clamp3(p1[r], lo, hi);
+                            else
+                                total[a][c][r] = kSat16 ? add_sat16_pair(total[a][c][r], p0[r], p1[r], low_clear)
+                                                        : add_sat8_pair(total[a][c][r], p0[r], p1[r]);
+                        }
                     }
             }
         } else if (kReq) {
@@ -1415,7 +1441,8 @@ hipError_t launch_gemm_fast(const GemmArgs& g_in, hipStream_t stream)
         } else if (!wide && sat8_path(g)) {
             if (g.s == 32) HDQT_LAUNCH_FLEX(EPI_SAT8_S32, false);
             else HDQT_LAUNCH_FLEX(EPI_SAT8_S64, false);
-        } else if (g.s % KS_LONG == 0) HDQT_LAUNCH_FLEX2(EPI_STAGES);
+        } else if (wide && g.s == 64) HDQT_LAUNCH_FLEX(EPI_CLAMP_S64, true);
+        else if (g.s % KS_LONG == 0) HDQT_LAUNCH_FLEX2(EPI_STAGES);
         else HDQT_LAUNCH_FLEX2(EPI_GENERIC);
 #undef HDQT_LAUNCH_FLEX2
 #undef HDQT_LAUNCH_FLEX
@@ -1431,6 +1458,8 @@ hipError_t launch_gemm_fast(const GemmArgs& g_in, hipStream_t stream)
         else if (g.s == 32 && cert16_tiles(g)) HDQT_LAUNCH_SAT16(EPI_CERT16_S32, false);
         else if (g.s == 32) HDQT_LAUNCH_SAT16(EPI_SAT16_S32, false);
         else HDQT_LAUNCH_SAT16(EPI_SAT16_S64, false);
+    } else if (wide && g.s == 64) {
+        HDQT_LAUNCH_SAT16(EPI_CLAMP_S64, true);
     } else if (wide) {
         const dim3 block(64 * kWaves);
         if (g.s % KS_LONG == 0) {

@@ -9,7 +9,7 @@ from test_gpu_parity import check_gemm_codes
 pytestmark = pytest.mark.gpu
 
 PACKED = ((32, 8), (64, 8), (16, 8), (32, 12), (16, 9), (16, 6), (96, 32), (128, 16), (256, 16), (8192, 32))
-BYTES = ((32, 16), (64, 16), (16, 16), (16, 12), (96, 32), (32, 12), (256, 16))
+BYTES = ((32, 16), (64, 16), (64, 12), (64, 8), (16, 16), (16, 12), (96, 32), (32, 12), (256, 16))
 
 
 def both_kinds(RA, RB, D, extreme):
@@ -40,3 +40,9 @@ def test_long_contractions_on_large_tiles(D):
 @pytest.mark.parametrize("D", [27, 64, 100, 129, 520])
 def test_many_blocks_on_large_tiles(D):
     both_kinds(1100, 1000, D, 0.2)
+
+
+def test_tiles_of_64_bytes_streamed_output():
+    """Outputs of 128 MB take the instances with streaming stores, whose waves are one block high."""
+    for a in (8, 16):
+        check_gemm_codes(8200, 4100, 192, 8, 8, 64, a, extreme=0.3)
