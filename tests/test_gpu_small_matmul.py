@@ -42,6 +42,12 @@ def test_many_blocks_on_large_tiles(D):
     both_kinds(1100, 1000, D, 0.2)
 
 
+@pytest.mark.parametrize("RB,D", [(37, 27), (64, 27), (64, 100), (50, 37), (64, 561)])
+def test_narrow_outputs_with_ragged_rows(RB, D):
+    for s, a in ((32, 8), (64, 8), (128, 16), (96, 32), (32, 32)):
+        check_gemm_codes(17000, RB, D, 4, 4, s, a, extreme=0.3)
+
+
 def test_tiles_of_64_bytes_streamed_output():
     """Outputs of 128 MB take the instances with streaming stores, whose waves are one block high."""
     for a in (8, 16):
