@@ -223,11 +223,19 @@ hdqt::QuantArgs half_of(const hdqt::DualArgs& d, int axis)
     return q;
 }
 
-// Elements (over all pairs) up to which a whole set goes to the any-shape kernel.
-constexpr int64_t kAnySet = (int64_t)1 << 20;
-// Elements up to which a pair that a tuned kernel would take joins the any-shape pairs of the set:
-// it saves the two launches of its own.
-constexpr int64_t kAnyPair = (int64_t)1 << 20;
+// Where the any-shape kernel is the faster one (us of whole calls, the tuned kernels first):
+// Elements, over all pairs, up to which a whole set goes to it: a 512 x 512 x 512 step 27.4 / 20.5,
+// 1024 x 1024 x 512 39.1 / 34.2; 2048 x 1152 x 128 (5.5 M) 35.4 / 36.8, 8192 x 1152 x 128 70.1 / 84.4.
+constexpr int64_t kAnySet = (int64_t)1 << 22;
+// Elements up to which a pair that has a tuned single-axis kernel joins the any-shape pairs of the
+// set, which saves the two launches of its own: G of a 131072 x 27 x 64 step (8.4 M) 86.5 / 80.1,
+// of 8192 x 1000 x 300 142.8 / 119.4; X of 2048 x 4608 x 512 at order 256 (9.4 M) 154.0 / 163.1.
+constexpr int64_t kAnyPair = (int64_t)1 << 23;
+// Elements up to which a tensor rounded stochastically on both axes leaves the two-axis kernel's
+// launch of a layer's tensors (64 values of two random streams a lane: its few waves end last) for
+// the any-shape workgroups beside it: G of 2048 x 4608 x 512 (1 M) 110.7 / 105.1, of 2048 x 1152 x 128
+// 35.9 / 31.8; of 16384 x 1152 x 128 (2.1 M) 105.9 / 123.0.
+constexpr int64_t kAnyStochastic = (int64_t)1 << 20;
 
 // Quantizes a set: one launch per pass for all tensors that the two-axis and the any-shape kernel
 // take (two for pass 2 where the rounding modes do not go together), two launches per large tensor
@@ -249,7 +257,8 @@ int run_quantize_set(const QuantSet& s, void* records, size_t record_bytes, hipS
     };
     for (int k = 0; k < s.n_both; ++k) {
         const hdqt::DualArgs& d = s.both[k];
-        if (d.conv || (!small && hdqt::quantize_dual_eligible(d))) {
+        const bool leaves = s.n_both > 1 && d.st_row && d.st_col && d.rows * d.cols <= kAnyStochastic;
+        if (d.conv || (!small && !leaves && hdqt::quantize_dual_eligible(d))) {
             dual[n_dual++] = d;
         } else {
             place(half_of(d, 1));
