@@ -6,7 +6,7 @@
 // What bounds these products is a chain, not a rate: with 128 x 128 tiles a layer of 128 x 561 x 561
 // has five workgroups, each of whose SIMDs multiplies, clamps and adds 18 steps of 8 blocks one
 // after the other (11 us), and a split contraction adds a launch.  Here a workgroup owns one
-// block of 32 x 32 outputs and its waves share the contraction between them, whole tiles
+// block of 32 x 32 outputs and its four waves share the contraction between them, whole tiles
 // each; the totals meet in LDS, so that nothing is left for a second launch.  The operands go
 // from memory straight to the registers the matrix core reads (a lane's 16 codes of a step are
 // eight consecutive bytes), four steps ahead of the multiplication and without a barrier.  Every
@@ -28,7 +28,8 @@ typedef int v16i __attribute__((ext_vector_type(16)));
 typedef short v2s __attribute__((ext_vector_type(2)));
 
 constexpr int kStep = 32;            // codes per MFMA
-constexpr int kWaves = 8;            // waves of a workgroup
+constexpr int kWaves = 4;            // waves of a workgroup (eight: 2947 x 561 x 561 17.3 us instead of 13.7,
+                                     // 4096 x 512 x 256 15.0 / 10.0, long contractions the same)
 
 // MODE_TILES: tiles of whole steps, compare-select clamp.  MODE_SAT8: tiles of one step, 8-bit
 // accumulators, packed codes: two tile sums per saturating conversion, added by one dot product
@@ -279,19 +280,24 @@ int mode_of(const GemmArgs& g)
 }
 
 // The products this kernel is the faster one for.  Measured on codes alone, the large tiles'
-// kernel (with the sum over a split contraction's parts) against this one, 4-bit codes, tiles of
-// 32: 128 x 561 x 561 (rows x columns x contraction) 13.7 / 7.4 us, 7.4 being what any call costs;
-// 1024 x 256 x 1024 14.6 / 7.5; 8192 x 128 x 1152 23.6 / 10.7; 512 x 512 x 4608 24.0 / 12.5.  Beyond:
-// 1152 x 128 x 8192 16.5 / 18.0 (a wave's chain of steps is too long), 2048 x 512 x 4608 28.7 / 38.3
-// (too many steps in all: the operands come from L2 once per 32 rows), 131072 x 64 x 27 26.7 / 40.3
-// (too many workgroups with one step each).  Between 512 and 1024 blocks it wins only where the
-// other one splits the contraction: 2048 x 512 x 512 15.8 / 8.9 with tiles of 32 (split), 8.2 / 9.9
-// with tiles of 64 (not split).
+// kernel (with the sum over a split contraction's parts) against this one, 4-bit codes in tiles of 32
+// unless said otherwise, 7.5 us being what any call costs: 128 x 561 x 561 (rows x columns x
+// contraction) 14.6 / 7.9; 1024 x 256 x 1024 14.6 / 8.0; 512 x 512 x 4608 23.7 / 12.5; 8192 x 256 x 1152
+// 27.0 / 19.8; 8192 x 128 x 1152 23.7 / 11.4, with a byte per code 23.3 / 21.4, in tiles of 16 25.0 / 20.9.
+// The lines: a wave's chain of steps (1152 x 128 x 8192 16.5 / 18.6); the steps in all, of which
+// those of bytes and of tiles of 16 cost twice as much (8192 x 256 x 1152, byte codes, 27.1 / 38.6);
+// the number of workgroups (65536 x 64 x 27 8.0 / 14.6).  Where the other kernel does not split the
+// contraction it is ahead earlier (4096 x 512 x 256 8.0 / 10.0), except for ragged rows
+// (2947 x 561 x 561 16.7 / 13.7, 4096 x 256 x 561 19.6 / 9.1; but 32768 x 64 x 27 7.8 / 8.7).
 bool small_enough(const GemmArgs& g)
 {
+    const bool wide = g.bA > 4;
     const int64_t blocks = ((g.RA + 31) / 32) * ((g.RB + 31) / 32), steps = (g.D + kStep - 1) / kStep;
-    return g.D <= 4608 && blocks <= (g.splits > 1 ? 1024 : 512) && blocks * steps <= 36864 &&
-           (g.RA + g.RB) * (g.pitchA + g.pitchB) < ((int64_t)1 << 31);
+    const int64_t cost = blocks * steps * (wide || g.s < kStep ? 2 : 1);
+    const bool ragged = g.D % (wide ? 4 : 8) != 0 && steps >= 8;
+    if (g.D > 4608 || (g.RA + g.RB) * (g.pitchA + g.pitchB) >= ((int64_t)1 << 31)) return false;
+    if (g.splits > 1) return blocks <= 2048 && cost <= 73728;
+    return blocks <= (ragged ? 2048 : 512) && cost <= 36864;
 }
 
 } // namespace
