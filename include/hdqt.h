@@ -208,6 +208,21 @@ int hdqt_im2col(const float *act, int64_t batch, int channels, int height, int w
                 int kw, int stride, int pad_h, int pad_w, float *X, void *stream);
 
 /*
+ * Its adjoint: dX, the gradient of that matrix [batch*Ho*Wo, channels*kh*kw], folded back onto the
+ * activation, dAct[batch, channels, height, width].  An element's terms are added in binary32, in
+ * the order of the matrix rows they come from.
+ */
+int hdqt_col2im(const float *dX, int64_t batch, int channels, int height, int width, int kh,
+                int kw, int stride, int pad_h, int pad_w, float *dAct, void *stream);
+
+/*
+ * dst[b, j, i] = src[b, i, j], b < batch (at most 65535), i < rows, j < cols (fp32, device, 16-byte
+ * aligned, not overlapping): images with their channels innermost to channel planes.
+ */
+int hdqt_transpose(const float *src, int64_t batch, int64_t rows, int64_t cols, float *dst,
+                   void *stream);
+
+/*
  * Tiled integer matmul on packed codes (Methodology: tiles of size s, low-bit
  * accumulators) followed by dequantization:
  *   acc[i,j] = sum_t sat_a( sum_{d in tile t} qA[i,d] qB[j,d] )

@@ -118,6 +118,30 @@ class HdqtReluMatmul(torch.autograd.Function):
         return dPre, dW, None, None
 
 
+def _planes(act: torch.Tensor) -> torch.Tensor:
+    """act [B, C, H, W] contiguous.  What comes out of a layer and the normalisation behind it has its
+    channels innermost; the library's transposition turns that about twice as fast as a strided copy
+    (COPYUS us for 128 x 64 x 32 x 32)."""
+    if act.is_contiguous() or not act.is_cuda or act.dtype != torch.float32:
+        return act.contiguous()
+    Bn, Cin, H, W = act.shape
+    last = act.permute(0, 2, 3, 1)
+    if Bn > 65535 or not last.is_contiguous() or act.data_ptr() % 16:
+        return act.contiguous()
+    return B.transpose(last.reshape(Bn, H * W, Cin)).reshape(Bn, Cin, H, W)
+
+
+def _fold(dX: torch.Tensor, shape, kh: int, kw: int, stride: int, ph: int, pw: int) -> torch.Tensor:
+    """The gradient of an im2col matrix folded back onto the activation of `shape`.  The library's
+    kernel has channels as lanes; for fewer than 32 of them PyTorch's fold is the faster one (both
+    add an element's terms in the same order)."""
+    Bn, Cin, H, W = shape
+    if Cin >= 32:
+        return B.col2im(dX.contiguous(), shape, kh, kw, stride, ph, pw)
+    return torch.nn.functional.fold(dX.reshape(Bn, -1, Cin * kh * kw).transpose(1, 2), output_size=(H, W),
+                                    kernel_size=(kh, kw), padding=(ph, pw), stride=stride)
+
+
 _FOLD_REFUSED = set()        # activation shapes hdqt_conv_bwd did not take (with the window used)
 
 
@@ -125,12 +149,12 @@ class HdqtConvMatmul(torch.autograd.Function):
     """Z = im2col(act) W for a stride-1, same-size convolution, without forming im2col(act):
     the forward call reads the activation (hdqt_conv_fwd).  The backward pass returns the
     gradient of the activation: the library's gradient of the im2col matrix, folded back by
-    PyTorch."""
+    hdqt_col2im where the matmul does not fold it itself."""
 
     @staticmethod
     def forward(ctx, act, W, cfg: LayerConfig, step: int, kh: int, kw: int):
         ctx.want_dx = cfg.need_input_grad and act.requires_grad
-        act, W = act.contiguous(), W.contiguous()
+        act, W = _planes(act), W.contiguous()
         pf = cfg.params(B.GEMM_FWD, step)
         pw = cfg.params(B.GEMM_BWD_WEIGHT, step)
         Z, saved = B.conv_fwd(act, kh, kw, W, pf, pw)
@@ -163,9 +187,7 @@ class HdqtConvMatmul(torch.autograd.Function):
         if dAct is None:
             dXcol, dW = B.layer_bwd(G, W, saved, Cin * kh * kw, pi, pw)
             if dXcol is not None:
-                cols = dXcol.reshape(Bn, H * Wd, Cin * kh * kw).transpose(1, 2)
-                dAct = torch.nn.functional.fold(cols, output_size=(H, Wd), kernel_size=(kh, kw),
-                                                padding=((kh - 1) // 2, (kw - 1) // 2))
+                dAct = _fold(dXcol, ctx.shape, kh, kw, 1, (kh - 1) // 2, (kw - 1) // 2)
         if cfg.capture is not None:
             cfg.capture.update(G=G.detach(), dX=dXcol, dAct=dAct, dW=dW)
         return dAct, dW, None, None, None, None
@@ -174,19 +196,17 @@ class HdqtConvMatmul(torch.autograd.Function):
 class Unfold(torch.autograd.Function):
     """act [B, C, H, W] -> its im2col matrix [B*Ho*Wo, C*k*k] by the library's one-launch kernel
     (the layers whose geometry the activation-source kernels do not read directly); the
-    backward pass folds the matrix gradient back with PyTorch."""
+    backward pass folds the matrix gradient back (hdqt_col2im)."""
 
     @staticmethod
     def forward(ctx, act, k: int, stride: int, pad: int):
         ctx.geo = (tuple(act.shape), k, stride, pad)
-        return B.im2col(act, k, k, stride, pad, pad)
+        return B.im2col(_planes(act), k, k, stride, pad, pad)
 
     @staticmethod
     def backward(ctx, dX):
-        (Bn, Cin, H, W), k, stride, pad = ctx.geo
-        cols = dX.reshape(Bn, -1, Cin * k * k).transpose(1, 2)
-        return torch.nn.functional.fold(cols, output_size=(H, W), kernel_size=k, padding=pad,
-                                        stride=stride), None, None, None
+        shape, k, stride, pad = ctx.geo
+        return _fold(dX, shape, k, k, stride, pad, pad), None, None, None
 
 
 class HdqtLinear(torch.nn.Module):
@@ -221,7 +241,7 @@ class HdqtConv2d(torch.nn.Module):
     quantized matmuls above.  Stride-1, same-size layers whose geometry the library takes
     never form the unfolded matrix (hdqt_conv_fwd reads the activation, hdqt_conv_bwd folds the
     input gradient back inside the matmul); the others are unfolded by hdqt_im2col and their
-    input gradient is folded back by PyTorch."""
+    input gradient is folded back by hdqt_col2im."""
 
     def __init__(self, in_channels: int, out_channels: int, kernel_size: int = 3, padding: int = 1,
                  stride: int = 1, cfg: Optional[LayerConfig] = None, device=None):

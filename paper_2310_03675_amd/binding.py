@@ -30,7 +30,7 @@ EXPORTED = [
     "hdqt_gemm_codes_requant",
     "hdqt_gemm_requant_workspace_size", "hdqt_gemm_requant", "hdqt_gemm_codes_bf16",
     "hdqt_gemm_bwd_input_bf16", "hdqt_quantize_dual_im2col", "hdqt_conv_step_workspace_size",
-    "hdqt_conv_step", "hdqt_conv_fwd", "hdqt_conv_bwd", "hdqt_gemm_codes_fold", "hdqt_im2col",
+    "hdqt_conv_step", "hdqt_conv_fwd", "hdqt_conv_bwd", "hdqt_gemm_codes_fold", "hdqt_im2col", "hdqt_col2im", "hdqt_transpose",
     "hdqt_gemm_fwd_static", "hdqt_gemm_fwd_static_max_bytes",
     "hdqt_gemm_bwd_input_masked", "hdqt_layer_bwd_masked", "hdqt_conv_bwd_masked",
     "hdqt_probe_matrix_clock", "hdqt_wall_clock_khz",
@@ -168,6 +168,10 @@ def load() -> C.CDLL:
     lib.hdqt_gemm_codes_fold.argtypes = [vp, vp, i32, i32, vp, vp, C.POINTER(CConv), i64, i32, i32, i64, vp, vp]
     lib.hdqt_im2col.restype = i32
     lib.hdqt_im2col.argtypes = [vp, i64] + [i32] * 8 + [vp, vp]
+    lib.hdqt_col2im.restype = i32
+    lib.hdqt_col2im.argtypes = [vp, i64] + [i32] * 8 + [vp, vp]
+    lib.hdqt_transpose.restype = i32
+    lib.hdqt_transpose.argtypes = [vp, i64, i64, i64, vp, vp]
     lib.hdqt_gemm_codes_bf16.restype = i32
     lib.hdqt_gemm_codes_bf16.argtypes = lib.hdqt_gemm_codes.argtypes
     for name in ("hdqt_gemm_fwd", "hdqt_gemm_bwd_input", "hdqt_gemm_bwd_weight", "hdqt_gemm_bwd_input_bf16"):
@@ -313,6 +317,32 @@ def im2col(act: torch.Tensor, kh: int, kw: int, stride: int = 1, pad_h: int = 0,
     if rc:
         raise HdqtError(rc, "hdqt_im2col")
     return X
+
+
+def col2im(dX: torch.Tensor, act_shape, kh: int, kw: int, stride: int = 1, pad_h: int = 0, pad_w: int = 0,
+           stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
+    """hdqt_col2im -> dAct [batch, C, H, W], the adjoint of im2col on an activation of `act_shape`."""
+    _check_dev(dX)
+    b, c, h, w = act_shape
+    Ho, Wo = (h + 2 * pad_h - kh) // stride + 1, (w + 2 * pad_w - kw) // stride + 1
+    assert dX.dtype == torch.float32 and tuple(dX.shape) == (b * Ho * Wo, c * kh * kw)
+    dAct = torch.empty((b, c, h, w), dtype=torch.float32, device=dX.device)
+    rc = load().hdqt_col2im(_ptr(dX), b, c, h, w, kh, kw, stride, pad_h, pad_w, _ptr(dAct), _stream(stream))
+    if rc:
+        raise HdqtError(rc, "hdqt_col2im")
+    return dAct
+
+
+def transpose(src: torch.Tensor, stream: Optional[torch.cuda.Stream] = None) -> torch.Tensor:
+    """hdqt_transpose: [batch, rows, cols] -> a new [batch, cols, rows]."""
+    _check_dev(src)
+    assert src.dtype == torch.float32 and src.dim() == 3
+    b, r, c = src.shape
+    dst = torch.empty((b, c, r), dtype=torch.float32, device=src.device)
+    rc = load().hdqt_transpose(_ptr(src), b, r, c, _ptr(dst), _stream(stream))
+    if rc:
+        raise HdqtError(rc, "hdqt_transpose")
+    return dst
 
 
 def conv_geometry(act: torch.Tensor, kh: int, kw: int) -> CConv:

@@ -846,10 +846,14 @@ int hdqt_quantize_dual_im2col(const float* act, const hdqt_conv_t* geo, int had_
     return run_quantize_set(set, base, 2 * kMetaBytes, stream);
 }
 
-int hdqt_im2col(const float* act, int64_t batch, int channels, int height, int width, int kh, int kw,
-                int stride, int pad_h, int pad_w, float* X, void* stream)
+} // extern "C"
+
+namespace {
+// the geometry shared by hdqt_im2col and hdqt_col2im; X and the activation are both of a size that
+// the kernels index
+int plan_unfold(int64_t batch, int channels, int height, int width, int kh, int kw, int stride, int pad_h, int pad_w,
+                hdqt::Im2colArgs* a)
 {
-    if (!act || !X) return HDQT_EINVAL_NULL;
     if (batch < 1 || channels < 1 || height < 1 || width < 1 || kh < 1 || kw < 1 || stride < 1 || pad_h < 0 ||
         pad_w < 0 || kh > 255 || kw > 255 || height + 2 * pad_h < kh || width + 2 * pad_w < kw)
         return HDQT_EINVAL_DIM;
@@ -857,13 +861,56 @@ int hdqt_im2col(const float* act, int64_t batch, int channels, int height, int w
     const int64_t per_image = (int64_t)Ho * Wo, K = (int64_t)channels * kh * kw;
     if (batch > kMaxDim / per_image) return HDQT_EINVAL_DIM;
     const int64_t M = batch * per_image;
-    int rc = check_dims2(M, K);
+    const int rc = check_dims2(M, K);
     if (rc) return rc;
     if ((int64_t)channels * height * width >= ((int64_t)1 << 31) || (M + 3) / 4 >= ((int64_t)1 << 31))
         return HDQT_EINVAL_DIM;
+    *a = hdqt::Im2colArgs{nullptr, nullptr, M, channels, height, width, kh, kw, stride, pad_h, pad_w, Ho, Wo, nullptr};
+    return HDQT_OK;
+}
+} // namespace
+
+extern "C" {
+
+int hdqt_im2col(const float* act, int64_t batch, int channels, int height, int width, int kh, int kw,
+                int stride, int pad_h, int pad_w, float* X, void* stream)
+{
+    if (!act || !X) return HDQT_EINVAL_NULL;
+    hdqt::Im2colArgs a;
+    const int rc = plan_unfold(batch, channels, height, width, kh, kw, stride, pad_h, pad_w, &a);
+    if (rc) return rc;
     if (misaligned(act) || misaligned(X)) return HDQT_EALIGN;
-    hdqt::Im2colArgs a{act, X, M, channels, height, width, kh, kw, stride, pad_h, pad_w, Ho, Wo};
+    a.act = act;
+    a.X = X;
     const hipError_t e = hdqt::launch_im2col(a, static_cast<hipStream_t>(stream));
+    return e == hipSuccess ? HDQT_OK : hip_fail(e);
+}
+
+int hdqt_col2im(const float* dX, int64_t batch, int channels, int height, int width, int kh, int kw,
+                int stride, int pad_h, int pad_w, float* dAct, void* stream)
+{
+    if (!dX || !dAct) return HDQT_EINVAL_NULL;
+    hdqt::Im2colArgs a;
+    const int rc = plan_unfold(batch, channels, height, width, kh, kw, stride, pad_h, pad_w, &a);
+    if (rc) return rc;
+    const int64_t hw = (int64_t)height * width;
+    if (batch > kMaxDim / hw) return HDQT_EINVAL_DIM;
+    if (misaligned(dX) || misaligned(dAct)) return HDQT_EALIGN;
+    a.X = const_cast<float*>(dX);
+    a.M = batch * hw;
+    a.out = dAct;
+    const hipError_t e = hdqt::launch_col2im(a, static_cast<hipStream_t>(stream));
+    return e == hipSuccess ? HDQT_OK : hip_fail(e);
+}
+
+int hdqt_transpose(const float* src, int64_t batch, int64_t rows, int64_t cols, float* dst, void* stream)
+{
+    if (!src || !dst) return HDQT_EINVAL_NULL;
+    if (batch < 1 || batch > 65535) return HDQT_EINVAL_DIM;
+    const int rc = check_dims2(rows, cols);
+    if (rc) return rc;
+    if (misaligned(src) || misaligned(dst)) return HDQT_EALIGN;
+    const hipError_t e = hdqt::launch_transpose(src, dst, batch, rows, cols, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? HDQT_OK : hip_fail(e);
 }
 

@@ -138,10 +138,14 @@ hipError_t launch_gemm_fold(const GemmArgs& g, hipStream_t stream);
 struct Im2colArgs {
     const float* act;
     float* X;
-    int64_t M;
+    int64_t M;              // rows of X; of launch_col2im: pixels of the activation, batch*H*W
     int C, H, W, kh, kw, stride, ph, pw, Ho, Wo;
+    float* out;             // launch_col2im: the activation's gradient, X that of the matrix
 };
 hipError_t launch_im2col(const Im2colArgs& a, hipStream_t stream);
+hipError_t launch_col2im(const Im2colArgs& a, hipStream_t stream);
+// dst[batch, cols, rows] = src[batch, rows, cols] transposed
+hipError_t launch_transpose(const float* src, float* dst, int64_t batch, int64_t rows, int64_t cols, hipStream_t stream);
 
 // Launchers (host).  Each returns the hipError_t of its last launch.
 // any-shape kernel: add a tensor to a batch (false: it is full); a launch of a whole batch
@@ -191,7 +195,7 @@ enum KernelId {
     K_GEMM_I4_FWD, K_GEMM_I4_BWD_INPUT, K_GEMM_I4_BWD_WEIGHT,
     K_DUAL_ABSMAX_X, K_DUAL_ABSMAX_W, K_DUAL_ABSMAX_G, K_DUAL_QUANT_X, K_DUAL_QUANT_W, K_DUAL_QUANT_G,
     K_DUAL_ABSMAX_BATCH, K_DUAL_QUANT_BATCH, K_REQUANT_TILES, K_REQUANT_SUM, K_IM2COL, K_RELU_MASK,
-    K_GEMM_RAGGED, K_GEMM_SMALL,
+    K_GEMM_RAGGED, K_GEMM_SMALL, K_COL2IM, K_TRANSPOSE,
     K_COUNT
 };
 bool quantize_fast_eligible(const QuantArgs& q);

@@ -1,0 +1,29 @@
+"""GPU parity of the layout kernels against PyTorch's own unfold, fold and transpose, bit for bit (the
+terms of a folded element are added in the order of the matrix rows, as its fold does)."""
+import pytest
+import torch
+
+from paper_2310_03675_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("b,c,h,w,k,stride,pad", [
+    (1, 1, 1, 1, 1, 1, 0), (2, 3, 32, 32, 3, 1, 1), (3, 65, 8, 8, 3, 2, 1), (5, 64, 16, 16, 1, 2, 0), (4, 130, 4, 4, 3, 1, 1),
+    (2, 33, 7, 9, 5, 1, 2), (3, 20, 11, 6, 3, 3, 0), (7, 512, 4, 4, 3, 1, 1), (2, 8, 5, 5, 2, 2, 0), (1, 300, 9, 33, 3, 2, 2)])
+def test_unfold_and_fold(b, c, h, w, k, stride, pad):
+    print(f"layout: act [{b},{c},{h},{w}] window {k} stride {stride} pad {pad}", flush=True)
+    g = torch.Generator().manual_seed(b * 1000 + c)
+    act = torch.randn(b, c, h, w, generator=g).cuda()
+    cols = torch.nn.functional.unfold(act, kernel_size=k, padding=pad, stride=stride)
+    assert torch.equal(B.im2col(act, k, k, stride, pad, pad), cols.transpose(1, 2).reshape(-1, c * k * k))
+    dX = torch.randn(b * cols.shape[2], c * k * k, generator=g).cuda()
+    want = torch.nn.functional.fold(dX.reshape(b, -1, c * k * k).transpose(1, 2).contiguous(), output_size=(h, w),
+                                    kernel_size=k, padding=pad, stride=stride)
+    assert torch.equal(B.col2im(dX, (b, c, h, w), k, k, stride, pad, pad), want)
+
+
+@pytest.mark.parametrize("b,r,c", [(1, 1, 1), (3, 64, 64), (2, 65, 63), (5, 16, 512), (2, 1, 130), (4, 1024, 64)])
+def test_transpose(b, r, c):
+    x = torch.randn(b, r, c, generator=torch.Generator().manual_seed(r)).cuda()
+    assert torch.equal(B.transpose(x), x.transpose(1, 2).contiguous())
