@@ -131,12 +131,24 @@ def _planes(act: torch.Tensor) -> torch.Tensor:
     return B.transpose(last.reshape(Bn, H * W, Cin)).reshape(Bn, Cin, H, W)
 
 
+def _opaque_call_will_do(t: torch.Tensor) -> bool:
+    """Whether a library call may stand for an operation on t: t has memory of its own (a batch of
+    gradients has none), and no derivative of the result will be asked for (the library's results
+    carry no graph and no tangent)."""
+    try:
+        t.data_ptr()
+    except RuntimeError:
+        return False
+    return not (torch.is_grad_enabled() and t.requires_grad) and \
+        torch.autograd.forward_ad.unpack_dual(t).tangent is None
+
+
 def _fold(dX: torch.Tensor, shape, kh: int, kw: int, stride: int, ph: int, pw: int) -> torch.Tensor:
     """The gradient of an im2col matrix folded back onto the activation of `shape`.  The library's
     kernel has channels as lanes; for fewer than 32 of them PyTorch's fold is the faster one (both
     add an element's terms in the same order)."""
     Bn, Cin, H, W = shape
-    if Cin >= 32:
+    if Cin >= 32 and _opaque_call_will_do(dX):
         return B.col2im(dX.contiguous(), shape, kh, kw, stride, ph, pw)
     return torch.nn.functional.fold(dX.reshape(Bn, -1, Cin * kh * kw).transpose(1, 2), output_size=(H, W),
                                     kernel_size=(kh, kw), padding=(ph, pw), stride=stride)

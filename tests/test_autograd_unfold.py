@@ -1,0 +1,71 @@
+"""The autograd functions around the layout kernels, on the CPU: the library's calls are replaced by
+PyTorch's own unfold and fold, detached, as results of the library are, and with its alignment
+and size checks."""
+import pytest
+import torch
+import torch.nn.functional as F
+
+from paper_2310_03675_amd import autograd as A
+from paper_2310_03675_amd import binding as B
+
+
+def _im2col(act, kh, kw, stride=1, pad_h=0, pad_w=0, stream=None):
+    cols = F.unfold(act.detach(), (kh, kw), padding=(pad_h, pad_w), stride=stride)
+    return cols.transpose(1, 2).reshape(-1, act.shape[1] * kh * kw)
+
+
+def _col2im(dX, act_shape, kh, kw, stride=1, pad_h=0, pad_w=0, stream=None):
+    b, c, h, w = act_shape
+    assert dX.is_contiguous() and dX.data_ptr() % 16 == 0
+    return F.fold(dX.detach().reshape(b, -1, c * kh * kw).transpose(1, 2), (h, w), (kh, kw), padding=(pad_h, pad_w),
+                  stride=stride)
+
+
+@pytest.fixture
+def library(monkeypatch):
+    monkeypatch.setattr(B, "im2col", _im2col)
+    monkeypatch.setattr(B, "col2im", _col2im)
+
+
+def _plain(act, k, stride, pad):
+    return F.unfold(act, k, padding=pad, stride=stride).transpose(1, 2).reshape(-1, act.shape[1] * k * k)
+
+
+GEOMETRIES = [(2, 32, 6, 6, 3, 1, 1), (3, 40, 7, 5, 3, 2, 1), (2, 5, 6, 6, 3, 1, 1)]
+
+
+@pytest.mark.parametrize("b,c,h,w,k,stride,pad", GEOMETRIES)
+def test_gradient_of_a_gradient(library, b, c, h, w, k, stride, pad):
+    """create_graph: the gradient itself can be differentiated."""
+    got = []
+    for unfold in (A.Unfold.apply, _plain):
+        act = torch.randn(b, c, h, w, generator=torch.Generator().manual_seed(1)).requires_grad_()
+        first, = torch.autograd.grad((unfold(act, k, stride, pad) ** 3).sum(), act, create_graph=True)
+        assert first.requires_grad
+        second, = torch.autograd.grad((first ** 2).sum(), act)
+        got.append((first, second))
+    assert torch.equal(got[0][0], got[1][0])
+    # (two binary32 sums of the same k * k terms a rounding apart)
+    assert torch.allclose(got[0][1], got[1][1], rtol=1e-5, atol=1e-5 * float(got[1][1].abs().max()))
+
+
+@pytest.mark.parametrize("b,c,h,w,k,stride,pad", GEOMETRIES)
+def test_batched_gradients(library, b, c, h, w, k, stride, pad):
+    """is_grads_batched: many gradients of the matrix in one backward pass."""
+    act = torch.randn(b, c, h, w, generator=torch.Generator().manual_seed(2)).requires_grad_()
+    X = A.Unfold.apply(act, k, stride, pad)
+    many = torch.randn(4, *X.shape, generator=torch.Generator().manual_seed(3))
+    got, = torch.autograd.grad(X, act, many, is_grads_batched=True, retain_graph=True)
+    for g, one in zip(got, many):
+        assert torch.equal(g, torch.autograd.grad(X, act, one, retain_graph=True)[0])
+
+
+def test_forward_mode_through_the_gradient(library):
+    """A tangent of the matrix's gradient comes out as the tangent of the activation's."""
+    import torch.autograd.forward_ad as fa
+    g = torch.Generator().manual_seed(4)
+    dX, tangent = torch.randn(72, 32 * 9, generator=g), torch.randn(72, 32 * 9, generator=g)
+    geometry = ((2, 32, 6, 6), 3, 3, 1, 1, 1)
+    with fa.dual_level():
+        got = fa.unpack_dual(A._fold(fa.make_dual(dX, tangent), *geometry))
+    assert torch.equal(got.primal, _col2im(dX, *geometry)) and torch.equal(got.tangent, _col2im(tangent, *geometry))
