@@ -154,7 +154,7 @@ def _fold(dX: torch.Tensor, shape, kh: int, kw: int, stride: int, ph: int, pw: i
                                     kernel_size=(kh, kw), padding=(ph, pw), stride=stride)
 
 
-_FOLD_REFUSED = set()        # activation shapes hdqt_conv_bwd did not take (with the window used)
+_FOLD_REFUSED = set()        # products hdqt_conv_bwd did not take, by everything that this depends on
 
 
 class HdqtConvMatmul(torch.autograd.Function):
@@ -186,7 +186,7 @@ class HdqtConvMatmul(torch.autograd.Function):
         pw = cfg.params(B.GEMM_BWD_WEIGHT, ctx.step)
         G = G.contiguous()
         dAct = dXcol = None
-        key = (ctx.shape, kh, kw)
+        key = pi and (ctx.shape, kh, kw, W.shape[1], pi.A.b, pi.B.b, pi.acc_bits, pi.s)
         if pi is not None and cfg.fold_in_matmul and key not in _FOLD_REFUSED:
             # the input gradient folded onto the activation inside the matmul: the gradient of
             # the im2col matrix is never written

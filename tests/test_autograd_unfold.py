@@ -69,3 +69,41 @@ def test_forward_mode_through_the_gradient(library):
     with fa.dual_level():
         got = fa.unpack_dual(A._fold(fa.make_dual(dX, tangent), *geometry))
     assert torch.equal(got.primal, _col2im(dX, *geometry)) and torch.equal(got.tangent, _col2im(tangent, *geometry))
+
+
+def test_a_refused_layer_does_not_decide_for_others(monkeypatch):
+    """What hdqt_conv_bwd takes depends on the output channels and the quantization too: a layer that
+    it refused leaves the next one of the same input shape alone, and is itself not asked again."""
+    asked, unfolded = [], []
+
+    def conv_fwd(act, kh, kw, W, fwd, bww):
+        return torch.zeros(act.shape[0] * act.shape[2] * act.shape[3], W.shape[1]), torch.zeros(1)
+
+    def conv_bwd(G, W, saved, shape, kh, kw, bwi, bww):
+        asked.append((W.shape[1], bwi.A.b, bwi.s, bwi.acc_bits))
+        if W.shape[1] % 32 or bwi.A.b > 4 or bwi.s % 32 or bwi.acc_bits > 8:
+            raise B.HdqtError(-13, "hdqt_conv_bwd")
+        return torch.zeros(shape), torch.zeros_like(W)
+
+    def layer_bwd(G, W, saved, K, bwi, bww):
+        unfolded.append(W.shape[1])
+        return torch.zeros(G.shape[0], K), torch.zeros_like(W)
+
+    monkeypatch.setattr(B, "conv_fwd", conv_fwd)
+    monkeypatch.setattr(B, "conv_bwd", conv_bwd)
+    monkeypatch.setattr(B, "layer_bwd", layer_bwd)
+    monkeypatch.setattr(B, "col2im", _col2im)
+
+    def step(cout, **cfg):
+        act = torch.randn(2, 32, 8, 8).requires_grad_()
+        W = torch.randn(32 * 9, cout).requires_grad_()
+        A.HdqtConvMatmul.apply(act, W, A.LayerConfig(**cfg), 0, 3, 3).sum().backward()
+
+    for refused in (dict(cout=16), dict(cout=64, bits=8, acc_bits=16), dict(cout=64, s=48), dict(cout=64, acc_bits=12)):
+        asked.clear(), unfolded.clear()
+        step(**refused)
+        assert len(asked) == 1 and len(unfolded) == 1
+        step(cout=64)
+        assert len(asked) == 2 and len(unfolded) == 1, refused
+        step(**refused)
+        assert len(asked) == 2 and len(unfolded) == 2
