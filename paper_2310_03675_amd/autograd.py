@@ -149,7 +149,10 @@ def _fold(dX: torch.Tensor, shape, kh: int, kw: int, stride: int, ph: int, pw: i
     add an element's terms in the same order)."""
     Bn, Cin, H, W = shape
     if Cin >= 32 and _opaque_call_will_do(dX):
-        return B.col2im(dX.contiguous(), shape, kh, kw, stride, ph, pw)
+        dX = dX.contiguous()
+        if dX.data_ptr() % 16:           # a part of another tensor; the library takes whole 16-byte units
+            dX = dX.clone()
+        return B.col2im(dX, shape, kh, kw, stride, ph, pw)
     return torch.nn.functional.fold(dX.reshape(Bn, -1, Cin * kh * kw).transpose(1, 2), output_size=(H, W),
                                     kernel_size=(kh, kw), padding=(ph, pw), stride=stride)
 

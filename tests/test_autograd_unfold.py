@@ -107,3 +107,16 @@ def test_a_refused_layer_does_not_decide_for_others(monkeypatch):
         assert len(asked) == 2 and len(unfolded) == 1, refused
         step(**refused)
         assert len(asked) == 2 and len(unfolded) == 2
+
+
+def test_gradient_that_does_not_start_on_16_bytes(library):
+    """The matrix as a part of something larger: its gradient is a view at any float."""
+    act = torch.randn(2, 33, 6, 6, generator=torch.Generator().manual_seed(5)).requires_grad_()
+    got = []
+    for unfold in (A.Unfold.apply, _plain):
+        X = unfold(act, 3, 1, 1)
+        whole = torch.cat([torch.ones(1, X.shape[1]), X])
+        weights = torch.randn(whole.shape, generator=torch.Generator().manual_seed(6))
+        assert weights[1:].data_ptr() % 16
+        got.append(torch.autograd.grad(whole, act, weights)[0])
+    assert torch.equal(*got)
