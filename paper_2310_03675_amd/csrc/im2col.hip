@@ -21,15 +21,18 @@ constexpr int kThreads = 256;
 constexpr int kRows = 32;          // per thread
 constexpr int kUnroll = 8;
 
-__global__ __launch_bounds__(kThreads) void im2col_kernel(Im2colArgs a, int width, int log2w)
+__global__ __launch_bounds__(kThreads) void im2col_kernel(Im2colArgs a, int width, int log2w, uint32_t n_col)
 {
     const int K = a.C * a.kh * a.kw, khw = a.kh * a.kw;
-    const int k = (int)blockIdx.x * width + ((int)threadIdx.x & (width - 1));
+    // (runs of rows and, fastest, of columns on one axis of the grid: the others hold 65535 workgroups,
+    // 2097120 rows of more than 128 columns)
+    const uint32_t run = blockIdx.x / n_col;
+    const int k = (int)(blockIdx.x - run * n_col) * width + ((int)threadIdx.x & (width - 1));
     if (k >= K) return;
     const int c = k / khw, tap = k - c * khw, ty = tap / a.kw, tx = tap - ty * a.kw;
     const int side = kThreads >> log2w;                  // rows of the workgroup at a time
     const int64_t per_image = (int64_t)a.Ho * a.Wo;
-    int64_t m = (int64_t)blockIdx.y * ((int64_t)side * kRows) + ((int)threadIdx.x >> log2w);
+    int64_t m = (int64_t)run * ((int64_t)side * kRows) + ((int)threadIdx.x >> log2w);
     const int64_t b = m / per_image;
     int yo = (int)((m - b * per_image) / a.Wo), xo = (int)(m - b * per_image - (int64_t)yo * a.Wo);
     // (an image and its next: the offsets inside one fit 32 bits)
@@ -160,9 +163,10 @@ hipError_t launch_im2col(const Im2colArgs& a, hipStream_t stream)
     while (log2w < 8 && (1 << log2w) < K) ++log2w;
     const int width = 1 << log2w;
     const int64_t tall = (int64_t)(kThreads / width) * kRows;
-    const dim3 grid((unsigned)((K + width - 1) / width), (unsigned)((a.M + tall - 1) / tall));
+    const int64_t n_col = (K + width - 1) / width, runs = (a.M + tall - 1) / tall;
     ProfileScope ps(K_IM2COL, stream);
-    hipLaunchKernelGGL(im2col_kernel, grid, dim3(kThreads), 0, stream, a, width, log2w);
+    hipLaunchKernelGGL(im2col_kernel, dim3((unsigned)(n_col * runs)), dim3(kThreads), 0, stream, a, width, log2w,
+                       (uint32_t)n_col);
     return hipGetLastError();
 }
 

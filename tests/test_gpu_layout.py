@@ -27,3 +27,17 @@ def test_unfold_and_fold(b, c, h, w, k, stride, pad):
 def test_transpose(b, r, c):
     x = torch.randn(b, r, c, generator=torch.Generator().manual_seed(r)).cuda()
     assert torch.equal(B.transpose(x), x.transpose(1, 2).contiguous())
+
+
+@pytest.mark.parametrize("b,c,h,w,k,stride,pad", [(168, 3, 224, 224, 7, 2, 3),        # 2.1 M rows of 147
+                                                  (4112, 3, 30, 34, 7, 1, 3)])        # 4194240, the most there may be
+def test_unfold_many_rows(b, c, h, w, k, stride, pad):
+    """More runs of rows than the second axis of a grid holds (65535, of 32 rows each)."""
+    print(f"layout: act [{b},{c},{h},{w}] window {k} stride {stride} pad {pad}", flush=True)
+    act = torch.randn(b, c, h, w, generator=torch.Generator().manual_seed(b)).cuda()
+    X = B.im2col(act, k, k, stride, pad, pad)
+    per = X.shape[0] // b
+    assert X.shape[0] > 65535 * 32
+    for first in (0, 65535 * 32 // per - 1, b - 2):
+        cols = torch.nn.functional.unfold(act[first:first + 2], kernel_size=k, padding=pad, stride=stride)
+        assert torch.equal(X[first * per:(first + 2) * per], cols.transpose(1, 2).reshape(-1, c * k * k))
