@@ -893,8 +893,9 @@ int hdqt_col2im(const float* dX, int64_t batch, int channels, int height, int wi
     hdqt::Im2colArgs a;
     const int rc = plan_unfold(batch, channels, height, width, kh, kw, stride, pad_h, pad_w, &a);
     if (rc) return rc;
+    // (the activation of a strided layer has many times the pixels that the matrix has rows)
     const int64_t hw = (int64_t)height * width;
-    if (batch > kMaxDim / hw) return HDQT_EINVAL_DIM;
+    if (batch > kMaxElems / channels / hw) return HDQT_EINVAL_DIM;
     if (misaligned(dX) || misaligned(dAct)) return HDQT_EALIGN;
     a.X = const_cast<float*>(dX);
     a.M = batch * hw;

@@ -66,13 +66,13 @@ __global__ __launch_bounds__(kThreads) void im2col_kernel(Im2colArgs a, int widt
 // lines its neighbours read too, and which taps there are is the same for the whole wave; the sums
 // turn through LDS and leave as runs of pixels.  The taps are added from the window's end to its
 // start, i.e. in the order of the matrix rows.
-constexpr int kFoldPixels = 32, kFoldChannels = 64;
-
 //
 // A pixel has at most ceil(kh / stride) x ceil(kw / stride) taps, whose loads go out NY x NX at a time:
 // all of them, or (NY = 1, larger windows) along one row of the window.  Of those that fall outside
 // the matrix a zero is added.  128 x 64 x 32 x 32, window 3, stride 2: 94 -> 68 us against a loop over
 // the window that loads and adds tap by tap.
+constexpr int kFoldPixels = 32, kFoldChannels = 64;
+
 __device__ __forceinline__ int last_tap(int at, int k, int stride)      // largest t < k, t = at modulo stride
 {
     return k - 1 - (k - 1 + stride - at % stride) % stride;
@@ -84,47 +84,51 @@ __global__ __launch_bounds__(kThreads) void col2im_kernel(Im2colArgs a)
     __shared__ float turn[kFoldChannels][kFoldPixels + 1];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int khw = a.kh * a.kw, K = a.C * khw, HW = a.H * a.W;
-    const int64_t p0 = (int64_t)blockIdx.x * kFoldPixels;
     const int c0 = (int)blockIdx.y * kFoldChannels, c = c0 + lane < a.C ? c0 + lane : a.C - 1;
     const int lane_off = c * khw;
-    // (the same in every lane) the wave's first pixel
-    const int64_t p_first = p0 + wave * (kFoldPixels / 4);
-    int64_t b = p_first / HW;
-    int y = (int)((uint32_t)(p_first - b * HW) / (uint32_t)a.W), x = (int)(p_first - b * HW) - y * a.W;
-    for (int i = 0; i < kFoldPixels / 4; ++i) {
-        if (p_first + i >= a.M) break;
-        float sum = 0.0f;
-        // the last tap whose matrix row or column is a whole number of strides away, and every
-        // stride-th before it
-        const int ty_last = last_tap(y + a.ph, a.kh, a.stride), tx_last = last_tap(x + a.pw, a.kw, a.stride);
-        for (int ty0 = ty_last; ty0 >= 0; ty0 -= NY * a.stride)
-            for (int tx0 = tx_last; tx0 >= 0; tx0 -= NX * a.stride) {
-                float v[NY * NX];
+    // (a grid holds 2^32 threads; the activation of a strided layer has more pixels than its matrix rows)
+    for (int64_t p0 = (int64_t)blockIdx.x * kFoldPixels; p0 < a.M; p0 += (int64_t)gridDim.x * kFoldPixels) {
+        // (the same in every lane) the wave's first pixel
+        const int64_t p_first = p0 + wave * (kFoldPixels / 4);
+        int64_t b = p_first / HW;
+        int y = (int)((uint32_t)(p_first - b * HW) / (uint32_t)a.W), x = (int)(p_first - b * HW) - y * a.W;
+        for (int i = 0; i < kFoldPixels / 4; ++i) {
+            if (p_first + i >= a.M) break;
+            float sum = 0.0f;
+            // the last tap whose matrix row or column is a whole number of strides away, and every
+            // stride-th before it
+            const int ty_last = last_tap(y + a.ph, a.kh, a.stride), tx_last = last_tap(x + a.pw, a.kw, a.stride);
+            for (int ty0 = ty_last; ty0 >= 0; ty0 -= NY * a.stride)
+                for (int tx0 = tx_last; tx0 >= 0; tx0 -= NX * a.stride) {
+                    float v[NY * NX];
 #pragma unroll
-                for (int u = 0; u < NY * NX; ++u) {
-                    const int ty = ty0 - u / NX * a.stride, tx = tx0 - u % NX * a.stride;
-                    const int yo = (y + a.ph - ty) / a.stride, xo = (x + a.pw - tx) / a.stride;
-                    const bool ok = ty >= 0 && tx >= 0 && y + a.ph >= ty && x + a.pw >= tx && yo < a.Ho && xo < a.Wo;
-                    const float* row = a.X + (ok ? ((b * a.Ho + yo) * a.Wo + xo) * (int64_t)K + ty * a.kw + tx : 0);
-                    v[u] = row[lane_off];
-                    if (!ok) v[u] = 0.0f;
+                    for (int u = 0; u < NY * NX; ++u) {
+                        const int ty = ty0 - u / NX * a.stride, tx = tx0 - u % NX * a.stride;
+                        const int yo = (y + a.ph - ty) / a.stride, xo = (x + a.pw - tx) / a.stride;
+                        const bool ok = ty >= 0 && tx >= 0 && y + a.ph >= ty && x + a.pw >= tx && yo < a.Ho && xo < a.Wo;
+                        const float* row = a.X + (ok ? ((b * a.Ho + yo) * a.Wo + xo) * (int64_t)K + ty * a.kw + tx : 0);
+                        v[u] = row[lane_off];
+                        if (!ok) v[u] = 0.0f;
+                    }
+#pragma unroll
+                    for (int u = 0; u < NY * NX; ++u) sum += v[u];
                 }
-#pragma unroll
-                for (int u = 0; u < NY * NX; ++u) sum += v[u];
+            turn[lane][wave * (kFoldPixels / 4) + i] = sum;
+            if (++x == a.W) {
+                x = 0;
+                if (++y == a.H) { y = 0; ++b; }
             }
-        turn[lane][wave * (kFoldPixels / 4) + i] = sum;
-        if (++x == a.W) {
-            x = 0;
-            if (++y == a.H) { y = 0; ++b; }
         }
-    }
-    __syncthreads();
-    const int64_t p = p0 + (lane & 31);
-    if (p >= a.M) return;
-    const int64_t bp = p / HW, at = p - bp * HW;
-    for (int i = 0; i < kFoldChannels / 8; ++i) {
-        const int ch = wave * (kFoldChannels / 4) + 2 * i + (lane >> 5);
-        if (c0 + ch < a.C) a.out[(bp * a.C + c0 + ch) * HW + at] = turn[ch][lane & 31];
+        __syncthreads();
+        const int64_t p = p0 + (lane & 31);
+        if (p < a.M) {
+            const int64_t bp = p / HW, at = p - bp * HW;
+            for (int i = 0; i < kFoldChannels / 8; ++i) {
+                const int ch = wave * (kFoldChannels / 4) + 2 * i + (lane >> 5);
+                if (c0 + ch < a.C) a.out[(bp * a.C + c0 + ch) * HW + at] = turn[ch][lane & 31];
+            }
+        }
+        if (p0 + (int64_t)gridDim.x * kFoldPixels < a.M) __syncthreads();
     }
 }
 
@@ -172,7 +176,9 @@ hipError_t launch_im2col(const Im2colArgs& a, hipStream_t stream)
 
 hipError_t launch_col2im(const Im2colArgs& a, hipStream_t stream)
 {
-    const dim3 grid((unsigned)((a.M + kFoldPixels - 1) / kFoldPixels), (unsigned)((a.C + kFoldChannels - 1) / kFoldChannels));
+    const int64_t runs = (a.M + kFoldPixels - 1) / kFoldPixels;
+    const unsigned across = (unsigned)((a.C + kFoldChannels - 1) / kFoldChannels);
+    const dim3 grid((unsigned)(runs < (1 << 23) ? runs : (1 << 23)), across);
     ProfileScope ps(K_COL2IM, stream);
     const int ny = (a.kh + a.stride - 1) / a.stride, nx = (a.kw + a.stride - 1) / a.stride, n = ny > nx ? ny : nx;
     if (n == 1) hipLaunchKernelGGL((col2im_kernel<1, 1>), grid, dim3(kThreads), 0, stream, a);

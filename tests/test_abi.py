@@ -400,3 +400,19 @@ def test_im2col_argument_errors():
     assert bad(5, 12) == E["HDQT_EINVAL_DIM"]         # window taller than the padded image
     assert bad(8, -1) == E["HDQT_EINVAL_DIM"]         # negative padding
     assert bad(10, C.c_void_p(0x10008)) == E["HDQT_EALIGN"]
+
+
+def test_col2im_argument_errors():
+    f = B.load().hdqt_col2im
+    ok = (FAKE, 2, 64, 8, 8, 3, 3, 1, 1, 1, FAKE, None)
+    bad = lambda i, v, base=ok: f(*(base[:i] + (v,) + base[i + 1:]))
+    assert bad(0, None) == E["HDQT_EINVAL_NULL"] and bad(10, None) == E["HDQT_EINVAL_NULL"]
+    assert bad(1, 0) == E["HDQT_EINVAL_DIM"] and bad(7, 0) == E["HDQT_EINVAL_DIM"]
+    assert bad(10, C.c_void_p(0x10008)) == E["HDQT_EALIGN"]
+    # what is limited is the matrix, not the pixels of a strided layer's activation: these get as far as
+    # the check of the pointers, the last that is made
+    odd = C.c_void_p(0x10008)
+    for strided in ((FAKE, 335, 64, 112, 112, 3, 3, 2, 1, 1, FAKE, None),          # 4.2 M pixels, 1.05 M rows
+                    (FAKE, 63, 32, 4096, 4096, 16, 16, 16, 0, 0, FAKE, None)):     # 1.06 G pixels, 4.13 M rows
+        assert bad(10, odd, strided) == E["HDQT_EALIGN"]
+    assert f(FAKE, 335, 64, 112, 112, 3, 3, 1, 1, 1, odd, None) == E["HDQT_EINVAL_DIM"]      # 4.2 M rows

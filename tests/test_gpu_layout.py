@@ -41,3 +41,17 @@ def test_unfold_many_rows(b, c, h, w, k, stride, pad):
     for first in (0, 65535 * 32 // per - 1, b - 2):
         cols = torch.nn.functional.unfold(act[first:first + 2], kernel_size=k, padding=pad, stride=stride)
         assert torch.equal(X[first * per:(first + 2) * per], cols.transpose(1, 2).reshape(-1, c * k * k))
+
+
+@pytest.mark.parametrize("b,c,h,w,k,stride,pad", [(335, 32, 112, 112, 3, 2, 1),      # 4.2 M pixels, 1.05 M rows
+                                                  (5, 1, 8192, 8192, 16, 16, 0)])    # 2^23 workgroups, and a second turn
+def test_fold_many_pixels(b, c, h, w, k, stride, pad):
+    """Strided layers: many times the pixels that the matrix has rows."""
+    print(f"layout: fold to [{b},{c},{h},{w}] window {k} stride {stride} pad {pad}", flush=True)
+    rows = ((h + 2 * pad - k) // stride + 1) * ((w + 2 * pad - k) // stride + 1)
+    dX = torch.randn(b * rows, c * k * k, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1))
+    got = B.col2im(dX, (b, c, h, w), k, k, stride, pad, pad)
+    for first in (0, b // 2, b - 2):
+        part = dX[first * rows:(first + 2) * rows].reshape(2, rows, c * k * k).transpose(1, 2).contiguous()
+        want = torch.nn.functional.fold(part, output_size=(h, w), kernel_size=k, padding=pad, stride=stride)
+        assert torch.equal(got[first:first + 2], want)
