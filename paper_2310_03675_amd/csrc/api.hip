@@ -865,6 +865,9 @@ int plan_unfold(int64_t batch, int channels, int height, int width, int kh, int 
     if (rc) return rc;
     if ((int64_t)channels * height * width >= ((int64_t)1 << 31) || (M + 3) / 4 >= ((int64_t)1 << 31))
         return HDQT_EINVAL_DIM;
+    // (a stride longer than the padded image is as good as one of its length, and the kernels may add to it)
+    const int longest = height + 2 * pad_h > width + 2 * pad_w ? height + 2 * pad_h : width + 2 * pad_w;
+    if (stride > longest) stride = longest;
     *a = hdqt::Im2colArgs{nullptr, nullptr, M, channels, height, width, kh, kw, stride, pad_h, pad_w, Ho, Wo, nullptr};
     return HDQT_OK;
 }

@@ -10,7 +10,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("b,c,h,w,k,stride,pad", [
     (1, 1, 1, 1, 1, 1, 0), (2, 3, 32, 32, 3, 1, 1), (3, 65, 8, 8, 3, 2, 1), (5, 64, 16, 16, 1, 2, 0), (4, 130, 4, 4, 3, 1, 1),
-    (2, 33, 7, 9, 5, 1, 2), (3, 20, 11, 6, 3, 3, 0), (7, 512, 4, 4, 3, 1, 1), (2, 8, 5, 5, 2, 2, 0), (1, 300, 9, 33, 3, 2, 2)])
+    (2, 33, 7, 9, 5, 1, 2), (3, 20, 11, 6, 3, 3, 0), (7, 512, 4, 4, 3, 1, 1), (2, 8, 5, 5, 2, 2, 0), (1, 300, 9, 33, 3, 2, 2),
+    (3, 33, 7, 9, 3, 8, 1), (2, 33, 7, 9, 3, 2**31 - 1, 1), (2, 5, 4, 6, 1, 2**31 - 1, 0)])
 def test_unfold_and_fold(b, c, h, w, k, stride, pad):
     print(f"layout: act [{b},{c},{h},{w}] window {k} stride {stride} pad {pad}", flush=True)
     g = torch.Generator().manual_seed(b * 1000 + c)
