@@ -126,7 +126,7 @@ def _planes(act: torch.Tensor) -> torch.Tensor:
         return act.contiguous()
     Bn, Cin, H, W = act.shape
     last = act.permute(0, 2, 3, 1)
-    if Bn > 65535 or not last.is_contiguous() or act.data_ptr() % 16:
+    if Bn > 65535 or max(H * W, Cin) > 65535 * 64 or not last.is_contiguous() or act.data_ptr() % 16:
         return act.contiguous()
     return B.transpose(last.reshape(Bn, H * W, Cin)).reshape(Bn, Cin, H, W)
 

@@ -3,6 +3,7 @@ terms of a folded element are added in the order of the matrix rows, as its fold
 import pytest
 import torch
 
+from paper_2310_03675_amd import autograd as A
 from paper_2310_03675_amd import binding as B
 
 pytestmark = pytest.mark.gpu
@@ -56,3 +57,31 @@ def test_fold_many_pixels(b, c, h, w, k, stride, pad):
         part = dX[first * rows:(first + 2) * rows].reshape(2, rows, c * k * k).transpose(1, 2).contiguous()
         want = torch.nn.functional.fold(part, output_size=(h, w), kernel_size=k, padding=pad, stride=stride)
         assert torch.equal(got[first:first + 2], want)
+
+
+@pytest.mark.parametrize("shape,stride", [((3, 40, 8, 6), 1), ((3, 40, 8, 6), 2), ((2, 2, 2049, 2048), 2)])
+@pytest.mark.parametrize("layout", ["innermost", "misaligned", "transposed", "part"])
+def test_unfold_of_any_layout(shape, stride, layout):
+    """Activations with their channels innermost (the library's own transposition where it takes the
+    sizes: at most 4194240 pixels), off the 16-byte grid, and in orders it does not take."""
+    print(f"layout: {layout} act {shape} stride {stride}", flush=True)
+    b, c, h, w = shape
+    act = torch.randn(shape, generator=torch.Generator().manual_seed(c))
+    if layout in ("innermost", "misaligned"):
+        room = torch.empty(act.numel() + 1, device="cuda")[layout == "misaligned":][:act.numel()]
+        x = room.reshape(b, h, w, c).permute(0, 3, 1, 2)
+        assert (x.data_ptr() % 16 != 0) == (layout == "misaligned")
+    elif layout == "transposed":
+        x = torch.empty(b, c, w, h, device="cuda").transpose(2, 3)
+    else:
+        x = torch.empty(b, c + 1, h, w, device="cuda")[:, :c]
+    x.copy_(act)
+    assert not x.is_contiguous()
+    x.requires_grad_()
+    X = A.Unfold.apply(x, 1 if stride > 1 else 3, stride, 0 if stride > 1 else 1)
+    k, pad = (1, 0) if stride > 1 else (3, 1)
+    want = torch.nn.functional.unfold(act.cuda(), kernel_size=k, padding=pad, stride=stride)
+    assert torch.equal(X, want.transpose(1, 2).reshape(-1, c * k * k))
+    X.backward(torch.ones_like(X))
+    fold = torch.nn.functional.fold(torch.ones_like(want), output_size=(h, w), kernel_size=k, padding=pad, stride=stride)
+    assert torch.equal(x.grad, fold)
