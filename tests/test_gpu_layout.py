@@ -59,7 +59,8 @@ def test_fold_many_pixels(b, c, h, w, k, stride, pad):
         assert torch.equal(got[first:first + 2], want)
 
 
-@pytest.mark.parametrize("shape,stride", [((3, 40, 8, 6), 1), ((3, 40, 8, 6), 2), ((2, 2, 2049, 2048), 2)])
+@pytest.mark.parametrize("shape,stride", [((3, 40, 8, 6), 1), ((3, 40, 8, 6), 2), ((50, 65, 26, 25), 1),
+                                          ((2, 2, 2049, 2048), 2)])
 @pytest.mark.parametrize("layout", ["innermost", "misaligned", "transposed", "part"])
 def test_unfold_of_any_layout(shape, stride, layout):
     """Activations with their channels innermost (the library's own transposition where it takes the
