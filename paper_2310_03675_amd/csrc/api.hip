@@ -398,13 +398,15 @@ size_t partial_bytes(int64_t RA, int64_t RB, int64_t D, int64_t s)
 int run_planned_gemm(hdqt::GemmArgs g, void* ws, size_t ws_bytes, hipStream_t stream)
 {
     hipError_t e;
+    // (asked for also where the small products' kernel then does without: which one multiplies is
+    // not the caller's to know)
+    if (g.splits > 1 && (!ws || ws_bytes < (size_t)g.splits * (size_t)(g.RA * g.RB) * sizeof(int32_t)))
+        return HDQT_EWORKSPACE;
     if (hdqt::gemm_small_eligible(g)) {
         e = hdqt::launch_gemm_small(&g, 1, stream);
         return e == hipSuccess ? HDQT_OK : hip_fail(e);
     }
     if (g.splits > 1) {
-        if (!ws || ws_bytes < (size_t)g.splits * (size_t)(g.RA * g.RB) * sizeof(int32_t))
-            return HDQT_EWORKSPACE;
         g.partial = static_cast<int32_t*>(ws);
         // A part of few tiles has totals of 16 bits: slices of half the bytes (the matrix-core
         // kernel's packed-code instances write them, the many-slices pass reads them).

@@ -140,6 +140,10 @@ def test_gemm_codes_argument_errors():
     assert rc(D=96, n=64) == -3
     assert rc(a=40) == -5
     assert rc(s=0) == -6
+    # a long contraction of few outputs asks for a workspace, whichever kernel then multiplies it
+    for RA, RB, D in ((64, 64, 2048), (512, 512, 4608), (64, 96, 20000)):
+        assert lib.hdqt_gemm_codes_workspace_size(RA, RB, D, 32) > 0
+        assert rc(RA=RA, RB=RB, D=D, n=32) == E["HDQT_EWORKSPACE"]
 
 
 def test_strerror_texts():
