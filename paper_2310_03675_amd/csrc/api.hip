@@ -251,8 +251,9 @@ int run_quantize_set(const QuantSet& s, void* records, size_t record_bytes, hipS
     hdqt::QuantArgs alone[hdqt::kMaxAny];
     hdqt::AnyBatch any{};
     int n_dual = 0, n_alone = 0;
+    bool fits = true;        // (2^31 workgroups: tensors of more than a card's memory)
     auto place = [&](const hdqt::QuantArgs& q) {
-        if (small || q.rows * q.cols <= kAnyPair || !hdqt::quantize_fast_eligible(q)) hdqt::plan_any(q, &any);
+        if (small || q.rows * q.cols <= kAnyPair || !hdqt::quantize_fast_eligible(q)) fits = hdqt::plan_any(q, &any) && fits;
         else alone[n_alone++] = q;
     };
     for (int k = 0; k < s.n_both; ++k) {
@@ -266,6 +267,7 @@ int run_quantize_set(const QuantSet& s, void* records, size_t record_bytes, hipS
         }
     }
     for (int k = 0; k < s.n_one; ++k) place(s.one[k]);
+    if (!fits) return HDQT_EINVAL_DIM;
 
     // maxima side by side, and nothing to clear, if every tensor has few enough workgroups
     bool dense = n_alone == 0;

@@ -220,6 +220,16 @@ def test_layer_step_argument_errors():
     assert rc(G=C.c_void_p(0x1004)) == E["HDQT_EALIGN"]
 
 
+def test_tensors_of_more_workgroups_than_a_launch_counts():
+    """Six code sets of 2^40 values each: within the limits of each tensor, together more workgroups than
+    the launch that would make them all counts.  Refused before anything is launched."""
+    side = (1 << 20) - 1         # (odd, so that no tuned kernel takes a part of them)
+    p = _cparams()
+    rc = B.load().hdqt_layer_step(FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, side, side, side, C.byref(p), C.byref(p), C.byref(p),
+                                  FAKE, 1 << 62, None)
+    assert rc == E["HDQT_EINVAL_DIM"]
+
+
 def test_layer_fwd_bwd_argument_errors():
     lib = B.load()
     M, K, N = 256, 128, 64
