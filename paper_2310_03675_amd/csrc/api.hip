@@ -229,8 +229,29 @@ hdqt::QuantArgs half_of(const hdqt::DualArgs& d, int axis)
 constexpr int64_t kAnySet = (int64_t)1 << 22;
 // Elements up to which a pair that has a tuned single-axis kernel joins the any-shape pairs of the
 // set, which saves the two launches of its own: G of a 131072 x 27 x 64 step (8.4 M) 86.5 / 80.1,
-// of 8192 x 1000 x 300 142.8 / 119.4; X of 2048 x 4608 x 512 at order 256 (9.4 M) 154.0 / 163.1.
+// of 8192 x 1000 x 300 142.8 / 119.4; both operands of 2816 x 2816 x 2816 (7.9 M each) 86.3 / 83.5.
 constexpr int64_t kAnyPair = (int64_t)1 << 23;
+// The same along axis 0 with orders above 64, where the any-shape kernel pairs waves through LDS
+// (the tuned kernel takes 16.5 us at least, 21 with stochastic rounding).  At order 256: X of a
+// forward call of 2048 x 1152 x 128 (2.4 M) 35.4 / 29.7, of 65536 x 64 x 64 (4.2 M) 40.3 / 42.4, of
+// 16384 x 512 x 64 (8.4 M) 53.4 / 71.0; stochastically, G of a backward call of 65536 x 64 x 64
+// 59.5 / 56.5, a 12288 x 512 tensor (6.3 M) on both axes 45.6 / 50.8.
+constexpr int64_t kAnyDeep = (int64_t)7 << 19, kAnyDeepStochastic = (int64_t)5 << 20;
+// Workgroups (2048 values) up to which a pair goes there although no other tensor shares the
+// launches.  Up to kDenseMost the record need not be cleared: 4096 x 512 along axis 0 11.5 / 10.8, but
+// 6144 x 512 13.4 / 14.9 and 4096 x 2048 20.2 / 23.7.  Along axis 0 with stochastic rounding a little
+// more: G of a 5312 x 3520 x 512 layer without input gradient (1328) 53.8 / 51.9, 8192 x 512 (2048)
+// 15.9 / 17.7.  Half of it with orders above 64 along axis 0 (4096 x 512 16.7 / 18.0), and where a
+// tensor with launches of its own has the records cleared anyway.
+constexpr int64_t kAnyLone = hdqt::kDenseMost, kAnyLoneStochastic = kAnyLone * 11 / 8;
+// Not where the tuned kernel along axis 0, of strips of 64 rows and 128 columns (64, 32 for narrow
+// tensors), has much of a strip or the 16-byte stores of its codes wasted: 5000 x 1000 21.3 / 20.3, with
+// bytes 33.5 / 21.7; G of 24640 x 320 x 192 without input gradient 41.5 / 39.
+bool whole_strips(const hdqt::QuantArgs& q)
+{
+    const int64_t across = q.cols > 96 ? 128 : q.cols > 32 ? 64 : 32, padded = (q.cols + across - 1) / across * across;
+    return q.axis || (q.rows % 64 == 0 && (q.log2n > 6 || 7 * padded <= 8 * q.cols));
+}
 // Elements up to which a tensor rounded stochastically on both axes leaves the two-axis kernel's
 // launch of a layer's tensors (64 values of two random streams a lane: its few waves end last) for
 // the any-shape workgroups beside it: G of 2048 x 4608 x 512 (1 M) 110.7 / 105.1, of 2048 x 1152 x 128
@@ -238,8 +259,8 @@ constexpr int64_t kAnyPair = (int64_t)1 << 23;
 constexpr int64_t kAnyStochastic = (int64_t)1 << 20;
 
 // Quantizes a set: one launch per pass for all tensors that the two-axis and the any-shape kernel
-// take (two for pass 2 where the rounding modes do not go together), two launches per large tensor
-// that has a single-axis kernel.  `records`, `record_bytes`: the calibration records of all of them.
+// take (two for pass 2 where the rounding modes do not go together), two launches per tensor that
+// its single-axis kernel is the faster one for.  `records`, `record_bytes`: the calibration records of all of them.
 int run_quantize_set(const QuantSet& s, void* records, size_t record_bytes, hipStream_t stream)
 {
     int64_t work = 0;
@@ -253,7 +274,9 @@ int run_quantize_set(const QuantSet& s, void* records, size_t record_bytes, hipS
     int n_dual = 0, n_alone = 0;
     bool fits = true;        // (2^31 workgroups: tensors of more than a card's memory)
     auto place = [&](const hdqt::QuantArgs& q) {
-        if (small || q.rows * q.cols <= kAnyPair || !hdqt::quantize_fast_eligible(q)) fits = hdqt::plan_any(q, &any) && fits;
+        const bool deep = !q.axis && q.log2n > 6;
+        const int64_t most = !deep ? kAnyPair : q.stochastic ? kAnyDeepStochastic : kAnyDeep;
+        if (q.rows * q.cols <= most || !hdqt::quantize_fast_eligible(q)) fits = hdqt::plan_any(q, &any) && fits;
         else alone[n_alone++] = q;
     };
     for (int k = 0; k < s.n_both; ++k) {
@@ -268,6 +291,15 @@ int run_quantize_set(const QuantSet& s, void* records, size_t record_bytes, hipS
     }
     for (int k = 0; k < s.n_one; ++k) place(s.one[k]);
     if (!fits) return HDQT_EINVAL_DIM;
+    if (any.n == 1 && !n_dual && hdqt::quantize_fast_eligible(any.t[0]) && whole_strips(any.t[0])) {
+        const hdqt::QuantArgs& q = any.t[0];
+        int64_t most = q.axis || !q.stochastic ? kAnyLone : kAnyLoneStochastic;
+        if (n_alone || (!q.axis && q.log2n > 6 && !q.stochastic)) most /= 2;
+        if (any.total > most) {
+            alone[n_alone++] = q;
+            any.n = any.total = 0;
+        }
+    }
 
     // maxima side by side, and nothing to clear, if every tensor has few enough workgroups
     bool dense = n_alone == 0;

@@ -32,6 +32,48 @@ def test_quantize_many_workgroups(rows, cols, axis):
     check_quantize(T, axis, 64, B.Operand(4, ST, 1.0, 2), seed=3)
 
 
+def kernels_of(call):
+    B.profile_enable(True)
+    B.profile_collect()
+    call()
+    torch.cuda.synchronize()
+    B.profile_enable(False)
+    return {name for name, (launches, _) in B.profile_collect().items() if launches}
+
+
+# a tensor without company on both sides of the lines between the any-shape kernel and the tuned ones
+@pytest.mark.parametrize("rows,cols,axis,n,b,rounding,kernel", [
+    (2048, 1024, 1, 64, 4, NE, "any"), (2056, 1024, 1, 64, 4, NE, "row"), (4096, 1024, 1, 64, 8, ST, "row"),
+    (2048, 1024, 0, 64, 4, NE, "any"), (2112, 1024, 0, 64, 4, NE, "col"), (4096, 2048, 0, 256, 4, NE, "col"),
+    (5632, 512, 0, 64, 4, ST, "any"), (5696, 512, 0, 64, 4, ST, "col"), (4096, 640, 0, 128, 4, ST, "any"),
+    (2048, 512, 0, 256, 4, NE, "any"), (2304, 512, 0, 256, 4, NE, "col"), (4096, 768, 0, 256, 8, ST, "col"),
+    (5000, 1000, 0, 64, 8, ST, "any"), (24640, 192, 0, 64, 4, ST, "any"), (24640, 128, 0, 64, 4, ST, "col")])
+def test_lone_tensor_takes_the_faster_kernel(rows, cols, axis, n, b, rounding, kernel):
+    op = B.Operand(b, rounding, 1.0, 4)
+    T = np.random.default_rng(rows + cols).standard_normal((rows, cols)).astype(np.float32)
+    x = dev(T)
+    assert f"fwht_{kernel}_quant" in kernels_of(lambda: B.quantize(x, axis, n, op, 7))
+    check_quantize(T, axis, n, op, seed=7)
+
+
+@pytest.mark.parametrize("kind,M,K,N,n,kernels", [
+    (B.GEMM_FWD, 2048, 2048, 2048, 64, {"any"}), (B.GEMM_FWD, 2048, 4608, 512, 256, {"row", "col"}),
+    (B.GEMM_BWD_WEIGHT, 16384, 512, 64, 256, {"col", "any"}), (B.GEMM_BWD_WEIGHT, 2048, 1152, 128, 256, {"any"})])
+def test_operands_of_a_product_share_launches_where_that_is_faster(kind, M, K, N, n, kernels):
+    layer = workloads.fc_layer(M, K, N, seed=2)
+    P, Q = {B.GEMM_FWD: (layer.X, layer.W), B.GEMM_BWD_WEIGHT: (layer.X, layer.G)}[kind]
+    P, Q = dev(P), dev(Q)
+    prm = B.Params(had_block=n, acc_bits=8, s=32, seed=9, A=B.Operand(4, NE, 1.0, 0), B=B.Operand(4, ST, 1.0, 1))
+    used = kernels_of(lambda: B.gemm(kind, P, Q, M, K, N, prm))
+    assert {k for k in ("any", "row", "col", "dual") if f"fwht_{k}_quant" in used} == kernels
+    out, acc, _ = B.gemm(kind, P, Q, M, K, N, prm, want_acc=True)
+    axis = (1, 0) if kind == B.GEMM_FWD else (0, 0)
+    (qa, sa), (qb, sb) = (B.quantize(t, a, n, o, 9) for t, a, o in zip((P, Q), axis, (prm.A, prm.B)))
+    D = K if kind == B.GEMM_FWD else M
+    want, want_acc = B.gemm_codes(qa, qb, 4, 4, sa, sb, D, B.n_eff(D, n), 8, 32)
+    assert torch.equal(acc, want_acc) and torch.equal(out, want)
+
+
 def test_zeros_and_lone_values():
     for rows, cols in ((65, 33), (64, 64)):
         for axis in (0, 1):
