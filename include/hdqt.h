@@ -233,7 +233,7 @@ int hdqt_transpose(const float *src, int64_t batch, int64_t rows, int64_t cols, 
  *   out     fp32 [RA, RB] (device, may be NULL if acc_out is given)
  *   acc_out int32 [RA, RB] (device, may be NULL)
  *   workspace: hdqt_gemm_codes_workspace_size(RA, RB, D, s) bytes of device memory
- *   (0 for most shapes, then NULL is fine).  Few output tiles with a long
+ *   (0 for most shapes, then NULL is fine; HDQT_EWORKSPACE without it otherwise).  Few output tiles with a long
  *   contraction are split over workgroups along the contraction; every part
  *   writes its totals (sums of whole clamped tiles, so the result is the same)
  *   to a slice of the workspace and a second pass adds the slices.
@@ -400,12 +400,11 @@ int hdqt_conv_fwd(const float *act, const hdqt_conv_t *geo, const float *W, floa
  * order-free) and dequantized once.  dW as for hdqt_layer_bwd.  dAct, bwd_input and W are
  * required.  Workspace: hdqt_layer_bwd_workspace_size(M, K, N, ...) with M = batch*height*width,
  * K = channels*kh*kw.
- * Taken: 4-bit codes, s and N multiples of 32, ceil(N/s) * min(2^(acc_bits-1), 64 s) <= 32767
- * (the folded tile is kept as 16-bit integers); kh, kw odd; width a power
- * of two <= 128; height*width a power of two <= 128, or height*width = 256 with N <= 128
- * and a window of at most nine taps (a workgroup multiplies both halves of an image), or
- * 128/width >= kh image rows per strip.  Anything else: HDQT_EINVAL_GEOMETRY (before anything is launched), and the caller
- * takes hdqt_layer_bwd and folds its dX.
+ * Taken: 4-bit codes, s and N multiples of 32, ceil(N/s) * min(2^(acc_bits-1), 64 s) <= 32767;
+ * kh, kw odd; width a power of two <= 128; height*width a power of two <= 128, or
+ * height*width = 256 with N <= 128 and a window of at most nine taps, or 128/width >= kh.
+ * Anything else: HDQT_EINVAL_GEOMETRY (before anything is launched), and the caller takes
+ * hdqt_layer_bwd and folds its dX.
  */
 int hdqt_conv_bwd(const float *G, const float *W, const void *saved, const hdqt_conv_t *geo,
                   float *dAct, float *dW, int64_t N, const hdqt_params_t *bwd_input,

@@ -447,7 +447,7 @@ int run_planned_gemm(hdqt::GemmArgs g, void* ws, size_t ws_bytes, hipStream_t st
         const int64_t max_prod = ((int64_t)1 << (g.bA - 1)) * ((int64_t)1 << (g.bB - 1));
         const int64_t tile_sum = g.s * max_prod;
         const int64_t per_tile = tile_sum < (int64_t)g.acc_hi + 1 ? tile_sum : (int64_t)g.acc_hi + 1;
-        g.partial16 = (hdqt::gemm_fast_eligible(g) && g.bA <= 4 && !g.fold &&
+        g.partial16 = (hdqt::gemm_fast_eligible(g) && g.bA <= 4 &&
                        per_tile * g.tiles_per_split <= 32767 &&
                        hdqt::reduce_takes_slices16(g.splits, g.RA * g.RB)) ? 1 : 0;
         e = hdqt::launch_gemm(g, stream);
@@ -1482,9 +1482,9 @@ int hdqt_gemm_fwd_static(const float* X, const float* W, float* Z, int64_t M, in
     if (L.total > kStaticScratchBytes) return HDQT_ESCRATCH;
     void* ptr = static_scratch();
     if (!ptr) return HDQT_EHIP;
-    // run_gemm clears the calibration records with a kernel before anything reads them, and
-    // writes every code byte that the matmul reads: what an earlier call left behind in the
-    // array is never seen.
+    // run_gemm writes every word of the calibration records that it reads, or clears them with a
+    // kernel first, and every code byte that the matmul reads: what an earlier call left behind in
+    // the array is never seen.
     return run_gemm(HDQT_GEMM_FWD, X, W, Z, M, K, N, params, acc_out, ptr, kStaticScratchBytes, stream);
 }
 

@@ -1238,6 +1238,8 @@ bool sat16_path(const GemmArgs& g, GemmArgs* plan = nullptr)
 
 } // namespace
 
+// (g.fold: asked by gemm_fold_plan, whose kernel has the packed-code clamps of this one in tiles of whole
+// steps; a product that is folded never comes to this file)
 bool gemm_fast_eligible(const GemmArgs& g)
 {
     if ((g.bA > 4) != (g.bB > 4)) return false;      // packed or bytes, the same on both sides
@@ -1276,10 +1278,9 @@ bool gemm_fast_eligible(const GemmArgs& g)
     return per_tile * g.tiles_per_split < ((int64_t)1 << 22);
 }
 
-// Whether the kernel applies g.mask_src itself: the instances of the
-// packed-code epilogues HDQT_LAUNCH_I4 covers with a whole, unsplit output.  Everything else
-// is masked by a pass of its own after the matmul (or by the pass that adds a split
-// contraction's slices).
+// Whether the kernel applies g.mask_src itself: every whole, unsplit fp32 output, in the masked
+// instances of HDQT_LAUNCH_I4 or in the FLEX ones (see `flexible`).  A split contraction is masked by
+// the pass that adds its slices, what the generic kernel multiplies by a pass of its own.
 bool gemm_fast_masks(const GemmArgs& g)
 {
     if (!g.mask_src || !g.out || !gemm_fast_eligible(g)) return false;
@@ -1291,7 +1292,6 @@ bool gemm_fast_masks(const GemmArgs& g)
 // code.
 static bool flexible(const GemmArgs& g)
 {
-    if (g.fold) return false;
     if (g.D % (g.bA > 4 ? 4 : 8) != 0) return true;
     return (g.out_bf16 || (g.mask_src && g.splits == 1)) && (g.bA > 4 || g.s == 16 || sat16_path(g));
 }
@@ -1300,7 +1300,7 @@ static bool flexible(const GemmArgs& g)
 // (packed codes, fp32 / int32 output, the epilogues of the paper's settings).
 static bool narrow_tiles(const GemmArgs& g)
 {
-    if (g.RB > 64 || g.fold || g.out_bf16 || g.bA > 4 || g.s == 16 || g.mask_src) return false;
+    if (g.RB > 64 || g.out_bf16 || g.bA > 4 || g.s == 16 || g.mask_src) return false;
     return !sat16_path(g);
 }
 
@@ -1319,7 +1319,7 @@ static bool narrow_tiles(const GemmArgs& g)
 // six interleaved runs; with fewer column tiles (576 or 320 columns) it is 5 to 7 % slower.
 static bool cert_tiles(const GemmArgs& g, int64_t n_ct)
 {
-    if (g.fold || g.out_bf16 || g.bA > 4 || g.bB > 4 || g.mask_src || flexible(g)) return false;
+    if (g.out_bf16 || g.bA > 4 || g.bB > 4 || g.mask_src || flexible(g)) return false;
     if (g.acc_hi != 127 || g.s != 32 || g.tiles_per_split > 255) return false;
     if (g.tiles_per_split * g.s > 4 * KS_LONG) return true;
     return g.stream_out && n_ct >= 8 && g.D >= KS_LONG;
@@ -1338,7 +1338,7 @@ static bool cert16_tiles(const GemmArgs& g)
 // |value| < 2^22), at most kReqTable tiles per part, tile sums times 256 inside int32.
 bool gemm_requant_fast_eligible(const GemmArgs& g, int acc_bits)
 {
-    if (g.bA > 4 || g.bB > 4 || g.fold || g.out_bf16 || g.mask_src) return false;
+    if (g.bA > 4 || g.bB > 4 || g.out_bf16 || g.mask_src) return false;
     if (g.D % 8 != 0 || g.s % KSTEP != 0) return false;
     if (acc_bits < 2 || acc_bits > 16) return false;
     if (g.RB > ((int64_t)1 << 21)) return false;

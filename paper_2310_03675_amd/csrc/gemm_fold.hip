@@ -211,8 +211,9 @@ __global__ __launch_bounds__(64 * kWaves, 4) void gemm_fold_kernel(GemmArgs g)
 
 } // namespace
 
-// Geometries the folded product takes: odd windows of at most 128 taps; W a power of two up to 128;
-// images of a power of two up to 128 pixels, or so wide that 128 pixels hold the window's rows.
+// What hdqt_conv_bwd promises to take, which is less than the kernel above could: it divides by any width
+// and has neither row tiles nor 16-bit totals.  A caller takes a refusal as the sign to unfold, and the
+// unfolded gradient is rounded term by term; which layers that concerns is part of their results.
 bool gemm_fold_plan(GemmArgs* g, int64_t batch, int C, int H, int W, int kh, int kw)
 {
     auto pow2 = [](int64_t v) { return v > 0 && (v & (v - 1)) == 0; };
@@ -220,8 +221,8 @@ bool gemm_fold_plan(GemmArgs* g, int64_t batch, int C, int H, int W, int kh, int
     if (!pow2(W) || W > 128 || kh * kw > 128 || kh > 15 || kw > 15) return false;
     if (g->RA != batch * (int64_t)H * W || g->RB != (int64_t)C * kh * kw || g->D % kStep != 0) return false;
     if (batch * (int64_t)C * H * W >= ((int64_t)1 << 40)) return false;
-    // whole images of up to 128 pixels; else strips of 128 pixels (256 where that is an image) that
-    // hold the window's rows, at most 65535 of either
+    // images of a power of two up to 128 pixels, images of 256, or rows so short that 128 pixels hold the
+    // window's, and at most 65535 such pieces
     const int64_t hw = (int64_t)H * W;
     int64_t parts;
     if (hw <= 128) {
@@ -235,7 +236,7 @@ bool gemm_fold_plan(GemmArgs* g, int64_t batch, int C, int H, int W, int kh, int
         parts = batch * ((H + rows_out - 1) / rows_out);
     }
     if (parts > 65535) return false;
-    // a pixel's and a column's total fits 16 bits, the kh * kw of them (times 256) 32
+    // a pixel's and a column's total fits 16 bits; the kh * kw of them, times 256, then fit the kernel's 32
     const int64_t tile_sum = g->s * (((int64_t)1 << (g->bA - 1)) * ((int64_t)1 << (g->bB - 1)));
     const int64_t per_tile = tile_sum < (int64_t)g->acc_hi + 1 ? tile_sum : (int64_t)g->acc_hi + 1;
     if (per_tile > 32767 || per_tile * g->n_tiles > 32767) return false;
