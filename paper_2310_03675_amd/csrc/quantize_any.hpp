@@ -50,14 +50,18 @@ __device__ __forceinline__ void random8(const QuantArgs& q, uint64_t e, uint32_t
     for (int k = 0; k < 4; ++k) r[k] = __builtin_amdgcn_alignbyte(y[k + 1], y[k], 2 * (sh & 1));
 }
 
-// eight codes of one line, `count` of them inside it (the others are zeros)
+// eight codes of one line, `count` of them inside it (zero bits behind them)
 __device__ __forceinline__ void store8(const QuantArgs& q, const uint32_t cw[8], uint8_t* dst, int count)
 {
     if (q.b <= 4) {
-        const uint32_t w = pack_nibbles(cw);
-        if (count >= 8) reinterpret_cast<Dword*>(dst)->v = w;
-        else
+        uint32_t w = pack_nibbles(cw);
+        if (count >= 8) {
+            reinterpret_cast<Dword*>(dst)->v = w;
+        } else {
+            // (a zero behind the line is no zero where the step's inverse is infinite)
+            w &= (1u << (4 * count)) - 1u;
             for (int k = 0; 2 * k < count; ++k) dst[k] = (uint8_t)(w >> (8 * k));
+        }
     } else {
         const uint32_t w0 = pack_bytes(cw), w1 = pack_bytes(cw + 4);
         if (count >= 8) {

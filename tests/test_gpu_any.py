@@ -140,6 +140,20 @@ def test_values_that_are_not_finite(rows, cols, values):
                 assert np.array_equal(host(codes), capi.pack_codes(want, b))
 
 
+@pytest.mark.parametrize("rows,cols", [(3, 5), (65, 33), (561, 11)])
+def test_pad_nibble_when_the_inverse_of_the_step_overflows(rows, cols):
+    """A maximum below 2^-125: one over the step is infinite, and zero times it no number.  The half byte
+    behind the last code of an odd line is zero all the same."""
+    T = (np.random.default_rng(rows).standard_normal((rows, cols)) * 1e-39).astype(np.float32)
+    T[0, 0] = 0.0
+    for axis in (0, 1):
+        want, want_scale = reference_codes(T, axis, 1, 4)
+        codes, scale = B.quantize(dev(T), axis, 1, B.Operand(4))
+        got = host(codes)
+        assert not (got[:, -1] >> 4).any()
+        assert host(scale)[0] == want_scale and np.array_equal(got, capi.pack_codes(want, 4))
+
+
 @pytest.mark.parametrize("M,K,N,n,dx", [(200, 132, 70, 64, True), (64, 256, 128, 16, True), (128, 561, 11, 64, True),
                                         (131, 27, 64, 32, False), (1024, 1152, 100, 64, True),
                                         (2048, 640, 70, 64, False), (1088, 576, 24, 64, True), (512, 640, 384, 256, True)])
