@@ -325,8 +325,8 @@ __device__ __forceinline__ int clamp3(int v, int lo, int hi)
 // of a tile (all of a wave's values in flight together) and the output is written where it is
 // positive, +0 elsewhere.  An instance of its own: the 32 values cost registers.
 // FLEX: rows of codes that are no whole dwords (D no multiple of 8, or of 4 with a byte per
-// code), and the outputs the other instances of an epilogue do not write (bfloat16, masked):
-// chosen at run time, element by element.  What it replaces there is the generic kernel of
+// code), and the bfloat16 outputs the other instances of an epilogue do not write: chosen at
+// run time, element by element.  What it replaces there is the generic kernel of
 // gemm.hip, which fetches, sign-extends and pads code by code and is bound by that: a forward
 // call of 2947 x 561 x 561 in tiles of 32, quantization included, 178 -> 38 us; a square one
 // of 3309 rows 2430 -> 306 us.  One dword more per unit and four byte shifts are what the
@@ -1031,7 +1031,6 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
         float* ob = (g.splits == 1 && g.out) ? g.out + tile_off : nullptr;
         // (the narrow output has kernel instances of its own: its epilogue costs the others registers)
         uint16_t* hb = ((BF16 || FLEX) && g.splits == 1 && g.out_bf16) ? g.out_bf16 + tile_off : nullptr;
-        const float* fm = (FLEX && g.mask_src) ? g.mask_src + tile_off : nullptr;
         // bfloat16 output of an interior tile with an even row length: lanes l and l ^ 1 hold
         // neighbouring columns and trade their values, so that every lane stores one dword
         const bool pair_bf16 = BF16 && hb && interior && (g.RB % 2 == 0);
@@ -1093,7 +1092,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
         // nothing is tested per element, so the 32 stores of a wave are one run of
         // conversions and stores (with the tests, each store sat in an exec-masked block of
         // its own behind its own branches).
-        const bool plain_out = !MASK && !fm && interior && ob && !ab && !ab16 && !((BF16 || FLEX) && hb);
+        const bool plain_out = !MASK && interior && ob && !ab && !ab16 && !((BF16 || FLEX) && hb);
         if (plain_out) {
 #pragma unroll
             for (int a = 0; a < RS; ++a)
@@ -1149,7 +1148,6 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
                             // would drop the streaming hint)
                             float f = (float)v * dq;
                             if constexpr (MASK) f = mk[a][c][r] > 0.0f ? f : 0.0f;
-                            if (FLEX && fm) f = (fm + uo)[lane_off] > 0.0f ? f : 0.0f;
                             if (STREAM) __builtin_nontemporal_store(f, &(ob + uo)[lane_off]);
                             else (ob + uo)[lane_off] = f;
                         }
@@ -1278,22 +1276,24 @@ bool gemm_fast_eligible(const GemmArgs& g)
     return per_tile * g.tiles_per_split < ((int64_t)1 << 22);
 }
 
-// Whether the kernel applies g.mask_src itself: every whole, unsplit fp32 output, in the masked
-// instances of HDQT_LAUNCH_I4 or in the FLEX ones (see `flexible`).  A split contraction is masked by
-// the pass that adds its slices, what the generic kernel multiplies by a pass of its own.
+// Whether the kernel applies g.mask_src itself: whole, unsplit fp32 outputs of the packed-code epilogues
+// HDQT_LAUNCH_I4 has masked instances of.  A split contraction is masked by the pass that adds its
+// slices, everything else by a pass of its own.  (In the epilogue of the FLEX instances, element by
+// element, the mask costs more than that pass: 39040 x 1024 x 128 with a byte per code 218 / 141 us,
+// 34688 x 1152 x 22 207 / 118, 3456 x 1152 x 129 28.7 / 27.1.)
 bool gemm_fast_masks(const GemmArgs& g)
 {
     if (!g.mask_src || !g.out || !gemm_fast_eligible(g)) return false;
-    return g.splits == 1 && !g.out_bf16;
+    if (g.splits > 1 || g.out_bf16 || g.bA > 4 || g.s == 16 || g.D % 8 != 0) return false;
+    return !sat16_path(g);
 }
 
-// Rows of codes that are no whole dwords, and outputs that only some epilogues have instances
-// for: bfloat16 and masked ones with tiles of 16, with the int16 saturation or with a byte per
-// code.
+// Rows of codes that are no whole dwords, and the bfloat16 outputs that only some epilogues have
+// instances for: with tiles of 16, with the int16 saturation or with a byte per code they have none.
 static bool flexible(const GemmArgs& g)
 {
     if (g.D % (g.bA > 4 ? 4 : 8) != 0) return true;
-    return (g.out_bf16 || (g.mask_src && g.splits == 1)) && (g.bA > 4 || g.s == 16 || sat16_path(g));
+    return g.out_bf16 && (g.bA > 4 || g.s == 16 || sat16_path(g));
 }
 
 // Outputs of at most 64 columns take the 128 x 64 workgroup tile where such instances exist
@@ -1389,13 +1389,14 @@ hipError_t launch_gemm_fast(const GemmArgs& g_in, hipStream_t stream)
     g.acc_hi_scaled = hi > INT32_MAX ? INT32_MAX : (int)hi;
     // Short contractions (at most two stages per output tile): a workgroup walks along
     // its row strip of the output as long as that leaves about two workgroups per CU.
+    const bool masked = gemm_fast_masks(g);
+    if (!masked) g.mask_src = nullptr;       // (applied by a later pass)
     const bool flex = flexible(g);
     const bool narrow = narrow_tiles(g);
     int64_t n_ct = (g.RB + BN - 1) / BN, n_rt = (g.RA + BM - 1) / BM;
     if (narrow) n_ct = (g.RB + 63) / 64;
     const bool s32 = sat8_path(g) && g.s == 32;
     const bool sat16 = sat16_path(g, &g);
-    const bool masked = gemm_fast_masks(g);
     const int64_t KS = KS_LONG;
     const int64_t stages = (g.tiles_per_split * g.s + KS - 1) / KS;
     int64_t gx = n_ct;

@@ -152,3 +152,21 @@ def test_relu_linear_module_matches_separate_rectifier():
     torch.cuda.synchronize()
     assert torch.equal(z1, z2) and torch.equal(fused.weight.grad, plain.weight.grad)
     assert torch.equal(pre1.grad, pre2.grad)
+
+
+@pytest.mark.parametrize("N,s,a,b,own", [(128, 32, 8, 4, False), (128, 32, 16, 8, True), (128, 32, 12, 4, True),
+                                         (96, 16, 8, 4, True), (129, 32, 8, 4, True)])
+def test_masks_without_an_instance_are_a_pass_of_their_own(N, s, a, b, own):
+    """Byte codes, the int16 saturation, tiles of 16 and ragged rows have no masked epilogue."""
+    M, K = 4096, 640
+    layer = workloads.fc_layer(M, K, N, seed=3)
+    X, p = torch.relu(layer.X), params(32, s, a, b)
+    G, W, x = dev(layer.G), dev(layer.W), dev(X)
+    plain, _, _ = B.gemm(BWI, G, W, M, K, N, p)
+    B.profile_enable(True)
+    B.profile_collect()
+    got, _, _ = B.gemm(BWI, G, W, M, K, N, p, mask=x)
+    torch.cuda.synchronize()
+    B.profile_enable(False)
+    assert ("relu_mask" in B.profile_collect()) == own
+    assert torch.equal(got, torch.where(x > 0, plain, torch.zeros_like(plain)))
