@@ -407,8 +407,12 @@ hdqt::GemmArgs plan_gemm(const void* qA, const void* qB, int bA, int bB, const f
     // someone reads it; written normally it would sit there dirty and be written back
     // in the middle of the next kernel's reads (measured: the pass over X that follows
     // the input gradient of the 65536 x 1152 layer takes 90 us instead of 53 us).
-    const int64_t out_elem = out ? (int64_t)sizeof(float) : (int64_t)sizeof(uint16_t);
-    g.stream_out = (RA * RB * out_elem >= ((int64_t)128 << 20)) ? 1 : 0;
+    // Rows that are no whole 128-byte lines are the exception: a streaming store that ends inside
+    // a line does not wait for the neighbour that fills it (68160 x 1150 x 128 264 us, written
+    // normally 122, 32000 x 2298 x 48 164 / 54; rows of whole half lines lose it from 512 MB on:
+    // 68992 x 1136 x 128, 300 MB, 117 / 110, twice that 214 / 220).
+    const int64_t row = RB * (out ? (int64_t)sizeof(float) : (int64_t)sizeof(uint16_t)), out_bytes = RA * row;
+    g.stream_out = row % 128 == 0 ? out_bytes >= ((int64_t)128 << 20) : row % 64 == 0 && out_bytes >= ((int64_t)512 << 20);
     g.tiles_per_split = g.splits > 1 ? part_codes / g.s : g.n_tiles;
     g.splits = (int)((g.n_tiles + g.tiles_per_split - 1) / g.tiles_per_split);
     return g;
@@ -1120,7 +1124,7 @@ int run_layer_step(const float* X, const hdqt_conv_t* geo, const float* W, const
     // lines it is written back under the kernels that follow -- forward 30.1 -> 28.1 us, and
     // the next call's pass over X 66.6 -> 60.8 us.)  The forward call on its own keeps the
     // 128 MB mark: its caller reads Z next.
-    if (M * N * (int64_t)sizeof(float) >= ((int64_t)16 << 20)) g_fwd.stream_out = 1;
+    if (M * N * (int64_t)sizeof(float) >= ((int64_t)16 << 20) && N % 32 == 0) g_fwd.stream_out = 1;
     // The weight gradient goes before the input gradient: its operand, X's codes along M, is the
     // older data in the memory-side cache; the input gradient's large output comes last.
     PlannedGemm ps[3];

@@ -118,7 +118,7 @@ struct GemmArgs {
     uint32_t* tile_max;     // second reading only: max |tile sum| per tile, zero beforehand
     int req_bits;           // second reading in the matrix-core kernel: a, and the clamp bounds
     float req_lo, req_hi;   // -2^(a-1) and 2^(a-1) - 1, each plus 1.5 * 2^23
-    int stream_out;         // fp32 output too large to stay cached: written with streaming stores
+    int stream_out;         // output too large to stay cached, in whole lines: written with streaming stores
     int profile_tag;        // which matmul of the step this is (timing table only): 0 none, 1 + kind
     int splits;             // workgroups sharing one output tile along the contraction
     int64_t tiles_per_split;

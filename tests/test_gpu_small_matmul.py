@@ -2,6 +2,7 @@
 blocks, the contraction shared by a workgroup's waves) and those just behind it, which go to the
 large tiles: long contractions, and outputs of many blocks."""
 import pytest
+import torch
 
 from paper_2310_03675_amd import binding as B  # noqa: F401
 from test_gpu_parity import check_gemm_codes
@@ -49,6 +50,23 @@ def test_narrow_outputs_with_ragged_rows(RB, D):
 
 
 def test_tiles_of_64_bytes_streamed_output():
-    """Outputs of 128 MB take the instances with streaming stores, whose waves are one block high."""
+    """Outputs of 128 MB in whole lines take the instances with streaming stores, whose waves are one
+    block high; in rows that end inside a line, the others."""
     for a in (8, 16):
+        check_gemm_codes(8200, 4096, 192, 8, 8, 64, a, extreme=0.3)
         check_gemm_codes(8200, 4100, 192, 8, 8, 64, a, extreme=0.3)
+
+
+@pytest.mark.parametrize("RA,RB", [(33000, 1024), (33000, 1025), (33000, 1040), (16400, 8208)])
+@pytest.mark.parametrize("D,s,a", [(64, 32, 8), (48, 48, 8), (128, 64, 16), (27, 32, 8)])
+def test_large_outputs_in_whole_and_broken_lines(RA, RB, D, s, a):
+    """Either way of storing a large output against the same product in pieces that stay in the caches."""
+    print(f"large outputs {RA}x{RB}x{D} s={s} a={a}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(RB)
+    pitch = B.codes_pitch(D, 4)
+    qA, qB = (torch.randint(0, 256, (n, pitch), dtype=torch.uint8, device="cuda", generator=g) for n in (RA, RB))
+    one = torch.full((1,), 0.5, device="cuda")
+    out, _ = B.gemm_codes(qA, qB, 4, 4, one, one, D, 1, a, s, want_acc=False)
+    for r in range(0, RA, 8192):
+        part, _ = B.gemm_codes(qA[r:r + 8192].contiguous(), qB, 4, 4, one, one, D, 1, a, s, want_acc=False)
+        assert torch.equal(out[r:r + 8192], part)
