@@ -408,9 +408,9 @@ hdqt::GemmArgs plan_gemm(const void* qA, const void* qB, int bA, int bB, const f
     // in the middle of the next kernel's reads (measured: the pass over X that follows
     // the input gradient of the 65536 x 1152 layer takes 90 us instead of 53 us).
     // Rows that are no whole 128-byte lines are the exception: a streaming store that ends inside
-    // a line does not wait for the neighbour that fills it (68160 x 1150 x 128 264 us, written
-    // normally 122, 32000 x 2298 x 48 164 / 54; rows of whole half lines lose it from 512 MB on:
-    // 68992 x 1136 x 128, 300 MB, 117 / 110, twice that 214 / 220).
+    // a line does not wait for the neighbour that fills it (input gradients of 31936 x 1150 x 128
+    // 140 us, written normally 53, 16000 x 2298 x 48 129 / 42; rows of whole half lines lose it from
+    // 512 MB on: 69248 x 1136 x 128 128 / 118, 138496 x 1136 x 128, 600 MB, 214 / 220).
     const int64_t row = RB * (out ? (int64_t)sizeof(float) : (int64_t)sizeof(uint16_t)), out_bytes = RA * row;
     g.stream_out = row % 128 == 0 ? out_bytes >= ((int64_t)128 << 20) : row % 64 == 0 && out_bytes >= ((int64_t)512 << 20);
     g.tiles_per_split = g.splits > 1 ? part_codes / g.s : g.n_tiles;
