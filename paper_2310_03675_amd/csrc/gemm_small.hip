@@ -289,6 +289,26 @@ int mode_of(const GemmArgs& g)
 // the number of workgroups (65536 x 64 x 27 8.0 / 14.6).  Where the other kernel does not split the
 // contraction it is ahead earlier (4096 x 512 x 256 8.0 / 10.0), except for ragged rows
 // (2947 x 561 x 561 16.7 / 13.7, 4096 x 256 x 561 19.6 / 9.1; but 32768 x 64 x 27 7.8 / 8.7).
+//
+// Inside these lines the other kernel is still ahead of long chains of few workgroups or of one too
+// many per CU (224 x 256 x 4480 in tiles of 16 13.8 / 20.2; 288 blocks of bytes, 2299 x 128 x 3712, 19.7 /
+// 31.0), where that kernel splits the contraction and these do not take the paper's clamp: both times
+// are estimated, in us, and the other kernel taken where it is clearly ahead.  The constants fit 6037
+// products of all kinds and random sizes inside the lines, of which the lines alone put 110 on a kernel
+// that is more than 15 % slower (of those that take over 10 us); with the estimates 47, and 3 are new.
+bool estimated_faster(const GemmArgs& g, int64_t blocks, int64_t steps)
+{
+    const bool wide = g.bA > 4, half = g.s < kStep, ragged = g.D % (wide ? 4 : 8) != 0;
+    const double chain = (double)(steps * ((blocks + 255) / 256)) * (g.pitchA % 4 != 0 ? 1.35 : 1.0);
+    const double here = 5.5 + chain * (wide || half ? 0.075 : 0.043);
+    const int64_t tiles = ((g.RA + 127) / 128) * ((g.RB + 127) / 128), stages = (steps + 3) / 4;
+    const int64_t rounds = (tiles * g.splits + 511) / 512, in_a_row = (stages + g.splits - 1) / g.splits * rounds;
+    const double stage = (half ? 1.7 : wide ? 0.65 : 0.47) + (!ragged ? 0.0 : half ? 1.2 : 0.2);
+    // (two launches, and every part's slice written and read)
+    const double there = 9.4 + (double)in_a_row * stage + 0.4e-6 * (double)g.splits * (double)(g.RA * g.RB) * sizeof(int32_t);
+    return here <= 1.05 * there;
+}
+
 bool small_enough(const GemmArgs& g)
 {
     const bool wide = g.bA > 4;
@@ -296,8 +316,10 @@ bool small_enough(const GemmArgs& g)
     const int64_t cost = blocks * steps * (wide || g.s < kStep ? 2 : 1);
     const bool ragged = g.D % (wide ? 4 : 8) != 0 && steps >= 8;
     if (g.D > 4608 || (g.RA + g.RB) * (g.pitchA + g.pitchB) >= ((int64_t)1 << 31)) return false;
-    if (g.splits > 1) return blocks <= 2048 && cost <= 73728;
-    return blocks <= (ragged ? 2048 : 512) && cost <= 36864;
+    if (g.splits > 1 ? blocks > 2048 || cost > 73728 : blocks > (ragged ? 2048 : 512) || cost > 36864) return false;
+    // (in the paper's setting, and where the other kernel does not split the contraction, the lines are
+    // good enough and the estimates are not: 320 x 1024 x 4384, 2947 x 561 x 561)
+    return mode_of(g) == MODE_SAT8 || g.splits == 1 || estimated_faster(g, blocks, steps);
 }
 
 } // namespace

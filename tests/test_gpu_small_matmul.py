@@ -38,6 +38,14 @@ def test_long_contractions_on_large_tiles(D):
     both_kinds(131, 70, D, 0.3)
 
 
+@pytest.mark.parametrize("RA,RB,D,b,s,a", [(224, 256, 4480, 4, 16, 8), (2299, 128, 3712, 8, 64, 16), (288, 1024, 3456, 8, 128, 32),
+                                           (224, 192, 4480, 4, 16, 8), (507, 512, 4240, 8, 16, 16), (1504, 192, 4480, 4, 256, 16),
+                                           (539, 512, 3707, 8, 32, 16), (64, 192, 4235, 8, 256, 16)])
+def test_long_chains_around_the_estimates(RA, RB, D, b, s, a):
+    """Products inside the small kernel's lines, on both sides of what its estimate gives away."""
+    check_gemm_codes(RA, RB, D, b, b, s, a, extreme=0.2)
+
+
 @pytest.mark.parametrize("D", [27, 64, 100, 129, 520])
 def test_many_blocks_on_large_tiles(D):
     both_kinds(1100, 1000, D, 0.2)
