@@ -237,6 +237,10 @@ constexpr int64_t kAnyPair = (int64_t)1 << 23;
 // 16384 x 512 x 64 (8.4 M) 53.4 / 71.0; stochastically, G of a backward call of 65536 x 64 x 64
 // 59.5 / 56.5, a 12288 x 512 tensor (6.3 M) on both axes 45.6 / 50.8.
 constexpr int64_t kAnyDeep = (int64_t)7 << 19, kAnyDeepStochastic = (int64_t)5 << 20;
+// Elements of two such pairs that make up a set, up to which they go there together (stochastic rounding at
+// seven tenths): X and G of a weight gradient of 13056 x 256 x 256 (6.7 M) 50.6 / 58.5, of 6144 x 512 x 768
+// (3.1 M and, stochastically, 4.7 M) 62.0 / 68.5, of 16384 x 128 x 192 (2.1 and 3.1 M) 52.6 / 46.2.
+constexpr int64_t kAnyDeepTwo = (int64_t)5 << 20;
 // Workgroups (2048 values) up to which a pair goes there although no other tensor shares the
 // launches.  Up to kDenseMost the record need not be cleared: 4096 x 512 along axis 0 11.5 / 10.8, but
 // 6144 x 512 13.4 / 14.9 and 4096 x 2048 20.2 / 23.7.  Along axis 0 with stochastic rounding a little
@@ -272,10 +276,10 @@ int run_quantize_set(const QuantSet& s, void* records, size_t record_bytes, hipS
     hdqt::QuantArgs alone[hdqt::kMaxAny];
     hdqt::AnyBatch any{};
     int n_dual = 0, n_alone = 0;
+    auto deep = [](const hdqt::QuantArgs& q) { return !q.axis && q.log2n > 6; };
     bool fits = true;        // (2^31 workgroups: tensors of more than a card's memory)
     auto place = [&](const hdqt::QuantArgs& q) {
-        const bool deep = !q.axis && q.log2n > 6;
-        const int64_t most = !deep ? kAnyPair : q.stochastic ? kAnyDeepStochastic : kAnyDeep;
+        const int64_t most = !deep(q) ? kAnyPair : q.stochastic ? kAnyDeepStochastic : kAnyDeep;
         if (q.rows * q.cols <= most || !hdqt::quantize_fast_eligible(q)) fits = hdqt::plan_any(q, &any) && fits;
         else alone[n_alone++] = q;
     };
@@ -294,9 +298,17 @@ int run_quantize_set(const QuantSet& s, void* records, size_t record_bytes, hipS
     if (any.n == 1 && !n_dual && hdqt::quantize_fast_eligible(any.t[0]) && whole_strips(any.t[0])) {
         const hdqt::QuantArgs& q = any.t[0];
         int64_t most = q.axis || !q.stochastic ? kAnyLone : kAnyLoneStochastic;
-        if (n_alone || (!q.axis && q.log2n > 6 && !q.stochastic)) most /= 2;
+        if (n_alone || (deep(q) && !q.stochastic)) most /= 2;
         if (any.total > most) {
             alone[n_alone++] = q;
+            any.n = any.total = 0;
+        }
+    }
+    if (any.n == 2 && !n_dual && !n_alone && deep(any.t[0]) && deep(any.t[1])) {
+        int64_t sum = 0;
+        for (int k = 0; k < 2; ++k) sum += any.t[k].rows * any.t[k].cols * (any.t[k].stochastic ? 7 : 10) / 10;
+        if (sum > kAnyDeepTwo && hdqt::quantize_fast_eligible(any.t[0]) && hdqt::quantize_fast_eligible(any.t[1])) {
+            for (int k = 0; k < 2; ++k) alone[n_alone++] = any.t[k];
             any.n = any.total = 0;
         }
     }

@@ -84,7 +84,8 @@ def test_lone_tensor_takes_the_faster_kernel(rows, cols, axis, n, b, rounding, k
 
 @pytest.mark.parametrize("kind,M,K,N,n,kernels", [
     (B.GEMM_FWD, 2048, 2048, 2048, 64, {"any"}), (B.GEMM_FWD, 2048, 4608, 512, 256, {"row", "col"}),
-    (B.GEMM_BWD_WEIGHT, 16384, 512, 64, 256, {"col", "any"}), (B.GEMM_BWD_WEIGHT, 2048, 1152, 128, 256, {"any"})])
+    (B.GEMM_BWD_WEIGHT, 16384, 512, 64, 256, {"col", "any"}), (B.GEMM_BWD_WEIGHT, 2048, 1152, 128, 256, {"any"}),
+    (B.GEMM_BWD_WEIGHT, 6144, 512, 768, 128, {"col"}), (B.GEMM_BWD_WEIGHT, 16384, 128, 192, 256, {"any"})])
 def test_operands_of_a_product_share_launches_where_that_is_faster(kind, M, K, N, n, kernels):
     layer = workloads.fc_layer(M, K, N, seed=2)
     P, Q = {B.GEMM_FWD: (layer.X, layer.W), B.GEMM_BWD_WEIGHT: (layer.X, layer.G)}[kind]
