@@ -1132,11 +1132,11 @@ int run_layer_step(const float* X, const hdqt_conv_t* geo, const float* W, const
                                      1 + HDQT_GEMM_FWD);
     // Nobody can read Z before the two backward products of this call have run, and those move
     // several times the memory-side cache: from 16 MB on, Z is written with streaming stores
-    // too.  (Measured on the 65536 x 1152 x 128 layer, Z = 33.5 MB: left in the cache as dirty
+    // too, if its rows are whole half lines.  (Measured on the 65536 x 1152 x 128 layer, Z = 33.5 MB: left in the cache as dirty
     // lines it is written back under the kernels that follow -- forward 30.1 -> 28.1 us, and
     // the next call's pass over X 66.6 -> 60.8 us.)  The forward call on its own keeps the
     // 128 MB mark: its caller reads Z next.
-    if (M * N * (int64_t)sizeof(float) >= ((int64_t)16 << 20) && N % 32 == 0) g_fwd.stream_out = 1;
+    if (M * N * (int64_t)sizeof(float) >= ((int64_t)16 << 20) && N % 16 == 0) g_fwd.stream_out = 1;
     // The weight gradient goes before the input gradient: its operand, X's codes along M, is the
     // older data in the memory-side cache; the input gradient's large output comes last.
     PlannedGemm ps[3];
@@ -1151,6 +1151,10 @@ int run_layer_step(const float* X, const hdqt_conv_t* geo, const float* W, const
                              &meta(T_W1)->scale, M, K, N, nI, bwd_input->acc_bits, bwd_input->s, dX, nullptr,
                              1 + HDQT_GEMM_BWD_INPUT),
                    acc(HDQT_GEMM_BWD_INPUT), L.acc_bytes[HDQT_GEMM_BWD_INPUT]};
+    // dX in rows of whole half lines streams from the 128 MB mark on here, where a product on its own
+    // does not: written normally it goes back to memory under the passes that follow (normal / streamed:
+    // 65536 x 1136 x 128 422 / 398 us, 37816 x 1168 x 96 305 / 295, 32768 x 2320 x 256 475 / 447).
+    if (with_dx && K % 16 == 0 && M * K * (int64_t)sizeof(float) >= ((int64_t)128 << 20)) ps[2].g.stream_out = 1;
     return run_planned_gemms(ps, n, stream);
 }
 
