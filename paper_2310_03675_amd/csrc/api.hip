@@ -489,15 +489,17 @@ struct PlannedGemm { hdqt::GemmArgs g; void* ws; size_t ws_bytes; };
 int run_planned_gemms(const PlannedGemm* ps, int n, hipStream_t stream)
 {
     hdqt::GemmArgs small[hdqt::kMaxSmallBatch];
-    int n_small = 0;
+    int n_small = 0, n_near = 0;
+    for (int k = 0; k < n; ++k) n_near += hdqt::gemm_small_eligible(ps[k].g, false);
+    const bool alone = n_near < 2;
     for (int k = 0; k < n; ++k)
-        if (hdqt::gemm_small_eligible(ps[k].g)) small[n_small++] = ps[k].g;
+        if (hdqt::gemm_small_eligible(ps[k].g, alone)) small[n_small++] = ps[k].g;
     if (n_small) {
         const hipError_t e = hdqt::launch_gemm_small(small, n_small, stream);
         if (e != hipSuccess) return hip_fail(e);
     }
     for (int k = 0; k < n; ++k) {
-        if (hdqt::gemm_small_eligible(ps[k].g)) continue;
+        if (hdqt::gemm_small_eligible(ps[k].g, alone)) continue;
         const int rc = run_planned_gemm(ps[k].g, ps[k].ws, ps[k].ws_bytes, stream);
         if (rc) return rc;
     }

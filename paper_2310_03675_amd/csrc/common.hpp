@@ -204,7 +204,7 @@ bool quantize_dual_eligible(const DualArgs& q);
 // products that cannot fill the chip with large tiles: up to kMaxSmallBatch of them in one launch,
 // never split (gemm_small.hip)
 constexpr int kMaxSmallBatch = 3;
-bool gemm_small_eligible(const GemmArgs& g);
+bool gemm_small_eligible(const GemmArgs& g, bool alone = true);      // alone: no other product in the launch
 hipError_t launch_gemm_small(const GemmArgs* gs, int n, hipStream_t stream);
 bool gemm_fast_eligible(const GemmArgs& g);
 hipError_t launch_gemm_fast(const GemmArgs& g, hipStream_t stream);

@@ -309,7 +309,7 @@ bool estimated_faster(const GemmArgs& g, int64_t blocks, int64_t steps)
     return here <= 1.05 * there;
 }
 
-bool small_enough(const GemmArgs& g)
+bool small_enough(const GemmArgs& g, bool alone)
 {
     const bool wide = g.bA > 4;
     const int64_t blocks = ((g.RA + 31) / 32) * ((g.RB + 31) / 32), steps = (g.D + kStep - 1) / kStep;
@@ -318,23 +318,26 @@ bool small_enough(const GemmArgs& g)
     if (g.D > 4608 || (g.RA + g.RB) * (g.pitchA + g.pitchB) >= ((int64_t)1 << 31)) return false;
     if (g.splits > 1 ? blocks > 2048 || cost > 73728 : blocks > (ragged ? 2048 : 512) || cost > 36864) return false;
     // (in the paper's setting, and where the other kernel does not split the contraction, the lines are
-    // good enough and the estimates are not: 320 x 1024 x 4384, 2947 x 561 x 561)
-    return mode_of(g) == MODE_SAT8 || g.splits == 1 || estimated_faster(g, blocks, steps);
+    // good enough and the estimates are not: 320 x 1024 x 4384, 2947 x 561 x 561; and where the launch
+    // is there for other products anyway a long chain runs beside them.  Steps, the weight gradient by
+    // itself / in company: 3564 x 1152 x 32 in bytes 57.4 / 50.7, 2058 x 144 x 64 28.0 / 22.6, 2160 x 3456
+    // x 32 75.4 / 66.5, but 3969 x 144 x 128 39.9 / 53.1; of 400 random steps 38 gain over 2 %, 8 lose)
+    return !alone || mode_of(g) == MODE_SAT8 || g.splits == 1 || estimated_faster(g, blocks, steps);
 }
 
 } // namespace
 
-bool gemm_small_eligible(const GemmArgs& g)
+bool gemm_small_eligible(const GemmArgs& g, bool alone)
 {
     if (g.fold || (g.bA > 4) != (g.bB > 4)) return false;      // packed or bytes, the same on both sides
     if (g.s != 16 && g.s % kStep != 0) return false;
     if (g.RA * g.pitchA < 8 || g.RB * g.pitchB < 8) return false;      // (see load_tail)
-    if (mode_of(g) == MODE_SAT8) return small_enough(g);       // unscaled totals: covered by the API's range check
+    if (mode_of(g) == MODE_SAT8) return small_enough(g, alone);       // unscaled totals: covered by the API's range check
     // a tile's sum and the totals, times 256 with packed codes, must stay inside int32
     const int64_t max_prod = ((int64_t)1 << (g.bA - 1)) * ((int64_t)1 << (g.bB - 1)), room = g.bA > 4 ? ((int64_t)1 << 31) : ((int64_t)1 << 23);
     const int64_t tile_max = g.s * max_prod, acc_max = (int64_t)g.acc_hi + 1;
     const int64_t n_tiles = (g.D + g.s - 1) / g.s;
-    return tile_max < room && (tile_max < acc_max ? tile_max : acc_max) * n_tiles < room && small_enough(g);
+    return tile_max < room && (tile_max < acc_max ? tile_max : acc_max) * n_tiles < room && small_enough(g, alone);
 }
 
 hipError_t launch_gemm_small(const GemmArgs* gs, int n, hipStream_t stream)

@@ -80,14 +80,17 @@ def test_large_outputs_in_whole_and_broken_lines(RA, RB, D, s, a):
         assert torch.equal(out[r:r + 8192], part)
 
 
-@pytest.mark.parametrize("M,K,N", [(33000, 1040, 112), (33000, 1032, 136), (36000, 1168, 128)])
-def test_step_with_large_outputs_equals_its_products(M, K, N):
-    """A step streams Z and dX by lines of its own; the same products by themselves give the same."""
-    print(f"large step {M}x{K}x{N}", flush=True)
+@pytest.mark.parametrize("M,K,N,b,s,a", [
+    (33000, 1040, 112, 4, 32, 8), (33000, 1032, 136, 4, 32, 8), (36000, 1168, 128, 4, 32, 8),
+    (3564, 1152, 32, 8, 64, 16), (2058, 144, 64, 6, 32, 12), (4608, 1728, 16, 5, 16, 12), (3969, 144, 128, 4, 16, 12)])
+def test_step_equals_its_products_where_they_take_other_routes(M, K, N, b, s, a):
+    """A step streams Z and dX by lines of its own, and its small products keep a long chain in their
+    launch; the same products by themselves give the same."""
+    print(f"step {M}x{K}x{N} b={b} s={s} a={a}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(K)
     X, W, G = (torch.randn(*n, device="cuda", generator=g) for n in ((M, K), (K, N), (M, N)))
-    prm = [B.Params(had_block=64, acc_bits=8, s=32, seed=i, A=B.Operand(4, B.ROUND_NEAREST, 1.0, 2 * i),
-                    B=B.Operand(4, B.ROUND_NEAREST, 1.0, 2 * i + 1)) for i in range(3)]
+    prm = [B.Params(had_block=64, acc_bits=a, s=s, seed=i, A=B.Operand(b, B.ROUND_NEAREST, 1.0, 2 * i),
+                    B=B.Operand(b, B.ROUND_NEAREST, 1.0, 2 * i + 1)) for i in range(3)]
     step = B.layer_step(X, W, G, *prm)[:3]
     kinds = (B.GEMM_FWD, X, W), (B.GEMM_BWD_INPUT, G, W), (B.GEMM_BWD_WEIGHT, X, G)
     for got, (kind, P, Q), p in zip(step, kinds, prm):
