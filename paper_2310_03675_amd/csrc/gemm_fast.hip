@@ -340,7 +340,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
     static_assert(!MASK || (!BF16 && !WIDE && !NARROW), "masked output: plain packed instances only");
     static_assert(!NARROW || (WAVES == 8 && !BF16 && !WIDE), "narrow tiles: plain packed instances only");
     constexpr int TM = BM, TN = NARROW ? 64 : BN;   // the workgroup's tile
-    // ROWWIDE (streamed outputs, i.e. at least 128 MB): a wave is one block high and two wide
+    // ROWWIDE (streamed outputs): a wave is one block high and two wide
     // instead of two high and one wide, so that its two stores of a row are neighbours (256
     // bytes; streaming stores of 256-byte pieces reach 5.0 TB/s where 128-byte pieces reach
     // 4.6).  Same fragment reads per MFMA.  The benchmark layer's input gradient inside the
