@@ -248,13 +248,17 @@ constexpr int64_t kAnyDeepTwo = (int64_t)5 << 20;
 // 15.9 / 17.7.  Half of it with orders above 64 along axis 0 (4096 x 512 16.7 / 18.0), and where a
 // tensor with launches of its own has the records cleared anyway.
 constexpr int64_t kAnyLone = hdqt::kDenseMost, kAnyLoneStochastic = kAnyLone * 11 / 8;
-// Not where the tuned kernel along axis 0, of strips of 64 rows and 128 columns (64, 32 for narrow
-// tensors), has much of a strip or the 16-byte stores of its codes wasted: 5000 x 1000 21.3 / 20.3, with
-// bytes 33.5 / 21.7; G of 24640 x 320 x 192 without input gradient 41.5 / 39.
+// Not where much of a strip of the tuned kernel along axis 0, of 64 rows and 128 columns (64, 32 for narrow
+// tensors), is wasted: G of 24640 x 320 x 192 without input gradient 41.5 / 39.  Rows that are no whole
+// strips go there too since its codes leave in 16-byte stores at any pitch: 5000 x 1000 14.8 / 20.3, 9002 x 512
+// 12.5 / 16.8, stochastically 15.8 / 17.7, 20000 x 128 13.8 / 13.8; with a byte per code and stochastic rounding,
+// which gains least (9002 x 512 16.9 / 18.2, 2200 x 1024 12.9 / 12.9), they stay.
 bool whole_strips(const hdqt::QuantArgs& q)
 {
+    if (q.axis || q.log2n > 6) return true;
+    if (q.rows % 64 != 0 && q.b > 4 && q.stochastic) return false;
     const int64_t across = q.cols > 96 ? 128 : q.cols > 32 ? 64 : 32, padded = (q.cols + across - 1) / across * across;
-    return q.axis || (q.rows % 64 == 0 && (q.log2n > 6 || 7 * padded <= 8 * q.cols));
+    return 7 * padded <= 8 * q.cols;
 }
 // Elements up to which a tensor rounded stochastically on both axes leaves the two-axis kernel's
 // launch of a layer's tensors (64 values of two random streams a lane: its few waves end last) for
