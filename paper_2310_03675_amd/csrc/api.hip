@@ -299,33 +299,33 @@ int run_quantize_set(const QuantSet& s, void* records, size_t record_bytes, hipS
     }
     for (int k = 0; k < s.n_one; ++k) place(s.one[k]);
     if (!fits) return HDQT_EINVAL_DIM;
-    if (any.n == 1 && !n_dual && hdqt::quantize_fast_eligible(any.t[0]) && whole_strips(any.t[0])) {
-        const hdqt::QuantArgs& q = any.t[0];
+    if (any.h.n == 1 && !n_dual && hdqt::quantize_fast_eligible(any.t[0].q) && whole_strips(any.t[0].q)) {
+        const hdqt::QuantArgs& q = any.t[0].q;
         int64_t most = q.axis || !q.stochastic ? kAnyLone : kAnyLoneStochastic;
         if (n_alone || (deep(q) && !q.stochastic)) most /= 2;
-        if (any.total > most) {
+        if (any.h.total > most) {
             alone[n_alone++] = q;
-            any.n = any.total = 0;
+            any.h.n = any.h.total = 0;
         }
     }
-    if (any.n == 2 && !n_dual && !n_alone && deep(any.t[0]) && deep(any.t[1])) {
+    if (any.h.n == 2 && !n_dual && !n_alone && deep(any.t[0].q) && deep(any.t[1].q)) {
         int64_t sum = 0;
-        for (int k = 0; k < 2; ++k) sum += any.t[k].rows * any.t[k].cols * (any.t[k].stochastic ? 7 : 10) / 10;
-        if (sum > kAnyDeepTwo && hdqt::quantize_fast_eligible(any.t[0]) && hdqt::quantize_fast_eligible(any.t[1])) {
-            for (int k = 0; k < 2; ++k) alone[n_alone++] = any.t[k];
-            any.n = any.total = 0;
+        for (int k = 0; k < 2; ++k) sum += any.t[k].q.rows * any.t[k].q.cols * (any.t[k].q.stochastic ? 7 : 10) / 10;
+        if (sum > kAnyDeepTwo && hdqt::quantize_fast_eligible(any.t[0].q) && hdqt::quantize_fast_eligible(any.t[1].q)) {
+            for (int k = 0; k < 2; ++k) alone[n_alone++] = any.t[k].q;
+            any.h.n = any.h.total = 0;
         }
     }
 
     // maxima side by side, and nothing to clear, if every tensor has few enough workgroups
     bool dense = n_alone == 0;
     for (int k = 0; k < n_dual; ++k) dense = dense && hdqt::dual_workgroups(dual[k]) <= hdqt::kDenseMost;
-    for (int k = 0; k < any.n; ++k) dense = dense && any.p[k].count <= hdqt::kDenseMost;
-    for (int k = 0; k < any.n; ++k) any.p[k].dense = dense ? any.p[k].count : 0;
+    for (int k = 0; k < any.h.n; ++k) dense = dense && any.t[k].p.count <= hdqt::kDenseMost;
+    for (int k = 0; k < any.h.n; ++k) any.t[k].p.dense = dense ? any.t[k].p.count : 0;
     hipError_t e = hipSuccess;
     if (!dense) e = hdqt::launch_zero2(static_cast<uint32_t*>(records), (int64_t)(record_bytes / 4), nullptr, 0, stream);
 
-    const bool ride = n_dual && any.total < (1 << 20);
+    const bool ride = n_dual && any.h.total < (1 << 20);
     if (n_dual) {
         const hdqt::AnyBatch* riders = ride ? &any : nullptr;
         if (e == hipSuccess) e = hdqt::launch_dual_pass1(dual, n_dual, dense, riders, stream);
@@ -345,7 +345,7 @@ int run_quantize_set(const QuantSet& s, void* records, size_t record_bytes, hipS
             }
         }
     }
-    if (any.n && !ride) {
+    if (any.h.n && !ride) {
         if (e == hipSuccess) e = hdqt::launch_any(any, 1, stream);
         if (e == hipSuccess) e = hdqt::launch_any(any, 2, stream);
     }

@@ -44,21 +44,45 @@ struct QuantArgs {
     float* scale_out;       // device, may alias &meta->scale, may be null
 };
 
+// n / d for any 32-bit n, by multiplication (Granlund and Montgomery, PLDI'94, with the round-up
+// multiplier): a handful of scalar instructions instead of some forty vector ones.
+struct Divisor {
+    uint32_t d, mul, sh1, sh2;
+};
+inline Divisor make_divisor(uint32_t d)
+{
+    uint32_t l = 0;
+    while (((uint64_t)1 << l) < d) ++l;
+    const uint64_t mul = ((((uint64_t)1 << l) - d) << 32) / d + 1;      // (2^(32 + l) / d, rounded up, minus 2^32)
+    return {d, (uint32_t)mul, l < 1 ? l : 1, l < 1 ? 0 : l - 1};
+}
+__host__ __device__ __forceinline__ uint32_t divide(uint32_t n, const Divisor& v)
+{
+    const uint32_t t = (uint32_t)(((uint64_t)v.mul * n) >> 32);
+    return (t + ((n - t) >> v.sh1)) >> v.sh2;
+}
+
 // How the any-shape kernel cuts one tensor of a launch (plan_any).
 struct AnyPlan {
-    int first;              // the tensor's first workgroup in the launch
     int count;              // its workgroups
     int dense;              // `count` if the maxima stand side by side, 0 for atomic slots
-    int gx;                 // axis 0: workgroups along the columns
     int wc;                 // axis 0: waves side by side in a workgroup (1, 2 or 4)
-    uint32_t upl;           // axis 1: threads per line
+    int unused;
+    Divisor per;            // axis 1: threads per line; axis 0: workgroups along the columns
 };
 constexpr int kMaxAny = 6;
-struct AnyBatch {
-    QuantArgs t[kMaxAny];
-    AnyPlan p[kMaxAny];
+struct AnyTensor {
+    QuantArgs q;
+    AnyPlan p;
+};
+struct AnyHeader {
+    int first[kMaxAny];     // a tensor's first workgroup in the launch, INT_MAX behind the last tensor
     int n;
     int total;              // workgroups
+};
+struct AnyBatch {
+    AnyHeader h;
+    AnyTensor t[kMaxAny];
 };
 
 // One tensor quantized along both axes from one read ("row" = axis 1, along the
@@ -264,14 +288,48 @@ __device__ __forceinline__ float inverse_step(float amax_clipped, int b)
     return (float)(levels / (double)amax_clipped);
 }
 
+// A block of kernel arguments, all of it asked for at once.  Left to itself the compiler asks for a
+// member where it is first used, one after the other, and a trip to an argument takes some hundred
+// cycles: a good part of what a launch of a few workgroups takes.  (The statement only wants the
+// members in registers; pointers stay pointers, whose address space the compiler knows.)
+__device__ __forceinline__ AnyHeader whole_args(const AnyHeader& x)
+{
+    const AnyHeader h = x;
+    static_assert(kMaxAny == 6, "every member is named below");
+    asm volatile("" ::"s"(h.first[0]), "s"(h.first[1]), "s"(h.first[2]), "s"(h.first[3]), "s"(h.first[4]), "s"(h.first[5]),
+                 "s"(h.n), "s"(h.total));
+    return h;
+}
+
+__device__ __forceinline__ AnyTensor whole_args(const AnyTensor& x)
+{
+    const AnyTensor t = x;
+    asm volatile("" ::"s"(t.q.T), "s"(t.q.rows), "s"(t.q.cols), "s"(t.q.axis), "s"(t.q.log2n), "s"(t.q.b), "s"(t.q.stochastic),
+                 "s"(t.q.clip), "s"(t.q.tensor_id), "s"(t.q.seed_lo), "s"(t.q.seed_hi), "s"(t.q.meta), "s"(t.q.codes),
+                 "s"(t.q.scale_out), "s"(t.p.count), "s"(t.p.dense), "s"(t.p.wc), "s"(t.p.per.d), "s"(t.p.per.mul),
+                 "s"(t.p.per.sh1), "s"(t.p.per.sh2));
+    return t;
+}
+
 // ---- calibration helpers --------------------------------------------------
 
-__device__ __forceinline__ float wave_max_shfl(float m)
+// Largest of the wave's values, none of which is negative or NaN (such floats order like their bit
+// patterns), in every lane: moves inside rows of sixteen lanes, then lane swaps.  (Six LDS permutes, one
+// waiting for the other, take 600 cycles, of which a launch of a small tensor has two such reductions.)
+__device__ __forceinline__ uint32_t wave_max_bits(uint32_t m)
 {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, kWave));
-    return m;
+    auto larger = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
+    m = larger(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0xB1, 0xF, 0xF, true));       // lane ^ 1
+    m = larger(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x4E, 0xF, 0xF, true));       // lane ^ 2
+    m = larger(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x141, 0xF, 0xF, true));      // the other four of eight
+    m = larger(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x140, 0xF, 0xF, true));      // the other eight of sixteen
+    const auto r16 = __builtin_amdgcn_permlane16_swap(m, m, false, false);
+    m = larger(r16[0], r16[1]);
+    const auto r32 = __builtin_amdgcn_permlane32_swap(m, m, false, false);
+    return larger(r32[0], r32[1]);
 }
+
+__device__ __forceinline__ float wave_max(float m) { return __uint_as_float(wave_max_bits(__float_as_uint(m))); }
 
 // The workgroup's maximum into its record.  dense: the word of its own (number `local`); else
 // one atomicMax into slot local % 64, and only if it can raise the slot.
@@ -289,7 +347,7 @@ __device__ __forceinline__ void record_word(float m, QMeta* meta, int local, int
 // The same from every thread's maximum (256 threads).  `smem` holds one float per wave.
 __device__ __forceinline__ void record_max(float m, QMeta* meta, float* smem, int local, int dense)
 {
-    m = wave_max_shfl(m);
+    m = wave_max(m);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane == 0) smem[wave] = m;
     __syncthreads();
@@ -305,33 +363,51 @@ struct Scaling {
     float scale;    // value of one code step
 };
 
-// Must be reached by whole waves: lane l reads slot l, or the words l, l + 64, ... of `dense`.
-__device__ __forceinline__ Scaling load_scaling(const QMeta* meta, float clip, int b, int dense = 0)
+// Must be reached by whole waves: lane l reads slot l, or the words l, l + 64, ... of `dense`.  In two
+// halves, so that a caller has the words on their way before the loads of its tensor.
+struct Maxima {
+    uint32_t w[4];           // (clamped: four loads in flight, a word twice does no harm)
+};
+
+__device__ __forceinline__ Maxima fetch_maxima(const QMeta* meta, int dense)
 {
     const int lane = threadIdx.x & 63;
-    float slot;
-    if (dense) {
-        slot = 0.0f;
-        for (int i = 0; i < dense; i += 256) {
-            uint32_t w[4];       // (clamped: four loads in flight, a word twice does no harm)
+    Maxima x;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int at = i + 64 * k + lane;
-                w[k] = meta->amax[at < dense ? at : dense - 1];
-            }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) slot = fmaxf(slot, __uint_as_float(w[k]));
-        }
-    } else {
-        slot = __uint_as_float(meta->amax[lane * kAmaxSlotStride]);
+    for (int k = 0; k < 4; ++k) {
+        const int at = 64 * k + lane;
+        // (the slots: one load, and three of a word that every lane reads, rather than a branch)
+        x.w[k] = meta->amax[dense ? (at < dense ? at : dense - 1) : (k ? 0 : lane * kAmaxSlotStride)];
     }
-    const float amax = wave_max_shfl(slot);
+    return x;
+}
+
+__device__ __forceinline__ Scaling scaling_of(const Maxima& x, const QMeta* meta, float clip, int b, int dense)
+{
+    const int lane = threadIdx.x & 63;
+    auto larger = [](uint32_t p, uint32_t q) { return p > q ? p : q; };
+    uint32_t slot = larger(larger(x.w[0], x.w[1]), larger(x.w[2], x.w[3]));
+    for (int i = 256; i < dense; i += 256) {
+        uint32_t w[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int at = i + 64 * k + lane;
+            w[k] = meta->amax[at < dense ? at : dense - 1];
+        }
+        slot = larger(slot, larger(larger(w[0], w[1]), larger(w[2], w[3])));
+    }
+    const float amax = __uint_as_float(wave_max_bits(slot));
     const float amax_c = clip * amax;
     Scaling s;
     const bool zero = (amax_c == 0.0f);
     s.inv = zero ? 0.0f : inverse_step(amax_c, b);
     s.scale = zero ? 0.0f : amax_c / (float)(1 << (b - 1));
     return s;
+}
+
+__device__ __forceinline__ Scaling load_scaling(const QMeta* meta, float clip, int b, int dense = 0)
+{
+    return scaling_of(fetch_maxima(meta, dense), meta, clip, b, dense);
 }
 
 __device__ __forceinline__ void publish_scale(const QuantArgs& q, const Scaling& s)

@@ -65,7 +65,7 @@ using Codes = uint32_t __attribute__((ext_vector_type(WIDE ? 4 : 2)));
 // the byte of the lane's line in the operand, `left` the codes of the line from k on (TAIL: fewer
 // than a step's).
 template <bool WIDE, bool HALF, bool TAIL>
-__device__ __forceinline__ Codes<WIDE> load_step(const uint8_t* q, uint32_t line, int64_t k, int half, int64_t left)
+__device__ __forceinline__ Codes<WIDE> load_step(const uint8_t* q, uint32_t line, int k, int half, int left)
 {
     constexpr int N = WIDE ? 4 : 2, PER = HALF ? N / 2 : N;              // dwords, dwords of one run
     const uint32_t k_byte = (uint32_t)(WIDE ? k : k >> 1);
@@ -77,10 +77,10 @@ __device__ __forceinline__ Codes<WIDE> load_step(const uint8_t* q, uint32_t line
         const int code = HALF ? 16 * (i / PER) + 8 * half : 16 * half + 4 * (WIDE ? i : 0);
         const uint32_t at = line + (uint32_t)(WIDE ? code : code >> 1);
         if constexpr (TAIL && PER == 1) {
-            w[0] = (uint32_t)load_tail<WIDE>(q, k_byte + at, (int)left - code);
-            w[1] = (uint32_t)load_tail<WIDE>(q, k_byte + at + 8, (int)left - code - 16);
+            w[0] = (uint32_t)load_tail<WIDE>(q, k_byte + at, left - code);
+            w[1] = (uint32_t)load_tail<WIDE>(q, k_byte + at + 8, left - code - 16);
         } else if constexpr (TAIL) {
-            const uint64_t two = load_tail<WIDE>(q, k_byte + at, (int)left - code);
+            const uint64_t two = load_tail<WIDE>(q, k_byte + at, left - code);
             w[i] = (uint32_t)two;
             w[i + 1] = (uint32_t)(two >> 32);
         } else if constexpr (PER == 1) {
@@ -123,23 +123,53 @@ __device__ __forceinline__ int clamp3(int v, int lo, int hi)      // (plain C++:
     return t > hi ? hi : t;
 }
 
+// One product as this kernel wants it: everything that is the same for all its workgroups is worked
+// out on the host (a 64-bit division on the device is a hundred instructions), and the kernel has it in one
+// trip to its arguments (2947 x 561 x 561, both passes of the quantizer included, 24.5 -> 22.0 us).
+struct SmallArgs {
+    const uint8_t *qA, *qB;
+    const float *scaleA, *scaleB;
+    float* out;
+    uint16_t* out_bf16;
+    int32_t* acc_out;
+    const float* mask_src;
+    int pitchA, pitchB, RA, RB, D;
+    int acc_lo_scaled, acc_hi_scaled;
+    float inv_n;
+    int mode;                        // Mode, + kModeWide with a byte per code
+    int unit, units;                 // what the waves share out (a tile, or a step), and how many there are
+    int steps_per_tile;
+    Divisor n_ct;                    // blocks along a row of the output
+};
+
+// (see common.hpp: the arguments in one go)
+__device__ __forceinline__ SmallArgs whole_args(const SmallArgs& x)
+{
+    const SmallArgs g = x;
+    asm volatile("" ::"s"(g.qA), "s"(g.qB), "s"(g.scaleA), "s"(g.scaleB), "s"(g.out), "s"(g.out_bf16), "s"(g.acc_out),
+                 "s"(g.mask_src), "s"(g.pitchA), "s"(g.pitchB), "s"(g.RA), "s"(g.RB), "s"(g.D), "s"(g.acc_lo_scaled),
+                 "s"(g.acc_hi_scaled), "s"(g.inv_n), "s"(g.mode), "s"(g.unit), "s"(g.units), "s"(g.steps_per_tile),
+                 "s"(g.n_ct.d), "s"(g.n_ct.mul), "s"(g.n_ct.sh1), "s"(g.n_ct.sh2));
+    return g;
+}
+
 // The totals of a wave: the 32 x 32 block at (row0, col0), codes [k_begin, k_end), whole tiles.
 template <bool WIDE, int MODE>
-__device__ __forceinline__ v16i contract(const GemmArgs& g, int64_t row0, int64_t col0, int64_t k_begin, int64_t k_end)
+__device__ __forceinline__ v16i contract(const SmallArgs& g, int row0, int col0, int k_begin, int k_end)
 {
     constexpr bool HALF = MODE == MODE_HALF;
     constexpr int G = WIDE || HALF ? 2 : 4;  // steps per group of loads (tiles of 16 keep the sums of two a step)
     const int lane = threadIdx.x & 63, half = lane >> 5;
     // (rows outside the operands: the last one, nothing of it is written)
-    const int64_t ra = row0 + (lane & 31), rb = col0 + (lane & 31);
+    const int ra = row0 + (lane & 31), rb = col0 + (lane & 31);
     const uint32_t la = (uint32_t)(ra < g.RA ? ra : g.RA - 1) * (uint32_t)g.pitchA;
     const uint32_t lb = (uint32_t)(rb < g.RB ? rb : g.RB - 1) * (uint32_t)g.pitchB;
     struct Group {
         Codes<WIDE> a[G], b[G];
     };
-    const int64_t whole_steps = k_end > k_begin ? (k_end - k_begin) / kStep : 0, k_whole = k_begin + whole_steps * kStep;
+    const int whole_steps = k_end > k_begin ? (k_end - k_begin) / kStep : 0, k_whole = k_begin + whole_steps * kStep;
     // the group of steps at k; past the whole steps: zeros (a tile of them adds nothing)
-    auto fetch = [&](Group& f, int64_t k) {
+    auto fetch = [&](Group& f, int k) {
 #pragma unroll
         for (int i = 0; i < G; ++i) {
             Codes<WIDE> a = 0, b = 0;
@@ -153,7 +183,7 @@ __device__ __forceinline__ v16i contract(const GemmArgs& g, int64_t row0, int64_
     };
     const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
     const int lo = g.acc_lo_scaled, hi = g.acc_hi_scaled;
-    const int steps_per_tile = (int)(g.s / kStep);
+    const int steps_per_tile = g.steps_per_tile;
     int in_tile = 0;
     v16i total = zero, part = zero;          // part: the sums of the running tile (MODE_TILES)
     auto finish_tile = [&] {
@@ -163,7 +193,7 @@ __device__ __forceinline__ v16i contract(const GemmArgs& g, int64_t row0, int64_
         part = zero;
     };
     // the first `valid` steps of a group count; COUNT: how many there are at most
-    auto multiply = [&](const Group& f, int64_t valid, auto count) {
+    auto multiply = [&](const Group& f, int valid, auto count) {
         constexpr int COUNT = decltype(count)::value;
 #pragma unroll
         for (int i = 0; i < COUNT; i += MODE == MODE_SAT8 ? 2 : 1) {
@@ -192,7 +222,7 @@ __device__ __forceinline__ v16i contract(const GemmArgs& g, int64_t row0, int64_
     };
     Group now, next;
     fetch(now, k_begin);
-    for (int64_t done = 0; done < whole_steps; done += G) {
+    for (int done = 0; done < whole_steps; done += G) {
         fetch(next, k_begin + (done + G) * kStep);
         multiply(now, whole_steps - done, std::integral_constant<int, G>{});
         now = next;
@@ -212,34 +242,34 @@ __device__ __forceinline__ v16i contract(const GemmArgs& g, int64_t row0, int64_
 }
 
 struct SmallBatch {
-    GemmArgs g[kMaxSmallBatch];
+    int first[kMaxSmallBatch];       // a product's first workgroup, INT_MAX behind the last product
     int n;
-    int first[kMaxSmallBatch + 1];
-    int n_ct[kMaxSmallBatch];
-    int mode[kMaxSmallBatch];        // Mode, + kModeWide with a byte per code
+    SmallArgs g[kMaxSmallBatch];
 };
 
 __global__ __launch_bounds__(64 * kWaves, 4) void gemm_small_kernel(SmallBatch b)
 {
     __shared__ int meet[kWaves][16][64];
-    int p = 0;
-    while (p + 1 < b.n && (int)blockIdx.x >= b.first[p + 1]) ++p;
-    const GemmArgs& g = b.g[p];
-    const int local = (int)blockIdx.x - b.first[p];
-    const int rt = local / b.n_ct[p], ct = local - rt * b.n_ct[p];
-    const int64_t row0 = (int64_t)rt * 32, col0 = (int64_t)ct * 32;
+    int p = 0, local = (int)blockIdx.x;
+#pragma unroll
+    for (int j = 1; j < kMaxSmallBatch; ++j) {
+        const bool beyond = (int)blockIdx.x >= b.first[j];
+        p = beyond ? j : p;
+        local = beyond ? (int)blockIdx.x - b.first[j] : local;
+    }
+    const SmallArgs g = whole_args(b.g[p]);
+    const int rt = (int)divide((uint32_t)local, g.n_ct), ct = local - rt * (int)g.n_ct.d;
+    const int row0 = rt * 32, col0 = ct * 32;
+    const float scaleA = g.scaleA[0], scaleB = g.scaleB[0];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
 
-    // the wave's share of the contraction, in tiles (in steps, where a step holds two tiles or
-    // nothing is clamped)
-    const int64_t unit = g.s < kStep || g.acc_hi == INT_MAX ? kStep : g.s;
-    const int64_t units = (g.D + unit - 1) / unit;
-    const int64_t k_begin = units * wave / kWaves * unit;
-    int64_t k_end = units * (wave + 1) / kWaves * unit;
+    // the wave's share of the contraction
+    const int k_begin = g.units * wave / kWaves * g.unit;
+    int k_end = g.units * (wave + 1) / kWaves * g.unit;
     if (k_end > g.D) k_end = g.D;
 
     v16i total;
-    switch (b.mode[p]) {
+    switch (g.mode) {
     case MODE_TILES: total = contract<false, MODE_TILES>(g, row0, col0, k_begin, k_end); break;
     case MODE_SAT8: total = contract<false, MODE_SAT8>(g, row0, col0, k_begin, k_end); break;
     case MODE_HALF: total = contract<false, MODE_HALF>(g, row0, col0, k_begin, k_end); break;
@@ -250,17 +280,17 @@ __global__ __launch_bounds__(64 * kWaves, 4) void gemm_small_kernel(SmallBatch b
 #pragma unroll
     for (int r = 0; r < 16; ++r) meet[wave][r][lane] = total[r];
     __syncthreads();
-    const float dq = (g.scaleA[0] * g.scaleB[0]) * g.inv_n;
-    const int64_t col = col0 + (lane & 31);
+    const float dq = (scaleA * scaleB) * g.inv_n;
+    const int col = col0 + (lane & 31);
 #pragma unroll
     for (int i = 0; i < 16 / kWaves; ++i) {
         const int r = wave * (16 / kWaves) + i;
         int v = 0;
 #pragma unroll
         for (int w = 0; w < kWaves; ++w) v += meet[w][r][lane];
-        const int64_t row = row0 + 8 * (r >> 2) + (r & 3) + 4 * (lane >> 5);
+        const int row = row0 + 8 * (r >> 2) + (r & 3) + 4 * (lane >> 5);
         if (row < g.RA && col < g.RB) {
-            const int64_t o = row * g.RB + col;
+            const int64_t o = (int64_t)row * g.RB + col;
             float f = (float)v * dq;
             if (g.acc_out) g.acc_out[o] = v;
             if (g.out_bf16) g.out_bf16[o] = (uint16_t)bf16_bits(f);
@@ -346,17 +376,28 @@ hipError_t launch_gemm_small(const GemmArgs* gs, int n, hipStream_t stream)
     SmallBatch b{};
     b.n = n;
     int64_t total = 0;
+    for (int k = 0; k < kMaxSmallBatch; ++k) b.first[k] = INT_MAX;
     for (int k = 0; k < n; ++k) {
-        GemmArgs& g = b.g[k] = gs[k];
+        const GemmArgs& g = gs[k];
+        SmallArgs& a = b.g[k];
         const int64_t f = g.bA > 4 ? 1 : 256, lo = (int64_t)g.acc_lo * f, hi = (int64_t)g.acc_hi * f;
-        g.acc_lo_scaled = lo < INT_MIN ? INT_MIN : (int)lo;
-        g.acc_hi_scaled = hi > INT_MAX ? INT_MAX : (int)hi;
-        b.mode[k] = mode_of(g);
-        b.n_ct[k] = (int)((g.RB + 31) / 32);
+        a.qA = g.qA; a.qB = g.qB; a.scaleA = g.scaleA; a.scaleB = g.scaleB;
+        a.out = g.out; a.out_bf16 = g.out_bf16; a.acc_out = g.acc_out; a.mask_src = g.mask_src;
+        // (all below 2^31: small_enough)
+        a.pitchA = (int)g.pitchA; a.pitchB = (int)g.pitchB;
+        a.RA = (int)g.RA; a.RB = (int)g.RB; a.D = (int)g.D;
+        a.acc_lo_scaled = lo < INT_MIN ? INT_MIN : (int)lo;
+        a.acc_hi_scaled = hi > INT_MAX ? INT_MAX : (int)hi;
+        a.inv_n = g.inv_n;
+        a.mode = mode_of(g);
+        // (steps, where a step holds two tiles or nothing is clamped)
+        a.unit = (int)(g.s < kStep || g.acc_hi == INT_MAX ? kStep : g.s);
+        a.units = (int)((g.D + a.unit - 1) / a.unit);
+        a.steps_per_tile = (int)(g.s / kStep);
+        a.n_ct = make_divisor((uint32_t)((g.RB + 31) / 32));
         b.first[k] = (int)total;
-        total += b.n_ct[k] * ((g.RA + 31) / 32);
+        total += (int64_t)a.n_ct.d * ((g.RA + 31) / 32);
     }
-    b.first[n] = (int)total;
     ProfileScope ps(n > 1 ? K_GEMM_SMALL : gs[0].profile_tag ? K_GEMM_I4_FWD + (gs[0].profile_tag - 1) : K_GEMM_I4, stream);
     hipLaunchKernelGGL(gemm_small_kernel, dim3((unsigned)total), dim3(64 * kWaves), 0, stream, b);
     return hipGetLastError();

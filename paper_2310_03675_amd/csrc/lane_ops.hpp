@@ -155,17 +155,6 @@ __device__ __forceinline__ void butterfly8(float v[8], int log2n)
     }
 }
 
-__device__ __forceinline__ float wave_max(float m)
-{
-    m = fmaxf(m, lane_xor<1>(m));
-    m = fmaxf(m, lane_xor<2>(m));
-    m = fmaxf(m, lane_xor<4>(m));
-    m = fmaxf(m, lane_xor<8>(m));
-    m = fmaxf(m, __shfl_xor(m, 16, kWave));
-    m = fmaxf(m, __shfl_xor(m, 32, kWave));
-    return m;
-}
-
 // ---- rounding and packing -------------------------------------------------
 // code_word() returns 0x4B400000 + code + offset, offset = 8 (b <= 4) or 128:
 // adding 1.5 * 2^23 (+ offset) to a binary32 value of magnitude below 2^22 rounds

@@ -15,6 +15,8 @@
 #include "common.hpp"
 #include "quantize_any.hpp"
 
+#include <limits.h>
+
 namespace hdqt {
 
 namespace {
@@ -24,10 +26,11 @@ __global__ __launch_bounds__(any::kThreads) void fwht_any_kernel(AnyBatch b)
 {
     __shared__ float red[any::kThreads / kWave];
     __shared__ float lds[any::kLdsFloats];
+    const AnyHeader h = whole_args(b.h);
     // (a grid holds 2^32 threads)
-    for (int64_t vb = blockIdx.x; vb < b.total; vb += gridDim.x) {
-        any::batch_block<QUANT>(b, (int)vb, red, lds);
-        if (vb + gridDim.x < b.total) __syncthreads();
+    for (int64_t vb = blockIdx.x; vb < h.total; vb += gridDim.x) {
+        any::batch_block<QUANT>(b, h, (int)vb, red, lds);
+        if (vb + gridDim.x < h.total) __syncthreads();
     }
 }
 
@@ -54,33 +57,35 @@ hipError_t launch_zero2(uint32_t* a, int64_t na, uint32_t* b, int64_t nb, hipStr
 
 bool plan_any(const QuantArgs& q, AnyBatch* b)
 {
-    if (b->n == kMaxAny) return false;
+    AnyHeader& h = b->h;
+    if (h.n == kMaxAny) return false;
     AnyPlan p{};
     int64_t count;
     if (q.axis) {
-        p.upl = (uint32_t)((q.cols + 7) / 8);
-        count = (q.rows * (int64_t)p.upl + any::kThreads - 1) / any::kThreads;
+        p.per = make_divisor((uint32_t)((q.cols + 7) / 8));
+        count = (q.rows * (int64_t)p.per.d + any::kThreads - 1) / any::kThreads;
     } else {
         // as many of the four waves side by side as there are columns for (32 columns are one
         // 128-byte line of a row); block orders above 64 need them on top of each other
         p.wc = q.log2n > 6 || q.cols <= 8 ? 1 : q.cols <= 16 ? 2 : 4;
-        p.gx = (int)((q.cols + 8 * p.wc - 1) / (8 * p.wc));
+        p.per = make_divisor((uint32_t)((q.cols + 8 * p.wc - 1) / (8 * p.wc)));
         const int64_t tall = 64 * (4 / p.wc);
-        count = p.gx * ((q.rows + tall - 1) / tall);
+        count = (int64_t)p.per.d * ((q.rows + tall - 1) / tall);
     }
-    if (count + b->total >= ((int64_t)1 << 31)) return false;
-    p.first = b->total;
+    if (count + h.total >= ((int64_t)1 << 31)) return false;
+    if (!h.n)
+        for (int k = 0; k < kMaxAny; ++k) h.first[k] = INT_MAX;
+    h.first[h.n] = h.total;
     p.count = (int)count;
-    b->t[b->n] = q;
-    b->p[b->n] = p;
-    b->total += p.count;
-    ++b->n;
+    b->t[h.n] = {q, p};
+    h.total += p.count;
+    ++h.n;
     return true;
 }
 
 hipError_t launch_any(const AnyBatch& b, int pass, hipStream_t stream)
 {
-    const dim3 grid((unsigned)(b.total < (1 << 23) ? b.total : (1 << 23)));
+    const dim3 grid((unsigned)(b.h.total < (1 << 23) ? b.h.total : (1 << 23)));
     ProfileScope ps(pass == 1 ? K_ANY_ABSMAX : K_ANY_QUANT, stream);
     if (pass == 1) hipLaunchKernelGGL(fwht_any_kernel<false>, grid, dim3(any::kThreads), 0, stream, b);
     else hipLaunchKernelGGL(fwht_any_kernel<true>, grid, dim3(any::kThreads), 0, stream, b);

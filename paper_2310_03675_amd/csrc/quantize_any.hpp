@@ -9,6 +9,11 @@
 //     any length: a line's last thread holds what is left, the codes behind it are zeros.
 //   axis 0: lane (rg, cg) = (lane / 8, lane % 8) has rows 8 rg .. 8 rg + 7 of column cg of the
 //     wave's 64 x 8 piece; strides 8, 16, 32 pair lanes, 64 and 128 pair waves through LDS.
+// What bounds a small launch is one chain of trips: to the arguments, to the tensor, in pass 2 to the
+// maxima.  The arguments come in two trips (whole_args), the maxima are on their way before the
+// tensor, nothing is divided (Divisor) and no reduction goes through LDS permutes: the step of 64 x 256 x 128
+// 14.4 -> 10.7 us together with the product's kernel, quantize of 1315 x 362 7.5 -> 6.2 us, of which an empty
+// kernel has 1.6 a launch.
 // The butterfly runs with strides 1, 2, 4, ..., n/2 in that order: this fixes the binary32
 // rounding to the balanced pairwise tree over the signed terms in natural index order.
 #pragma once
@@ -102,13 +107,15 @@ __device__ __forceinline__ float block(const QuantArgs& q, const AnyPlan& p, int
     int count = 0;                       // codes of this thread inside the tensor
     const int64_t pitch = q.b <= 4 ? ((q.axis ? q.cols : q.rows) + 1) >> 1 : (q.axis ? q.cols : q.rows);
     const int per = q.b <= 4 ? 4 : 8;    // bytes of eight codes
+    Maxima maxima{};
+    if (QUANT) maxima = fetch_maxima(q.meta, p.dense);
     if (q.axis) {
         // (the workgroup's first line: a 32-bit division wherever that is enough)
         const int64_t base = (int64_t)local * kThreads;
-        const int64_t line0 = local < (1 << 23) ? (int64_t)((uint32_t)base / p.upl) : base / (int64_t)p.upl;
-        const uint32_t at = (uint32_t)(base - line0 * p.upl) + (uint32_t)tid;
-        const uint32_t down = at / p.upl;
-        const uint32_t j = at - down * p.upl;
+        const int64_t line0 = local < (1 << 23) ? (int64_t)divide((uint32_t)base, p.per) : base / (int64_t)p.per.d;
+        const uint32_t at = (uint32_t)(base - line0 * p.per.d) + (uint32_t)tid;
+        const uint32_t down = divide(at, p.per);
+        const uint32_t j = at - down * p.per.d;
         const int64_t line = line0 + down;
         const float* src = q.T + line * q.cols + 8 * (int64_t)j;
         if (line < q.rows) {
@@ -149,10 +156,11 @@ __device__ __forceinline__ float block(const QuantArgs& q, const AnyPlan& p, int
             if (q.stochastic) random8(q, (uint64_t)(line * q.cols) + 8 * (uint64_t)j, rnd);
         }
     } else {
-        const int64_t by = local / p.gx, bx = local - by * p.gx;
-        const int wc = wave & (p.wc - 1), wr = wave / p.wc;
+        const uint32_t across = divide((uint32_t)local, p.per);
+        const int64_t by = across, bx = (uint32_t)local - across * p.per.d;
+        const int wc = wave & (p.wc - 1), wr = wave >> (p.wc >> 1);      // (wc: 1, 2 or 4)
         const int rg = lane >> 3, cg = lane & 7;
-        const int64_t row0 = (by * (4 / p.wc) + wr) * 64, col0 = (bx * p.wc + wc) * 8;       // the wave's piece
+        const int64_t row0 = (by * (4 >> (p.wc >> 1)) + wr) * 64, col0 = (bx * p.wc + wc) * 8;       // the wave's piece
         const int64_t row = row0 + rg * 8, col = col0 + cg;
         if (col < q.cols && row < q.rows) {
             const int64_t left = q.rows - row;
@@ -215,7 +223,7 @@ __device__ __forceinline__ float block(const QuantArgs& q, const AnyPlan& p, int
         }
     }
     if (QUANT) {
-        const Scaling sc = load_scaling(q.meta, q.clip, q.b, p.dense);
+        const Scaling sc = scaling_of(maxima, q.meta, q.clip, q.b, p.dense);
         if (local == 0 && tid == 0) {
             q.meta->scale = sc.scale;
             if (q.scale_out) *q.scale_out = sc.scale;
@@ -231,16 +239,19 @@ __device__ __forceinline__ float block(const QuantArgs& q, const AnyPlan& p, int
 
 // both passes of workgroup `vb` of a batch; `red`: one float per wave
 template <bool QUANT>
-__device__ __forceinline__ void batch_block(const AnyBatch& b, int vb, float* red, float* lds)
+__device__ __forceinline__ void batch_block(const AnyBatch& b, const AnyHeader& h, int vb, float* red, float* lds)
 {
-    int k = 0;
-    while (k + 1 < b.n && vb >= b.p[k + 1].first) ++k;
-    const QuantArgs& q = b.t[k];
-    const AnyPlan& p = b.p[k];
-    int local = vb - p.first;
-    if (QUANT) local = p.count - 1 - local;      // what pass 1 read last is in the caches still
-    const float m = block<QUANT>(q, p, local, lds);
-    if (!QUANT) record_max(m, q.meta, red, local, p.dense);
+    int k = 0, local = vb;
+#pragma unroll
+    for (int j = 1; j < kMaxAny; ++j) {
+        const bool beyond = vb >= h.first[j];
+        k = beyond ? j : k;
+        local = beyond ? vb - h.first[j] : local;
+    }
+    const AnyTensor t = whole_args(b.t[k]);
+    if (QUANT) local = t.p.count - 1 - local;      // what pass 1 read last is in the caches still
+    const float m = block<QUANT>(t.q, t.p, local, lds);
+    if (!QUANT) record_max(m, t.q.meta, red, local, t.p.dense);
 }
 
 } // namespace any

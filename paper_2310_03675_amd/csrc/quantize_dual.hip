@@ -514,15 +514,28 @@ __device__ __forceinline__ void dual_codes(Tile& t, const DualCtx& x, int64_t ro
 // Small tensors (a layer's weights) ride along with a large one instead of paying
 // for a launch of their own.
 struct DualBatch {
-    DualArgs t[kMaxDualBatch];
-    int n;
-    int first[kMaxDualBatch + 1];
+    int first[kMaxDualBatch + 1];        // (behind the last tensor: the workgroups of all)
     int gx[kMaxDualBatch];       // workgroups along the columns
     int WC[kMaxDualBatch];       // waves side by side in a workgroup (1, 2 or 4)
     int lds_per_wave;            // floats of LDS per wave (convolution sources), a multiple of 4
     int dense;                   // the maxima stand side by side (see QMeta)
     int spread;                  // pass 2: every spread-th workgroup of the grid is one of tensor 0 (0: off)
+    DualArgs t[kMaxDualBatch];
 };
+
+// (see common.hpp: the arguments in one go)
+template <bool CONV>
+__device__ __forceinline__ DualArgs whole_args(const DualArgs& x)
+{
+    const DualArgs q = x;
+    asm volatile("" ::"s"(q.T), "s"(q.rows), "s"(q.cols), "s"(q.log2n_row), "s"(q.log2n_col), "s"(q.b_row), "s"(q.clip_row),
+                 "s"(q.tid_row), "s"(q.b_col), "s"(q.clip_col), "s"(q.tid_col), "s"(q.seed_row_lo), "s"(q.seed_row_hi),
+                 "s"(q.seed_col_lo), "s"(q.seed_col_hi), "s"(q.meta_row), "s"(q.meta_col), "s"(q.codes_row), "s"(q.codes_col),
+                 "s"(q.scale_row_out), "s"(q.scale_col_out));
+    if constexpr (CONV)
+        asm volatile("" ::"s"(q.conv), "s"(q.cC), "s"(q.cH), "s"(q.cW), "s"(q.ckh), "s"(q.ckw), "s"(q.pPH), "s"(q.pPW), "s"(q.pCN));
+    return q;
+}
 
 // Workgroup number -> number in the tensor-after-tensor order.  With `spread`, the workgroups of
 // tensor 0 (the stochastically rounded one of a per-tensor launch: twice the vector
@@ -556,7 +569,7 @@ constexpr int kRoundWide = 8;        // added to ROUND: codes of 5 to 8 bits, on
 template <bool QUANT, int ROUND, bool N64, bool CONV>
 __device__ __forceinline__ void dual_block(const DualBatch& b, int k, int vb, float (*red)[2], float* lds)
 {
-    const DualArgs& q = b.t[k];
+    const DualArgs q = whole_args<CONV>(b.t[k]);
     const int count = b.first[k + 1] - b.first[k];
     // pass 2 walks a tensor from its end to its start: it begins with what pass 1
     // read last, which is most likely still in the memory-side cache
@@ -574,15 +587,20 @@ __device__ __forceinline__ void dual_block(const DualBatch& b, int k, int vb, fl
 
     DualCtx x;
     dual_setup<N64>(x, q, lane);
+    const int dense = b.dense ? count : 0;
+    Maxima max_row{}, max_col{};         // (on their way before the tile)
+    if (QUANT) {
+        max_row = fetch_maxima(q.meta_row, dense);
+        max_col = fetch_maxima(q.meta_col, dense);
+    }
     Tile t;
     if (live) {
         if (CONV && q.conv) tile_load_conv(t, q, x, row0, col0, lds + wave * b.lds_per_wave, lane);
         else tile_load(t, q, x, row0, col0);
     }
     if (QUANT) {
-        const int dense = b.dense ? count : 0;
-        const Scaling s_row = load_scaling(q.meta_row, q.clip_row, q.b_row, dense);
-        const Scaling s_col = load_scaling(q.meta_col, q.clip_col, q.b_col, dense);
+        const Scaling s_row = scaling_of(max_row, q.meta_row, q.clip_row, q.b_row, dense);
+        const Scaling s_col = scaling_of(max_col, q.meta_col, q.clip_col, q.b_col, dense);
         dual_set_scaling(x, q, s_row, s_col, local == 0);
         if (live) dual_codes<(ROUND & 1) != 0, (ROUND & 2) != 0, (ROUND & kRoundWide) != 0>(t, x, row0, col0);
     } else {
@@ -598,13 +616,14 @@ __global__ __launch_bounds__(kThreads) void fwht_dual_kernel(DualBatch b, AnyBat
     __shared__ float red[kThreads / kWave][2];
     extern __shared__ __attribute__((aligned(16))) float lds[];      // CONV: one patch per wave; riders' exchange
 
-    if ((int)blockIdx.x >= b.first[b.n]) {
-        any::batch_block<QUANT>(ride, (int)blockIdx.x - b.first[b.n], &red[0][0], lds);
+    if ((int)blockIdx.x >= b.first[kMaxDualBatch]) {
+        any::batch_block<QUANT>(ride, hdqt::whole_args(ride.h), (int)blockIdx.x - b.first[kMaxDualBatch], &red[0][0], lds);
         return;
     }
     const int vb = QUANT ? batch_order(b) : (int)blockIdx.x;
     int k = 0;
-    while (k + 1 < b.n && vb >= b.first[k + 1]) ++k;
+#pragma unroll
+    for (int j = 1; j < kMaxDualBatch; ++j) k = vb >= b.first[j] ? j : k;
     if constexpr ((ROUND & 7) == kRoundPerTensor) {
         // two complete bodies, chosen per workgroup: sharing anything between them
         // (one load, one setup) lets the compiler keep both paths' registers alive
@@ -632,7 +651,6 @@ int waves_across(const DualArgs& q)
 bool make_batch(const DualArgs* qs, int n, bool dense, const AnyBatch* ride, DualBatch* b)
 {
     if (n < 1 || n > kMaxDualBatch) return false;
-    b->n = n;
     b->dense = dense ? 1 : 0;
     int64_t total = 0;
     int lds = 0;
@@ -651,8 +669,8 @@ bool make_batch(const DualArgs* qs, int n, bool dense, const AnyBatch* ride, Dua
         total += wgs;
         if (total >= ((int64_t)1 << 30)) return false;
     }
-    if (ride && ride->total >= (1 << 30)) return false;
-    b->first[n] = (int)total;
+    if (ride && ride->h.total >= (1 << 30)) return false;
+    for (int k = n; k <= kMaxDualBatch; ++k) b->first[k] = (int)total;
     b->lds_per_wave = lds;
     b->spread = 0;
     return true;
@@ -702,7 +720,7 @@ bool quantize_dual_eligible(const DualArgs& q)
 size_t launch_lds(const DualBatch& b, const AnyBatch* ride)
 {
     size_t lds = (size_t)(kThreads / kWave) * b.lds_per_wave;
-    if (ride && ride->n && lds < any::kLdsFloats) lds = any::kLdsFloats;
+    if (ride && ride->h.n && lds < any::kLdsFloats) lds = any::kLdsFloats;
     return lds * sizeof(float);
 }
 
@@ -717,7 +735,7 @@ hipError_t launch_dual_pass1(const DualArgs* qs, int n, bool dense, const AnyBat
     const int id = n > 1 ? K_DUAL_ABSMAX_BATCH
                          : (qs[0].profile_tag ? K_DUAL_ABSMAX_X + (qs[0].profile_tag - 1) : K_DUAL_ABSMAX);
     ProfileScope ps(id, stream);
-    const dim3 grid((unsigned)(b.first[n] + ride->total)), block(kThreads);
+    const dim3 grid((unsigned)(b.first[n] + ride->h.total)), block(kThreads);
     const size_t lds = launch_lds(b, ride);
     const bool n64 = all_order_64(qs, n);
     if (b.lds_per_wave) {      // a convolution source among the tensors
@@ -758,7 +776,7 @@ hipError_t launch_dual_pass2(const DualArgs* qs, int n, bool dense, const AnyBat
     const int id = n > 1 ? K_DUAL_QUANT_BATCH
                          : (qs[0].profile_tag ? K_DUAL_QUANT_X + (qs[0].profile_tag - 1) : K_DUAL_QUANT);
     ProfileScope ps(id, stream);
-    const dim3 grid((unsigned)(b.first[n] + ride->total)), block(kThreads);
+    const dim3 grid((unsigned)(b.first[n] + ride->h.total)), block(kThreads);
     const bool n64 = all_order_64(qs, n);
     const size_t lds = launch_lds(b, ride);
     const bool conv = b.lds_per_wave != 0;
