@@ -12,6 +12,15 @@ from typing import Optional
 
 import torch
 
+try:
+    from . import _host          # csrc/host.cpp: the calls of the hot path, marshalled in native code
+except ImportError:
+    class _NotBuilt:             # (every call goes the long way, whose first step is load(), which raises)
+        def __getattr__(self, name):
+            return lambda *args: None
+
+    _host = _NotBuilt()
+
 ROUND_NEAREST, ROUND_STOCHASTIC = 0, 1
 GEMM_FWD, GEMM_BWD_INPUT, GEMM_BWD_WEIGHT = 0, 1, 2
 
@@ -103,7 +112,10 @@ def load() -> C.CDLL:
     if not os.path.exists(LIB_PATH):
         raise ImportError(f"{LIB_PATH} is missing: run `python -m paper_2310_03675_amd.build` "
                           "(there is no fallback path)")
+    if type(_host).__name__ == "_NotBuilt":
+        raise ImportError("the module _host is missing: run `python -m paper_2310_03675_amd.build`")
     lib = C.CDLL(LIB_PATH)
+    _host.bind(LIB_PATH, torch.cuda.current_device, torch._C._cuda_getCurrentRawStream)
     vp, i64, i32, sz = C.c_void_p, C.c_int64, C.c_int, C.c_size_t
     lib.hdqt_n_eff.restype = i32
     lib.hdqt_n_eff.argtypes = [i64, i32]
@@ -253,6 +265,14 @@ def _stream(stream: Optional[torch.cuda.Stream]):
     return C.c_void_p(stream.cuda_stream)
 
 
+def _native(r, where: str):
+    """What a function of _host returned: its result, the library's refusal as an error, or None for a
+    call that is not of the ordinary form (another type or layout, say), which goes the long way."""
+    if r.__class__ is int:
+        raise HdqtError(r, where)
+    return r
+
+
 def _check_dev(*tensors):
     for t in tensors:
         if t is not None and not (t.is_cuda and t.is_contiguous()):
@@ -262,6 +282,9 @@ def _check_dev(*tensors):
 def quantize(T: torch.Tensor, axis: int, had_block: int, op: Operand, seed: int = 0,
              stream: Optional[torch.cuda.Stream] = None):
     """hdqt_quantize -> (codes uint8 [lines, pitch], scale float32 [1]) on the device."""
+    r = _native(_host.quantize(T, axis, had_block, op, seed, stream), "hdqt_quantize")
+    if r is not None:
+        return r
     _check_dev(T)
     assert T.dtype == torch.float32 and T.dim() == 2
     rows, cols = T.shape
@@ -443,6 +466,11 @@ def gemm(kind: int, P: torch.Tensor, Q: torch.Tensor, M: int, K: int, N: int, pa
     `kind`: (X, W), (G, W), (X, G).  -> (out, acc | None, workspace).  bf16=True (input
     gradient only): hdqt_gemm_bwd_input_bf16, `out` is a torch.bfloat16 tensor.  mask (input
     gradient only): hdqt_gemm_bwd_input_masked, the layer's input X [M, K]."""
+    r = _native(_host.gemm(kind, P, Q, M, K, N, params, out, acc, want_acc, workspace, stream, bf16, mask),
+                "hdqt_gemm_bwd_input_bf16" if bf16 else "hdqt_gemm_bwd_input_masked" if mask is not None
+                else _GEMM_FN.get(kind))
+    if r is not None:
+        return r
     _check_dev(P, Q, out, acc, workspace, mask)
     shape = out_shape(kind, M, K, N)
     assert not bf16 or kind == GEMM_BWD_INPUT
@@ -542,6 +570,9 @@ def layer_step(X: torch.Tensor, W: torch.Tensor, G: torch.Tensor, fwd: Params,
                workspace: Optional[torch.Tensor] = None, stream: Optional[torch.cuda.Stream] = None):
     """hdqt_layer_step -> (Z, dX | None, dW, workspace).  dX is skipped when
     `bwd_input` is None.  `out` may carry preallocated (Z, dX, dW)."""
+    r = _native(_host.layer_step(X, W, G, fwd, bwd_input, bwd_weight, out, workspace, stream), "hdqt_layer_step")
+    if r is not None:
+        return r
     _check_dev(X, W, G, workspace)
     M, K = X.shape
     N = W.shape[1]
@@ -572,6 +603,9 @@ def layer_fwd(X: torch.Tensor, W: torch.Tensor, fwd: Params, bwd_weight: Optiona
               workspace: Optional[torch.Tensor] = None, stream: Optional[torch.cuda.Stream] = None):
     """hdqt_layer_fwd -> (Z, saved | None).  With `bwd_weight`, `saved` receives X's codes
     along M for layer_bwd (a uint8 tensor of hdqt_layer_saved_size bytes)."""
+    r = _native(_host.layer_fwd(X, W, fwd, bwd_weight, out, saved, workspace, stream), "hdqt_layer_fwd")
+    if r is not None:
+        return r
     _check_dev(X, W, out, saved, workspace)
     M, K = X.shape
     N = W.shape[1]
@@ -598,6 +632,9 @@ def conv_fwd(act: torch.Tensor, kh: int, kw: int, W: torch.Tensor, fwd: Params, 
              stream: Optional[torch.cuda.Stream] = None):
     """hdqt_conv_fwd -> (Z [batch*H*W, N], saved): hdqt_layer_fwd with X given as the activation.
     Raises HdqtError with code -13 for geometries the activation-source kernels do not take."""
+    r = _native(_host.conv_fwd(act, kh, kw, W, fwd, bwd_weight, stream), "hdqt_conv_fwd")
+    if r is not None:
+        return r
     _check_dev(act, W)
     geo = conv_geometry(act, kh, kw)
     M, K, N = act.shape[0] * act.shape[2] * act.shape[3], act.shape[1] * kh * kw, W.shape[1]
@@ -620,6 +657,9 @@ def conv_bwd(G: torch.Tensor, W: torch.Tensor, saved: torch.Tensor, act_shape, k
     """hdqt_conv_bwd -> (dAct [batch, C, H, W], dW [K, N]): hdqt_layer_bwd with the input gradient
     folded back onto the activation inside the matmul.  HdqtError -13 for geometries not taken.
     mask: hdqt_conv_bwd_masked, the activation itself (dAct is written where it is positive)."""
+    r = _native(_host.conv_bwd(G, W, saved, act_shape, kh, kw, bwd_input, bwd_weight, stream, mask), "hdqt_conv_bwd")
+    if r is not None:
+        return r
     _check_dev(G, W, saved, mask)
     batch, Cin, H, Wd = act_shape
     geo = CConv(batch, Cin, H, Wd, kh, kw)
@@ -667,6 +707,10 @@ def layer_bwd(G: torch.Tensor, W: torch.Tensor, saved: torch.Tensor, K: int,
     """hdqt_layer_bwd -> (dX | None, dW).  dX is skipped when `bwd_input` is None.
     `out` may carry preallocated (dX, dW).  mask: hdqt_layer_bwd_masked, the layer's input
     X [M, K] (dX is written where it is positive, zero elsewhere)."""
+    r = _native(_host.layer_bwd(G, W, saved, K, bwd_input, bwd_weight, out, workspace, stream, mask),
+                "hdqt_layer_bwd_masked" if mask is not None else "hdqt_layer_bwd")
+    if r is not None:
+        return r
     _check_dev(G, W, saved, workspace, mask)
     M, N = G.shape
     if out is None:

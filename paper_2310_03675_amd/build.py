@@ -1,4 +1,5 @@
-"""Compile the HIP library for gfx950 into paper_2310_03675_amd/libhdqt.so.
+"""Compile the HIP library for gfx950 into paper_2310_03675_amd/libhdqt.so, and the native part of
+its Python binding (csrc/host.cpp, no device code) into _host.so beside it.
 
     python -m paper_2310_03675_amd.build
 """
@@ -23,6 +24,24 @@ HIPCC_FLAGS = [
 ]
 
 
+HOST = os.path.join(HERE, "_host.so")
+
+
+def build_host(verbose: bool = False) -> str:
+    import sysconfig
+
+    from torch.utils import cpp_extension
+
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           *(f"-I{d}" for d in cpp_extension.include_paths()), f"-I{sysconfig.get_paths()['include']}",
+           os.path.join(CSRC, "host.cpp"), *(f"-L{d}" for d in cpp_extension.library_paths()),
+           "-ltorch_python", "-ltorch", "-ltorch_cpu", "-lc10", "-o", HOST]
+    if verbose:
+        print(" ".join(cmd))
+    subprocess.run(cmd, check=True)
+    return HOST
+
+
 def build(verbose: bool = False, extra=()) -> str:
     """One object per source, compiled side by side (the two large files take a minute
     each), then one link."""
@@ -42,7 +61,9 @@ def build(verbose: bool = False, extra=()) -> str:
 
     jobs = min(len(SOURCES), int(os.environ.get("MAX_JOBS", "0")) or os.cpu_count() or 1, 8)
     with ThreadPoolExecutor(max_workers=jobs) as pool:
+        host = pool.submit(build_host, verbose)
         objs = list(pool.map(compile_one, SOURCES))
+        host.result()
     cmd = [hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB]
     if verbose:
         print(" ".join(cmd))

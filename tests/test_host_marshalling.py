@@ -1,0 +1,90 @@
+"""The native marshalling of the binding's calls (csrc/host.cpp) against the long way through ctypes: the
+same results and the same refusals, and every call that is not of the ordinary form left to the long way."""
+import pytest
+import torch
+
+from paper_2310_03675_amd import binding as B
+
+NE, ST = B.ROUND_NEAREST, B.ROUND_STOCHASTIC
+
+
+def _prm(n=64, a=8, s=32, seed=5, A=(4, NE), Bq=(4, NE)):
+    return B.Params(had_block=n, acc_bits=a, s=s, seed=seed, A=B.Operand(*A, 0.975, 2), B=B.Operand(*Bq, 1.0, 3))
+
+
+def test_calls_of_another_form_are_left_alone():
+    """CPU tensors, wrong types and missing attributes: None, no error left behind."""
+    B.load()
+    X, p = torch.zeros(64, 64), _prm()
+    assert B._host.layer_step(X, X, X, p, p, p, None, None, None) is None
+    assert B._host.quantize(X, 1, 64, p.A, 0, None) is None
+    assert B._host.quantize(None, 1, 64, p.A, 0, None) is None
+    assert B._host.gemm(0, X, X, 64, 64, 64, p, None, None, False, None, None, False, None) is None
+    assert B._host.layer_step(X, X) is None
+    with pytest.raises(ValueError):
+        B.quantize(X, 1, 64, p.A)
+
+
+def _calls():
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    new = lambda *shape: torch.randn(shape, generator=g, device="cuda")
+    M, K, N = 96, 72, 40
+    X, W, G, act = torch.relu(new(M, K)), new(K, N), new(M, N), torch.relu(new(2, 8, 8, 8))
+    Wc, Gc, mask = new(72, 24), new(128, 24), torch.relu(new(M, K))
+    st = lambda **k: _prm(Bq=(4, ST), **k)
+    fwd, bwi, bww = _prm(), _prm(A=(4, ST)), st(seed=2 ** 64 - 1)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+
+    def bwd(**k):
+        _, saved = B.layer_fwd(X, W, fwd, bww)
+        return B.layer_bwd(G, W, saved, K, bwi, bww, **k)
+
+    def conv(**k):
+        Z, saved = B.conv_fwd(act, 3, 3, Wc, fwd, bww)
+        return (Z,) + B.conv_bwd(Gc, Wc, saved, act.shape, 3, 3, bwi, bww, **k)
+
+    out = tuple(torch.empty(s, device="cuda") for s in ((M, N), (M, K), (K, N)))
+    return [
+        lambda: B.quantize(X, 0, 64, B.Operand(4, ST, 1.0, 7), 2 ** 64 - 1), lambda: B.quantize(X, 1, 16, B.Operand(8), -1),
+        lambda: B.gemm(0, X, W, M, K, N, fwd, want_acc=True)[:2], lambda: B.gemm(1, G, W, M, K, N, bwi, bf16=True)[:1],
+        lambda: B.gemm(1, G, W, M, K, N, bwi, mask=mask)[:1], lambda: B.gemm(2, X, G, M, K, N, bww, stream=side)[:1],
+        lambda: B.layer_step(X, W, G, fwd, bwi, bww)[:3], lambda: B.layer_step(X, W, G, fwd, None, bww)[:3],
+        lambda: B.layer_step(X, W, G, fwd, bwi, bww, out=out)[:3], lambda: B.layer_fwd(X, W, fwd)[:1], bwd,
+        lambda: bwd(mask=X), conv, lambda: conv(mask=act),
+        # refused by the library, and of another form
+        lambda: B.gemm(0, X, W, M, K, N, _prm(n=48)), lambda: B.layer_step(X, W, G, fwd, bwi, _prm(s=0)),
+        lambda: B.conv_fwd(act, 2, 2, new(32, 8), fwd, bww), lambda: B.quantize(X, 2, 64, B.Operand()),
+        lambda: B.quantize(X.t(), 1, 64, B.Operand()), lambda: B.gemm(0, X, W, M, K, N, _prm(n="64")),
+        lambda: B.layer_step(X, G, W, fwd, bwi, bww)]
+
+
+def _outcome(call):
+    try:
+        r = call()
+    except Exception as exc:
+        return type(exc), getattr(exc, "code", None), str(exc) if isinstance(exc, B.HdqtError) else None
+    torch.cuda.synchronize()
+    return [None if t is None else (t.dtype, tuple(t.shape), t.clone()) for t in r]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("k", range(21))
+def test_same_as_through_ctypes(k, monkeypatch):
+    class Off:
+        def __getattr__(self, name):
+            return lambda *args: None
+
+    call = _calls()[k]
+    here = _outcome(call)
+    monkeypatch.setattr(B, "_host", Off())
+    there = _outcome(call)
+    if isinstance(there, tuple):
+        assert here == there
+        return
+    assert len(here) == len(there)
+    for a, b in zip(here, there):
+        assert (a is None) == (b is None)
+        if a is not None:
+            assert a[:2] == b[:2] and torch.equal(a[2], b[2])
