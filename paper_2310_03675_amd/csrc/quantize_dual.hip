@@ -81,9 +81,12 @@ __device__ __forceinline__ void tile_load(Tile& t, const DualArgs& q, const Dual
 // The activation is read from HBM about once per pass instead of kh*kw times.
 constexpr int kPatchUnroll = 6;
 
-__device__ __forceinline__ void tile_load_conv(Tile& t, const DualArgs& q, const DualCtx& x,
+//
+// Returns whether a value of the patch has its sign bit set (the same in every lane).
+__device__ __forceinline__ bool tile_load_conv(Tile& t, const DualArgs& q, const DualCtx& x,
                                                int64_t row0, int64_t col0, float* patch, int lane)
 {
+    uint32_t signs = 0;
     const int W = q.cW, H = q.cH, C = q.cC, kw = q.ckw, khw = q.ckh * q.ckw;
     const int ph = (q.ckh - 1) / 2, pw = (kw - 1) / 2;
     const int PH = q.pPH, PW = q.pPW, CN = q.pCN;
@@ -133,6 +136,7 @@ __device__ __forceinline__ void tile_load_conv(Tile& t, const DualArgs& q, const
 #pragma unroll
             for (int k = 0; k < kPatchUnroll; ++k) {
                 if (dst[k] < 0) continue;
+                signs |= (as_u(v[k].x) | as_u(v[k].y)) | (as_u(v[k].z) | as_u(v[k].w));
                 float* d = patch + dst[k];
                 d[0] = v[k].x; d[1] = v[k].y; d[2] = v[k].z; d[3] = v[k].w;
             }
@@ -153,6 +157,7 @@ __device__ __forceinline__ void tile_load_conv(Tile& t, const DualArgs& q, const
                 v = img[off + gx];
                 if (!in) v = 0.0f;
             }
+            signs |= as_u(v);
             patch[r * PW + px] = v;
         }
     }
@@ -210,6 +215,7 @@ __device__ __forceinline__ void tile_load_conv(Tile& t, const DualArgs& q, const
             }
         }
     }
+    return __builtin_amdgcn_ballot_w64((int)signs < 0) != 0;
 }
 
 // Random bits of stochastic rounding for the lane's elements of one tile row: four
@@ -479,6 +485,64 @@ __device__ __forceinline__ void dual_set_scaling(DualCtx& x, const DualArgs& q, 
     }
 }
 
+template <int CTRL>
+__device__ __forceinline__ float add_dpp(float x)
+{
+    return x + dpp_move<CTRL>(x);
+}
+
+// Both maxima of a tile without negative values, block orders 8 to 64.  The largest output of a
+// block is then its sum, in the order of the butterfly's own output 0: by induction over the stages no
+// |a +- c| exceeds the sum of the values below it, because rounding is monotone (an infinity gives
+// infinity and a NaN a block that counts for nothing, both ways).  So the sums replace the butterflies,
+// one addition per pair instead of two outputs: 190 vector instructions a tile instead of 900.  What a
+// convolution reads is what a rectifier wrote, and these passes are bound by vector issue:
+// 262144 x 576 from 256 x 64 x 32 x 32 91 -> 49 us, 32768 x 320 from 256 x 64 x 1 x 128 15 -> 8.
+__device__ __forceinline__ void sums_absmax(const Tile& t, const DualCtx& x, float& amax_row, float& amax_col)
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        float s[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            s[h] = (t.v[h][0][i] + t.v[h][1][i]) + (t.v[h][2][i] + t.v[h][3][i]);
+            s[h] = add_dpp<0xB1>(s[h]);                                   // lane ^ 1
+            if (x.log2n_row > 3) s[h] = add_dpp<0x4E>(s[h]);              // lane ^ 2
+            if (x.log2n_row > 4) s[h] = add_dpp<0x141>(s[h]);             // the other quad of eight lanes
+        }
+        if (x.log2n_row > 5) amax_row = fmaxf(amax_row, s[0] + s[1]);
+        else amax_row = fmaxf(amax_row, fmaxf(s[0], s[1]));
+    }
+    float c[8];                                                           // of column 32h + 4cg + j: c[4h + j]
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const float* v = t.v[k >> 2][k & 3];
+        c[k] = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+        if (x.log2n_col > 3) c[k] = add_dpp<0x128>(c[k]);                 // lane ^ 8
+    }
+    // (a swap brings the two halves of a pair into one lane: c[k]'s in the lower lanes, c[k + 1]'s in the upper)
+    int n = 8;
+    if (x.log2n_col > 4) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const v2u r = __builtin_amdgcn_permlane16_swap(as_u(c[2 * k]), as_u(c[2 * k + 1]), false, false);
+            c[k] = as_f(r[0]) + as_f(r[1]);
+        }
+        n = 4;
+    }
+    if (x.log2n_col > 5) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const v2u r = __builtin_amdgcn_permlane32_swap(as_u(c[2 * k]), as_u(c[2 * k + 1]), false, false);
+            c[k] = as_f(r[0]) + as_f(r[1]);
+        }
+        n = 2;
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+        if (k < n) amax_col = fmaxf(amax_col, c[k]);
+}
+
 // both maxima of a tile; `t` is spent afterwards
 __device__ __forceinline__ void dual_absmax(Tile& t, const DualCtx& x, int64_t row0, int64_t col0,
                                             float& amax_row, float& amax_col)
@@ -594,8 +658,9 @@ __device__ __forceinline__ void dual_block(const DualBatch& b, int k, int vb, fl
         max_col = fetch_maxima(q.meta_col, dense);
     }
     Tile t;
+    bool signs = true;                   // (of an ordinary source nobody asks: its passes wait for memory)
     if (live) {
-        if (CONV && q.conv) tile_load_conv(t, q, x, row0, col0, lds + wave * b.lds_per_wave, lane);
+        if (CONV && q.conv) signs = tile_load_conv(t, q, x, row0, col0, lds + wave * b.lds_per_wave, lane);
         else tile_load(t, q, x, row0, col0);
     }
     if (QUANT) {
@@ -605,7 +670,8 @@ __device__ __forceinline__ void dual_block(const DualBatch& b, int k, int vb, fl
         if (live) dual_codes<(ROUND & 1) != 0, (ROUND & 2) != 0, (ROUND & kRoundWide) != 0>(t, x, row0, col0);
     } else {
         float amax_row = 0.0f, amax_col = 0.0f;
-        if (live) dual_absmax(t, x, row0, col0, amax_row, amax_col);
+        if (CONV && !signs && x.log2n_row >= 3 && x.log2n_col >= 3) sums_absmax(t, x, amax_row, amax_col);
+        else if (live) dual_absmax(t, x, row0, col0, amax_row, amax_col);
         record_max2(amax_row, amax_col, q.meta_row, q.meta_col, red, local, b.dense);
     }
 }
