@@ -8,8 +8,8 @@
 // after the other (11 us), and a split contraction adds a launch.  Here a workgroup owns one
 // block of 32 x 32 outputs and its four waves share the contraction between them, whole tiles
 // each; the totals meet in LDS, so that nothing is left for a second launch.  The operands go
-// from memory straight to the registers the matrix core reads (a lane's 16 codes of a step are
-// eight consecutive bytes), four steps ahead of the multiplication and without a barrier.  Every
+// from memory straight to the registers the matrix core reads (16 bytes a lane and load, halves of which change
+// places across the wave), four steps ahead of the multiplication and without a barrier.  Every
 // element is fetched once per 32 rows of the other operand: small products live in the L2 caches.
 // Up to three products share a launch (a layer's forward product and both gradients).
 
@@ -40,6 +40,7 @@ constexpr int kModeWide = 4;
 // codes at any byte address
 struct __attribute__((packed)) Bytes4 { uint32_t v; };
 struct __attribute__((packed)) Bytes8 { uint32_t x, y; };
+struct __attribute__((packed, aligned(4))) Words4 { uint32_t w[4]; };
 
 // The 8 bytes of codes at byte `at` of an operand, of which `codes` (any number, also none) lie
 // inside their line, the others as zeros: the 8 bytes up to the line's end (or the operand's first 8,
@@ -95,6 +96,70 @@ __device__ __forceinline__ Codes<WIDE> load_step(const uint8_t* q, uint32_t line
     return w;
 }
 
+// the upper half of the wave's v and the lower half's w change places
+__device__ __forceinline__ void swap_halves(uint32_t v, uint32_t w, uint32_t& x, uint32_t& y)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(v, w, false, false);
+    x = r[0];
+    y = r[1];
+}
+
+// N units of 32 bytes of a lane's line from byte k on, 16 bytes a lane: the lower half of the wave has a
+// unit's first 16, the upper half the others.  What these loads cost is not their bytes but that every
+// lane's are in a line of its own: with 8 bytes a lane a CU took some 80 cycles for each, three times
+// what its matrix cores needed for the step.
+// RAGGED: lines that do not start on a dword.  Loads of 16 bytes from such addresses cost twice, so the aligned
+// dwords are fetched and shifted into place; the dword behind a lane's four is the first of the lane that
+// has the next 16 bytes, only the last unit's upper half has to fetch it.  (2074 x 355 x 555, packed: 8.0 us
+// unaligned, 6.6 with a dword more per load, @R@.)
+template <bool RAGGED, int N>
+__device__ __forceinline__ void load_units(const uint8_t* q, uint32_t line, uint32_t k, int half, Words4 (&out)[N])
+{
+    const uint8_t* p = q + k;                                            // (the same in every lane)
+    const uint32_t at = (line & ~3u) + 16 * (uint32_t)half, phase = line & 3u;
+#pragma unroll
+    for (int u = 0; u < N; ++u) out[u] = *reinterpret_cast<const Words4*>(p + (at + 32 * u));
+    if constexpr (RAGGED) {
+        // (the dword that holds the last byte)
+        const uint32_t behind = *reinterpret_cast<const uint32_t*>(p + ((line + 32 * N - 1) & ~3u));
+        Words4 d[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) d[u] = out[u];
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            uint32_t of_upper, of_lower;
+            swap_halves(d[u].w[0], u + 1 < N ? d[u + 1 < N ? u + 1 : u].w[0] : behind, of_lower, of_upper);
+            const uint32_t next = half ? of_lower : of_upper;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                out[u].w[i] = __builtin_amdgcn_alignbyte(i < 3 ? d[u].w[i < 3 ? i + 1 : 3] : next, d[u].w[i], phase);
+        }
+    }
+}
+
+// A unit's codes: two steps of packed codes, one with a byte per code.  A lane has 16 consecutive bytes where
+// the matrix core wants its share of either half: half the dwords change places with the other half of the wave.
+template <bool WIDE, bool HALF>
+__device__ __forceinline__ void unit_codes(const Words4& u, Codes<WIDE>* c)
+{
+    uint32_t x[4];
+    if constexpr (!WIDE && HALF) {           // tiles of 16: dwords 0, 1 are the first tile's of the step, one per half
+        swap_halves(u.w[0], u.w[1], x[0], x[2]);
+        swap_halves(u.w[2], u.w[3], x[1], x[3]);
+    } else if constexpr (!WIDE || HALF) {    // 16 bytes are a step, or a tile: two dwords per half
+        swap_halves(u.w[0], u.w[2], x[0], x[2]);
+        swap_halves(u.w[1], u.w[3], x[1], x[3]);
+    } else {
+        for (int i = 0; i < 4; ++i) x[i] = u.w[i];
+    }
+    if constexpr (WIDE) {
+        c[0] = Codes<WIDE>{x[0], x[1], x[2], x[3]};
+    } else {
+        c[0] = Codes<WIDE>{x[0], x[1]};
+        c[1] = Codes<WIDE>{x[2], x[3]};
+    }
+}
+
 // the fragment(s) the matrix core wants: packed codes as bytes 16 * code, even positions first
 template <bool WIDE>
 __device__ __forceinline__ v4i whole(Codes<WIDE> w)
@@ -139,6 +204,7 @@ struct SmallArgs {
     int mode;                        // Mode, + kModeWide with a byte per code
     int unit, units;                 // what the waves share out (a tile, or a step), and how many there are
     int steps_per_tile;
+    int ragged;                      // lines that do not start on a dword
     Divisor n_ct;                    // blocks along a row of the output
 };
 
@@ -149,12 +215,13 @@ __device__ __forceinline__ SmallArgs whole_args(const SmallArgs& x)
     asm volatile("" ::"s"(g.qA), "s"(g.qB), "s"(g.scaleA), "s"(g.scaleB), "s"(g.out), "s"(g.out_bf16), "s"(g.acc_out),
                  "s"(g.mask_src), "s"(g.pitchA), "s"(g.pitchB), "s"(g.RA), "s"(g.RB), "s"(g.D), "s"(g.acc_lo_scaled),
                  "s"(g.acc_hi_scaled), "s"(g.inv_n), "s"(g.mode), "s"(g.unit), "s"(g.units), "s"(g.steps_per_tile),
+                 "s"(g.ragged),
                  "s"(g.n_ct.d), "s"(g.n_ct.mul), "s"(g.n_ct.sh1), "s"(g.n_ct.sh2));
     return g;
 }
 
 // The totals of a wave: the 32 x 32 block at (row0, col0), codes [k_begin, k_end), whole tiles.
-template <bool WIDE, int MODE>
+template <bool WIDE, int MODE, bool RAGGED>
 __device__ __forceinline__ v16i contract(const SmallArgs& g, int row0, int col0, int k_begin, int k_end)
 {
     constexpr bool HALF = MODE == MODE_HALF;
@@ -168,17 +235,35 @@ __device__ __forceinline__ v16i contract(const SmallArgs& g, int row0, int col0,
         Codes<WIDE> a[G], b[G];
     };
     const int whole_steps = k_end > k_begin ? (k_end - k_begin) / kStep : 0, k_whole = k_begin + whole_steps * kStep;
-    // the group of steps at k; past the whole steps: zeros (a tile of them adds nothing)
+    constexpr int PER_UNIT = WIDE ? 1 : 2, N = G / PER_UNIT;
+    // a group of whole steps
     auto fetch = [&](Group& f, int k) {
+        Words4 a[N], b[N];
+        load_units<RAGGED, N>(g.qA, la, (uint32_t)(WIDE ? k : k >> 1), half, a);
+        load_units<RAGGED, N>(g.qB, lb, (uint32_t)(WIDE ? k : k >> 1), half, b);
 #pragma unroll
-        for (int i = 0; i < G; ++i) {
-            Codes<WIDE> a = 0, b = 0;
-            if (k + kStep * i < k_whole) {
-                a = load_step<WIDE, HALF, false>(g.qA, la, k + kStep * i, half, 0);
-                b = load_step<WIDE, HALF, false>(g.qB, lb, k + kStep * i, half, 0);
+        for (int u = 0; u < N; ++u) {
+            unit_codes<WIDE, HALF>(a[u], f.a + u * PER_UNIT);
+            unit_codes<WIDE, HALF>(b[u], f.b + u * PER_UNIT);
+        }
+    };
+    // what is left of the whole steps, fewer than a group; behind them zeros (a tile of them adds nothing)
+    auto fetch_rest = [&](Group& f, int k) {
+#pragma unroll
+        for (int i = 0; i < G; i += PER_UNIT) {
+            const int at = k + kStep * i;
+#pragma unroll
+            for (int j = 0; j < PER_UNIT; ++j) f.a[i + j] = f.b[i + j] = 0;
+            if (at + kStep * PER_UNIT <= k_whole) {
+                Words4 a[1], b[1];
+                load_units<RAGGED, 1>(g.qA, la, (uint32_t)(WIDE ? at : at >> 1), half, a);
+                load_units<RAGGED, 1>(g.qB, lb, (uint32_t)(WIDE ? at : at >> 1), half, b);
+                unit_codes<WIDE, HALF>(a[0], f.a + i);
+                unit_codes<WIDE, HALF>(b[0], f.b + i);
+            } else if (at < k_whole) {
+                f.a[i] = load_step<WIDE, HALF, false>(g.qA, la, at, half, 0);
+                f.b[i] = load_step<WIDE, HALF, false>(g.qB, lb, at, half, 0);
             }
-            f.a[i] = a;
-            f.b[i] = b;
         }
     };
     const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
@@ -220,13 +305,21 @@ __device__ __forceinline__ v16i contract(const SmallArgs& g, int row0, int col0,
             }
         }
     };
+    const int full = whole_steps / G;        // groups
     Group now, next;
-    fetch(now, k_begin);
-    for (int done = 0; done < whole_steps; done += G) {
-        fetch(next, k_begin + (done + G) * kStep);
-        multiply(now, whole_steps - done, std::integral_constant<int, G>{});
-        now = next;
+    if (full) {
+        // (the loop's loads are unconditional: the compiler can count them and waits for the older ones only)
+        fetch(now, k_begin);
+        for (int done = 1; done < full; ++done) {
+            fetch(next, k_begin + done * G * kStep);
+            multiply(now, G, std::integral_constant<int, G>{});
+            now = next;
+        }
     }
+    const int rest = whole_steps - full * G;
+    if (rest) fetch_rest(next, k_whole - rest * kStep);
+    if (full) multiply(now, G, std::integral_constant<int, G>{});
+    if (rest) multiply(next, rest, std::integral_constant<int, G>{});
     if (k_whole < k_end) {                   // the line ends inside a step
         Group last{};
         last.a[0] = load_step<WIDE, HALF, true>(g.qA, la, k_whole, half, k_end - k_whole);
@@ -269,13 +362,16 @@ __global__ __launch_bounds__(64 * kWaves, 4) void gemm_small_kernel(SmallBatch b
     if (k_end > g.D) k_end = g.D;
 
     v16i total;
+#define HDQT_CONTRACT(WIDE, MODE)                                                                        \
+    total = g.ragged ? contract<WIDE, MODE, true>(g, row0, col0, k_begin, k_end) : contract<WIDE, MODE, false>(g, row0, col0, k_begin, k_end)
     switch (g.mode) {
-    case MODE_TILES: total = contract<false, MODE_TILES>(g, row0, col0, k_begin, k_end); break;
-    case MODE_SAT8: total = contract<false, MODE_SAT8>(g, row0, col0, k_begin, k_end); break;
-    case MODE_HALF: total = contract<false, MODE_HALF>(g, row0, col0, k_begin, k_end); break;
-    case MODE_TILES + kModeWide: total = contract<true, MODE_TILES>(g, row0, col0, k_begin, k_end); break;
-    default: total = contract<true, MODE_HALF>(g, row0, col0, k_begin, k_end); break;
+    case MODE_TILES: HDQT_CONTRACT(false, MODE_TILES); break;
+    case MODE_SAT8: HDQT_CONTRACT(false, MODE_SAT8); break;
+    case MODE_HALF: HDQT_CONTRACT(false, MODE_HALF); break;
+    case MODE_TILES + kModeWide: HDQT_CONTRACT(true, MODE_TILES); break;
+    default: HDQT_CONTRACT(true, MODE_HALF); break;
     }
+#undef HDQT_CONTRACT
 
 #pragma unroll
     for (int r = 0; r < 16; ++r) meet[wave][r][lane] = total[r];
@@ -394,6 +490,7 @@ hipError_t launch_gemm_small(const GemmArgs* gs, int n, hipStream_t stream)
         a.unit = (int)(g.s < kStep || g.acc_hi == INT_MAX ? kStep : g.s);
         a.units = (int)((g.D + a.unit - 1) / a.unit);
         a.steps_per_tile = (int)(g.s / kStep);
+        a.ragged = g.pitchA % 4 != 0 || g.pitchB % 4 != 0;
         a.n_ct = make_divisor((uint32_t)((g.RB + 31) / 32));
         b.first[k] = (int)total;
         total += (int64_t)a.n_ct.d * ((g.RA + 31) / 32);

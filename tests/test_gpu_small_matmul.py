@@ -95,3 +95,11 @@ def test_step_equals_its_products_where_they_take_other_routes(M, K, N, b, s, a)
     kinds = (B.GEMM_FWD, X, W), (B.GEMM_BWD_INPUT, G, W), (B.GEMM_BWD_WEIGHT, X, G)
     for got, (kind, P, Q), p in zip(step, kinds, prm):
         assert torch.equal(got, B.gemm(kind, P, Q, M, K, N, p)[0])
+
+
+@pytest.mark.parametrize("s,a,b", [(32, 8, 4), (64, 12, 4), (16, 8, 4), (96, 10, 3), (32, 16, 8), (16, 12, 6), (64, 16, 5)])
+def test_every_length_of_a_waves_chain(s, a, b):
+    """Chains of no step to ten per wave, whole groups of loads and remainders, lines of every phase modulo
+    four bytes, aligned and ragged, ends inside a step and inside a tile."""
+    for D in [8 * k for k in (3, 5, 8, 9, 17, 33, 52, 63, 80, 129, 160)] + [k for k in (33, 65, 130, 199, 262, 325, 519, 645, 1034, 1282)]:
+        check_gemm_codes(70, 45, D, b, b, s, a, extreme=0.2)
