@@ -405,50 +405,52 @@ int mode_of(const GemmArgs& g)
     return MODE_TILES + (g.bA > 4 ? kModeWide : 0);
 }
 
-// The products this kernel is the faster one for.  Measured on codes alone, the large tiles'
-// kernel (with the sum over a split contraction's parts) against this one, 4-bit codes in tiles of 32
-// unless said otherwise, 7.5 us being what any call costs: 128 x 561 x 561 (rows x columns x
-// contraction) 14.6 / 7.9; 1024 x 256 x 1024 14.6 / 8.0; 512 x 512 x 4608 23.7 / 12.5; 8192 x 256 x 1152
-// 27.0 / 19.8; 8192 x 128 x 1152 23.7 / 11.4, with a byte per code 23.3 / 21.4, in tiles of 16 25.0 / 20.9.
-// The lines: a wave's chain of steps (1152 x 128 x 8192 16.5 / 18.6); the steps in all, of which
-// those of bytes and of tiles of 16 cost twice as much (8192 x 256 x 1152, byte codes, 27.1 / 38.6);
-// the number of workgroups (65536 x 64 x 27 8.0 / 14.6).  Where the other kernel does not split the
-// contraction it is ahead earlier (4096 x 512 x 256 8.0 / 10.0), except for ragged rows
-// (2947 x 561 x 561 16.7 / 13.7, 4096 x 256 x 561 19.6 / 9.1; but 32768 x 64 x 27 7.8 / 8.7).
-//
-// Inside these lines the other kernel is still ahead of long chains of few workgroups or of one too
-// many per CU (224 x 256 x 4480 in tiles of 16 13.8 / 20.2; 288 blocks of bytes, 2299 x 128 x 3712, 19.7 /
-// 31.0), where that kernel splits the contraction and these do not take the paper's clamp: both times
-// are estimated, in us, and the other kernel taken where it is clearly ahead.  The constants fit 6037
-// products of all kinds and random sizes inside the lines, of which the lines alone put 110 on a kernel
-// that is more than 15 % slower (of those that take over 10 us); with the estimates 47, and 3 are new.
-bool estimated_faster(const GemmArgs& g, int64_t blocks, int64_t steps)
+// The products this kernel is the faster one for, by an estimate in us of what a call takes longer with it than
+// with the large tiles' kernel (gemm_fast.hip, and the sum over a split contraction's parts): a sum over what
+// the product has of
+//   here: steps of a wave's chain; steps, and blocks, per CU; the same steps where lines do not start on a
+//     dword; rounds of workgroups (four per CU) beyond the first;
+//   there: stages in a row; the second launch, and the slices' elements (10^6), of a split; the output's elements;
+//     the stages again where rows are no whole dwords; tiles per place of the chip;
+// and a difference of what any launch takes.  The coefficients are least squares over 900 forward products and
+// gradients of random sizes (outputs of 16 to 20000 rows and columns, contractions from 16 to 20000) and settings, each
+// timed with its quantization and both kernels: the choice takes 0.3 % more time than the better of the two would,
+// always this kernel 6.8 %, never 13.7 %.  Codes alone, there / here: 3505 x 456 x 640 23.8 / 9.2 us, 667 x 320 x 2080
+// 17.5 / 5.2, 467 x 3208 x 576 in tiles of 16 17.2 / 10.2, but 8513 x 1396 x 64 15.4 / 25.7, 250 x 200 x 64384 22 / 105.
+// A product that shares its launch with others does not pay for one here (an empty kernel: 1.6 us).
+struct Estimate {
+    double here[5], there[6], launch;
+};
+constexpr Estimate kEstimates[4] = {
+    {{0.127, 0.0171, 0.316, 0.0080, 0.0}, {1.175, 2.70, 1.484, 0.0, 0.186, 1.746}, -3.12},          // MODE_SAT8
+    {{0.172, 0.0159, 0.711, 0.0056, 0.800}, {0.565, 2.84, 1.223, 2.514, 0.083, 0.0}, -3.97},        // MODE_TILES
+    {{0.295, 0.0252, 1.079, 0.0046, 0.348}, {1.802, 4.30, 1.081, 2.692, 0.0, 4.412}, -3.40},        // MODE_HALF
+    {{0.229, 0.0316, 0.489, 0.0349, 1.323}, {1.228, 2.83, 0.315, 1.227, 0.698, 7.491}, -3.13}};     // a byte per code
+constexpr double kLaunchUs = 1.6;
+
+bool faster_here(const GemmArgs& g, bool alone)
 {
     const bool wide = g.bA > 4, half = g.s < kStep, ragged = g.D % (wide ? 4 : 8) != 0;
-    const double chain = (double)(steps * ((blocks + 255) / 256)) * (g.pitchA % 4 != 0 ? 1.35 : 1.0);
-    const double here = 5.5 + chain * (wide || half ? 0.075 : 0.043);
-    const int64_t tiles = ((g.RA + 127) / 128) * ((g.RB + 127) / 128), stages = (steps + 3) / 4;
-    const int64_t rounds = (tiles * g.splits + 511) / 512, in_a_row = (stages + g.splits - 1) / g.splits * rounds;
-    const double stage = (half ? 1.7 : wide ? 0.65 : 0.47) + (!ragged ? 0.0 : half ? 1.2 : 0.2);
-    // (two launches, and every part's slice written and read)
-    const double there = 9.4 + (double)in_a_row * stage + 0.4e-6 * (double)g.splits * (double)(g.RA * g.RB) * sizeof(int32_t);
-    return here <= 1.05 * there;
+    const Estimate& e = kEstimates[wide ? 3 : half ? 2 : mode_of(g) == MODE_SAT8 ? 0 : 1];
+    const int64_t blocks = ((g.RA + 31) / 32) * ((g.RB + 31) / 32), steps = (g.D + kStep - 1) / kStep, rounds = (blocks + 1023) / 1024;
+    // (masked outputs: 4096 x 640 x 128 takes 17.9 to 20.2 us here and 19.2 to 19.6 there, with the mask's own pass)
+    if (g.mask_src && blocks > 2048) return false;
+    const double per_cu = (double)blocks / 256.0, outputs = 1e-6 * (double)g.RA * (double)g.RB;
+    const double here = e.here[0] * (double)steps / kWaves + (e.here[1] + (g.pitchA % 4 != 0 ? e.here[3] : 0.0)) * (double)steps * per_cu +
+                        e.here[2] * per_cu + e.here[4] * (double)(rounds - 1) + e.launch - (alone ? 0.0 : kLaunchUs);
+    const int64_t across = g.RB <= 64 && !wide && !half ? 64 : 128, stages = (steps + 3) / 4;
+    const int64_t tiles = ((g.RA + 127) / 128) * ((g.RB + across - 1) / across), places = (tiles * g.splits + 511) / 512;
+    const double in_a_row = (double)((stages + g.splits - 1) / g.splits * places);
+    const double there = (e.there[0] + (ragged ? e.there[4] : 0.0)) * in_a_row + e.there[3] * outputs +
+                         (g.splits > 1 ? e.there[1] + e.there[2] * g.splits * outputs : 0.0) + e.there[5] * (double)(tiles * g.splits) / 512.0;
+    return here <= there;
 }
 
+// (32-bit offsets into the operands)
 bool small_enough(const GemmArgs& g, bool alone)
 {
-    const bool wide = g.bA > 4;
-    const int64_t blocks = ((g.RA + 31) / 32) * ((g.RB + 31) / 32), steps = (g.D + kStep - 1) / kStep;
-    const int64_t cost = blocks * steps * (wide || g.s < kStep ? 2 : 1);
-    const bool ragged = g.D % (wide ? 4 : 8) != 0 && steps >= 8;
-    if (g.D > 4608 || (g.RA + g.RB) * (g.pitchA + g.pitchB) >= ((int64_t)1 << 31)) return false;
-    if (g.splits > 1 ? blocks > 2048 || cost > 73728 : blocks > (ragged ? 2048 : 512) || cost > 36864) return false;
-    // (in the paper's setting, and where the other kernel does not split the contraction, the lines are
-    // good enough and the estimates are not: 320 x 1024 x 4384, 2947 x 561 x 561; and where the launch
-    // is there for other products anyway a long chain runs beside them.  Steps, the weight gradient by
-    // itself / in company: 3564 x 1152 x 32 in bytes 57.4 / 50.7, 2058 x 144 x 64 28.0 / 22.6, 2160 x 3456
-    // x 32 75.4 / 66.5, but 3969 x 144 x 128 39.9 / 53.1; of 400 random steps 38 gain over 2 %, 8 lose)
-    return !alone || mode_of(g) == MODE_SAT8 || g.splits == 1 || estimated_faster(g, blocks, steps);
+    if ((g.RA + g.RB) * (g.pitchA + g.pitchB) >= ((int64_t)1 << 31)) return false;
+    return faster_here(g, alone);
 }
 
 } // namespace
