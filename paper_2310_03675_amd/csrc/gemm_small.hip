@@ -37,6 +37,12 @@ constexpr int kWaves = 4;            // waves of a workgroup (eight: 2947 x 561 
 enum Mode { MODE_TILES = 0, MODE_SAT8 = 1, MODE_HALF = 2 };
 constexpr int kModeWide = 4;
 
+// How the codes come from memory: FETCH_LINES 16 bytes of a line of its own per lane, FETCH_RAGGED the same where
+// lines do not start on a dword, FETCH_STAGED 64 bytes of a line per four lanes, through LDS.
+enum Fetch { FETCH_LINES = 0, FETCH_RAGGED = 1, FETCH_STAGED = 2 };
+constexpr int kStageLine = 80;               // bytes from line to line in LDS (of 64: the reads of eight lines meet no bank twice)
+constexpr int kStage = 2 * 32 * kStageLine;  // bytes per wave (and its totals, in the end)
+
 // codes at any byte address
 struct __attribute__((packed)) Bytes4 { uint32_t v; };
 struct __attribute__((packed)) Bytes8 { uint32_t x, y; };
@@ -221,11 +227,18 @@ __device__ __forceinline__ SmallArgs whole_args(const SmallArgs& x)
 }
 
 // The totals of a wave: the 32 x 32 block at (row0, col0), codes [k_begin, k_end), whole tiles.
-template <bool WIDE, int MODE, bool RAGGED>
-__device__ __forceinline__ v16i contract(const SmallArgs& g, int row0, int col0, int k_begin, int k_end)
+//
+// STAGED: chunks of 64 bytes of every line go through the wave's own piece of LDS, in which four lanes fetch a line's
+// 64 bytes and two read them: a load's lanes then touch 16 lines instead of 32, and what a CU takes for it (77 cycles
+// otherwise) no longer decides.  That costs every chain a trip through LDS per chunk, so it is for launches with
+// enough of them per CU (launch_gemm_small).
+template <bool WIDE, int MODE, int FETCH>
+__device__ __forceinline__ v16i contract(const SmallArgs& g, int row0, int col0, int k_begin, int k_end, uint8_t* stage)
 {
+    constexpr bool RAGGED = FETCH == FETCH_RAGGED;
     constexpr bool HALF = MODE == MODE_HALF;
-    constexpr int G = WIDE || HALF ? 2 : 4;  // steps per group of loads (tiles of 16 keep the sums of two a step)
+    // steps per group of loads (tiles of 16 keep the sums of two a step; staged: what is left of a chunk)
+    constexpr int G = FETCH == FETCH_STAGED ? (WIDE ? 2 : 4) : WIDE || HALF ? 2 : 4;
     const int lane = threadIdx.x & 63, half = lane >> 5;
     // (rows outside the operands: the last one, nothing of it is written)
     const int ra = row0 + (lane & 31), rb = col0 + (lane & 31);
@@ -305,8 +318,59 @@ __device__ __forceinline__ v16i contract(const SmallArgs& g, int row0, int col0,
             }
         }
     };
-    const int full = whole_steps / G;        // groups
     Group now, next;
+    if constexpr (FETCH == FETCH_STAGED) {
+        constexpr int CHUNK = 2 * PER_UNIT * kStep;                      // codes of 64 bytes
+        const int chunks = (k_whole - k_begin) / CHUNK, k_rest = k_begin + chunks * CHUNK;
+        const int quarter = lane & 3, line = lane >> 2;
+        const uint8_t *pa[2], *pb[2];                                    // lines `line` and line + 16
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int r = row0 + line + 16 * i, c = col0 + line + 16 * i;
+            pa[i] = g.qA + ((uint32_t)(r < g.RA ? r : g.RA - 1) * (uint32_t)g.pitchA + 16 * quarter);
+            pb[i] = g.qB + ((uint32_t)(c < g.RB ? c : g.RB - 1) * (uint32_t)g.pitchB + 16 * quarter);
+        }
+        Words4 r[4];
+        auto load = [&](int k) {
+            const int at = WIDE ? k : k >> 1;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                r[i] = *reinterpret_cast<const Words4*>(pa[i] + at);
+                r[2 + i] = *reinterpret_cast<const Words4*>(pb[i] + at);
+            }
+        };
+        uint8_t* put = stage + line * kStageLine + 16 * quarter;
+        const uint8_t* take = stage + (lane & 31) * kStageLine + 16 * half;
+        if (chunks) load(k_begin);
+        for (int c = 0; c < chunks; ++c) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) *reinterpret_cast<uint4*>(put + i * 16 * kStageLine) = make_uint4(r[i].w[0], r[i].w[1], r[i].w[2], r[i].w[3]);
+            if (c + 1 < chunks) load(k_begin + (c + 1) * CHUNK);
+            // LDS operations of one wave are carried out in order; the fences keep the compiler from moving
+            // them across each other
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            Words4 u[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint4 x = *reinterpret_cast<const uint4*>(take + (i >> 1) * 32 * kStageLine + (i & 1) * 32);
+                u[i] = Words4{{x.x, x.y, x.z, x.w}};
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                unit_codes<WIDE, HALF>(u[i], now.a);
+                unit_codes<WIDE, HALF>(u[2 + i], now.b);
+                multiply(now, PER_UNIT, std::integral_constant<int, PER_UNIT>{});
+            }
+        }
+        if (k_rest < k_whole) fetch_rest(next, k_rest);
+        if (k_rest < k_whole) multiply(next, (k_whole - k_rest) / kStep, std::integral_constant<int, G>{});
+    } else {
+    const int full = whole_steps / G;        // groups
     if (full) {
         // (the loop's loads are unconditional: the compiler can count them and waits for the older ones only)
         fetch(now, k_begin);
@@ -320,6 +384,7 @@ __device__ __forceinline__ v16i contract(const SmallArgs& g, int row0, int col0,
     if (rest) fetch_rest(next, k_whole - rest * kStep);
     if (full) multiply(now, G, std::integral_constant<int, G>{});
     if (rest) multiply(next, rest, std::integral_constant<int, G>{});
+    }
     if (k_whole < k_end) {                   // the line ends inside a step
         Group last{};
         last.a[0] = load_step<WIDE, HALF, true>(g.qA, la, k_whole, half, k_end - k_whole);
@@ -340,9 +405,10 @@ struct SmallBatch {
     SmallArgs g[kMaxSmallBatch];
 };
 
+template <bool STAGED>
 __global__ __launch_bounds__(64 * kWaves, 4) void gemm_small_kernel(SmallBatch b)
 {
-    __shared__ int meet[kWaves][16][64];
+    __shared__ __attribute__((aligned(16))) uint8_t lds[kWaves][kStage];
     int p = 0, local = (int)blockIdx.x;
 #pragma unroll
     for (int j = 1; j < kMaxSmallBatch; ++j) {
@@ -361,9 +427,11 @@ __global__ __launch_bounds__(64 * kWaves, 4) void gemm_small_kernel(SmallBatch b
     int k_end = g.units * (wave + 1) / kWaves * g.unit;
     if (k_end > g.D) k_end = g.D;
 
+    uint8_t* stage = lds[wave];
     v16i total;
 #define HDQT_CONTRACT(WIDE, MODE)                                                                        \
-    total = g.ragged ? contract<WIDE, MODE, true>(g, row0, col0, k_begin, k_end) : contract<WIDE, MODE, false>(g, row0, col0, k_begin, k_end)
+    total = g.ragged ? contract<WIDE, MODE, FETCH_RAGGED>(g, row0, col0, k_begin, k_end, stage)                             \
+                     : contract<WIDE, MODE, STAGED ? FETCH_STAGED : FETCH_LINES>(g, row0, col0, k_begin, k_end, stage)
     switch (g.mode) {
     case MODE_TILES: HDQT_CONTRACT(false, MODE_TILES); break;
     case MODE_SAT8: HDQT_CONTRACT(false, MODE_SAT8); break;
@@ -374,7 +442,7 @@ __global__ __launch_bounds__(64 * kWaves, 4) void gemm_small_kernel(SmallBatch b
 #undef HDQT_CONTRACT
 
 #pragma unroll
-    for (int r = 0; r < 16; ++r) meet[wave][r][lane] = total[r];
+    for (int r = 0; r < 16; ++r) reinterpret_cast<int*>(stage)[r * 64 + lane] = total[r];
     __syncthreads();
     const float dq = (scaleA * scaleB) * g.inv_n;
     const int col = col0 + (lane & 31);
@@ -383,7 +451,7 @@ __global__ __launch_bounds__(64 * kWaves, 4) void gemm_small_kernel(SmallBatch b
         const int r = wave * (16 / kWaves) + i;
         int v = 0;
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) v += meet[w][r][lane];
+        for (int w = 0; w < kWaves; ++w) v += reinterpret_cast<const int*>(lds[w])[r * 64 + lane];
         const int row = row0 + 8 * (r >> 2) + (r & 3) + 4 * (lane >> 5);
         if (row < g.RA && col < g.RB) {
             const int64_t o = (int64_t)row * g.RB + col;
@@ -473,7 +541,8 @@ hipError_t launch_gemm_small(const GemmArgs* gs, int n, hipStream_t stream)
     if (n < 1 || n > kMaxSmallBatch) return hipErrorInvalidValue;
     SmallBatch b{};
     b.n = n;
-    int64_t total = 0;
+    int64_t total = 0, work = 0;
+    bool packed_halves = false, paired = true;
     for (int k = 0; k < kMaxSmallBatch; ++k) b.first[k] = INT_MAX;
     for (int k = 0; k < n; ++k) {
         const GemmArgs& g = gs[k];
@@ -493,12 +562,23 @@ hipError_t launch_gemm_small(const GemmArgs* gs, int n, hipStream_t stream)
         a.units = (int)((g.D + a.unit - 1) / a.unit);
         a.steps_per_tile = (int)(g.s / kStep);
         a.ragged = g.pitchA % 4 != 0 || g.pitchB % 4 != 0;
+        const int64_t blocks = ((g.RA + 31) / 32) * ((g.RB + 31) / 32), steps = (g.D + kStep - 1) / kStep;
+        if (!a.ragged) work += blocks * steps;
+        packed_halves |= a.mode == MODE_HALF;
+        paired &= a.mode == MODE_SAT8;
         a.n_ct = make_divisor((uint32_t)((g.RB + 31) / 32));
         b.first[k] = (int)total;
         total += (int64_t)a.n_ct.d * ((g.RA + 31) / 32);
     }
     ProfileScope ps(n > 1 ? K_GEMM_SMALL : gs[0].profile_tag ? K_GEMM_I4_FWD + (gs[0].profile_tag - 1) : K_GEMM_I4, stream);
-    hipLaunchKernelGGL(gemm_small_kernel, dim3((unsigned)total), dim3(64 * kWaves), 0, stream, b);
+    // Steps of blocks from which the launch waits for its loads' lanes rather than for one chain: 2048 x 512 x 4608
+    // beside 4608 x 512 x 2048 (294912) 42 -> 33 us, 502 x 1053 x 9472 (156288) 29.5 -> 25.3, but 1642 x 857 x 3712 (162864)
+    // 23.1 / 23.3 and 266 x 424 x 11456 (45108) 11.7 / 15.1; other modes, whose steps take longer, earlier: 576 x 1108 x 6400
+    // (126000) 25.1 -> 20.0, 759 x 1008 x 2752 in bytes and tiles of 16 (66048) 18.0 / 18.4.  Not for packed codes in tiles
+    // of 16, whose two sums a step leave no registers for it (1280 x 2304 x 192, a step, 35 / 40).
+    const bool staged = !packed_halves && work >= (paired ? 150000 : 65536);
+    if (staged) hipLaunchKernelGGL(gemm_small_kernel<true>, dim3((unsigned)total), dim3(64 * kWaves), 0, stream, b);
+    else hipLaunchKernelGGL(gemm_small_kernel<false>, dim3((unsigned)total), dim3(64 * kWaves), 0, stream, b);
     return hipGetLastError();
 }
 

@@ -103,3 +103,10 @@ def test_every_length_of_a_waves_chain(s, a, b):
     four bytes, aligned and ragged, ends inside a step and inside a tile."""
     for D in [8 * k for k in (3, 5, 8, 9, 17, 33, 52, 63, 80, 129, 160)] + [k for k in (33, 65, 130, 199, 262, 325, 519, 645, 1034, 1282)]:
         check_gemm_codes(70, 45, D, b, b, s, a, extreme=0.2)
+
+
+@pytest.mark.parametrize("RA,RB,D,b,s,a", [(480, 1000, 12288, 4, 32, 8), (481, 1001, 12312, 4, 32, 8), (700, 640, 6000, 4, 64, 12),
+                                           (1300, 500, 4120, 8, 32, 16), (500, 900, 4136, 8, 16, 16), (500, 1000, 5184, 3, 96, 10)])
+def test_products_through_lds(RA, RB, D, b, s, a):
+    """Enough work for the chunks that go through LDS: whole chunks, what is left of one, an end inside a step."""
+    check_gemm_codes(RA, RB, D, b, b, s, a, extreme=0.1)
