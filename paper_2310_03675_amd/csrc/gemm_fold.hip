@@ -14,7 +14,8 @@
 // those passes through LDS and the barriers around them.)
 //
 // A workgroup owns 256 pixels and 64 channels; a wave 32 pixels and all 64 channels (two MFMA
-// blocks, channels as rows, so that a store writes 32 neighbouring pixels).  W goes through LDS,
+// blocks, channels as rows, so that a store writes 32 neighbouring pixels).  Where that leaves CUs idle what counts
+// is a wave's chain: half the channels and half the waves per workgroup, four times the workgroups.  W goes through LDS,
 // unpacked once per workgroup, 256 codes of the contraction at a time, double-buffered; a wave's
 // rows of G go straight to its registers, four steps ahead: the nine shifted reads of a row hit
 // the CU's L1.  What is left is the clamp: one vector instruction per tile sum.
@@ -34,14 +35,10 @@ constexpr int kStep = 32;                 // codes per MFMA
 constexpr int kChunk = 256;               // codes of the contraction per LDS buffer
 constexpr int kSteps = kChunk / kStep;
 constexpr int kAhead = 4;                 // steps of G in flight, and in hand
-constexpr int kWaves = 8;
-constexpr int kPixels = 32 * kWaves;      // of a workgroup
-constexpr int kBlocks = 2;                // 32-channel blocks of a workgroup
-constexpr int kChannels = 32 * kBlocks;
 constexpr int kPitch = kChunk + 16;       // bytes of a channel's line in LDS
 constexpr uint32_t kOutside = 0x80000000u;      // operands are smaller than 2 GB
 
-static_assert(kSteps == 2 * kAhead && kChannels * kSteps == 64 * kWaves, "one 16-byte unit of W per thread and chunk");
+static_assert(kSteps == 2 * kAhead, "a chunk is two groups of G");
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t operand_rsrc(const uint8_t* q, int64_t bytes)
 {
@@ -57,9 +54,12 @@ __device__ __forceinline__ int clamp3(int v, int lo, int hi)      // (plain C++:
 // SAT8: tiles of one step, 8-bit accumulators: two tile sums per saturating conversion, added by
 // one dot product (see EPI_SAT8_S32 in gemm_fast.hip); else tiles of whole steps and a
 // compare-select clamp, totals times 256.
-template <bool SAT8>
-__global__ __launch_bounds__(64 * kWaves, 4) void gemm_fold_kernel(GemmArgs g)
+// BLOCKS: 32-channel blocks of a workgroup; its waves are 4 per block (one 16-byte unit of W per thread and chunk).
+template <bool SAT8, int BLOCKS>
+__global__ __launch_bounds__(256 * BLOCKS, 4) void gemm_fold_kernel(GemmArgs g)
 {
+    constexpr int kBlocks = BLOCKS, kWaves = 4 * BLOCKS, kPixels = 32 * kWaves, kChannels = 32 * kBlocks;
+    static_assert(kChannels * kSteps == 64 * kWaves, "one unit of W per thread and chunk");
     __shared__ __attribute__((aligned(16))) uint8_t Ws[2][kChannels][kPitch];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5;
     const int N = (int)g.D, W = g.fW, H = g.fH, khw = g.fkh * g.fkw;
@@ -247,16 +247,28 @@ bool gemm_fold_plan(GemmArgs* g, int64_t batch, int C, int H, int W, int kh, int
     return gemm_fast_eligible(*g);
 }
 
+// Workgroups of 256 pixels and 64 channels below which the chip has too few of them.  Over 640 layers (windows of
+// 3 x 3 and 1 x 5, 32 to 256 codes a tap): 1.4 to 1.8 times faster with a quarter of that each up to 64
+// workgroups, 1.3 to 1.4 at 128, 1.04 to 1.17 at 192 (128 channels of 16 x 16, 256 codes a tap, 27.6 / 29.1 us), 0.86 to 1.08
+// at 256 to 511, 0.7 to 1.0 beyond.
+constexpr int64_t kFewWorkgroups = 192;
+
 hipError_t launch_gemm_fold(const GemmArgs& g_in, hipStream_t stream)
 {
     GemmArgs g = g_in;
     const int64_t lo = (int64_t)g.acc_lo * 256, hi = (int64_t)g.acc_hi * 256;
     g.acc_lo_scaled = lo < INT32_MIN ? INT32_MIN : (int)lo;
     g.acc_hi_scaled = hi > INT32_MAX ? INT32_MAX : (int)hi;
-    const dim3 grid((unsigned)((g.RA + kPixels - 1) / kPixels), (unsigned)((g.fC + kChannels - 1) / kChannels));
+    const int64_t wide = ((g.RA + 255) / 256) * ((g.fC + 63) / 64);
+    const int blocks = wide < kFewWorkgroups ? 1 : 2;
+    const dim3 grid((unsigned)((g.RA + 128 * blocks - 1) / (128 * blocks)), (unsigned)((g.fC + 32 * blocks - 1) / (32 * blocks)));
+    const dim3 block(256 * blocks);
     ProfileScope ps(g.profile_tag ? K_GEMM_I4_FWD + (g.profile_tag - 1) : K_GEMM_I4, stream);
-    if (g.s == kStep && g.acc_hi == 127) hipLaunchKernelGGL(gemm_fold_kernel<true>, grid, dim3(64 * kWaves), 0, stream, g);
-    else hipLaunchKernelGGL(gemm_fold_kernel<false>, grid, dim3(64 * kWaves), 0, stream, g);
+    const bool sat8 = g.s == kStep && g.acc_hi == 127;
+    if (sat8 && blocks == 1) hipLaunchKernelGGL((gemm_fold_kernel<true, 1>), grid, block, 0, stream, g);
+    else if (sat8) hipLaunchKernelGGL((gemm_fold_kernel<true, 2>), grid, block, 0, stream, g);
+    else if (blocks == 1) hipLaunchKernelGGL((gemm_fold_kernel<false, 1>), grid, block, 0, stream, g);
+    else hipLaunchKernelGGL((gemm_fold_kernel<false, 2>), grid, block, 0, stream, g);
     return hipGetLastError();
 }
 
