@@ -61,24 +61,123 @@ __global__ __launch_bounds__(kThreads) void im2col_kernel(Im2colArgs a, int widt
     }
 }
 
-// ---- folding: a workgroup has 32 pixels of the activation (of the batch's pixels in a row) and 64
-// channels.  Lanes are channels, so that the kh * kw elements a lane adds up for a pixel lie in the
-// lines its neighbours read too, and which taps there are is the same for the whole wave; the sums
-// turn through LDS and leave as runs of pixels.  The taps are added from the window's end to its
-// start, i.e. in the order of the matrix rows.
-//
-// A pixel has at most ceil(kh / stride) x ceil(kw / stride) taps, whose loads go out NY x NX at a time:
-// all of them, or (NY = 1, larger windows) along one row of the window.  Of those that fall outside
-// the matrix a zero is added.  128 x 64 x 32 x 32, window 3, stride 2: 94 -> 68 us against a loop over
-// the window that loads and adds tap by tap.
-constexpr int kFoldPixels = 32, kFoldChannels = 64;
+// ---- folding through LDS: a workgroup has a tile of TX x TY pixels of one image and CB channels.  The
+// elements that it adds up are CB * kh * kw neighbours in each of the matrix rows whose window meets the
+// tile; they are fetched as whole runs of 16 bytes a lane, and a thread then picks its pixel's taps, at
+// the same places for every channel, and writes runs of pixels.  What bounds it is memory: the matrix is
+// read once (rows at the tiles' edges up to three times, from the caches).  Fetched from memory tap by
+// tap, lanes kh * kw elements apart, every load spread over 18 lines and a pixel's chain of loads and
+// index divisions was all a wave had in flight.  At batch 128, us a call, then and now (4.9 TB/s: the floor):
+// 64 x 32 x 32, stride 2, window 3 69 / 27 (22), window 1 37 / 8.6 (8.6); 128 x 16 x 16, stride 2, window 3
+// 36 / 13.4 (11); 512 x 4 x 4, stride 1, window 3 19 / 9.3 (8.6).
+// At most NY x NX taps meet in a pixel; they are added from the window's end to its start, i.e. in the order
+// of the matrix rows, a zero for those outside the matrix.
+struct FoldTile {
+    int TY, log2p;          // pixel rows of a tile; lanes are dealt 2^log2p pixels
+    int CB, pitch;          // channels, floats per matrix row in LDS
+    int rows_x;             // matrix rows side by side that the tile's pixels meet
+    Divisor TX, stride, across, down, blocks;      // (across, down: tiles of an image; blocks of channels)
+    Divisor units, row_x;   // loads per matrix row; rows_x
+};
+constexpr int kFoldLds = 32 * 1024;
+constexpr int64_t kFoldTiles = (int64_t)1 << 22;      // (a grid holds 2^32 threads)
+
+__device__ __forceinline__ int last_tap(int r, int k, const Divisor& stride)      // largest t < k, t = r modulo stride
+{
+    const uint32_t over = (uint32_t)(k - 1 - r) + stride.d;
+    return k - 1 - (int)(over - divide(over, stride) * stride.d);
+}
+
+template <int NY, int NX, bool WIDE>
+__global__ __launch_bounds__(kThreads) void col2im_tile_kernel(Im2colArgs a, FoldTile t)
+{
+    extern __shared__ __attribute__((aligned(16))) float part[];
+    const int tid = threadIdx.x;
+    const int khw = a.kh * a.kw, K = a.C * khw, HW = a.H * a.W;
+    const uint32_t i1 = divide(blockIdx.x, t.blocks), i2 = divide(i1, t.across), b = divide(i2, t.down);
+    const int c0 = (int)(blockIdx.x - i1 * t.blocks.d) * t.CB, x0 = (int)((i1 - i2 * t.across.d) * t.TX.d);
+    const int y0 = (int)(i2 - b * t.down.d) * t.TY;
+    const int cn = a.C - c0 < t.CB ? a.C - c0 : t.CB, TX = (int)t.TX.d, s = (int)t.stride.d;
+    const int y_end = a.H - y0 < t.TY ? a.H : y0 + t.TY, x_end = a.W - x0 < TX ? a.W : x0 + TX;
+
+    // the matrix rows that meet the tile
+    const int yb = y0 + a.ph - a.kh, xb = x0 + a.pw - a.kw;
+    const int yo_lo = yb < 0 ? 0 : (int)divide((uint32_t)yb, t.stride) + 1, xo_lo = xb < 0 ? 0 : (int)divide((uint32_t)xb, t.stride) + 1;
+    const int yo_in = (int)divide((uint32_t)(y_end - 1 + a.ph), t.stride), xo_in = (int)divide((uint32_t)(x_end - 1 + a.pw), t.stride);
+    const int yo_hi = yo_in < a.Ho ? yo_in : a.Ho - 1, xo_hi = xo_in < a.Wo ? xo_in : a.Wo - 1;
+    {
+        constexpr int PER = WIDE ? 4 : 1, UNROLL = WIDE ? 4 : 8;
+        const int have = cn * khw / PER;                  // (wide: K and c0 * khw are multiples of 4)
+        const int total = (yo_hi - yo_lo + 1) * t.rows_x * (int)t.units.d;      // (<= 0: no row meets it)
+        const float* src = a.X + (((int64_t)b * a.Ho + yo_lo) * a.Wo + xo_lo) * K + (int64_t)c0 * khw;
+        for (int i0 = tid; i0 < total; i0 += kThreads * UNROLL) {
+            float4 v[UNROLL];
+            int at[UNROLL];
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) {
+                const uint32_t i = (uint32_t)(i0 + u * kThreads), row = divide(i, t.units), ry = divide(row, t.row_x);
+                const int unit = (int)(i - row * t.units.d), rx = (int)(row - ry * t.row_x.d);
+                const bool in = (int)i < total && unit < have && xo_lo + rx <= xo_hi;
+                at[u] = in ? (int)row * t.pitch + unit * PER : -1;
+                const float* from = src + ((int64_t)(int)ry * a.Wo + rx) * K + unit * PER;
+                if constexpr (WIDE) v[u] = in ? *reinterpret_cast<const float4*>(from) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                else v[u].x = in ? *from : 0.0f;
+            }
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) {
+                if (at[u] < 0) continue;
+                if constexpr (WIDE) *reinterpret_cast<float4*>(part + at[u]) = v[u];
+                else part[at[u]] = v[u].x;
+            }
+        }
+    }
+    __syncthreads();
+
+    const int p = tid & ((1 << t.log2p) - 1), py = (int)divide((uint32_t)p, t.TX);
+    const int y = y0 + py, x = x0 + p - py * TX;
+    if (y >= y_end) return;       // (x < x_end or another tile's column)
+    if (x >= x_end) return;
+    const int qy = (int)divide((uint32_t)(y + a.ph), t.stride), qx = (int)divide((uint32_t)(x + a.pw), t.stride);
+    const int ry = y + a.ph - qy * s, rx = x + a.pw - qx * s;
+    const int ty0 = last_tap(ry, a.kh, t.stride), tx0 = last_tap(rx, a.kw, t.stride);
+    // (a multiple of the stride, minus one stride where the pixel lies between the windows)
+    const int yo0 = qy - ((int)divide((uint32_t)(ty0 - ry + s), t.stride) - 1), xo0 = qx - ((int)divide((uint32_t)(tx0 - rx + s), t.stride) - 1);
+    int at[NY * NX];
+    bool ok[NY * NX];
+#pragma unroll
+    for (int u = 0; u < NY * NX; ++u) {
+        const int j = u / NX, i = u % NX;
+        const int ty = ty0 - j * s, tx = tx0 - i * s, yo = yo0 + j, xo = xo0 + i;
+        ok[u] = ty >= 0 && tx >= 0 && yo >= 0 && yo < a.Ho && xo >= 0 && xo < a.Wo;
+        at[u] = ok[u] ? ((yo - yo_lo) * t.rows_x + (xo - xo_lo)) * t.pitch + ty * a.kw + tx : 0;
+    }
+    const int side = kThreads >> t.log2p;
+    float* out = a.out + ((int64_t)b * a.C + c0) * HW + (int64_t)y * a.W + x;
+#pragma unroll 4
+    for (int ch = tid >> t.log2p; ch < cn; ch += side) {
+        float sum = 0.0f;
+#pragma unroll
+        for (int u = 0; u < NY * NX; ++u) {
+            const float v = part[at[u] + ch * khw];
+            sum += ok[u] ? v : 0.0f;
+        }
+        out[(int64_t)ch * HW] = sum;
+    }
+}
+
+// ---- folding for every geometry (windows of more than three strides; such strides and windows that a
+// tile's matrix rows do not fit LDS): a workgroup has 32 pixels of the activation (of the batch's pixels in
+// a row) and 64 channels.  Lanes are channels, so that the kh * kw elements a lane adds up for a pixel lie
+// in the lines its neighbours read too, and which taps there are is the same for the whole wave; the sums
+// turn through LDS and leave as runs of pixels.  The loads of three taps along a row of the window go out
+// at a time.
+constexpr int kFoldPixels = 32, kFoldChannels = 64, kFoldTaps = 3;
 
 __device__ __forceinline__ int last_tap(int at, int k, int stride)      // largest t < k, t = at modulo stride
 {
     return k - 1 - (k - 1 + stride - at % stride) % stride;
 }
 
-template <int NY, int NX>
 __global__ __launch_bounds__(kThreads) void col2im_kernel(Im2colArgs a)
 {
     __shared__ float turn[kFoldChannels][kFoldPixels + 1];
@@ -98,12 +197,12 @@ __global__ __launch_bounds__(kThreads) void col2im_kernel(Im2colArgs a)
             // the last tap whose matrix row or column is a whole number of strides away, and every
             // stride-th before it
             const int ty_last = last_tap(y + a.ph, a.kh, a.stride), tx_last = last_tap(x + a.pw, a.kw, a.stride);
-            for (int ty0 = ty_last; ty0 >= 0; ty0 -= NY * a.stride)
-                for (int tx0 = tx_last; tx0 >= 0; tx0 -= NX * a.stride) {
-                    float v[NY * NX];
+            for (int ty0 = ty_last; ty0 >= 0; ty0 -= a.stride)
+                for (int tx0 = tx_last; tx0 >= 0; tx0 -= kFoldTaps * a.stride) {
+                    float v[kFoldTaps];
 #pragma unroll
-                    for (int u = 0; u < NY * NX; ++u) {
-                        const int ty = ty0 - u / NX * a.stride, tx = tx0 - u % NX * a.stride;
+                    for (int u = 0; u < kFoldTaps; ++u) {
+                        const int ty = ty0, tx = tx0 - u * a.stride;
                         const int yo = (y + a.ph - ty) / a.stride, xo = (x + a.pw - tx) / a.stride;
                         const bool ok = ty >= 0 && tx >= 0 && y + a.ph >= ty && x + a.pw >= tx && yo < a.Ho && xo < a.Wo;
                         const float* row = a.X + (ok ? ((b * a.Ho + yo) * a.Wo + xo) * (int64_t)K + ty * a.kw + tx : 0);
@@ -111,7 +210,7 @@ __global__ __launch_bounds__(kThreads) void col2im_kernel(Im2colArgs a)
                         if (!ok) v[u] = 0.0f;
                     }
 #pragma unroll
-                    for (int u = 0; u < NY * NX; ++u) sum += v[u];
+                    for (int u = 0; u < kFoldTaps; ++u) sum += v[u];
                 }
             turn[lane][wave * (kFoldPixels / 4) + i] = sum;
             if (++x == a.W) {
@@ -174,17 +273,76 @@ hipError_t launch_im2col(const Im2colArgs& a, hipStream_t stream)
     return hipGetLastError();
 }
 
+namespace {
+
+// How the tiles are cut; false where a tile of one pixel row and four channels does not fit.
+// Tiles of whole image rows where they are short, up to 128 pixels (64 or 256: 32.6 and 26.7 us for 128 x 64 x
+// 32 x 32, window 3, stride 2, which takes 26.7; its 1 x 1 neighbour 9.8 and 11.8 against 8.6); the channels
+// that fit 32 KB then (48 KB: 13.4 -> 13.7 and 9.3 -> 10.4 us at 16 x 16 and 4 x 4 images), but runs of a line
+// at least (of 512 bytes: tiles of two rows for 96 x 14 x 14, window 3, 46 us instead of 26).
+bool plan_fold_tile(const Im2colArgs& a, FoldTile* t, unsigned* grid, size_t* lds)
+{
+    const int64_t khw = (int64_t)a.kh * a.kw, most_rows = kFoldLds / 4;
+    const int64_t across = ((int64_t)a.W + 63) / 64, TX = ((int64_t)a.W + across - 1) / across;
+    int64_t TY = 1;
+    while (2 * TY * TX <= 128 && TY < a.H) TY *= 2;
+    const auto rows = [&](int64_t pixels, int k, int out) {
+        const int64_t r = (pixels + k - 2) / a.stride + 1;
+        return r < out ? r : (int64_t)out;
+    };
+    for (; TY >= 1; TY /= 2) {
+        const int64_t ny = rows(TY, a.kh, a.Ho), nx = rows(TX, a.kw, a.Wo);
+        if (ny > most_rows || nx > most_rows || ny * nx > most_rows || khw > most_rows) continue;
+        for (int64_t most = 64; most >= 4; most /= 2) {
+            const int64_t CB = most < a.C ? most : a.C;
+            int64_t pitch = (CB * khw + 3) / 4 * 4;
+            if (pitch % 8 == 0) pitch += 4;      // (an odd number of 16-byte units: a column's rows in different banks)
+            if (ny * nx * pitch * 4 > kFoldLds) continue;
+            if (CB < a.C && CB * khw * 4 < 128 && TY > 1) break;
+            const int64_t blocks = (a.C + CB - 1) / CB, down = (a.H + TY - 1) / TY, batch = a.M / ((int64_t)a.H * a.W);
+            const bool wide = a.C * khw % 4 == 0;
+            if (across * down > kFoldTiles || across * down * blocks > kFoldTiles / batch) return false;
+            int log2p = 0;
+            while ((1 << log2p) < TX * TY) ++log2p;
+            *t = {(int)TY, log2p, (int)CB, (int)pitch, (int)nx, make_divisor((uint32_t)TX), make_divisor((uint32_t)a.stride),
+                  make_divisor((uint32_t)across), make_divisor((uint32_t)down), make_divisor((uint32_t)blocks),
+                  make_divisor((uint32_t)(wide ? CB * khw / 4 : CB * khw)), make_divisor((uint32_t)nx)};
+            *grid = (unsigned)(across * down * blocks * batch);
+            *lds = (size_t)(ny * nx * pitch * 4);
+            return true;
+        }
+    }
+    return false;
+}
+
+template <int N>
+void launch_fold_tile(const Im2colArgs& a, const FoldTile& t, unsigned grid, size_t lds, hipStream_t stream)
+{
+    const bool wide = (int64_t)a.C * a.kh * a.kw % 4 == 0;      // (X itself is on a 16-byte boundary)
+    if (wide) hipLaunchKernelGGL((col2im_tile_kernel<N, N, true>), dim3(grid), dim3(kThreads), lds, stream, a, t);
+    else hipLaunchKernelGGL((col2im_tile_kernel<N, N, false>), dim3(grid), dim3(kThreads), lds, stream, a, t);
+}
+
+} // namespace
+
 hipError_t launch_col2im(const Im2colArgs& a, hipStream_t stream)
 {
+    ProfileScope ps(K_COL2IM, stream);
+    // (strides up to 2^31 - 1: no sum)
+    const int ny = (a.kh - 1) / a.stride + 1, nx = (a.kw - 1) / a.stride + 1, n = ny > nx ? ny : nx;
+    FoldTile t;
+    unsigned tiles;
+    size_t lds;
+    if (n <= 3 && plan_fold_tile(a, &t, &tiles, &lds)) {
+        if (n == 1) launch_fold_tile<1>(a, t, tiles, lds, stream);
+        else if (n == 2) launch_fold_tile<2>(a, t, tiles, lds, stream);
+        else launch_fold_tile<3>(a, t, tiles, lds, stream);
+        return hipGetLastError();
+    }
     const int64_t runs = (a.M + kFoldPixels - 1) / kFoldPixels;
     const unsigned across = (unsigned)((a.C + kFoldChannels - 1) / kFoldChannels);
     const dim3 grid((unsigned)(runs < (1 << 23) ? runs : (1 << 23)), across);
-    ProfileScope ps(K_COL2IM, stream);
-    const int ny = (a.kh + a.stride - 1) / a.stride, nx = (a.kw + a.stride - 1) / a.stride, n = ny > nx ? ny : nx;
-    if (n == 1) hipLaunchKernelGGL((col2im_kernel<1, 1>), grid, dim3(kThreads), 0, stream, a);
-    else if (n == 2) hipLaunchKernelGGL((col2im_kernel<2, 2>), grid, dim3(kThreads), 0, stream, a);
-    else if (n == 3) hipLaunchKernelGGL((col2im_kernel<3, 3>), grid, dim3(kThreads), 0, stream, a);
-    else hipLaunchKernelGGL((col2im_kernel<1, 3>), grid, dim3(kThreads), 0, stream, a);
+    hipLaunchKernelGGL(col2im_kernel, grid, dim3(kThreads), 0, stream, a);
     return hipGetLastError();
 }
 

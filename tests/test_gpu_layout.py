@@ -25,6 +25,27 @@ def test_unfold_and_fold(b, c, h, w, k, stride, pad):
     assert torch.equal(B.col2im(dX, (b, c, h, w), k, k, stride, pad, pad), want)
 
 
+@pytest.mark.parametrize("b,c,h,w,kh,kw,stride,ph,pw", [
+    (2, 17, 9, 65, 3, 3, 1, 1, 1),        # rows of 17 * 9 elements: single ones; two tiles across, the second shorter
+    (2, 68, 13, 40, 3, 3, 2, 1, 1),       # a block of 4 channels behind those of 16; rows of windows that end inside a tile
+    (3, 20, 33, 7, 2, 2, 3, 0, 0),        # pixels between the windows
+    (3, 130, 14, 14, 1, 1, 2, 0, 0), (1, 6, 200, 5, 7, 7, 3, 3, 3), (2, 12, 1, 130, 1, 3, 1, 0, 1),
+    (2, 12, 6, 130, 1, 5, 1, 0, 2),       # more taps in a row than a tile's pixel holds
+    (1, 2, 120, 110, 100, 100, 40, 5, 0), # windows that do not fit LDS
+    (1, 1, 300, 260, 9, 9, 4, 4, 4), (40, 513, 2, 2, 3, 3, 1, 1, 1)])
+def test_unfold_and_fold_tiles(b, c, h, w, kh, kw, stride, ph, pw):
+    """Edges of the tiles: images, channels and windows that end inside one, do not fill one, or have none."""
+    print(f"layout: tiles of act [{b},{c},{h},{w}] window {kh}x{kw} stride {stride} pad {ph},{pw}", flush=True)
+    g = torch.Generator().manual_seed(b * 1000 + c)
+    act = torch.randn(b, c, h, w, generator=g).cuda()
+    cols = torch.nn.functional.unfold(act, kernel_size=(kh, kw), padding=(ph, pw), stride=stride)
+    assert torch.equal(B.im2col(act, kh, kw, stride, ph, pw), cols.transpose(1, 2).reshape(-1, c * kh * kw))
+    dX = torch.randn(b * cols.shape[2], c * kh * kw, generator=g).cuda()
+    want = torch.nn.functional.fold(dX.reshape(b, -1, c * kh * kw).transpose(1, 2).contiguous(), output_size=(h, w),
+                                    kernel_size=(kh, kw), padding=(ph, pw), stride=stride)
+    assert torch.equal(B.col2im(dX, (b, c, h, w), kh, kw, stride, ph, pw), want)
+
+
 @pytest.mark.parametrize("b,r,c", [(1, 1, 1), (3, 64, 64), (2, 65, 63), (5, 16, 512), (2, 1, 130), (4, 1024, 64)])
 def test_transpose(b, r, c):
     x = torch.randn(b, r, c, generator=torch.Generator().manual_seed(r)).cuda()
