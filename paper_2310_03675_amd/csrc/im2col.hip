@@ -8,14 +8,88 @@
 //   images (channel planes).
 #include "common.hpp"
 
+#include <limits.h>
+
 namespace hdqt {
 
 namespace {
 
 constexpr int kThreads = 256;
 
-// ---- unfolding: a thread has one column of X (its channel and tap are worked out once) and kRows
-// rows of it, kUnroll loads in flight.  (A row at a time, with the divisions of every element in front
+// ---- unfolding through LDS: a workgroup has TX x TY windows of one image (a tile of the matrix rows) and CB
+// channels.  It fetches the part of the activation under them as runs of a row's pixels and writes CB * kh *
+// kw neighbours in each matrix row, 16 bytes a lane; where a column's element lies in LDS stands in a
+// table.  What bounds it is writing X.  Of windows that leave pixels out (1 x 1 with stride 2) only those
+// under a window are fetched.  At batch 128, us a call, with a thread's column at a time and now (4.9 TB/s:
+// the floor): 64 x 32 x 32, stride 2, window 3 42 / 26 (22), window 1 11.4 / 8.7 (8.6); 256 x 8 x 8, stride 2,
+// window 1 9.2 / 4.3 (2.1); 96 x 14 x 14, stride 1, window 3 31 / 21 (20).
+struct UnfoldTile {
+    int TY, CB;             // windows on top of each other; channels
+    int sy, sx;             // from a window to the next in LDS: the stride, or the window where that is less
+    int plane;              // floats per channel in LDS
+    Divisor TX, across, down, blocks;              // (tiles of an image; blocks of channels)
+    Divisor width, height, step_y, step_x;         // of a plane; sy, sx
+    Divisor taps, kw, units;                       // kh * kw; stores per matrix row
+};
+constexpr int kTileLds = 32 * 1024;
+constexpr int64_t kTiles = (int64_t)1 << 22;       // (a grid holds 2^32 threads)
+
+__global__ __launch_bounds__(kThreads) void im2col_tile_kernel(Im2colArgs a, UnfoldTile t)
+{
+    extern __shared__ __attribute__((aligned(16))) float part[];
+    const int tid = threadIdx.x;
+    const int khw = (int)t.taps.d, K = a.C * khw;
+    const uint32_t i1 = divide(blockIdx.x, t.blocks), i2 = divide(i1, t.across), b = divide(i2, t.down);
+    const int c0 = (int)(blockIdx.x - i1 * t.blocks.d) * t.CB, xo0 = (int)((i1 - i2 * t.across.d) * t.TX.d);
+    const int yo0 = (int)(i2 - b * t.down.d) * t.TY;
+    const int cn = a.C - c0 < t.CB ? a.C - c0 : t.CB, TY = a.Ho - yo0 < t.TY ? a.Ho - yo0 : t.TY;
+    int* column = reinterpret_cast<int*>(part);
+    float* patch = part + (t.CB * khw + 3 & ~3);
+    for (int q = tid; q < cn * khw; q += kThreads) {
+        const uint32_t c = divide((uint32_t)q, t.taps), tap = (uint32_t)q - c * t.taps.d, ty = divide(tap, t.kw);
+        column[q] = (int)(c * t.plane + ty * t.width.d + tap - ty * t.kw.d);
+    }
+    {
+        constexpr int UNROLL = 8;
+        const int total = cn * t.plane, yb = yo0 * a.stride - a.ph, xb = xo0 * a.stride - a.pw;
+        const float* src = a.act + ((int64_t)b * a.C + c0) * a.H * a.W;
+        for (int i0 = tid; i0 < total; i0 += kThreads * UNROLL) {
+            float v[UNROLL];
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u) {
+                const uint32_t i = (uint32_t)(i0 + u * kThreads), line = divide(i, t.width), j = i - line * t.width.d;
+                const uint32_t c = divide(line, t.height), r = line - c * t.height.d;
+                const int y = yb + (int)r + (int)divide(r, t.step_y) * (a.stride - t.sy);
+                const int x = xb + (int)j + (int)divide(j, t.step_x) * (a.stride - t.sx);
+                const bool in = (int)i < total && y >= 0 && y < a.H && x >= 0 && x < a.W;
+                // (an image's offsets fit 32 bits)
+                v[u] = in ? src[((int)c * a.H + y) * a.W + x] : 0.0f;
+            }
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u)
+                if (i0 + u * kThreads < total) patch[i0 + u * kThreads] = v[u];
+        }
+    }
+    __syncthreads();
+
+    const int have = cn * khw / 4;                     // (K and c0 * khw are multiples of 4)
+    const int total = TY * (int)(t.TX.d * t.units.d);
+    float* dst = a.X + (((int64_t)b * a.Ho + yo0) * a.Wo + xo0) * K + (int64_t)c0 * khw;
+#pragma unroll 4
+    for (int i = tid; i < total; i += kThreads) {
+        const uint32_t row = divide((uint32_t)i, t.units), ry = divide(row, t.TX);
+        const int unit = i - (int)(row * t.units.d), rx = (int)(row - ry * t.TX.d);
+        if (unit >= have || xo0 + rx >= a.Wo) continue;
+        const float* from = patch + (int)ry * t.sy * (int)t.width.d + rx * t.sx;
+        float* to = dst + ((int64_t)(int)ry * a.Wo + rx) * K + unit * 4;
+        const int4 at = *reinterpret_cast<const int4*>(column + 4 * unit);
+        *reinterpret_cast<float4*>(to) = make_float4(from[at.x], from[at.y], from[at.z], from[at.w]);
+    }
+}
+
+// ---- unfolding for every geometry (rows of X that are no whole 16-byte units, where a tile's stores would be
+// single elements: 16 x 3 x 224 x 224, window 7, stride 2 50 us against 43; windows whose part of the activation
+// does not fit LDS): a thread has one column of X (its channel and tap are worked out once) and kRows rows of it, kUnroll loads in flight.  (A row at a time, with the divisions of every element in front
 // of a single load: 330 us for the ten such layers of a ResNet-18 at batch 128, 270 MB of
 // matrices; now 170.)
 constexpr int kRows = 32;          // per thread
@@ -79,8 +153,6 @@ struct FoldTile {
     Divisor TX, stride, across, down, blocks;      // (across, down: tiles of an image; blocks of channels)
     Divisor units, row_x;   // loads per matrix row; rows_x
 };
-constexpr int kFoldLds = 32 * 1024;
-constexpr int64_t kFoldTiles = (int64_t)1 << 22;      // (a grid holds 2^32 threads)
 
 __device__ __forceinline__ int last_tap(int r, int k, const Divisor& stride)      // largest t < k, t = r modulo stride
 {
@@ -259,15 +331,58 @@ __global__ __launch_bounds__(kThreads) void transpose_kernel(const float* src, f
 
 } // namespace
 
+namespace {
+
+// How the tiles are cut; false where a tile of one row of windows and four channels does not fit.
+// Tiles of whole matrix rows of an image where they are short, up to 128 of them and 64 KB of X (16 KB: 26 -> 31
+// us for 64 x 32 x 32, window 3, stride 2); the channels that fit 32 KB then, but runs of at least 256 bytes.
+bool plan_unfold_tile(const Im2colArgs& a, UnfoldTile* t, unsigned* grid, size_t* lds)
+{
+    const int64_t khw = (int64_t)a.kh * a.kw, most_floats = kTileLds / 4;
+    const int64_t across = ((int64_t)a.Wo + 63) / 64, TX = ((int64_t)a.Wo + across - 1) / across;
+    int64_t TY = 1;
+    while (2 * TY * TX <= 128 && 2 * TY * TX * khw * (a.C < 16 ? a.C : 16) <= 16384 && TY < a.Ho) TY *= 2;
+    // (coordinates of a tile's last window, also one behind the image, fit 32 bits)
+    if (((int64_t)a.Ho + TY) * a.stride + a.kh >= INT_MAX || ((int64_t)a.Wo + TX) * a.stride + a.kw >= INT_MAX) return false;
+    const int64_t sy = a.stride < a.kh ? a.stride : a.kh, sx = a.stride < a.kw ? a.stride : a.kw;
+    for (; TY >= 1; TY /= 2) {
+        const int64_t height = (TY - 1) * sy + a.kh, width = (TX - 1) * sx + a.kw;
+        for (int64_t most = 64; most >= 4; most /= 2) {
+            const int64_t CB = most < a.C ? most : a.C, seg = (CB * khw + 3) / 4 * 4, floats = seg + CB * height * width;
+            if (floats > most_floats) continue;
+            if (CB < a.C && CB * khw * 4 < 256 && TY > 1) break;
+            const int64_t blocks = (a.C + CB - 1) / CB, down = (a.Ho + TY - 1) / TY, batch = a.M / ((int64_t)a.Ho * a.Wo);
+            if (across * down > kTiles || across * down * blocks > kTiles / batch) return false;
+            const auto div = [](int64_t d) { return make_divisor((uint32_t)d); };
+            *t = {(int)TY, (int)CB, (int)sy, (int)sx, (int)(height * width), div(TX), div(across), div(down), div(blocks),
+                  div(width), div(height), div(sy), div(sx), div(khw), div(a.kw), div(CB * khw / 4)};
+            *grid = (unsigned)(across * down * blocks * batch);
+            *lds = (size_t)floats * 4;
+            return true;
+        }
+    }
+    return false;
+}
+
+} // namespace
+
 hipError_t launch_im2col(const Im2colArgs& a, hipStream_t stream)
 {
+    ProfileScope ps(K_IM2COL, stream);
     const int64_t K = (int64_t)a.C * a.kh * a.kw;
+    UnfoldTile t;
+    unsigned tiles;
+    size_t lds;
+    // (X itself is on a 16-byte boundary)
+    if (K % 4 == 0 && plan_unfold_tile(a, &t, &tiles, &lds)) {
+        hipLaunchKernelGGL(im2col_tile_kernel, dim3(tiles), dim3(kThreads), lds, stream, a, t);
+        return hipGetLastError();
+    }
     int log2w = 5;
     while (log2w < 8 && (1 << log2w) < K) ++log2w;
     const int width = 1 << log2w;
     const int64_t tall = (int64_t)(kThreads / width) * kRows;
     const int64_t n_col = (K + width - 1) / width, runs = (a.M + tall - 1) / tall;
-    ProfileScope ps(K_IM2COL, stream);
     hipLaunchKernelGGL(im2col_kernel, dim3((unsigned)(n_col * runs)), dim3(kThreads), 0, stream, a, width, log2w,
                        (uint32_t)n_col);
     return hipGetLastError();
@@ -282,7 +397,7 @@ namespace {
 // at least (of 512 bytes: tiles of two rows for 96 x 14 x 14, window 3, 46 us instead of 26).
 bool plan_fold_tile(const Im2colArgs& a, FoldTile* t, unsigned* grid, size_t* lds)
 {
-    const int64_t khw = (int64_t)a.kh * a.kw, most_rows = kFoldLds / 4;
+    const int64_t khw = (int64_t)a.kh * a.kw, most_rows = kTileLds / 4;
     const int64_t across = ((int64_t)a.W + 63) / 64, TX = ((int64_t)a.W + across - 1) / across;
     int64_t TY = 1;
     while (2 * TY * TX <= 128 && TY < a.H) TY *= 2;
@@ -297,11 +412,11 @@ bool plan_fold_tile(const Im2colArgs& a, FoldTile* t, unsigned* grid, size_t* ld
             const int64_t CB = most < a.C ? most : a.C;
             int64_t pitch = (CB * khw + 3) / 4 * 4;
             if (pitch % 8 == 0) pitch += 4;      // (an odd number of 16-byte units: a column's rows in different banks)
-            if (ny * nx * pitch * 4 > kFoldLds) continue;
+            if (ny * nx * pitch * 4 > kTileLds) continue;
             if (CB < a.C && CB * khw * 4 < 128 && TY > 1) break;
             const int64_t blocks = (a.C + CB - 1) / CB, down = (a.H + TY - 1) / TY, batch = a.M / ((int64_t)a.H * a.W);
             const bool wide = a.C * khw % 4 == 0;
-            if (across * down > kFoldTiles || across * down * blocks > kFoldTiles / batch) return false;
+            if (across * down > kTiles || across * down * blocks > kTiles / batch) return false;
             int log2p = 0;
             while ((1 << log2p) < TX * TY) ++log2p;
             *t = {(int)TY, log2p, (int)CB, (int)pitch, (int)nx, make_divisor((uint32_t)TX), make_divisor((uint32_t)a.stride),
