@@ -118,19 +118,25 @@ class HdqtReluMatmul(torch.autograd.Function):
         return dPre, dW, None, None
 
 
+def _innermost(act: torch.Tensor) -> bool:
+    """Whether act [B, C, H, W] has its channels innermost and is of a size that the library's
+    transposition is for."""
+    if act.is_contiguous() or not act.is_cuda or act.dtype != torch.float32 or act.numel() < 1 << 21:
+        return False
+    Bn, Cin, H, W = act.shape
+    # (the library transposes at most 65535 matrices of 4194240 rows or columns)
+    return Bn <= 65535 and max(H * W, Cin) <= 65535 * 64 and act.permute(0, 2, 3, 1).is_contiguous()
+
+
 def _planes(act: torch.Tensor) -> torch.Tensor:
     """act [B, C, H, W] contiguous.  What comes out of a layer and the normalisation behind it has its
     channels innermost; the library's transposition turns that faster than a strided copy (40 -> 11 us
     for 128 x 64 x 32 x 32, 10.2 -> 9.4 for 128 x 256 x 8 x 8).  Below 2 M elements a call is host time,
     of which the copy has less (128 x 512 x 4 x 4 6.3 / 9.2)."""
-    if act.is_contiguous() or not act.is_cuda or act.dtype != torch.float32 or act.numel() < 1 << 21:
+    if not _innermost(act) or act.data_ptr() % 16:
         return act.contiguous()
     Bn, Cin, H, W = act.shape
-    last = act.permute(0, 2, 3, 1)
-    # (the library transposes at most 65535 matrices of 4194240 rows or columns)
-    if Bn > 65535 or max(H * W, Cin) > 65535 * 64 or not last.is_contiguous() or act.data_ptr() % 16:
-        return act.contiguous()
-    return B.transpose(last.reshape(Bn, H * W, Cin)).reshape(Bn, Cin, H, W)
+    return B.transpose(act.permute(0, 2, 3, 1).reshape(Bn, H * W, Cin)).reshape(Bn, Cin, H, W)
 
 
 def _opaque_call_will_do(t: torch.Tensor) -> bool:
@@ -159,6 +165,17 @@ def _fold(dX: torch.Tensor, shape, kh: int, kw: int, stride: int, ph: int, pw: i
                                     kernel_size=(kh, kw), padding=(ph, pw), stride=stride)
 
 
+def _as_activation(dAct: torch.Tensor, innermost: bool) -> torch.Tensor:
+    """The gradient of an activation in the activation's layout.  The kernels write channel planes; behind a
+    normalisation everything else has its channels innermost, and PyTorch's elementwise kernels take
+    three times as long over two layouts as over one (the rectifier's backward pass at 128 x 64 x 32 x 32
+    55 against 16 us, the transposition 12; at 128 x 256 x 8 x 8 17, 5 and 7)."""
+    if not innermost or dAct.data_ptr() % 16 or not dAct.is_contiguous():
+        return dAct
+    Bn, Cin, H, W = dAct.shape
+    return B.transpose(dAct.reshape(Bn, Cin, H * W)).reshape(Bn, H, W, Cin).permute(0, 3, 1, 2)
+
+
 _FOLD_REFUSED = set()        # products hdqt_conv_bwd did not take, by everything that this depends on
 
 
@@ -171,6 +188,7 @@ class HdqtConvMatmul(torch.autograd.Function):
     @staticmethod
     def forward(ctx, act, W, cfg: LayerConfig, step: int, kh: int, kw: int):
         ctx.want_dx = cfg.need_input_grad and act.requires_grad
+        ctx.innermost = _innermost(act)
         act, W = _planes(act), W.contiguous()
         pf = cfg.params(B.GEMM_FWD, step)
         pw = cfg.params(B.GEMM_BWD_WEIGHT, step)
@@ -205,6 +223,8 @@ class HdqtConvMatmul(torch.autograd.Function):
             dXcol, dW = B.layer_bwd(G, W, saved, Cin * kh * kw, pi, pw)
             if dXcol is not None:
                 dAct = _fold(dXcol, ctx.shape, kh, kw, 1, (kh - 1) // 2, (kw - 1) // 2)
+        if dAct is not None:
+            dAct = _as_activation(dAct, ctx.innermost)
         if cfg.capture is not None:
             cfg.capture.update(G=G.detach(), dX=dXcol, dAct=dAct, dW=dW)
         return dAct, dW, None, None, None, None
@@ -217,13 +237,16 @@ class Unfold(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, act, k: int, stride: int, pad: int):
-        ctx.geo = (tuple(act.shape), k, stride, pad)
+        ctx.geo, ctx.innermost = (tuple(act.shape), k, stride, pad), _innermost(act)
         return B.im2col(_planes(act), k, k, stride, pad, pad)
 
     @staticmethod
     def backward(ctx, dX):
         shape, k, stride, pad = ctx.geo
-        return _fold(dX, shape, k, k, stride, pad, pad), None, None, None
+        dAct = _fold(dX, shape, k, k, stride, pad, pad)
+        if ctx.innermost and _opaque_call_will_do(dAct):
+            dAct = _as_activation(dAct, True)
+        return dAct, None, None, None
 
 
 class HdqtLinear(torch.nn.Module):

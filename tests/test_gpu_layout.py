@@ -107,3 +107,31 @@ def test_unfold_of_any_layout(shape, stride, layout):
     X.backward(torch.ones_like(X))
     fold = torch.nn.functional.fold(torch.ones_like(want), output_size=(h, w), kernel_size=k, padding=pad, stride=stride)
     assert torch.equal(x.grad, fold)
+
+
+@pytest.mark.parametrize("shape,k,stride", [((32, 64, 32, 32), 3, 1), ((33, 64, 32, 32), 3, 2), ((40, 52, 32, 32), 1, 2),
+                                            ((8, 64, 32, 32), 3, 1)])       # the last: too small to be turned
+def test_gradient_in_the_layout_of_its_activation(shape, k, stride):
+    """Channels innermost or planes: the same gradients, each in its activation's layout."""
+    print(f"layout: gradient of act {shape} window {k} stride {stride}", flush=True)
+    b, c, h, w = shape
+    act = torch.randn(shape, generator=torch.Generator().manual_seed(c)).cuda()
+    grads = []
+    for innermost in (False, True):
+        layer = A.HdqtConv2d(c, 32, kernel_size=k, padding=k // 2, stride=stride, cfg=A.LayerConfig(), device="cuda")
+        with torch.no_grad():
+            layer.weight.copy_(torch.randn(layer.weight.shape, generator=torch.Generator().manual_seed(1)))
+        leaf = act.clone().requires_grad_()
+        x = leaf * 1.0
+        if innermost:
+            x = x.permute(0, 2, 3, 1).contiguous().permute(0, 3, 1, 2)
+        x.retain_grad()
+        seen = []
+        x.register_hook(lambda grad: seen.append(grad.stride()))
+        z = layer(x)
+        z.backward(torch.randn(z.shape, generator=torch.Generator().manual_seed(2)).cuda())
+        turned = innermost and act.numel() >= 1 << 21
+        assert seen[0] == (x.stride() if turned else act.stride())
+        grads.append((leaf.grad, layer.weight.grad))
+    for p, q in zip(*grads):
+        assert torch.equal(p, q)
