@@ -116,8 +116,7 @@ __device__ __forceinline__ void swap_halves(uint32_t v, uint32_t w, uint32_t& x,
 // what its matrix cores needed for the step.
 // RAGGED: lines that do not start on a dword.  Loads of 16 bytes from such addresses cost twice, so the aligned
 // dwords are fetched and shifted into place; the dword behind a lane's four is the first of the lane that
-// has the next 16 bytes, only the last unit's upper half has to fetch it.  (2074 x 355 x 555, packed: 8.0 us
-// unaligned, 6.6 with a dword more per load, @R@.)
+// has the next 16 bytes, only the last unit's upper half has to fetch it.  (2074 x 355 x 555, packed: 7.4 us.)
 template <bool RAGGED, int N>
 __device__ __forceinline__ void load_units(const uint8_t* q, uint32_t line, uint32_t k, int half, Words4 (&out)[N])
 {
@@ -541,8 +540,8 @@ hipError_t launch_gemm_small(const GemmArgs* gs, int n, hipStream_t stream)
     if (n < 1 || n > kMaxSmallBatch) return hipErrorInvalidValue;
     SmallBatch b{};
     b.n = n;
-    int64_t total = 0, work = 0;
-    bool packed_halves = false, paired = true;
+    int64_t total = 0, work = 0, staged_blocks = 0;
+    bool packed_halves = false, paired = true, all_aligned = true;
     for (int k = 0; k < kMaxSmallBatch; ++k) b.first[k] = INT_MAX;
     for (int k = 0; k < n; ++k) {
         const GemmArgs& g = gs[k];
@@ -563,7 +562,12 @@ hipError_t launch_gemm_small(const GemmArgs* gs, int n, hipStream_t stream)
         a.steps_per_tile = (int)(g.s / kStep);
         a.ragged = g.pitchA % 4 != 0 || g.pitchB % 4 != 0;
         const int64_t blocks = ((g.RA + 31) / 32) * ((g.RB + 31) / 32), steps = (g.D + kStep - 1) / kStep;
-        if (!a.ragged) work += blocks * steps;
+        const bool aligned = g.pitchA % 64 == 0 && g.pitchB % 64 == 0;
+        if (!a.ragged && (aligned || a.mode != MODE_SAT8)) {
+            work += blocks * steps;
+            staged_blocks += blocks;
+        }
+        all_aligned &= aligned;
         packed_halves |= a.mode == MODE_HALF;
         paired &= a.mode == MODE_SAT8;
         a.n_ct = make_divisor((uint32_t)((g.RB + 31) / 32));
@@ -571,12 +575,17 @@ hipError_t launch_gemm_small(const GemmArgs* gs, int n, hipStream_t stream)
         total += (int64_t)a.n_ct.d * ((g.RA + 31) / 32);
     }
     ProfileScope ps(n > 1 ? K_GEMM_SMALL : gs[0].profile_tag ? K_GEMM_I4_FWD + (gs[0].profile_tag - 1) : K_GEMM_I4, stream);
-    // Steps of blocks from which the launch waits for its loads' lanes rather than for one chain: 2048 x 512 x 4608
-    // beside 4608 x 512 x 2048 (294912) 42 -> 33 us, 502 x 1053 x 9472 (156288) 29.5 -> 25.3, but 1642 x 857 x 3712 (162864)
-    // 23.1 / 23.3 and 266 x 424 x 11456 (45108) 11.7 / 15.1; other modes, whose steps take longer, earlier: 576 x 1108 x 6400
-    // (126000) 25.1 -> 20.0, 759 x 1008 x 2752 in bytes and tiles of 16 (66048) 18.0 / 18.4.  Not for packed codes in tiles
-    // of 16, whose two sums a step leave no registers for it (1280 x 2304 x 192, a step, 35 / 40).
-    const bool staged = !packed_halves && work >= (paired ? 150000 : 65536);
+    // Steps of blocks from which the launch waits for its loads' lanes rather than for one chain, lanes / staged in us of 360
+    // products.  In pairs (MODE_SAT8) the steps of lines of whole 64 bytes count, where a chunk is one piece of a line: 2304 x 256
+    // x 8192 (147456) 27.4 / 22.6, 798 x 657 x 4864 (79800) 16.6 / 14.0, 434 x 1236 x 3840 (65520) 13.7 / 12.3, 5992 x 152 x 1152 (33840)
+    // 8.5 / 8.7, and never below one block per CU (575 x 445 x 9344, 252 blocks, 10.8 / 12.5); of other lines 1800 x 1920 x
+    // 1472 (157320) takes 21.6 / 23.0, 736 x 1152 x 6464 (167256) 23.6 / 24.9, 592 x 1096 x 10816 (224770) 33.5 / 31.6.  The other modes,
+    // whose steps take longer: tiles of 64 579 x 830 x 1792 (27664) 7.4 / 6.8, 7333 x 99 x 2304 (66240) 15.4 / 12.5; bytes 3251 x
+    // 83 x 3328 (31824) 14.4 / 10.8, 1262 x 1555 x 1024 (62720) 18.4 / 13.6; where a chunk lies over two pieces later: bytes
+    // 1924 x 1345 x 544 (44591) 12.5 / 13.3, 7027 x 95 x 2512 (52140) 20.7 / 17.4.  Not for packed codes in tiles of 16, whose two
+    // sums a step leave no registers for it (1280 x 2304 x 192, a step, 35 / 40).
+    const int64_t least = paired ? 64000 : all_aligned ? 24000 : 50000;
+    const bool staged = !packed_halves && work >= least && (!paired || staged_blocks >= 256);
     if (staged) hipLaunchKernelGGL(gemm_small_kernel<true>, dim3((unsigned)total), dim3(64 * kWaves), 0, stream, b);
     else hipLaunchKernelGGL(gemm_small_kernel<false>, dim3((unsigned)total), dim3(64 * kWaves), 0, stream, b);
     return hipGetLastError();

@@ -106,7 +106,9 @@ def test_every_length_of_a_waves_chain(s, a, b):
 
 
 @pytest.mark.parametrize("RA,RB,D,b,s,a", [(480, 1000, 12288, 4, 32, 8), (481, 1001, 12312, 4, 32, 8), (700, 640, 6000, 4, 64, 12),
-                                           (1300, 500, 4120, 8, 32, 16), (500, 900, 4136, 8, 16, 16), (500, 1000, 5184, 3, 96, 10)])
+                                           (1300, 500, 4120, 8, 32, 16), (500, 900, 4136, 8, 16, 16), (500, 1000, 5184, 3, 96, 10),
+                                           (600, 660, 4863, 4, 32, 8), (257, 640, 12287, 4, 32, 8), (320, 900, 2559, 4, 64, 12),
+                                           (1000, 90, 3392, 8, 32, 16), (400, 130, 3391, 8, 16, 12)])
 def test_products_through_lds(RA, RB, D, b, s, a):
     """Enough work for the chunks that go through LDS: whole chunks, what is left of one, an end inside a step."""
     check_gemm_codes(RA, RB, D, b, b, s, a, extreme=0.1)
