@@ -14,6 +14,7 @@
 // Up to three products share a launch (a layer's forward product and both gradients).
 
 #include "common.hpp"
+#include "ragged.hpp"
 
 #include <limits.h>
 #include <type_traits>
@@ -116,29 +117,29 @@ __device__ __forceinline__ void swap_halves(uint32_t v, uint32_t w, uint32_t& x,
 // what its matrix cores needed for the step.
 // RAGGED: lines that do not start on a dword.  Loads of 16 bytes from such addresses cost twice, so the aligned
 // dwords are fetched and shifted into place; the dword behind a lane's four is the first of the lane that
-// has the next 16 bytes, only the last unit's upper half has to fetch it.  (2074 x 355 x 555, packed: 7.4 us.)
+// has the next 16 bytes, and the last unit's upper half fetches its fourth whole from where it is.  (2074 x 355 x 555, packed: 7.4 us.)
 template <bool RAGGED, int N>
 __device__ __forceinline__ void load_units(const uint8_t* q, uint32_t line, uint32_t k, int half, Words4 (&out)[N])
 {
     const uint8_t* p = q + k;                                            // (the same in every lane)
-    const uint32_t at = (line & ~3u) + 16 * (uint32_t)half, phase = line & 3u;
+    const uint32_t at = RAGGED ? ragged_at(line, half) : line + 16 * (uint32_t)half, phase = line & 3u;
 #pragma unroll
     for (int u = 0; u < N; ++u) out[u] = *reinterpret_cast<const Words4*>(p + (at + 32 * u));
     if constexpr (RAGGED) {
-        // (the dword that holds the last byte)
-        const uint32_t behind = *reinterpret_cast<const uint32_t*>(p + ((line + 32 * N - 1) & ~3u));
+        const uint32_t last = reinterpret_cast<const Bytes4*>(p + ragged_last_at(line, 32 * N))->v;
         Words4 d[N];
 #pragma unroll
         for (int u = 0; u < N; ++u) d[u] = out[u];
 #pragma unroll
         for (int u = 0; u < N; ++u) {
             uint32_t of_upper, of_lower;
-            swap_halves(d[u].w[0], u + 1 < N ? d[u + 1 < N ? u + 1 : u].w[0] : behind, of_lower, of_upper);
+            swap_halves(d[u].w[0], d[u + 1 < N ? u + 1 : u].w[0], of_lower, of_upper);
             const uint32_t next = half ? of_lower : of_upper;
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 out[u].w[i] = __builtin_amdgcn_alignbyte(i < 3 ? d[u].w[i < 3 ? i + 1 : 3] : next, d[u].w[i], phase);
         }
+        if (half) out[N - 1].w[3] = last;
     }
 }
 
