@@ -6,20 +6,35 @@ library is missing the import of a function fails loudly: there is no CPU or
 PyTorch fallback.
 """
 import ctypes as C
+import importlib
 import os
+import warnings
 from dataclasses import dataclass, field
 from typing import Optional
 
 import torch
 
-try:
-    from . import _host          # csrc/host.cpp: the calls of the hot path, marshalled in native code
-except ImportError:
-    class _NotBuilt:             # (every call goes the long way, whose first step is load(), which raises)
-        def __getattr__(self, name):
-            return lambda *args: None
 
-    _host = _NotBuilt()
+class _LongWay:
+    """In the place of _host where that is not built: every call goes through ctypes."""
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _import_host():
+    """csrc/host.cpp, the calls of the hot path marshalled in native code.  It is built against one PyTorch and one
+    Python; the library itself needs neither, and is served without."""
+    try:
+        return importlib.import_module(__package__ + "._host")
+    except ModuleNotFoundError:
+        return _LongWay()
+    except ImportError as exc:
+        warnings.warn(f"the native part of the binding does not load, calls go through ctypes ({exc}): "
+                      "run `python -m paper_2310_03675_amd.build`", RuntimeWarning)
+        return _LongWay()
+
+
+_host = _import_host()
 
 ROUND_NEAREST, ROUND_STOCHASTIC = 0, 1
 GEMM_FWD, GEMM_BWD_INPUT, GEMM_BWD_WEIGHT = 0, 1, 2
@@ -112,8 +127,6 @@ def load() -> C.CDLL:
     if not os.path.exists(LIB_PATH):
         raise ImportError(f"{LIB_PATH} is missing: run `python -m paper_2310_03675_amd.build` "
                           "(there is no fallback path)")
-    if type(_host).__name__ == "_NotBuilt":
-        raise ImportError("the module _host is missing: run `python -m paper_2310_03675_amd.build`")
     lib = C.CDLL(LIB_PATH)
     _host.bind(LIB_PATH, torch.cuda.current_device, torch._C._cuda_getCurrentRawStream)
     vp, i64, i32, sz = C.c_void_p, C.c_int64, C.c_int, C.c_size_t

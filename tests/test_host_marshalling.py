@@ -1,11 +1,16 @@
 """The native marshalling of the binding's calls (csrc/host.cpp) against the long way through ctypes: the
 same results and the same refusals, and every call that is not of the ordinary form left to the long way."""
+import os
+import subprocess
+import sys
+
 import pytest
 import torch
 
 from paper_2310_03675_amd import binding as B
 
 NE, ST = B.ROUND_NEAREST, B.ROUND_STOCHASTIC
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 def _prm(n=64, a=8, s=32, seed=5, A=(4, NE), Bq=(4, NE)):
@@ -88,3 +93,24 @@ def test_same_as_through_ctypes(k, monkeypatch):
         assert (a is None) == (b is None)
         if a is not None:
             assert a[:2] == b[:2] and torch.equal(a[2], b[2])
+
+
+@pytest.mark.parametrize("error,warned", [("ModuleNotFoundError", False), ("ImportError", True)])
+def test_library_is_served_without_the_native_part(error, warned):
+    """A process that has libhdqt.so alone, or a module built for another PyTorch, goes through ctypes; why a
+    module that is there does not load is said."""
+    program = f"""
+import sys, warnings
+class Refuse:
+    def find_spec(self, name, path=None, target=None):
+        if name.endswith("._host"): raise {error}("undefined symbol: abc")
+sys.meta_path.insert(0, Refuse())
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    from paper_2310_03675_amd import binding as B
+assert any("undefined symbol: abc" in str(w.message) for w in seen) == {warned}
+assert B.load().hdqt_n_eff(576, 64) == 64
+assert B._host.quantize(None, 1, 64, B.Operand(), 0, None) is None
+"""
+    r = subprocess.run([sys.executable, "-c", program], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
