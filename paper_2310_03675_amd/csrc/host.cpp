@@ -359,7 +359,9 @@ PyObject* conv_bwd(PyObject* const* a)
 }
 
 // What a function may throw (a call of another form; whatever an allocation or a tensor without
-// memory of its own raises, which the other way raises again) ends here.
+// memory of its own raises, which the other way raises again) ends here.  So do the interpreter's errors that
+// only say that a member is missing or no number; any other (an interrupt or a time limit's exception out of
+// torch's functions, a property's own error) is the caller's.
 template <PyObject* (*F)(PyObject* const*), Py_ssize_t ARGS>
 PyObject* entry(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
@@ -367,6 +369,9 @@ PyObject* entry(PyObject*, PyObject* const* a, Py_ssize_t n)
         try {
             return F(a);
         } catch (...) {
+            if (PyErr_Occurred() && !PyErr_ExceptionMatches(PyExc_AttributeError) && !PyErr_ExceptionMatches(PyExc_TypeError) &&
+                !PyErr_ExceptionMatches(PyExc_OverflowError))
+                return nullptr;
             PyErr_Clear();
         }
     }

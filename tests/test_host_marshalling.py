@@ -114,3 +114,31 @@ assert B._host.quantize(None, 1, 64, B.Operand(), 0, None) is None
 """
     r = subprocess.run([sys.executable, "-c", program], cwd=ROOT, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr
+
+
+@pytest.mark.gpu
+def test_interrupts_are_not_lost():
+    """An exception that interrupts the marshalling ends the call; one that says the call is of another form does not."""
+    class Once(B.Operand):
+        raises = None
+
+        def __getattribute__(self, name):
+            if name == "tensor_id" and Once.raises is not None:
+                error, Once.raises = Once.raises, None
+                raise error
+            return super().__getattribute__(name)
+
+    B.load()
+    X = torch.ones(64, 64, device="cuda")
+    want = B.quantize(X, 1, 64, B.Operand())
+    for error in (KeyboardInterrupt(), TimeoutError()):
+        op = Once()
+        Once.raises = error
+        with pytest.raises(type(error)):
+            B.quantize(X, 1, 64, op)
+    for error in (AttributeError(), TypeError()):
+        op = Once()
+        Once.raises = error
+        for got, ref in zip(B.quantize(X, 1, 64, op), want):
+            assert torch.equal(got, ref)
+        assert Once.raises is None
