@@ -473,6 +473,9 @@ int mode_of(const GemmArgs& g)
     return MODE_TILES + (g.bA > 4 ? kModeWide : 0);
 }
 
+// What the waves share out: tiles, or steps where a step holds two tiles or nothing is clamped.
+int64_t unit_of(const GemmArgs& g) { return g.s < kStep || g.acc_hi == INT_MAX ? kStep : g.s; }
+
 // The products this kernel is the faster one for, by an estimate in us of what a call takes longer with it than
 // with the large tiles' kernel (gemm_fast.hip, and the sum over a split contraction's parts): a sum over what
 // the product has of
@@ -486,6 +489,11 @@ int mode_of(const GemmArgs& g)
 // always this kernel 6.8 %, never 13.7 %.  Codes alone, there / here: 3505 x 456 x 640 23.8 / 9.2 us, 667 x 320 x 2080
 // 17.5 / 5.2, 467 x 3208 x 576 in tiles of 16 17.2 / 10.2, but 8513 x 1396 x 64 15.4 / 25.7, 250 x 200 x 64384 22 / 105.
 // A product that shares its launch with others does not pay for one here (an empty kernel: 1.6 us).
+// With a byte per code and long tiles a wave that gets fewer tiles than another leaves its SIMD idle, and the steps per
+// CU are those of the longest share: 2304 x 586 x 16987 in one tile 149 / 292, 1920 x 600 x 5632 39 / 59.  Over 1005 such products
+// in one to some dozen tiles the choice then takes 1.6 % more time than the better kernel, otherwise 3.3 %.  Not so with packed codes, whose long
+// tiles cost less a step than the fit's short ones (28 x 115 x 16248 in one tile 94 / 46, 800 x 832 x 8384 54 / 28): there
+// the even share is the better estimate (0.4 % against 2 to 21 %).
 struct Estimate {
     double here[5], there[6], launch;
 };
@@ -503,8 +511,10 @@ bool faster_here(const GemmArgs& g, bool alone)
     const int64_t blocks = ((g.RA + 31) / 32) * ((g.RB + 31) / 32), steps = (g.D + kStep - 1) / kStep, rounds = (blocks + 1023) / 1024;
     // (masked outputs: 4096 x 640 x 128 takes 17.9 to 20.2 us here and 19.2 to 19.6 there, with the mask's own pass)
     if (g.mask_src && blocks > 2048) return false;
+    const int64_t unit = unit_of(g), longest = ((g.D + unit - 1) / unit + kWaves - 1) / kWaves * (unit / kStep);
+    const double busy = (double)(wide && unit > kStep ? kWaves * (longest < steps ? longest : steps) : steps);
     const double per_cu = (double)blocks / 256.0, outputs = 1e-6 * (double)g.RA * (double)g.RB;
-    const double here = e.here[0] * (double)steps / kWaves + (e.here[1] + (g.pitchA % 4 != 0 ? e.here[3] : 0.0)) * (double)steps * per_cu +
+    const double here = e.here[0] * (double)steps / kWaves + (e.here[1] + (g.pitchA % 4 != 0 ? e.here[3] : 0.0)) * busy * per_cu +
                         e.here[2] * per_cu + e.here[4] * (double)(rounds - 1) + e.launch - (alone ? 0.0 : kLaunchUs);
     const int64_t across = g.RB <= 64 && !wide && !half ? 64 : 128, stages = (steps + 3) / 4;
     const int64_t tiles = ((g.RA + 127) / 128) * ((g.RB + across - 1) / across), places = (tiles * g.splits + 511) / 512;
@@ -557,8 +567,7 @@ hipError_t launch_gemm_small(const GemmArgs* gs, int n, hipStream_t stream)
         a.acc_hi_scaled = hi > INT_MAX ? INT_MAX : (int)hi;
         a.inv_n = g.inv_n;
         a.mode = mode_of(g);
-        // (steps, where a step holds two tiles or nothing is clamped)
-        a.unit = (int)(g.s < kStep || g.acc_hi == INT_MAX ? kStep : g.s);
+        a.unit = (int)unit_of(g);
         a.units = (int)((g.D + a.unit - 1) / a.unit);
         a.steps_per_tile = (int)(g.s / kStep);
         a.ragged = g.pitchA % 4 != 0 || g.pitchB % 4 != 0;

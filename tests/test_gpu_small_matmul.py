@@ -13,6 +13,17 @@ PACKED = ((32, 8), (64, 8), (16, 8), (32, 12), (16, 9), (16, 6), (96, 32), (128,
 BYTES = ((32, 16), (64, 16), (64, 12), (64, 8), (16, 16), (16, 12), (96, 32), (32, 12), (256, 16))
 
 
+def kernels(RA, RB, D, b, s, a):
+    """What a product launches."""
+    pitch = B.codes_pitch(D, b)
+    qA, qB = (torch.zeros((n, pitch), dtype=torch.uint8, device="cuda") for n in (RA, RB))
+    one = torch.ones(1, device="cuda")
+    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as watch:
+        B.gemm_codes(qA, qB, b, b, one, one, D, 1, a, s, want_acc=False)
+        torch.cuda.synchronize()
+    return " ".join(e.key for e in watch.key_averages() if "kernel" in e.key)
+
+
 def both_kinds(RA, RB, D, extreme):
     for s, a in PACKED:
         check_gemm_codes(RA, RB, D, 4, 4, s, a, extreme=extreme)
@@ -112,3 +123,10 @@ def test_every_length_of_a_waves_chain(s, a, b):
 def test_products_through_lds(RA, RB, D, b, s, a):
     """Enough work for the chunks that go through LDS: whole chunks, what is left of one, an end inside a step."""
     check_gemm_codes(RA, RB, D, b, b, s, a, extreme=0.1)
+
+
+@pytest.mark.parametrize("RA,RB,D,b,s,a,small", [(2304, 586, 16987, 6, 16960, 12, False), (1920, 600, 5632, 8, 5632, 16, False),
+                                                 (64, 586, 16987, 6, 16960, 12, True), (800, 832, 8384, 4, 8384, 16, True)])
+def test_which_kernel_has_a_few_long_tiles(RA, RB, D, b, s, a, small):
+    """Bytes in fewer tiles than a workgroup has waves: many blocks of them are the large tiles' kernel's."""
+    assert ("gemm_small_kernel" in kernels(RA, RB, D, b, s, a)) == small
