@@ -89,9 +89,10 @@ __global__ __launch_bounds__(kThreads) void im2col_tile_kernel(Im2colArgs a, Unf
 
 // ---- unfolding for every geometry (rows of X that are no whole 16-byte units, where a tile's stores would be
 // single elements: 16 x 3 x 224 x 224, window 7, stride 2 50 us against 43; windows whose part of the activation
-// does not fit LDS): a thread has one column of X (its channel and tap are worked out once) and kRows rows of it, kUnroll loads in flight.  (A row at a time, with the divisions of every element in front
-// of a single load: 330 us for the ten such layers of a ResNet-18 at batch 128, 270 MB of
-// matrices; now 170.)
+// does not fit LDS; tiles that do not pay, see unfold_tiles_pay): a thread has one column of X (its channel and
+// tap are worked out once) and kRows rows of it, kUnroll loads in flight.  (A row at a time, with the divisions of
+// every element in front of a single load: 330 us for the ten such layers of a ResNet-18 at batch 128, 270 MB
+// of matrices; this way 170.)
 constexpr int kRows = 32;          // per thread
 constexpr int kUnroll = 8;
 
@@ -238,18 +239,19 @@ __global__ __launch_bounds__(kThreads) void col2im_tile_kernel(Im2colArgs a, Fol
 }
 
 // ---- folding for every geometry (windows of more than three strides; such strides and windows that a
-// tile's matrix rows do not fit LDS): a workgroup has 32 pixels of the activation (of the batch's pixels in
-// a row) and 64 channels.  Lanes are channels, so that the kh * kw elements a lane adds up for a pixel lie
-// in the lines its neighbours read too, and which taps there are is the same for the whole wave; the sums
-// turn through LDS and leave as runs of pixels.  The loads of three taps along a row of the window go out
-// at a time.
-constexpr int kFoldPixels = 32, kFoldChannels = 64, kFoldTaps = 3;
+// tile's matrix rows do not fit LDS; images of fewer than four pixels): a workgroup has 32 pixels of the
+// activation (of the batch's pixels in a row) and 64 channels.  Lanes are channels, so that the kh * kw
+// elements a lane adds up for a pixel lie in the lines its neighbours read too, and which taps there are is
+// the same for the whole wave; the sums turn through LDS and leave as runs of pixels.  The loads of a
+// pixel's taps go out NY x NX at a time: all of them, or (NY = 1) along one row of a larger window.
+constexpr int kFoldPixels = 32, kFoldChannels = 64;
 
 __device__ __forceinline__ int last_tap(int at, int k, int stride)      // largest t < k, t = at modulo stride
 {
     return k - 1 - (k - 1 + stride - at % stride) % stride;
 }
 
+template <int NY, int NX>
 __global__ __launch_bounds__(kThreads) void col2im_kernel(Im2colArgs a)
 {
     __shared__ float turn[kFoldChannels][kFoldPixels + 1];
@@ -269,12 +271,12 @@ __global__ __launch_bounds__(kThreads) void col2im_kernel(Im2colArgs a)
             // the last tap whose matrix row or column is a whole number of strides away, and every
             // stride-th before it
             const int ty_last = last_tap(y + a.ph, a.kh, a.stride), tx_last = last_tap(x + a.pw, a.kw, a.stride);
-            for (int ty0 = ty_last; ty0 >= 0; ty0 -= a.stride)
-                for (int tx0 = tx_last; tx0 >= 0; tx0 -= kFoldTaps * a.stride) {
-                    float v[kFoldTaps];
+            for (int ty0 = ty_last; ty0 >= 0; ty0 -= NY * a.stride)
+                for (int tx0 = tx_last; tx0 >= 0; tx0 -= NX * a.stride) {
+                    float v[NY * NX];
 #pragma unroll
-                    for (int u = 0; u < kFoldTaps; ++u) {
-                        const int ty = ty0, tx = tx0 - u * a.stride;
+                    for (int u = 0; u < NY * NX; ++u) {
+                        const int ty = ty0 - u / NX * a.stride, tx = tx0 - u % NX * a.stride;
                         const int yo = (y + a.ph - ty) / a.stride, xo = (x + a.pw - tx) / a.stride;
                         const bool ok = ty >= 0 && tx >= 0 && y + a.ph >= ty && x + a.pw >= tx && yo < a.Ho && xo < a.Wo;
                         const float* row = a.X + (ok ? ((b * a.Ho + yo) * a.Wo + xo) * (int64_t)K + ty * a.kw + tx : 0);
@@ -282,7 +284,7 @@ __global__ __launch_bounds__(kThreads) void col2im_kernel(Im2colArgs a)
                         if (!ok) v[u] = 0.0f;
                     }
 #pragma unroll
-                    for (int u = 0; u < kFoldTaps; ++u) sum += v[u];
+                    for (int u = 0; u < NY * NX; ++u) sum += v[u];
                 }
             turn[lane][wave * (kFoldPixels / 4) + i] = sum;
             if (++x == a.W) {
@@ -333,7 +335,21 @@ __global__ __launch_bounds__(kThreads) void transpose_kernel(const float* src, f
 
 namespace {
 
-// How the tiles are cut; false where a tile of one row of windows and four channels does not fit.
+// Whether tiles are the faster way, us with a thread's column at a time / in tiles.  Over 1800 random geometries (half of
+// them not looked at for the rule) all in tiles take 1.14 times as long as none (899 lose more than 5 %), with this rule
+// 0.92 (95 lose).  A workgroup costs 0.9 ns whatever it writes: not where
+// images hold few windows (18436 x 384 x 1 x 1, window 1, 17.2 / 106; 29865 x 208 x 1 x 2 19.7 / 142; 16384 x 64 x 2 x 2, window 3, 40 /
+// 54) or little of X comes of them.  Of windows up to two wide a thread's column reads a line of every plane per
+// element and tiles gain most (422 x 384 x 22 x 14, window 1, 298 / 107).  Wider ones share lines between the lanes; there tiles
+// need pixels that several windows read (398 x 72 x 3 x 96, window 4, stride 4, 16.6 / 31.6; H = 1 with a window of 3 x 3, two
+// thirds of them padding, 44 / 66) and workgroups for every CU (7 x 154 x 8 x 62, window 4, stride 2, 140 of them, 9.4 / 14.7).
+bool unfold_tiles_pay(const Im2colArgs& a, int64_t windows, int64_t written, int64_t fetched, int64_t workgroups)
+{
+    if (windows < 16 || written < 1024) return false;
+    return a.kw <= 2 || (2 * written >= 3 * fetched && workgroups >= 400);
+}
+
+// How the tiles are cut; false where a tile of one row of windows and four channels does not fit, or tiles do not pay.
 // Tiles of whole matrix rows of an image where they are short, up to 128 of them and 64 KB of X (16 KB: 26 -> 31
 // us for 64 x 32 x 32, window 3, stride 2); the channels that fit 32 KB then, but runs of at least 256 bytes.
 bool plan_unfold_tile(const Im2colArgs& a, UnfoldTile* t, unsigned* grid, size_t* lds)
@@ -353,6 +369,8 @@ bool plan_unfold_tile(const Im2colArgs& a, UnfoldTile* t, unsigned* grid, size_t
             if (CB < a.C && CB * khw * 4 < 256 && TY > 1) break;
             const int64_t blocks = (a.C + CB - 1) / CB, down = (a.Ho + TY - 1) / TY, batch = a.M / ((int64_t)a.Ho * a.Wo);
             if (across * down > kTiles || across * down * blocks > kTiles / batch) return false;
+            const int64_t windows = TX * (TY < a.Ho ? TY : a.Ho);
+            if (!unfold_tiles_pay(a, windows, windows * CB * khw, CB * height * width, across * down * blocks * batch)) return false;
             const auto div = [](int64_t d) { return make_divisor((uint32_t)d); };
             *t = {(int)TY, (int)CB, (int)sy, (int)sx, (int)(height * width), div(TX), div(across), div(down), div(blocks),
                   div(width), div(height), div(sy), div(sx), div(khw), div(a.kw), div(CB * khw / 4)};
@@ -390,7 +408,7 @@ hipError_t launch_im2col(const Im2colArgs& a, hipStream_t stream)
 
 namespace {
 
-// How the tiles are cut; false where a tile of one pixel row and four channels does not fit.
+// How the tiles are cut; false where a tile of one pixel row and four channels does not fit, or has too few pixels.
 // Tiles of whole image rows where they are short, up to 128 pixels (64 or 256: 32.6 and 26.7 us for 128 x 64 x
 // 32 x 32, window 3, stride 2, which takes 26.7; its 1 x 1 neighbour 9.8 and 11.8 against 8.6); the channels
 // that fit 32 KB then (48 KB: 13.4 -> 13.7 and 9.3 -> 10.4 us at 16 x 16 and 4 x 4 images), but runs of a line
@@ -417,6 +435,9 @@ bool plan_fold_tile(const Im2colArgs& a, FoldTile* t, unsigned* grid, size_t* ld
             const int64_t blocks = (a.C + CB - 1) / CB, down = (a.H + TY - 1) / TY, batch = a.M / ((int64_t)a.H * a.W);
             const bool wide = a.C * khw % 4 == 0;
             if (across * down > kTiles || across * down * blocks > kTiles / batch) return false;
+            // (a workgroup for three pixels: 18436 x 384 x 1 x 1, window 1, 44 / 101 us, 38580 x 144 x 1 x 1, window 3, 60 / 150.  Of
+            // 1800 random geometries 93 lose more than 5 % without this line, 13 with it)
+            if (TX * (TY < a.H ? TY : a.H) < 4) return false;
             int log2p = 0;
             while ((1 << log2p) < TX * TY) ++log2p;
             *t = {(int)TY, log2p, (int)CB, (int)pitch, (int)nx, make_divisor((uint32_t)TX), make_divisor((uint32_t)a.stride),
@@ -457,7 +478,10 @@ hipError_t launch_col2im(const Im2colArgs& a, hipStream_t stream)
     const int64_t runs = (a.M + kFoldPixels - 1) / kFoldPixels;
     const unsigned across = (unsigned)((a.C + kFoldChannels - 1) / kFoldChannels);
     const dim3 grid((unsigned)(runs < (1 << 23) ? runs : (1 << 23)), across);
-    hipLaunchKernelGGL(col2im_kernel, grid, dim3(kThreads), 0, stream, a);
+    if (n == 1) hipLaunchKernelGGL((col2im_kernel<1, 1>), grid, dim3(kThreads), 0, stream, a);
+    else if (n == 2) hipLaunchKernelGGL((col2im_kernel<2, 2>), grid, dim3(kThreads), 0, stream, a);
+    else if (n == 3) hipLaunchKernelGGL((col2im_kernel<3, 3>), grid, dim3(kThreads), 0, stream, a);
+    else hipLaunchKernelGGL((col2im_kernel<1, 3>), grid, dim3(kThreads), 0, stream, a);
     return hipGetLastError();
 }
 

@@ -5,6 +5,7 @@ import torch
 
 from paper_2310_03675_amd import autograd as A
 from paper_2310_03675_amd import binding as B
+from launches import launched
 
 pytestmark = pytest.mark.gpu
 
@@ -44,6 +45,23 @@ def test_unfold_and_fold_tiles(b, c, h, w, kh, kw, stride, ph, pw):
     want = torch.nn.functional.fold(dX.reshape(b, -1, c * kh * kw).transpose(1, 2).contiguous(), output_size=(h, w),
                                     kernel_size=(kh, kw), padding=(ph, pw), stride=stride)
     assert torch.equal(B.col2im(dX, (b, c, h, w), kh, kw, stride, ph, pw), want)
+
+
+@pytest.mark.parametrize("b,c,h,w,kh,kw,stride,ph,pw,unfolds,folds", [
+    # few windows or pixels per image, little of X per tile, few tiles, padding for the most part: a thread's column
+    (400, 64, 1, 1, 1, 1, 1, 0, 0, False, False), (500, 64, 1, 3, 3, 3, 1, 1, 1, False, False), (500, 64, 2, 2, 3, 3, 1, 1, 1, False, True),
+    (300, 4, 1, 20, 1, 2, 1, 0, 0, False, True), (40, 516, 4, 4, 3, 3, 1, 1, 1, False, True), (400, 64, 1, 25, 3, 3, 3, 1, 1, False, True),
+    # tiles: blocks of 4 channels behind those of 16 and 64, tiles cut off by the last row and the last column, pixels
+    # between the windows, rows of a window longer than its stride
+    (60, 68, 13, 40, 3, 3, 2, 1, 1, True, True), (50, 516, 4, 4, 3, 3, 1, 1, 1, True, True), (100, 20, 33, 7, 2, 2, 3, 0, 0, True, True),
+    (3, 132, 14, 14, 1, 1, 2, 0, 0, True, True), (100, 8, 200, 5, 7, 7, 3, 3, 3, True, True), (300, 12, 1, 130, 1, 3, 1, 0, 1, True, True),
+    (120, 12, 6, 130, 1, 5, 1, 0, 2, True, False)])
+def test_which_layouts_go_in_tiles(b, c, h, w, kh, kw, stride, ph, pw, unfolds, folds):
+    test_unfold_and_fold_tiles(b, c, h, w, kh, kw, stride, ph, pw)
+    act = torch.zeros(b, c, h, w, device="cuda")
+    X = B.im2col(act, kh, kw, stride, ph, pw)
+    assert ("im2col_tile_kernel" in launched(lambda: B.im2col(act, kh, kw, stride, ph, pw))) == unfolds
+    assert ("col2im_tile_kernel" in launched(lambda: B.col2im(X, act.shape, kh, kw, stride, ph, pw))) == folds
 
 
 @pytest.mark.parametrize("b,r,c", [(1, 1, 1), (3, 64, 64), (2, 65, 63), (5, 16, 512), (2, 1, 130), (4, 1024, 64)])

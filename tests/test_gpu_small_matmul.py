@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from paper_2310_03675_amd import binding as B  # noqa: F401
+from launches import launched
 from test_gpu_parity import check_gemm_codes
 
 pytestmark = pytest.mark.gpu
@@ -18,10 +19,7 @@ def kernels(RA, RB, D, b, s, a):
     pitch = B.codes_pitch(D, b)
     qA, qB = (torch.zeros((n, pitch), dtype=torch.uint8, device="cuda") for n in (RA, RB))
     one = torch.ones(1, device="cuda")
-    with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as watch:
-        B.gemm_codes(qA, qB, b, b, one, one, D, 1, a, s, want_acc=False)
-        torch.cuda.synchronize()
-    return " ".join(e.key for e in watch.key_averages() if "kernel" in e.key)
+    return launched(lambda: B.gemm_codes(qA, qB, b, b, one, one, D, 1, a, s, want_acc=False))
 
 
 def both_kinds(RA, RB, D, extreme):
