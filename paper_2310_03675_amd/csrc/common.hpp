@@ -383,6 +383,18 @@ __device__ __forceinline__ Maxima fetch_maxima(const QMeta* meta, int dense)
     return x;
 }
 
+// From one of the record's largest values in every lane.
+__device__ __forceinline__ Scaling scaling_from(uint32_t slot, float clip, int b)
+{
+    const float amax = __uint_as_float(wave_max_bits(slot));
+    const float amax_c = clip * amax;
+    Scaling s;
+    const bool zero = (amax_c == 0.0f);
+    s.inv = zero ? 0.0f : inverse_step(amax_c, b);
+    s.scale = zero ? 0.0f : amax_c / (float)(1 << (b - 1));
+    return s;
+}
+
 __device__ __forceinline__ Scaling scaling_of(const Maxima& x, const QMeta* meta, float clip, int b, int dense)
 {
     const int lane = threadIdx.x & 63;
@@ -397,18 +409,14 @@ __device__ __forceinline__ Scaling scaling_of(const Maxima& x, const QMeta* meta
         }
         slot = larger(slot, larger(larger(w[0], w[1]), larger(w[2], w[3])));
     }
-    const float amax = __uint_as_float(wave_max_bits(slot));
-    const float amax_c = clip * amax;
-    Scaling s;
-    const bool zero = (amax_c == 0.0f);
-    s.inv = zero ? 0.0f : inverse_step(amax_c, b);
-    s.scale = zero ? 0.0f : amax_c / (float)(1 << (b - 1));
-    return s;
+    return scaling_from(slot, clip, b);
 }
 
-__device__ __forceinline__ Scaling load_scaling(const QMeta* meta, float clip, int b, int dense = 0)
+// Where the maxima always stand in slots.  (An ordinary load that stays where it is written: the compiler moves others
+// to where the value is needed.)
+__device__ __forceinline__ uint32_t fetch_slot(const QMeta* meta)
 {
-    return scaling_of(fetch_maxima(meta, dense), meta, clip, b, dense);
+    return __hip_atomic_load(&meta->amax[(threadIdx.x & 63) * kAmaxSlotStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
 __device__ __forceinline__ void publish_scale(const QuantArgs& q, const Scaling& s)
