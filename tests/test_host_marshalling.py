@@ -3,6 +3,7 @@ same results and the same refusals, and every call that is not of the ordinary f
 import os
 import subprocess
 import sys
+import threading
 
 import pytest
 import torch
@@ -35,8 +36,8 @@ def _calls():
     g.manual_seed(3)
     new = lambda *shape: torch.randn(shape, generator=g, device="cuda")
     M, K, N = 96, 72, 40
-    X, W, G, act = torch.relu(new(M, K)), new(K, N), new(M, N), torch.relu(new(2, 8, 8, 8))
-    Wc, Gc, mask = new(72, 24), new(128, 24), torch.relu(new(M, K))
+    X, W, G, act = torch.relu(new(M, K)), new(K, N), new(M, N), torch.relu(new(2, 64, 8, 8))
+    Wc, Gc, mask = new(576, 64), new(128, 64), torch.relu(new(M, K))
     st = lambda **k: _prm(Bq=(4, ST), **k)
     fwd, bwi, bww = _prm(), _prm(A=(4, ST)), st(seed=2 ** 64 - 1)
     side = torch.cuda.Stream()
@@ -51,18 +52,52 @@ def _calls():
         return (Z,) + B.conv_bwd(Gc, Wc, saved, act.shape, 3, 3, bwi, bww, **k)
 
     out = tuple(torch.empty(s, device="cuda") for s in ((M, N), (M, K), (K, N)))
-    return [
+    room, small = (torch.empty(n, dtype=torch.uint8, device="cuda") for n in (1 << 20, 64))
+    acc = torch.empty((M, N), dtype=torch.int32, device="cuda")
+    saved = lambda: torch.empty(1 << 16, dtype=torch.uint8, device="cuda")
+    parameter = torch.nn.Parameter(W)
+    NATIVE = [
         lambda: B.quantize(X, 0, 64, B.Operand(4, ST, 1.0, 7), 2 ** 64 - 1), lambda: B.quantize(X, 1, 16, B.Operand(8), -1),
         lambda: B.gemm(0, X, W, M, K, N, fwd, want_acc=True)[:2], lambda: B.gemm(1, G, W, M, K, N, bwi, bf16=True)[:1],
         lambda: B.gemm(1, G, W, M, K, N, bwi, mask=mask)[:1], lambda: B.gemm(2, X, G, M, K, N, bww, stream=side)[:1],
         lambda: B.layer_step(X, W, G, fwd, bwi, bww)[:3], lambda: B.layer_step(X, W, G, fwd, None, bww)[:3],
         lambda: B.layer_step(X, W, G, fwd, bwi, bww, out=out)[:3], lambda: B.layer_fwd(X, W, fwd)[:1], bwd,
         lambda: bwd(mask=X), conv, lambda: conv(mask=act),
-        # refused by the library, and of another form
+        # buffers of the caller's, weights that are parameters
+        lambda: B.gemm(0, X, parameter, M, K, N, fwd, out=out[0], acc=acc, workspace=room)[:2],
+        lambda: B.layer_step(X, parameter, G, fwd, bwi, bww, workspace=room)[:3],
+        lambda: B.layer_fwd(X, W, fwd, bww, out=out[0], saved=saved(), workspace=room)[:1], lambda: bwd(workspace=room)]
+    REFUSED = [
         lambda: B.gemm(0, X, W, M, K, N, _prm(n=48)), lambda: B.layer_step(X, W, G, fwd, bwi, _prm(s=0)),
-        lambda: B.conv_fwd(act, 2, 2, new(32, 8), fwd, bww), lambda: B.quantize(X, 2, 64, B.Operand()),
-        lambda: B.quantize(X.t(), 1, 64, B.Operand()), lambda: B.gemm(0, X, W, M, K, N, _prm(n="64")),
-        lambda: B.layer_step(X, G, W, fwd, bwi, bww)]
+        lambda: B.conv_fwd(act, 2, 2, new(256, 64), fwd, bww), lambda: B.quantize(X, 1, 64, B.Operand(9)),
+        lambda: B.gemm(0, X, W, M, K, N, fwd, workspace=small), lambda: B.layer_step(X, W, G, fwd, bwi, bww, workspace=small),
+        lambda: B.layer_fwd(X, W, fwd, bww, saved=small), lambda: bwd(workspace=room[4:]),
+        lambda: B.gemm(0, X, W, M, K, N, fwd, workspace=room[1:]), lambda: B.layer_fwd(X, W, fwd, bww, saved=saved()[8:])]
+    OTHER = [
+        lambda: B.quantize(X, 2, 64, B.Operand()), lambda: B.quantize(X.t(), 1, 64, B.Operand()),
+        lambda: B.gemm(0, X, W, M, K, N, _prm(n="64")), lambda: B.layer_step(X, G, W, fwd, bwi, bww),
+        lambda: B.gemm(0, X, W, M, K, N, fwd, out=out[0].half()), lambda: B.layer_step(X, W, G, fwd, bwi, bww, out=list(out))[:3]]
+    return [(c, tuple) for c in NATIVE] + [(c, int) for c in REFUSED] + [(c, type(None)) for c in OTHER]
+
+
+class _Watched:
+    """_host, with the types of what its functions returned."""
+    def __init__(self, host):
+        self._host, self.returned = host, []
+
+    def __getattr__(self, name):
+        f = getattr(self._host, name)
+
+        def call(*args):
+            r = f(*args)
+            self.returned.append(type(r))
+            return r
+        return call
+
+
+class _Off:
+    def __getattr__(self, name):
+        return lambda *args: None
 
 
 def _outcome(call):
@@ -74,17 +109,7 @@ def _outcome(call):
     return [None if t is None else (t.dtype, tuple(t.shape), t.clone()) for t in r]
 
 
-@pytest.mark.gpu
-@pytest.mark.parametrize("k", range(21))
-def test_same_as_through_ctypes(k, monkeypatch):
-    class Off:
-        def __getattr__(self, name):
-            return lambda *args: None
-
-    call = _calls()[k]
-    here = _outcome(call)
-    monkeypatch.setattr(B, "_host", Off())
-    there = _outcome(call)
+def _same(here, there):
     if isinstance(there, tuple):
         assert here == there
         return
@@ -93,6 +118,48 @@ def test_same_as_through_ctypes(k, monkeypatch):
         assert (a is None) == (b is None)
         if a is not None:
             assert a[:2] == b[:2] and torch.equal(a[2], b[2])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("k", range(34))
+def test_same_as_through_ctypes(k, monkeypatch):
+    B.load()
+    calls = _calls()
+    assert len(calls) == 34
+    call, returns = calls[k]
+    watched = _Watched(B._host)
+    monkeypatch.setattr(B, "_host", watched)
+    here = _outcome(call)
+    assert watched.returned and watched.returned[-1] is returns
+    monkeypatch.setattr(B, "_host", _Off())
+    _same(here, _outcome(call))
+
+
+@pytest.mark.gpu
+def test_calls_of_several_threads(monkeypatch):
+    """The interpreter's lock is not held during the library's call: threads on streams of their own."""
+    B.load()
+    g = torch.Generator(device="cuda").manual_seed(9)
+    prm = [_prm(seed=i) for i in range(3)]
+    work = [[torch.randn(s, generator=g, device="cuda") for s in ((200 + 8 * i, 72), (72, 40), (200 + 8 * i, 40))] for i in range(4)]
+    torch.cuda.synchronize()
+    got = [None] * len(work)
+
+    def run(i):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            got[i] = [B.layer_step(*work[i], *prm)[:3] for _ in range(20)]
+        stream.synchronize()
+
+    threads = [threading.Thread(target=run, args=(i,)) for i in range(len(work))]
+    for t in threads: t.start()
+    for t in threads: t.join()
+    monkeypatch.setattr(B, "_host", _Off())
+    for i, w in enumerate(work):
+        want = B.layer_step(*w, *prm)[:3]
+        for step in got[i]:
+            for a, b in zip(step, want):
+                assert torch.equal(a, b)
 
 
 @pytest.mark.parametrize("error,warned", [("ModuleNotFoundError", False), ("ImportError", True)])
