@@ -1,6 +1,6 @@
 """GPU parity of the matmul on both sides of the line between its two kernels: small products (32 x 32
-blocks, the contraction shared by a workgroup's waves) and those just behind it, which go to the
-large tiles: long contractions, and outputs of many blocks."""
+blocks, the contraction shared by a workgroup's waves) and those that an estimate gives to the large tiles:
+long contractions, and outputs of many blocks.  Which kernel a case is for is checked with it."""
 import pytest
 import torch
 
@@ -37,14 +37,34 @@ def test_small_products(D):
     both_kinds(1, 40, D, 0.1)
 
 
-def test_small_products_at_the_longest_contraction():
+def test_small_products_of_long_contractions():
     both_kinds(40, 33, 4608, 0.3)
     both_kinds(33, 31, 4607, 0.05)
 
 
+# (a single tile of packed codes stays with the small kernel at any length)
+SINGLE = (8192, 32)
+
+
 @pytest.mark.parametrize("D", [4640, 5003, 8200])
-def test_long_contractions_on_large_tiles(D):
+def test_contractions_on_either_kernel(D):
     both_kinds(131, 70, D, 0.3)
+
+
+@pytest.mark.parametrize("D", [24008, 40003])
+def test_long_contractions_on_large_tiles(D):
+    """In parts, with rows that end inside a tile, a step and a dword."""
+    for b, settings in ((4, PACKED), (7, BYTES)):
+        for s, a in settings:
+            assert ("gemm_small_kernel" in kernels(131, 70, D, b, s, a)) == ((s, a) == SINGLE)
+    both_kinds(131, 70, D, 0.3)
+
+
+@pytest.mark.parametrize("RA,RB,D", [(771, 1025, 6008), (515, 1027, 8203)])
+@pytest.mark.parametrize("b,s,a", [(4, 64, 8), (4, 16, 9), (4, 96, 32), (4, 128, 16), (7, 32, 16), (7, 16, 12), (7, 64, 12)])
+def test_many_large_tiles_in_parts(RA, RB, D, b, s, a):
+    assert "gemm_small_kernel" not in kernels(RA, RB, D, b, s, a)
+    check_gemm_codes(RA, RB, D, b, b, s, a, extreme=0.2)
 
 
 @pytest.mark.parametrize("RA,RB,D,b,s,a", [(224, 256, 4480, 4, 16, 8), (2299, 128, 3712, 8, 64, 16), (288, 1024, 3456, 8, 128, 32),
@@ -56,8 +76,17 @@ def test_long_chains_around_the_estimates(RA, RB, D, b, s, a):
 
 
 @pytest.mark.parametrize("D", [27, 64, 100, 129, 520])
-def test_many_blocks_on_large_tiles(D):
+def test_many_blocks(D):
     both_kinds(1100, 1000, D, 0.2)
+
+
+@pytest.mark.parametrize("D", [27, 64, 100, 129, 264])
+def test_many_blocks_on_large_tiles(D):
+    """Short contractions in one part, rows and columns that end inside a tile."""
+    for b, settings in ((4, PACKED), (7, BYTES)):
+        for s, a in settings:
+            assert "gemm_small_kernel" not in kernels(4100, 2001, D, b, s, a)
+    both_kinds(4100, 2001, D, 0.2)
 
 
 @pytest.mark.parametrize("RB,D", [(37, 27), (64, 27), (64, 100), (50, 37), (64, 561)])
@@ -114,13 +143,37 @@ def test_every_length_of_a_waves_chain(s, a, b):
         check_gemm_codes(70, 45, D, b, b, s, a, extreme=0.2)
 
 
-@pytest.mark.parametrize("RA,RB,D,b,s,a", [(480, 1000, 12288, 4, 32, 8), (481, 1001, 12312, 4, 32, 8), (700, 640, 6000, 4, 64, 12),
-                                           (1300, 500, 4120, 8, 32, 16), (500, 900, 4136, 8, 16, 16), (500, 1000, 5184, 3, 96, 10),
-                                           (600, 660, 4863, 4, 32, 8), (257, 640, 12287, 4, 32, 8), (320, 900, 2559, 4, 64, 12),
-                                           (1000, 90, 3392, 8, 32, 16), (400, 130, 3391, 8, 16, 12)])
+@pytest.mark.parametrize("RA,RB,D,b,s,a", [(481, 1001, 12312, 4, 32, 8), (600, 660, 4863, 4, 32, 8), (257, 640, 12287, 4, 32, 8),
+                                           (320, 900, 2559, 4, 64, 12), (1000, 90, 3392, 8, 32, 16), (400, 130, 3391, 8, 16, 12)])
+def test_products_with_less_work_than_lds_takes(RA, RB, D, b, s, a):
+    assert "gemm_small_kernel<true>" not in kernels(RA, RB, D, b, s, a)
+    check_gemm_codes(RA, RB, D, b, b, s, a, extreme=0.1)
+
+
+@pytest.mark.parametrize("RA,RB,D,b,s,a", [
+    (480, 1000, 12288, 4, 32, 8), (600, 900, 4863, 4, 32, 8), (520, 1001, 4735, 4, 32, 8), (480, 1000, 12287, 4, 32, 8), (512, 1024, 4736, 4, 32, 8),
+    (700, 640, 6000, 4, 64, 12), (400, 900, 2559, 4, 64, 12), (400, 901, 2560, 4, 64, 12), (700, 641, 6000, 4, 96, 10), (500, 1000, 5184, 3, 96, 10),
+    (1300, 500, 4120, 8, 32, 16), (1300, 501, 4100, 8, 32, 16), (500, 900, 4136, 8, 16, 16), (600, 600, 4160, 7, 16, 12),
+    (1000, 300, 3392, 8, 32, 16), (601, 660, 4096, 8, 64, 12), (601, 661, 4108, 8, 64, 12)])
 def test_products_through_lds(RA, RB, D, b, s, a):
     """Enough work for the chunks that go through LDS: whole chunks, what is left of one, an end inside a step."""
+    assert "gemm_small_kernel<true>" in kernels(RA, RB, D, b, s, a)
     check_gemm_codes(RA, RB, D, b, b, s, a, extreme=0.1)
+
+
+@pytest.mark.parametrize("M,K,N,b,s,a", [(517, 4736, 840, 4, 32, 8), (1032, 2504, 454, 4, 64, 12), (1156, 2052, 430, 7, 32, 12)])
+def test_step_whose_products_share_a_launch_through_lds(M, K, N, b, s, a):
+    """Lines in whole pieces, lines that are not, and lines off a dword beside each other: the same as one by one."""
+    g = torch.Generator(device="cuda").manual_seed(M)
+    X, W, G = (torch.randn(*n, device="cuda", generator=g) for n in ((M, K), (K, N), (M, N)))
+    prm = [B.Params(had_block=64, acc_bits=a, s=s, seed=i, A=B.Operand(b, B.ROUND_NEAREST, 1.0, 2 * i),
+                    B=B.Operand(b, B.ROUND_NEAREST, 1.0, 2 * i + 1)) for i in range(3)]
+    step = []
+    names = launched(lambda: step.extend(B.layer_step(X, W, G, *prm)[:3]))
+    assert names.count("gemm_small_kernel<true>") == 1 and "gemm_i4" not in names, names
+    kinds = (B.GEMM_FWD, X, W), (B.GEMM_BWD_INPUT, G, W), (B.GEMM_BWD_WEIGHT, X, G)
+    for got, (kind, P, Q), p in zip(step, kinds, prm):
+        assert torch.equal(got, B.gemm(kind, P, Q, M, K, N, p)[0])
 
 
 @pytest.mark.parametrize("RA,RB,D,b,s,a,small", [(2304, 586, 16987, 6, 16960, 12, False), (1920, 600, 5632, 8, 5632, 16, False),
