@@ -67,7 +67,6 @@ struct AnyPlan {
     int count;              // its workgroups
     int dense;              // `count` if the maxima stand side by side, 0 for atomic slots
     int wc;                 // axis 0: waves side by side in a workgroup (1, 2 or 4)
-    int unused;
     Divisor per;            // axis 1: threads per line; axis 0: workgroups along the columns
 };
 constexpr int kMaxAny = 6;

@@ -370,20 +370,20 @@ __device__ __forceinline__ v16i contract(const SmallArgs& g, int row0, int col0,
         if (k_rest < k_whole) fetch_rest(next, k_rest);
         if (k_rest < k_whole) multiply(next, (k_whole - k_rest) / kStep, std::integral_constant<int, G>{});
     } else {
-    const int full = whole_steps / G;        // groups
-    if (full) {
-        // (the loop's loads are unconditional: the compiler can count them and waits for the older ones only)
-        fetch(now, k_begin);
-        for (int done = 1; done < full; ++done) {
-            fetch(next, k_begin + done * G * kStep);
-            multiply(now, G, std::integral_constant<int, G>{});
-            now = next;
+        const int full = whole_steps / G;        // groups
+        if (full) {
+            // (the loop's loads are unconditional: the compiler can count them and waits for the older ones only)
+            fetch(now, k_begin);
+            for (int done = 1; done < full; ++done) {
+                fetch(next, k_begin + done * G * kStep);
+                multiply(now, G, std::integral_constant<int, G>{});
+                now = next;
+            }
         }
-    }
-    const int rest = whole_steps - full * G;
-    if (rest) fetch_rest(next, k_whole - rest * kStep);
-    if (full) multiply(now, G, std::integral_constant<int, G>{});
-    if (rest) multiply(next, rest, std::integral_constant<int, G>{});
+        const int rest = whole_steps - full * G;
+        if (rest) fetch_rest(next, k_whole - rest * kStep);
+        if (full) multiply(now, G, std::integral_constant<int, G>{});
+        if (rest) multiply(next, rest, std::integral_constant<int, G>{});
     }
     if (k_whole < k_end) {                   // the line ends inside a step
         Group last{};
@@ -401,7 +401,6 @@ __device__ __forceinline__ v16i contract(const SmallArgs& g, int row0, int col0,
 
 struct SmallBatch {
     int first[kMaxSmallBatch];       // a product's first workgroup, INT_MAX behind the last product
-    int n;
     SmallArgs g[kMaxSmallBatch];
 };
 
@@ -435,7 +434,11 @@ __global__ __launch_bounds__(64 * kWaves, 4) void gemm_small_kernel(SmallBatch b
     switch (g.mode) {
     case MODE_TILES: HDQT_CONTRACT(false, MODE_TILES); break;
     case MODE_SAT8: HDQT_CONTRACT(false, MODE_SAT8); break;
-    case MODE_HALF: HDQT_CONTRACT(false, MODE_HALF); break;
+    case MODE_HALF:
+        // (launch_gemm_small sends none to the staged kernel)
+        if constexpr (STAGED) total = v16i{};
+        else HDQT_CONTRACT(false, MODE_HALF);
+        break;
     case MODE_TILES + kModeWide: HDQT_CONTRACT(true, MODE_TILES); break;
     default: HDQT_CONTRACT(true, MODE_HALF); break;
     }
@@ -550,7 +553,6 @@ hipError_t launch_gemm_small(const GemmArgs* gs, int n, hipStream_t stream)
 {
     if (n < 1 || n > kMaxSmallBatch) return hipErrorInvalidValue;
     SmallBatch b{};
-    b.n = n;
     int64_t total = 0, work = 0, staged_blocks = 0;
     bool packed_halves = false, paired = true, all_aligned = true;
     for (int k = 0; k < kMaxSmallBatch; ++k) b.first[k] = INT_MAX;
