@@ -34,14 +34,14 @@ HBM_PEAK_GBPS = 8000.0          # MI355X HBM3E
 TRAFFIC_SOURCE = "profiles/bench_resnet_k1152_hbm_traffic.md (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE, not measured in this run)"
 VALU_SOURCE = "profiles/bench_resnet_k1152_valu_issue.md (rocprofv3 --pmc SQ_INSTS_VALU, not measured in this run)"
 MEASURED_TRAFFIC = {
-    "fwht_dual_absmax_batch": 336.5e6, "fwht_dual_quant_batch": 424.1e6,
+    "fwht_dual_absmax_batch": 336.5e6, "fwht_dual_quant_batch": 423.9e6,
     "gemm_i4_fwd": 74.6e6, "gemm_i4_bwd_input": 307.4e6, "gemm_i4_bwd_weight": 61.8e6,
 }
 # The kernels' sources as they were when those counters were collected: a SHA-256 over the
 # files below, in this order.  The bench line says whether they have changed since (then the
 # counter figures describe older kernels; re-collect them and update this value).
 PROFILED_SOURCES = ("common.hpp", "lane_ops.hpp", "quantize_any.hpp", "quantize_dual.hip", "gemm_fast.hip", "gemm.hip")
-PROFILED_SOURCES_SHA256 = "1e5a373ec03228fc39dba24c2daf9eb29911b1076745152914cb7db74f0a9b8f"
+PROFILED_SOURCES_SHA256 = "0dbbd51ad509b476aa4b12e20df5947cd333b13d4c957593e7cceb3bc113be30"
 
 
 def profiled_sources_sha256():

@@ -169,7 +169,9 @@ def _as_activation(dAct: torch.Tensor, innermost: bool) -> torch.Tensor:
     """The gradient of an activation in the activation's layout.  The kernels write channel planes; behind a
     normalisation everything else has its channels innermost, and PyTorch's elementwise kernels take
     three times as long over two layouts as over one (the rectifier's backward pass at 128 x 64 x 32 x 32
-    55 against 16 us, the transposition 12; at 128 x 256 x 8 x 8 17, 5 and 7)."""
+    55 against 16 us, the transposition 12; at 128 x 256 x 8 x 8 17, 5 and 7).  The gradient's values are the same
+    bit for bit; what PyTorch adds up behind it (a bias over that activation, say) it may add in another order, as
+    behind a gradient of its own in that layout.  For the moment of the transposition there are two of them."""
     if not innermost or dAct.data_ptr() % 16 or not dAct.is_contiguous():
         return dAct
     Bn, Cin, H, W = dAct.shape

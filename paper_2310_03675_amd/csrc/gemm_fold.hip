@@ -247,10 +247,10 @@ bool gemm_fold_plan(GemmArgs* g, int64_t batch, int C, int H, int W, int kh, int
     return gemm_fast_eligible(*g);
 }
 
-// Workgroups of 256 pixels and 64 channels below which the chip has too few of them.  Over 640 layers (windows of
-// 3 x 3 and 1 x 5, 32 to 256 codes a tap): 1.4 to 1.8 times faster with a quarter of that each up to 64
-// workgroups, 1.3 to 1.4 at 128, 1.04 to 1.17 at 192 (128 channels of 16 x 16, 256 codes a tap, 27.6 / 29.1 us), 0.86 to 1.08
-// at 256 to 511, 0.7 to 1.0 beyond.
+// Workgroups of 256 pixels and 64 channels below which the chip has too few of them.  Over 900 layers (windows of
+// 1 x 1 to 5 x 5, 32 to 512 codes a tap), large workgroups / a quarter of that each, geometric means and ranges of the
+// times' ratio: 1.53 (0.90 to 2.06) below 64 workgroups, 1.35 (1.02 to 1.94) below 128, 1.14 (0.88 to 1.93) below 192, 1.00 (0.72 to 1.44)
+// from there to 255, 1.16 (0.73 to 1.77) at 256 to 340, where which is ahead changes with the layer.
 constexpr int64_t kFewWorkgroups = 192;
 
 hipError_t launch_gemm_fold(const GemmArgs& g_in, hipStream_t stream)

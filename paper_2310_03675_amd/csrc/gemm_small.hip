@@ -117,7 +117,7 @@ __device__ __forceinline__ void swap_halves(uint32_t v, uint32_t w, uint32_t& x,
 // what its matrix cores needed for the step.
 // RAGGED: lines that do not start on a dword.  Loads of 16 bytes from such addresses cost twice, so the aligned
 // dwords are fetched and shifted into place; the dword behind a lane's four is the first of the lane that
-// has the next 16 bytes, and the last unit's upper half fetches its fourth whole from where it is.  (2074 x 355 x 555, packed: 7.4 us.)
+// has the next 16 bytes, and the last unit's upper half fetches its fourth whole from where it is.  (2074 x 355 x 555, packed: 7.3 us.)
 template <bool RAGGED, int N>
 __device__ __forceinline__ void load_units(const uint8_t* q, uint32_t line, uint32_t k, int half, Words4 (&out)[N])
 {
@@ -489,8 +489,9 @@ int64_t unit_of(const GemmArgs& g) { return g.s < kStep || g.acc_hi == INT_MAX ?
 // and a difference of what any launch takes.  The coefficients are least squares over 900 forward products and
 // gradients of random sizes (outputs of 16 to 20000 rows and columns, contractions from 16 to 20000) and settings, each
 // timed with its quantization and both kernels: the choice takes 0.3 % more time than the better of the two would,
-// always this kernel 6.8 %, never 13.7 %.  Codes alone, there / here: 3505 x 456 x 640 23.8 / 9.2 us, 667 x 320 x 2080
-// 17.5 / 5.2, 467 x 3208 x 576 in tiles of 16 17.2 / 10.2, but 8513 x 1396 x 64 15.4 / 25.7, 250 x 200 x 64384 22 / 105.
+// always this kernel 6.8 %, never 13.7 %.  Over others than the fit's, codes alone: 0.9 % over 250 of the
+// same ranges, nothing over 200 with contractions of 20000 to 300000.  There / here: 3505 x 456 x 640 23.8 / 9.2 us, 667 x 320 x
+// 2080 17.5 / 5.2, 467 x 3208 x 576 in tiles of 16 17.2 / 10.2, but 8513 x 1396 x 64 15.4 / 25.7, 250 x 200 x 64384 22 / 105.
 // A product that shares its launch with others does not pay for one here (an empty kernel: 1.6 us).
 // With a byte per code and long tiles a wave that gets fewer tiles than another leaves its SIMD idle, and the steps per
 // CU are those of the longest share: 2304 x 586 x 16987 in one tile 149 / 292, 1920 x 600 x 5632 39 / 59.  Over 1005 such products
