@@ -14,6 +14,8 @@
 #include <Python.h>
 #include <dlfcn.h>
 
+#include <optional>
+
 #include <ATen/ops/empty.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -75,6 +77,19 @@ struct Member {
     PyObject* o;
     Member(PyObject* of, PyObject* name) : o(PyObject_GetAttr(of, name)) { if (!o) throw Other(); }
     ~Member() { Py_DECREF(o); }
+};
+
+// The members of a tuple or a list of n, kept for the call (a list may change while the interpreter's lock is not held).
+struct Members {
+    PyObject* t;
+    Members(PyObject* o, Py_ssize_t n) : t(PyTuple_Check(o) || PyList_CheckExact(o) ? PySequence_Tuple(o) : nullptr)
+    {
+        if (t && PyTuple_GET_SIZE(t) == n) return;
+        Py_XDECREF(t);
+        throw Other();
+    }
+    ~Members() { Py_DECREF(t); }
+    PyObject* operator[](Py_ssize_t k) const { return PyTuple_GET_ITEM(t, k); }
 };
 
 // (modulo 2^64 and then the field's width, as ctypes stores an integer)
@@ -224,7 +239,7 @@ PyObject* layer_step(PyObject* const* a)
     const MaybeParams bwi(a[4]);
     const at::Tensor* given_ws = maybe(a[7], at::kByte);
     void* stream = handle_of(a[8]);
-    PyObject* given[3] = {nullptr, nullptr, nullptr};
+    std::optional<Members> given;
     at::Tensor made[3], ws;
     float* po[3];
     if (a[6] == Py_None) {
@@ -233,11 +248,8 @@ PyObject* layer_step(PyObject* const* a)
         made[2] = fresh({K, N}, at::kFloat, X);
         for (int k = 0; k < 3; ++k) po[k] = made[k].defined() ? (float*)address(made[k]) : nullptr;
     } else {
-        if (!PyTuple_CheckExact(a[6]) || PyTuple_GET_SIZE(a[6]) != 3) throw Other();
-        for (int k = 0; k < 3; ++k) {
-            given[k] = PyTuple_GET_ITEM(a[6], k);
-            po[k] = (float*)address(maybe(given[k], at::kFloat));
-        }
+        given.emplace(a[6], 3);
+        for (int k = 0; k < 3; ++k) po[k] = (float*)address(maybe((*given)[k], at::kFloat));
     }
     if (!given_ws) ws = bytes(lib.step_workspace_size(M, K, N, &fwd, bwi.p, &bww), X);
     const float *pX = (const float*)address(X), *pW = (const float*)address(W), *pG = (const float*)address(G);
@@ -245,7 +257,7 @@ PyObject* layer_step(PyObject* const* a)
     const size_t n = (size_t)(given_ws ? given_ws->numel() : ws.numel());
     const int rc = unlocked([&] { return lib.step(pX, pW, pG, po[0], po[1], po[2], M, K, N, &fwd, bwi.p, &bww, pw, n, stream); });
     if (rc) return PyLong_FromLong(rc);
-    auto result = [&](int k) { return given[k] ? Result(given[k]) : Result(std::move(made[k])); };
+    auto result = [&](int k) { return given ? Result((*given)[k]) : Result(std::move(made[k])); };
     return tuple(result(0), result(1), result(2), given_ws ? Result(a[7]) : Result(std::move(ws)));
 }
 
@@ -282,22 +294,32 @@ PyObject* layer_bwd(PyObject* const* a)
     const MaybeParams bwi(a[4]);
     const hdqt_params_t bww = params(a[5]);
     const at::Tensor *given_ws = maybe(a[7], at::kByte), *mask = maybe(a[9], at::kFloat);
-    if (a[6] != Py_None || K < 0) throw Other();
+    if (K < 0) throw Other();
     if (mask && (!bwi.p || mask->dim() != 2 || mask->size(0) != M || mask->size(1) != K)) throw Other();
     void* stream = handle_of(a[8]);
-    at::Tensor dX, dW = fresh({K, N}, at::kFloat, G), ws;
-    if (bwi.p) dX = fresh({M, K}, at::kFloat, G);
+    std::optional<Members> given;
+    at::Tensor made[2], ws;                  // dX, dW
+    float* po[2];
+    if (a[6] == Py_None) {
+        if (bwi.p) made[0] = fresh({M, K}, at::kFloat, G);
+        made[1] = fresh({K, N}, at::kFloat, G);
+        for (int k = 0; k < 2; ++k) po[k] = made[k].defined() ? (float*)address(made[k]) : nullptr;
+    } else {
+        given.emplace(a[6], 2);
+        for (int k = 0; k < 2; ++k) po[k] = (float*)address(maybe((*given)[k], at::kFloat));
+        if (mask && !po[0]) throw Other();
+    }
     if (!given_ws) ws = bytes(lib.bwd_workspace_size(M, K, N, bwi.p, &bww), G);
     const float *pG = (const float*)address(G), *pW = (const float*)address(W), *pm = (const float*)address(mask);
-    float *px = dX.defined() ? (float*)address(dX) : nullptr, *pd = (float*)address(dW);
     void *ps = address(saved), *pw = given_ws ? address(given_ws) : address(ws);
     const size_t n = (size_t)(given_ws ? given_ws->numel() : ws.numel());
     const int rc = unlocked([&] {
-        return pm ? lib.bwd_masked(pG, pW, ps, pm, px, pd, M, K, N, bwi.p, &bww, pw, n, stream)
-                  : lib.bwd(pG, pW, ps, px, pd, M, K, N, bwi.p, &bww, pw, n, stream);
+        return pm ? lib.bwd_masked(pG, pW, ps, pm, po[0], po[1], M, K, N, bwi.p, &bww, pw, n, stream)
+                  : lib.bwd(pG, pW, ps, po[0], po[1], M, K, N, bwi.p, &bww, pw, n, stream);
     });
     if (rc) return PyLong_FromLong(rc);
-    return tuple(Result(std::move(dX)), Result(std::move(dW)));
+    auto result = [&](int k) { return given ? Result((*given)[k]) : Result(std::move(made[k])); };
+    return tuple(result(0), result(1));
 }
 
 // (window sizes that the geometry's fields hold)
@@ -332,10 +354,10 @@ PyObject* conv_fwd(PyObject* const* a)
 PyObject* conv_bwd(PyObject* const* a)
 {
     const at::Tensor &G = tensor(a[0], at::kFloat, 2), &W = tensor(a[1], at::kFloat, 2), &saved = tensor(a[2], at::kByte);
-    if (!PyTuple_Check(a[3]) || PyTuple_GET_SIZE(a[3]) != 4) throw Other();      // (a torch.Size is one)
+    const Members shape(a[3], 4);
     int64_t d[4];
     for (int k = 0; k < 4; ++k) {
-        d[k] = integer(PyTuple_GET_ITEM(a[3], k));
+        d[k] = integer(shape[k]);
         if (d[k] < 0 || d[k] > INT32_MAX) throw Other();
     }
     const hdqt_conv_t geo = {d[0], (int32_t)d[1], (int32_t)d[2], (int32_t)d[3], window(a[4]), window(a[5])};

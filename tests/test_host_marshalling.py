@@ -66,17 +66,23 @@ def _calls():
         # buffers of the caller's, weights that are parameters
         lambda: B.gemm(0, X, parameter, M, K, N, fwd, out=out[0], acc=acc, workspace=room)[:2],
         lambda: B.layer_step(X, parameter, G, fwd, bwi, bww, workspace=room)[:3],
-        lambda: B.layer_fwd(X, W, fwd, bww, out=out[0], saved=saved(), workspace=room)[:1], lambda: bwd(workspace=room)]
+        lambda: B.layer_fwd(X, W, fwd, bww, out=out[0], saved=saved(), workspace=room)[:1], lambda: bwd(workspace=room),
+        lambda: B.layer_step(X, W, G, fwd, bwi, bww, out=list(out))[:3], lambda: bwd(out=out[1:], workspace=room),
+        lambda: bwd(out=list(out[1:]), mask=X), lambda: bwd(out=(None, out[2])),
+        lambda: B.layer_bwd(G, W, B.layer_fwd(X, W, fwd, bww)[1], K, None, bww, out=(None, out[2])),
+        lambda: B.conv_bwd(Gc, Wc, B.conv_fwd(act, 3, 3, Wc, fwd, bww)[1], list(act.shape), 3, 3, bwi, bww)]
     REFUSED = [
         lambda: B.gemm(0, X, W, M, K, N, _prm(n=48)), lambda: B.layer_step(X, W, G, fwd, bwi, _prm(s=0)),
         lambda: B.conv_fwd(act, 2, 2, new(256, 64), fwd, bww), lambda: B.quantize(X, 1, 64, B.Operand(9)),
         lambda: B.gemm(0, X, W, M, K, N, fwd, workspace=small), lambda: B.layer_step(X, W, G, fwd, bwi, bww, workspace=small),
         lambda: B.layer_fwd(X, W, fwd, bww, saved=small), lambda: bwd(workspace=room[4:]),
-        lambda: B.gemm(0, X, W, M, K, N, fwd, workspace=room[1:]), lambda: B.layer_fwd(X, W, fwd, bww, saved=saved()[8:])]
+        lambda: B.gemm(0, X, W, M, K, N, fwd, workspace=room[1:]), lambda: B.layer_fwd(X, W, fwd, bww, saved=saved()[8:]),
+        lambda: bwd(out=(out[1], None))]
     OTHER = [
         lambda: B.quantize(X, 2, 64, B.Operand()), lambda: B.quantize(X.t(), 1, 64, B.Operand()),
         lambda: B.gemm(0, X, W, M, K, N, _prm(n="64")), lambda: B.layer_step(X, G, W, fwd, bwi, bww),
-        lambda: B.gemm(0, X, W, M, K, N, fwd, out=out[0].half()), lambda: B.layer_step(X, W, G, fwd, bwi, bww, out=list(out))[:3]]
+        lambda: B.gemm(0, X, W, M, K, N, fwd, out=out[0].half()), lambda: B.layer_step(X, W, G, fwd, bwi, bww, out=iter(out))[:3],
+        lambda: bwd(out=(None, out[2]), mask=X), lambda: bwd(out=out)]
     return [(c, tuple) for c in NATIVE] + [(c, int) for c in REFUSED] + [(c, type(None)) for c in OTHER]
 
 
@@ -121,11 +127,11 @@ def _same(here, there):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("k", range(34))
+@pytest.mark.parametrize("k", range(43))
 def test_same_as_through_ctypes(k, monkeypatch):
     B.load()
     calls = _calls()
-    assert len(calls) == 34
+    assert len(calls) == 43
     call, returns = calls[k]
     watched = _Watched(B._host)
     monkeypatch.setattr(B, "_host", watched)
