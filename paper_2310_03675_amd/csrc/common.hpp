@@ -111,7 +111,12 @@ struct DualArgs {
     // holds act[b, c, y + ty - ph, x + tx - pw].  rows = batch*H*W, cols = C*kh*kw.
     int conv;
     int cC, cH, cW, ckh, ckw;
-    int pPH, pPW, pCN;      // the part of the activation a 64 x 64 tile reads: rows, row length, channels
+    int pPH, pPW, pCN;      // the part of the activation a 64 x 64 tile reads: rows, row length in LDS, channels
+    int pCP, pLead;         // distance of its channels in LDS; of a row's first pixel from the row's start
+    uint32_t pPieces, pPerCh, pPerRow;       // 16-byte pieces of the part, of a channel, of a row (0: pixel by pixel)
+    uint32_t pInvCh, pInvRow;                // 2^20 / pPerCh and / pPerRow, rounded up
+    int pSteps;             // tiles a wave of pass 2 takes one after the other
+    Divisor dHW, dW, dTaps, dkw;
 };
 
 struct GemmArgs {

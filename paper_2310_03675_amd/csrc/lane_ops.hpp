@@ -187,9 +187,13 @@ constexpr uint32_t pack_bias(int fields, int width)
 // eight words -> eight two's-complement nibbles (low nibble = first code)
 __device__ __forceinline__ uint32_t pack_nibbles(const uint32_t w[8])
 {
-    uint32_t acc = w[0];
+    // (from the last code on: one shift-and-add each, which the compiler makes two of otherwise)
+    uint32_t acc = w[7];
 #pragma unroll
-    for (int i = 1; i < 8; ++i) acc += w[i] << (4 * i);
+    for (int i = 6; i >= 0; --i) {
+        acc = (acc << 4) + w[i];
+        asm("" : "+v"(acc));
+    }
     return (acc - pack_bias(8, 4)) ^ 0x88888888u;
 }
 

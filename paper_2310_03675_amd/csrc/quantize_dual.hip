@@ -23,7 +23,8 @@
 // (-1)^popcount(lane & 7) after axis 1 and (-1)^(lane bit 3) after axis 0, is
 // folded into the reciprocal step the lane quantizes with.
 // The axis-1 transform is done row by row on copies (eight values at a time),
-// the axis-0 transform then in place.  No LDS is involved.
+// the axis-0 transform then in place.  No LDS is involved.  (Pass 2 of a convolution source is another matter,
+// see below.)
 // Requires rows and cols multiples of 64 and block orders up to 64.  Codes of up to
 // 4 bits are packed two per byte; the WIDE instances write codes of 5 to 8 bits, one
 // per byte (both axes of a tensor, and all tensors of a launch, on the same side).
@@ -40,6 +41,23 @@ using namespace lanes;
 
 constexpr int kThreads = 256;
 constexpr int kTile = 64;
+
+constexpr int kPieces = 7;               // 16-byte pieces of a patch per lane, in flight (four workgroups' patches fill the LDS)
+
+// floats of a wave's LDS that hold the patch
+__host__ __device__ inline int patch_floats(const DualArgs& q)
+{
+    return q.pPerRow ? (int)((q.pPieces + 64 * kPieces - 1) / (64 * kPieces)) * 256 * kPieces : (q.pCN * q.pCP + 3) & ~3;
+}
+
+// LDS operations of one wave are carried out in order; this keeps the compiler from moving reads above the
+// writes of other lanes.
+__device__ __forceinline__ void wave_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 struct Tile {
     float v[2][4][8];        // [h][j][i]
@@ -79,143 +97,143 @@ __device__ __forceinline__ void tile_load(Tile& t, const DualArgs& q, const Dual
 // with coalesced reads, then gathers its 64 x 64 values from there: an element's patch
 // address is (row part of its pixel) + (column part of its channel and tap).
 // The activation is read from HBM about once per pass instead of kh*kw times.
-constexpr int kPatchUnroll = 6;
-
 //
-// Returns whether a value of the patch has its sign bit set (the same in every lane).
-__device__ __forceinline__ bool tile_load_conv(Tile& t, const DualArgs& q, const DualCtx& x,
-                                               int64_t row0, int64_t col0, float* patch, int lane)
+// Rows are padded to whole 16-byte pieces on either side and pieces lie one after the other, so piece u of the
+// patch is the same place of every tile relative to the tile's first: a lane works out its pieces once,
+// and a wave of pass 2 goes through pSteps tiles.  (Working them out for each tile was a quarter of the kernel's vector instructions.)
+struct PatchPieces {
+    int off[kPieces];                    // bytes from the image's element (c_lo, y_first - ph, x_first - lead)
+    int y[kPieces];                      // four times the patch row (far outside for pieces that hold nothing), plus 1 for
+                                         // pieces left of the tile's own columns and 2 for those right of them
+};
+
+struct PatchPlace {                      // of one tile, the same in every lane
+    const float* img;
+    int at, y, c_lo;                     // bytes of (c_lo, y_first - ph, x_first - lead) from `img`; y_first - ph
+    int beside;                          // 1: the tile's columns start an image row, 2: they end one, 3: both
+};
+
+__device__ __forceinline__ void patch_pieces(PatchPieces& p, const DualArgs& q, uint32_t u0, int lane)
+{
+    const int wt = q.cW < kTile ? q.cW : kTile;
+#pragma unroll
+    for (int k = 0; k < kPieces; ++k) {
+        const uint32_t u = u0 + 64 * k + lane;
+        const uint32_t c = (u * q.pInvCh) >> 20, rest = u - c * q.pPerCh;          // (below 2^20 / pPerCh: dual_conv_plan)
+        const uint32_t y = (rest * q.pInvRow) >> 20, x = (rest - y * q.pPerRow) * 4;
+        p.off[k] = 4 * (((int)c * q.cH + (int)y) * q.cW + (int)x);
+        const int beside = (int)x < q.pLead ? 1 : (int)x >= q.pLead + wt ? 2 : 0;
+        p.y[k] = u < q.pPieces && (int)y < q.pPH ? 4 * (int)y + beside : INT_MIN / 2;
+    }
+}
+
+__device__ __forceinline__ PatchPlace patch_place(const DualArgs& q, uint32_t row0, uint32_t col0)
+{
+    PatchPlace a;
+    const int W = q.cW, H = q.cH;
+    const uint32_t b = divide(row0, q.dHW), rem = row0 - b * q.dHW.d;
+    const int y_first = (int)divide(rem, q.dW), x_first = (int)rem - y_first * W;
+    a.c_lo = (int)divide(col0, q.dTaps);
+    a.y = y_first - (q.ckh - 1) / 2;
+    a.img = q.T + (int64_t)b * q.cC * H * W;
+    a.at = 4 * ((a.c_lo * H + a.y) * W + x_first - q.pLead);
+    a.beside = (x_first == 0 ? 1 : 0) | (x_first + kTile >= W ? 2 : 0);
+    return a;
+}
+
+// (what lies outside the image is asked for beyond its end, where a buffer load returns zeros)
+__device__ __forceinline__ void patch_load(float4 (&v)[kPieces], const PatchPieces& p, const PatchPlace& a, const DualArgs& q)
+{
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(a.img), 0, 4 * q.cC * q.cH * q.cW, 0x00020000);
+#pragma unroll
+    for (int k = 0; k < kPieces; ++k) {
+        const bool in = (uint32_t)(p.y[k] + 4 * a.y) < 4u * (uint32_t)q.cH && !(p.y[k] & a.beside);
+        v[k] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, in ? p.off[k] + a.at : -16, 0, 0));
+    }
+}
+
+// Into LDS; returns the values' sign bits, put together.
+__device__ __forceinline__ uint32_t patch_store(const float4 (&v)[kPieces], float* patch, uint32_t u0, int lane)
 {
     uint32_t signs = 0;
-    const int W = q.cW, H = q.cH, C = q.cC, kw = q.ckw, khw = q.ckh * q.ckw;
-    const int ph = (q.ckh - 1) / 2, pw = (kw - 1) / 2;
-    const int PH = q.pPH, PW = q.pPW, CN = q.pCN;
-    int* coltab = reinterpret_cast<int*>(patch + ((CN * PH * PW + 3) & ~3));      // 64 column parts
-
-    // where the tile lies (the same in every lane)
-    const uint32_t m0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)row0);
-    const uint32_t k0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)col0);
-    const uint32_t HW = (uint32_t)(H * W);
-    const uint32_t b = m0 / HW, rem = m0 - b * HW;
-    const int y_first = (int)(rem / (uint32_t)W), x_first = (int)(rem - (uint32_t)y_first * (uint32_t)W);
-    const int c_lo = (int)(k0 / (uint32_t)khw);
-
-    // ---- patch: row r = (channel c_lo + r / PH, image row y_first - ph + r % PH).  The tile's own
-    // columns are whole image rows, or 64 pixels from a multiple of 64 on: four pixels per lane and
-    // load, kPatchUnroll loads in flight (every address is clamped into the activation, so no load
-    // is conditional).  (One pixel per lane and load cost 64 times the twelve instructions of its
-    // address and border test, a third of the kernel: 262144 x 576 from 256 x 64 x 32 x 32, pass 1
-    // 143 -> 91 us, pass 2 180 -> 135 us.)
-    const int wt = W < kTile ? W : kTile;
-    const int rows_total = CN * PH;
-    const float* img = q.T + (int64_t)b * C * H * W;
-    // (r / PH for r below 2^20 / PH: dual_conv_plan)
-    const uint32_t inv_ph = ((1u << 20) + (uint32_t)PH - 1) / (uint32_t)PH;
-    auto source = [&](int r, int& off) {          // whether row r lies in the activation, and where
-        const int c_rel = (int)(((uint32_t)r * inv_ph) >> 20);
-        const int gy = y_first - ph + r - c_rel * PH, c = c_lo + c_rel;
-        const int gyc = gy < 0 ? 0 : (gy >= H ? H - 1 : gy), cc = c >= C ? C - 1 : c;
-        off = (cc * H + gyc) * W;
-        return gy == gyc && c < C;
-    };
-    if (wt >= 4) {
-        const int log2u = 29 - __builtin_clz((unsigned)wt);      // (wt is a power of two) units of four pixels per row
-        const int units = rows_total << log2u;
-        for (int u0 = 0; u0 < units; u0 += 64 * kPatchUnroll) {
-            float4 v[kPatchUnroll];
-            int dst[kPatchUnroll];
 #pragma unroll
-            for (int k = 0; k < kPatchUnroll; ++k) {
-                const int u = u0 + 64 * k + lane, r = u >> log2u, xq = (u - (r << log2u)) * 4;
-                int off;
-                const bool in = source(r, off);
-                v[k] = *reinterpret_cast<const float4*>(img + off + x_first + xq);
-                if (!in) v[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                dst[k] = u < units ? r * PW + pw + xq : -1;
-            }
-#pragma unroll
-            for (int k = 0; k < kPatchUnroll; ++k) {
-                if (dst[k] < 0) continue;
-                signs |= (as_u(v[k].x) | as_u(v[k].y)) | (as_u(v[k].z) | as_u(v[k].w));
-                float* d = patch + dst[k];
-                d[0] = v[k].x; d[1] = v[k].y; d[2] = v[k].z; d[3] = v[k].w;
-            }
-        }
+    for (int k = 0; k < kPieces; ++k) {
+        signs |= (as_u(v[k].x) | as_u(v[k].y)) | (as_u(v[k].z) | as_u(v[k].w));
+        *reinterpret_cast<float4*>(patch + 4 * (u0 + 64 * k + lane)) = v[k];
     }
-    // ---- the window's columns beside them (all columns of images one or two pixels wide): zeros
-    // next to a whole image row, else pixels one by one
-    const int n_side = wt >= 4 ? kw - 1 : PW;
-    if (n_side) {
-        const uint32_t inv_ns = ((1u << 20) + (uint32_t)n_side - 1) / (uint32_t)n_side;
-        for (int e = lane; e < rows_total * n_side; e += 64) {
-            const int r = (int)(((uint32_t)e * inv_ns) >> 20), k = e - r * n_side;
-            const int px = wt >= 4 && k >= pw ? wt + k : k, gx = x_first - pw + px;
-            float v = 0.0f;
-            if (gx >= 0 && gx < W) {
-                int off;
-                const bool in = source(r, off);
-                v = img[off + gx];
-                if (!in) v = 0.0f;
-            }
-            signs |= as_u(v);
-            patch[r * PW + px] = v;
-        }
-    }
-    // ---- column parts of the tile's 64 columns, one per lane
-    {
-        const uint32_t k = k0 + (uint32_t)lane;
-        const uint32_t c = k / (uint32_t)khw, tap = k - c * (uint32_t)khw;
-        const uint32_t ty = tap / (uint32_t)kw, tx = tap - ty * (uint32_t)kw;
-        coltab[lane] = ((int)c - c_lo) * PH * PW + (int)ty * PW + (int)tx;
-    }
-    // LDS operations of one wave are carried out in order; the fence keeps the compiler
-    // from moving the reads below above the writes of other lanes
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    return signs;
+}
 
-    // ---- gather: pixel 8*rg + i of the tile is (image row off / Wt, position off % Wt),
-    // Wt = min(W, 64), a power of two.  With Wt >= 8 the lane's eight pixels are neighbours
-    // in one image row: eight consecutive patch words per column.
-    const int wt_shift = (W >= 64) ? 6 : (31 - __builtin_clz((unsigned)W));
-    if (wt_shift >= 3) {
-        const int off = x.rg * 8;
-        const float* base = patch + (off >> wt_shift) * PW + (off & ((1 << wt_shift) - 1));
+// The patch pixel by pixel: images narrower than four pixels and patches that no plan with pieces fits.
+__device__ __forceinline__ uint32_t patch_by_pixel(const DualArgs& q, const PatchPlace& a, float* patch, int lane)
+{
+    uint32_t signs = 0;
+    const int total = q.pCN * q.pPH * q.pPW, x_first = a.at / 4 + q.pLead - (a.c_lo * q.cH + a.y) * q.cW;
+    for (int e = lane; e < total; e += 64) {
+        const int r = e / q.pPW, x = x_first - q.pLead + e - r * q.pPW, c = a.c_lo + r / q.pPH, y = a.y + r % q.pPH;
+        const bool in = x >= 0 && x < q.cW && y >= 0 && y < q.cH && c < q.cC;
+        const float v = in ? a.img[((int64_t)c * q.cH + y) * q.cW + x] : 0.0f;
+        signs |= as_u(v);
+        patch[e] = v;
+    }
+    return signs;
+}
+
+// Column parts of the tile's 64 columns, one per lane, in bytes.
+__device__ __forceinline__ void column_table(const DualArgs& q, int c_lo, uint32_t col0, float* patch, int lane)
+{
+    int* coltab = reinterpret_cast<int*>(patch + patch_floats(q));
+    const uint32_t k = col0 + (uint32_t)lane;
+    const uint32_t c = divide(k, q.dTaps), tap = k - c * q.dTaps.d;
+    const uint32_t ty = divide(tap, q.dkw), tx = tap - ty * q.dkw.d;
+    coltab[lane] = 4 * (((int)c - c_lo) * q.pCP + (int)ty * q.pPW + (int)tx + q.pLead - (q.ckw - 1) / 2);
+}
+
+__device__ __forceinline__ const int* column_parts(const DualArgs& q, const float* patch)
+{
+    return reinterpret_cast<const int*>(patch + patch_floats(q));
+}
+
+__device__ __forceinline__ const float* at_byte(const float* p, int bytes)
+{
+    return reinterpret_cast<const float*>(reinterpret_cast<const char*>(p) + bytes);
+}
+
+// The tile of pass 1 from the patch: pixel 8*rg + i of the tile is (image row off / Wt, position off % Wt),
+// Wt = min(W, 64), a power of two.  With Wt >= 8 the lane's eight pixels are neighbours
+// in one image row: eight consecutive patch words per column.
+__device__ __forceinline__ void tile_gather(Tile& t, const DualArgs& q, const float* patch, int lane)
+{
+    const int* coltab = column_parts(q, patch);
+    int shift = q.cW >= kTile ? 6 : 31 - __builtin_clz((unsigned)q.cW), PW = q.pPW;
+    const int off = lane & ~7, cg = lane & 7;
+    if (shift >= 3) {
+        const float* base = patch + (off >> shift) * PW + (off & ((1 << shift) - 1));
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const int4 cp = *reinterpret_cast<const int4*>(coltab + 32 * h + 4 * x.cg);
-            const float* p0 = base + cp.x;
-            const float* p1 = base + cp.y;
-            const float* p2 = base + cp.z;
-            const float* p3 = base + cp.w;
+            const int4 cp = *reinterpret_cast<const int4*>(coltab + 32 * h + 4 * cg);
+            const float* p[4] = {at_byte(base, cp.x), at_byte(base, cp.y), at_byte(base, cp.z), at_byte(base, cp.w)};
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                t.v[h][0][i] = p0[i];
-                t.v[h][1][i] = p1[i];
-                t.v[h][2][i] = p2[i];
-                t.v[h][3][i] = p3[i];
-            }
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) t.v[h][j][i] = p[j][i];
         }
     } else {
-        int rowpart[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int off = x.rg * 8 + i;
-            rowpart[i] = (off >> wt_shift) * PW + (off & ((1 << wt_shift) - 1));
-        }
+        asm volatile("" : "+s"(PW), "+s"(shift));
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const int4 cp = *reinterpret_cast<const int4*>(coltab + 32 * h + 4 * x.cg);
+            const int4 cp = *reinterpret_cast<const int4*>(coltab + 32 * h + 4 * cg);
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                t.v[h][0][i] = patch[rowpart[i] + cp.x];
-                t.v[h][1][i] = patch[rowpart[i] + cp.y];
-                t.v[h][2][i] = patch[rowpart[i] + cp.z];
-                t.v[h][3][i] = patch[rowpart[i] + cp.w];
+                const float* p = patch + ((off + i) >> shift) * PW + ((off + i) & ((1 << shift) - 1));
+                t.v[h][0][i] = *at_byte(p, cp.x);
+                t.v[h][1][i] = *at_byte(p, cp.y);
+                t.v[h][2][i] = *at_byte(p, cp.z);
+                t.v[h][3][i] = *at_byte(p, cp.w);
             }
         }
     }
-    return __builtin_amdgcn_ballot_w64((int)signs < 0) != 0;
 }
 
 // Random bits of stochastic rounding for the lane's elements of one tile row: four
@@ -573,14 +591,149 @@ __device__ __forceinline__ void dual_codes(Tile& t, const DualCtx& x, int64_t ro
     col_codes<ST_COL, WIDE>(t, x, row0, col0);
 }
 
+// ---- pass 2 of a convolution source: every lane has a whole line of its wave's tile, first a row (64 columns),
+// then a column (64 rows), so that both transforms and the packing stay inside the lane.  The patch is in LDS
+// anyway, and gathering it twice is cheaper than pairing lanes: an addition of two registers takes two
+// cycles a wave here, one with a lane move four and a lane swap eight (measured at four waves per SIMD).
+// Pass 2 of 262144 x 576 from 256 x 64 x 32 x 32 136 -> 102 us, of 32768 x 320 from 256 x 64 x 1 x 128 18.7 -> 17.1.
+// What bounds it is still vector issue (1400 instructions a tile), with the LDS busy 40 % of the time.  Not for
+// an ordinary source: its tile would have to go through LDS too, 17 KB a wave, which leaves two waves per SIMD
+// (the 65536 x 1152 x 128 step 259 -> 265 us).
+
+// Lane's row (AXIS 1) or column (AXIS 0) of the tile.
+template <int AXIS>
+__device__ __forceinline__ void line_gather(float (&v)[kTile], const DualArgs& q, const float* patch, int lane)
+{
+    const int* coltab = column_parts(q, patch);
+    const int PW = q.pPW, shift = q.cW >= kTile ? 6 : 31 - __builtin_clz((unsigned)q.cW), mask = (1 << shift) - 1;
+    if (AXIS == 1) {
+        const float* base = patch + (lane >> shift) * PW + (lane & mask);
+#pragma unroll
+        for (int k = 0; k < kTile; k += 4) {
+            const int4 cp = *reinterpret_cast<const int4*>(coltab + k);
+            v[k] = *at_byte(base, cp.x); v[k + 1] = *at_byte(base, cp.y);
+            v[k + 2] = *at_byte(base, cp.z); v[k + 3] = *at_byte(base, cp.w);
+        }
+    } else {
+        const float* base = at_byte(patch, coltab[lane]);
+        if (shift >= 3) {
+#pragma unroll
+            for (int k = 0; k < kTile; k += 8) {
+                const float* p = base + ((k >> shift) * PW + (k & mask));
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[k + i] = p[i];
+            }
+        } else {
+            int pitch = PW, sh = shift;
+            asm volatile("" : "+s"(pitch), "+s"(sh));     // (keeps 64 addresses of narrow images out of the common path)
+#pragma unroll
+            for (int k = 0; k < kTile; ++k) v[k] = base[(k >> sh) * pitch + (k & ((1 << sh) - 1))];
+        }
+    }
+}
+
+__device__ __forceinline__ void butterfly64(float (&v)[kTile], int log2n)
+{
+#pragma unroll
+    for (int s = 0; s < 6; ++s)
+        if (log2n > s) {
+#pragma unroll
+            for (int k = 0; k < kTile; ++k)
+                if (!(k & (1 << s))) {
+                    const float a = v[k], c = v[k + (1 << s)];
+                    v[k] = a + c;
+                    v[k + (1 << s)] = a - c;
+                }
+        }
+}
+
+// Codes of a line, 32 (WIDE: 64) consecutive bytes.  `random(g, u)` gives the random 16 bits of its elements 8g .. 8g+7.
+// They leave by way of LDS, neighbouring lanes with neighbouring pieces of a line.
+template <bool STOCH, bool WIDE, typename Random>
+__device__ __forceinline__ void line_codes(const float (&v)[kTile], float inv, float qmin, float qmax, uint8_t* dst, int64_t pitch,
+                                           uint4* words, int lane, Random random)
+{
+    constexpr int kPieces = WIDE ? 4 : 2;        // 16-byte pieces of a line
+    uint4 mine[kPieces];
+    const float magic = kMagic + (WIDE ? 128.0f : 8.0f);
+    uint32_t out[4];
+#pragma unroll
+    for (int g = 0; g < 8; ++g) {
+        uint32_t u[8] = {}, cw[8];
+        if (STOCH) random(g, u);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) cw[i] = code_word<STOCH>(v[8 * g + i], inv, qmin, qmax, magic, u[i]);
+        if constexpr (WIDE) {
+            out[2 * (g & 1)] = pack_bytes(cw);
+            out[2 * (g & 1) + 1] = pack_bytes(cw + 4);
+            if (g & 1) mine[g >> 1] = make_uint4(out[0], out[1], out[2], out[3]);
+        } else {
+            out[g & 3] = pack_nibbles(cw);
+            if ((g & 3) == 3) mine[g >> 2] = make_uint4(out[0], out[1], out[2], out[3]);
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < kPieces; ++k) words[lane * kPieces + k] = mine[k];
+    wave_order();
+#pragma unroll
+    for (int k = 0; k < kPieces; ++k) {
+        const int at = 64 * k + lane, line = at / kPieces;
+        *reinterpret_cast<uint4*>(dst + line * pitch + 16 * (at % kPieces)) = words[at];
+    }
+    wave_order();
+}
+
+// Both code sets of a tile.  `piece`: the wave's LDS: patch, column table, codes on their way out.
+template <bool ST_ROW, bool ST_COL, bool WIDE, bool N64>
+__device__ __forceinline__ void line_tile(const DualArgs& q, const Scaling& s_row, const Scaling& s_col, int64_t row0,
+                                          int64_t col0, float* piece, int lane)
+{
+    const int half = WIDE ? 0 : 1;
+    uint4* const words = reinterpret_cast<uint4*>(piece + patch_floats(q) + kTile);
+    float v[kTile];
+    line_gather<1>(v, q, piece, lane);
+    butterfly64(v, N64 ? 6 : q.log2n_row);
+    {
+        const int64_t row = row0 + lane;
+        const uint64_t blk = (uint64_t)(row * q.cols + col0) >> 3;
+        line_codes<ST_ROW, WIDE>(v, s_row.inv, (float)(-(1 << (q.b_row - 1))), (float)((1 << (q.b_row - 1)) - 1),
+                                 q.codes_row + ((row0 * q.cols + col0) >> half), q.cols >> half, words, lane, [&](int g, uint32_t (&u)[8]) {
+                                     uint32_t r[4];
+                                     philox4x32_10((uint32_t)(blk + g), (uint32_t)((blk + g) >> 32), q.tid_row, 0u,
+                                                   q.seed_row_lo, q.seed_row_hi, r);
+#pragma unroll
+                                     for (int i = 0; i < 8; ++i) u[i] = (r[i >> 1] >> (16 * (i & 1))) & 0xFFFFu;
+                                 });
+    }
+    line_gather<0>(v, q, piece, lane);
+    butterfly64(v, N64 ? 6 : q.log2n_col);
+    line_codes<ST_COL, WIDE>(v, s_col.inv, (float)(-(1 << (q.b_col - 1))), (float)((1 << (q.b_col - 1)) - 1),
+                             q.codes_col + ((col0 * q.rows + row0) >> half), q.rows >> half, words, lane, [&](int g, uint32_t (&u)[8]) {
+                                 // eight lanes need the same eight blocks, of rows 8g .. 8g+7 at their columns: each
+                                 // makes one, and they are handed over through LDS
+                                 const uint64_t blk = (uint64_t)((row0 + 8 * g + (lane & 7)) * q.cols + col0 + (lane & ~7)) >> 3;
+                                 uint32_t r[4];
+                                 philox4x32_10((uint32_t)blk, (uint32_t)(blk >> 32), q.tid_col, 0u, q.seed_col_lo,
+                                               q.seed_col_hi, r);
+                                 words[lane] = make_uint4(r[0], r[1], r[2], r[3]);
+                                 wave_order();
+                                 const uint16_t* mine = reinterpret_cast<const uint16_t*>(words + (lane & ~7)) + (lane & 7);
+#pragma unroll
+                                 for (int i = 0; i < 8; ++i) u[i] = mine[8 * i];
+                                 wave_order();
+                             });
+}
+
 // One launch covers up to kMaxBatch tensors: the workgroups of tensor k are
 // [first[k], first[k+1]) of a one-dimensional grid, numbered along its columns first.
 // Small tensors (a layer's weights) ride along with a large one instead of paying
 // for a launch of their own.
 struct DualBatch {
     int first[kMaxDualBatch + 1];        // (behind the last tensor: the workgroups of all)
-    int gx[kMaxDualBatch];       // workgroups along the columns
+    Divisor gx[kMaxDualBatch];   // workgroups along the columns
     int WC[kMaxDualBatch];       // waves side by side in a workgroup (1, 2 or 4)
+    int words[kMaxDualBatch];    // dense: pass 1's workgroups, whose maxima stand side by side
+    int steps[kMaxDualBatch];    // convolution sources: tiles a wave takes one after the other
     int lds_per_wave;            // floats of LDS per wave (convolution sources), a multiple of 4
     int dense;                   // the maxima stand side by side (see QMeta)
     int spread;                  // pass 2: every spread-th workgroup of the grid is one of tensor 0 (0: off)
@@ -597,7 +750,8 @@ __device__ __forceinline__ DualArgs whole_args(const DualArgs& x)
                  "s"(q.seed_col_lo), "s"(q.seed_col_hi), "s"(q.meta_row), "s"(q.meta_col), "s"(q.codes_row), "s"(q.codes_col),
                  "s"(q.scale_row_out), "s"(q.scale_col_out));
     if constexpr (CONV)
-        asm volatile("" ::"s"(q.conv), "s"(q.cC), "s"(q.cH), "s"(q.cW), "s"(q.ckh), "s"(q.ckw), "s"(q.pPH), "s"(q.pPW), "s"(q.pCN));
+        asm volatile("" ::"s"(q.conv), "s"(q.cC), "s"(q.cH), "s"(q.cW), "s"(q.ckh), "s"(q.ckw), "s"(q.pPH), "s"(q.pPW), "s"(q.pCN), "s"(q.pCP), "s"(q.pLead),
+                     "s"(q.pPieces), "s"(q.pPerCh), "s"(q.pPerRow), "s"(q.pInvCh), "s"(q.pInvRow), "s"(q.dHW.mul), "s"(q.dHW.sh1), "s"(q.dHW.sh2));
     return q;
 }
 
@@ -630,20 +784,103 @@ __device__ __forceinline__ int batch_order(const DualBatch& b)
 constexpr int kRoundPerTensor = 4;
 constexpr int kRoundWide = 8;        // added to ROUND: codes of 5 to 8 bits, one per byte
 
+// A convolution source: the workgroups' tiles, four rows of tiles high, are numbered strip by strip, and a
+// workgroup takes one of them in pass 1, `steps` in a row in pass 2; its waves lie above each other.
+template <bool QUANT, int ROUND, bool N64>
+__device__ __forceinline__ void conv_block(const DualBatch& b, int k, int vb, float (*red)[2], float* lds)
+{
+    constexpr bool kStRow = (ROUND & 1) != 0, kStCol = (ROUND & 2) != 0, kWide = (ROUND & kRoundWide) != 0;
+    const DualArgs q = whole_args<true>(b.t[k]);
+    const int count = b.first[k + 1] - b.first[k];
+    int local = vb - b.first[k];
+    if (QUANT) local = count - 1 - local;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    float* const piece = lds + wave * b.lds_per_wave;
+    const int dense = b.dense ? b.words[k] : 0;
+    Maxima max_row{}, max_col{};
+    if (QUANT) {
+        max_row = fetch_maxima(q.meta_row, dense);
+        max_col = fetch_maxima(q.meta_col, dense);
+    }
+    const uint32_t strips = b.gx[k].d, row_tiles = (uint32_t)(q.rows / kTile);
+    const uint32_t first = (uint32_t)local * (uint32_t)b.steps[k];
+    uint32_t by = divide(first, b.gx[k]), strip = first - by * strips;
+    const bool once = q.pPerRow && q.pPieces <= 64 * kPieces;       // (the lane's pieces are the same ones in every tile)
+    PatchPieces pieces;
+    auto live = [&](uint32_t y) { return 4 * y + (uint32_t)wave < row_tiles; };
+    if (once) patch_pieces(pieces, q, 0, lane);
+    Scaling s_row{}, s_col{};
+    if (QUANT) {
+        s_row = scaling_of(max_row, q.meta_row, q.clip_row, q.b_row, dense);
+        s_col = scaling_of(max_col, q.meta_col, q.clip_col, q.b_col, dense);
+        if (local == 0 && threadIdx.x == 0) {
+            q.meta_row->scale = s_row.scale;
+            q.meta_col->scale = s_col.scale;
+            if (q.scale_row_out) *q.scale_row_out = s_row.scale;
+            if (q.scale_col_out) *q.scale_col_out = s_col.scale;
+        }
+    }
+    DualCtx x;
+    if (!QUANT) dual_setup<N64>(x, q, lane);
+    float amax_row = 0.0f, amax_col = 0.0f;
+    const int steps = QUANT ? b.steps[k] : 1;
+    for (int step = 0; step < steps && live(by); ++step) {
+        int l = lane;
+        asm volatile("" : "+v"(l));      // (what follows from the lane is worked out where it is used, not kept for the loop)
+        const int64_t row0 = (int64_t)(4 * by + wave) * kTile, col0 = (int64_t)strip * kTile;
+        const PatchPlace at = patch_place(q, (uint32_t)row0, (uint32_t)col0);
+        uint32_t signs = 0;
+        if (once) {
+            float4 v[kPieces];
+            patch_load(v, pieces, at, q);
+            signs = patch_store(v, piece, 0, l);
+        } else if (q.pPerRow) {
+            for (uint32_t u = 0; u < q.pPieces; u += 64 * kPieces) {
+                PatchPieces p;
+                float4 v[kPieces];
+                patch_pieces(p, q, u, l);
+                patch_load(v, p, at, q);
+                signs |= patch_store(v, piece, u, l);
+            }
+        } else {
+            signs = patch_by_pixel(q, at, piece, l);
+        }
+        column_table(q, at.c_lo, (uint32_t)col0, piece, l);
+        wave_order();
+        if (++strip == strips) { strip = 0; ++by; }
+        if (QUANT) {
+            line_tile<kStRow, kStCol, kWide, N64>(q, s_row, s_col, row0, col0, piece, l);
+        } else {
+            const bool negative = __builtin_amdgcn_ballot_w64((int)signs < 0) != 0;
+            Tile t;
+            tile_gather(t, q, piece, l);
+            if (!negative && x.log2n_row >= 3 && x.log2n_col >= 3) sums_absmax(t, x, amax_row, amax_col);
+            else dual_absmax(t, x, row0, col0, amax_row, amax_col);
+            wave_order();
+        }
+    }
+    if (!QUANT) record_max2(amax_row, amax_col, q.meta_row, q.meta_col, red, local, b.dense);
+}
+
 template <bool QUANT, int ROUND, bool N64, bool CONV>
 __device__ __forceinline__ void dual_block(const DualBatch& b, int k, int vb, float (*red)[2], float* lds)
 {
-    const DualArgs q = whole_args<CONV>(b.t[k]);
+    if (CONV && b.t[k].conv) {
+        conv_block<QUANT, ROUND, N64>(b, k, vb, red, lds);
+        return;
+    }
+    const DualArgs q = whole_args<false>(b.t[k]);
     const int count = b.first[k + 1] - b.first[k];
     // pass 2 walks a tensor from its end to its start: it begins with what pass 1
     // read last, which is most likely still in the memory-side cache
     int local = vb - b.first[k];
     if (QUANT) local = count - 1 - local;
-    const int gx = b.gx[k], WC = b.WC[k];
-    const int64_t by = local / gx, bx = local - (local / gx) * gx;
+    const int WC = b.WC[k];
+    const uint32_t by32 = divide((uint32_t)local, b.gx[k]);
+    const int64_t by = by32, bx = (uint32_t)local - by32 * b.gx[k].d;
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int wc = wave % WC, wr = wave / WC, WR = 4 / WC;
+    const int log2wc = WC >> 1, wc = wave & (WC - 1), wr = wave >> log2wc, WR = 4 >> log2wc;      // (WC is 1, 2 or 4)
     const int64_t col0 = (bx * WC + wc) * kTile;
     const int64_t row0 = (by * WR + wr) * kTile;
     // rows % 64 == cols % 64 == 0: a tile is entirely inside the tensor or entirely outside
@@ -651,18 +888,14 @@ __device__ __forceinline__ void dual_block(const DualBatch& b, int k, int vb, fl
 
     DualCtx x;
     dual_setup<N64>(x, q, lane);
-    const int dense = b.dense ? count : 0;
+    const int dense = b.dense ? b.words[k] : 0;
     Maxima max_row{}, max_col{};         // (on their way before the tile)
     if (QUANT) {
         max_row = fetch_maxima(q.meta_row, dense);
         max_col = fetch_maxima(q.meta_col, dense);
     }
     Tile t;
-    bool signs = true;                   // (of an ordinary source nobody asks: its passes wait for memory)
-    if (live) {
-        if (CONV && q.conv) signs = tile_load_conv(t, q, x, row0, col0, lds + wave * b.lds_per_wave, lane);
-        else tile_load(t, q, x, row0, col0);
-    }
+    if (live) tile_load(t, q, x, row0, col0);
     if (QUANT) {
         const Scaling s_row = scaling_of(max_row, q.meta_row, q.clip_row, q.b_row, dense);
         const Scaling s_col = scaling_of(max_col, q.meta_col, q.clip_col, q.b_col, dense);
@@ -670,14 +903,13 @@ __device__ __forceinline__ void dual_block(const DualBatch& b, int k, int vb, fl
         if (live) dual_codes<(ROUND & 1) != 0, (ROUND & 2) != 0, (ROUND & kRoundWide) != 0>(t, x, row0, col0);
     } else {
         float amax_row = 0.0f, amax_col = 0.0f;
-        if (CONV && !signs && x.log2n_row >= 3 && x.log2n_col >= 3) sums_absmax(t, x, amax_row, amax_col);
-        else if (live) dual_absmax(t, x, row0, col0, amax_row, amax_col);
+        if (live) dual_absmax(t, x, row0, col0, amax_row, amax_col);
         record_max2(amax_row, amax_col, q.meta_row, q.meta_col, red, local, b.dense);
     }
 }
 
 template <bool QUANT, int ROUND, bool N64, bool CONV>
-__global__ __launch_bounds__(kThreads) void fwht_dual_kernel(DualBatch b, AnyBatch ride)
+__global__ __launch_bounds__(kThreads, CONV ? 4 : 1) void fwht_dual_kernel(DualBatch b, AnyBatch ride)
 {
     __shared__ float red[kThreads / kWave][2];
     extern __shared__ __attribute__((aligned(16))) float lds[];      // CONV: one patch per wave; riders' exchange
@@ -700,6 +932,9 @@ __global__ __launch_bounds__(kThreads) void fwht_dual_kernel(DualBatch b, AnyBat
     }
 }
 
+// floats of LDS of a wave of pass 2: patch, column table, codes on their way out
+int conv_floats(const DualArgs& q) { return patch_floats(q) + kTile + (q.b_row > 4 ? 16 : 8) * kTile; }
+
 bool all_order_64(const DualArgs* qs, int n)
 {
     for (int k = 0; k < n; ++k)
@@ -711,10 +946,11 @@ bool all_order_64(const DualArgs* qs, int n)
 int waves_across(const DualArgs& q)
 {
     const int64_t strips = q.cols / kTile;
+    if (q.conv) return 1;
     return (strips % 4 == 0) ? 4 : (strips % 2 == 0) ? 2 : 1;
 }
 
-bool make_batch(const DualArgs* qs, int n, bool dense, const AnyBatch* ride, DualBatch* b)
+bool make_batch(const DualArgs* qs, int n, bool dense, const AnyBatch* ride, bool quant, DualBatch* b)
 {
     if (n < 1 || n > kMaxDualBatch) return false;
     b->dense = dense ? 1 : 0;
@@ -723,15 +959,18 @@ bool make_batch(const DualArgs* qs, int n, bool dense, const AnyBatch* ride, Dua
     for (int k = 0; k < n; ++k) {
         const DualArgs& q = qs[k];
         const int WC = waves_across(q);
-        const int64_t gx = q.cols / kTile / WC, wgs = dual_workgroups(q);
+        const int64_t gx = q.cols / kTile / WC, tiles = dual_workgroups(q);
+        const int64_t steps = q.conv && quant ? q.pSteps : 1, wgs = (tiles + steps - 1) / steps;
         b->t[k] = q;
         if (q.conv) {
-            const int need = ((q.pCN * q.pPH * q.pPW + 3) & ~3) + kTile;
+            const int need = quant ? conv_floats(q) : patch_floats(q) + kTile;
             if (need > lds) lds = need;
         }
         b->first[k] = (int)total;
-        b->gx[k] = (int)gx;
+        b->gx[k] = make_divisor((uint32_t)gx);
         b->WC[k] = WC;
+        b->words[k] = (int)tiles;
+        b->steps[k] = (int)steps;
         total += wgs;
         if (total >= ((int64_t)1 << 30)) return false;
     }
@@ -771,7 +1010,30 @@ bool dual_conv_plan(DualArgs* q)
     q->pPH = (row_run ? 1 : kTile / W) + kh - 1;
     q->pPW = (row_run ? kTile : W) + kw - 1;
     q->pCN = (kTile - 1) / (kh * kw) + 2;
-    return q->pCN * q->pPH * q->pPW <= kMaxPatchFloats;
+    if (q->pCN * q->pPH * q->pPW > kMaxPatchFloats) return false;
+    q->dHW = make_divisor((uint32_t)(H * W)); q->dW = make_divisor((uint32_t)W);
+    q->dTaps = make_divisor((uint32_t)(kh * kw)); q->dkw = make_divisor((uint32_t)kw);
+    q->pLead = (kw - 1) / 2;
+    q->pCP = q->pPH * q->pPW;
+    q->pPieces = q->pPerCh = q->pPerRow = q->pInvCh = q->pInvRow = 0;
+    // In pieces where a row is a whole number of them and one image is addressed with 31 bits.  Seven pieces behind
+    // every channel put the columns of a tile on different banks (two or three of 64 lanes on one, up to eight without
+    // them); left out where they make the patch longer than a lane's pieces in flight.
+    const int wt = row_run ? kTile : W, lead = (q->pLead + 3) & ~3;
+    if (W >= 4 && (int64_t)q->cC * H * W < ((int64_t)1 << 29)) {
+        const uint32_t per_row = (uint32_t)(wt + 2 * lead) / 4, bare = per_row * (uint32_t)q->pPH;
+        const uint32_t per_ch = bare + ((bare + 7) * (uint32_t)q->pCN <= 64u * kPieces ? 7 : 0);
+        q->pLead = lead; q->pPW = 4 * (int)per_row; q->pCP = 4 * (int)per_ch;
+        q->pPieces = per_ch * (uint32_t)q->pCN; q->pPerCh = per_ch; q->pPerRow = per_row;
+        q->pInvCh = ((1u << 20) + per_ch - 1) / per_ch;
+        q->pInvRow = ((1u << 20) + per_row - 1) / per_row;
+    }
+    // pass 2: as many tiles a wave as make one round of the chip's workgroups
+    const int64_t tiles = q->cols / kTile * ((q->rows / kTile + 3) / 4);
+    int64_t places = (160 << 10) / (4 * (int64_t)sizeof(float) * conv_floats(*q));
+    places = 256 * (places < 1 ? 1 : places > 4 ? 4 : places);
+    q->pSteps = (int)((tiles + places - 1) / places);
+    return true;
 }
 
 bool quantize_dual_eligible(const DualArgs& q)
@@ -797,7 +1059,7 @@ hipError_t launch_dual_pass1(const DualArgs* qs, int n, bool dense, const AnyBat
     static const AnyBatch none{};
     if (!ride) ride = &none;
     DualBatch b;
-    if (!make_batch(qs, n, dense, ride, &b)) return hipErrorInvalidValue;
+    if (!make_batch(qs, n, dense, ride, false, &b)) return hipErrorInvalidValue;
     const int id = n > 1 ? K_DUAL_ABSMAX_BATCH
                          : (qs[0].profile_tag ? K_DUAL_ABSMAX_X + (qs[0].profile_tag - 1) : K_DUAL_ABSMAX);
     ProfileScope ps(id, stream);
@@ -835,7 +1097,7 @@ hipError_t launch_dual_pass2(const DualArgs* qs, int n, bool dense, const AnyBat
     static const AnyBatch none{};
     if (!ride) ride = &none;
     DualBatch b;
-    if (!make_batch(qs, n, dense, ride, &b) || !dual_pass2_batchable(qs, n)) return hipErrorInvalidValue;
+    if (!make_batch(qs, n, dense, ride, true, &b) || !dual_pass2_batchable(qs, n)) return hipErrorInvalidValue;
     bool same = true;
     for (int k = 1; k < n; ++k)
         if (qs[k].st_row != qs[0].st_row || qs[k].st_col != qs[0].st_col) same = false;
@@ -845,7 +1107,8 @@ hipError_t launch_dual_pass2(const DualArgs* qs, int n, bool dense, const AnyBat
     const dim3 grid((unsigned)(b.first[n] + ride->h.total)), block(kThreads);
     const bool n64 = all_order_64(qs, n);
     const size_t lds = launch_lds(b, ride);
-    const bool conv = b.lds_per_wave != 0;
+    bool conv = false;
+    for (int k = 0; k < n; ++k) conv = conv || qs[k].conv;
 #define HDQT_LAUNCH_PASS2(ROUND)                                                                     \
     do {                                                                                            \
         if (conv && n64) hipLaunchKernelGGL((fwht_dual_kernel<true, ROUND, true, true>), grid, block, lds, stream, b, *ride); \
