@@ -102,8 +102,10 @@ typedef struct {
     size_t scaleB;   /* float */
     size_t codesA;   /* packed codes [RA, D] */
     size_t codesB;   /* packed codes [RB, D] */
-    size_t acc;      /* int32 slices of a split contraction (see hdqt_gemm_codes) */
-    size_t total;    /* bytes required */
+    size_t acc;      /* int32 slices of a split contraction, or a large product's codes in
+                        another form (see hdqt_gemm_codes) */
+    size_t total;    /* bytes required; the other form is done without where the workspace
+                        ends before it */
     int64_t RA, RB, D;
     int32_t n_eff;
 } hdqt_ws_layout_t;
@@ -236,7 +238,8 @@ int hdqt_transpose(const float *src, int64_t batch, int64_t rows, int64_t cols, 
  *   (0 for most shapes, then NULL is fine; HDQT_EWORKSPACE without it otherwise).  Few output tiles with a long
  *   contraction are split over workgroups along the contraction; every part
  *   writes its totals (sums of whole clamped tiles, so the result is the same)
- *   to a slice of the workspace and a second pass adds the slices.
+ *   to a slice of the workspace and a second pass adds the slices.  Large products of packed
+ *   codes are faster with three quarters of a byte of workspace per code, and do without.
  */
 size_t hdqt_gemm_codes_workspace_size(int64_t RA, int64_t RB, int64_t D, int64_t s);
 int hdqt_gemm_codes(const void *qA, const void *qB, int bA, int bB, const float *scaleA,

@@ -449,6 +449,15 @@ size_t partial_bytes(int64_t RA, int64_t RB, int64_t D, int64_t s)
     return splits > 1 ? (size_t)splits * (size_t)(RA * RB) * sizeof(int32_t) : 0;
 }
 
+// Bytes that a call does without if it has to, but is faster with: the codes of a large product expanded for the
+// 6-bit matrix instructions.
+size_t expanded_bytes(int64_t RA, int64_t RB, int64_t D, int bA, int bB, int acc_bits, int64_t s)
+{
+    if (!hdqt::gemm_six_shape(RA, RB, D)) return 0;
+    const hdqt::GemmArgs g = plan_gemm(nullptr, nullptr, bA, bB, nullptr, nullptr, RA, RB, D, 1, acc_bits, s, nullptr, nullptr);
+    return hdqt::gemm_six_eligible(g) ? (size_t)hdqt::gemm_six_bytes(g) : 0;
+}
+
 int run_planned_gemm(hdqt::GemmArgs g, void* ws, size_t ws_bytes, hipStream_t stream)
 {
     hipError_t e;
@@ -458,6 +467,10 @@ int run_planned_gemm(hdqt::GemmArgs g, void* ws, size_t ws_bytes, hipStream_t st
         return HDQT_EWORKSPACE;
     if (hdqt::gemm_small_eligible(g)) {
         e = hdqt::launch_gemm_small(&g, 1, stream);
+        return e == hipSuccess ? HDQT_OK : hip_fail(e);
+    }
+    if (hdqt::gemm_six_eligible(g) && ws && (int64_t)ws_bytes >= hdqt::gemm_six_bytes(g)) {
+        e = hdqt::launch_gemm_six(g, ws, stream);
         return e == hipSuccess ? HDQT_OK : hip_fail(e);
     }
     if (g.splits > 1) {
@@ -533,6 +546,12 @@ int run_gemm_codes(const void* qA, const void* qB, int bA, int bB, const float* 
                             workspace, workspace_bytes, static_cast<hipStream_t>(stream));
 }
 
+// What a call needs of a layout's total.
+size_t least_bytes(const hdqt_ws_layout_t& L, const hdqt_params_t* prm)
+{
+    return align_up(L.acc + partial_bytes(L.RA, L.RB, L.D, prm->s) + 256, 256);
+}
+
 int run_gemm(int kind, const float* P, const float* Q, float* out, int64_t M, int64_t K, int64_t N,
              const hdqt_params_t* prm, int32_t* acc_out, void* ws, size_t ws_bytes, void* stream_v,
              uint16_t* out_bf16 = nullptr, const float* mask_src = nullptr)
@@ -541,7 +560,7 @@ int run_gemm(int kind, const float* P, const float* Q, float* out, int64_t M, in
     int rc = hdqt_workspace_layout(kind, M, K, N, prm, &L);
     if (rc) return rc;
     if (!P || !Q || (!out && !out_bf16 && !acc_out)) return HDQT_EINVAL_NULL;
-    if (!ws || ws_bytes < L.total) return HDQT_EWORKSPACE;
+    if (!ws || ws_bytes < least_bytes(L, prm)) return HDQT_EWORKSPACE;
     if (misaligned(P) || misaligned(Q) || misaligned(out) || misaligned(out_bf16) || misaligned(acc_out) ||
         misaligned(ws))
         return HDQT_EALIGN;
@@ -562,7 +581,7 @@ int run_gemm(int kind, const float* P, const float* Q, float* out, int64_t M, in
     set.add(make_quant_args(P, o.a_rows, o.a_cols, o.a_axis, L.n_eff, &prm->A, prm->seed, metaA, codesA, nullptr));
     set.add(make_quant_args(Q, o.b_rows, o.b_cols, o.b_axis, L.n_eff, &prm->B, prm->seed, metaB, codesB, nullptr));
     if ((rc = run_quantize_set(set, metaA, 2 * kMetaBytes, stream))) return rc;
-    return run_planned_gemm(g, base + L.acc, L.total - L.acc, stream);
+    return run_planned_gemm(g, base + L.acc, ws_bytes - L.acc, stream);
 }
 
 
@@ -813,7 +832,9 @@ int hdqt_workspace_layout(int gemm_kind, int64_t M, int64_t K, int64_t N,
     L.codesB = off;
     off = align_up(off + (size_t)(o.RB * hdqt_codes_pitch(o.D, params->B.b)), 256);
     L.acc = off;
-    off = align_up(off + partial_bytes(o.RA, o.RB, o.D, params->s) + 256, 256);
+    const size_t slices = partial_bytes(o.RA, o.RB, o.D, params->s);
+    const size_t expanded = expanded_bytes(o.RA, o.RB, o.D, params->A.b, params->B.b, params->acc_bits, params->s);
+    off = align_up(off + (slices > expanded ? slices : expanded) + 256, 256);
     L.total = off;
     if (layout) *layout = L;
     return HDQT_OK;
@@ -979,7 +1000,10 @@ int hdqt_transpose(const float* src, int64_t batch, int64_t rows, int64_t cols, 
 size_t hdqt_gemm_codes_workspace_size(int64_t RA, int64_t RB, int64_t D, int64_t s)
 {
     if (RA <= 0 || RB <= 0 || D <= 0 || s < 1 || RA >= kMaxDim || RB >= kMaxDim || D >= kMaxDim) return 0;
-    return partial_bytes(RA, RB, D, s);
+    // (the widths are not known here: for packed codes and an accumulator that the expanded form is for)
+    const size_t slices = partial_bytes(RA, RB, D, s), clamped = expanded_bytes(RA, RB, D, 4, 4, 8, s),
+                 plain = expanded_bytes(RA, RB, D, 4, 4, 32, s), expanded = clamped > plain ? clamped : plain;
+    return slices > expanded ? slices : expanded;
 }
 
 int hdqt_gemm_codes(const void* qA, const void* qB, int bA, int bB, const float* scaleA,
@@ -1505,7 +1529,7 @@ int hdqt_gemm_fwd_static(const float* X, const float* W, float* Z, int64_t M, in
     hdqt_ws_layout_t L;
     const int rc = hdqt_workspace_layout(HDQT_GEMM_FWD, M, K, N, params, &L);
     if (rc) return rc;
-    if (L.total > kStaticScratchBytes) return HDQT_ESCRATCH;
+    if (least_bytes(L, params) > kStaticScratchBytes) return HDQT_ESCRATCH;
     void* ptr = static_scratch();
     if (!ptr) return HDQT_EHIP;
     // run_gemm writes every word of the calibration records that it reads, or clears them with a

@@ -223,7 +223,7 @@ enum KernelId {
     K_GEMM_I4_FWD, K_GEMM_I4_BWD_INPUT, K_GEMM_I4_BWD_WEIGHT,
     K_DUAL_ABSMAX_X, K_DUAL_ABSMAX_W, K_DUAL_ABSMAX_G, K_DUAL_QUANT_X, K_DUAL_QUANT_W, K_DUAL_QUANT_G,
     K_DUAL_ABSMAX_BATCH, K_DUAL_QUANT_BATCH, K_REQUANT_TILES, K_REQUANT_SUM, K_IM2COL, K_RELU_MASK,
-    K_GEMM_RAGGED, K_GEMM_SMALL, K_COL2IM, K_TRANSPOSE,
+    K_GEMM_RAGGED, K_GEMM_SMALL, K_COL2IM, K_TRANSPOSE, K_EXPAND,
     K_COUNT
 };
 bool quantize_fast_eligible(const QuantArgs& q);
@@ -234,6 +234,12 @@ bool quantize_dual_eligible(const DualArgs& q);
 constexpr int kMaxSmallBatch = 3;
 bool gemm_small_eligible(const GemmArgs& g, bool alone = true);      // alone: no other product in the launch
 hipError_t launch_gemm_small(const GemmArgs* gs, int n, hipStream_t stream);
+// large products of packed codes through the 6-bit floating-point matrix instructions, and the scratch they
+// need for the codes in that form (gemm_six.hip)
+bool gemm_six_shape(int64_t RA, int64_t RB, int64_t D);
+bool gemm_six_eligible(const GemmArgs& g);
+int64_t gemm_six_bytes(const GemmArgs& g);
+hipError_t launch_gemm_six(const GemmArgs& g, void* frags, hipStream_t stream);
 bool gemm_fast_eligible(const GemmArgs& g);
 hipError_t launch_gemm_fast(const GemmArgs& g, hipStream_t stream);
 const char* kernel_name(int id);

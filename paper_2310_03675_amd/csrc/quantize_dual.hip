@@ -100,7 +100,9 @@ __device__ __forceinline__ void tile_load(Tile& t, const DualArgs& q, const Dual
 //
 // Rows are padded to whole 16-byte pieces on either side and pieces lie one after the other, so piece u of the
 // patch is the same place of every tile relative to the tile's first: a lane works out its pieces once,
-// and a wave of pass 2 goes through pSteps tiles.  (Working them out for each tile was a quarter of the kernel's vector instructions.)
+// and a wave of pass 2 goes through pSteps tiles.  (Working them out for each tile was a quarter of the kernel's vector
+// instructions.)  Pass 1, which has little else to do, is better off with a tile a wave, more of them in flight:
+// 262144 x 576 52 -> 42 us, in steps 85.
 struct PatchPieces {
     int off[kPieces];                    // bytes from the image's element (c_lo, y_first - ph, x_first - lead)
     int y[kPieces];                      // four times the patch row (far outside for pieces that hold nothing), plus 1 for
