@@ -317,6 +317,8 @@ int run_quantize_set(const QuantSet& s, void* records, size_t record_bytes, hipS
         }
     }
 
+    const bool ride = n_dual && any.h.total < (1 << 20);
+    if (!ride) hdqt::finish_any(&any);
     // maxima side by side, and nothing to clear, if every tensor has few enough workgroups
     bool dense = n_alone == 0;
     for (int k = 0; k < n_dual; ++k) dense = dense && hdqt::dual_workgroups(dual[k]) <= hdqt::kDenseMost;
@@ -325,7 +327,6 @@ int run_quantize_set(const QuantSet& s, void* records, size_t record_bytes, hipS
     hipError_t e = hipSuccess;
     if (!dense) e = hdqt::launch_zero2(static_cast<uint32_t*>(records), (int64_t)(record_bytes / 4), nullptr, 0, stream);
 
-    const bool ride = n_dual && any.h.total < (1 << 20);
     if (n_dual) {
         const hdqt::AnyBatch* riders = ride ? &any : nullptr;
         if (e == hipSuccess) e = hdqt::launch_dual_pass1(dual, n_dual, dense, riders, stream);

@@ -67,7 +67,8 @@ struct AnyPlan {
     int count;              // its workgroups
     int dense;              // `count` if the maxima stand side by side, 0 for atomic slots
     int wc;                 // axis 0: waves side by side in a workgroup (1, 2 or 4)
-    Divisor per;            // axis 1: threads per line; axis 0: workgroups along the columns
+    Divisor per;            // axis 1: threads per line; axis 0: pieces along the columns
+    int pieces, steps;      // of 2048 values; how many of them a workgroup takes one after the other
 };
 constexpr int kMaxAny = 6;
 struct AnyTensor {
@@ -178,6 +179,8 @@ hipError_t launch_transpose(const float* src, float* dst, int64_t batch, int64_t
 // Launchers (host).  Each returns the hipError_t of its last launch.
 // any-shape kernel: add a tensor to a batch (false: it is full); a launch of a whole batch
 bool plan_any(const QuantArgs& q, AnyBatch* b);
+// the workgroups of a batch that nothing is added to any more
+void finish_any(AnyBatch* b);
 hipError_t launch_any(const AnyBatch& b, int pass, hipStream_t stream);
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t stream);
 // Second reading of the low-bit accumulator: every tile's partial sums to g.partial and their

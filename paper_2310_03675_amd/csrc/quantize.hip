@@ -21,7 +21,7 @@ namespace hdqt {
 
 namespace {
 
-template <bool QUANT>
+template <bool QUANT, bool MANY>
 __global__ __launch_bounds__(any::kThreads) void fwht_any_kernel(AnyBatch b)
 {
     __shared__ float red[any::kThreads / kWave];
@@ -29,7 +29,7 @@ __global__ __launch_bounds__(any::kThreads) void fwht_any_kernel(AnyBatch b)
     const AnyHeader h = whole_args(b.h);
     // (a grid holds 2^32 threads)
     for (int64_t vb = blockIdx.x; vb < h.total; vb += gridDim.x) {
-        any::batch_block<QUANT>(b, h, (int)vb, red, lds);
+        any::batch_block<QUANT, MANY>(b, h, (int)vb, red, lds);
         if (vb + gridDim.x < h.total) __syncthreads();
     }
 }
@@ -76,19 +76,48 @@ bool plan_any(const QuantArgs& q, AnyBatch* b)
     if (!h.n)
         for (int k = 0; k < kMaxAny; ++k) h.first[k] = INT_MAX;
     h.first[h.n] = h.total;
-    p.count = (int)count;
+    p.count = p.pieces = (int)count;
+    p.steps = 1;
     b->t[h.n] = {q, p};
     h.total += p.count;
     ++h.n;
     return true;
 }
 
+// Workgroups that run at a time (79 registers a thread with a second piece on its way: six to a CU), and the most
+// pieces that one takes: with two rounds of them or more, four at most (three and eight measured alike).  us before / after:
+// steps of 131072 x 27 x 64 63.0 / 59.7, 20000 x 250 x 100 75.8 / 73.5 and 4000 x 561 x 561 51.4 / 49.4, weight gradients of
+// 40000 x 601 x 99 104.5 / 92.9 and 9000 x 1023 x 333 59.3 / 56.5, 9001 x 901 along axis 0 27.7 / 24.6; below two rounds
+// it loses (3001 x 1777 along axis 1 15.8 / 17.3).  Long lines rounded to nearest have little in front of a piece and run at
+// the memory's pace either way: 40000 x 901 x 77 76.9 / 77.5, so they stay as they are.
+constexpr int kAnyPlaces = 1536, kAnyMostSteps = 4, kAnyLongLines = 8192;
+
+void finish_any(AnyBatch* b)
+{
+    AnyHeader& h = b->h;
+    const int rounds = h.total / kAnyPlaces, steps = rounds < kAnyMostSteps ? rounds : kAnyMostSteps;
+    if (steps < 2) return;
+    for (int k = 0; k < h.n; ++k)
+        if (b->t[k].q.axis && !b->t[k].q.stochastic && b->t[k].p.pieces > kAnyLongLines) return;
+    h.total = 0;
+    for (int k = 0; k < h.n; ++k) {
+        AnyPlan& p = b->t[k].p;
+        p.steps = steps;
+        p.count = (p.pieces + steps - 1) / steps;
+        h.first[k] = h.total;
+        h.total += p.count;
+    }
+}
+
 hipError_t launch_any(const AnyBatch& b, int pass, hipStream_t stream)
 {
     const dim3 grid((unsigned)(b.h.total < (1 << 23) ? b.h.total : (1 << 23)));
     ProfileScope ps(pass == 1 ? K_ANY_ABSMAX : K_ANY_QUANT, stream);
-    if (pass == 1) hipLaunchKernelGGL(fwht_any_kernel<false>, grid, dim3(any::kThreads), 0, stream, b);
-    else hipLaunchKernelGGL(fwht_any_kernel<true>, grid, dim3(any::kThreads), 0, stream, b);
+    const bool many = b.h.n && b.t[0].p.steps > 1;
+    if (pass == 1 && many) hipLaunchKernelGGL((fwht_any_kernel<false, true>), grid, dim3(any::kThreads), 0, stream, b);
+    else if (pass == 1) hipLaunchKernelGGL((fwht_any_kernel<false, false>), grid, dim3(any::kThreads), 0, stream, b);
+    else if (many) hipLaunchKernelGGL((fwht_any_kernel<true, true>), grid, dim3(any::kThreads), 0, stream, b);
+    else hipLaunchKernelGGL((fwht_any_kernel<true, false>), grid, dim3(any::kThreads), 0, stream, b);
     return hipGetLastError();
 }
 

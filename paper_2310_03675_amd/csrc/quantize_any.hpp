@@ -95,122 +95,153 @@ __device__ __forceinline__ void emit(const QuantArgs& q, const float v[8], const
     store8(q, cw, dst, count);
 }
 
-// One workgroup of one tensor: transform, then the maximum (returned) or the codes.  `local` is
-// the workgroup's number within the tensor, `p` how the tensor is cut (plan_any).
-template <bool QUANT>
-__device__ __forceinline__ float block(const QuantArgs& q, const AnyPlan& p, int local, float* lds)
+// Eight values of a thread, where they come from (number of the first element, of the random bits) and where their
+// codes go (bytes).
+struct Eight {
+    float v[8];
+    int64_t from, to;
+    int count;                           // of them inside the tensor
+};
+
+// Those of a workgroup's piece of the tensor, loads only.
+template <int AXIS>
+__device__ __forceinline__ void load8(Eight& t, const QuantArgs& q, const AnyPlan& p, int piece, int64_t pitch)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    float v[8];
-    uint32_t rnd[4] = {0, 0, 0, 0};
-    uint8_t* dst = nullptr;
-    int count = 0;                       // codes of this thread inside the tensor
-    const int64_t pitch = q.b <= 4 ? ((q.axis ? q.cols : q.rows) + 1) >> 1 : (q.axis ? q.cols : q.rows);
     const int per = q.b <= 4 ? 4 : 8;    // bytes of eight codes
-    Maxima maxima{};
-    if (QUANT) maxima = fetch_maxima(q.meta, p.dense);
-    if (q.axis) {
+    t.count = 0;
+    if (AXIS) {
         // (the workgroup's first line: a 32-bit division wherever that is enough)
-        const int64_t base = (int64_t)local * kThreads;
-        const int64_t line0 = local < (1 << 23) ? (int64_t)divide((uint32_t)base, p.per) : base / (int64_t)p.per.d;
+        const int64_t base = (int64_t)piece * kThreads;
+        const int64_t line0 = piece < (1 << 23) ? (int64_t)divide((uint32_t)base, p.per) : base / (int64_t)p.per.d;
         const uint32_t at = (uint32_t)(base - line0 * p.per.d) + (uint32_t)tid;
         const uint32_t down = divide(at, p.per);
         const uint32_t j = at - down * p.per.d;
         const int64_t line = line0 + down;
-        const float* src = q.T + line * q.cols + 8 * (int64_t)j;
+        t.from = line * q.cols + 8 * (int64_t)j;
+        const float* src = q.T + t.from;
         if (line < q.rows) {
             const int64_t left = q.cols - 8 * (int64_t)j;
-            count = left < 8 ? (int)left : 8;
+            t.count = left < 8 ? (int)left : 8;
         }
-        if (count == 8) {
+        if (t.count == 8) {
             const Float4 lo = reinterpret_cast<const Float4*>(src)[0], hi = reinterpret_cast<const Float4*>(src)[1];
-            v[0] = lo.x; v[1] = lo.y; v[2] = lo.z; v[3] = lo.w;
-            v[4] = hi.x; v[5] = hi.y; v[6] = hi.z; v[7] = hi.w;
+            t.v[0] = lo.x; t.v[1] = lo.y; t.v[2] = lo.z; t.v[3] = lo.w;
+            t.v[4] = hi.x; t.v[5] = hi.y; t.v[6] = hi.z; t.v[7] = hi.w;
         } else {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = i < count ? src[i] : 0.0f;
+            for (int i = 0; i < 8; ++i) t.v[i] = i < t.count ? src[i] : 0.0f;
         }
-        butterfly8(v, q.log2n);
-        if (q.log2n > 3) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = stage_dpp<1>(v[i], (uint32_t)(lane & 1) << 31);
-        }
-        if (q.log2n > 4) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = stage_dpp<2>(v[i], (uint32_t)(lane & 2) << 30);
-        }
-        if (q.log2n > 5) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = stage_dpp<4>(v[i], (uint32_t)(lane & 4) << 29);
-        }
-        if (q.log2n > 6) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = stage_dpp<8>(v[i], (uint32_t)(lane & 8) << 28);
-        }
-        if (q.log2n > 7) {
-#pragma unroll
-            for (int i = 0; i < 8; i += 2) stage_swap<false>(v[i], v[i + 1]);
-        }
-        if (QUANT) {
-            dst = q.codes + line * pitch + (int64_t)j * per;
-            if (q.stochastic) random8(q, (uint64_t)(line * q.cols) + 8 * (uint64_t)j, rnd);
-        }
+        t.to = line * pitch + (int64_t)j * per;
     } else {
-        const uint32_t across = divide((uint32_t)local, p.per);
-        const int64_t by = across, bx = (uint32_t)local - across * p.per.d;
+        const uint32_t across = divide((uint32_t)piece, p.per);
+        const int64_t by = across, bx = (uint32_t)piece - across * p.per.d;
         const int wc = wave & (p.wc - 1), wr = wave >> (p.wc >> 1);      // (wc: 1, 2 or 4)
         const int rg = lane >> 3, cg = lane & 7;
         const int64_t row0 = (by * (4 >> (p.wc >> 1)) + wr) * 64, col0 = (bx * p.wc + wc) * 8;       // the wave's piece
         const int64_t row = row0 + rg * 8, col = col0 + cg;
         if (col < q.cols && row < q.rows) {
             const int64_t left = q.rows - row;
-            count = left < 8 ? (int)left : 8;
+            t.count = left < 8 ? (int)left : 8;
         }
         // (clamped addresses: every load is unconditional)
-        const int64_t rc = count ? row : 0, cc = count ? col : 0;
+        const int64_t rc = t.count ? row : 0, cc = t.count ? col : 0;
         const float* src = q.T + rc * q.cols + cc;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = src[(i < count ? i : 0) * q.cols];
+        for (int i = 0; i < 8; ++i) t.v[i] = src[(i < t.count ? i : 0) * q.cols];
+        t.from = (row + cg) * q.cols + col0;
+        t.to = col * pitch + (row >> 3) * per;
+    }
+}
+
+// One workgroup of one tensor: transform, then the maximum (returned) or the codes.  `local` is
+// the workgroup's number within the tensor, `p` how the tensor is cut (plan_any).  It takes p.steps pieces one after the
+// other, the next one's values on their way while this one's are worked on: in a tensor of thousands of pieces the
+// trips and the scaling in front of a piece took most of its time (finish_any).
+// (MANY: with a piece to a workgroup there is no loop, and no registers for a second piece)
+template <bool QUANT, bool MANY, int AXIS>
+__device__ __forceinline__ float block(const QuantArgs& q, const AnyPlan& p, int local, float* lds)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t pitch = q.b <= 4 ? ((AXIS ? q.cols : q.rows) + 1) >> 1 : (AXIS ? q.cols : q.rows);
+    Maxima maxima{};
+    if (QUANT) maxima = fetch_maxima(q.meta, p.dense);
+    int piece = MANY ? local * p.steps : local;
+    const int last = MANY ? (piece + p.steps < p.pieces ? piece + p.steps : p.pieces) : local + 1;
+    Eight next;
+    load8<AXIS>(next, q, p, piece, pitch);
+    Scaling sc{};
+    float amax = 0.0f;
+    for (bool first = true; !MANY || piece < last; ++piece, first = false) {
+        Eight t = next;
+        if (MANY && piece + 1 < last) load8<AXIS>(next, q, p, piece + 1, pitch);
+        float (&v)[8] = t.v;
+        uint32_t rnd[4] = {0, 0, 0, 0};
+        if (AXIS) {
+            butterfly8(v, q.log2n);
+            if (q.log2n > 3) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = i < count ? v[i] : 0.0f;
-        butterfly8(v, q.log2n);
-        if (q.log2n > 3) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = stage_dpp<8>(v[i], (uint32_t)(lane & 8) << 28);
-        }
-        if (q.log2n > 4) {
-#pragma unroll
-            for (int i = 0; i < 8; i += 2) stage_swap<false>(v[i], v[i + 1]);
-        }
-        if (q.log2n > 5) {
-#pragma unroll
-            for (int i = 0; i < 8; i += 2) stage_swap<true>(v[i], v[i + 1]);
-        }
-        // strides 64 and 128: the partner is another wave (four waves on top of each other: plan_any)
-        for (int st = 6; st < q.log2n; ++st) {
-            const int mask = 64 << (st - 6);
-            __syncthreads();
-#pragma unroll
-            for (int i = 0; i < 8; ++i) lds[i * kThreads + tid] = v[i];
-            __syncthreads();
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const float other = lds[i * kThreads + (tid ^ mask)];
-                v[i] = (tid & mask) ? other - v[i] : v[i] + other;
+                for (int i = 0; i < 8; ++i) v[i] = stage_dpp<1>(v[i], (uint32_t)(lane & 1) << 31);
             }
-        }
-        if (QUANT) {
-            dst = q.codes + col * pitch + (row >> 3) * per;
-            if (q.stochastic) {
+            if (q.log2n > 4) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = stage_dpp<2>(v[i], (uint32_t)(lane & 2) << 30);
+            }
+            if (q.log2n > 5) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = stage_dpp<4>(v[i], (uint32_t)(lane & 4) << 29);
+            }
+            if (q.log2n > 6) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = stage_dpp<8>(v[i], (uint32_t)(lane & 8) << 28);
+            }
+            if (q.log2n > 7) {
+#pragma unroll
+                for (int i = 0; i < 8; i += 2) stage_swap<false>(v[i], v[i + 1]);
+            }
+            if (QUANT && q.stochastic) random8(q, (uint64_t)t.from, rnd);
+        } else {
+            const int rg = lane >> 3, cg = lane & 7;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = i < t.count ? v[i] : 0.0f;
+            butterfly8(v, q.log2n);
+            if (q.log2n > 3) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = stage_dpp<8>(v[i], (uint32_t)(lane & 8) << 28);
+            }
+            if (q.log2n > 4) {
+#pragma unroll
+                for (int i = 0; i < 8; i += 2) stage_swap<false>(v[i], v[i + 1]);
+            }
+            if (q.log2n > 5) {
+#pragma unroll
+                for (int i = 0; i < 8; i += 2) stage_swap<true>(v[i], v[i + 1]);
+            }
+            // strides 64 and 128: the partner is another wave (four waves on top of each other: plan_any)
+            for (int st = 6; st < q.log2n; ++st) {
+                const int mask = 64 << (st - 6);
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < 8; ++i) lds[i * kThreads + tid] = v[i];
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const float other = lds[i * kThreads + (tid ^ mask)];
+                    v[i] = (tid & mask) ? other - v[i] : v[i] + other;
+                }
+            }
+            if (QUANT && q.stochastic) {
                 // the wave's 64 rows of eight halfwords: lane (rg, cg) draws row 8 rg + cg, then
                 // reads column cg of its own eight rows
                 if (q.log2n > 6) __syncthreads();
                 uint32_t* words = reinterpret_cast<uint32_t*>(lds) + wave * 64 * kRandPitch;
-                random8(q, (uint64_t)((row + cg) * q.cols + col0), rnd);
+                random8(q, (uint64_t)t.from, rnd);
+                // LDS operations of one wave are carried out in order; the fences keep the compiler
+                // from moving reads above the writes of other lanes, and writes above the last piece's reads
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
 #pragma unroll
                 for (int k = 0; k < 4; ++k) words[(rg * 8 + cg) * kRandPitch + k] = rnd[k];
-                // LDS operations of one wave are carried out in order; the fence keeps the compiler
-                // from moving the reads above the writes of other lanes
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -221,24 +252,26 @@ __device__ __forceinline__ float block(const QuantArgs& q, const AnyPlan& p, int
                                   (uint32_t)half[(rg * 8 + i + 1) * 2 * kRandPitch + cg] << 16;
             }
         }
-    }
-    if (QUANT) {
-        const Scaling sc = scaling_of(maxima, q.meta, q.clip, q.b, p.dense);
-        if (local == 0 && tid == 0) {
-            q.meta->scale = sc.scale;
-            if (q.scale_out) *q.scale_out = sc.scale;
-        }
-        if (count) emit(q, v, rnd, sc.inv, dst, count);
-        return 0.0f;
-    }
-    float amax = 0.0f;
+        if (QUANT) {
+            if (first) {
+                sc = scaling_of(maxima, q.meta, q.clip, q.b, p.dense);
+                if (local == 0 && tid == 0) {
+                    q.meta->scale = sc.scale;
+                    if (q.scale_out) *q.scale_out = sc.scale;
+                }
+            }
+            if (t.count) emit(q, v, rnd, sc.inv, q.codes + t.to, t.count);
+        } else {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf(v[i]));
+            for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf(v[i]));
+        }
+        if (!MANY) break;
+    }
     return amax;
 }
 
 // both passes of workgroup `vb` of a batch; `red`: one float per wave
-template <bool QUANT>
+template <bool QUANT, bool MANY>
 __device__ __forceinline__ void batch_block(const AnyBatch& b, const AnyHeader& h, int vb, float* red, float* lds)
 {
     int k = 0, local = vb;
@@ -250,7 +283,7 @@ __device__ __forceinline__ void batch_block(const AnyBatch& b, const AnyHeader& 
     }
     const AnyTensor t = whole_args(b.t[k]);
     if (QUANT) local = t.p.count - 1 - local;      // what pass 1 read last is in the caches still
-    const float m = block<QUANT>(t.q, t.p, local, lds);
+    const float m = t.q.axis ? block<QUANT, MANY, 1>(t.q, t.p, local, lds) : block<QUANT, MANY, 0>(t.q, t.p, local, lds);
     if (!QUANT) record_max(m, t.q.meta, red, local, t.p.dense);
 }
 

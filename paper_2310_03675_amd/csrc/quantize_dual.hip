@@ -917,7 +917,7 @@ __global__ __launch_bounds__(kThreads, CONV ? 4 : 1) void fwht_dual_kernel(DualB
     extern __shared__ __attribute__((aligned(16))) float lds[];      // CONV: one patch per wave; riders' exchange
 
     if ((int)blockIdx.x >= b.first[kMaxDualBatch]) {
-        any::batch_block<QUANT>(ride, hdqt::whole_args(ride.h), (int)blockIdx.x - b.first[kMaxDualBatch], &red[0][0], lds);
+        any::batch_block<QUANT, false>(ride, hdqt::whole_args(ride.h), (int)blockIdx.x - b.first[kMaxDualBatch], &red[0][0], lds);
         return;
     }
     const int vb = QUANT ? batch_order(b) : (int)blockIdx.x;
