@@ -47,7 +47,8 @@ constexpr int kPieces = 7;               // 16-byte pieces of a patch per lane, 
 // floats of a wave's LDS that hold the patch
 __host__ __device__ inline int patch_floats(const DualArgs& q)
 {
-    return q.pPerRow ? (int)((q.pPieces + 64 * kPieces - 1) / (64 * kPieces)) * 256 * kPieces : (q.pCN * q.pCP + 3) & ~3;
+    return q.pPerRow ? (int)((q.pPieces + 64 * kPieces - 1) / (64 * kPieces)) * 256 * kPieces
+                     : q.pCN * q.pCP < 4 * kTile ? 4 * kTile : (q.pCN * q.pCP + 3) & ~3;      // (line_tile's random blocks take its place)
 }
 
 // LDS operations of one wave are carried out in order; this keeps the compiler from moving reads above the
@@ -656,7 +657,6 @@ __device__ __forceinline__ void line_codes(const float (&v)[kTile], float inv, f
                                            uint4* words, int lane, Random random)
 {
     constexpr int kPieces = WIDE ? 4 : 2;        // 16-byte pieces of a line
-    uint4 mine[kPieces];
     const float magic = kMagic + (WIDE ? 128.0f : 8.0f);
     uint32_t out[4];
 #pragma unroll
@@ -668,14 +668,12 @@ __device__ __forceinline__ void line_codes(const float (&v)[kTile], float inv, f
         if constexpr (WIDE) {
             out[2 * (g & 1)] = pack_bytes(cw);
             out[2 * (g & 1) + 1] = pack_bytes(cw + 4);
-            if (g & 1) mine[g >> 1] = make_uint4(out[0], out[1], out[2], out[3]);
+            if (g & 1) words[lane * kPieces + (g >> 1)] = make_uint4(out[0], out[1], out[2], out[3]);
         } else {
             out[g & 3] = pack_nibbles(cw);
-            if ((g & 3) == 3) mine[g >> 2] = make_uint4(out[0], out[1], out[2], out[3]);
+            if ((g & 3) == 3) words[lane * kPieces + (g >> 2)] = make_uint4(out[0], out[1], out[2], out[3]);
         }
     }
-#pragma unroll
-    for (int k = 0; k < kPieces; ++k) words[lane * kPieces + k] = mine[k];
     wave_order();
 #pragma unroll
     for (int k = 0; k < kPieces; ++k) {
@@ -708,6 +706,7 @@ __device__ __forceinline__ void line_tile(const DualArgs& q, const Scaling& s_ro
                                  });
     }
     line_gather<0>(v, q, piece, lane);
+    uint4* const blocks = reinterpret_cast<uint4*>(piece);      // (the patch has been read)
     butterfly64(v, N64 ? 6 : q.log2n_col);
     line_codes<ST_COL, WIDE>(v, s_col.inv, (float)(-(1 << (q.b_col - 1))), (float)((1 << (q.b_col - 1)) - 1),
                              q.codes_col + ((col0 * q.rows + row0) >> half), q.rows >> half, words, lane, [&](int g, uint32_t (&u)[8]) {
@@ -717,9 +716,9 @@ __device__ __forceinline__ void line_tile(const DualArgs& q, const Scaling& s_ro
                                  uint32_t r[4];
                                  philox4x32_10((uint32_t)blk, (uint32_t)(blk >> 32), q.tid_col, 0u, q.seed_col_lo,
                                                q.seed_col_hi, r);
-                                 words[lane] = make_uint4(r[0], r[1], r[2], r[3]);
+                                 blocks[lane] = make_uint4(r[0], r[1], r[2], r[3]);
                                  wave_order();
-                                 const uint16_t* mine = reinterpret_cast<const uint16_t*>(words + (lane & ~7)) + (lane & 7);
+                                 const uint16_t* mine = reinterpret_cast<const uint16_t*>(blocks + (lane & ~7)) + (lane & 7);
 #pragma unroll
                                  for (int i = 0; i < 8; ++i) u[i] = mine[8 * i];
                                  wave_order();
