@@ -1010,8 +1010,9 @@ bool dual_conv_plan(DualArgs* q)
     if (q->rows % ((int64_t)H * W) != 0 || q->cols != (int64_t)q->cC * kh * kw) return false;
     q->pPH = (row_run ? 1 : kTile / W) + kh - 1;
     q->pPW = (row_run ? kTile : W) + kw - 1;
-    q->pCN = (kTile - 1) / (kh * kw) + 2;
-    if (q->pCN * q->pPH * q->pPW > kMaxPatchFloats) return false;
+    // (what is refused has always been told from one channel more than some windows need)
+    if (((kTile - 1) / (kh * kw) + 2) * q->pPH * q->pPW > kMaxPatchFloats) return false;
+    q->pCN = (kTile - 2) / (kh * kw) + 2;      // 64 columns that start at any tap of a channel
     q->dHW = make_divisor((uint32_t)(H * W)); q->dW = make_divisor((uint32_t)W);
     q->dTaps = make_divisor((uint32_t)(kh * kw)); q->dkw = make_divisor((uint32_t)kw);
     q->pLead = (kw - 1) / 2;
@@ -1019,11 +1020,11 @@ bool dual_conv_plan(DualArgs* q)
     q->pPieces = q->pPerCh = q->pPerRow = q->pInvCh = q->pInvRow = 0;
     // In pieces where a row is a whole number of them and one image is addressed with 31 bits.  Seven pieces behind
     // every channel put the columns of a tile on different banks (two or three of 64 lanes on one, up to eight without
-    // them); left out where they make the patch longer than a lane's pieces in flight.
+    // them); one, or none, where they would make the patch longer than a lane's pieces in flight.
     const int wt = row_run ? kTile : W, lead = (q->pLead + 3) & ~3;
     if (W >= 4 && (int64_t)q->cC * H * W < ((int64_t)1 << 29)) {
         const uint32_t per_row = (uint32_t)(wt + 2 * lead) / 4, bare = per_row * (uint32_t)q->pPH;
-        const uint32_t per_ch = bare + ((bare + 7) * (uint32_t)q->pCN <= 64u * kPieces ? 7 : 0);
+        const uint32_t most = 64u * kPieces / (uint32_t)q->pCN, per_ch = bare + 7 <= most ? bare + 7 : bare + 1 <= most ? bare + 1 : bare;
         q->pLead = lead; q->pPW = 4 * (int)per_row; q->pCP = 4 * (int)per_ch;
         q->pPieces = per_ch * (uint32_t)q->pCN; q->pPerCh = per_ch; q->pPerRow = per_row;
         q->pInvCh = ((1u << 20) + per_ch - 1) / per_ch;
