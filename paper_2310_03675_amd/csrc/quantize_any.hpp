@@ -154,118 +154,158 @@ __device__ __forceinline__ void load8(Eight& t, const QuantArgs& q, const AnyPla
     }
 }
 
-// One workgroup of one tensor: transform, then the maximum (returned) or the codes.  `local` is
-// the workgroup's number within the tensor, `p` how the tensor is cut (plan_any).  It takes p.steps pieces one after the
-// other, the next one's values on their way while this one's are worked on: in a tensor of thousands of pieces the
-// trips and the scaling in front of a piece took most of its time (finish_any).
-// (MANY: with a piece to a workgroup there is no loop, and no registers for a second piece)
-template <bool QUANT, bool MANY, int AXIS>
-__device__ __forceinline__ float block(const QuantArgs& q, const AnyPlan& p, int local, float* lds)
+// Their transform, and in pass 2 their random bits.
+template <bool QUANT, int AXIS>
+__device__ __forceinline__ void transform8(Eight& t, const QuantArgs& q, uint32_t (&rnd)[4], float* lds)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    float (&v)[8] = t.v;
+    if (AXIS) {
+        butterfly8(v, q.log2n);
+        if (q.log2n > 3) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = stage_dpp<1>(v[i], (uint32_t)(lane & 1) << 31);
+        }
+        if (q.log2n > 4) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = stage_dpp<2>(v[i], (uint32_t)(lane & 2) << 30);
+        }
+        if (q.log2n > 5) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = stage_dpp<4>(v[i], (uint32_t)(lane & 4) << 29);
+        }
+        if (q.log2n > 6) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = stage_dpp<8>(v[i], (uint32_t)(lane & 8) << 28);
+        }
+        if (q.log2n > 7) {
+#pragma unroll
+            for (int i = 0; i < 8; i += 2) stage_swap<false>(v[i], v[i + 1]);
+        }
+        if (QUANT && q.stochastic) random8(q, (uint64_t)t.from, rnd);
+    } else {
+        const int rg = lane >> 3, cg = lane & 7;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = i < t.count ? v[i] : 0.0f;
+        butterfly8(v, q.log2n);
+        if (q.log2n > 3) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = stage_dpp<8>(v[i], (uint32_t)(lane & 8) << 28);
+        }
+        if (q.log2n > 4) {
+#pragma unroll
+            for (int i = 0; i < 8; i += 2) stage_swap<false>(v[i], v[i + 1]);
+        }
+        if (q.log2n > 5) {
+#pragma unroll
+            for (int i = 0; i < 8; i += 2) stage_swap<true>(v[i], v[i + 1]);
+        }
+        // strides 64 and 128: the partner is another wave (four waves on top of each other: plan_any)
+        for (int st = 6; st < q.log2n; ++st) {
+            const int mask = 64 << (st - 6);
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < 8; ++i) lds[i * kThreads + tid] = v[i];
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float other = lds[i * kThreads + (tid ^ mask)];
+                v[i] = (tid & mask) ? other - v[i] : v[i] + other;
+            }
+        }
+        if (QUANT && q.stochastic) {
+            // the wave's 64 rows of eight halfwords: lane (rg, cg) draws row 8 rg + cg, then
+            // reads column cg of its own eight rows
+            if (q.log2n > 6) __syncthreads();
+            uint32_t* words = reinterpret_cast<uint32_t*>(lds) + wave * 64 * kRandPitch;
+            random8(q, (uint64_t)t.from, rnd);
+            // LDS operations of one wave are carried out in order; the fences keep the compiler
+            // from moving reads above the writes of other lanes, and writes above the last piece's reads
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int k = 0; k < 4; ++k) words[(rg * 8 + cg) * kRandPitch + k] = rnd[k];
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            const uint16_t* half = reinterpret_cast<const uint16_t*>(words);
+#pragma unroll
+            for (int i = 0; i < 8; i += 2)
+                rnd[i >> 1] = (uint32_t)half[(rg * 8 + i) * 2 * kRandPitch + cg] |
+                              (uint32_t)half[(rg * 8 + i + 1) * 2 * kRandPitch + cg] << 16;
+        }
+    }
+}
+
+__device__ __forceinline__ void publish(const QuantArgs& q, const Scaling& sc, int local)
+{
+    if (local == 0 && threadIdx.x == 0) {
+        q.meta->scale = sc.scale;
+        if (q.scale_out) *q.scale_out = sc.scale;
+    }
+}
+
+__device__ __forceinline__ float largest8(const Eight& t, float amax)
+{
+#pragma unroll
+    for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf(t.v[i]));
+    return amax;
+}
+
+// One workgroup of one tensor: transform, then the maximum (returned) or the codes.  `local` is
+// the workgroup's number within the tensor, `p` how the tensor is cut (plan_any).  Here it has one piece of it.
+template <bool QUANT>
+__device__ __forceinline__ float block(const QuantArgs& q, const AnyPlan& p, int local, float* lds)
+{
+    const int64_t pitch = q.b <= 4 ? ((q.axis ? q.cols : q.rows) + 1) >> 1 : (q.axis ? q.cols : q.rows);
+    Maxima maxima{};
+    if (QUANT) maxima = fetch_maxima(q.meta, p.dense);
+    Eight t;
+    uint32_t rnd[4] = {0, 0, 0, 0};
+    if (q.axis) {
+        load8<1>(t, q, p, local, pitch);
+        transform8<QUANT, 1>(t, q, rnd, lds);
+    } else {
+        load8<0>(t, q, p, local, pitch);
+        transform8<QUANT, 0>(t, q, rnd, lds);
+    }
+    if (!QUANT) return largest8(t, 0.0f);
+    const Scaling sc = scaling_of(maxima, q.meta, q.clip, q.b, p.dense);
+    publish(q, sc, local);
+    if (t.count) emit(q, t.v, rnd, sc.inv, q.codes + t.to, t.count);
+    return 0.0f;
+}
+
+// Here p.steps pieces one after the
+// other, the next one's values on their way while this one's are worked on: in a tensor of thousands of pieces the
+// trips and the scaling in front of a piece took most of its time (finish_any).  (Not with the axis told apart inside
+// the loop: where its two sides meet the compiler copies every value.)
+template <bool QUANT, int AXIS>
+__device__ __forceinline__ float block_of_many(const QuantArgs& q, const AnyPlan& p, int local, float* lds)
+{
     const int64_t pitch = q.b <= 4 ? ((AXIS ? q.cols : q.rows) + 1) >> 1 : (AXIS ? q.cols : q.rows);
     Maxima maxima{};
     if (QUANT) maxima = fetch_maxima(q.meta, p.dense);
-    int piece = MANY ? local * p.steps : local;
-    const int last = MANY ? (piece + p.steps < p.pieces ? piece + p.steps : p.pieces) : local + 1;
+    int piece = local * p.steps;
+    const int last = piece + p.steps < p.pieces ? piece + p.steps : p.pieces;
     Eight next;
     load8<AXIS>(next, q, p, piece, pitch);
     Scaling sc{};
     float amax = 0.0f;
-    for (bool first = true; !MANY || piece < last; ++piece, first = false) {
+    for (bool first = true; piece < last; ++piece, first = false) {
         Eight t = next;
-        if (MANY && piece + 1 < last) load8<AXIS>(next, q, p, piece + 1, pitch);
-        float (&v)[8] = t.v;
+        if (piece + 1 < last) load8<AXIS>(next, q, p, piece + 1, pitch);
         uint32_t rnd[4] = {0, 0, 0, 0};
-        if (AXIS) {
-            butterfly8(v, q.log2n);
-            if (q.log2n > 3) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] = stage_dpp<1>(v[i], (uint32_t)(lane & 1) << 31);
-            }
-            if (q.log2n > 4) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] = stage_dpp<2>(v[i], (uint32_t)(lane & 2) << 30);
-            }
-            if (q.log2n > 5) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] = stage_dpp<4>(v[i], (uint32_t)(lane & 4) << 29);
-            }
-            if (q.log2n > 6) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] = stage_dpp<8>(v[i], (uint32_t)(lane & 8) << 28);
-            }
-            if (q.log2n > 7) {
-#pragma unroll
-                for (int i = 0; i < 8; i += 2) stage_swap<false>(v[i], v[i + 1]);
-            }
-            if (QUANT && q.stochastic) random8(q, (uint64_t)t.from, rnd);
-        } else {
-            const int rg = lane >> 3, cg = lane & 7;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = i < t.count ? v[i] : 0.0f;
-            butterfly8(v, q.log2n);
-            if (q.log2n > 3) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) v[i] = stage_dpp<8>(v[i], (uint32_t)(lane & 8) << 28);
-            }
-            if (q.log2n > 4) {
-#pragma unroll
-                for (int i = 0; i < 8; i += 2) stage_swap<false>(v[i], v[i + 1]);
-            }
-            if (q.log2n > 5) {
-#pragma unroll
-                for (int i = 0; i < 8; i += 2) stage_swap<true>(v[i], v[i + 1]);
-            }
-            // strides 64 and 128: the partner is another wave (four waves on top of each other: plan_any)
-            for (int st = 6; st < q.log2n; ++st) {
-                const int mask = 64 << (st - 6);
-                __syncthreads();
-#pragma unroll
-                for (int i = 0; i < 8; ++i) lds[i * kThreads + tid] = v[i];
-                __syncthreads();
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const float other = lds[i * kThreads + (tid ^ mask)];
-                    v[i] = (tid & mask) ? other - v[i] : v[i] + other;
-                }
-            }
-            if (QUANT && q.stochastic) {
-                // the wave's 64 rows of eight halfwords: lane (rg, cg) draws row 8 rg + cg, then
-                // reads column cg of its own eight rows
-                if (q.log2n > 6) __syncthreads();
-                uint32_t* words = reinterpret_cast<uint32_t*>(lds) + wave * 64 * kRandPitch;
-                random8(q, (uint64_t)t.from, rnd);
-                // LDS operations of one wave are carried out in order; the fences keep the compiler
-                // from moving reads above the writes of other lanes, and writes above the last piece's reads
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                for (int k = 0; k < 4; ++k) words[(rg * 8 + cg) * kRandPitch + k] = rnd[k];
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                const uint16_t* half = reinterpret_cast<const uint16_t*>(words);
-#pragma unroll
-                for (int i = 0; i < 8; i += 2)
-                    rnd[i >> 1] = (uint32_t)half[(rg * 8 + i) * 2 * kRandPitch + cg] |
-                                  (uint32_t)half[(rg * 8 + i + 1) * 2 * kRandPitch + cg] << 16;
-            }
-        }
+        transform8<QUANT, AXIS>(t, q, rnd, lds);
         if (QUANT) {
             if (first) {
                 sc = scaling_of(maxima, q.meta, q.clip, q.b, p.dense);
-                if (local == 0 && tid == 0) {
-                    q.meta->scale = sc.scale;
-                    if (q.scale_out) *q.scale_out = sc.scale;
-                }
+                publish(q, sc, local);
             }
-            if (t.count) emit(q, v, rnd, sc.inv, q.codes + t.to, t.count);
+            if (t.count) emit(q, t.v, rnd, sc.inv, q.codes + t.to, t.count);
         } else {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) amax = fmaxf(amax, fabsf(v[i]));
+            amax = largest8(t, amax);
         }
-        if (!MANY) break;
     }
     return amax;
 }
@@ -283,7 +323,9 @@ __device__ __forceinline__ void batch_block(const AnyBatch& b, const AnyHeader& 
     }
     const AnyTensor t = whole_args(b.t[k]);
     if (QUANT) local = t.p.count - 1 - local;      // what pass 1 read last is in the caches still
-    const float m = t.q.axis ? block<QUANT, MANY, 1>(t.q, t.p, local, lds) : block<QUANT, MANY, 0>(t.q, t.p, local, lds);
+    float m;
+    if constexpr (!MANY) m = block<QUANT>(t.q, t.p, local, lds);
+    else m = t.q.axis ? block_of_many<QUANT, 1>(t.q, t.p, local, lds) : block_of_many<QUANT, 0>(t.q, t.p, local, lds);
     if (!QUANT) record_max(m, t.q.meta, red, local, t.p.dense);
 }
 
