@@ -112,7 +112,8 @@ struct PatchPieces {
 
 struct PatchPlace {                      // of one tile, the same in every lane
     const float* img;
-    int at, y, c_lo;                     // bytes of (c_lo, y_first - ph, x_first - lead) from `img`; y_first - ph
+    int x, y, c_lo;                      // x_first - lead, y_first - ph
+    int at;                              // in pieces: bytes of (c_lo, y, x) from `img` (images of less than 2^31 bytes)
     int beside;                          // 1: the tile's columns start an image row, 2: they end one, 3: both
 };
 
@@ -139,7 +140,8 @@ __device__ __forceinline__ PatchPlace patch_place(const DualArgs& q, uint32_t ro
     a.c_lo = (int)divide(col0, q.dTaps);
     a.y = y_first - (q.ckh - 1) / 2;
     a.img = q.T + (int64_t)b * q.cC * H * W;
-    a.at = 4 * ((a.c_lo * H + a.y) * W + x_first - q.pLead);
+    a.x = x_first - q.pLead;
+    a.at = (int)(4u * (uint32_t)((a.c_lo * H + a.y) * W + a.x));
     a.beside = (x_first == 0 ? 1 : 0) | (x_first + kTile >= W ? 2 : 0);
     return a;
 }
@@ -172,9 +174,9 @@ __device__ __forceinline__ uint32_t patch_store(const float4 (&v)[kPieces], floa
 __device__ __forceinline__ uint32_t patch_by_pixel(const DualArgs& q, const PatchPlace& a, float* patch, int lane)
 {
     uint32_t signs = 0;
-    const int total = q.pCN * q.pPH * q.pPW, x_first = a.at / 4 + q.pLead - (a.c_lo * q.cH + a.y) * q.cW;
+    const int total = q.pCN * q.pPH * q.pPW;
     for (int e = lane; e < total; e += 64) {
-        const int r = e / q.pPW, x = x_first - q.pLead + e - r * q.pPW, c = a.c_lo + r / q.pPH, y = a.y + r % q.pPH;
+        const int r = e / q.pPW, x = a.x + e - r * q.pPW, c = a.c_lo + r / q.pPH, y = a.y + r % q.pPH;
         const bool in = x >= 0 && x < q.cW && y >= 0 && y < q.cH && c < q.cC;
         const float v = in ? a.img[((int64_t)c * q.cH + y) * q.cW + x] : 0.0f;
         signs |= as_u(v);
