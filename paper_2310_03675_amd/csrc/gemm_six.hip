@@ -29,7 +29,7 @@ namespace {
 
 constexpr int kPanel = 128, kStage = 128;                   // rows and codes of a stage of one operand
 constexpr int kBlockBytes = 1536, kStageBytes = 8 * kBlockBytes;
-constexpr int kThreads = 512;
+constexpr int kThreads = 512, kExpandThreads = 256;
 
 typedef int v2i __attribute__((ext_vector_type(2)));
 typedef int v8i __attribute__((ext_vector_type(8)));
@@ -65,7 +65,7 @@ __device__ __forceinline__ uint32_t six_of(uint32_t x)
 }
 
 // A wave turns 32 rows x 64 codes into one block; a workgroup's four waves read 128 bytes of every row.
-__global__ __launch_bounds__(256) void expand_kernel(ExpandArgs e)
+__global__ __launch_bounds__(kExpandThreads) void expand_kernel(ExpandArgs e)
 {
     const int which = blockIdx.x >= e.first;
     const uint32_t id = blockIdx.x - (which ? e.first : 0);
@@ -221,9 +221,10 @@ bool gemm_six_eligible(const GemmArgs& g)
     if (!clamped && !plain) return false;
     const double codes = (double)(g.RA + g.RB) * (double)g.D, products = (double)g.RA * (double)g.RB * (double)g.D;
     if ((clamped ? 7.5e-10 : 4.4e-10) * products < (clamped ? 6.5 : 8.0) + 2.8e-7 * codes) return false;
-    const int64_t stages = (g.D + kStage - 1) / kStage;
-    return stages * kStageBytes < ((int64_t)1 << 31) && (g.RA + kPanel) / kPanel * ((g.RB + kPanel) / kPanel) < ((int64_t)1 << 28) &&
-           (g.RA + g.RB + 64) / 32 * ((stages + 1) / 2) < ((int64_t)1 << 30);
+    // a panel's bytes in 31 bits, and grids of less than 2^32 threads (with what they are rounded up by)
+    const int64_t stages = (g.D + kStage - 1) / kStage, n_rt = (g.RA + kPanel - 1) / kPanel, n_ct = (g.RB + kPanel - 1) / kPanel;
+    return stages * kStageBytes < ((int64_t)1 << 31) && (n_rt * n_ct + 7) * kThreads < ((int64_t)1 << 32) &&
+           4 * (n_rt + n_ct) * ((stages + 1) / 2) * kExpandThreads < ((int64_t)1 << 32);
 }
 
 hipError_t launch_gemm_six(const GemmArgs& g, void* frags, hipStream_t stream)
@@ -246,7 +247,7 @@ hipError_t launch_gemm_six(const GemmArgs& g, void* frags, hipStream_t stream)
     e.first = 4 * k.n_rt * pairs;
     {
         ProfileScope ps(K_EXPAND, stream);
-        hipLaunchKernelGGL(expand_kernel, dim3(e.first + 4 * k.n_ct * pairs), dim3(256), 0, stream, e);
+        hipLaunchKernelGGL(expand_kernel, dim3(e.first + 4 * k.n_ct * pairs), dim3(kExpandThreads), 0, stream, e);
     }
     ProfileScope ps(g.profile_tag ? K_GEMM_I4_FWD + (g.profile_tag - 1) : K_GEMM_I4, stream);
     const dim3 grid(8 * k.per_xcd), block(kThreads);
