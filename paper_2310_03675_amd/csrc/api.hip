@@ -194,7 +194,6 @@ bool conv_matrix_shape(const hdqt_conv_t* geo, int64_t* M, int64_t* K)
 // kernels do not take that geometry.
 bool set_conv_source(hdqt::DualArgs* d, const hdqt_conv_t* geo)
 {
-    d->conv = 1;
     d->cC = geo->channels; d->cH = geo->height; d->cW = geo->width;
     d->ckh = geo->kh; d->ckw = geo->kw;
     return hdqt::dual_conv_plan(d);

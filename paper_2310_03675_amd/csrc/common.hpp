@@ -87,6 +87,8 @@ struct AnyBatch {
 
 // One tensor quantized along both axes from one read ("row" = axis 1, along the
 // columns; "col" = axis 0, along the rows).
+enum ConvWay { kConvLines = 1, kConvTiles = 2 };      // how a convolution source is read: see quantize_dual.hip
+
 struct DualArgs {
     const float* T;
     int64_t rows, cols;
@@ -110,13 +112,15 @@ struct DualArgs {
     // tensor that is quantized is its im2col matrix for a kh x kw window, stride 1, zero
     // padding (kh - 1) / 2 and (kw - 1) / 2: row = pixel (b, y, x), column c*kh*kw + ty*kw + tx
     // holds act[b, c, y + ty - ph, x + tx - pw].  rows = batch*H*W, cols = C*kh*kw.
-    int conv;
+    int conv;               // 0 or one of ConvWay
     int cC, cH, cW, ckh, ckw;
     int pPH, pPW, pCN;      // the part of the activation a 64 x 64 tile reads: rows, row length in LDS, channels
     int pCP, pLead;         // distance of its channels in LDS; of a row's first pixel from the row's start
-    uint32_t pPieces, pPerCh, pPerRow;       // 16-byte pieces of the part, of a channel, of a row (0: pixel by pixel)
+    // kConvLines alone:
+    uint32_t pPieces, pPerCh, pPerRow;       // 16-byte pieces of the part, of a channel, of a row
     uint32_t pInvCh, pInvRow;                // 2^20 / pPerCh and / pPerRow, rounded up
     int pSteps;             // tiles a wave of pass 2 takes one after the other
+    // both:
     Divisor dHW, dW, dTaps, dkw;
 };
 

@@ -43,13 +43,8 @@ constexpr int kThreads = 256;
 constexpr int kTile = 64;
 
 constexpr int kPieces = 7;               // 16-byte pieces of a patch per lane, in flight (four workgroups' patches fill the LDS)
-
-// floats of a wave's LDS that hold the patch
-__host__ __device__ inline int patch_floats(const DualArgs& q)
-{
-    return q.pPerRow ? (int)((q.pPieces + 64 * kPieces - 1) / (64 * kPieces)) * 256 * kPieces
-                     : q.pCN * q.pCP < 4 * kTile ? 4 * kTile : (q.pCN * q.pCP + 3) & ~3;      // (line_tile's random blocks take its place)
-}
+constexpr int kPatchFloats = 256 * kPieces;      // of LDS that hold it
+__host__ __device__ inline int tile_patch_floats(const DualArgs& q) { return (q.pCN * q.pCP + 3) & ~3; }      // (kConvTiles)
 
 // LDS operations of one wave are carried out in order; this keeps the compiler from moving reads above the
 // writes of other lanes.
@@ -99,7 +94,8 @@ __device__ __forceinline__ void tile_load(Tile& t, const DualArgs& q, const Dual
 // address is (row part of its pixel) + (column part of its channel and tap).
 // The activation is read from HBM about once per pass instead of kh*kw times.
 //
-// Rows are padded to whole 16-byte pieces on either side and pieces lie one after the other, so piece u of the
+// Two ways to it (dual_conv_plan).  Where the patch is at most kPieces 16-byte pieces a lane, kConvLines: its rows are padded
+// to whole pieces on either side and pieces lie one after the other, so piece u of the
 // patch is the same place of every tile relative to the tile's first: a lane works out its pieces once,
 // and a wave of pass 2 goes through pSteps tiles.  (Working them out for each tile was a quarter of the kernel's vector
 // instructions.)  Pass 1, which has little else to do, is better off with a tile a wave, more of them in flight:
@@ -117,12 +113,12 @@ struct PatchPlace {                      // of one tile, the same in every lane
     int beside;                          // 1: the tile's columns start an image row, 2: they end one, 3: both
 };
 
-__device__ __forceinline__ void patch_pieces(PatchPieces& p, const DualArgs& q, uint32_t u0, int lane)
+__device__ __forceinline__ void patch_pieces(PatchPieces& p, const DualArgs& q, int lane)
 {
     const int wt = q.cW < kTile ? q.cW : kTile;
 #pragma unroll
     for (int k = 0; k < kPieces; ++k) {
-        const uint32_t u = u0 + 64 * k + lane;
+        const uint32_t u = 64 * k + lane;
         const uint32_t c = (u * q.pInvCh) >> 20, rest = u - c * q.pPerCh;          // (below 2^20 / pPerCh: dual_conv_plan)
         const uint32_t y = (rest * q.pInvRow) >> 20, x = (rest - y * q.pPerRow) * 4;
         p.off[k] = 4 * (((int)c * q.cH + (int)y) * q.cW + (int)x);
@@ -159,58 +155,39 @@ __device__ __forceinline__ void patch_load(float4 (&v)[kPieces], const PatchPiec
 }
 
 // Into LDS; returns the values' sign bits, put together.
-__device__ __forceinline__ uint32_t patch_store(const float4 (&v)[kPieces], float* patch, uint32_t u0, int lane)
+__device__ __forceinline__ uint32_t patch_store(const float4 (&v)[kPieces], float* patch, int lane)
 {
     uint32_t signs = 0;
 #pragma unroll
     for (int k = 0; k < kPieces; ++k) {
         signs |= (as_u(v[k].x) | as_u(v[k].y)) | (as_u(v[k].z) | as_u(v[k].w));
-        *reinterpret_cast<float4*>(patch + 4 * (u0 + 64 * k + lane)) = v[k];
-    }
-    return signs;
-}
-
-// The patch pixel by pixel: images narrower than four pixels and patches that no plan with pieces fits.
-__device__ __forceinline__ uint32_t patch_by_pixel(const DualArgs& q, const PatchPlace& a, float* patch, int lane)
-{
-    uint32_t signs = 0;
-    const int total = q.pCN * q.pPH * q.pPW;
-    for (int e = lane; e < total; e += 64) {
-        const int r = e / q.pPW, x = a.x + e - r * q.pPW, c = a.c_lo + r / q.pPH, y = a.y + r % q.pPH;
-        const bool in = x >= 0 && x < q.cW && y >= 0 && y < q.cH && c < q.cC;
-        const float v = in ? a.img[((int64_t)c * q.cH + y) * q.cW + x] : 0.0f;
-        signs |= as_u(v);
-        patch[e] = v;
+        *reinterpret_cast<float4*>(patch + 4 * (64 * k + lane)) = v[k];
     }
     return signs;
 }
 
 // Column parts of the tile's 64 columns, one per lane, in bytes.
-__device__ __forceinline__ void column_table(const DualArgs& q, int c_lo, uint32_t col0, float* patch, int lane)
+__device__ __forceinline__ void column_table(int* coltab, const DualArgs& q, int c_lo, uint32_t col0, int lane)
 {
-    int* coltab = reinterpret_cast<int*>(patch + patch_floats(q));
     const uint32_t k = col0 + (uint32_t)lane;
     const uint32_t c = divide(k, q.dTaps), tap = k - c * q.dTaps.d;
     const uint32_t ty = divide(tap, q.dkw), tx = tap - ty * q.dkw.d;
     coltab[lane] = 4 * (((int)c - c_lo) * q.pCP + (int)ty * q.pPW + (int)tx + q.pLead - (q.ckw - 1) / 2);
 }
 
-__device__ __forceinline__ const int* column_parts(const DualArgs& q, const float* patch)
-{
-    return reinterpret_cast<const int*>(patch + patch_floats(q));
-}
+// (of a patch in pieces)
+__device__ __forceinline__ int* column_parts(float* patch) { return reinterpret_cast<int*>(patch + kPatchFloats); }
 
 __device__ __forceinline__ const float* at_byte(const float* p, int bytes)
 {
     return reinterpret_cast<const float*>(reinterpret_cast<const char*>(p) + bytes);
 }
 
-// The tile of pass 1 from the patch: pixel 8*rg + i of the tile is (image row off / Wt, position off % Wt),
+// The tile in registers from the patch: pixel 8*rg + i of the tile is (image row off / Wt, position off % Wt),
 // Wt = min(W, 64), a power of two.  With Wt >= 8 the lane's eight pixels are neighbours
 // in one image row: eight consecutive patch words per column.
-__device__ __forceinline__ void tile_gather(Tile& t, const DualArgs& q, const float* patch, int lane)
+__device__ __forceinline__ void tile_gather(Tile& t, const DualArgs& q, const float* patch, const int* coltab, int lane)
 {
-    const int* coltab = column_parts(q, patch);
     int shift = q.cW >= kTile ? 6 : 31 - __builtin_clz((unsigned)q.cW), PW = q.pPW;
     const int off = lane & ~7, cg = lane & 7;
     if (shift >= 3) {
@@ -239,6 +216,90 @@ __device__ __forceinline__ void tile_gather(Tile& t, const DualArgs& q, const fl
             }
         }
     }
+}
+
+// Any other patch, kConvTiles: row by row, unpadded, for tiles in registers in both passes.  In pieces these take more LDS than
+// four workgroups have, and their rows meet on the same banks.  Both passes over 75 M elements of 64 channels, tiles in registers / pieces in
+// two or three parts (in units of 64 pieces with the best padding): 3 x 1 in images 32 wide 132 / 233 us (155), 1 x 3 in 8 95 / 149 (145),
+// 5 x 3 in 64 92 / 118 (97), 9 x 3 in 64 90 / 117 (143).
+constexpr int kPatchUnroll = 6;
+
+// Returns whether a value of the patch has its sign bit set (the same in every lane).
+__device__ __forceinline__ bool tile_load_conv(Tile& t, const DualArgs& q, int64_t row0, int64_t col0, float* patch, int lane)
+{
+    uint32_t signs = 0;
+    const int W = q.cW, H = q.cH, C = q.cC, kw = q.ckw, pw = (kw - 1) / 2;
+    const int PH = q.pPH, PW = q.pPW;
+    int* coltab = reinterpret_cast<int*>(patch + tile_patch_floats(q));
+    const uint32_t m0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)row0);
+    const uint32_t k0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)col0);
+    const PatchPlace at = patch_place(q, m0, k0);
+    const int x_first = at.x + pw;
+
+    // ---- patch: row r = (channel c_lo + r / PH, image row y_first - ph + r % PH).  The tile's own
+    // columns are whole image rows, or 64 pixels from a multiple of 64 on: four pixels per lane and
+    // load, kPatchUnroll loads in flight (every address is clamped into the activation, so no load
+    // is conditional).  (One pixel per lane and load cost 64 times the twelve instructions of its
+    // address and border test, a third of the kernel: 262144 x 576 from 256 x 64 x 32 x 32, pass 1
+    // 143 -> 91 us, pass 2 180 -> 135 us.)
+    const int wt = W < kTile ? W : kTile;
+    const int rows_total = q.pCN * PH;
+    // (r / PH for r below 2^20 / PH: dual_conv_plan)
+    const uint32_t inv_ph = ((1u << 20) + (uint32_t)PH - 1) / (uint32_t)PH;
+    auto source = [&](int r, int& off) {          // whether row r lies in the activation, and where
+        const int c_rel = (int)(((uint32_t)r * inv_ph) >> 20);
+        const int gy = at.y + r - c_rel * PH, c = at.c_lo + c_rel;
+        const int gyc = gy < 0 ? 0 : (gy >= H ? H - 1 : gy), cc = c >= C ? C - 1 : c;
+        off = (cc * H + gyc) * W;
+        return gy == gyc && c < C;
+    };
+    if (wt >= 4) {
+        const int log2u = 29 - __builtin_clz((unsigned)wt);      // (wt is a power of two) units of four pixels per row
+        const int units = rows_total << log2u;
+        for (int u0 = 0; u0 < units; u0 += 64 * kPatchUnroll) {
+            float4 v[kPatchUnroll];
+            int dst[kPatchUnroll];
+#pragma unroll
+            for (int k = 0; k < kPatchUnroll; ++k) {
+                const int u = u0 + 64 * k + lane, r = u >> log2u, xq = (u - (r << log2u)) * 4;
+                int off;
+                const bool in = source(r, off);
+                v[k] = *reinterpret_cast<const float4*>(at.img + off + x_first + xq);
+                if (!in) v[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                dst[k] = u < units ? r * PW + pw + xq : -1;
+            }
+#pragma unroll
+            for (int k = 0; k < kPatchUnroll; ++k) {
+                if (dst[k] < 0) continue;
+                signs |= (as_u(v[k].x) | as_u(v[k].y)) | (as_u(v[k].z) | as_u(v[k].w));
+                float* d = patch + dst[k];
+                d[0] = v[k].x; d[1] = v[k].y; d[2] = v[k].z; d[3] = v[k].w;
+            }
+        }
+    }
+    // ---- the window's columns beside them (all columns of images one or two pixels wide): zeros
+    // next to a whole image row, else pixels one by one
+    const int n_side = wt >= 4 ? kw - 1 : PW;
+    if (n_side) {
+        const uint32_t inv_ns = ((1u << 20) + (uint32_t)n_side - 1) / (uint32_t)n_side;
+        for (int e = lane; e < rows_total * n_side; e += 64) {
+            const int r = (int)(((uint32_t)e * inv_ns) >> 20), k = e - r * n_side;
+            const int px = wt >= 4 && k >= pw ? wt + k : k, gx = at.x + px;
+            float v = 0.0f;
+            if (gx >= 0 && gx < W) {
+                int off;
+                const bool in = source(r, off);
+                v = at.img[off + gx];
+                if (!in) v = 0.0f;
+            }
+            signs |= as_u(v);
+            patch[r * PW + px] = v;
+        }
+    }
+    column_table(coltab, q, at.c_lo, k0, lane);
+    wave_order();
+    tile_gather(t, q, patch, coltab, lane);
+    return __builtin_amdgcn_ballot_w64((int)signs < 0) != 0;
 }
 
 // Random bits of stochastic rounding for the lane's elements of one tile row: four
@@ -607,9 +668,9 @@ __device__ __forceinline__ void dual_codes(Tile& t, const DualCtx& x, int64_t ro
 
 // Lane's row (AXIS 1) or column (AXIS 0) of the tile.
 template <int AXIS>
-__device__ __forceinline__ void line_gather(float (&v)[kTile], const DualArgs& q, const float* patch, int lane)
+__device__ __forceinline__ void line_gather(float (&v)[kTile], const DualArgs& q, float* patch, int lane)
 {
-    const int* coltab = column_parts(q, patch);
+    const int* coltab = column_parts(patch);
     const int PW = q.pPW, shift = q.cW >= kTile ? 6 : 31 - __builtin_clz((unsigned)q.cW), mask = (1 << shift) - 1;
     if (AXIS == 1) {
         const float* base = patch + (lane >> shift) * PW + (lane & mask);
@@ -691,7 +752,7 @@ __device__ __forceinline__ void line_tile(const DualArgs& q, const Scaling& s_ro
                                           int64_t col0, float* piece, int lane)
 {
     const int half = WIDE ? 0 : 1;
-    uint4* const words = reinterpret_cast<uint4*>(piece + patch_floats(q) + kTile);
+    uint4* const words = reinterpret_cast<uint4*>(piece + kPatchFloats + kTile);
     float v[kTile];
     line_gather<1>(v, q, piece, lane);
     butterfly64(v, N64 ? 6 : q.log2n_row);
@@ -744,7 +805,7 @@ struct DualBatch {
 };
 
 // (see common.hpp: the arguments in one go)
-template <bool CONV>
+template <int CONV>
 __device__ __forceinline__ DualArgs whole_args(const DualArgs& x)
 {
     const DualArgs q = x;
@@ -752,9 +813,11 @@ __device__ __forceinline__ DualArgs whole_args(const DualArgs& x)
                  "s"(q.tid_row), "s"(q.b_col), "s"(q.clip_col), "s"(q.tid_col), "s"(q.seed_row_lo), "s"(q.seed_row_hi),
                  "s"(q.seed_col_lo), "s"(q.seed_col_hi), "s"(q.meta_row), "s"(q.meta_col), "s"(q.codes_row), "s"(q.codes_col),
                  "s"(q.scale_row_out), "s"(q.scale_col_out));
-    if constexpr (CONV)
-        asm volatile("" ::"s"(q.conv), "s"(q.cC), "s"(q.cH), "s"(q.cW), "s"(q.ckh), "s"(q.ckw), "s"(q.pPH), "s"(q.pPW), "s"(q.pCN), "s"(q.pCP), "s"(q.pLead),
-                     "s"(q.pPieces), "s"(q.pPerCh), "s"(q.pPerRow), "s"(q.pInvCh), "s"(q.pInvRow), "s"(q.dHW.mul), "s"(q.dHW.sh1), "s"(q.dHW.sh2));
+    if constexpr (CONV != 0)
+        asm volatile("" ::"s"(q.conv), "s"(q.cC), "s"(q.cH), "s"(q.cW), "s"(q.ckh), "s"(q.ckw), "s"(q.pPH), "s"(q.pPW), "s"(q.pCN), "s"(q.pCP),
+                     "s"(q.pLead), "s"(q.dHW.mul), "s"(q.dHW.sh1), "s"(q.dHW.sh2));
+    if constexpr (CONV == kConvLines)
+        asm volatile("" ::"s"(q.pPieces), "s"(q.pPerCh), "s"(q.pPerRow), "s"(q.pInvCh), "s"(q.pInvRow));
     return q;
 }
 
@@ -793,7 +856,7 @@ template <bool QUANT, int ROUND, bool N64>
 __device__ __forceinline__ void conv_block(const DualBatch& b, int k, int vb, float (*red)[2], float* lds)
 {
     constexpr bool kStRow = (ROUND & 1) != 0, kStCol = (ROUND & 2) != 0, kWide = (ROUND & kRoundWide) != 0;
-    const DualArgs q = whole_args<true>(b.t[k]);
+    const DualArgs q = whole_args<kConvLines>(b.t[k]);
     const int count = b.first[k + 1] - b.first[k];
     int local = vb - b.first[k];
     if (QUANT) local = count - 1 - local;
@@ -808,10 +871,9 @@ __device__ __forceinline__ void conv_block(const DualBatch& b, int k, int vb, fl
     const uint32_t strips = b.gx[k].d, row_tiles = (uint32_t)(q.rows / kTile);
     const uint32_t first = (uint32_t)local * (uint32_t)b.steps[k];
     uint32_t by = divide(first, b.gx[k]), strip = first - by * strips;
-    const bool once = q.pPerRow && q.pPieces <= 64 * kPieces;       // (the lane's pieces are the same ones in every tile)
     PatchPieces pieces;
     auto live = [&](uint32_t y) { return 4 * y + (uint32_t)wave < row_tiles; };
-    if (once) patch_pieces(pieces, q, 0, lane);
+    patch_pieces(pieces, q, lane);
     Scaling s_row{}, s_col{};
     if (QUANT) {
         s_row = scaling_of(max_row, q.meta_row, q.clip_row, q.b_row, dense);
@@ -832,23 +894,10 @@ __device__ __forceinline__ void conv_block(const DualBatch& b, int k, int vb, fl
         asm volatile("" : "+v"(l));      // (what follows from the lane is worked out where it is used, not kept for the loop)
         const int64_t row0 = (int64_t)(4 * by + wave) * kTile, col0 = (int64_t)strip * kTile;
         const PatchPlace at = patch_place(q, (uint32_t)row0, (uint32_t)col0);
-        uint32_t signs = 0;
-        if (once) {
-            float4 v[kPieces];
-            patch_load(v, pieces, at, q);
-            signs = patch_store(v, piece, 0, l);
-        } else if (q.pPerRow) {
-            for (uint32_t u = 0; u < q.pPieces; u += 64 * kPieces) {
-                PatchPieces p;
-                float4 v[kPieces];
-                patch_pieces(p, q, u, l);
-                patch_load(v, p, at, q);
-                signs |= patch_store(v, piece, u, l);
-            }
-        } else {
-            signs = patch_by_pixel(q, at, piece, l);
-        }
-        column_table(q, at.c_lo, (uint32_t)col0, piece, l);
+        float4 v[kPieces];
+        patch_load(v, pieces, at, q);
+        const uint32_t signs = patch_store(v, piece, l);
+        column_table(column_parts(piece), q, at.c_lo, (uint32_t)col0, l);
         wave_order();
         if (++strip == strips) { strip = 0; ++by; }
         if (QUANT) {
@@ -856,7 +905,7 @@ __device__ __forceinline__ void conv_block(const DualBatch& b, int k, int vb, fl
         } else {
             const bool negative = __builtin_amdgcn_ballot_w64((int)signs < 0) != 0;
             Tile t;
-            tile_gather(t, q, piece, l);
+            tile_gather(t, q, piece, column_parts(piece), l);
             if (!negative && x.log2n_row >= 3 && x.log2n_col >= 3) sums_absmax(t, x, amax_row, amax_col);
             else dual_absmax(t, x, row0, col0, amax_row, amax_col);
             wave_order();
@@ -865,14 +914,14 @@ __device__ __forceinline__ void conv_block(const DualBatch& b, int k, int vb, fl
     if (!QUANT) record_max2(amax_row, amax_col, q.meta_row, q.meta_col, red, local, b.dense);
 }
 
-template <bool QUANT, int ROUND, bool N64, bool CONV>
+template <bool QUANT, int ROUND, bool N64, int CONV>
 __device__ __forceinline__ void dual_block(const DualBatch& b, int k, int vb, float (*red)[2], float* lds)
 {
-    if (CONV && b.t[k].conv) {
+    if (CONV == kConvLines && b.t[k].conv) {
         conv_block<QUANT, ROUND, N64>(b, k, vb, red, lds);
         return;
     }
-    const DualArgs q = whole_args<false>(b.t[k]);
+    const DualArgs q = whole_args<CONV == kConvTiles ? kConvTiles : 0>(b.t[k]);
     const int count = b.first[k + 1] - b.first[k];
     // pass 2 walks a tensor from its end to its start: it begins with what pass 1
     // read last, which is most likely still in the memory-side cache
@@ -898,7 +947,11 @@ __device__ __forceinline__ void dual_block(const DualBatch& b, int k, int vb, fl
         max_col = fetch_maxima(q.meta_col, dense);
     }
     Tile t;
-    if (live) tile_load(t, q, x, row0, col0);
+    bool signs = true;                   // (of an ordinary source nobody asks: its passes wait for memory)
+    if (live) {
+        if (CONV == kConvTiles && q.conv) signs = tile_load_conv(t, q, row0, col0, lds + wave * b.lds_per_wave, lane);
+        else tile_load(t, q, x, row0, col0);
+    }
     if (QUANT) {
         const Scaling s_row = scaling_of(max_row, q.meta_row, q.clip_row, q.b_row, dense);
         const Scaling s_col = scaling_of(max_col, q.meta_col, q.clip_col, q.b_col, dense);
@@ -906,13 +959,14 @@ __device__ __forceinline__ void dual_block(const DualBatch& b, int k, int vb, fl
         if (live) dual_codes<(ROUND & 1) != 0, (ROUND & 2) != 0, (ROUND & kRoundWide) != 0>(t, x, row0, col0);
     } else {
         float amax_row = 0.0f, amax_col = 0.0f;
-        if (live) dual_absmax(t, x, row0, col0, amax_row, amax_col);
+        if (CONV == kConvTiles && !signs && x.log2n_row >= 3 && x.log2n_col >= 3) sums_absmax(t, x, amax_row, amax_col);
+        else if (live) dual_absmax(t, x, row0, col0, amax_row, amax_col);
         record_max2(amax_row, amax_col, q.meta_row, q.meta_col, red, local, b.dense);
     }
 }
 
-template <bool QUANT, int ROUND, bool N64, bool CONV>
-__global__ __launch_bounds__(kThreads, CONV ? 4 : 1) void fwht_dual_kernel(DualBatch b, AnyBatch ride)
+template <bool QUANT, int ROUND, bool N64, int CONV>
+__global__ __launch_bounds__(kThreads, CONV == kConvLines ? 4 : 1) void fwht_dual_kernel(DualBatch b, AnyBatch ride)
 {
     __shared__ float red[kThreads / kWave][2];
     extern __shared__ __attribute__((aligned(16))) float lds[];      // CONV: one patch per wave; riders' exchange
@@ -935,8 +989,12 @@ __global__ __launch_bounds__(kThreads, CONV ? 4 : 1) void fwht_dual_kernel(DualB
     }
 }
 
-// floats of LDS of a wave of pass 2: patch, column table, codes on their way out
-int conv_floats(const DualArgs& q) { return patch_floats(q) + kTile + (q.b_row > 4 ? 16 : 8) * kTile; }
+// floats of LDS of a wave: patch, column table; pass 2 by lines: codes on their way out
+int conv_floats(const DualArgs& q, bool quant)
+{
+    if (q.conv == kConvTiles) return tile_patch_floats(q) + kTile;
+    return kPatchFloats + kTile + (!quant ? 0 : q.b_row > 4 ? 16 * kTile : 8 * kTile);
+}
 
 bool all_order_64(const DualArgs* qs, int n)
 {
@@ -949,7 +1007,7 @@ bool all_order_64(const DualArgs* qs, int n)
 int waves_across(const DualArgs& q)
 {
     const int64_t strips = q.cols / kTile;
-    if (q.conv) return 1;
+    if (q.conv == kConvLines) return 1;
     return (strips % 4 == 0) ? 4 : (strips % 2 == 0) ? 2 : 1;
 }
 
@@ -963,10 +1021,10 @@ bool make_batch(const DualArgs* qs, int n, bool dense, const AnyBatch* ride, boo
         const DualArgs& q = qs[k];
         const int WC = waves_across(q);
         const int64_t gx = q.cols / kTile / WC, tiles = dual_workgroups(q);
-        const int64_t steps = q.conv && quant ? q.pSteps : 1, wgs = (tiles + steps - 1) / steps;
+        const int64_t steps = q.conv == kConvLines && quant ? q.pSteps : 1, wgs = (tiles + steps - 1) / steps;
         b->t[k] = q;
         if (q.conv) {
-            const int need = quant ? conv_floats(q) : patch_floats(q) + kTile;
+            const int need = conv_floats(q, quant);
             if (need > lds) lds = need;
         }
         b->first[k] = (int)total;
@@ -1019,22 +1077,22 @@ bool dual_conv_plan(DualArgs* q)
     q->dTaps = make_divisor((uint32_t)(kh * kw)); q->dkw = make_divisor((uint32_t)kw);
     q->pLead = (kw - 1) / 2;
     q->pCP = q->pPH * q->pPW;
-    q->pPieces = q->pPerCh = q->pPerRow = q->pInvCh = q->pInvRow = 0;
-    // In pieces where a row is a whole number of them and one image is addressed with 31 bits.  Seven pieces behind
-    // every channel put the columns of a tile on different banks (two or three of 64 lanes on one, up to eight without
-    // them); one, or none, where they would make the patch longer than a lane's pieces in flight.
+    q->conv = kConvTiles;
+    // By lines where a row is a whole number of pieces, one image is addressed with 31 bits and the patch is no more than a
+    // lane's pieces in flight.  Seven pieces behind every channel put the columns of a tile on different banks (two or
+    // three of 64 lanes on one, up to eight without them); one, or none, where seven would make it longer than that.
     const int wt = row_run ? kTile : W, lead = (q->pLead + 3) & ~3;
-    if (W >= 4 && (int64_t)q->cC * H * W < ((int64_t)1 << 29)) {
-        const uint32_t per_row = (uint32_t)(wt + 2 * lead) / 4, bare = per_row * (uint32_t)q->pPH;
-        const uint32_t most = 64u * kPieces / (uint32_t)q->pCN, per_ch = bare + 7 <= most ? bare + 7 : bare + 1 <= most ? bare + 1 : bare;
-        q->pLead = lead; q->pPW = 4 * (int)per_row; q->pCP = 4 * (int)per_ch;
-        q->pPieces = per_ch * (uint32_t)q->pCN; q->pPerCh = per_ch; q->pPerRow = per_row;
-        q->pInvCh = ((1u << 20) + per_ch - 1) / per_ch;
-        q->pInvRow = ((1u << 20) + per_row - 1) / per_row;
-    }
+    const uint32_t per_row = (uint32_t)(wt + 2 * lead) / 4, bare = per_row * (uint32_t)q->pPH, most = 64u * kPieces / (uint32_t)q->pCN;
+    if (W < 4 || (int64_t)q->cC * H * W >= ((int64_t)1 << 29) || bare > most) return true;
+    q->conv = kConvLines;
+    const uint32_t per_ch = bare + 7 <= most ? bare + 7 : bare + 1 <= most ? bare + 1 : bare;
+    q->pLead = lead; q->pPW = 4 * (int)per_row; q->pCP = 4 * (int)per_ch;
+    q->pPieces = per_ch * (uint32_t)q->pCN; q->pPerCh = per_ch; q->pPerRow = per_row;
+    q->pInvCh = ((1u << 20) + per_ch - 1) / per_ch;
+    q->pInvRow = ((1u << 20) + per_row - 1) / per_row;
     // pass 2: as many tiles a wave as make one round of the chip's workgroups
     const int64_t tiles = q->cols / kTile * ((q->rows / kTile + 3) / 4);
-    int64_t places = (160 << 10) / (4 * (int64_t)sizeof(float) * conv_floats(*q));
+    int64_t places = (160 << 10) / (4 * (int64_t)sizeof(float) * conv_floats(*q, true));
     places = 256 * (places < 1 ? 1 : places > 4 ? 4 : places);
     q->pSteps = (int)((tiles + places - 1) / places);
     return true;
@@ -1046,6 +1104,15 @@ bool quantize_dual_eligible(const DualArgs& q)
     return (q.rows % kTile == 0) && (q.cols % kTile == 0) && q.log2n_row <= 6 && q.log2n_col <= 6 &&
            q.b_row <= 8 && q.b_col <= 8 && (q.b_row <= 4) == (q.b_col <= 4) &&
            (q.rows / kTile) * (q.cols / kTile) < ((int64_t)1 << 30);
+}
+
+// The way of a convolution source among the tensors (a launch has one at most), 0 without one.
+int conv_among(const DualArgs* qs, int n)
+{
+    int conv = 0;
+    for (int k = 0; k < n; ++k)
+        if (qs[k].conv) conv = qs[k].conv;
+    return conv;
 }
 
 // Dynamic LDS of a launch: the patches of a convolution source, or the riders' exchange
@@ -1070,14 +1137,16 @@ hipError_t launch_dual_pass1(const DualArgs* qs, int n, bool dense, const AnyBat
     const dim3 grid((unsigned)(b.first[n] + ride->h.total)), block(kThreads);
     const size_t lds = launch_lds(b, ride);
     const bool n64 = all_order_64(qs, n);
-    if (b.lds_per_wave) {      // a convolution source among the tensors
-        if (n64) hipLaunchKernelGGL((fwht_dual_kernel<false, 0, true, true>), grid, block, lds, stream, b, *ride);
-        else hipLaunchKernelGGL((fwht_dual_kernel<false, 0, false, true>), grid, block, lds, stream, b, *ride);
-    } else if (n64) {
-        hipLaunchKernelGGL((fwht_dual_kernel<false, 0, true, false>), grid, block, lds, stream, b, *ride);
-    } else {
-        hipLaunchKernelGGL((fwht_dual_kernel<false, 0, false, false>), grid, block, lds, stream, b, *ride);
-    }
+    const int conv = conv_among(qs, n);
+#define HDQT_LAUNCH_PASS1(CONV)                                                                     \
+    do {                                                                                            \
+        if (n64) hipLaunchKernelGGL((fwht_dual_kernel<false, 0, true, CONV>), grid, block, lds, stream, b, *ride); \
+        else hipLaunchKernelGGL((fwht_dual_kernel<false, 0, false, CONV>), grid, block, lds, stream, b, *ride); \
+    } while (0)
+    if (conv == kConvLines) HDQT_LAUNCH_PASS1(kConvLines);
+    else if (conv == kConvTiles) HDQT_LAUNCH_PASS1(kConvTiles);
+    else HDQT_LAUNCH_PASS1(0);
+#undef HDQT_LAUNCH_PASS1
     return hipGetLastError();
 }
 
@@ -1111,14 +1180,17 @@ hipError_t launch_dual_pass2(const DualArgs* qs, int n, bool dense, const AnyBat
     const dim3 grid((unsigned)(b.first[n] + ride->h.total)), block(kThreads);
     const bool n64 = all_order_64(qs, n);
     const size_t lds = launch_lds(b, ride);
-    bool conv = false;
-    for (int k = 0; k < n; ++k) conv = conv || qs[k].conv;
+    const int conv = conv_among(qs, n);
+#define HDQT_LAUNCH_ORDER(ROUND, CONV)                                                               \
+    do {                                                                                            \
+        if (n64) hipLaunchKernelGGL((fwht_dual_kernel<true, ROUND, true, CONV>), grid, block, lds, stream, b, *ride); \
+        else hipLaunchKernelGGL((fwht_dual_kernel<true, ROUND, false, CONV>), grid, block, lds, stream, b, *ride); \
+    } while (0)
 #define HDQT_LAUNCH_PASS2(ROUND)                                                                     \
     do {                                                                                            \
-        if (conv && n64) hipLaunchKernelGGL((fwht_dual_kernel<true, ROUND, true, true>), grid, block, lds, stream, b, *ride); \
-        else if (conv) hipLaunchKernelGGL((fwht_dual_kernel<true, ROUND, false, true>), grid, block, lds, stream, b, *ride); \
-        else if (n64) hipLaunchKernelGGL((fwht_dual_kernel<true, ROUND, true, false>), grid, block, lds, stream, b, *ride); \
-        else hipLaunchKernelGGL((fwht_dual_kernel<true, ROUND, false, false>), grid, block, lds, stream, b, *ride); \
+        if (conv == kConvLines) HDQT_LAUNCH_ORDER(ROUND, kConvLines);                               \
+        else if (conv == kConvTiles) HDQT_LAUNCH_ORDER(ROUND, kConvTiles);                          \
+        else HDQT_LAUNCH_ORDER(ROUND, 0);                                                           \
     } while (0)
     const int mode = !same ? kRoundPerTensor : (qs[0].st_row ? 1 : 0) | (qs[0].st_col ? 2 : 0);
     // A stochastic tensor in front of nearest ones: its workgroups among theirs (see batch_order),
@@ -1151,6 +1223,7 @@ hipError_t launch_dual_pass2(const DualArgs* qs, int n, bool dense, const AnyBat
         }
     }
 #undef HDQT_LAUNCH_PASS2
+#undef HDQT_LAUNCH_ORDER
     return hipGetLastError();
 }
 
