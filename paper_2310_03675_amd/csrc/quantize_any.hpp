@@ -129,8 +129,11 @@ __device__ __forceinline__ void load8(Eight& t, const QuantArgs& q, const AnyPla
             t.v[0] = lo.x; t.v[1] = lo.y; t.v[2] = lo.z; t.v[3] = lo.w;
             t.v[4] = hi.x; t.v[5] = hi.y; t.v[6] = hi.z; t.v[7] = hi.w;
         } else {
+            // (seven at most; with an eighth the compiler makes its load one with the eighth of a whole piece, three loads
+            // then: 9431 x 301 10.1 / 10.8 us, 18863 x 301 with nothing else changed 16.0 / 16.6)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) t.v[i] = i < t.count ? src[i] : 0.0f;
+            for (int i = 0; i < 7; ++i) t.v[i] = i < t.count ? src[i] : 0.0f;
+            t.v[7] = 0.0f;
         }
         t.to = line * pitch + (int64_t)j * per;
     } else {
