@@ -84,21 +84,22 @@ bool plan_any(const QuantArgs& q, AnyBatch* b)
     return true;
 }
 
-// Workgroups that run at a time (79 registers a thread with a second piece on its way: six to a CU), and the most
-// pieces that one takes: with two rounds of them or more, four at most (three and eight measured alike).  us before / after:
-// steps of 131072 x 27 x 64 63.0 / 59.7, 20000 x 250 x 100 75.8 / 73.5 and 4000 x 561 x 561 51.4 / 49.4, weight gradients of
-// 40000 x 601 x 99 104.5 / 92.9 and 9000 x 1023 x 333 59.3 / 56.5, 9001 x 901 along axis 0 27.7 / 24.6; below two rounds
-// it loses (3001 x 1777 along axis 1 15.8 / 17.3).  Long lines rounded to nearest have little in front of a piece and run at
-// the memory's pace either way: 40000 x 901 x 77 76.9 / 77.5, so they stay as they are.
-constexpr int kAnyPlaces = 1536, kAnyMostSteps = 4, kAnyLongLines = 8192;
+// Workgroups that run at a time (73 registers a thread with a second piece on its way: six to a CU), and the most
+// pieces that one takes: with two rounds of them or more, four at most (three and eight measured alike).  Only where at least
+// half of the pieces are along axis 0, whose eight rows a thread are eight loads; along axis 1 a piece is two, and more waves in
+// flight do better.  us without / with: axis 0 5000 x 1269 22.6 / 21.6, 5000 x 3277 45.8 / 37.5, at order 256 5120 x 3201 88.9 / 68.9;
+// weight gradients of 99 features and outputs 32064 rows 42.9 / 40.3, 64129 64.4 / 53.1; steps of 4000 x 561 x 561 52.2 / 50.5,
+// 60001 x 77 x 50 80.9 / 75.5; of 70 random sets of a layer's tensors just above the line 66 gain 1 to 13 % and two lose 1.  Axis 1
+// alone 22231 x 301 17.8 / 18.4, forward products of 12544 x 502 x 32 21.0 / 23.
+constexpr int kAnyPlaces = 1536, kAnyMostSteps = 4;
 
 void finish_any(AnyBatch* b)
 {
     AnyHeader& h = b->h;
     const int rounds = h.total / kAnyPlaces, steps = rounds < kAnyMostSteps ? rounds : kAnyMostSteps;
-    if (steps < 2) return;
-    for (int k = 0; k < h.n; ++k)
-        if (b->t[k].q.axis && !b->t[k].q.stochastic && b->t[k].p.pieces > kAnyLongLines) return;
+    int down = 0;
+    for (int k = 0; k < h.n; ++k) down += b->t[k].q.axis ? 0 : b->t[k].p.pieces;
+    if (steps < 2 || down < h.total - down) return;
     h.total = 0;
     for (int k = 0; k < h.n; ++k) {
         AnyPlan& p = b->t[k].p;
