@@ -208,10 +208,14 @@ bool gemm_six_shape(int64_t RA, int64_t RB, int64_t D)
 }
 
 // Against the integer kernel it saves 0.75 us per 10^9 multiply-adds where tiles are clamped and 0.44 where they are
-// not, and pays for the launch of expand_kernel and its 1.25 bytes per code.  The line is where the two meet (us,
-// integer kernel / this one with expand_kernel): clamped 8192 x 8192 x 8192 926 / 541, 4096 x 4096 x 4096 113 / 83, 5120 cubed
-// 228 / 154, 8192 x 1024 x 8192 112 / 85, 2048 x 4096 x 2048 33.8 / 33.2, 24576 x 768 x 768 33.0 / 35.3; not clamped 566 / 351, 79 / 68, 158 / 117, 78 / 62,
-// 25.6 / 28.9, 16384 x 2048 x 1024 52.8 / 55.1.
+// not, and pays for the launch of expand_kernel and its 1.25 bytes per code.  The line is where the two meet (us, inside
+// a graph, integer kernel / this one with expand_kernel): clamped 8192 x 8192 x 8192 771 / 520, 4096 x 4096 x 4096 107 / 80, 8192 x 1024 x 8192
+// 106 / 82, 1920 x 11136 x 544 36.0 / 36.2, 24576 x 768 x 768 35.4 / 36.6; not clamped 558 / 363, 81 / 68, 78 / 63, 4096 x 4096 x 2048 46.5 / 45.7, 16384 x
+// 1024 x 2048 46.2 / 47.1, 4864 x 18816 x 512 96 / 92.  Later where the tiles fill half rounds of 512 (two to a CU), which is where the integer
+// kernel wastes nothing: by 1.4 us a round if they are clamped (1536 x 32768 x 512 63.4 / 67.1, 1024 x 32768 x 512 46.0 / 51.7, 2048 x 4096 x 2048 33.1 / 34.0),
+// and if not in short contractions of wide outputs (2048 x 32768 x 512 74 / 82, 2048 x 16384 x 1024 57 / 60, but 32768 x 2048 x 512 80 / 74; 16384 x 2048 x 1024
+// 55.7 / 55.9).  Of 612 products (339 clamped) up to 15 and 40 us beyond the estimate, each timed four times, it takes 505; ten of these are
+// 1 to 3 % slower than with the integer kernel, which without the rule for half rounds were 39, up to 14 %.
 bool gemm_six_eligible(const GemmArgs& g)
 {
     if (!gemm_six_shape(g.RA, g.RB, g.D)) return false;
@@ -220,9 +224,15 @@ bool gemm_six_eligible(const GemmArgs& g)
     const bool plain = g.acc_hi == INT_MAX && g.D <= 16384;      // totals of at most 2^20
     if (!clamped && !plain) return false;
     const double codes = (double)(g.RA + g.RB) * (double)g.D, products = (double)g.RA * (double)g.RB * (double)g.D;
-    if ((clamped ? 7.5e-10 : 4.4e-10) * products < (clamped ? 6.5 : 8.0) + 2.8e-7 * codes) return false;
-    // a panel's bytes in 31 bits, and grids of less than 2^32 threads (with what they are rounded up by)
+    const double gain = (clamped ? 7.5e-10 : 4.4e-10) * products - (clamped ? 6.5 : 8.0) - 2.8e-7 * codes;
     const int64_t stages = (g.D + kStage - 1) / kStage, n_rt = (g.RA + kPanel - 1) / kPanel, n_ct = (g.RB + kPanel - 1) / kPanel;
+    double least = 0.0;
+    if (n_rt * n_ct % 256 == 0 && (clamped || (g.RB >= g.RA && stages <= 8))) {
+        least = 1.4 / 512 * (double)(n_rt * n_ct);
+        if (clamped && least < 3.0) least = 3.0;
+    }
+    if (gain < least) return false;
+    // a panel's bytes in 31 bits, and grids of less than 2^32 threads (with what they are rounded up by)
     return stages * kStageBytes < ((int64_t)1 << 31) && (n_rt * n_ct + 7) * kThreads < ((int64_t)1 << 32) &&
            4 * (n_rt + n_ct) * ((stages + 1) / 2) * kExpandThreads < ((int64_t)1 << 32);
 }

@@ -19,3 +19,21 @@ def test_products_whose_grids_cannot_be_launched_stay_with_the_integer_kernel(RA
     threads = max(-(-RA // 128) * -(-RB // 128) * 512, (-(-RA // 128) + -(-RB // 128)) * 4 * (D // 256) * 256)
     assert (threads < MOST_THREADS) == fits
     assert (other_form(RA, RB, D) > 0) == fits
+
+
+def has_other_form(RA, RB, D, acc, s):
+    op = B.Operand(4, B.ROUND_NEAREST, 1.0, 0)
+    L = B.workspace_layout(B.GEMM_FWD, RA, D, RB, B.Params(had_block=64, acc_bits=acc, s=s, seed=0, A=op, B=op))
+    return L.total - L.acc >= 96 * 256 * 512 // 128      # (the codes of 256 rows at least)
+
+
+# products timed with either kernel, on both sides of the line; those that fill half rounds of 512 tiles come later
+@pytest.mark.parametrize("RA,RB,D,acc,s,other", [
+    (8192, 8192, 8192, 8, 64, True), (4096, 4096, 4096, 8, 64, True), (8192, 1024, 8192, 8, 64, True), (2304, 10368, 2048, 8, 64, True),
+    (24576, 768, 768, 8, 64, False), (1536, 32768, 512, 8, 64, False), (1024, 32768, 512, 8, 64, False),
+    (2048, 16384, 512, 8, 64, False), (2048, 4096, 2048, 8, 64, False), (1536, 24832, 512, 8, 64, True),
+    (8192, 8192, 8192, 32, 256, True), (4096, 4096, 2048, 32, 256, True), (16384, 1024, 2048, 32, 256, False),
+    (2048, 32768, 512, 32, 256, False), (32768, 2048, 512, 32, 256, True), (4096, 8192, 1024, 32, 256, False),
+    (8192, 4096, 1024, 32, 256, True), (4096, 8192, 1536, 32, 256, True)])
+def test_which_products_take_the_other_form(RA, RB, D, acc, s, other):
+    assert has_other_form(RA, RB, D, acc, s) == other
