@@ -104,8 +104,8 @@ typedef struct {
     size_t codesB;   /* packed codes [RB, D] */
     size_t acc;      /* int32 slices of a split contraction, or a large product's codes in
                         another form (see hdqt_gemm_codes) */
-    size_t total;    /* bytes required; the other form is done without where the workspace
-                        ends before it */
+    size_t total;    /* bytes with which the call is fastest; it does without the other form
+                        where the workspace ends before it: see hdqt_workspace_least */
     int64_t RA, RB, D;
     int32_t n_eff;
 } hdqt_ws_layout_t;
@@ -121,12 +121,17 @@ int64_t hdqt_codes_pitch(int64_t D, int b);
 /* Workspace bytes hdqt_quantize needs (a small constant). */
 size_t hdqt_quantize_workspace_size(void);
 
-/* Workspace bytes (and layout) one hdqt_gemm_* call needs.  Returns 0 and
- * fills *layout (if not NULL) on success, a negative code on bad arguments. */
+/* Workspace bytes (and layout) one hdqt_gemm_* call is fastest with.  Returns 0 and
+ * fills *layout (if not NULL) on success, a negative code on bad arguments.
+ * hdqt_workspace_least: the bytes without which it returns HDQT_EWORKSPACE.  The difference is a
+ * large product's codes in another form, which calls with a mask or a bfloat16 output
+ * never use. */
 int hdqt_workspace_layout(int gemm_kind, int64_t M, int64_t K, int64_t N,
                           const hdqt_params_t *params, hdqt_ws_layout_t *layout);
 size_t hdqt_workspace_size(int gemm_kind, int64_t M, int64_t K, int64_t N,
                            const hdqt_params_t *params); /* 0 on bad arguments */
+size_t hdqt_workspace_least(int gemm_kind, int64_t M, int64_t K, int64_t N,
+                            const hdqt_params_t *params); /* 0 on bad arguments */
 
 /*
  * Transform and quantize one tensor (Methodology: Hadamard domain + Q).
@@ -234,14 +239,21 @@ int hdqt_transpose(const float *src, int64_t batch, int64_t rows, int64_t cols, 
  *   scaleA, scaleB          device pointers to one float each
  *   out     fp32 [RA, RB] (device, may be NULL if acc_out is given)
  *   acc_out int32 [RA, RB] (device, may be NULL)
- *   workspace: hdqt_gemm_codes_workspace_size(RA, RB, D, s) bytes of device memory
- *   (0 for most shapes, then NULL is fine; HDQT_EWORKSPACE without it otherwise).  Few output tiles with a long
- *   contraction are split over workgroups along the contraction; every part
- *   writes its totals (sums of whole clamped tiles, so the result is the same)
- *   to a slice of the workspace and a second pass adds the slices.  Large products of packed
- *   codes are faster with three quarters of a byte of workspace per code, and do without.
+ *   workspace: device memory, used for one of two things (neither for most shapes, then NULL is
+ *   fine).  Few output tiles with a long contraction are split over workgroups along the
+ *   contraction; every part writes its totals (sums of whole clamped tiles, so the result is
+ *   the same) to a slice of the workspace and a second pass adds the slices: HDQT_EWORKSPACE
+ *   where it is NULL or too small for them.  Large products of packed codes (fp32 or int32
+ *   output; tiles of 64 in 8-bit accumulators, or tiles that cannot saturate) are faster with the
+ *   codes in another form, three quarters of a byte each, rows and contractions rounded up to
+ *   128; with less, or NULL, they are multiplied without it.
+ * hdqt_gemm_codes_workspace_size_for: the bytes with which a call of these widths, and with a
+ * bfloat16 output (bf16 != 0) or without, is fastest (0 on bad arguments).
+ * hdqt_gemm_codes_workspace_size: bytes that are enough for that whatever the widths.
  */
 size_t hdqt_gemm_codes_workspace_size(int64_t RA, int64_t RB, int64_t D, int64_t s);
+size_t hdqt_gemm_codes_workspace_size_for(int64_t RA, int64_t RB, int64_t D, int64_t s, int bA,
+                                          int bB, int acc_bits, int bf16);
 int hdqt_gemm_codes(const void *qA, const void *qB, int bA, int bB, const float *scaleA,
                     const float *scaleB, int64_t RA, int64_t RB, int64_t D, int n_eff,
                     int acc_bits, int64_t s, float *out, int32_t *acc_out, void *workspace,
@@ -315,8 +327,8 @@ int hdqt_gemm_bwd_input(const float *G, const float *W, float *dX, int64_t M, in
 int hdqt_gemm_bwd_weight(const float *X, const float *G, float *dW, int64_t M, int64_t K,
                          int64_t N, const hdqt_params_t *params, int32_t *acc_out,
                          void *workspace, size_t workspace_bytes, void *stream);
-/* hdqt_gemm_bwd_input with dX narrowed to bfloat16 (see hdqt_gemm_codes_bf16); same
- * workspace, same errors. */
+/* hdqt_gemm_bwd_input with dX narrowed to bfloat16 (see hdqt_gemm_codes_bf16); same errors, and
+ * hdqt_workspace_least(HDQT_GEMM_BWD_INPUT, ...) bytes of workspace are all that it uses. */
 int hdqt_gemm_bwd_input_bf16(const float *G, const float *W, uint16_t *dX, int64_t M, int64_t K,
                              int64_t N, const hdqt_params_t *params, int32_t *acc_out,
                              void *workspace, size_t workspace_bytes, void *stream);
@@ -329,7 +341,7 @@ int hdqt_gemm_bwd_input_bf16(const float *G, const float *W, uint16_t *dX, int64
  * (hdqt_gemm_fwd_static_max_bytes() = 8 MiB per GPU the library has run on, held until the
  * process ends); the call allocates nothing, on the host or the device (as long as the
  * optional profiling is off).
- *   HDQT_ESCRATCH   hdqt_workspace_size(HDQT_GEMM_FWD, M, K, N, params) exceeds the array
+ *   HDQT_ESCRATCH   hdqt_workspace_least(HDQT_GEMM_FWD, M, K, N, params) exceeds the array
  *                   (nothing is launched); other errors as for hdqt_gemm_fwd
  * All calls on one GPU share that GPU's array: two calls whose work overlaps in time on the
  * same GPU (different streams or threads) race.  Calls on one stream, one after the other,

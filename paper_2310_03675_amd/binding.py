@@ -48,7 +48,7 @@ EXPORTED = [
     "hdqt_gemm_bwd_input", "hdqt_gemm_bwd_weight", "hdqt_strerror", "hdqt_last_hip_error",
     "hdqt_profile_enable", "hdqt_profile_collect", "hdqt_quantize_dual",
     "hdqt_quantize_dual_workspace_size", "hdqt_layer_step_workspace_size", "hdqt_layer_step",
-    "hdqt_gemm_codes_workspace_size", "hdqt_layer_saved_size", "hdqt_layer_fwd_workspace_size",
+    "hdqt_workspace_least", "hdqt_gemm_codes_workspace_size", "hdqt_gemm_codes_workspace_size_for", "hdqt_layer_saved_size", "hdqt_layer_fwd_workspace_size",
     "hdqt_layer_fwd", "hdqt_layer_bwd_workspace_size", "hdqt_layer_bwd",
     "hdqt_gemm_codes_requant_workspace_size", "hdqt_gemm_codes_requant_workspace_size_for",
     "hdqt_gemm_codes_requant",
@@ -140,6 +140,8 @@ def load() -> C.CDLL:
     lib.hdqt_workspace_layout.argtypes = [i32, i64, i64, i64, C.POINTER(CParams), C.POINTER(CLayout)]
     lib.hdqt_workspace_size.restype = sz
     lib.hdqt_workspace_size.argtypes = [i32, i64, i64, i64, C.POINTER(CParams)]
+    lib.hdqt_workspace_least.restype = sz
+    lib.hdqt_workspace_least.argtypes = [i32, i64, i64, i64, C.POINTER(CParams)]
     lib.hdqt_quantize.restype = i32
     lib.hdqt_quantize.argtypes = [vp, i64, i64, i32, i32, C.POINTER(COperand), C.c_uint64, vp, vp,
                                   vp, sz, vp]
@@ -147,6 +149,8 @@ def load() -> C.CDLL:
     lib.hdqt_quantize_dual_workspace_size.argtypes = []
     lib.hdqt_gemm_codes_workspace_size.restype = sz
     lib.hdqt_gemm_codes_workspace_size.argtypes = [i64, i64, i64, i64]
+    lib.hdqt_gemm_codes_workspace_size_for.restype = sz
+    lib.hdqt_gemm_codes_workspace_size_for.argtypes = [i64, i64, i64, i64, i32, i32, i32, i32]
     lib.hdqt_gemm_codes_requant_workspace_size.restype = sz
     lib.hdqt_gemm_codes_requant_workspace_size.argtypes = [i64, i64, i64, i64]
     lib.hdqt_gemm_codes_requant_workspace_size_for.restype = sz
@@ -452,7 +456,7 @@ def gemm_codes(qA: torch.Tensor, qB: torch.Tensor, bA: int, bB: int, scaleA: tor
     if acc is None and want_acc:
         acc = torch.empty((RA, RB), dtype=torch.int32, device=qA.device)
     if workspace is None:
-        need = load().hdqt_gemm_codes_workspace_size(RA, RB, D, s)
+        need = load().hdqt_gemm_codes_workspace_size_for(RA, RB, D, s, bA, bB, acc_bits, int(bf16))
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=qA.device)
     rc = getattr(load(), fn)(_ptr(qA), _ptr(qB), bA, bB, _ptr(scaleA), _ptr(scaleB), RA, RB, D,
                              n, acc_bits, s, _ptr(out), _ptr(acc), _ptr(workspace),
@@ -494,7 +498,7 @@ def gemm(kind: int, P: torch.Tensor, Q: torch.Tensor, M: int, K: int, N: int, pa
     if acc is None and want_acc:
         acc = torch.empty(shape, dtype=torch.int32, device=P.device)
     p = params.c()
-    need = load().hdqt_workspace_size(kind, M, K, N, C.byref(p))
+    need = (load().hdqt_workspace_least if bf16 or mask is not None else load().hdqt_workspace_size)(kind, M, K, N, C.byref(p))
     if workspace is None:
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=P.device)
     if mask is not None:

@@ -812,6 +812,12 @@ int64_t hdqt_codes_pitch(int64_t D, int b) { return b <= 4 ? (D + 1) / 2 : D; }
 
 size_t hdqt_quantize_workspace_size(void) { return kMetaBytes; }
 
+size_t hdqt_workspace_least(int gemm_kind, int64_t M, int64_t K, int64_t N, const hdqt_params_t* params)
+{
+    hdqt_ws_layout_t L;
+    return hdqt_workspace_layout(gemm_kind, M, K, N, params, &L) == HDQT_OK ? least_bytes(L, params) : 0;
+}
+
 int hdqt_workspace_layout(int gemm_kind, int64_t M, int64_t K, int64_t N,
                           const hdqt_params_t* params, hdqt_ws_layout_t* layout)
 {
@@ -1000,9 +1006,18 @@ int hdqt_transpose(const float* src, int64_t batch, int64_t rows, int64_t cols, 
 size_t hdqt_gemm_codes_workspace_size(int64_t RA, int64_t RB, int64_t D, int64_t s)
 {
     if (RA <= 0 || RB <= 0 || D <= 0 || s < 1 || RA >= kMaxDim || RB >= kMaxDim || D >= kMaxDim) return 0;
-    // (the widths are not known here: for packed codes and an accumulator that the expanded form is for)
+    // (whatever the widths: for packed codes and an accumulator that the expanded form is for)
     const size_t slices = partial_bytes(RA, RB, D, s), clamped = expanded_bytes(RA, RB, D, 4, 4, 8, s),
                  plain = expanded_bytes(RA, RB, D, 4, 4, 32, s), expanded = clamped > plain ? clamped : plain;
+    return slices > expanded ? slices : expanded;
+}
+
+size_t hdqt_gemm_codes_workspace_size_for(int64_t RA, int64_t RB, int64_t D, int64_t s, int bA, int bB, int acc_bits,
+                                          int bf16)
+{
+    if (RA <= 0 || RB <= 0 || D <= 0 || s < 1 || RA >= kMaxDim || RB >= kMaxDim || D >= kMaxDim) return 0;
+    if (bA < 2 || bA > 8 || bB < 2 || bB > 8 || check_accumulation(D, s, acc_bits, bA, bB)) return 0;
+    const size_t slices = partial_bytes(RA, RB, D, s), expanded = bf16 ? 0 : expanded_bytes(RA, RB, D, bA, bB, acc_bits, s);
     return slices > expanded ? slices : expanded;
 }
 

@@ -27,7 +27,7 @@ struct Library {
     decltype(&hdqt_codes_pitch) codes_pitch;
     decltype(&hdqt_quantize_workspace_size) quantize_workspace_size;
     decltype(&hdqt_quantize) quantize;
-    decltype(&hdqt_workspace_size) workspace_size;
+    decltype(&hdqt_workspace_size) workspace_size, workspace_least;
     decltype(&hdqt_gemm_fwd) gemm[3];
     decltype(&hdqt_gemm_bwd_input_bf16) gemm_bf16;
     decltype(&hdqt_gemm_bwd_input_masked) gemm_masked;
@@ -214,7 +214,7 @@ PyObject* gemm(PyObject* const* a)
     at::Tensor out, acc, ws;
     if (!given) out = fresh({rows, cols}, type, P);
     if (!given_acc && want_acc) acc = fresh({rows, cols}, at::kInt, P);
-    if (!given_ws) ws = bytes(lib.workspace_size((int)kind, M, K, N, &p), P);
+    if (!given_ws) ws = bytes((bf16 || masked ? lib.workspace_least : lib.workspace_size)((int)kind, M, K, N, &p), P);
     const float *pP = (const float*)address(P), *pQ = (const float*)address(Q), *pm = (const float*)address(mask);
     void *po = given ? address(given) : address(out), *pw = given_ws ? address(given_ws) : address(ws);
     int32_t* pa = (int32_t*)(given_acc ? address(given_acc) : acc.defined() ? address(acc) : nullptr);
@@ -419,6 +419,7 @@ PyObject* bind(PyObject*, PyObject* args)
     find(l.quantize_workspace_size, "hdqt_quantize_workspace_size");
     find(l.quantize, "hdqt_quantize");
     find(l.workspace_size, "hdqt_workspace_size");
+    find(l.workspace_least, "hdqt_workspace_least");
     find(l.gemm[HDQT_GEMM_FWD], "hdqt_gemm_fwd");
     find(l.gemm[HDQT_GEMM_BWD_INPUT], "hdqt_gemm_bwd_input");
     find(l.gemm[HDQT_GEMM_BWD_WEIGHT], "hdqt_gemm_bwd_weight");

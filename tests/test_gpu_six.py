@@ -56,3 +56,13 @@ def test_gemm_takes_a_workspace_without_room_for_it():
             for n in (full, least)]
     torch.cuda.synchronize()
     assert torch.equal(*outs)
+
+
+def test_masked_and_narrow_calls_hold_only_what_they_use():
+    M, K, N = 3105, 2979, 2080
+    op = B.Operand(4, B.ROUND_NEAREST, 1.0, 0)
+    prm = B.Params(had_block=32, acc_bits=8, s=64, seed=0, A=op, B=op)
+    least = B.load().hdqt_workspace_least(B.GEMM_BWD_INPUT, M, K, N, prm.c())
+    G, W, X = (torch.ones(s, device="cuda:0") for s in ((M, N), (K, N), (M, K)))
+    held = lambda **how: B.gemm(B.GEMM_BWD_INPUT, G, W, M, K, N, prm, **how)[2].numel()
+    assert held(mask=X) == held(bf16=True) == least < held() == B.workspace_size(B.GEMM_BWD_INPUT, M, K, N, prm)

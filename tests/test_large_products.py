@@ -1,5 +1,7 @@
 """Which large products of packed codes multiply through the 6-bit matrix instructions, as far as the size of
 their workspace tells (host code): it holds the codes' other form."""
+import ctypes as C
+
 import pytest
 
 from paper_2310_03675_amd import binding as B
@@ -37,3 +39,24 @@ def has_other_form(RA, RB, D, acc, s):
     (8192, 4096, 1024, 32, 256, True), (4096, 8192, 1536, 32, 256, True)])
 def test_which_products_take_the_other_form(RA, RB, D, acc, s, other):
     assert has_other_form(RA, RB, D, acc, s) == other
+
+
+def test_only_calls_that_use_the_other_form_are_told_to_hold_it():
+    lib, (RA, RB, D) = B.load(), (4096, 4096, 4096)
+    size = lambda bA, bB, acc, bf16=0, s=64: lib.hdqt_gemm_codes_workspace_size_for(RA, RB, D, s, bA, bB, acc, bf16)
+    other = (RA + RB) * D * 3 // 4
+    assert size(4, 4, 8) == size(3, 2, 8) == size(4, 4, 32) == other == lib.hdqt_gemm_codes_workspace_size(RA, RB, D, 64)
+    assert size(8, 8, 32) == size(4, 5, 32) == size(4, 4, 12) == size(4, 4, 8, s=32) == size(4, 4, 8, bf16=1) == 0
+    assert size(9, 4, 8) == size(4, 4, 40) == 0 == lib.hdqt_gemm_codes_workspace_size_for(0, RB, D, 64, 4, 4, 8, 0)
+    # a split contraction's slices, whatever the widths
+    for args in ((4, 4, 8, 0), (8, 8, 16, 0), (4, 4, 8, 1)):
+        assert lib.hdqt_gemm_codes_workspace_size_for(1152, 128, 65536, 32, *args) == \
+            lib.hdqt_gemm_codes_workspace_size(1152, 128, 65536, 32) > 0
+    op = B.Operand(4, B.ROUND_NEAREST, 1.0, 0)
+    for M, K, N, more in ((RA, D, RB, other), (512, 576, 128, 0), (65536, 1152, 128, 0)):
+        p = B.Params(had_block=64, acc_bits=8, s=64, seed=0, A=op, B=op).c()
+        for kind in (B.GEMM_FWD, B.GEMM_BWD_INPUT, B.GEMM_BWD_WEIGHT):
+            assert lib.hdqt_workspace_size(kind, M, K, N, C.byref(p)) - lib.hdqt_workspace_least(kind, M, K, N, C.byref(p)) == more
+    assert lib.hdqt_workspace_least(7, 8, 8, 8, C.byref(p)) == 0
+    assert 0 < lib.hdqt_workspace_least(B.GEMM_FWD, 2304, 2048, 4224, C.byref(p)) < lib.hdqt_gemm_fwd_static_max_bytes() < \
+        lib.hdqt_workspace_size(B.GEMM_FWD, 2304, 2048, 4224, C.byref(p))
