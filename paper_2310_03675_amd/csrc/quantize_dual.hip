@@ -733,7 +733,7 @@ __device__ __forceinline__ void line_codes(const float (&v)[kTile], float inv, f
             out[2 * (g & 1) + 1] = pack_bytes(cw + 4);
             if (g & 1) words[lane * kPieces + (g >> 1)] = make_uint4(out[0], out[1], out[2], out[3]);
         } else {
-            out[g & 3] = pack_nibbles(cw);
+            out[g & 3] = pack_nibbles_chain(cw);
             if ((g & 3) == 3) words[lane * kPieces + (g >> 2)] = make_uint4(out[0], out[1], out[2], out[3]);
         }
     }

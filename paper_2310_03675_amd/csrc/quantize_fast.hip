@@ -121,7 +121,7 @@ __device__ __forceinline__ void row_compute(RowRegs<U>& r, const RowCtx& x, int6
                                      sr_halfword(rnd, (uint32_t)i));
         const bool full = !GUARD || (e0 + 8 <= x.total);
         if (q.b <= 4) {
-            const uint32_t w = pack_nibbles(cw);
+            const uint32_t w = pack_nibbles_chain(cw);
             if (full) {
                 reinterpret_cast<uint32_t*>(q.codes)[c] = w;
             } else {
