@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+from launches import launched
 from oracle import capi
 from paper_2310_03675_amd import binding as B
 
@@ -31,10 +32,12 @@ def test_gemm_codes_expanded(RA, RB, D, s, a, kind, b):
     cA, cB = codes(rng, RA, D, kind, b), codes(rng, RB, D, kind, b)
     qA, qB = (torch.from_numpy(capi.pack_codes(c, b)).to("cuda:0") for c in (cA, cB))
     sA, sB = torch.tensor([0.37], device="cuda:0"), torch.tensor([0.0113], device="cuda:0")
-    assert B.load().hdqt_gemm_codes_workspace_size(RA, RB, D, s) > 0      # (the other form is for this shape)
-    out, acc = B.gemm_codes(qA, qB, b, b, sA, sB, D, 32, a, s)
-    out_i, acc_i = B.gemm_codes(qA, qB, b, b, sA, sB, D, 32, a, s,
-                                workspace=torch.empty(256, dtype=torch.uint8, device="cuda:0"))
+    got = {}
+    room = lambda n: torch.empty(n, dtype=torch.uint8, device="cuda:0")
+    for name, ws in (("gemm_six_kernel", room(B.load().hdqt_gemm_codes_workspace_size(RA, RB, D, s))), ("gemm_i4_kernel", room(256))):
+        ran = launched(lambda: got.update({name: B.gemm_codes(qA, qB, b, b, sA, sB, D, 32, a, s, workspace=ws)}))
+        assert name in ran and (name == "gemm_six_kernel") == ("gemm_six_kernel" in ran), ran
+    (out, acc), (out_i, acc_i) = got.values()
     torch.cuda.synchronize()
     assert torch.equal(acc, acc_i) and torch.equal(out, out_i)
     ii, jj = rng.integers(0, RA, 512), rng.integers(0, RB, 512)
@@ -52,9 +55,10 @@ def test_gemm_takes_a_workspace_without_room_for_it():
     full = B.workspace_size(B.GEMM_FWD, M, K, N, prm)
     least = B.workspace_layout(B.GEMM_FWD, M, K, N, prm).acc + 256
     assert least < full
-    outs = [B.gemm(B.GEMM_FWD, X, W, M, K, N, prm, workspace=torch.empty(n, dtype=torch.uint8, device="cuda:0"))[0]
-            for n in (full, least)]
-    torch.cuda.synchronize()
+    outs = []
+    for n, name in ((full, "gemm_six_kernel"), (least, "gemm_i4_kernel")):
+        ws = torch.empty(n, dtype=torch.uint8, device="cuda:0")
+        assert name in launched(lambda: outs.append(B.gemm(B.GEMM_FWD, X, W, M, K, N, prm, workspace=ws)[0]))
     assert torch.equal(*outs)
 
 
