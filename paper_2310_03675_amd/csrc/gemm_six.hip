@@ -12,10 +12,10 @@
 // a row and goes to LDS without passing through registers.  gemm_six_kernel: a workgroup has a 128 x 128 tile of the
 // output, eight waves of 64 x 32, stages double-buffered in LDS.
 //
-// What bounds it: the LDS (73 KB of fragment reads and 24 KB of stage per workgroup and stage, 1600 cycles of a round of
-// two workgroups at the 118 bytes a clock it delivers) and, where tiles are clamped, vector issue and matrix pipe one
-// after the other (4 x 84 x 4 + 4 x 4 x 32 = 1860); measured 1780.  8192 cubed with tiles of 64: gemm_i4_kernel 850 to 930 us,
-// this one 480 to 510 and expand_kernel 30; without clamps 565, and 320 and 30.
+// What bounds it (counters, 8192 cubed): where tiles are clamped, vector issue and matrix pipe one after the other, busy in 75 and
+// 28 % of the cycles; the fragment reads take 31 % of the LDS's.  Without clamps nothing is busy all the time, the LDS in
+// 53 % of the cycles, the matrix pipe in 48: the waves spend 60 % of theirs waiting for the next stage and at its barrier.
+// 8192 cubed with tiles of 64: gemm_i4_kernel 850 to 930 us, this one 480 to 540 and expand_kernel 34; without clamps 565, and 320 to 350 and 34.
 //
 // Clamp of a 64-code tile to 8 bits: the sum arrives as (sum + 128.5) / 256, v_cvt_pknorm_u16_f32 clamps two of them
 // to [0, 1] and leaves clamp(sum) + 128 in the high byte of each half ((q + 0.5) * 65535 / 256 lies in
@@ -216,6 +216,8 @@ bool gemm_six_shape(int64_t RA, int64_t RB, int64_t D)
 // and if not in short contractions of wide outputs (2048 x 32768 x 512 74 / 82, 2048 x 16384 x 1024 57 / 60, but 32768 x 2048 x 512 80 / 74; 16384 x 2048 x 1024
 // 55.7 / 55.9).  Of 612 products (339 clamped) up to 15 and 40 us beyond the estimate, each timed four times, it takes 505; ten of these are
 // 1 to 3 % slower than with the integer kernel, which without the rule for half rounds were 39, up to 14 %.
+// (Tiles of 128 or 256 in 8-bit accumulators, two and four chained instructions and fewer clamps, have no instance:
+// nothing multiplies large products in them so far.)
 bool gemm_six_eligible(const GemmArgs& g)
 {
     if (!gemm_six_shape(g.RA, g.RB, g.D)) return false;

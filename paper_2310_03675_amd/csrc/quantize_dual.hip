@@ -661,8 +661,9 @@ __device__ __forceinline__ void dual_codes(Tile& t, const DualCtx& x, int64_t ro
 // then a column (64 rows), so that both transforms and the packing stay inside the lane.  The patch is in LDS
 // anyway, and gathering it twice is cheaper than pairing lanes: an addition of two registers takes two
 // cycles a wave here, one with a lane move four and a lane swap eight (measured at four waves per SIMD).
-// Pass 2 of 262144 x 576 from 256 x 64 x 32 x 32 136 -> 102 us, of 32768 x 320 from 256 x 64 x 1 x 128 18.7 -> 17.1.
-// What bounds it is still vector issue (1400 instructions a tile), with the LDS busy 40 % of the time.  Not for
+// Pass 2 of 262144 x 576 from 256 x 64 x 32 x 32 136 -> 99 us, of 32768 x 320 from 256 x 64 x 1 x 128 18.7 -> 16.4.
+// What bounds it is still vector issue: 1550 instructions a tile keep the ALU busy in all of the kernel's cycles (counters), the LDS
+// is busy in 46 % of them, a quarter of that with bank conflicts.  Not for
 // an ordinary source: its tile would have to go through LDS too, 17 KB a wave, which leaves two waves per SIMD
 // (the 65536 x 1152 x 128 step 259 -> 265 us).
 
