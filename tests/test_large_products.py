@@ -25,8 +25,8 @@ def test_products_whose_grids_cannot_be_launched_stay_with_the_integer_kernel(RA
 
 def has_other_form(RA, RB, D, acc, s):
     op = B.Operand(4, B.ROUND_NEAREST, 1.0, 0)
-    L = B.workspace_layout(B.GEMM_FWD, RA, D, RB, B.Params(had_block=64, acc_bits=acc, s=s, seed=0, A=op, B=op))
-    return L.total - L.acc >= 96 * 256 * 512 // 128      # (the codes of 256 rows at least)
+    prm = B.Params(had_block=64, acc_bits=acc, s=s, seed=0, A=op, B=op)
+    return B.workspace_size(B.GEMM_FWD, RA, D, RB, prm) > B.load().hdqt_workspace_least(B.GEMM_FWD, RA, D, RB, C.byref(prm.c()))
 
 
 # products timed with either kernel, on both sides of the line; those that fill half rounds of 512 tiles come later
