@@ -248,6 +248,9 @@ bool gemm_six_eligible(const GemmArgs& g);
 int64_t gemm_six_bytes(const GemmArgs& g);
 hipError_t launch_gemm_six(const GemmArgs& g, void* frags, hipStream_t stream);
 bool gemm_fast_eligible(const GemmArgs& g);
+// products of codes with a byte each that fill the chip with whole tiles (gemm_bytes.hip)
+bool gemm_bytes_eligible(const GemmArgs& g);
+hipError_t launch_gemm_bytes(const GemmArgs& g, hipStream_t stream);
 hipError_t launch_gemm_fast(const GemmArgs& g, hipStream_t stream);
 const char* kernel_name(int id);
 bool profiling_enabled();
