@@ -245,12 +245,18 @@ hipError_t launch_gemm_small(const GemmArgs* gs, int n, hipStream_t stream);
 // need for the codes in that form (gemm_six.hip)
 bool gemm_six_shape(int64_t RA, int64_t RB, int64_t D);
 bool gemm_six_eligible(const GemmArgs& g);
+bool gemm_six_pays(const GemmArgs& g);       // (of the eligible ones)
 int64_t gemm_six_bytes(const GemmArgs& g);
 hipError_t launch_gemm_six(const GemmArgs& g, void* frags, hipStream_t stream);
 bool gemm_fast_eligible(const GemmArgs& g);
+// whether gemm_i4_kernel asks of every tile if it can saturate (EPI_CERT8_S32)
+bool gemm_fast_tests_tiles(const GemmArgs& g);
 // products of codes with a byte each that fill the chip with whole tiles (gemm_bytes.hip)
 bool gemm_bytes_eligible(const GemmArgs& g);
 hipError_t launch_gemm_bytes(const GemmArgs& g, hipStream_t stream);
+// the same of packed codes, in tiles whose clamps are known to act or not to (gemm_packed.hip)
+bool gemm_packed_eligible(const GemmArgs& g);
+hipError_t launch_gemm_packed(const GemmArgs& g, hipStream_t stream);
 hipError_t launch_gemm_fast(const GemmArgs& g, hipStream_t stream);
 const char* kernel_name(int id);
 bool profiling_enabled();

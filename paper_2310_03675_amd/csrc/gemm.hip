@@ -419,6 +419,7 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t stream)
 {
     if (g.fold) return launch_gemm_fold(g, stream);
     if (gemm_bytes_eligible(g)) return launch_gemm_bytes(g, stream);
+    if (gemm_packed_eligible(g)) return launch_gemm_packed(g, stream);
     if (gemm_fast_eligible(g)) return launch_gemm_fast(g, stream);
     const dim3 grid((unsigned)((g.RB + BN - 1) / BN), (unsigned)((g.RA + BM - 1) / BM),
                     (unsigned)g.splits);

@@ -1312,17 +1312,14 @@ static bool narrow_tiles(const GemmArgs& g)
 // output channels) it loses 5 to 10 % where it fails and gains little where it holds.  The
 // 128 x 64 tile has no such instance either (half the clamps per wave to save, the same test
 // to pay: 4 % slower on the 262144 x 576 x 64 layer).
-// One more case, by measurement alone: a streamed output that a workgroup walks across for
-// eight column tiles or more (the input gradient of the 65536 x 1152 x 128 layer: one stage
-// per tile, codes that fail the test, so the workgroups give it up at their second tile) runs
-// 5 % faster in these instances' given-up state than in EPI_SAT8_S32 -- 68 against 72 us, in
-// six interleaved runs; with fewer column tiles (576 or 320 columns) it is 5 to 7 % slower.
-static bool cert_tiles(const GemmArgs& g, int64_t n_ct)
+// Where the test holds nearly everywhere (products with a rectifier's output: 65536 x 128 x 1152 20.0 us) this beats
+// lines_gemm_i4_kernel, which clamps every tile (24.7); where it fails it does not (24.3 / 24.9, 4096 cubed 136 / 125), which
+// only the codes tell.
+bool gemm_fast_tests_tiles(const GemmArgs& g)
 {
-    if (g.out_bf16 || g.bA > 4 || g.bB > 4 || g.mask_src || flexible(g)) return false;
+    if (g.RB <= 64 || g.out_bf16 || g.bA > 4 || g.bB > 4 || g.mask_src || flexible(g)) return false;
     if (g.acc_hi != 127 || g.s != 32 || g.tiles_per_split > 255) return false;
-    if (g.tiles_per_split * g.s > 4 * KS_LONG) return true;
-    return g.stream_out && n_ct >= 8 && g.D >= KS_LONG;
+    return g.tiles_per_split * g.s > 4 * KS_LONG;
 }
 
 // The same test in front of the int16-saturation instances (EPI_CERT16_S32): packed codes, at
@@ -1424,6 +1421,16 @@ hipError_t launch_gemm_fast(const GemmArgs& g_in, hipStream_t stream)
         else                                                                                         \
             hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, false, kWaves, false>), grid, block, 0, stream, g); \
     } while (0)
+// what lines_gemm_i4_kernel leaves: bfloat16 outputs, and masks behind lines that end inside 32 codes
+#define HDQT_LAUNCH_I4_REST(EPI)                                                                      \
+    do {                                                                                             \
+        const dim3 block(64 * kWaves);                                                               \
+        if (masked && g.stream_out) hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, true, kWaves, false, false, false, true>), grid, block, 0, stream, g); \
+        else if (masked) hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, false, kWaves, false, false, false, true>), grid, block, 0, stream, g); \
+        else if (!g.out_bf16) return hipErrorInvalidConfiguration;                                   \
+        else if (g.stream_out) hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, true, kWaves, true>), grid, block, 0, stream, g); \
+        else hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, false, kWaves, true>), grid, block, 0, stream, g); \
+    } while (0)
 #define HDQT_LAUNCH_SAT16(EPI, WIDE)                                                                  \
     do {                                                                                             \
         const dim3 block(64 * kWaves);                                                               \
@@ -1482,17 +1489,18 @@ hipError_t launch_gemm_fast(const GemmArgs& g_in, hipStream_t stream)
             if (g.stream_out) hipLaunchKernelGGL((gemm_i4_kernel<EPI_GENERIC, KS_LONG, true, kWaves, false, true>), grid, block, 0, stream, g);
             else hipLaunchKernelGGL((gemm_i4_kernel<EPI_GENERIC, KS_LONG, false, kWaves, false, true>), grid, block, 0, stream, g);
         }
-    } else if (s32 && !masked && !narrow && cert_tiles(g, n_ct)) {
+    } else if (gemm_fast_tests_tiles(g)) {
         const dim3 block(64 * kWaves);
         if (g.stream_out)
             hipLaunchKernelGGL((gemm_i4_kernel<EPI_CERT8_S32, KS_LONG, true, kWaves, false>), grid, block, 0, stream, g);
         else
             hipLaunchKernelGGL((gemm_i4_kernel<EPI_CERT8_S32, KS_LONG, false, kWaves, false>), grid, block, 0, stream, g);
-    } else if (s32) HDQT_LAUNCH_I4(EPI_SAT8_S32);
-    else if (sat8_path(g)) HDQT_LAUNCH_I4(EPI_SAT8_S64);
+    } else if (s32) HDQT_LAUNCH_I4_REST(EPI_SAT8_S32);
+    else if (sat8_path(g)) HDQT_LAUNCH_I4_REST(EPI_SAT8_S64);
     else if (g.s % KS_LONG == 0) HDQT_LAUNCH_I4(EPI_STAGES);
     else HDQT_LAUNCH_I4(EPI_GENERIC);
 #undef HDQT_LAUNCH_I4
+#undef HDQT_LAUNCH_I4_REST
 #undef HDQT_LAUNCH_SAT16
     return hipGetLastError();
 }

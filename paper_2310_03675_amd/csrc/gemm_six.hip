@@ -15,13 +15,14 @@
 // What bounds it (counters, 8192 cubed): where tiles are clamped, vector issue and matrix pipe one after the other, busy in 75 and
 // 28 % of the cycles; the fragment reads take 31 % of the LDS's.  Without clamps nothing is busy all the time, the LDS in
 // 53 % of the cycles, the matrix pipe in 48: the waves spend 60 % of theirs waiting for the next stage and at its barrier.
-// 8192 cubed with tiles of 64: gemm_i4_kernel 850 to 930 us, this one 480 to 540 and expand_kernel 34; without clamps 565, and 320 to 350 and 34.
+// 8192 cubed with tiles of 64: gemm_i4_kernel 850 to 930 us, lines_gemm_i4_kernel 683, this one 470 to 540 and expand_kernel 34; without
+// clamps 565, 454, and 320 to 350 and 34.  (Three stages in LDS, and waves of 64 x 64, change nothing where tiles are clamped.)
 //
 // Clamp of a 64-code tile to 8 bits: the sum arrives as (sum + 128.5) / 256, v_cvt_pknorm_u16_f32 clamps two of them
 // to [0, 1] and leaves clamp(sum) + 128 in the high byte of each half ((q + 0.5) * 65535 / 256 lies in
 // [256 q + 127, 256 q + 128] for q < 256), and v_msad_u8 adds 255 minus those two bytes to the total: one vector
 // instruction per sum, as in gemm_i4_kernel, but none on the matrix pipe (its v_dot4c is).
-#include "common.hpp"
+#include "gemm_lines.hpp"
 
 namespace hdqt {
 
@@ -40,11 +41,9 @@ struct SixArgs {
     int64_t panel_bytes;             // of one panel: stages * kStageBytes
     uint32_t stages, n_rt, n_ct, per_xcd;
     Divisor group;                   // 8 * n_ct tiles
-    int64_t RA, RB;
     const float *scaleA, *scaleB;
     float inv_n;
-    float* out;
-    int32_t* acc_out;
+    lines::OutArgs to;
 };
 
 struct ExpandArgs {
@@ -138,6 +137,7 @@ __global__ __launch_bounds__(kThreads, 4) void gemm_six_kernel(SixArgs g)
     v16f base;
 #pragma unroll
     for (int i = 0; i < 16; ++i) base[i] = SAT ? 128.5f / 256.0f : 0.0f;
+    const float scale = *g.scaleA * *g.scaleB * g.inv_n;
     uint32_t tot[2][16] = {};
     v16f sum[2] = {base, base};
     auto stage = [&](uint32_t s, int buf) {
@@ -174,24 +174,13 @@ __global__ __launch_bounds__(kThreads, 4) void gemm_six_kernel(SixArgs g)
         if (s + 1 < g.stages) stage(s + 1, 1);
     }
 
-    const float scale = *g.scaleA * *g.scaleB * g.inv_n;
-    const int64_t row0 = (int64_t)rt * kPanel + wr * 64 + 4 * (lane >> 5), col = (int64_t)ct * kPanel + wc * 32 + (lane & 31);
-    if (col >= g.RB) return;
+    // (each of the 2 * stages tiles added 255 - (clamped sum + 128))
+    int acc[2][1][16];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int64_t row = row0 + 32 * i + 8 * (r >> 2) + (r & 3);
-            if (row >= g.RA) continue;
-            // (each of the 2 * stages tiles added 255 - (clamped sum + 128))
-            const int acc = SAT ? (int)(254u * g.stages - tot[i][r]) : (int)(sum[i][r] * 64.0f);
-            if (g.out) {
-                const float v = (float)acc * scale;
-                if (STREAM) __builtin_nontemporal_store(v, g.out + row * g.RB + col);
-                else g.out[row * g.RB + col] = v;
-            }
-            if (g.acc_out) g.acc_out[row * g.RB + col] = acc;
-        }
+        for (int r = 0; r < 16; ++r) acc[i][0][r] = SAT ? (int)(254u * g.stages - tot[i][r]) : (int)(sum[i][r] * 64.0f);
+    lines::write_totals<STREAM, false, 2, 1>(g.to, 0, (int64_t)rt * kPanel + wr * 64, (int64_t)ct * kPanel + wc * 32, lane, scale, acc);
 }
 
 } // namespace
@@ -207,17 +196,10 @@ bool gemm_six_shape(int64_t RA, int64_t RB, int64_t D)
     return D % 32 == 0 && RA >= 256 && RB >= 256 && D >= 512;      // (rows of codes of whole 16-byte pieces)
 }
 
-// Against the integer kernel it saves 0.75 us per 10^9 multiply-adds where tiles are clamped and 0.44 where they are
-// not, and pays for the launch of expand_kernel and its 1.25 bytes per code.  The line is where the two meet (us, inside
-// a graph, integer kernel / this one with expand_kernel): clamped 8192 x 8192 x 8192 771 / 520, 4096 x 4096 x 4096 107 / 80, 8192 x 1024 x 8192
-// 106 / 82, 1920 x 11136 x 544 36.0 / 36.2, 24576 x 768 x 768 35.4 / 36.6; not clamped 558 / 363, 81 / 68, 78 / 63, 4096 x 4096 x 2048 46.5 / 45.7, 16384 x
-// 1024 x 2048 46.2 / 47.1, 4864 x 18816 x 512 96 / 92.  Later where the tiles fill half rounds of 512 (two to a CU), which is where the integer
-// kernel wastes nothing: by 1.4 us a round if they are clamped (1536 x 32768 x 512 63.4 / 67.1, 1024 x 32768 x 512 46.0 / 51.7, 2048 x 4096 x 2048 33.1 / 34.0),
-// and if not in short contractions of wide outputs (2048 x 32768 x 512 74 / 82, 2048 x 16384 x 1024 57 / 60, but 32768 x 2048 x 512 80 / 74; 16384 x 2048 x 1024
-// 55.7 / 55.9).  Of 612 products (339 clamped) up to 15 and 40 us beyond the estimate, each timed four times, it takes 505; ten of these are
-// 1 to 3 % slower than with the integer kernel, which without the rule for half rounds were 39, up to 14 %.
-// (Tiles of 128 or 256 in 8-bit accumulators, two and four chained instructions and fewer clamps, have no instance:
-// nothing multiplies large products in them so far.)
+// The products whose workspaces hold the codes' other form.  (An estimate against gemm_i4_kernel, which multiplied them
+// otherwise when the line was drawn; what is held is part of a caller's sizes and stays.  Of those, gemm_six_pays says which are
+// multiplied here.  Tiles of 128 or 256 in 8-bit accumulators, two and four chained instructions and fewer clamps, have no
+// instance: nothing multiplies large products in them so far.)
 bool gemm_six_eligible(const GemmArgs& g)
 {
     if (!gemm_six_shape(g.RA, g.RB, g.D)) return false;
@@ -239,6 +221,20 @@ bool gemm_six_eligible(const GemmArgs& g)
            4 * (n_rt + n_ct) * ((stages + 1) / 2) * kExpandThreads < ((int64_t)1 << 32);
 }
 
+// Against lines_gemm_i4_kernel, from 100 products of 12 to 120 10^9 multiply-adds and 2^39 (us, integer kernel / this one with
+// expand_kernel): what it saves grows with the products, what it pays with the codes that are laid out anew and with the outputs,
+// which it stores in pieces of 128 bytes (the other: 256).  Clamped 8192 cubed 683 / 508, 4096 cubed 88 / 78, 4137 x 4005 x 2080
+// 60 / 53.5, 4736 x 2944 x 1216 32.3 / 34.0, 2432 x 14976 x 512 32.9 / 44.4; not clamped 8192 cubed 454 / 352, 10752 x 2048 x 3648
+// 84 / 71, 4137 x 4005 x 2080 44.6 / 42.8, 4096 cubed 64.5 / 67.9, 3712 x 13568 x 768 47.1 / 63.9.  Of the 100 four fall on the
+// wrong side, by up to 5 us (4096 x 4096 x 2048 not clamped 35.0 / 40.2).
+bool gemm_six_pays(const GemmArgs& g)
+{
+    const double codes = 1e-6 * (double)(g.RA + g.RB) * (double)g.D, outputs = 1e-6 * (double)g.RA * (double)g.RB;
+    const double products = 1e-3 * outputs * (double)g.D;
+    return g.acc_hi == 127 ? 0.382 * products - 3.3 - 0.11 * codes - 0.204 * outputs > 0.0
+                           : 0.256 * products - 2.9 - 0.123 * codes - 0.197 * outputs > 0.0;
+}
+
 hipError_t launch_gemm_six(const GemmArgs& g, void* frags, hipStream_t stream)
 {
     SixArgs k{};
@@ -248,8 +244,8 @@ hipError_t launch_gemm_six(const GemmArgs& g, void* frags, hipStream_t stream)
     k.per_xcd = (k.n_rt * k.n_ct + 7) / 8;
     k.group = make_divisor(8 * k.n_ct);
     k.fA = static_cast<uint8_t*>(frags); k.fB = k.fA + k.n_rt * k.panel_bytes;
-    k.RA = g.RA; k.RB = g.RB; k.scaleA = g.scaleA; k.scaleB = g.scaleB; k.inv_n = g.inv_n;
-    k.out = g.out; k.acc_out = g.acc_out;
+    k.to = lines::out_args(g);
+    k.scaleA = g.scaleA; k.scaleB = g.scaleB; k.inv_n = g.inv_n;
     ExpandArgs e{};
     e.codes[0] = g.qA; e.codes[1] = g.qB;
     e.frags[0] = static_cast<uint8_t*>(frags); e.frags[1] = e.frags[0] + k.n_rt * k.panel_bytes;

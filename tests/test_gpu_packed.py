@@ -1,0 +1,61 @@
+"""Products of packed codes through the kernel that brings them straight to LDS: against the oracle on
+sampled outputs, at the edges of its tiles and stages, in parts, behind a mask and written past the caches."""
+import numpy as np
+import pytest
+import torch
+
+from launches import launched
+from oracle import capi
+from paper_2310_03675_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+SA, SB = np.float32(0.37), np.float32(0.0113)
+DQ = np.float32(np.float32(SA * SB) * np.float32(1 / 8))
+
+
+def codes(rng, R, D, kind, b):
+    lo, hi = -(1 << (b - 1)), (1 << (b - 1)) - 1
+    if kind == "lowest":
+        return np.full((R, D), lo, dtype=np.int8)
+    if kind == "uniform":
+        return rng.integers(lo, hi + 1, (R, D), dtype=np.int8)
+    return np.clip(np.rint(rng.standard_normal((R, D)) * 1.8), lo, hi).astype(np.int8)
+
+
+# rows and columns that end inside a tile and a block of 32; contractions that end inside a stage of 128, a tile and 32 codes
+# (8, 40, 136, 264), of one stage and of many; up to 64 columns, unsplit and in parts whose totals fit 16 bits (27 x 64,
+# 300 x 64) and do not (tiles that cannot saturate); 512 columns in whole lines, 135 MB
+@pytest.mark.parametrize("RA,RB,D", [(4100, 1290, 128), (30001, 130, 136), (12544, 700, 8), (2214, 10688, 40),
+                                     (131001, 63, 264), (27, 64, 131072), (300, 64, 16456), (66000, 512, 96)])
+@pytest.mark.parametrize("s,a", [(32, 8), (64, 8), (32, 32)])
+@pytest.mark.parametrize("kind,b", [("gauss", 4), ("uniform", 3), ("lowest", 4)])
+def test_gemm_codes_packed(RA, RB, D, s, a, kind, b):
+    print(f"gemm_codes RA={RA} RB={RB} D={D} s={s} a={a} {kind} b={b}", flush=True)
+    rng = np.random.default_rng(RA + D + s)
+    cA, cB = codes(rng, RA, D, kind, b), codes(rng, RB, D, kind, b)
+    qA, qB = (torch.from_numpy(capi.pack_codes(c, b)).to("cuda:0") for c in (cA, cB))
+    sA, sB = torch.tensor([SA], device="cuda:0"), torch.tensor([SB], device="cuda:0")
+    out, acc = torch.full((RA + 1, RB), -1.0, device="cuda:0"), torch.empty(RA, RB, dtype=torch.int32, device="cuda:0")
+    ran = launched(lambda: B.gemm_codes(qA, qB, b, b, sA, sB, D, 8, a, s, out=out[:RA], acc=acc))
+    torch.cuda.synchronize()
+    assert "lines_gemm_i4_kernel" in ran, ran
+    assert bool((out[RA] == -1.0).all())                 # nothing behind the output
+    ii, jj = rng.integers(0, RA, 1024), rng.integers(0, RB, 1024)
+    ii[:2], jj[:2] = (0, RA - 1), (0, RB - 1)
+    want = capi.tiled_matmul_sampled(cA, cB, s, a, ii, jj)
+    assert np.array_equal(acc.cpu().numpy()[ii, jj], want)
+    assert np.array_equal(out.cpu().numpy()[ii, jj], want.astype(np.float32) * DQ)
+
+
+@pytest.mark.parametrize("M,K,N", [(4099, 1153, 128), (131001, 60, 96), (66000, 512, 64)])
+def test_masked_input_gradient(M, K, N):
+    g = torch.Generator(device="cuda:0").manual_seed(5)
+    G, W, X = (torch.randn(s, generator=g, device="cuda:0") for s in ((M, N), (K, N), (M, K)))
+    X[:, ::7] = 0.0
+    op = B.Operand(4, B.ROUND_NEAREST, 1.0, 0)
+    prm = B.Params(had_block=32, acc_bits=8, s=32, seed=0, A=op, B=op)
+    got, plain = [], []
+    ran = launched(lambda: got.append(B.gemm(B.GEMM_BWD_INPUT, G, W, M, K, N, prm, mask=X)[0]))
+    assert "lines_gemm_i4_kernel" in ran and "relu_mask" not in ran, ran
+    plain.append(B.gemm(B.GEMM_BWD_INPUT, G, W, M, K, N, prm)[0])
+    assert torch.equal(got[0], torch.where(X > 0, plain[0], torch.zeros_like(plain[0])))
