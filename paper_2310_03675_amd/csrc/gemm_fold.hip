@@ -195,15 +195,27 @@ __global__ __launch_bounds__(256 * BLOCKS, 4) void gemm_fold_kernel(GemmArgs g)
 
     if (!live) return;
     const float dq = (g.scaleA[0] * g.scaleB[0]) * g.inv_n;
-    const int64_t o0 = (int64_t)img * g.fC * hw + at;
+    // from the workgroup's first image and channel: less than (kPixels + hw) * fC elements
+    const uint32_t first = (uint32_t)((int64_t)blockIdx.x * kPixels), img0 = first / hw;
+    const int64_t base = ((int64_t)img0 * g.fC + channel0) * hw;
+    const int64_t off = (int64_t)(img - img0) * g.fC * hw + at + 4 * half * (int64_t)hw;
+    auto value = [&](int c, int r) { return (float)(SAT8 ? total[c][r] : total[c][r] >> 8) * dq; };
+    auto channel = [](int c, int r) { return 32 * c + 8 * (r >> 2) + (r & 3); };       // (of the lower half's lanes)
+    if (channel0 + kChannels <= g.fC && !g.mask_src && (int64_t)(kPixels + hw) * g.fC < ((int64_t)1 << 31)) {
+        // Nothing is tested per element and a store's address is a uniform one plus the lane's: the stores are one run.
+#pragma unroll
+        for (int c = 0; c < kBlocks; ++c)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) (g.out + base + (int64_t)channel(c, r) * hw)[(uint32_t)off] = value(c, r);
+        return;
+    }
 #pragma unroll
     for (int c = 0; c < kBlocks; ++c)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-            const int64_t ch = channel0 + 32 * c + 8 * (r >> 2) + (r & 3) + 4 * half;
-            if (ch >= g.fC) continue;
-            const int64_t o = o0 + ch * hw;
-            float f = (float)(SAT8 ? total[c][r] : total[c][r] >> 8) * dq;
+            if (channel0 + channel(c, r) + 4 * half >= g.fC) continue;
+            const int64_t o = base + (int64_t)channel(c, r) * hw + off;
+            float f = value(c, r);
             if (g.mask_src && !(g.mask_src[o] > 0.0f)) f = 0.0f;
             g.out[o] = f;
         }
