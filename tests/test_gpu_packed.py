@@ -59,3 +59,39 @@ def test_masked_input_gradient(M, K, N):
     assert "lines_gemm_i4_kernel" in ran and "relu_mask" not in ran, ran
     plain.append(B.gemm(B.GEMM_BWD_INPUT, G, W, M, K, N, prm)[0])
     assert torch.equal(got[0], torch.where(X > 0, plain[0], torch.zeros_like(plain[0])))
+
+
+# Tiles asked whether they can saturate, where there are more than 512 workgroups of them: codes in patches that pass and that do
+# not, the first stage passing (the test goes on) and failing (it is given up behind the first), every tile saturating upwards
+# (255 of them), contractions that end inside a stage and a pair of tiles
+@pytest.mark.parametrize("RA,RB,D", [(66001, 128, 1152), (4100, 4130, 736), (3000, 3001, 544), (8300, 1030, 8160)])
+@pytest.mark.parametrize("kind", ["patches", "first passes", "first fails", "upwards"])
+def test_tiles_that_are_asked(RA, RB, D, kind):
+    print(f"gemm_codes RA={RA} RB={RB} D={D} {kind}", flush=True)
+    rng = np.random.default_rng(RA + D)
+
+    def make(R):
+        if kind == "upwards":
+            return np.full((R, D), 7, dtype=np.int8)
+        full = rng.integers(-8, 8, (R, D), dtype=np.int8)
+        small = rng.integers(-1, 2, (R, D), dtype=np.int8)
+        which = rng.random((-(-R // 96), -(-D // 80))) < 0.3
+        which = np.repeat(np.repeat(which, 96, 0), 80, 1)[:R, :D]
+        if kind == "first fails":
+            which[:, :128] = True
+        else:
+            which[:, :128] = False if kind == "first passes" else which[:, :128] & (rng.random() < 0.5)
+        return np.where(which, full, small).astype(np.int8)
+
+    cA, cB = make(RA), make(RB)
+    qA, qB = (torch.from_numpy(capi.pack_codes(c, 4)).to("cuda:0") for c in (cA, cB))
+    sA, sB = torch.tensor([SA], device="cuda:0"), torch.tensor([SB], device="cuda:0")
+    got = []
+    ran = launched(lambda: got.append(B.gemm_codes(qA, qB, 4, 4, sA, sB, D, 8, 8, 32)))
+    assert "lines_gemm_i4_kernel<3" in ran, ran
+    ii, jj = rng.integers(0, RA, 4096), rng.integers(0, RB, 4096)
+    ii[:2], jj[:2] = (0, RA - 1), (0, RB - 1)
+    want = capi.tiled_matmul_sampled(cA, cB, 32, 8, ii, jj)
+    out, acc = got[0]
+    assert np.array_equal(acc.cpu().numpy()[ii, jj], want)
+    assert np.array_equal(out.cpu().numpy()[ii, jj], want.astype(np.float32) * DQ)
