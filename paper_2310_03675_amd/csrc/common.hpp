@@ -42,6 +42,7 @@ struct QuantArgs {
     QMeta* meta;            // device
     uint8_t* codes;         // device, packed, contraction-major
     float* scale_out;       // device, may alias &meta->scale, may be null
+    int pad;                // bytes of zeros behind a line of codes (any-shape kernel only)
 };
 
 // n / d for any 32-bit n, by multiplication (Granlund and Montgomery, PLDI'94, with the round-up
@@ -107,6 +108,7 @@ struct DualArgs {
     uint8_t* codes_col;     // [cols, rows/2]
     float* scale_row_out;   // may be null
     float* scale_col_out;
+    int pad_row, pad_col;   // of its halves, where the any-shape kernel has them
     int profile_tag;        // which tensor of the step this is (timing table only): 0 none, 1 X, 2 W, 3 G
     // Convolution source (conv != 0): T points at an activation [batch, C, H, W] and the
     // tensor that is quantized is its im2col matrix for a kh x kw window, stride 1, zero
@@ -333,7 +335,7 @@ __device__ __forceinline__ AnyTensor whole_args(const AnyTensor& x)
     const AnyTensor t = x;
     asm volatile("" ::"s"(t.q.T), "s"(t.q.rows), "s"(t.q.cols), "s"(t.q.axis), "s"(t.q.log2n), "s"(t.q.b), "s"(t.q.stochastic),
                  "s"(t.q.clip), "s"(t.q.tensor_id), "s"(t.q.seed_lo), "s"(t.q.seed_hi), "s"(t.q.meta), "s"(t.q.codes),
-                 "s"(t.q.scale_out), "s"(t.p.count), "s"(t.p.dense), "s"(t.p.wc), "s"(t.p.per.d), "s"(t.p.per.mul),
+                 "s"(t.q.scale_out), "s"(t.q.pad), "s"(t.p.count), "s"(t.p.dense), "s"(t.p.wc), "s"(t.p.per.d), "s"(t.p.per.mul),
                  "s"(t.p.per.sh1), "s"(t.p.per.sh2));
     return t;
 }

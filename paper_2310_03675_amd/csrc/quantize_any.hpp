@@ -101,7 +101,16 @@ struct Eight {
     float v[8];
     int64_t from, to;
     int count;                           // of them inside the tensor
+    bool last;                           // of a line
 };
+
+// The zeros behind a line whose codes are padded (a few bytes of one thread in a line's many).
+__device__ __forceinline__ void zeros_behind(const QuantArgs& q, const Eight& t)
+{
+    if (!t.last || !t.count) return;
+    uint8_t* dst = q.codes + t.to + (q.b <= 4 ? (t.count + 1) >> 1 : t.count);
+    for (int k = 0; k < q.pad; ++k) dst[k] = 0;
+}
 
 // Those of a workgroup's piece of the tensor, loads only.
 template <int AXIS>
@@ -136,6 +145,7 @@ __device__ __forceinline__ void load8(Eight& t, const QuantArgs& q, const AnyPla
             t.v[7] = 0.0f;
         }
         t.to = line * pitch + (int64_t)j * per;
+        t.last = j + 1 == p.per.d;
     } else {
         const uint32_t across = divide((uint32_t)piece, p.per);
         const int64_t by = across, bx = (uint32_t)piece - across * p.per.d;
@@ -154,6 +164,7 @@ __device__ __forceinline__ void load8(Eight& t, const QuantArgs& q, const AnyPla
         for (int i = 0; i < 8; ++i) t.v[i] = src[(i < t.count ? i : 0) * q.cols];
         t.from = (row + cg) * q.cols + col0;
         t.to = col * pitch + (row >> 3) * per;
+        t.last = row + 8 >= q.rows;
     }
 }
 
@@ -260,7 +271,7 @@ __device__ __forceinline__ float largest8(const Eight& t, float amax)
 template <bool QUANT>
 __device__ __forceinline__ float block(const QuantArgs& q, const AnyPlan& p, int local, float* lds)
 {
-    const int64_t pitch = q.b <= 4 ? ((q.axis ? q.cols : q.rows) + 1) >> 1 : (q.axis ? q.cols : q.rows);
+    const int64_t pitch = (q.b <= 4 ? ((q.axis ? q.cols : q.rows) + 1) >> 1 : (q.axis ? q.cols : q.rows)) + q.pad;
     Maxima maxima{};
     if (QUANT) maxima = fetch_maxima(q.meta, p.dense);
     Eight t;
@@ -276,6 +287,7 @@ __device__ __forceinline__ float block(const QuantArgs& q, const AnyPlan& p, int
     const Scaling sc = scaling_of(maxima, q.meta, q.clip, q.b, p.dense);
     publish(q, sc, local);
     if (t.count) emit(q, t.v, rnd, sc.inv, q.codes + t.to, t.count);
+    if (q.pad) zeros_behind(q, t);
     return 0.0f;
 }
 
@@ -286,7 +298,7 @@ __device__ __forceinline__ float block(const QuantArgs& q, const AnyPlan& p, int
 template <bool QUANT, int AXIS>
 __device__ __forceinline__ float block_of_many(const QuantArgs& q, const AnyPlan& p, int local, float* lds)
 {
-    const int64_t pitch = q.b <= 4 ? ((AXIS ? q.cols : q.rows) + 1) >> 1 : (AXIS ? q.cols : q.rows);
+    const int64_t pitch = (q.b <= 4 ? ((AXIS ? q.cols : q.rows) + 1) >> 1 : (AXIS ? q.cols : q.rows)) + q.pad;
     Maxima maxima{};
     if (QUANT) maxima = fetch_maxima(q.meta, p.dense);
     int piece = local * p.steps;
@@ -306,6 +318,7 @@ __device__ __forceinline__ float block_of_many(const QuantArgs& q, const AnyPlan
                 publish(q, sc, local);
             }
             if (t.count) emit(q, t.v, rnd, sc.inv, q.codes + t.to, t.count);
+            if (q.pad) zeros_behind(q, t);
         } else {
             amax = largest8(t, amax);
         }
