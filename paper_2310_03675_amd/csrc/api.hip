@@ -144,8 +144,9 @@ int choose_splits(int64_t RA, int64_t RB, int64_t D, int64_t n_tiles)
 // are quantized by the any-shape kernel alone, which writes the zeros.  Lines that start on any byte go through a shift per
 // fragment in the matmul kernels, and do not go straight to LDS.  Steps, unpadded / padded, us: 64000 x 99 x 99 99.2 / 86.2, 16384 x
 // 405 x 243 99.0 / 85.0, 8192 x 1001 x 333 95 / 86, 4097 x 27 x 64 17.4 / 15.5, 131072 x 27 x 64 without input gradient 56.2 / 53.8,
-// 1000 x 301 x 77 14.9 / 14.0.  The codes that hdqt_workspace_layout and a saved activation describe lie as ever.)
-int64_t inner_codes(int64_t D) { return D & 1 ? (D + 31) / 32 * 32 : D; }
+// 1000 x 301 x 77 14.9 / 14.0, 1000000 x 3 x 64 345 / 300, 3 x 2048 x 2048 28.8 / 28.5; but 1 x 4096 x 4096 58.8 / 59.3: a single
+// position, whose zeros are fifteen stores to a code, stays alone.  The codes that hdqt_workspace_layout and a saved activation describe lie as ever.)
+int64_t inner_codes(int64_t D) { return (D & 1) && D > 1 ? (D + 31) / 32 * 32 : D; }
 int64_t inner_tile(int64_t D, int64_t s) { return s < D ? s : inner_codes(D); }
 int64_t inner_pitch(int64_t D, int b) { return hdqt_codes_pitch(inner_codes(D), b); }
 int inner_pad(int64_t D, int b) { return (int)(inner_pitch(D, b) - hdqt_codes_pitch(D, b)); }

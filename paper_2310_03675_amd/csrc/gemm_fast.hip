@@ -8,6 +8,9 @@
 //   with zeros on its way to LDS, and rows that are no whole dwords (D no multiple of 8 packed
 //   codes or 4 bytes) are shifted into place there (the FLEX instances).
 //
+// Lines of whole 16-byte pieces whose tiles are whole ones go to gemm_bytes.hip and, from a size on,
+// to gemm_packed.hip, which bring them to LDS without registers.
+//
 // What differs from the generic kernel:
 //   * v_mfma_i32_32x32x32_i8: one MFMA consumes 32 contraction positions.
 //   * eight waves per 128 x 128 workgroup tile, each 64 rows x 32 columns: 106-124
@@ -343,8 +346,8 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
     // ROWWIDE (streamed outputs): a wave is one block high and two wide
     // instead of two high and one wide, so that its two stores of a row are neighbours (256
     // bytes; streaming stores of 256-byte pieces reach 5.0 TB/s where 128-byte pieces reach
-    // 4.6).  Same fragment reads per MFMA.  The benchmark layer's input gradient inside the
-    // step: 73.3 -> 70.6 us; its bfloat16 variant 57.7 -> 55.4 us.
+    // 4.6).  Same fragment reads per MFMA.  The bfloat16 input gradient of the 65536 x 1152 x
+    // 128 layer: 57.7 -> 55.4 us.
     constexpr bool ROWWIDE = STREAM && !NARROW && WAVES == 8;
     constexpr int RS = (NARROW || ROWWIDE) ? 1 : 2; // 32-row MFMA blocks per wave
     constexpr int WROWS = 32 * RS;
@@ -501,8 +504,9 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
 
     // MASK: the values of g.mask_src at the wave's output positions of tile `ct`, requested a
     // whole tile ahead of the epilogue that tests them (read there, right before the stores,
-    // their latency stood in front of every tile: 245 us instead of 71 us for the benchmark
-    // layer's input gradient)
+    // their latency stood in front of every tile: 245 us for the 302 MB input gradient of the
+    // 65536 x 1152 x 128 layer, which took 71 without a mask.  Lines of whole 32-code pieces go to
+    // lines_gemm_i4_kernel; the others come here)
     float mk[MASK ? RS : 1][MASK ? CS : 1][MASK ? 16 : 1];
     auto prefetch_mask = [&](const int ct) {
         if (ct >= n_ct) return;
@@ -1170,9 +1174,7 @@ __global__ __launch_bounds__(64 * WAVES, WAVES == 8 ? (MASK ? 3 : 4) : 2) void g
     // EPI_CERT8_S32 has the loop of its given-up stages (see `stage`) in the instances for
     // outputs that stay in the caches.  Those for streamed outputs go on in the testing stage
     // with every flag down: with the second loop compiled in, their testing stage came out 14 %
-    // slower (the forward product of the 65536 x 1152 x 128 layer: 25.7 against 22.6 us), and
-    // the one given-up case measured there, that layer's input gradient, is 10 % faster with
-    // its clamps cut into pairs (67.4 against 75.6 us: it is bound by its stores).
+    // slower (the forward product of the 65536 x 1152 x 128 layer: 25.7 against 22.6 us).
     constexpr bool kTwoLoops = kCert && !STREAM;
     if constexpr (kDeep) {
         Staged<UNITS * REGS, UNITS_B * REGS> st0, st1;

@@ -104,11 +104,14 @@ struct Eight {
     bool last;                           // of a line
 };
 
-// The zeros behind a line whose codes are padded (a few bytes of one thread in a line's many).
+// The zeros behind a line whose codes are padded (a few bytes of one thread in a line's many).  Written before the transform: behind the codes
+// they cost fwht_dual_kernel<true, 4, true, 0>, which takes such tensors along, 30 registers and its fourth wave per SIMD
+// (65536 x 1152 x 128's step 252.6 / 254.9 us).
 __device__ __forceinline__ void zeros_behind(const QuantArgs& q, const Eight& t)
 {
     if (!t.last || !t.count) return;
     uint8_t* dst = q.codes + t.to + (q.b <= 4 ? (t.count + 1) >> 1 : t.count);
+#pragma unroll 1
     for (int k = 0; k < q.pad; ++k) dst[k] = 0;
 }
 
@@ -278,16 +281,17 @@ __device__ __forceinline__ float block(const QuantArgs& q, const AnyPlan& p, int
     uint32_t rnd[4] = {0, 0, 0, 0};
     if (q.axis) {
         load8<1>(t, q, p, local, pitch);
+        if (QUANT) zeros_behind(q, t);
         transform8<QUANT, 1>(t, q, rnd, lds);
     } else {
         load8<0>(t, q, p, local, pitch);
+        if (QUANT) zeros_behind(q, t);
         transform8<QUANT, 0>(t, q, rnd, lds);
     }
     if (!QUANT) return largest8(t, 0.0f);
     const Scaling sc = scaling_of(maxima, q.meta, q.clip, q.b, p.dense);
     publish(q, sc, local);
     if (t.count) emit(q, t.v, rnd, sc.inv, q.codes + t.to, t.count);
-    if (q.pad) zeros_behind(q, t);
     return 0.0f;
 }
 
@@ -311,6 +315,7 @@ __device__ __forceinline__ float block_of_many(const QuantArgs& q, const AnyPlan
         Eight t = next;
         if (piece + 1 < last) load8<AXIS>(next, q, p, piece + 1, pitch);
         uint32_t rnd[4] = {0, 0, 0, 0};
+        if (QUANT) zeros_behind(q, t);
         transform8<QUANT, AXIS>(t, q, rnd, lds);
         if (QUANT) {
             if (first) {
@@ -318,7 +323,6 @@ __device__ __forceinline__ float block_of_many(const QuantArgs& q, const AnyPlan
                 publish(q, sc, local);
             }
             if (t.count) emit(q, t.v, rnd, sc.inv, q.codes + t.to, t.count);
-            if (q.pad) zeros_behind(q, t);
         } else {
             amax = largest8(t, amax);
         }
