@@ -64,34 +64,53 @@ def test_masked_input_gradient(M, K, N):
 # Tiles asked whether they can saturate, where there are more than 512 workgroups of them: codes in patches that pass and that do
 # not, the first stage passing (the test goes on) and failing (it is given up behind the first), every tile saturating upwards
 # (255 of them), contractions that end inside a stage and a pair of tiles
-@pytest.mark.parametrize("RA,RB,D", [(66001, 128, 1152), (4100, 4130, 736), (3000, 3001, 544), (8300, 1030, 8160)])
-@pytest.mark.parametrize("kind", ["patches", "first passes", "first fails", "upwards"])
-def test_tiles_that_are_asked(RA, RB, D, kind):
-    print(f"gemm_codes RA={RA} RB={RB} D={D} {kind}", flush=True)
-    rng = np.random.default_rng(RA + D)
+KINDS = ["patches", "first passes", "first fails", "upwards"]
 
-    def make(R):
-        if kind == "upwards":
-            return np.full((R, D), 7, dtype=np.int8)
-        full = rng.integers(-8, 8, (R, D), dtype=np.int8)
-        small = rng.integers(-1, 2, (R, D), dtype=np.int8)
-        which = rng.random((-(-R // 96), -(-D // 80))) < 0.3
-        which = np.repeat(np.repeat(which, 96, 0), 80, 1)[:R, :D]
-        if kind == "first fails":
-            which[:, :128] = True
-        else:
-            which[:, :128] = False if kind == "first passes" else which[:, :128] & (rng.random() < 0.5)
-        return np.where(which, full, small).astype(np.int8)
 
-    cA, cB = make(RA), make(RB)
+def asked_codes(rng, R, D, kind):
+    if kind == "upwards":
+        return np.full((R, D), 7, dtype=np.int8)
+    full = rng.integers(-8, 8, (R, D), dtype=np.int8)
+    small = rng.integers(-1, 2, (R, D), dtype=np.int8)
+    which = rng.random((-(-R // 96), -(-D // 80))) < 0.3
+    which = np.repeat(np.repeat(which, 96, 0), 80, 1)[:R, :D]
+    if kind == "first fails":
+        which[:, :128] = True
+    else:
+        which[:, :128] = False if kind == "first passes" else which[:, :128] & (rng.random() < 0.5)
+    return np.where(which, full, small).astype(np.int8)
+
+
+def multiply_and_compare(rng, cA, cB):
+    """The kernels that ran; outputs drawn and those of the last rows against the oracle's."""
+    (RA, D), RB = cA.shape, cB.shape[0]
     qA, qB = (torch.from_numpy(capi.pack_codes(c, 4)).to("cuda:0") for c in (cA, cB))
     sA, sB = torch.tensor([SA], device="cuda:0"), torch.tensor([SB], device="cuda:0")
     got = []
     ran = launched(lambda: got.append(B.gemm_codes(qA, qB, 4, 4, sA, sB, D, 8, 8, 32)))
-    assert "lines_gemm_i4_kernel<3" in ran, ran
     ii, jj = rng.integers(0, RA, 4096), rng.integers(0, RB, 4096)
     ii[:2], jj[:2] = (0, RA - 1), (0, RB - 1)
+    ii[2:66] = RA - 1
     want = capi.tiled_matmul_sampled(cA, cB, 32, 8, ii, jj)
     out, acc = got[0]
     assert np.array_equal(acc.cpu().numpy()[ii, jj], want)
     assert np.array_equal(out.cpu().numpy()[ii, jj], want.astype(np.float32) * DQ)
+    return ran
+
+
+@pytest.mark.parametrize("RA,RB,D", [(66001, 128, 1152), (4100, 4130, 736), (3000, 3001, 544), (8300, 1030, 8160)])
+@pytest.mark.parametrize("kind", KINDS)
+def test_tiles_that_are_asked(RA, RB, D, kind):
+    print(f"gemm_codes RA={RA} RB={RB} D={D} {kind}", flush=True)
+    rng = np.random.default_rng(RA + D)
+    assert "lines_gemm_i4_kernel<3" in multiply_and_compare(rng, asked_codes(rng, RA, D, kind), asked_codes(rng, RB, D, kind))
+
+
+# The same with lines that end inside 32 codes, 8, 16 and 24 behind the last whole ones: the next line's first codes, in the
+# same 16 bytes, are no part of the sums
+@pytest.mark.parametrize("RA,RB,D", [(16384, 1024, 1000), (3000, 3001, 592), (66001, 128, 536), (4100, 4130, 760), (8300, 1030, 8152)])
+@pytest.mark.parametrize("kind", KINDS)
+def test_tiles_that_are_asked_in_lines_that_end_inside_32_codes(RA, RB, D, kind):
+    print(f"gemm_codes RA={RA} RB={RB} D={D} {kind}", flush=True)
+    rng = np.random.default_rng(RA + D)
+    multiply_and_compare(rng, asked_codes(rng, RA, D, kind), asked_codes(rng, RB, D, kind))
