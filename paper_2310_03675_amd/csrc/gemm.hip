@@ -415,9 +415,13 @@ hipError_t launch_reduce(const int32_t* partial, int splits, int64_t count, cons
     return hipGetLastError();
 }
 
-hipError_t launch_gemm(const GemmArgs& g, hipStream_t stream)
+hipError_t launch_gemm(const GemmArgs& g_in, hipStream_t stream)
 {
-    if (g.fold) return launch_gemm_fold(g, stream);
+    if (g_in.fold) return launch_gemm_fold(g_in, stream);
+    // A mask that no epilogue applies is not these kernels' matter (the pass behind the product applies it): what multiplies is
+    // the same as without one, and where a mask is left, every rule below knows that it is the kernel's to apply.
+    GemmArgs g = g_in;
+    if (!gemm_fast_masks(g)) g.mask_src = nullptr;
     if (gemm_bytes_eligible(g)) return launch_gemm_bytes(g, stream);
     if (gemm_packed_eligible(g)) return launch_gemm_packed(g, stream);
     if (gemm_fast_eligible(g)) return launch_gemm_fast(g, stream);

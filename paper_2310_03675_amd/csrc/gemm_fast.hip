@@ -1388,8 +1388,7 @@ hipError_t launch_gemm_fast(const GemmArgs& g_in, hipStream_t stream)
     g.acc_hi_scaled = hi > INT32_MAX ? INT32_MAX : (int)hi;
     // Short contractions (at most two stages per output tile): a workgroup walks along
     // its row strip of the output as long as that leaves about two workgroups per CU.
-    const bool masked = gemm_fast_masks(g);
-    if (!masked) g.mask_src = nullptr;       // (applied by a later pass)
+    const bool masked = g.mask_src != nullptr;       // (launch_gemm leaves no other mask)
     const bool flex = flexible(g);
     const bool narrow = narrow_tiles(g);
     int64_t n_ct = (g.RB + BN - 1) / BN, n_rt = (g.RA + BM - 1) / BM;
@@ -1423,7 +1422,9 @@ hipError_t launch_gemm_fast(const GemmArgs& g_in, hipStream_t stream)
         else                                                                                         \
             hipLaunchKernelGGL((gemm_i4_kernel<EPI, KS_LONG, false, kWaves, false>), grid, block, 0, stream, g); \
     } while (0)
-// what lines_gemm_i4_kernel leaves: bfloat16 outputs, and masks behind lines that end inside 32 codes
+// What lines_gemm_i4_kernel leaves: bfloat16 outputs, and masks behind lines that end inside 32 codes.  (Every other product that
+// gets here passes gemm_packed_eligible, unless its tiles are asked whether they can saturate: those are launched above.  Outputs of
+// 2^38 elements, whose grids it refuses, are a terabyte.)
 #define HDQT_LAUNCH_I4_REST(EPI)                                                                      \
     do {                                                                                             \
         const dim3 block(64 * kWaves);                                                               \

@@ -385,7 +385,7 @@ bool gemm_packed_eligible(const GemmArgs& g)
 
 hipError_t launch_gemm_packed(const GemmArgs& g, hipStream_t stream)
 {
-    const bool narrow = narrow_tiles(g), masked = g.mask_src && g.splits == 1, tail = g.D % 32 != 0;
+    const bool narrow = narrow_tiles(g), masked = g.mask_src != nullptr, tail = g.D % 32 != 0;
     const LinesArgs k = lines_args(g, kRows, narrow ? 64 : 128, kStage);
     const int clamp = g.acc_hi != 127 ? CLAMP_NONE : g.s == 32 ? CLAMP_32 : CLAMP_64;
     ProfileScope ps(g.profile_tag ? K_GEMM_I4_FWD + (g.profile_tag - 1) : K_GEMM_I4, stream);

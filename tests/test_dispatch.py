@@ -1,4 +1,7 @@
 """Which kernel multiplies, at the edges of the rules (host code: nothing is launched)."""
+import math
+import random
+
 import pytest
 
 from dispatch import dispatch
@@ -21,3 +24,32 @@ def test_tiles_that_are_asked_lie_in_whole_32_codes(M, K, N):
         asked = [k for k in instance(kernels, LINES) if k[0] == TEST_32]
         assert rc == 0
         assert len(asked) == (call[2] % 32 == 0), (call, kernels)
+
+
+# masks behind contractions that are split (the pass that adds the parts masks) and that end inside 32 codes
+@pytest.mark.parametrize("M,K,N", [(1024, 2080, 1000), (4096, 1024, 2040), (5060, 412, 1360), (128, 4096, 4008), (70, 640, 3992)])
+def test_masked_gradients_in_parts_are_multiplied(M, K, N):
+    calls = [(kind, M, K, N, b, 8, s, 1) for kind in ("bwd_input", "layer_bwd") for b in (4, 3) for s in (32, 64)]
+    for call, (rc, kernels) in zip(calls, dispatch(calls)):
+        assert rc == 0, (call, kernels)
+        assert any("gemm" in k for k in kernels), (call, kernels)
+
+
+def _size(rng, lo, hi):
+    v, q = round(math.exp(rng.uniform(math.log(lo), math.log(hi)))), rng.choice((1, 8, 8, 32, 64))
+    return max(q, v // q * q)
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_no_call_is_left_without_a_kernel(seed):
+    """Layers and products at random, over every kind of call, width, accumulator and tile: arguments that are valid
+    are multiplied."""
+    rng, calls = random.Random(seed), []
+    for _ in range(5000):
+        kind, option = rng.choice((("fwd", 0), ("bwd_weight", 0), ("bwd_input", 0), ("bwd_input", 1), ("bwd_input", 1), ("bwd_input", 2),
+                                   ("codes", 0), ("step", 0), ("step", 1), ("layer_fwd", 0), ("layer_bwd", 0), ("layer_bwd", 1)))
+        b, acc = rng.choice(((4, 8),) * 6 + ((3, 8), (2, 8), (4, 12), (4, 16), (4, 32), (6, 12), (8, 16), (5, 12), (8, 8), (8, 24)))
+        s = rng.choice((32, 32, 32, 64, 64, 16, 96, 128, 160, 192, 224, 256, 24, 4000))
+        calls.append((kind, _size(rng, 1, 65536), _size(rng, 10, 4096), _size(rng, 10, 4096), b, acc, s, option))
+    for call, (rc, kernels) in zip(calls, dispatch(calls)):
+        assert rc == 0, (call, kernels)

@@ -61,6 +61,28 @@ def test_masked_input_gradient(M, K, N):
     assert torch.equal(got[0], torch.where(X > 0, plain[0], torch.zeros_like(plain[0])))
 
 
+# split contractions, whose parts the pass behind them adds and masks, that end 8, 16 and 24 codes behind whole 32s
+@pytest.mark.parametrize("M,K,N", [(1024, 2080, 1000), (5060, 412, 1360), (4096, 1024, 2040)])
+@pytest.mark.parametrize("s", [32, 64])
+def test_masked_input_gradient_in_parts(M, K, N, s):
+    print(f"bwd_input M={M} K={K} N={N} s={s}", flush=True)
+    g = torch.Generator(device="cuda:0").manual_seed(M + N + s)
+    G, W, X = (torch.randn(shape, generator=g, device="cuda:0") for shape in ((M, N), (K, N), (M, K)))
+    X[:, ::7] = 0.0
+    op = B.Operand(4, B.ROUND_NEAREST, 1.0, 0)
+    prm = B.Params(had_block=8, acc_bits=8, s=s, seed=0, A=op, B=op)
+    want, acc, _ = B.gemm(B.GEMM_BWD_INPUT, G, W, M, K, N, prm, want_acc=True)
+    masked = torch.where(X > 0, want, torch.zeros_like(want))
+    got = []
+    ran = launched(lambda: got.append(B.gemm(B.GEMM_BWD_INPUT, G, W, M, K, N, prm, mask=X, want_acc=True)))
+    assert "reduce" in ran and "relu_mask" not in ran, ran
+    assert torch.equal(got[0][0], masked) and torch.equal(got[0][1], acc)
+    _, saved = B.layer_fwd(X, W, prm, prm)
+    dX, dW = B.layer_bwd(G, W, saved, K, prm, prm, mask=X)
+    assert torch.equal(dX, masked)
+    assert torch.equal(dW, B.gemm(B.GEMM_BWD_WEIGHT, X, G, M, K, N, prm)[0])
+
+
 # Tiles asked whether they can saturate, where there are more than 512 workgroups of them: codes in patches that pass and that do
 # not, the first stage passing (the test goes on) and failing (it is given up behind the first), every tile saturating upwards
 # (255 of them), contractions that end inside a stage and a pair of tiles
