@@ -153,7 +153,7 @@ bool gemm_bytes_eligible(const GemmArgs& g)
     if (g.bA <= 4 || g.bB <= 4 || g.fold || g.out_bf16) return false;
     if (g.D % 16 != 0 || (g.n_tiles > 1 && g.s % kStage != 0)) return false;
     if (!g.stream_out && g.splits == 1 && g.RB <= 4 * kTile && 4 * g.RA * g.RB > ((int64_t)240 << 20)) return false;
-    return gemm_fast_eligible(g) && lines_grid(g, kTile, kTile);
+    return gemm_fast_eligible(g) && lines_fit(g, kTile, kTile, kStage);
 }
 
 hipError_t launch_gemm_bytes(const GemmArgs& g, hipStream_t stream)

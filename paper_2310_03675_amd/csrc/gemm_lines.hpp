@@ -52,9 +52,12 @@ inline LinesArgs lines_args(const GemmArgs& g, int64_t tile_rows, int64_t tile_c
     k.to = out_args(g);
     return k;
 }
-// grids of less than 2^32 threads (with what they are rounded up by)
-inline bool lines_grid(const GemmArgs& g, int64_t tile_rows, int64_t tile_cols)
+// Grids of less than 2^32 threads (with what they are rounded up by), and parts of whole stages: tiles_per_split tiles then end
+// where the next part begins, so that no part begins at or behind a line's end (all but the last have fewer than n_tiles tiles
+// together) and none has more codes than those by which its totals were found to fit 16 bits.
+inline bool lines_fit(const GemmArgs& g, int64_t tile_rows, int64_t tile_cols, int64_t stage)
 {
+    if (g.splits > 1 && g.tiles_per_split * g.s % stage != 0) return false;
     const int64_t tiles = ((g.RA + tile_rows - 1) / tile_rows) * ((g.RB + tile_cols - 1) / tile_cols) * g.splits;
     return (tiles + 7) * kThreads < ((int64_t)1 << 32);
 }
@@ -79,6 +82,7 @@ __device__ __forceinline__ Place place_of(const LinesArgs& g, uint32_t stage)
     p.rt = 8 * grp + in - p.ct * tall;
     const uint32_t all = (uint32_t)((g.D + stage - 1) / stage);
     p.s_begin = p.share * g.part_stages;
+    if (p.s_begin > all) p.s_begin = all;
     p.n_stages = all - p.s_begin < g.part_stages ? all - p.s_begin : g.part_stages;
     return p;
 }
@@ -87,7 +91,7 @@ __device__ __forceinline__ Place place_of(const LinesArgs& g, uint32_t stage)
 __device__ __forceinline__ int bytes_left(int64_t rows, int64_t first, int64_t pitch, int64_t begin)
 {
     const int64_t n = (rows - first) * pitch - begin;
-    return (int)(n < (int64_t)kOutside ? n : (int64_t)kOutside - 1);
+    return n <= 0 ? 0 : (int)(n < (int64_t)kOutside ? n : (int64_t)kOutside - 1);
 }
 
 // A wave's totals, RBLK x CBLK blocks of 32 x 32 at (row0, col0), to where they belong.  Stores through a descriptor that ends

@@ -366,21 +366,21 @@ static int64_t wide_workgroups(const GemmArgs& g) { return ((g.RA + 127) / 128) 
 // workgroups, 32.7 / 30.6, 174 x 16256 x 1024, 254, 9.9 / 9.1, but 18995 x 373 x 1088, 447, 15.0 / 16.5, 8404 x 832 x 5640, 462, 49.8 / 62.0).
 static bool narrow_tiles(const GemmArgs& g) { return g.RB <= 64 || wide_workgroups(g) <= (g.acc_hi == 127 ? 512 : 384); }
 
-// What gemm_i4_kernel keeps of these: lines that are no whole dwords, bfloat16 outputs, a mask behind lines that end inside 32
-// codes, and, of the products whose tiles are asked whether they can saturate, those whose lines end inside 32 codes (a line's
-// last piece brings codes of the next line, and the testing loop has no place to clear them before they are squared) and those
-// of up to 512 workgroups: eight waves each do better there than four (65536 x 128 x 1152, test passed 19.6 / 20.5, failed 24.4 /
-// 26.3; with clamps and tiles of 128 x 64 24.0 and 24.2), not beyond (131072 x 128 x 576 passed 26.9 / 25.0, 4096 cubed failed
-// 145 / 128, passed 86.5 / 85.3).  Of 331 drawn products (3- and 4-bit codes, 32 to 168000 rows and columns, contractions of 8 to
-// 16384) the 170 that come here are faster by 27 to 38 % in the median; the one class that is not is a narrow output's very long
-// contraction in parts (576 x 64 x 262144 32.0 / 32.9, x 131072 21.7 / 21.4).
+// What gemm_i4_kernel keeps of these: lines that are no whole dwords, bfloat16 outputs, parts of no whole stages (tiles of 96 or
+// 160 codes), a mask behind lines that end inside 32 codes, and, of the products whose tiles are asked whether they can saturate,
+// those whose lines end inside 32 codes (a line's last piece brings codes of the next line, and the testing loop has no place to
+// clear them before they are squared) and those of up to 512 workgroups: eight waves each do better there than four (65536 x
+// 128 x 1152, test passed 19.6 / 20.5, failed 24.4 / 26.3; with clamps and tiles of 128 x 64 24.0 and 24.2), not beyond (131072 x
+// 128 x 576 passed 26.9 / 25.0, 4096 cubed failed 145 / 128, passed 86.5 / 85.3).  Of 331 drawn products (3- and 4-bit codes, 32 to
+// 168000 rows and columns, contractions of 8 to 16384) the 170 that come here are faster by 27 to 38 % in the median; the one
+// class that is not is a narrow output's very long contraction in parts (576 x 64 x 262144 32.0 / 32.9, x 131072 21.7 / 21.4).
 bool gemm_packed_eligible(const GemmArgs& g)
 {
     if (g.bA > 4 || g.bB > 4 || g.fold || g.out_bf16) return false;
     if (g.D % 8 != 0 || (g.D % 32 != 0 && g.mask_src)) return false;
     const bool clamped = g.acc_hi == 127 && (g.s == 32 || g.s == 64), plain = g.acc_hi == INT_MAX && g.s % 32 == 0;
     if (!(clamped || plain) || (gemm_fast_tests_tiles(g) && (g.D % 32 != 0 || wide_workgroups(g) <= 512))) return false;
-    return gemm_fast_eligible(g) && lines_grid(g, kRows, narrow_tiles(g) ? 64 : 128);
+    return gemm_fast_eligible(g) && lines_fit(g, kRows, narrow_tiles(g) ? 64 : 128, kStage);
 }
 
 hipError_t launch_gemm_packed(const GemmArgs& g, hipStream_t stream)

@@ -12,6 +12,10 @@ def instance(kernels, name):
     return [k[len(name) + 1:k.index(">")].split(", ") for k in kernels if k.startswith(name + "<")]
 
 
+def field(kernel, name):
+    return int(kernel.split(f" {name}=")[1].split()[0])
+
+
 LINES, TEST_32 = "lines_gemm_i4_kernel", "3"      # (its first argument: the clamp)
 
 
@@ -53,3 +57,26 @@ def test_no_call_is_left_without_a_kernel(seed):
         calls.append((kind, _size(rng, 1, 65536), _size(rng, 10, 4096), _size(rng, 10, 4096), b, acc, s, option))
     for call, (rc, kernels) in zip(calls, dispatch(calls)):
         assert rc == 0, (call, kernels)
+
+
+# Tiles that divide no stage of 128 codes, in as many parts as the products of any size are split into: where lines go straight
+# to LDS no part begins at or behind a line's end, and 16-bit slices hold what a part can add up to
+@pytest.mark.parametrize("b,acc", [(4, 32), (3, 32), (2, 32), (4, 8), (3, 8), (8, 32), (8, 16)])
+def test_parts_end_inside_their_lines(b, acc):
+    rng, calls = random.Random(b + acc), [("codes", 129, 131080, 512, b, acc, 96, 0), ("codes", 129, 100000, 129, b, acc, 96, 0)]
+    for _ in range(3000):
+        calls.append(("codes", _size(rng, 1, 1500), _size(rng, 512, 300000), _size(rng, 1, 1500), b, acc,
+                      rng.choice((32, 64, 128)) if acc == 8 else 32 * rng.choice((1, 2, 3, 3, 4, 5, 5, 6, 7, 8, 9, 10, 11, 20, 33)), 0))
+    seen = 0
+    for call, (rc, kernels) in zip(calls, dispatch(calls)):
+        assert rc in (0, -5, -6), (call, kernels)            # (more than 32 bits hold)
+        for k in kernels:
+            if " parts=" not in k or field(k, "parts") == 1:
+                continue
+            parts, codes = field(k, "parts"), field(k, "part_codes")
+            seen += 1
+            assert (parts - 1) * codes < call[2], (call, k)
+            if field(k, "slices16"):
+                most = min(codes << 2 * (b - 1), -(-codes // call[6]) << (acc - 1))
+                assert most < 1 << 15, (call, k)
+    assert seen > 20

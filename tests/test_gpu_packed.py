@@ -61,6 +61,25 @@ def test_masked_input_gradient(M, K, N):
     assert torch.equal(got[0], torch.where(X > 0, plain[0], torch.zeros_like(plain[0])))
 
 
+# parts of tiles that divide no stage: one line in the last rows of tiles, slices of 16 bits that the lowest codes fill (480 codes
+# of 64 each) and of 32
+@pytest.mark.parametrize("RA,RB,D,s", [(64, 128, 15384, 96), (300, 512, 15416, 96), (129, 129, 100000, 96), (129, 129, 99968, 160),
+                                       (129, 512, 131080, 96), (130, 385, 50056, 224)])
+@pytest.mark.parametrize("kind", ["gauss", "lowest"])
+def test_parts_of_no_whole_stages(RA, RB, D, s, kind):
+    print(f"gemm_codes RA={RA} RB={RB} D={D} s={s} a=32 {kind}", flush=True)
+    rng = np.random.default_rng(D + s)
+    cA, cB = codes(rng, RA, D, kind, 4), codes(rng, RB, D, kind, 4)
+    qA, qB = (torch.from_numpy(capi.pack_codes(c, 4)).to("cuda:0") for c in (cA, cB))
+    sA, sB = torch.tensor([SA], device="cuda:0"), torch.tensor([SB], device="cuda:0")
+    out, acc = B.gemm_codes(qA, qB, 4, 4, sA, sB, D, 8, 32, s)
+    ii, jj = rng.integers(0, RA, 1024), rng.integers(0, RB, 1024)
+    ii[:64], jj[64:128] = RA - 1, RB - 1
+    want = capi.tiled_matmul_sampled(cA, cB, s, 32, ii, jj)
+    assert np.array_equal(acc.cpu().numpy()[ii, jj], want)
+    assert np.array_equal(out.cpu().numpy()[ii, jj], want.astype(np.float32) * DQ)
+
+
 # split contractions, whose parts the pass behind them adds and masks, that end 8, 16 and 24 codes behind whole 32s
 @pytest.mark.parametrize("M,K,N", [(1024, 2080, 1000), (5060, 412, 1360), (4096, 1024, 2040)])
 @pytest.mark.parametrize("s", [32, 64])
