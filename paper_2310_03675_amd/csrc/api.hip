@@ -1370,9 +1370,11 @@ int run_layer_bwd(const float* G, const float* W, const void* saved, const hdqt_
     auto meta = [&](size_t off) { return reinterpret_cast<hdqt::QMeta*>(base + off); };
     hdqt::GemmArgs g_dx{};
     if (with_dx) {
+        // (A folded gradient is planned over the caller's contraction: which layers are refused is part of their results, and
+        // padding an odd one to whole 32s would take it.)
         g_dx = plan_gemm(base + L.codesG1, base + L.codesW1, bwd_input->A.b, bwd_input->B.b,
-                         &meta(L.metaG1)->scale, &meta(L.metaW1)->scale, M, K, inner_codes(N), L.n_bwi,
-                         bwd_input->acc_bits, inner_tile(N, bwd_input->s), dX, nullptr, 1 + HDQT_GEMM_BWD_INPUT);
+                         &meta(L.metaG1)->scale, &meta(L.metaW1)->scale, M, K, geo ? N : inner_codes(N), L.n_bwi,
+                         bwd_input->acc_bits, geo ? bwd_input->s : inner_tile(N, bwd_input->s), dX, nullptr, 1 + HDQT_GEMM_BWD_INPUT);
         // (nothing is launched before the geometry is known to be taken)
         if (geo && !hdqt::gemm_fold_plan(&g_dx, geo->batch, geo->channels, geo->height, geo->width, geo->kh,
                                          geo->kw))

@@ -80,3 +80,13 @@ def test_parts_end_inside_their_lines(b, acc):
                 most = min(codes << 2 * (b - 1), -(-codes // call[6]) << (acc - 1))
                 assert most < 1 << 15, (call, k)
     assert seen > 20
+
+
+# Folded input gradients: whole steps of 32 codes a tap, odd widths no more than even ones (whose codes a call keeps in
+# padded lines where nothing is folded)
+@pytest.mark.parametrize("batch,C,side", [(8, 64, 8), (2, 64, 16), (2, 128, 32)])
+def test_folded_gradients_take_whole_32_channels(batch, C, side):
+    calls = [("conv_bwd", batch, C, N, 4, 8, 32, side) for N in (32, 64, 96, 33, 65, 31, 1, 63, 95, 97, 40, 48)]
+    for call, (rc, kernels) in zip(calls, dispatch(calls)):
+        assert rc == (0 if call[3] % 32 == 0 else -13), (call, kernels)
+        assert (call[3] % 32 == 0) == any(k.startswith("gemm_fold_kernel") for k in kernels), (call, kernels)

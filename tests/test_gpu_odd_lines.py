@@ -32,3 +32,29 @@ def test_layer_calls(M, K, N, b, acc, s):
     masked, _ = B.layer_bwd(G, W, saved, K, prm[1], prm[2], mask=X)
     assert torch.equal(Z, want[0]) and torch.equal(dX, want[1]) and torch.equal(dW, want[2])
     assert torch.equal(masked, torch.where(X > 0, want[1], torch.zeros_like(want[1])))
+
+
+# odd numbers of output channels are not folded inside the product: the gradient of the activation is the layer's, folded
+# tap by tap in fp32
+@pytest.mark.parametrize("N", [33, 65])
+def test_convolutions_with_odd_channels(N):
+    from paper_2310_03675_amd import autograd as A
+    batch, C, side = 4, 64, 16
+    g = torch.Generator(device="cuda:0").manual_seed(N)
+    act, G, W = (torch.randn(s, generator=g, device="cuda:0") for s in ((batch, C, side, side), (batch * side * side, N), (9 * C, N)))
+    op = lambda rnd, t: B.Operand(4, rnd, 1.0, t)
+    fwd, bwi, bww = (B.Params(had_block=16, acc_bits=8, s=32, seed=3, A=a, B=b)
+                     for a, b in ((op(NE, 0), op(NE, 1)), (op(ST, 6), op(NE, 5)), (op(NE, 8), op(ST, 10))))
+    _, saved = B.conv_fwd(act, 3, 3, W, fwd, bww)
+    with pytest.raises(B.HdqtError) as e:
+        B.conv_bwd(G, W, saved, act.shape, 3, 3, bwi, bww)
+    assert e.value.code == -13
+    grads = []
+    for folds in (True, False):
+        m = A.HdqtConv2d(C, N, cfg=A.LayerConfig(layer_id=3, seed=2, fold_in_matmul=folds), device="cuda:0")
+        m.weight.data.copy_(W)
+        x = act.clone().requires_grad_(True)
+        z = m(x)
+        (z * torch.linspace(-1, 1, z.numel(), device="cuda:0").reshape(z.shape)).sum().backward()
+        grads.append((z.detach(), x.grad, m.weight.grad))
+    assert all(torch.equal(a, b) for a, b in zip(*grads))
