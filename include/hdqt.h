@@ -366,7 +366,10 @@ int hdqt_gemm_fwd_static(const float *X, const float *W, float *Z, int64_t M, in
  * (bwd_input may be NULL when dX is); the operands' tensor_ids and the seeds
  * are taken from the params of the matmul each quantization belongs to.
  * Workspace: hdqt_layer_step_workspace_size(...) bytes (0 = invalid arguments),
- * device memory, 16-byte aligned, contents undefined on entry and on return.
+ * device memory, 16-byte aligned, contents undefined on entry and on return.  With an odd
+ * M, K or N some of these bytes (up to 31 for each line of codes) only make the call
+ * faster: one that has room for the codes at hdqt_codes_pitch is enough, here and for
+ * hdqt_layer_fwd and hdqt_layer_bwd, and the results are the same.
  */
 size_t hdqt_layer_step_workspace_size(int64_t M, int64_t K, int64_t N, const hdqt_params_t *fwd,
                                       const hdqt_params_t *bwd_input,

@@ -140,22 +140,27 @@ int choose_splits(int64_t RA, int64_t RB, int64_t D, int64_t n_tiles)
 }
 
 // Codes that a call keeps to itself lie in lines of whole 16-byte pieces where the contraction is odd, zeros behind them: the
-// product then runs over inner_codes(D) of them, in tiles that end with whole pieces or are one tile as before.  (Odd contractions
+// product then runs over codes(D) of them, in tiles that end with whole pieces or are one tile as before.  (Odd contractions
 // are quantized by the any-shape kernel alone, which writes the zeros.  Lines that start on any byte go through a shift per
 // fragment in the matmul kernels, and do not go straight to LDS.  Steps, unpadded / padded, us: 64000 x 99 x 99 99.2 / 86.2, 16384 x
 // 405 x 243 99.0 / 85.0, 8192 x 1001 x 333 95 / 86, 4097 x 27 x 64 17.4 / 15.5, 131072 x 27 x 64 without input gradient 56.2 / 53.8,
 // 1000 x 301 x 77 14.9 / 14.0, 1000000 x 3 x 64 345 / 300, 3 x 2048 x 2048 28.8 / 28.5; but 1 x 4096 x 4096 58.8 / 59.3: a single
 // position, whose zeros are fifteen stores to a code, stays alone.  The codes that hdqt_workspace_layout and a saved activation describe lie as ever.)
-int64_t inner_codes(int64_t D) { return (D & 1) && D > 1 ? (D + 31) / 32 * 32 : D; }
-int64_t inner_tile(int64_t D, int64_t s) { return s < D ? s : inner_codes(D); }
-int64_t inner_pitch(int64_t D, int b) { return hdqt_codes_pitch(inner_codes(D), b); }
-int inner_pad(int64_t D, int b) { return (int)(inner_pitch(D, b) - hdqt_codes_pitch(D, b)); }
+// A workspace that has room for the codes without the zeros is enough: they then lie without.
+struct Lines {
+    bool padded;
+    int64_t codes(int64_t D) const { return padded && (D & 1) && D > 1 ? (D + 31) / 32 * 32 : D; }
+    int64_t tile(int64_t D, int64_t s) const { return s < D ? s : codes(D); }
+    int64_t pitch(int64_t D, int b) const { return hdqt_codes_pitch(codes(D), b); }
+    int pad(int64_t D, int b) const { return (int)(pitch(D, b) - hdqt_codes_pitch(D, b)); }
+};
+constexpr Lines kAsTheyAre{false};
 
 constexpr size_t kMetaBytes = (sizeof(hdqt::QMeta) + 255) / 256 * 256;
 
 hdqt::QuantArgs make_quant_args(const float* T, int64_t rows, int64_t cols, int axis, int n_eff,
                                 const hdqt_operand_t* op, uint64_t seed, hdqt::QMeta* meta, void* codes,
-                                float* scale_out, bool inner = false)
+                                float* scale_out, Lines lines = kAsTheyAre)
 {
     hdqt::QuantArgs q{};
     q.T = T; q.rows = rows; q.cols = cols; q.axis = axis;
@@ -164,7 +169,7 @@ hdqt::QuantArgs make_quant_args(const float* T, int64_t rows, int64_t cols, int 
     q.clip = op->clip; q.tensor_id = op->tensor_id;
     q.seed_lo = (uint32_t)seed; q.seed_hi = (uint32_t)(seed >> 32);
     q.meta = meta; q.codes = static_cast<uint8_t*>(codes); q.scale_out = scale_out;
-    if (inner) q.pad = inner_pad(axis ? cols : rows, op->b);
+    q.pad = lines.pad(axis ? cols : rows, op->b);
     return q;
 }
 
@@ -172,7 +177,7 @@ hdqt::DualArgs make_dual_args(const float* T, int64_t rows, int64_t cols, int n1
                               const hdqt_operand_t* op1, uint64_t seed1, int n0,
                               const hdqt_operand_t* op0, uint64_t seed0, hdqt::QMeta* meta1,
                               hdqt::QMeta* meta0, void* codes1, void* codes0, float* scale1_out,
-                              float* scale0_out, int profile_tag, bool inner1 = false, bool inner0 = false)
+                              float* scale0_out, int profile_tag, Lines lines1 = kAsTheyAre, Lines lines0 = kAsTheyAre)
 {
     hdqt::DualArgs d{};
     d.profile_tag = profile_tag;
@@ -187,8 +192,8 @@ hdqt::DualArgs make_dual_args(const float* T, int64_t rows, int64_t cols, int n1
     d.meta_row = meta1; d.meta_col = meta0;
     d.codes_row = static_cast<uint8_t*>(codes1); d.codes_col = static_cast<uint8_t*>(codes0);
     d.scale_row_out = scale1_out; d.scale_col_out = scale0_out;
-    if (inner1) d.pad_row = inner_pad(cols, op1->b);
-    if (inner0) d.pad_col = inner_pad(rows, op0->b);
+    d.pad_row = lines1.pad(cols, op1->b);
+    d.pad_col = lines0.pad(rows, op0->b);
     return d;
 }
 
@@ -605,6 +610,7 @@ int run_gemm(int kind, const float* P, const float* Q, float* out, int64_t M, in
 // contiguous from offset 0, so one launch clears them all.
 enum { T_X1, T_X0, T_W0, T_W1, T_G1, T_G0, T_COUNT };
 struct StepLayout {
+    Lines lines;
     size_t meta[T_COUNT];
     size_t codes[T_COUNT];
     size_t acc[3];           // per matmul: slices of a split contraction
@@ -616,8 +622,9 @@ struct StepLayout {
 };
 
 int plan_step(int64_t M, int64_t K, int64_t N, const hdqt_params_t* const prm[3], bool with_dx,
-              StepLayout* L)
+              Lines lines, StepLayout* L)
 {
+    L->lines = lines;
     Orientation o[3];
     for (int k = 0; k < 3; ++k) {
         if (k == HDQT_GEMM_BWD_INPUT && !with_dx) continue;
@@ -633,24 +640,24 @@ int plan_step(int64_t M, int64_t K, int64_t N, const hdqt_params_t* const prm[3]
         L->n_eff[k] = 1;
         if (k == HDQT_GEMM_BWD_INPUT && !with_dx) continue;
         L->n_eff[k] = hdqt_n_eff(o[k].D, prm[k]->had_block);
-        const int64_t D = inner_codes(o[k].D), s = inner_tile(o[k].D, prm[k]->s);
+        const int64_t D = lines.codes(o[k].D), s = lines.tile(o[k].D, prm[k]->s);
         L->splits[k] = choose_splits(o[k].RA, o[k].RB, D, (D + s - 1) / s);
     }
     L->zero_bytes = off;
     for (int k = 0; k < 3; ++k) {
         L->acc[k] = off;
         if (k == HDQT_GEMM_BWD_INPUT && !with_dx) continue;
-        L->acc_bytes[k] = partial_bytes(o[k].RA, o[k].RB, inner_codes(o[k].D), inner_tile(o[k].D, prm[k]->s));
+        L->acc_bytes[k] = partial_bytes(o[k].RA, o[k].RB, lines.codes(o[k].D), lines.tile(o[k].D, prm[k]->s));
         off = align_up(off + L->acc_bytes[k], 256);
     }
     const hdqt_params_t *fwd = prm[0], *bwi = prm[1], *bww = prm[2];
     const size_t bytes[T_COUNT] = {
-        (size_t)(M * inner_pitch(K, fwd->A.b)),                 // X along K
-        (size_t)(K * inner_pitch(M, bww->A.b)),                 // X along M
-        (size_t)(N * inner_pitch(K, fwd->B.b)),                 // W along K
-        with_dx ? (size_t)(K * inner_pitch(N, bwi->B.b)) : 0,   // W along N
-        with_dx ? (size_t)(M * inner_pitch(N, bwi->A.b)) : 0,   // G along N
-        (size_t)(N * inner_pitch(M, bww->B.b)),                 // G along M
+        (size_t)(M * lines.pitch(K, fwd->A.b)),                 // X along K
+        (size_t)(K * lines.pitch(M, bww->A.b)),                 // X along M
+        (size_t)(N * lines.pitch(K, fwd->B.b)),                 // W along K
+        with_dx ? (size_t)(K * lines.pitch(N, bwi->B.b)) : 0,   // W along N
+        with_dx ? (size_t)(M * lines.pitch(N, bwi->A.b)) : 0,   // G along N
+        (size_t)(N * lines.pitch(M, bww->B.b)),                 // G along M
     };
     for (int t = 0; t < T_COUNT; ++t) {
         L->codes[t] = off;
@@ -665,6 +672,7 @@ int plan_step(int64_t M, int64_t K, int64_t N, const hdqt_params_t* const prm[3]
 constexpr size_t kSavedHeader = 256;     // the scale (one float) of the saved codes, then padding
 
 struct FwdLayout {
+    Lines lines;
     size_t metaX1, metaX0, metaW0;       // contiguous from offset 0
     size_t acc, acc_bytes;
     size_t codesX1, codesW0;
@@ -673,8 +681,9 @@ struct FwdLayout {
 };
 
 int plan_fwd(int64_t M, int64_t K, int64_t N, const hdqt_params_t* fwd, const hdqt_params_t* bww,
-             FwdLayout* L)
+             Lines lines, FwdLayout* L)
 {
+    L->lines = lines;
     Orientation o;
     int rc = check_gemm(HDQT_GEMM_FWD, M, K, N, fwd, &o);
     if (rc) return rc;
@@ -690,17 +699,18 @@ int plan_fwd(int64_t M, int64_t K, int64_t N, const hdqt_params_t* fwd, const hd
     L->metaX0 = off; off += kMetaBytes;
     L->metaW0 = off; off += kMetaBytes;
     L->acc = off;
-    L->acc_bytes = partial_bytes(M, N, inner_codes(K), inner_tile(K, fwd->s));
+    L->acc_bytes = partial_bytes(M, N, lines.codes(K), lines.tile(K, fwd->s));
     off = align_up(off + L->acc_bytes, 256);
     L->codesX1 = off;
-    off = align_up(off + (size_t)(M * inner_pitch(K, fwd->A.b)), 256);
+    off = align_up(off + (size_t)(M * lines.pitch(K, fwd->A.b)), 256);
     L->codesW0 = off;
-    off = align_up(off + (size_t)(N * inner_pitch(K, fwd->B.b)), 256);
+    off = align_up(off + (size_t)(N * lines.pitch(K, fwd->B.b)), 256);
     L->total = off;
     return HDQT_OK;
 }
 
 struct BwdLayout {
+    Lines lines;
     size_t metaG1, metaG0, metaW1;       // contiguous from offset 0
     size_t acc[2], acc_bytes[2];         // input gradient, weight gradient
     size_t codesG1, codesG0, codesW1;
@@ -709,8 +719,9 @@ struct BwdLayout {
 };
 
 int plan_bwd(int64_t M, int64_t K, int64_t N, const hdqt_params_t* bwi, const hdqt_params_t* bww,
-             BwdLayout* L)
+             Lines lines, BwdLayout* L)
 {
+    L->lines = lines;
     Orientation o;
     int rc = check_gemm(HDQT_GEMM_BWD_WEIGHT, M, K, N, bww, &o);
     if (rc) return rc;
@@ -725,17 +736,17 @@ int plan_bwd(int64_t M, int64_t K, int64_t N, const hdqt_params_t* bwi, const hd
     L->metaG0 = off; off += kMetaBytes;
     L->metaW1 = off; off += kMetaBytes;
     L->acc[0] = off;
-    L->acc_bytes[0] = bwi ? partial_bytes(M, K, inner_codes(N), inner_tile(N, bwi->s)) : 0;
+    L->acc_bytes[0] = bwi ? partial_bytes(M, K, lines.codes(N), lines.tile(N, bwi->s)) : 0;
     off = align_up(off + L->acc_bytes[0], 256);
     L->acc[1] = off;
     L->acc_bytes[1] = partial_bytes(K, N, M, bww->s);
     off = align_up(off + L->acc_bytes[1], 256);
     L->codesG1 = off;
-    off = align_up(off + (bwi ? (size_t)(M * inner_pitch(N, bwi->A.b)) : 0), 256);
+    off = align_up(off + (bwi ? (size_t)(M * lines.pitch(N, bwi->A.b)) : 0), 256);
     L->codesG0 = off;
     off = align_up(off + (size_t)(N * hdqt_codes_pitch(M, bww->B.b)), 256);
     L->codesW1 = off;
-    off = align_up(off + (bwi ? (size_t)(K * inner_pitch(N, bwi->B.b)) : 0), 256);
+    off = align_up(off + (bwi ? (size_t)(K * lines.pitch(N, bwi->B.b)) : 0), 256);
     L->total = off;
     return HDQT_OK;
 }
@@ -1133,7 +1144,7 @@ size_t hdqt_layer_step_workspace_size(int64_t M, int64_t K, int64_t N, const hdq
 {
     const hdqt_params_t* prm[3] = {fwd, bwd_input, bwd_weight};
     StepLayout L;
-    return plan_step(M, K, N, prm, bwd_input != nullptr, &L) == HDQT_OK ? L.total : 0;
+    return plan_step(M, K, N, prm, bwd_input != nullptr, {true}, &L) == HDQT_OK ? L.total : 0;
 }
 
 } // extern "C"
@@ -1151,7 +1162,8 @@ int run_layer_step(const float* X, const hdqt_conv_t* geo, const float* W, const
     if (with_dx && !bwd_input) return HDQT_EINVAL_NULL;
     const hdqt_params_t* prm[3] = {fwd, bwd_input, bwd_weight};
     StepLayout L;
-    int rc = plan_step(M, K, N, prm, with_dx, &L);
+    int rc = plan_step(M, K, N, prm, with_dx, {true}, &L);
+    if (!rc && workspace_bytes < L.total) rc = plan_step(M, K, N, prm, with_dx, kAsTheyAre, &L);
     if (rc) return rc;
     if (!workspace || workspace_bytes < L.total) return HDQT_EWORKSPACE;
     if (misaligned(X) || misaligned(W) || misaligned(G) || misaligned(Z) || misaligned(dX) ||
@@ -1170,12 +1182,12 @@ int run_layer_step(const float* X, const hdqt_conv_t* geo, const float* W, const
     if (geo && !with_dx) return HDQT_EINVAL_GEOMETRY;       // (hdqt_conv_step asks for dXcol)
     QuantSet set;
     set.add(make_dual_args(X, M, K, nF, &fwd->A, fwd->seed, nW, &bwd_weight->A, bwd_weight->seed, meta(T_X1),
-                           meta(T_X0), codes(T_X1), codes(T_X0), nullptr, nullptr, 1, true, true));
+                           meta(T_X0), codes(T_X1), codes(T_X0), nullptr, nullptr, 1, L.lines, L.lines));
     if (with_dx) {
         set.add(make_dual_args(W, K, N, nI, &bwd_input->B, bwd_input->seed, nF, &fwd->B, fwd->seed, meta(T_W1),
-                               meta(T_W0), codes(T_W1), codes(T_W0), nullptr, nullptr, 2, true, true));
+                               meta(T_W0), codes(T_W1), codes(T_W0), nullptr, nullptr, 2, L.lines, L.lines));
         set.add(make_dual_args(G, M, N, nI, &bwd_input->A, bwd_input->seed, nW, &bwd_weight->B, bwd_weight->seed,
-                               meta(T_G1), meta(T_G0), codes(T_G1), codes(T_G0), nullptr, nullptr, 3, true, true));
+                               meta(T_G1), meta(T_G0), codes(T_G1), codes(T_G0), nullptr, nullptr, 3, L.lines, L.lines));
         // an activation source is read by the two-axis kernels only, and its layer's other tensors
         // are of a kind they take (nothing is launched before this is known)
         if (geo) {
@@ -1184,12 +1196,12 @@ int run_layer_step(const float* X, const hdqt_conv_t* geo, const float* W, const
                 if (!hdqt::quantize_dual_eligible(set.both[k])) return HDQT_EINVAL_GEOMETRY;
         }
     } else {
-        set.add(make_quant_args(W, K, N, 0, nF, &fwd->B, fwd->seed, meta(T_W0), codes(T_W0), nullptr, true));
-        set.add(make_quant_args(G, M, N, 0, nW, &bwd_weight->B, bwd_weight->seed, meta(T_G0), codes(T_G0), nullptr, true));
+        set.add(make_quant_args(W, K, N, 0, nF, &fwd->B, fwd->seed, meta(T_W0), codes(T_W0), nullptr, L.lines));
+        set.add(make_quant_args(G, M, N, 0, nW, &bwd_weight->B, bwd_weight->seed, meta(T_G0), codes(T_G0), nullptr, L.lines));
     }
     if ((rc = run_quantize_set(set, base, L.zero_bytes, stream))) return rc;
     hdqt::GemmArgs g_fwd = plan_gemm(codes(T_X1), codes(T_W0), fwd->A.b, fwd->B.b, &meta(T_X1)->scale,
-                                     &meta(T_W0)->scale, M, N, inner_codes(K), nF, fwd->acc_bits, inner_tile(K, fwd->s), Z, nullptr,
+                                     &meta(T_W0)->scale, M, N, L.lines.codes(K), nF, fwd->acc_bits, L.lines.tile(K, fwd->s), Z, nullptr,
                                      1 + HDQT_GEMM_FWD);
     // Nobody can read Z before the two backward products of this call have run, and those move
     // several times the memory-side cache: from 16 MB on, Z is written with streaming stores
@@ -1204,12 +1216,12 @@ int run_layer_step(const float* X, const hdqt_conv_t* geo, const float* W, const
     int n = 0;
     ps[n++] = {g_fwd, acc(HDQT_GEMM_FWD), L.acc_bytes[HDQT_GEMM_FWD]};
     ps[n++] = {plan_gemm(codes(T_X0), codes(T_G0), bwd_weight->A.b, bwd_weight->B.b, &meta(T_X0)->scale,
-                         &meta(T_G0)->scale, K, N, inner_codes(M), nW, bwd_weight->acc_bits, inner_tile(M, bwd_weight->s), dW, nullptr,
+                         &meta(T_G0)->scale, K, N, L.lines.codes(M), nW, bwd_weight->acc_bits, L.lines.tile(M, bwd_weight->s), dW, nullptr,
                          1 + HDQT_GEMM_BWD_WEIGHT),
                acc(HDQT_GEMM_BWD_WEIGHT), L.acc_bytes[HDQT_GEMM_BWD_WEIGHT]};
     if (with_dx)
         ps[n++] = {plan_gemm(codes(T_G1), codes(T_W1), bwd_input->A.b, bwd_input->B.b, &meta(T_G1)->scale,
-                             &meta(T_W1)->scale, M, K, inner_codes(N), nI, bwd_input->acc_bits, inner_tile(N, bwd_input->s), dX, nullptr,
+                             &meta(T_W1)->scale, M, K, L.lines.codes(N), nI, bwd_input->acc_bits, L.lines.tile(N, bwd_input->s), dX, nullptr,
                              1 + HDQT_GEMM_BWD_INPUT),
                    acc(HDQT_GEMM_BWD_INPUT), L.acc_bytes[HDQT_GEMM_BWD_INPUT]};
     // dX in rows of whole half lines streams from the 128 MB mark on here, where a product on its own
@@ -1265,7 +1277,7 @@ size_t hdqt_layer_fwd_workspace_size(int64_t M, int64_t K, int64_t N, const hdqt
                                      const hdqt_params_t* bwd_weight)
 {
     FwdLayout L;
-    return plan_fwd(M, K, N, fwd, bwd_weight, &L) == HDQT_OK ? L.total : 0;
+    return plan_fwd(M, K, N, fwd, bwd_weight, {true}, &L) == HDQT_OK ? L.total : 0;
 }
 
 } // extern "C"
@@ -1280,7 +1292,8 @@ int run_layer_fwd(const float* X, const hdqt_conv_t* geo, const float* W, float*
     if (!X || !W || !Z || !fwd) return HDQT_EINVAL_NULL;
     if (bwd_weight && !saved) return HDQT_EINVAL_NULL;
     FwdLayout L;
-    int rc = plan_fwd(M, K, N, fwd, bwd_weight, &L);
+    int rc = plan_fwd(M, K, N, fwd, bwd_weight, {true}, &L);
+    if (!rc && workspace_bytes < L.total) rc = plan_fwd(M, K, N, fwd, bwd_weight, kAsTheyAre, &L);
     if (rc) return rc;
     if (!workspace || workspace_bytes < L.total) return HDQT_EWORKSPACE;
     if (bwd_weight && saved_bytes < hdqt_layer_saved_size(M, K, bwd_weight)) return HDQT_EWORKSPACE;
@@ -1294,9 +1307,9 @@ int run_layer_fwd(const float* X, const hdqt_conv_t* geo, const float* W, float*
     if (bwd_weight)
         set.add(make_dual_args(X, M, K, L.n_fwd, &fwd->A, fwd->seed, L.n_bww, &bwd_weight->A, bwd_weight->seed,
                                meta(L.metaX1), meta(L.metaX0), base + L.codesX1, sv + kSavedHeader, nullptr,
-                               reinterpret_cast<float*>(sv), 1, true));
+                               reinterpret_cast<float*>(sv), 1, L.lines));
     else
-        set.add(make_quant_args(X, M, K, 1, L.n_fwd, &fwd->A, fwd->seed, meta(L.metaX1), base + L.codesX1, nullptr, true));
+        set.add(make_quant_args(X, M, K, 1, L.n_fwd, &fwd->A, fwd->seed, meta(L.metaX1), base + L.codesX1, nullptr, L.lines));
     if (geo) {
         // an activation source is read by the two-axis kernels only: both code sets are made,
         // and nothing is launched before the geometry is known to be taken
@@ -1304,11 +1317,11 @@ int run_layer_fwd(const float* X, const hdqt_conv_t* geo, const float* W, float*
         if (!set_conv_source(&set.both[0], geo) || !hdqt::quantize_dual_eligible(set.both[0]))
             return HDQT_EINVAL_GEOMETRY;
     }
-    set.add(make_quant_args(W, K, N, 0, L.n_fwd, &fwd->B, fwd->seed, meta(L.metaW0), base + L.codesW0, nullptr, true));
+    set.add(make_quant_args(W, K, N, 0, L.n_fwd, &fwd->B, fwd->seed, meta(L.metaW0), base + L.codesW0, nullptr, L.lines));
     if ((rc = run_quantize_set(set, base, 3 * kMetaBytes, stream))) return rc;
     return run_planned_gemm(plan_gemm(base + L.codesX1, base + L.codesW0, fwd->A.b, fwd->B.b,
-                                      &meta(L.metaX1)->scale, &meta(L.metaW0)->scale, M, N, inner_codes(K), L.n_fwd,
-                                      fwd->acc_bits, inner_tile(K, fwd->s), Z, nullptr, 1 + HDQT_GEMM_FWD),
+                                      &meta(L.metaX1)->scale, &meta(L.metaW0)->scale, M, N, L.lines.codes(K), L.n_fwd,
+                                      fwd->acc_bits, L.lines.tile(K, fwd->s), Z, nullptr, 1 + HDQT_GEMM_FWD),
                             base + L.acc, L.acc_bytes, stream);
 }
 
@@ -1339,7 +1352,7 @@ size_t hdqt_layer_bwd_workspace_size(int64_t M, int64_t K, int64_t N, const hdqt
                                      const hdqt_params_t* bwd_weight)
 {
     BwdLayout L;
-    return plan_bwd(M, K, N, bwd_input, bwd_weight, &L) == HDQT_OK ? L.total : 0;
+    return plan_bwd(M, K, N, bwd_input, bwd_weight, {true}, &L) == HDQT_OK ? L.total : 0;
 }
 
 } // extern "C"
@@ -1358,7 +1371,10 @@ int run_layer_bwd(const float* G, const float* W, const void* saved, const hdqt_
     if (misaligned(mask_src)) return HDQT_EALIGN;
     if (with_dx && (!bwd_input || !W)) return HDQT_EINVAL_NULL;
     BwdLayout L;
-    int rc = plan_bwd(M, K, N, with_dx ? bwd_input : nullptr, bwd_weight, &L);
+    // (A folded gradient is planned over the caller's contraction: which layers are refused is part of their results, and
+    // padding an odd one to whole 32s would take it.)
+    int rc = plan_bwd(M, K, N, with_dx ? bwd_input : nullptr, bwd_weight, {geo == nullptr}, &L);
+    if (!rc && workspace_bytes < L.total) rc = plan_bwd(M, K, N, with_dx ? bwd_input : nullptr, bwd_weight, kAsTheyAre, &L);
     if (rc) return rc;
     if (!workspace || workspace_bytes < L.total) return HDQT_EWORKSPACE;
     if (misaligned(G) || misaligned(W) || misaligned(saved) || misaligned(dX) || misaligned(dW) ||
@@ -1370,11 +1386,9 @@ int run_layer_bwd(const float* G, const float* W, const void* saved, const hdqt_
     auto meta = [&](size_t off) { return reinterpret_cast<hdqt::QMeta*>(base + off); };
     hdqt::GemmArgs g_dx{};
     if (with_dx) {
-        // (A folded gradient is planned over the caller's contraction: which layers are refused is part of their results, and
-        // padding an odd one to whole 32s would take it.)
         g_dx = plan_gemm(base + L.codesG1, base + L.codesW1, bwd_input->A.b, bwd_input->B.b,
-                         &meta(L.metaG1)->scale, &meta(L.metaW1)->scale, M, K, geo ? N : inner_codes(N), L.n_bwi,
-                         bwd_input->acc_bits, geo ? bwd_input->s : inner_tile(N, bwd_input->s), dX, nullptr, 1 + HDQT_GEMM_BWD_INPUT);
+                         &meta(L.metaG1)->scale, &meta(L.metaW1)->scale, M, K, L.lines.codes(N), L.n_bwi,
+                         bwd_input->acc_bits, L.lines.tile(N, bwd_input->s), dX, nullptr, 1 + HDQT_GEMM_BWD_INPUT);
         // (nothing is launched before the geometry is known to be taken)
         if (geo && !hdqt::gemm_fold_plan(&g_dx, geo->batch, geo->channels, geo->height, geo->width, geo->kh,
                                          geo->kw))
@@ -1387,9 +1401,9 @@ int run_layer_bwd(const float* G, const float* W, const void* saved, const hdqt_
     if (with_dx) {
         set.add(make_dual_args(G, M, N, L.n_bwi, &bwd_input->A, bwd_input->seed, L.n_bww, &bwd_weight->B,
                                bwd_weight->seed, meta(L.metaG1), meta(L.metaG0), base + L.codesG1,
-                               base + L.codesG0, nullptr, nullptr, 3, true));
+                               base + L.codesG0, nullptr, nullptr, 3, L.lines));
         set.add(make_quant_args(W, K, N, 1, L.n_bwi, &bwd_input->B, bwd_input->seed, meta(L.metaW1),
-                                base + L.codesW1, nullptr, true));
+                                base + L.codesW1, nullptr, L.lines));
     } else {
         set.add(make_quant_args(G, M, N, 0, L.n_bww, &bwd_weight->B, bwd_weight->seed, meta(L.metaG0),
                                 base + L.codesG0, nullptr));

@@ -92,6 +92,17 @@ int main()
         if (!strcmp(what, "step"))             // option: 1 without input gradient
             rc = hdqt_layer_step(at(0), at(1), at(2), at(4), option ? nullptr : at(5), at(6), M, K, N, &p, option ? nullptr : &p, &p, at(3),
                                  hdqt_layer_step_workspace_size(M, K, N, &p, option ? nullptr : &p, &p), nullptr);
+        // (workspaces of the next larger layer of even sizes: lines as long as hdqt_codes_pitch has them, and no zeros behind)
+        const long long M2 = M + M % 2, K2 = K + K % 2, N2 = N + N % 2;
+        if (!strcmp(what, "step_even"))
+            rc = hdqt_layer_step(at(0), at(1), at(2), at(4), option ? nullptr : at(5), at(6), M, K, N, &p, option ? nullptr : &p, &p, at(3),
+                                 hdqt_layer_step_workspace_size(M2, K2, N2, &p, option ? nullptr : &p, &p), nullptr);
+        if (!strcmp(what, "layer_fwd_even"))
+            rc = hdqt_layer_fwd(at(0), at(1), at(2), M, K, N, &p, &p, at(3), hdqt_layer_saved_size(M, K, &p), at(4),
+                                hdqt_layer_fwd_workspace_size(M2, K2, N2, &p, &p), nullptr);
+        if (!strcmp(what, "layer_bwd_even"))
+            rc = hdqt_layer_bwd(at(0), at(1), at(2), at(3), at(4), M, K, N, &p, &p, at(5),
+                                hdqt_layer_bwd_workspace_size(M2, K2, N2, &p, &p), nullptr);
         if (!strcmp(what, "layer_fwd"))
             rc = hdqt_layer_fwd(at(0), at(1), at(2), M, K, N, &p, &p, at(3), hdqt_layer_saved_size(M, K, &p), at(4),
                                 hdqt_layer_fwd_workspace_size(M, K, N, &p, &p), nullptr);

@@ -90,3 +90,12 @@ def test_folded_gradients_take_whole_32_channels(batch, C, side):
     for call, (rc, kernels) in zip(calls, dispatch(calls)):
         assert rc == (0 if call[3] % 32 == 0 else -13), (call, kernels)
         assert (call[3] % 32 == 0) == any(k.startswith("gemm_fold_kernel") for k in kernels), (call, kernels)
+
+
+# Odd contractions: a workspace with room for the codes alone is enough, the zeros behind them are not asked for
+@pytest.mark.parametrize("M,K,N", [(1000001, 3, 64), (4097, 27, 64), (64000, 99, 99), (16384, 405, 243), (128, 561, 11), (1023, 64, 129)])
+def test_codes_lie_without_padding_where_there_is_no_room(M, K, N):
+    calls = [(kind + even, M, K, N, b, acc, s, 0) for kind in ("step", "layer_fwd", "layer_bwd") for even in ("", "_even")
+             for b, acc, s in ((4, 8, 32), (4, 8, 1000), (8, 16, 32))]
+    for call, (rc, kernels) in zip(calls, dispatch(calls)):
+        assert rc == 0, (call, kernels)
