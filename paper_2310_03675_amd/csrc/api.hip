@@ -490,7 +490,7 @@ int run_planned_gemm(hdqt::GemmArgs g, void* ws, size_t ws_bytes, hipStream_t st
         e = hdqt::launch_gemm_small(&g, 1, stream);
         return e == hipSuccess ? HDQT_OK : hip_fail(e);
     }
-    if (hdqt::gemm_six_eligible(g) && hdqt::gemm_six_pays(g) && ws && (int64_t)ws_bytes >= hdqt::gemm_six_bytes(g)) {
+    if (hdqt::gemm_six_eligible(g) && ws && (int64_t)ws_bytes >= hdqt::gemm_six_bytes(g)) {
         e = hdqt::launch_gemm_six(g, ws, stream);
         return e == hipSuccess ? HDQT_OK : hip_fail(e);
     }

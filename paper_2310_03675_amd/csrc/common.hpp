@@ -247,7 +247,6 @@ hipError_t launch_gemm_small(const GemmArgs* gs, int n, hipStream_t stream);
 // need for the codes in that form (gemm_six.hip)
 bool gemm_six_shape(int64_t RA, int64_t RB, int64_t D);
 bool gemm_six_eligible(const GemmArgs& g);
-bool gemm_six_pays(const GemmArgs& g);       // (of the eligible ones)
 int64_t gemm_six_bytes(const GemmArgs& g);
 hipError_t launch_gemm_six(const GemmArgs& g, void* frags, hipStream_t stream);
 bool gemm_fast_eligible(const GemmArgs& g);

@@ -196,17 +196,32 @@ bool gemm_six_shape(int64_t RA, int64_t RB, int64_t D)
     return D % 32 == 0 && RA >= 256 && RB >= 256 && D >= 512;      // (rows of codes of whole 16-byte pieces)
 }
 
-// The products whose workspaces hold the codes' other form.  (An estimate against gemm_i4_kernel, which multiplied them
-// otherwise when the line was drawn; what is held is part of a caller's sizes and stays.  Of those, gemm_six_pays says which are
-// multiplied here.  Tiles of 128 or 256 in 8-bit accumulators, two and four chained instructions and fewer clamps, have no
-// instance: nothing multiplies large products in them so far.)
+// Against lines_gemm_i4_kernel, from 100 products of 12 to 120 10^9 multiply-adds and 2^39 (us, integer kernel / this one with
+// expand_kernel): what it saves grows with the products, what it pays with the codes that are laid out anew and with the outputs,
+// which it stores in pieces of 128 bytes (the other: 256).  Clamped 8192 cubed 683 / 508, 4096 cubed 88 / 78, 4137 x 4005 x 2080
+// 60 / 53.5, 4736 x 2944 x 1216 32.3 / 34.0, 2432 x 14976 x 512 32.9 / 44.4; not clamped 8192 cubed 454 / 352, 10752 x 2048 x 3648
+// 84 / 71, 4137 x 4005 x 2080 44.6 / 42.8, 4096 cubed 64.5 / 67.9, 3712 x 13568 x 768 47.1 / 63.9.  Of the 100 four fall on the
+// wrong side, by up to 5 us (4096 x 4096 x 2048 not clamped 35.0 / 40.2).
+static bool pays(const GemmArgs& g)
+{
+    const double codes = 1e-6 * (double)(g.RA + g.RB) * (double)g.D, outputs = 1e-6 * (double)g.RA * (double)g.RB;
+    const double products = 1e-3 * outputs * (double)g.D;
+    return g.acc_hi == 127 ? 0.382 * products - 3.3 - 0.11 * codes - 0.204 * outputs > 0.0
+                           : 0.256 * products - 2.9 - 0.123 * codes - 0.197 * outputs > 0.0;
+}
+
+// The products that are multiplied here, whose workspaces hold the codes' other form.  (Two lines have to be passed: `pays`, and
+// the estimate that was drawn against gemm_i4_kernel, which multiplied them otherwise then: the least gain of outputs that fill
+// whole half rounds of its workgroups still keeps products away of which `pays` makes next to nothing, 0.2 us for 2048 x 4096 x 2048
+// clamped.  Tiles of 128 or 256 in 8-bit accumulators, two and four chained instructions and fewer clamps, have no instance:
+// nothing multiplies large products in them so far.)
 bool gemm_six_eligible(const GemmArgs& g)
 {
     if (!gemm_six_shape(g.RA, g.RB, g.D)) return false;
     if (g.bA > 4 || g.bB > 4 || g.splits > 1 || g.fold || g.mask_src || g.out_bf16) return false;
     const bool clamped = g.s == 64 && g.acc_lo == -128 && g.acc_hi == 127;
     const bool plain = g.acc_hi == INT_MAX && g.D <= 16384;      // totals of at most 2^20
-    if (!clamped && !plain) return false;
+    if (!(clamped || plain) || !pays(g)) return false;
     const double codes = (double)(g.RA + g.RB) * (double)g.D, products = (double)g.RA * (double)g.RB * (double)g.D;
     const double gain = (clamped ? 7.5e-10 : 4.4e-10) * products - (clamped ? 6.5 : 8.0) - 2.8e-7 * codes;
     const int64_t stages = (g.D + kStage - 1) / kStage, n_rt = (g.RA + kPanel - 1) / kPanel, n_ct = (g.RB + kPanel - 1) / kPanel;
@@ -219,20 +234,6 @@ bool gemm_six_eligible(const GemmArgs& g)
     // a panel's bytes in 31 bits, and grids of less than 2^32 threads (with what they are rounded up by)
     return stages * kStageBytes < ((int64_t)1 << 31) && (n_rt * n_ct + 7) * kThreads < ((int64_t)1 << 32) &&
            4 * (n_rt + n_ct) * ((stages + 1) / 2) * kExpandThreads < ((int64_t)1 << 32);
-}
-
-// Against lines_gemm_i4_kernel, from 100 products of 12 to 120 10^9 multiply-adds and 2^39 (us, integer kernel / this one with
-// expand_kernel): what it saves grows with the products, what it pays with the codes that are laid out anew and with the outputs,
-// which it stores in pieces of 128 bytes (the other: 256).  Clamped 8192 cubed 683 / 508, 4096 cubed 88 / 78, 4137 x 4005 x 2080
-// 60 / 53.5, 4736 x 2944 x 1216 32.3 / 34.0, 2432 x 14976 x 512 32.9 / 44.4; not clamped 8192 cubed 454 / 352, 10752 x 2048 x 3648
-// 84 / 71, 4137 x 4005 x 2080 44.6 / 42.8, 4096 cubed 64.5 / 67.9, 3712 x 13568 x 768 47.1 / 63.9.  Of the 100 four fall on the
-// wrong side, by up to 5 us (4096 x 4096 x 2048 not clamped 35.0 / 40.2).
-bool gemm_six_pays(const GemmArgs& g)
-{
-    const double codes = 1e-6 * (double)(g.RA + g.RB) * (double)g.D, outputs = 1e-6 * (double)g.RA * (double)g.RB;
-    const double products = 1e-3 * outputs * (double)g.D;
-    return g.acc_hi == 127 ? 0.382 * products - 3.3 - 0.11 * codes - 0.204 * outputs > 0.0
-                           : 0.256 * products - 2.9 - 0.123 * codes - 0.197 * outputs > 0.0;
 }
 
 hipError_t launch_gemm_six(const GemmArgs& g, void* frags, hipStream_t stream)

@@ -1,9 +1,10 @@
 """Which large products of packed codes multiply through the 6-bit matrix instructions, as far as the size of
-their workspace tells (host code): it holds the codes' other form."""
+their workspace tells (host code): it holds the codes' other form, for those and for no others."""
 import ctypes as C
 
 import pytest
 
+from dispatch import dispatch
 from paper_2310_03675_amd import binding as B
 
 MOST_THREADS = 1 << 32          # of a grid
@@ -16,7 +17,7 @@ def other_form(RA, RB, D, s=64):
 # (RA, RB, D): on both sides of what a grid holds, of the kernel that writes the other form (256 threads for 32 rows
 # of 256 codes) and of the product's (512 threads for 128 x 128 outputs)
 @pytest.mark.parametrize("RA,RB,D,fits", [(1 << 20, 512, 1 << 17, False), ((1 << 20) - 1024, 512, 1 << 17, True),
-                                          (1 << 19, 1 << 18, 512, False), (1 << 19, (1 << 18) - 256, 512, True)])
+                                          (1 << 19, 1 << 18, 1024, False), (1 << 19, (1 << 18) - 256, 1024, True)])
 def test_products_whose_grids_cannot_be_launched_stay_with_the_integer_kernel(RA, RB, D, fits):
     threads = max(-(-RA // 128) * -(-RB // 128) * 512, (-(-RA // 128) + -(-RB // 128)) * 4 * (D // 256) * 256)
     assert (threads < MOST_THREADS) == fits
@@ -29,15 +30,18 @@ def has_other_form(RA, RB, D, acc, s):
     return B.workspace_size(B.GEMM_FWD, RA, D, RB, prm) > B.load().hdqt_workspace_least(B.GEMM_FWD, RA, D, RB, C.byref(prm.c()))
 
 
-# products timed with either kernel, on both sides of the line; those that fill half rounds of 512 tiles come later
+# products timed with either kernel, on both sides of the line; those that fill half rounds of 512 tiles come later, and wide
+# outputs of short contractions not at all (1536 x 24832 x 512, 32768 x 2048 x 512)
 @pytest.mark.parametrize("RA,RB,D,acc,s,other", [
     (8192, 8192, 8192, 8, 64, True), (4096, 4096, 4096, 8, 64, True), (8192, 1024, 8192, 8, 64, True), (2304, 10368, 2048, 8, 64, True),
     (24576, 768, 768, 8, 64, False), (1536, 32768, 512, 8, 64, False), (1024, 32768, 512, 8, 64, False),
-    (2048, 16384, 512, 8, 64, False), (2048, 4096, 2048, 8, 64, False), (1536, 24832, 512, 8, 64, True),
+    (2048, 16384, 512, 8, 64, False), (2048, 4096, 2048, 8, 64, False), (1536, 24832, 512, 8, 64, False),
     (8192, 8192, 8192, 32, 256, True), (4096, 4096, 2048, 32, 256, True), (16384, 1024, 2048, 32, 256, False),
-    (2048, 32768, 512, 32, 256, False), (32768, 2048, 512, 32, 256, True), (4096, 8192, 1024, 32, 256, False),
-    (8192, 4096, 1024, 32, 256, True), (4096, 8192, 1536, 32, 256, True)])
+    (2048, 32768, 512, 32, 256, False), (32768, 2048, 512, 32, 256, False), (4096, 8192, 1024, 32, 256, False),
+    (8192, 4096, 1024, 32, 256, False), (4096, 8192, 1536, 32, 256, True)])
 def test_which_products_take_the_other_form(RA, RB, D, acc, s, other):
+    (rc, kernels), = dispatch([("fwd", RA, D, RB, 4, acc, s, 0)])
+    assert rc == 0 and any(k.startswith("gemm_six_kernel") for k in kernels) == other, kernels
     assert has_other_form(RA, RB, D, acc, s) == other
 
 
