@@ -28,6 +28,7 @@ typedef short v2s __attribute__((ext_vector_type(2)));
 
 constexpr int kStage = 128, kLine = kStage / 2;     // codes of a line in a stage, and their bytes
 constexpr int kRows = 128, kWaves = 4;
+constexpr int kStages = 3;                          // in LDS
 
 // TEST_32: CLAMP_32 where a tile is asked first whether it can saturate at all (see below)
 enum Clamp { CLAMP_32, CLAMP_64, CLAMP_NONE, TEST_32 };
@@ -124,8 +125,8 @@ __device__ __forceinline__ int max_dpp(int x)
     return x > y ? x : y;
 }
 
-template <int CLAMP, bool STREAM, bool NARROW, bool MASK, bool TAIL, int kStages = 3>
-__global__ __launch_bounds__(kThreads, kStages > 3 ? 2 : NARROW ? 4 : MASK || TAIL ? 2 : 3) void lines_gemm_i4_kernel(LinesArgs g)
+template <int CLAMP, bool STREAM, bool NARROW, bool MASK, bool TAIL>
+__global__ __launch_bounds__(kThreads, NARROW ? 4 : MASK || TAIL ? 2 : 3) void lines_gemm_i4_kernel(LinesArgs g)
 {
     constexpr int kCols = NARROW ? 64 : 128, kBlocks = NARROW ? 1 : 2;      // blocks of a wave one above the other; two side by side
     constexpr int kPanelA = kRows * kLine, kPanelB = kCols * kLine, kStageBytes = kPanelA + kPanelB;
@@ -170,9 +171,7 @@ __global__ __launch_bounds__(kThreads, kStages > 3 ? 2 : NARROW ? 4 : MASK || TA
     v16i sum[kBlocks][2] = {};           // CLAMP_NONE, TEST_32
     uint32_t buf = 0;
     bring(0, 0);
-#pragma unroll
-    for (int k = 1; k < kStages - 1; ++k)
-        if (at.n_stages > (uint32_t)k) bring(k, k * kStageBytes);
+    if (at.n_stages > 1) bring(1, kStageBytes);
     // TEST_32: where the largest sums are, and the word that says that the test was given up
     [[maybe_unused]] __shared__ int norms[CLAMP == TEST_32 ? kNorms + 1 : 1];
     const uint32_t norm0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int*)norms, norm_off = norm0 + 4 * kNorms;
@@ -265,12 +264,12 @@ __global__ __launch_bounds__(kThreads, kStages > 3 ? 2 : NARROW ? 4 : MASK || TA
         // loads go to: a wave's reads of it were waited for where they stand.
         // (TEST_32 gives up behind a stage's barrier)
         if (CLAMP != TEST_32 || s != s_given_up) {
-            if (s + kStages - 2 < at.n_stages) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((kStages - 2) * (kBringA + kBringB)) : "memory");
+            if (s + 1 < at.n_stages) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kBringA + kBringB) : "memory");
             else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
         }
-        if (s + kStages - 1 < at.n_stages) bring(s + kStages - 1, buf == 0 ? (kStages - 1) * kStageBytes : buf - kStageBytes);
+        if (s + 2 < at.n_stages) bring(s + 2, buf == 0 ? 2 * kStageBytes : buf - kStageBytes);
         std::conditional_t<NARROW, Codes12, Codes22> q[2];
         auto read = [&](int p) {
             read_steps((fa + buf) ^ (32 * p), (fb + buf) ^ (32 * p), q[p]);
@@ -338,7 +337,7 @@ __global__ __launch_bounds__(kThreads, kStages > 3 ? 2 : NARROW ? 4 : MASK || TA
                 }
             }
         }
-        buf = buf == (kStages - 1) * kStageBytes ? 0 : buf + kStageBytes;
+        buf = buf == 2 * kStageBytes ? 0 : buf + kStageBytes;
     }
     if constexpr (CLAMP == CLAMP_NONE || CLAMP == TEST_32) {
 #pragma unroll
