@@ -210,18 +210,19 @@ static bool pays(const GemmArgs& g)
                            : 0.256 * products - 2.9 - 0.123 * codes - 0.197 * outputs > 0.0;
 }
 
-// The products that are multiplied here, whose workspaces hold the codes' other form.  (Two lines have to be passed: `pays`, and
-// the estimate that was drawn against gemm_i4_kernel, which multiplied them otherwise then: the least gain of outputs that fill
-// whole half rounds of its workgroups still keeps products away of which `pays` makes next to nothing, 0.2 us for 2048 x 4096 x 2048
-// clamped.  Tiles of 128 or 256 in 8-bit accumulators, two and four chained instructions and fewer clamps, have no instance:
-// nothing multiplies large products in them so far.)
+// The products that are multiplied here, whose workspaces hold the codes' other form.  (Two lines have to be passed: `pays`, where
+// lines_gemm_i4_kernel is what multiplies otherwise -- not unclamped tiles of 24 or 33 codes, for which there is only the
+// generic kernel, 6825 x 2768 x 1792 1987 / 54 us -- and the estimate that was drawn against gemm_i4_kernel, which multiplied them
+// otherwise then: the least gain of outputs that fill whole half rounds of its workgroups still keeps products away of which
+// `pays` makes next to nothing, 0.2 us for 2048 x 4096 x 2048 clamped.  Tiles of 128 or 256 in 8-bit accumulators, two and four
+// chained instructions and fewer clamps, have no instance: nothing multiplies large products in them so far.)
 bool gemm_six_eligible(const GemmArgs& g)
 {
     if (!gemm_six_shape(g.RA, g.RB, g.D)) return false;
     if (g.bA > 4 || g.bB > 4 || g.splits > 1 || g.fold || g.mask_src || g.out_bf16) return false;
     const bool clamped = g.s == 64 && g.acc_lo == -128 && g.acc_hi == 127;
     const bool plain = g.acc_hi == INT_MAX && g.D <= 16384;      // totals of at most 2^20
-    if (!(clamped || plain) || !pays(g)) return false;
+    if (!(clamped || plain) || (gemm_packed_eligible(g) && !pays(g))) return false;
     const double codes = (double)(g.RA + g.RB) * (double)g.D, products = (double)g.RA * (double)g.RB * (double)g.D;
     const double gain = (clamped ? 7.5e-10 : 4.4e-10) * products - (clamped ? 6.5 : 8.0) - 2.8e-7 * codes;
     const int64_t stages = (g.D + kStage - 1) / kStage, n_rt = (g.RA + kPanel - 1) / kPanel, n_ct = (g.RB + kPanel - 1) / kPanel;

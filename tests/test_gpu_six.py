@@ -45,6 +45,23 @@ def test_gemm_codes_expanded(RA, RB, D, s, a, kind, b):
     assert np.array_equal(acc.cpu().numpy()[ii, jj], capi.tiled_matmul_sampled(cA, cB, s, a, ii, jj))
 
 
+@pytest.mark.parametrize("s", [24, 33])
+def test_unclamped_tiles_of_no_whole_32_codes(s):
+    """Otherwise the generic kernel's."""
+    RA, RB, D = 4137, 6005, 2080
+    rng = np.random.default_rng(s)
+    cA, cB = (rng.integers(-8, 8, (R, D), dtype=np.int8) for R in (RA, RB))
+    qA, qB = (torch.from_numpy(capi.pack_codes(c, 4)).to("cuda:0") for c in (cA, cB))
+    one, got = torch.full((1,), 0.5, device="cuda:0"), []
+    for name, n in (("gemm_six_kernel", B.load().hdqt_gemm_codes_workspace_size(RA, RB, D, s)), ("gemm_tiled_kernel", 256)):
+        ws = torch.empty(n, dtype=torch.uint8, device="cuda:0")
+        assert name in launched(lambda: got.append(B.gemm_codes(qA, qB, 4, 4, one, one, D, 32, 32, s, workspace=ws)))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    ii, jj = rng.integers(0, RA, 512), rng.integers(0, RB, 512)
+    ii[:2], jj[:2] = (0, RA - 1), (0, RB - 1)
+    assert np.array_equal(got[0][1].cpu().numpy()[ii, jj], capi.tiled_matmul_sampled(cA, cB, s, 32, ii, jj))
+
+
 def test_gemm_takes_a_workspace_without_room_for_it():
     """A workspace as large as the layout's parts, without the codes' other form behind them."""
     M, K, N = 3105, 2080, 2979

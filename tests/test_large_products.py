@@ -45,6 +45,16 @@ def test_which_products_take_the_other_form(RA, RB, D, acc, s, other):
     assert has_other_form(RA, RB, D, acc, s) == other
 
 
+
+# tiles of no whole 32 codes, which the kernel that `pays` compares with does not take: the other form from where it beats
+# the kernels that do
+@pytest.mark.parametrize("RA,RB,D,s,other", [(6825, 2768, 1792, 33, True), (148480, 1664, 512, 24, True), (4096, 8192, 1536, 24, True),
+                                             (8192, 4096, 1024, 33, True), (8192, 4096, 1024, 32, False), (16384, 1024, 2048, 33, False)])
+def test_unclamped_tiles_of_no_whole_32_codes(RA, RB, D, s, other):
+    (rc, kernels), = dispatch([("fwd", RA, D, RB, 4, 32, s, 0)])
+    assert rc == 0 and any(k.startswith("gemm_six_kernel") for k in kernels) == other, kernels
+    assert has_other_form(RA, RB, D, 32, s) == other
+
 def test_only_calls_that_use_the_other_form_are_told_to_hold_it():
     lib, (RA, RB, D) = B.load(), (4096, 4096, 4096)
     size = lambda bA, bB, acc, bf16=0, s=64: lib.hdqt_gemm_codes_workspace_size_for(RA, RB, D, s, bA, bB, acc, bf16)
