@@ -1394,6 +1394,7 @@ int run_layer_bwd(const float* G, const float* W, const void* saved, const hdqt_
                                          geo->kw))
             return HDQT_EINVAL_GEOMETRY;
         g_dx.mask_src = mask_src;
+        g_dx.padded = L.lines.codes(N) != N;
     } else if (geo) {
         return HDQT_EINVAL_NULL;
     }

@@ -146,6 +146,7 @@ struct GemmArgs {
     const float* mask_src;  // null, or a tensor of the fp32 output's shape: the output is written
                             // where mask_src > 0 and +0 elsewhere (the rectifier's backward pass
                             // behind an input gradient); the integer outputs are not masked
+    bool padded;            // D is an odd contraction with zeros behind it (asked for masked products only)
     int32_t* acc_out;       // [RA, RB] or null
     int partial16;          // the slices hold 16-bit integers (a part's totals fit: parts of few tiles)
     int32_t* partial;       // [splits, RA, RB] when splits > 1: one slice per part of the contraction;

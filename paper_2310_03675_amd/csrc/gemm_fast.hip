@@ -1282,11 +1282,15 @@ bool gemm_fast_eligible(const GemmArgs& g)
 // HDQT_LAUNCH_I4 has masked instances of.  A split contraction is masked by the pass that adds its
 // slices, everything else by a pass of its own.  (In the epilogue of the FLEX instances, element by
 // element, the mask costs more than that pass: 39040 x 1024 x 128 with a byte per code 218 / 141 us,
-// 34688 x 1152 x 22 207 / 118, 3456 x 1152 x 129 28.7 / 27.1.)
+// 34688 x 1152 x 22 207 / 118, 3456 x 1152 x 129 28.7 / 27.1.  So it does, by up to 36 us of a backward call, for the odd
+// contractions that padding brought from those to gemm_i4_kernel, as long as the pass finds the output in the memory-side cache:
+// 24059 x 1035 x 79 124 / 114, 198243 x 67 x 103 171 / 159, 25344 x 2298 x 1719, 233 MB, 678 / 668; beyond it does not: 17944 x
+// 3659 x 219, 263 MB, 370 / 414, 174 MB streamed 563 / 618.)
 bool gemm_fast_masks(const GemmArgs& g)
 {
     if (!g.mask_src || !g.out || !gemm_fast_eligible(g)) return false;
     if (g.splits > 1 || g.out_bf16 || g.bA > 4 || g.s == 16 || g.D % 8 != 0) return false;
+    if (g.padded && !g.stream_out && 4 * g.RA * g.RB <= ((int64_t)224 << 20) && !gemm_packed_eligible(g)) return false;
     return !sat16_path(g);
 }
 

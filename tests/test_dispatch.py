@@ -99,3 +99,12 @@ def test_codes_lie_without_padding_where_there_is_no_room(M, K, N):
              for b, acc, s in ((4, 8, 32), (4, 8, 1000), (8, 16, 32))]
     for call, (rc, kernels) in zip(calls, dispatch(calls)):
         assert rc == 0, (call, kernels)
+
+
+# Masks behind padded contractions: in the epilogue of the kernel that brings lines to LDS, by a pass where gemm_i4_kernel
+# multiplies and the output stays in the memory-side cache
+@pytest.mark.parametrize("M,K,N,s,by_pass", [(24059, 1035, 79, 32, False), (24059, 1035, 79, 256, True), (198243, 67, 103, 128, True),
+                                             (25344, 2298, 1719, 128, True), (25344, 2400, 1719, 128, False), (24059, 1035, 80, 256, False)])
+def test_masks_behind_padded_contractions(M, K, N, s, by_pass):
+    (rc, kernels), = dispatch([("layer_bwd", M, K, N, 4, 8, s, 1)])
+    assert rc == 0 and ("relu_mask_kernel" in kernels) == by_pass, kernels
