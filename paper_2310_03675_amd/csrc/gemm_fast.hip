@@ -8,8 +8,11 @@
 //   with zeros on its way to LDS, and rows that are no whole dwords (D no multiple of 8 packed
 //   codes or 4 bytes) are shifted into place there (the FLEX instances).
 //
-// Lines of whole 16-byte pieces whose tiles are whole ones go to gemm_bytes.hip and, from a size on,
-// to gemm_packed.hip, which bring them to LDS without registers.
+// fp32 and int32 outputs, unsplit or in parts of whole stages of 128 codes, go to kernels that bring lines to LDS without
+// registers where these have the tiles: bytes in lines of whole 16-byte pieces to gemm_bytes.hip (whole 128s, or one tile), packed
+// codes in lines of whole dwords to gemm_packed.hip (8-bit accumulators over 32 or 64 codes, or tiles that cannot saturate and are
+// whole 32s).  Of the latter, tiles that are asked whether they can saturate stay here up to 512 workgroups, and wherever their
+// lines end inside 32 codes; so do masks behind such lines.
 //
 // What differs from the generic kernel:
 //   * v_mfma_i32_32x32x32_i8: one MFMA consumes 32 contraction positions.
@@ -1319,8 +1322,7 @@ static bool narrow_tiles(const GemmArgs& g)
 // 128 x 64 tile has no such instance either (half the clamps per wave to save, the same test
 // to pay: 4 % slower on the 262144 x 576 x 64 layer).
 // Where the test holds nearly everywhere (products with a rectifier's output: 65536 x 128 x 1152 20.0 us) this beats
-// lines_gemm_i4_kernel, which clamps every tile (24.7); where it fails it does not (24.3 / 24.9, 4096 cubed 136 / 125), which
-// only the codes tell.
+// lines_gemm_i4_kernel, which clamps every tile (24.7); where it fails they are level (24.3 / 24.9), which only the codes tell.
 bool gemm_fast_tests_tiles(const GemmArgs& g)
 {
     if (g.RB <= 64 || g.out_bf16 || g.bA > 4 || g.bB > 4 || g.mask_src || flexible(g)) return false;

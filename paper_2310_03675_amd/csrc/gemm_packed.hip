@@ -9,8 +9,8 @@
 // waves, codes opened on their way to LDS, a workgroup walking along its strip of the output) / this one, us: 65536 x 1152 x 128
 // 66.6 / 56.6 (302 MB of stores: 5.3 TB/s), 8192 x 4096 x 128 38.5 / 26.7, 40000 x 425 x 256 28.1 / 17.3, 262144 x 64 x 576 34.4 / 30.6,
 // 2048 x 4608 x 512 20.4 / 17.7, 320 x 128 x 32768 in parts 18.6 / 15.7; tiles that cannot saturate 68160 x 576 x 672 70 / 41.  What
-// bounds the long contractions is the clamp, one vector instruction per sum and half of it on the matrix pipe: 4096 cubed
-// 136 / 125.
+// bounds the long contractions is the clamp, one vector instruction per sum and half of it on the matrix pipe: 4096 cubed of
+// codes that fill their range 125.5 / 128.5.
 #include "gemm_lines.hpp"
 
 #include <type_traits>
@@ -369,8 +369,10 @@ static bool narrow_tiles(const GemmArgs& g) { return g.RB <= 64 || wide_workgrou
 // 160 codes), a mask behind lines that end inside 32 codes, and, of the products whose tiles are asked whether they can saturate,
 // those whose lines end inside 32 codes (a line's last piece brings codes of the next line, and the testing loop has no place to
 // clear them before they are squared) and those of up to 512 workgroups: eight waves each do better there than four (65536 x
-// 128 x 1152, test passed 19.6 / 20.5, failed 24.4 / 26.3; with clamps and tiles of 128 x 64 24.0 and 24.2), not beyond (131072 x
-// 128 x 576 passed 26.9 / 25.0, 4096 cubed failed 145 / 128, passed 86.5 / 85.3).  Of 331 drawn products (3- and 4-bit codes, 32 to
+// 128 x 1152, test passed 19.6 / 20.5, failed 24.4 / 26.3; with clamps and tiles of 128 x 64 24.0 and 24.2), not beyond: of 60 drawn
+// products this kernel takes 0.83 of the time in the median where the test passes and 0.96 to 0.98 where it does not, 1.07 at the worst
+// (131072 x 128 x 576 passed 26.9 / 25.0, 2496 x 5179 x 6016 178 / 190 on codes with a deviation of 1.5, 4096 cubed 125.5 / 132 on
+// those, 125.5 / 128.5 on uniform ones and 86 / 85 passed).  Of 331 drawn products (3- and 4-bit codes, 32 to
 // 168000 rows and columns, contractions of 8 to 16384) the 170 that come here are faster by 27 to 38 % in the median; the one
 // class that is not is a narrow output's very long contraction in parts (576 x 64 x 262144 32.0 / 32.9, x 131072 21.7 / 21.4).
 bool gemm_packed_eligible(const GemmArgs& g)
