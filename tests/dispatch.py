@@ -122,13 +122,14 @@ int main()
 }
 """
 
-_EXE = None
+_EXE = _FOLDER = None
 
 
 def _program() -> str:
-    global _EXE
+    global _EXE, _FOLDER
     if _EXE is None:
-        folder = tempfile.mkdtemp(prefix="dispatch")
+        _FOLDER = tempfile.TemporaryDirectory(prefix="dispatch")      # (goes with the process)
+        folder = _FOLDER.name
         src, exe = os.path.join(folder, "dispatch.hip"), os.path.join(folder, "dispatch")
         with open(src, "w") as f:
             f.write(PROGRAM.replace("../../include", os.path.join(ROOT, "include")))
